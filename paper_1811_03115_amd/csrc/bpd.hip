@@ -10,6 +10,8 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <algorithm>
+#include <initializer_list>
 #include <map>
 #include <string>
 #include <vector>
@@ -54,7 +56,16 @@ struct bpd_ctx {
   int x_ready_k = 0;                   // > 0: the last step's accept kernel already embedded the next block of that many rows
   bool weights_exceed_llc = false;     // decoder-side weights read per step > 192 MB (the Infinity Cache holds 256 MB)
   const int* cur_imposed = nullptr; int cur_imposed_stride = 0, cur_imposed_step = 0;   // of the step being run
-  int* pinned = nullptr;       // small pinned host scratch
+  // pinned host memory, read and written by kernels directly: the words that say what has happened, the arguments of
+  // bpd_encode / a host schedule, and results on their way to the caller
+  unsigned long long* report = nullptr;       // [2][max_batch] bpd_decode: tokens still to come, tagged with the step; steps
+                                              // take turns (the next one may report before the host has looked)
+  unsigned long long* done = nullptr;         // [0]: last finished fetch, [1]: last encode whose arguments have been read
+  int *stage_in = nullptr, *stage_sched = nullptr, *stage_out = nullptr;
+  size_t n_stage_out = 0;
+  unsigned long long fetch_tag = 0, encode_tag = 0;
+  unsigned report_tag = 0;
+  std::vector<int> remaining;                  // tokens still to come per sequence as far as the host knows (-1: it does not)
   int prof_phase = 0;
   std::vector<hipEvent_t> prof_ev;
   size_t prof_used = 0;
@@ -888,15 +899,6 @@ int encoder(bpd_ctx* ctx) {
   return BPD_OK;
 }
 
-__global__ void sanitize_kernel(int* src_len, int* max_len, int* src_ids, int B, int S, int max_out, int V) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < B) {
-    int s = src_len[i]; src_len[i] = s < 1 ? 1 : (s > S ? S : s);
-    int m = max_len[i]; max_len[i] = m < 1 ? 1 : (m > max_out ? max_out : m);
-  }
-  if (i < B * S) { int t = src_ids[i]; src_ids[i] = t < 0 ? 0 : (t >= V ? V - 1 : t); }
-}
-
 bool is_host_ptr(const void* p) {
   hipPointerAttribute_t a;
   if (hipPointerGetAttributes(&a, p) != hipSuccess) { (void)hipGetLastError(); return true; }
@@ -911,6 +913,53 @@ bool is_host_ptr_cached(bpd_ctx* ctx, const void* p) {
   ctx->kind_ptr[ctx->kind_next] = p; ctx->kind_host[ctx->kind_next] = h;
   ctx->kind_next = (ctx->kind_next + 1) & 3;
   return h;
+}
+
+unsigned long long* report_of(bpd_ctx* ctx, unsigned tag) { return ctx->report + (size_t)(tag & 1) * ctx->cfg.max_batch; }
+
+// Waits until a kernel of the context's stream has stored `tag` in a word of pinned memory (shifted up by `shift`).  Ends also when the stream has nothing left to run: then the word is there, or the launch failed.
+int wait_word(bpd_ctx* ctx, const unsigned long long* word, unsigned long long tag, int shift = 0) {
+  auto there = [&] { return (__atomic_load_n(word, __ATOMIC_ACQUIRE) >> shift) == tag; };
+  for (unsigned spin = 1; !there(); ++spin) {
+    __builtin_ia32_pause();
+    if (spin % 8192) continue;
+    const hipError_t e = hipStreamQuery(ctx->stream);
+    if (e == hipErrorNotReady) continue;
+    if (e != hipSuccess) return fail(ctx, BPD_E_HIP, std::string("waiting for the stream: ") + hipGetErrorString(e));
+    if (!there()) return fail(ctx, BPD_E_HIP, "waiting for the stream: it ended without the awaited result");
+  }
+  return BPD_OK;
+}
+
+// Copies up to four arrays of ints to the caller (host or device memory; null: not wanted) and waits for them.
+struct Fetch { const int* src; size_t n; void* dst; };
+constexpr size_t FETCH_KERNEL_MAX = 32768;     // ints: one workgroup's copy, about 10 us; more goes through copies
+int fetch(bpd_ctx* ctx, std::initializer_list<Fetch> list) {
+  FetchP f{};
+  size_t total = 0;
+  int na = 0;
+  bool direct = true;
+  for (const Fetch& a : list) {
+    if (!a.dst || !a.n) continue;
+    f.src[na] = a.src; f.n[na] = (int)a.n; ++na;
+    total += a.n;
+    direct = direct && is_host_ptr(a.dst);
+  }
+  if (direct && total && total <= FETCH_KERNEL_MAX && total <= ctx->n_stage_out) {
+    f.dst = ctx->stage_out; f.done = &ctx->done[0]; f.tag = ++ctx->fetch_tag;
+    hipLaunchKernelGGL(fetch_kernel, dim3(1), dim3(1024), 0, ctx->stream, f);
+    LAUNCHCHK();
+    const int rc = wait_word(ctx, &ctx->done[0], f.tag);
+    if (rc) return rc;
+    const int* from = ctx->stage_out;
+    for (const Fetch& a : list)
+      if (a.dst && a.n) { memcpy(a.dst, from, a.n * 4); from += a.n; }
+    return BPD_OK;
+  }
+  for (const Fetch& a : list)
+    if (a.dst && a.n) HIPCHK(hipMemcpyAsync(a.dst, a.src, a.n * 4, hipMemcpyDefault, ctx->stream));
+  HIPCHK(hipStreamSynchronize(ctx->stream));
+  return BPD_OK;
 }
 
 }  // namespace
@@ -991,10 +1040,22 @@ int bpd_create(const bpd_config* cfg, void* workspace, size_t workspace_bytes, v
     (void)hipGetLastError();
   }
   (void)hipMemsetAsync(ctx->lay.zeros, 0, ctx->lay.n_zeros * 4, ctx->stream);
+  (void)hipMemsetAsync(ctx->lay.step_counter, 0, 4, ctx->stream);
   (void)hipMemsetAsync(ctx->lay.stats_ln, 0, 64 * 16 * 2 * 4, ctx->stream);
-  if (hipHostMalloc((void**)&ctx->pinned, 64 * sizeof(int), hipHostMallocDefault) != hipSuccess) {
-    delete ctx;
-    return BPD_E_HIP;
+  {
+    const size_t B = cfg->max_batch, k = cfg->k_max, S = cfg->max_src_len, T = cfg->max_out_len;
+    const size_t n_in = B * S + 2 * B, n_sched = B * T;
+    ctx->n_stage_out = std::min(FETCH_KERNEL_MAX, std::max(B * T + B + 64, B * k * (k + 1) + 2 * B));
+    const size_t ints = 4 * B + 16 + n_in + n_sched + ctx->n_stage_out;
+    if (hipHostMalloc((void**)&ctx->report, ints * sizeof(int), hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      delete ctx;
+      return BPD_E_HIP;
+    }
+    ctx->done = ctx->report + 2 * B;
+    ctx->stage_in = (int*)(ctx->done + 8); ctx->stage_sched = ctx->stage_in + n_in; ctx->stage_out = ctx->stage_sched + n_sched;
+    memset(ctx->report, 0, (2 * B + 8) * 8);
+    ctx->remaining.assign(B, -1);
   }
   *out = ctx;
   return BPD_OK;
@@ -1012,7 +1073,7 @@ int bpd_destroy(bpd_ctx* ctx) {
     }
   }
   for (auto e : ctx->prof_ev) (void)hipEventDestroy(e);
-  if (ctx->pinned) (void)hipHostFree(ctx->pinned);
+  if (ctx->report) (void)hipHostFree(ctx->report);
   delete ctx;
   return BPD_OK;
 }
@@ -1099,39 +1160,40 @@ int bpd_encode(bpd_ctx* ctx, const int32_t* src_ids, const int32_t* src_len, con
   if (B > c.max_batch || S > c.max_src_len) return fail(ctx, BPD_E_CAPACITY, "bpd_encode: batch or source length over the configured maximum");
   for (auto& kv : ctx->table)
     if (!kv.second.loaded) return fail(ctx, BPD_E_STATE, "bpd_encode: tensor not loaded: " + kv.first);
-  // host-side validation when the caller's arrays are host memory
-  if (is_host_ptr(src_len)) {
+  // host arrays are validated here and pass through the pinned staging area (free again once the encode before this one
+  // has read its own); the kernel that takes them clamps, so device arrays are safe as well
+  int *h_ids = ctx->stage_in, *h_len = h_ids + (size_t)c.max_batch * c.max_src_len, *h_max = h_len + c.max_batch;
+  const bool host_ids = is_host_ptr(src_ids), host_len = is_host_ptr(src_len), host_max = max_len && is_host_ptr(max_len);
+  if (host_len) {
     for (int b = 0; b < B; ++b)
       if (src_len[b] < 1 || src_len[b] > S) return fail(ctx, BPD_E_ARG, "bpd_encode: src_len out of range");
   }
-  if (is_host_ptr(src_ids)) {
+  if (host_ids) {
     for (long i = 0; i < (long)B * S; ++i)
       if (src_ids[i] < 0 || src_ids[i] >= c.vocab) return fail(ctx, BPD_E_ARG, "bpd_encode: source id out of range");
   }
-  if (max_len && is_host_ptr(max_len)) {
+  if (host_max) {
     for (int b = 0; b < B; ++b)
       if (max_len[b] < 1 || max_len[b] > c.max_out_len) return fail(ctx, BPD_E_ARG, "bpd_encode: max_len out of range");
   }
   Layout& L = ctx->lay;
   ctx->B = B; ctx->S = S; ctx->encoded = false; ctx->x_ready_k = 0;
   refresh_folded_weights(ctx);                    // (every tensor is loaded: checked above)
-  HIPCHK(hipMemcpyAsync(L.src_ids, src_ids, (size_t)B * S * 4, hipMemcpyDefault, ctx->stream));
-  HIPCHK(hipMemcpyAsync(L.src_len, src_len, (size_t)B * 4, hipMemcpyDefault, ctx->stream));
-  if (max_len) HIPCHK(hipMemcpyAsync(L.max_len, max_len, (size_t)B * 4, hipMemcpyDefault, ctx->stream));
-  else fill_i32(ctx, L.max_len, B, c.max_out_len);
-  hipLaunchKernelGGL(sanitize_kernel, dim3((B * S + 255) / 256), dim3(256), 0, ctx->stream, L.src_len, L.max_len, L.src_ids, B, S,
-                     c.max_out_len, c.vocab);
+  { const int rc = wait_word(ctx, &ctx->done[1], ctx->encode_tag); if (rc) return rc; }
+  if (host_ids) memcpy(h_ids, src_ids, (size_t)B * S * 4);
+  if (host_len) memcpy(h_len, src_len, (size_t)B * 4);
+  if (host_max) memcpy(h_max, max_len, (size_t)B * 4);
+  for (int b = 0; b < B; ++b) ctx->remaining[b] = !max_len ? c.max_out_len : (host_max ? max_len[b] : -1);
+  {
+    const size_t most = std::max((size_t)B * S, (size_t)B * std::max(c.max_out_len, c.k_max * c.k_max));
+    hipLaunchKernelGGL(encode_init_kernel, dim3((unsigned)std::min<size_t>(256, (most + 255) / 256)), dim3(256), 0, ctx->stream, state_params(ctx),
+                       host_ids ? h_ids : src_ids, host_len ? h_len : src_len, host_max ? h_max : max_len, L.src_ids, L.src_len, B, S, c.vocab, c.pad_id,
+                       (unsigned*)L.step_counter, &ctx->done[1], ctx->encode_tag + 1);
+    LAUNCHCHK();
+    ++ctx->encode_tag;
+  }
   int rc = encoder(ctx);
   if (rc) return rc;
-  // empty hypotheses
-  fill_i32(ctx, L.L, B, 0);
-  fill_i32(ctx, L.j, B, 0);
-  fill_i32(ctx, L.finished, B, 0);
-  fill_i32(ctx, L.accepted, B, 0);
-  fill_i32(ctx, L.out_ids, (long)B * c.max_out_len, c.pad_id);
-  fill_i32(ctx, (int*)L.stats, 64, 0);
-  fill_i32(ctx, L.P, (long)B * c.k_max, 0);
-  fill_i32(ctx, L.A, (long)B * c.k_max * c.k_max, 0);
   // first invocation: position 0 only, all heads -> first proposals
   rc = forward(ctx, 1, c.k_max, 1, nullptr);
   if (rc) return rc;
@@ -1142,8 +1204,10 @@ int bpd_encode(bpd_ctx* ctx, const int32_t* src_ids, const int32_t* src_len, con
   return BPD_OK;
 }
 
-static int step_impl(bpd_ctx* ctx, int k, const int* imposed_dev, int imposed_stride, int imposed_step, int* accepted_dev) {
+// report_tag: bpd_decode's tag of this step (0: the step reports nothing to the host)
+static int step_impl(bpd_ctx* ctx, int k, const int* imposed_dev, int imposed_stride, int imposed_step, int* accepted_dev, unsigned report_tag = 0) {
   Layout& L = ctx->lay;
+  if (!report_tag) std::fill(ctx->remaining.begin(), ctx->remaining.end(), -1);      // the host does not follow this step
   PhaseTimer whole(ctx, BPD_PHASE_STEP);
   ctx->cur_imposed = imposed_dev; ctx->cur_imposed_stride = imposed_stride; ctx->cur_imposed_step = imposed_step;
   int rc = forward(ctx, k, k, 0, nullptr);
@@ -1152,6 +1216,7 @@ static int step_impl(bpd_ctx* ctx, int k, const int* imposed_dev, int imposed_st
     PhaseTimer t(ctx, BPD_PHASE_ACCEPT);
     StateP s = state_params(ctx);
     s.imposed = imposed_dev; s.imposed_stride = imposed_stride;
+    if (report_tag) { s.report = report_of(ctx, report_tag); s.report_tag = report_tag; }
     const bpd_config& c = ctx->cfg;
     if (embed_in_accept(ctx)) {
       // the accept kernel also embeds the next block (same k assumed; checked by forward); its LayerNorm statistics go
@@ -1280,27 +1345,43 @@ int bpd_set_local_attention(bpd_ctx* ctx, int query_block, int memory_len) {
   return BPD_OK;
 }
 
-int bpd_get_stats(bpd_ctx* ctx, bpd_stats* st) {
-  if (!ctx || !st) return BPD_E_ARG;
-  long long raw[32];
-  HIPCHK(hipMemcpyAsync(raw, ctx->lay.stats, sizeof(raw), hipMemcpyDeviceToHost, ctx->stream));
-  HIPCHK(hipStreamSynchronize(ctx->stream));
+static void stats_of(const bpd_ctx* ctx, const long long* raw, bpd_stats* st) {
   st->steps = raw[20]; st->invocations = ctx->encoded ? raw[20] + 1 : 0;
   st->seq_steps = raw[0]; st->accepted_total = raw[1]; st->finished = (int32_t)raw[2];
   for (int i = 0; i < 17; ++i) st->hist[i] = raw[3 + i];
+}
+
+int bpd_get_stats(bpd_ctx* ctx, bpd_stats* st) {
+  if (!ctx || !st) return BPD_E_ARG;
+  long long raw[32];
+  const int rc = fetch(ctx, {{(const int*)ctx->lay.stats, 64, raw}});
+  if (rc) return rc;
+  stats_of(ctx, raw, st);
   return BPD_OK;
+}
+
+static int output_and_stats(bpd_ctx* ctx, int32_t* out_ids, int32_t* out_len, bpd_stats* st) {
+  Layout& L = ctx->lay;
+  long long raw[32];
+  const int rc = fetch(ctx, {{L.out_ids, (size_t)ctx->B * ctx->cfg.max_out_len, out_ids}, {L.j, (size_t)ctx->B, out_len},
+                             {(const int*)L.stats, 64, st ? raw : nullptr}});
+  if (rc) return rc;
+  if (st) stats_of(ctx, raw, st);
+  return stack_check(ctx);
 }
 
 int bpd_get_output(bpd_ctx* ctx, int32_t* out_ids, int32_t* out_len) {
   if (!ctx) return BPD_E_ARG;
   if (!ctx->encoded) return fail(ctx, BPD_E_STATE, "bpd_get_output: nothing decoded");
-  Layout& L = ctx->lay;
-  if (out_ids) HIPCHK(hipMemcpyAsync(out_ids, L.out_ids, (size_t)ctx->B * ctx->cfg.max_out_len * 4, hipMemcpyDefault, ctx->stream));
-  if (out_len) HIPCHK(hipMemcpyAsync(out_len, L.j, (size_t)ctx->B * 4, hipMemcpyDefault, ctx->stream));
-  HIPCHK(hipStreamSynchronize(ctx->stream));
-  return stack_check(ctx);
+  return output_and_stats(ctx, out_ids, out_len, nullptr);
 }
 
+// The host follows the decode through words that the accept kernel of every step stores in pinned memory (StateP::report),
+// and stays one step ahead of them: step s is enqueued while step s - 1 runs, then the host waits for the report of s - 1.
+// Enqueueing takes less than a step, so the stream never runs dry, and at most one step is enqueued in vain: where an
+// end-of-sequence token, not the length budget, ends the last sequence.  If the budgets say that step s - 1 may be the
+// last one, its report is awaited before step s is enqueued.  (Stopping the stream every four steps to ask cost 25 us per
+// step of the base model at batch 1 and up to three steps in vain at the end.)
 int bpd_decode(bpd_ctx* ctx, int k, const int32_t* schedule, int max_steps, int32_t* out_ids, int32_t* out_len, bpd_stats* stats) {
   if (!ctx) return BPD_E_ARG;
   if (!ctx->encoded) return fail(ctx, BPD_E_STATE, "bpd_decode: call bpd_encode first");
@@ -1308,26 +1389,59 @@ int bpd_decode(bpd_ctx* ctx, int k, const int32_t* schedule, int max_steps, int3
   Layout& L = ctx->lay;
   const int B = ctx->B;
   const int* imp = nullptr;
+  const int* host_sched = nullptr;
   if (schedule) {
     // a live sequence takes at least one token per step, so max_out_len rows always suffice
     const int rows = max_steps < ctx->cfg.max_out_len ? max_steps : ctx->cfg.max_out_len;
-    if (rows > 0) HIPCHK(hipMemcpyAsync(L.sched, schedule, (size_t)rows * B * 4, hipMemcpyDefault, ctx->stream));
     if (max_steps > rows) max_steps = rows;
     imp = L.sched;
-  }
-  for (int s = 0; s < max_steps; ++s) {
-    int rc = step_impl(ctx, k, imp, B, s, nullptr);
-    if (rc) return rc;
-    if ((s & 3) == 3 || s + 1 == max_steps) {
-      HIPCHK(hipMemcpyAsync(ctx->pinned, (int*)(L.stats + 2), 4, hipMemcpyDeviceToHost, ctx->stream));
-      HIPCHK(hipStreamSynchronize(ctx->stream));
-      if (ctx->pinned[0] >= B) break;
+    if (rows > 0 && is_host_ptr(schedule)) {     // (the decode before this one has ended: its copy has been made)
+      memcpy(ctx->stage_sched, schedule, (size_t)rows * B * 4);
+      hipLaunchKernelGGL(copy_i32_kernel, dim3((unsigned)(((size_t)rows * B + 255) / 256)), dim3(256), 0, ctx->stream, ctx->stage_sched, L.sched, (long)rows * B);
+      LAUNCHCHK();
+      host_sched = ctx->stage_sched;
+    } else if (rows > 0) {
+      HIPCHK(hipMemcpyAsync(L.sched, schedule, (size_t)rows * B * 4, hipMemcpyDefault, ctx->stream));
     }
   }
-  int rc = bpd_get_output(ctx, out_ids, out_len);
-  if (rc) return rc;
-  if (stats) return bpd_get_stats(ctx, stats);
-  return BPD_OK;
+  auto& rem = ctx->remaining;
+  // may step s end the last sequence by its budget, as far as the reports before s tell?
+  auto may_be_last = [&](int s) {
+    for (int b = 0; b < B; ++b) {
+      if (rem[b] < 0) return false;              // not known: run ahead, the report will tell
+      int most = k;
+      if (host_sched) { const int a = host_sched[(size_t)s * B + b]; most = a < 1 ? 1 : (a > k ? k : a); }
+      if (rem[b] > most) return false;
+    }
+    return true;
+  };
+  bool ended = false;
+  auto await = [&](unsigned tag) {               // the report of the step that was given this tag
+    ended = true;
+    const unsigned long long* words = report_of(ctx, tag);
+    for (int b = 0; b < B; ++b) {
+      const int rc = wait_word(ctx, &words[b], tag, 32);
+      if (rc) return rc;
+      rem[b] = (int)(unsigned)words[b];
+      ended = ended && rem[b] == 0;
+    }
+    return (int)BPD_OK;
+  };
+  for (int s = 0; s < max_steps && !ended; ++s) {
+    const unsigned before = ctx->report_tag;     // of step s - 1
+    bool know = false;
+    if (s > 0 && may_be_last(s - 1)) {
+      const int rc = await(before);
+      if (rc) return rc;
+      if (ended) break;
+      know = true;
+    }
+    ctx->report_tag = ctx->report_tag == 0xFFFFFFFFu ? 2 : ctx->report_tag + 1;       // (0 means "no report"; turns kept)
+    int rc = step_impl(ctx, k, imp, B, s, nullptr, ctx->report_tag);
+    if (rc == BPD_OK && s > 0 && !know) rc = await(before);
+    if (rc) return rc;
+  }
+  return output_and_stats(ctx, out_ids, out_len, stats);
 }
 
 int bpd_get_state(bpd_ctx* ctx, int32_t* P, int32_t* A, int32_t* j, int32_t* finished) {
@@ -1335,11 +1449,8 @@ int bpd_get_state(bpd_ctx* ctx, int32_t* P, int32_t* A, int32_t* j, int32_t* fin
   if (!ctx->encoded) return fail(ctx, BPD_E_STATE, "bpd_get_state: call bpd_encode first");
   Layout& L = ctx->lay;
   const size_t B = ctx->B, k = ctx->cfg.k_max;
-  if (P) HIPCHK(hipMemcpyAsync(P, L.P, B * k * 4, hipMemcpyDefault, ctx->stream));
-  if (A) HIPCHK(hipMemcpyAsync(A, L.A, B * k * k * 4, hipMemcpyDefault, ctx->stream));
-  if (j) HIPCHK(hipMemcpyAsync(j, L.j, B * 4, hipMemcpyDefault, ctx->stream));
-  if (finished) HIPCHK(hipMemcpyAsync(finished, L.finished, B * 4, hipMemcpyDefault, ctx->stream));
-  HIPCHK(hipStreamSynchronize(ctx->stream));
+  const int rc = fetch(ctx, {{L.P, B * k, P}, {L.A, B * k * k, A}, {L.j, B, j}, {L.finished, B, finished}});
+  if (rc) return rc;
   return stack_check(ctx);
 }
 
