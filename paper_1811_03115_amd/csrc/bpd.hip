@@ -53,7 +53,13 @@ struct bpd_ctx {
   int stack_xcc = 0, stack_nx = 0, stack_workers = 0;
   unsigned stack_epoch = 0;
   bool stack_off = false;
-  int x_ready_k = 0;                   // > 0: the last step's accept kernel already embedded the next block of that many rows
+  int x_ready_k = 0, x_ready_slots = 0;  // x_ready_k > 0: the last step's accept kernel already embedded the next block: that many rows
+                                         // for each of so many slots
+  // rows of the invocation being run: slots of sequences (StateP::slot_seq).  seq: their sequences (null: slot = sequence);
+  // live: their number on the device where the host only knows a bound, Bs (null: exactly Bs)
+  int Bs = 0; const int* seq = nullptr; const int* live = nullptr;
+  int live1 = -1, live2 = -1;            // sequences that had not ended after the last step and after the one before (-1: not known)
+  int budget_min = 0;                    // smallest length budget of the batch as far as the host knows
   bool weights_exceed_llc = false;     // decoder-side weights read per step > 192 MB (the Infinity Cache holds 256 MB)
   const int* cur_imposed = nullptr; int cur_imposed_stride = 0, cur_imposed_step = 0;   // of the step being run
   // pinned host memory, read and written by kernels directly: the words that say what has happened, the arguments of
@@ -246,6 +252,20 @@ void launch_stream(const bpd_ctx* ctx, const GemmP& p, const Epi& e, int groups)
 bool embed_in_accept(const bpd_ctx* ctx) {
   return ctx->cfg.dtype == BPD_BF16 && ctx->cfg.d_model <= 1024;
 }
+// Rows of ended sequences are left out of the steps of a batch: the accept kernel that also embeds the next block deals the
+// slots (with one sequence there is nothing to pack).
+bool slots_used(const bpd_ctx* ctx) { return embed_in_accept(ctx) && ctx->B > 1; }
+// Which slots the next invocation of the block runs on.  exact: their number, as a decode knows it (-1: not known, all of
+// the batch with the number on the device, unless no sequence can have ended yet).
+void use_slots(bpd_ctx* ctx, int exact) {
+  ctx->Bs = ctx->B; ctx->seq = nullptr; ctx->live = nullptr;
+  if (!slots_used(ctx) || exact == ctx->B) return;
+  if (exact < 0 && ctx->cfg.eos_id < 0 && (ctx->steps - 1) * ctx->cfg.k_max < ctx->budget_min) return;
+  ctx->seq = ctx->lay.slot_seq;
+  if (exact > 0) ctx->Bs = exact; else ctx->live = ctx->lay.n_live;
+}
+// ... and how a kernel of M rows (of all slots launched) is told to stop short
+LiveP live_rows(const bpd_ctx* ctx, int M) { return ctx->live ? LiveP{ctx->live, M / ctx->Bs} : LiveP{nullptr, 0}; }
 // LayerNorm statistics ride along with the residual stream when the whole block is one MFMA row tile and every GEMM
 // that updates the stream is one the skinny kernel takes (it is the one that writes them: K = d_ff must fit it)
 bool stats_path(const bpd_ctx* ctx, int M) {
@@ -254,7 +274,7 @@ bool stats_path(const bpd_ctx* ctx, int M) {
 
 // ---- ldsx path: many rows ---------------------------------------------------------------
 template <int MT, int NT, int KC, bool ARGMAX, bool XLN = false, bool STATS = false, bool ROWAFF = false>
-void launch_ldsx(const GemmP& p, const Epi& e, unsigned long long* keys, float* logits, int groups, hipStream_t s,
+void launch_ldsx(const GemmP& p, const Epi& e, unsigned long long* keys, float* logits, int groups, hipStream_t s, const LiveP& live,
                  const LnP& ln = LnP{}) {
   const int ntiles = p.N / 16;
   dim3 grid((ntiles + 4 * NT - 1) / (4 * NT), (p.M + 16 * MT - 1) / (16 * MT), groups);
@@ -266,7 +286,7 @@ void launch_ldsx(const GemmP& p, const Epi& e, unsigned long long* keys, float* 
   }
   GemmP q = p;
   q.lx = ldsx_map_of(p.K, KC, p.ksplit, grid.x, grid.y, grid.z);            // (grid.x * grid.y * grid.y * 4 < 2^32 by far: at most a few thousand blocks each way)
-  hipLaunchKernelGGL((gemm_ldsx_kernel<MT, NT, KC, ARGMAX, XLN, STATS, ROWAFF>), grid, dim3(256), lds, s, q, e, keys, logits, ln);
+  hipLaunchKernelGGL((gemm_ldsx_kernel<MT, NT, KC, ARGMAX, XLN, STATS, ROWAFF>), grid, dim3(256), lds, s, q, e, keys, logits, ln, live);
 }
 
 // Tile of the LDS-staged GEMM: 16*mt rows x 64*nt columns per workgroup, K walked in chunks of
@@ -287,7 +307,7 @@ void prefetch_epilogue(Epi& e, const GemmP& p, int mt, int nt, const float* zero
 
 template <bool ARGMAX>
 bool dispatch_ldsx(const GemmP& p, const Epi& e_in, unsigned long long* keys, float* logits, int groups, hipStream_t s,
-                   const float* zeros = nullptr) {
+                   const LiveP& live, const float* zeros = nullptr) {
   Epi e = e_in;
   int mt, nt;
   const int kslice = p.ksplit > 1 ? p.K / p.ksplit : p.K;
@@ -298,14 +318,14 @@ bool dispatch_ldsx(const GemmP& p, const Epi& e_in, unsigned long long* keys, fl
   if constexpr (!ARGMAX) prefetch_epilogue(e, p, mt, nt, zeros);
   if constexpr (!ARGMAX) {
     if (stats) {
-#define BPD_CASE(MT_, NT_, KC_) if (mt == MT_ && nt == NT_) { launch_ldsx<MT_, NT_, KC_, false, false, true>(p, e, keys, logits, groups, s); return true; }
+#define BPD_CASE(MT_, NT_, KC_) if (mt == MT_ && nt == NT_) { launch_ldsx<MT_, NT_, KC_, false, false, true>(p, e, keys, logits, groups, s, live); return true; }
       BPD_CASE(3, 1, 256) BPD_CASE(2, 1, 256) BPD_CASE(1, 1, 256)
       BPD_CASE(3, 2, 128) BPD_CASE(2, 2, 128) BPD_CASE(1, 2, 128)
       BPD_CASE(3, 4, 64) BPD_CASE(2, 4, 64) BPD_CASE(1, 4, 64)
 #undef BPD_CASE
     }
   }
-#define BPD_CASE(MT_, NT_, KC_) if (mt == MT_ && nt == NT_) { launch_ldsx<MT_, NT_, KC_, ARGMAX>(p, e, keys, logits, groups, s); return false; }
+#define BPD_CASE(MT_, NT_, KC_) if (mt == MT_ && nt == NT_) { launch_ldsx<MT_, NT_, KC_, ARGMAX>(p, e, keys, logits, groups, s, live); return false; }
   BPD_CASE(3, 1, 256) BPD_CASE(2, 1, 256) BPD_CASE(1, 1, 256)
   BPD_CASE(8, 2, 128) BPD_CASE(7, 2, 128) BPD_CASE(5, 2, 128) BPD_CASE(4, 2, 128) BPD_CASE(3, 2, 128) BPD_CASE(2, 2, 128) BPD_CASE(1, 2, 128)
   BPD_CASE(8, 4, 64) BPD_CASE(7, 4, 64) BPD_CASE(5, 4, 64) BPD_CASE(4, 4, 64) BPD_CASE(3, 4, 64) BPD_CASE(2, 4, 64) BPD_CASE(1, 4, 64)
@@ -320,7 +340,7 @@ void dispatch_ldsx_ln(const GemmP& p, const Epi& e_in, const LnP& ln, hipStream_
   int mt, nt;
   pick_tile(p.M, p.N, p.K, 1, mt, nt, LDSX_LN_MT_MAX);
   prefetch_epilogue(e, p, mt, nt, zeros);
-#define BPD_CASE(MT_, NT_, KC_) if (mt == MT_ && nt == NT_) { launch_ldsx<MT_, NT_, KC_, false, true>(p, e, nullptr, nullptr, 1, s, ln); return; }
+#define BPD_CASE(MT_, NT_, KC_) if (mt == MT_ && nt == NT_) { launch_ldsx<MT_, NT_, KC_, false, true>(p, e, nullptr, nullptr, 1, s, LiveP{}, ln); return; }
   BPD_CASE(3, 1, 256) BPD_CASE(2, 1, 256) BPD_CASE(1, 1, 256)
   BPD_CASE(3, 2, 128) BPD_CASE(2, 2, 128) BPD_CASE(1, 2, 128)
   BPD_CASE(3, 4, 64) BPD_CASE(2, 4, 64) BPD_CASE(1, 4, 64)
@@ -332,7 +352,7 @@ void dispatch_ldsx_fold(const GemmP& p, const Epi& e_in, hipStream_t s, const fl
   int mt, nt;
   pick_tile(p.M, p.N, p.K, 1, mt, nt, LDSX_LN_MT_MAX);
   prefetch_epilogue(e, p, mt, nt, zeros);
-#define BPD_CASE(MT_, NT_, KC_) if (mt == MT_ && nt == NT_) { launch_ldsx<MT_, NT_, KC_, false, false, false, true>(p, e, nullptr, nullptr, 1, s); return; }
+#define BPD_CASE(MT_, NT_, KC_) if (mt == MT_ && nt == NT_) { launch_ldsx<MT_, NT_, KC_, false, false, false, true>(p, e, nullptr, nullptr, 1, s, LiveP{}); return; }
   BPD_CASE(3, 1, 256) BPD_CASE(2, 1, 256) BPD_CASE(1, 1, 256)
   BPD_CASE(3, 2, 128) BPD_CASE(2, 2, 128) BPD_CASE(1, 2, 128)
   BPD_CASE(3, 4, 64) BPD_CASE(2, 4, 64) BPD_CASE(1, 4, 64)
@@ -374,12 +394,12 @@ bool gemm(bpd_ctx* ctx, const GemmP& p, const Epi& e_in, int groups = 1) {
         GemmP q = p;
         q.ksplit = ns; q.part = ctx->lay.kpart;
         e.stats_out = nullptr;                     // the slices are raw products: no statistics of the sum yet
-        dispatch_ldsx<false>(q, e, nullptr, nullptr, ns, s, ctx->lay.zeros);
+        dispatch_ldsx<false>(q, e, nullptr, nullptr, ns, s, live_rows(ctx, p.M), ctx->lay.zeros);
         ctx->pend_slices = ns; ctx->pend_bias = e.bias ? e.bias : ctx->lay.zeros; ctx->pend_x = e.Yf;
         return false;
       }
     }
-    return dispatch_ldsx<false>(p, e, nullptr, nullptr, groups, s, ctx->lay.zeros);
+    return dispatch_ldsx<false>(p, e, nullptr, nullptr, groups, s, live_rows(ctx, p.M), ctx->lay.zeros);
   } else {
     e.stats_out = nullptr;
     if (p.M > 64) launch_gemm_bf16<8, 1, 4>(p, e, groups, s);
@@ -451,7 +471,7 @@ void launch_stream_vocab_cfg(const bpd_ctx* ctx, const GemmP& p, unsigned long l
   auto k = stream_vocab_kernel<4, NT, UPT, false>;
   static size_t attr = 0;                       // per instantiation: allow more than 64 KiB of LDS
   if (attr < lds) { (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); attr = lds; }
-  hipLaunchKernelGGL(k, dim3(stream_vocab_gx(ctx, p), (p.M + 63) / 64), dim3(512), lds, ctx->stream, p, keys, logits);
+  hipLaunchKernelGGL(k, dim3(stream_vocab_gx(ctx, p), (p.M + 63) / 64), dim3(512), lds, ctx->stream, p, keys, logits, live_rows(ctx, p.M));
 }
 void launch_stream_vocab(const bpd_ctx* ctx, const GemmP& p, unsigned long long* keys, float* logits) {
   // one column tile at a time.  Two at a time (NT = 2: one LDS read feeds two MFMAs) measured slower, 20.2 vs 18.5 us at
@@ -466,7 +486,7 @@ void vocab_argmax(bpd_ctx* ctx, const GemmP& p, unsigned long long* keys, float*
   LnP noln{};
   if (skinny_ok(ctx, p)) launch_skinny<2, false, true>(ctx, p, none, noln, keys, logits, 1);
   else if (stream_vocab_ok(ctx, p)) launch_stream_vocab(ctx, p, keys, logits);
-  else if (p.K % 64 == 0) dispatch_ldsx<true>(p, none, keys, logits, 1, s);
+  else if (p.K % 64 == 0) dispatch_ldsx<true>(p, none, keys, logits, 1, s, live_rows(ctx, p.M));
   else {
     const int ntiles = p.N / 16;
     dim3 grid(ntiles, (p.M + 127) / 128, 1);
@@ -531,13 +551,13 @@ bool attention_qproj_ok(const bpd_ctx* ctx, int B, int R) {
 }
 
 void attention(bpd_ctx* ctx, const float* Q, const void* Kc, const void* Vc, void* out, int cap,
-               int B, int R, const int* limit, int causal, const QProjP* qproj = nullptr) {
+               int B, int R, const int* limit, int causal, const int* seq, const QProjP* qproj = nullptr) {
   const long kv_seq_stride = (long)cap * ctx->cfg.d_model;
   const bpd_config& c = ctx->cfg;
   const int dh = c.d_model / c.n_heads;
   AttnP p{};
   p.Q = Q; p.Kc = Kc; p.Vc = Vc; p.out = out; p.kv_seq_stride = kv_seq_stride; p.cap = cap; p.d = c.d_model; p.R = R;
-  p.limit = limit; p.causal = causal; p.scale = 1.0f / sqrtf((float)dh);
+  p.limit = limit; p.causal = causal; p.seq = seq; p.scale = 1.0f / sqrtf((float)dh);
   const bool local = causal && ctx->local_q > 0;
   p.local_q = local ? ctx->local_q : 0; p.local_m = local ? ctx->local_m : 0;
   const int tiles = (R + 15) / 16, wgs = c.n_heads * B * tiles;
@@ -552,22 +572,24 @@ void attention(bpd_ctx* ctx, const float* Q, const void* Kc, const void* Vc, voi
       // (a split launch walks a long cache, where nearly all fetched rows are in use: measured slower with the extra round trip)
       // (local attention: where the keys start depends on the length, so it is always read first)
       const bool limf = (nsplit == 1 && wgs >= ATTN_LIMF_MIN_WGS) || local;
+#define BPD_ATTN(...) { if (seq) hipLaunchKernelGGL((attention_mfma_slots_kernel<__VA_ARGS__>), grid, dim3(256), 0, ctx->stream, p, qp_); \
+                        else hipLaunchKernelGGL((attention_mfma_kernel<__VA_ARGS__>), grid, dim3(256), 0, ctx->stream, p, qp_); }
+      const QProjP qp_ = qproj ? *qproj : QProjP{};
       if (qproj) {                               // queries projected in the kernel (attention_qproj_ok() holds)
         switch (c.d_model / 128) {
-          case 1: hipLaunchKernelGGL((attention_mfma_kernel<false, false, 1>), grid, dim3(256), 0, ctx->stream, p, *qproj); break;
-          case 2: hipLaunchKernelGGL((attention_mfma_kernel<false, false, 2>), grid, dim3(256), 0, ctx->stream, p, *qproj); break;
-          case 4: hipLaunchKernelGGL((attention_mfma_kernel<false, false, 4>), grid, dim3(256), 0, ctx->stream, p, *qproj); break;
-          default: hipLaunchKernelGGL((attention_mfma_kernel<false, false, 8>), grid, dim3(256), 0, ctx->stream, p, *qproj); break;
+          case 1: BPD_ATTN(false, false, 1) break;
+          case 2: BPD_ATTN(false, false, 2) break;
+          case 4: BPD_ATTN(false, false, 4) break;
+          default: BPD_ATTN(false, false, 8) break;
         }
         return;
       }
       if (causal && kv_bytes > ((size_t)128 << 20)) {
-        if (limf) hipLaunchKernelGGL((attention_mfma_kernel<true, true, 0>), grid, dim3(256), 0, ctx->stream, p, QProjP{});
-        else hipLaunchKernelGGL((attention_mfma_kernel<true, false, 0>), grid, dim3(256), 0, ctx->stream, p, QProjP{});
+        if (limf) BPD_ATTN(true, true, 0) else BPD_ATTN(true, false, 0)
       } else {
-        if (limf) hipLaunchKernelGGL((attention_mfma_kernel<false, true, 0>), grid, dim3(256), 0, ctx->stream, p, QProjP{});
-        else hipLaunchKernelGGL((attention_mfma_kernel<false, false, 0>), grid, dim3(256), 0, ctx->stream, p, QProjP{});
+        if (limf) BPD_ATTN(false, true, 0) else BPD_ATTN(false, false, 0)
       }
+#undef BPD_ATTN
       if (nsplit > 1) launch_combine<bf16_t, 64>(p, cgrid, ctx->stream);
     } else {
       hipLaunchKernelGGL((attention_kernel<bf16_t, 16>), grid, dim3(256), 0, ctx->stream, p);
@@ -580,22 +602,22 @@ void attention(bpd_ctx* ctx, const float* Q, const void* Kc, const void* Vc, voi
 }
 
 void embed(bpd_ctx* ctx, const int* tok, int tok_ld, const int* base, int rows_per_seq, int M, const float* pos,
-           float* x, int zero_input, unsigned long long* keys = nullptr, int nkeys = 0) {
+           float* x, int zero_input, unsigned long long* keys = nullptr, int nkeys = 0, const int* seq = nullptr) {
   const bpd_config& c = ctx->cfg;
   const long n = (long)M * c.d_model;
   dim3 grid((unsigned)((n + 255) / 256));
   const float scale = sqrtf((float)c.d_model);
   if (stats_path(ctx, M) && x == ctx->lay.x) {
     hipLaunchKernelGGL(embed_stats_kernel, dim3(c.d_model / 16), dim3(64), 0, ctx->stream, tok, tok_ld, base, rows_per_seq, M,
-                       c.d_model, (const bf16_t*)ctx->lay.emb, c.vocab, pos, scale, x, zero_input, ctx->lay.stats_ln, keys, nkeys);
+                       c.d_model, (const bf16_t*)ctx->lay.emb, c.vocab, pos, scale, x, zero_input, ctx->lay.stats_ln, keys, nkeys, seq);
     return;
   }
   if (c.dtype == BPD_BF16)
     hipLaunchKernelGGL(embed_kernel<true>, grid, dim3(256), 0, ctx->stream, tok, tok_ld, base, rows_per_seq, M, c.d_model,
-                       ctx->lay.emb, c.vocab, pos, scale, x, zero_input, keys, nkeys);
+                       ctx->lay.emb, c.vocab, pos, scale, x, zero_input, keys, nkeys, seq);
   else
     hipLaunchKernelGGL(embed_kernel<false>, grid, dim3(256), 0, ctx->stream, tok, tok_ld, base, rows_per_seq, M, c.d_model,
-                       ctx->lay.emb, c.vocab, pos, scale, x, zero_input, keys, nkeys);
+                       ctx->lay.emb, c.vocab, pos, scale, x, zero_input, keys, nkeys, seq);
 }
 
 void fill_i32(bpd_ctx* ctx, int* p, long n, int v) {
@@ -617,7 +639,7 @@ int stack_lds_bytes(const bpd_ctx* ctx, int B, int R) { return stack_lds_need(st
 bool stack_usable(const bpd_ctx* ctx, int B, int R) {
   const bpd_config& c = ctx->cfg;
   const int M = B * R;
-  return ctx->stack_workers > 0 && !ctx->stack_off && ctx->lay.stack_ex != nullptr && M >= 1 && M <= 16 && ctx->local_q == 0 &&
+  return ctx->stack_workers > 0 && !ctx->stack_off && ctx->lay.stack_ex != nullptr && M >= 1 && M <= 16 && ctx->local_q == 0 && ctx->seq == nullptr &&
          attention_nsplit(ctx, c.max_out_len + c.k_max + 1, B, R, 1) == 1 && attention_nsplit(ctx, c.max_src_len, B, R, 0) == 1 &&
          stack_lds_bytes(ctx, B, R) <= 160 * 1024 &&
          (std::max(3 * c.d_model, c.d_ff) / 16 + ctx->stack_workers - 1) / ctx->stack_workers <= 8;     // tiles a helper wave finishes: two
@@ -699,8 +721,9 @@ StateP state_params(bpd_ctx* ctx);
 int heads_two_phase(bpd_ctx* ctx, int k) {
   const bpd_config& c = ctx->cfg;
   Layout& L = ctx->lay;
-  const int B = ctx->B, d = c.d_model, F = c.d_ff, M = B * k;
+  const int B = ctx->Bs, d = c.d_model, F = c.d_ff, M = B * k;
   const size_t as = act_size(c);
+  const int* seq = ctx->seq;
   // phase 1: head 1 (the base model's p_1) at every block row
   layernorm(ctx, L.x, L.dec_lnf, M, L.hn, L.h);
   gemm(ctx, gp(L.hn, d, L.hw1, c.k_max * F, M, F, d), plain(L.hb1, 1, nullptr, 0, nullptr, 0, L.H, F));
@@ -711,11 +734,11 @@ int heads_two_phase(bpd_ctx* ctx, int k) {
   vocab_argmax(ctx, gp(L.O, d, L.emb, c.vocab, M, c.vocab, d), L.keys_h1, topn ? L.logits_h1 : nullptr);
   if (topn)
     hipLaunchKernelGGL(topn_rank_kernel, dim3(k - 1, B), dim3(256), 0, ctx->stream, (const float*)L.logits_h1, c.vocab,
-                       (const int*)L.P, c.k_max, k, ctx->top_n, L.topn_ok);
+                       (const int*)L.P, c.k_max, k, ctx->top_n, L.topn_ok, seq);
   StateP st = state_params(ctx);
   st.imposed = ctx->cur_imposed; st.imposed_stride = ctx->cur_imposed_stride;
   hipLaunchKernelGGL(select_row_kernel, dim3(B), dim3(256), 0, ctx->stream, st, (const unsigned long long*)L.keys_h1, k,
-                     ctx->cur_imposed_step, (const bf16_t*)L.hn, (const float*)L.h, d, L.sel, (bf16_t*)L.hn2, L.h2);
+                     ctx->cur_imposed_step, (const bf16_t*)L.hn, (const float*)L.h, d, L.sel, (bf16_t*)L.hn2, L.h2, seq);
   // phase 2: heads 2..k at the selected row of each sequence
   const int kh = k - 1;
   const char* w1 = (const char*)L.hw1 + (size_t)F * d * as;          // packed by 16-column tiles: head 2 starts F columns in
@@ -730,7 +753,7 @@ int heads_two_phase(bpd_ctx* ctx, int k) {
   }
   vocab_argmax(ctx, gp(L.O, d, L.emb, c.vocab, B * kh, c.vocab, d), keys2, nullptr);
   hipLaunchKernelGGL(assemble_keys_kernel, dim3(B), dim3(256), 0, ctx->stream, (const unsigned long long*)L.keys_h1,
-                     (const unsigned long long*)keys2, (const int*)L.sel, k, L.keys);
+                     (const unsigned long long*)keys2, (const int*)L.sel, k, L.keys, seq);
   LAUNCHCHK();
   if (ctx->pend_slices) return fail(ctx, BPD_E_STATE, "split-K slices were left unreduced");
   return BPD_OK;
@@ -755,11 +778,13 @@ void refresh_folded_weights(bpd_ctx* ctx) {
 int forward(bpd_ctx* ctx, int R, int k, int zero_input, float* logits) {
   const bpd_config& c = ctx->cfg;
   Layout& L = ctx->lay;
-  const int B = ctx->B, d = c.d_model, F = c.d_ff, M = B * R;
+  const int B = ctx->Bs, d = c.d_model, F = c.d_ff, M = B * R;
   const int slots = c.max_out_len + c.k_max + 1;
   const size_t as = act_size(c);
   const long nk = (long)M * k;
   const bool sp = stats_path(ctx, M);
+  const int* seq = ctx->seq;
+  const int *base = seq ? L.slot_L : L.L, *srcs = seq ? L.slot_src : L.src_len;
   // residual update x += ...; on the statistics path the kernel also leaves LayerNorm partial sums
   // with more rows the LDS-staged kernel leaves them per tile in L.stats_big for the LayerNorm-fused GEMM that follows
   // (up to 128 rows: with more, every column block repeating the normalisation of its rows costs more than the kernel saved)
@@ -779,10 +804,10 @@ int forward(bpd_ctx* ctx, int R, int k, int zero_input, float* logits) {
     PhaseTimer t(ctx, BPD_PHASE_LAYERS);
     // (the previous step's accept kernel may already have embedded this block, with its statistics (and, beyond 16 rows,
     // its bf16 copy in L.xn), and cleared the keys)
-    const bool have_x = embed_in_accept(ctx) && !zero_input && R == k && ctx->x_ready_k == k;
+    const bool have_x = embed_in_accept(ctx) && !zero_input && R == k && ctx->x_ready_k == k && ctx->x_ready_slots == B && !(logits && slots_used(ctx));
     ctx->x_ready_k = 0;
     xs = have_x && !sp;
-    if (!have_x) embed(ctx, L.P, c.k_max, L.L, R, M, L.pos_tgt, L.x, zero_input, L.keys, (int)nk);
+    if (!have_x) embed(ctx, L.P, c.k_max, base, R, M, L.pos_tgt, L.x, zero_input, L.keys, (int)nk, seq);
     const bool stack = sp && stack_usable(ctx, B, R);
     if (stack) launch_stack(ctx, R);
     for (int l = 0; l < (stack ? 0 : c.n_dec_layers); ++l) {
@@ -792,16 +817,16 @@ int forward(bpd_ctx* ctx, int R, int k, int zero_input, float* logits) {
       char* cK = (char*)L.crossK + (size_t)l * c.max_batch * c.max_src_len * d * as;
       char* cV = (char*)L.crossV + (size_t)l * c.max_batch * c.max_src_len * d * as;
       // self-attention sublayer: K/V of the block rows go straight into the cache at L_b + i'
-      gemm_ln(ctx, L.x, w.ln1, L.xn, nullptr, gp(L.xn, d, w.wqkv, 3 * d, M, 3 * d, d), split(L.q, Kl, Vl, d, 0, R, slots, L.L), sp, xs, folds ? &w.f_qkv : nullptr);
-      attention(ctx, L.q, Kl, Vl, L.attn, slots, B, R, L.L, 1);
+      gemm_ln(ctx, L.x, w.ln1, L.xn, nullptr, gp(L.xn, d, w.wqkv, 3 * d, M, 3 * d, d), split(L.q, Kl, Vl, d, 0, R, seq ? 0 : slots, seq ? L.slot_row : L.L), sp, xs, folds ? &w.f_qkv : nullptr);
+      attention(ctx, L.q, Kl, Vl, L.attn, slots, B, R, base, 1, seq);
       xs = gemm(ctx, gp(L.attn, d, w.wo, d, M, d, d), residual(nullptr, d));
       // cross-attention sublayer over the encoder memory
       if ((sp || xs) && attention_qproj_ok(ctx, B, R)) {
         const QProjP qp{L.x, w.ln2.g, w.ln2.b, sp ? L.stats_ln : L.stats_big, sp ? 16 : M, w.cq, c.ln_eps};
-        attention(ctx, nullptr, cK, cV, L.attn, c.max_src_len, B, R, L.src_len, 0, &qp);
+        attention(ctx, nullptr, cK, cV, L.attn, c.max_src_len, B, R, srcs, 0, seq, &qp);
       } else {
         gemm_ln(ctx, L.x, w.ln2, L.xn, nullptr, gp(L.xn, d, w.cq, d, M, d, d), plain(nullptr, 0, nullptr, 0, L.q, d, nullptr, 0), sp, xs, folds ? &w.f_cq : nullptr);
-        attention(ctx, L.q, cK, cV, L.attn, c.max_src_len, B, R, L.src_len, 0);
+        attention(ctx, L.q, cK, cV, L.attn, c.max_src_len, B, R, srcs, 0, seq);
       }
       xs = gemm(ctx, gp(L.attn, d, w.co, d, M, d, d), residual(nullptr, d));
       // feed-forward sublayer
@@ -848,7 +873,7 @@ int forward(bpd_ctx* ctx, int R, int k, int zero_input, float* logits) {
                            (const float*)L.emb, M, c.vocab, d, L.keys_h1, L.logits_h1);
       }
       hipLaunchKernelGGL(topn_rank_kernel, dim3(k - 1, B), dim3(256), 0, ctx->stream, (const float*)L.logits_h1, c.vocab,
-                         (const int*)L.P, c.k_max, k, ctx->top_n, L.topn_ok);
+                         (const int*)L.P, c.k_max, k, ctx->top_n, L.topn_ok, seq);
     }
   }
   LAUNCHCHK();
@@ -864,6 +889,7 @@ StateP state_params(bpd_ctx* ctx) {
   s.kmax = ctx->cfg.k_max; s.max_out = ctx->cfg.max_out_len;
   s.eos_id = ctx->cfg.eos_id; s.distance_eps = ctx->distance_eps; s.min_block = ctx->min_block;
   s.topn_ok = ctx->top_n > 1 ? ctx->lay.topn_ok : nullptr;
+  s.fin_step = L.fin_step; s.slot_seq = L.slot_seq; s.slot_L = L.slot_L; s.slot_src = L.slot_src; s.slot_row = L.slot_row; s.cache_rows = ctx->cfg.max_out_len + ctx->cfg.k_max + 1; s.n_live = L.n_live; s.src_len = L.src_len;
   return s;
 }
 
@@ -884,7 +910,7 @@ int encoder(bpd_ctx* ctx) {
   for (int l = 0; l < c.n_enc_layers; ++l) {
     EncL& w = L.enc[l];
     gemm_ln(ctx, L.xe, w.ln1, L.xen, nullptr, gp(L.xen, d, w.wqkv, 3 * d, M, 3 * d, d), split(L.qe, L.ke, L.ve, d, 0, S, S, nullptr), false, xs);
-    attention(ctx, L.qe, L.ke, L.ve, L.attne, S, B, S, L.src_len, 0);
+    attention(ctx, L.qe, L.ke, L.ve, L.attne, S, B, S, L.src_len, 0, nullptr);
     xs = gemm(ctx, gp(L.attne, d, w.wo, d, M, d, d), residual(nullptr));
     gemm_ln(ctx, L.xe, w.ln2, L.xen, nullptr, gp(L.xen, d, w.w1, F, M, F, d), plain(w.b1, 1, nullptr, 0, nullptr, 0, L.ffhe, F), false, xs);
     xs = gemm(ctx, gp(L.ffhe, F, w.w2, d, M, d, F), residual(w.b2));
@@ -1192,6 +1218,7 @@ int bpd_encode(bpd_ctx* ctx, const int32_t* src_ids, const int32_t* src_len, con
     LAUNCHCHK();
     ++ctx->encode_tag;
   }
+  use_slots(ctx, B);
   int rc = encoder(ctx);
   if (rc) return rc;
   // first invocation: position 0 only, all heads -> first proposals
@@ -1200,32 +1227,38 @@ int bpd_encode(bpd_ctx* ctx, const int32_t* src_ids, const int32_t* src_len, con
   hipLaunchKernelGGL(prime_kernel, dim3(B), dim3(64), 0, ctx->stream, state_params(ctx), L.keys, B);
   LAUNCHCHK();
   ctx->steps = 0;
+  ctx->live1 = ctx->live2 = B;
+  ctx->budget_min = !max_len ? c.max_out_len : (host_max ? *std::min_element(max_len, max_len + B) : 0);
   ctx->encoded = true;
   return BPD_OK;
 }
 
-// report_tag: bpd_decode's tag of this step (0: the step reports nothing to the host)
-static int step_impl(bpd_ctx* ctx, int k, const int* imposed_dev, int imposed_stride, int imposed_step, int* accepted_dev, unsigned report_tag = 0) {
-  Layout& L = ctx->lay;
-  if (!report_tag) std::fill(ctx->remaining.begin(), ctx->remaining.end(), -1);      // the host does not follow this step
-  PhaseTimer whole(ctx, BPD_PHASE_STEP);
+// A step in two parts: the model invocation on the slots of use_slots(), then verify / accept / commit, which also embeds
+// the next block, for next_slots slots.
+static int step_forward(bpd_ctx* ctx, int k, const int* imposed_dev, int imposed_stride, int imposed_step) {
   ctx->cur_imposed = imposed_dev; ctx->cur_imposed_stride = imposed_stride; ctx->cur_imposed_step = imposed_step;
-  int rc = forward(ctx, k, k, 0, nullptr);
-  if (rc) return rc;
+  return forward(ctx, k, k, 0, nullptr);
+}
+// report_tag: bpd_decode's tag of this step (0: the step reports nothing to the host)
+static int step_accept(bpd_ctx* ctx, int k, int* accepted_dev, int next_slots, unsigned report_tag) {
+  Layout& L = ctx->lay;
   {
     PhaseTimer t(ctx, BPD_PHASE_ACCEPT);
     StateP s = state_params(ctx);
-    s.imposed = imposed_dev; s.imposed_stride = imposed_stride;
+    s.imposed = ctx->cur_imposed; s.imposed_stride = ctx->cur_imposed_stride;
     if (report_tag) { s.report = report_of(ctx, report_tag); s.report_tag = report_tag; }
     const bpd_config& c = ctx->cfg;
+    const int imposed_step = ctx->cur_imposed_step;
     if (embed_in_accept(ctx)) {
       // the accept kernel also embeds the next block (same k assumed; checked by forward); its LayerNorm statistics go
       // where the first layer will look for them: the single-tile layout for at most 16 rows, per-tile rows otherwise
-      const bool sp = stats_path(ctx, ctx->B * k);
+      const int rows = next_slots * k;
+      const bool sp = stats_path(ctx, rows);
       hipLaunchKernelGGL(accept_embed_kernel, dim3(ctx->B), dim3(1024), 0, ctx->stream, s, L.keys, k, ctx->B, imposed_step, accepted_dev,
                          c.d_model, (const bf16_t*)L.emb, c.vocab, (const float*)L.pos_tgt, sqrtf((float)c.d_model), L.x,
-                         sp ? L.stats_ln : L.stats_big, sp ? 16 : ctx->B * k, sp ? (bf16_t*)nullptr : (bf16_t*)L.xn, (int)ctx->steps);
-      ctx->x_ready_k = k;
+                         sp ? L.stats_ln : L.stats_big, sp ? 16 : rows, sp ? (bf16_t*)nullptr : (bf16_t*)L.xn, (int)ctx->steps,
+                         !slots_used(ctx) ? 0 : (ctx->seq ? 2 : 1));
+      ctx->x_ready_k = k; ctx->x_ready_slots = next_slots;
     } else {
       hipLaunchKernelGGL(accept_kernel, dim3(ctx->B), dim3(64), 0, ctx->stream, s, L.keys, k, ctx->B, 1, imposed_step, accepted_dev, (int)ctx->steps);
       ctx->x_ready_k = 0;
@@ -1234,6 +1267,16 @@ static int step_impl(bpd_ctx* ctx, int k, const int* imposed_dev, int imposed_st
   LAUNCHCHK();
   ctx->steps++;
   return BPD_OK;
+}
+// A whole step that the host does not follow (bpd_step, bpd_step_static).
+static int step_impl(bpd_ctx* ctx, int k, const int* imposed_dev, int* accepted_dev) {
+  PhaseTimer whole(ctx, BPD_PHASE_STEP);
+  std::fill(ctx->remaining.begin(), ctx->remaining.end(), -1);
+  ctx->live1 = ctx->live2 = -1;
+  use_slots(ctx, -1);
+  const int rc = step_forward(ctx, k, imposed_dev, 0, 0);
+  if (rc) return rc;
+  return step_accept(ctx, k, accepted_dev, ctx->B, 0);
 }
 
 int bpd_step(bpd_ctx* ctx, int k, const int32_t* imposed_accept, int32_t* accepted_len) {
@@ -1252,7 +1295,7 @@ int bpd_step(bpd_ctx* ctx, int k, const int32_t* imposed_accept, int32_t* accept
     }
   }
   const bool out_host = accepted_len && is_host_ptr_cached(ctx, accepted_len);
-  int rc = step_impl(ctx, k, imp, 0, 0, out_host ? nullptr : accepted_len);
+  int rc = step_impl(ctx, k, imp, out_host ? nullptr : accepted_len);
   if (rc) return rc;
   if (out_host) HIPCHK(hipMemcpyAsync(accepted_len, L.accepted, (size_t)ctx->B * 4, hipMemcpyDeviceToHost, ctx->stream));
   return BPD_OK;
@@ -1307,7 +1350,7 @@ int bpd_step_static(bpd_ctx* ctx, int k, const int32_t* imposed_accept, int32_t*
   // the array keeps the last call's contents and the keys are merged with atomic max: they start at zero
   // (a fill kernel, not a memset node: callers may be capturing the stream)
   fill_i32(ctx, (int*)L.keys, (long)(2 * M * k), 0);
-  int rc = step_impl(ctx, k, imp, 0, 0, out_host ? nullptr : accepted_len);
+  int rc = step_impl(ctx, k, imp, out_host ? nullptr : accepted_len);
   L.keys = keys0; L.keys_h1 = keys_h10; L.attn_part = attn0; L.kpart = kpart0;
   // (this step's accept kernel cleared the static keys, not the workspace's: the next step embeds its block and clears
   // its keys itself)
@@ -1377,7 +1420,8 @@ int bpd_get_output(bpd_ctx* ctx, int32_t* out_ids, int32_t* out_len) {
 }
 
 // The host follows the decode through words that the accept kernel of every step stores in pinned memory (StateP::report),
-// and stays one step ahead of them: step s is enqueued while step s - 1 runs, then the host waits for the report of s - 1.
+// and stays one step ahead of them: step s is enqueued while step s - 1 runs, then the host waits for the report of s - 1
+// (and tells the accept kernel of step s how many sequences step s + 1 will still have).
 // Enqueueing takes less than a step, so the stream never runs dry, and at most one step is enqueued in vain: where an
 // end-of-sequence token, not the length budget, ends the last sequence.  If the budgets say that step s - 1 may be the
 // last one, its report is awaited before step s is enqueued.  (Stopping the stream every four steps to ask cost 25 us per
@@ -1415,31 +1459,43 @@ int bpd_decode(bpd_ctx* ctx, int k, const int32_t* schedule, int max_steps, int3
     }
     return true;
   };
-  bool ended = false;
-  auto await = [&](unsigned tag) {               // the report of the step that was given this tag
-    ended = true;
+  // the report of the step that was given this tag: the sequences that go on after it
+  auto await = [&](unsigned tag, int& going) {
     const unsigned long long* words = report_of(ctx, tag);
+    going = 0;
     for (int b = 0; b < B; ++b) {
       const int rc = wait_word(ctx, &words[b], tag, 32);
       if (rc) return rc;
       rem[b] = (int)(unsigned)words[b];
-      ended = ended && rem[b] == 0;
+      going += rem[b] > 0;
     }
     return (int)BPD_OK;
   };
+  bool ended = true;                             // (known from an earlier decode: nothing is left to do)
+  for (int b = 0; b < B; ++b) ended = ended && rem[b] == 0;
   for (int s = 0; s < max_steps && !ended; ++s) {
+    PhaseTimer whole(ctx, BPD_PHASE_STEP);
     const unsigned before = ctx->report_tag;     // of step s - 1
-    bool know = false;
+    bool know = s == 0;
     if (s > 0 && may_be_last(s - 1)) {
-      const int rc = await(before);
+      const int rc = await(before, ctx->live1);
       if (rc) return rc;
-      if (ended) break;
+      if (ctx->live1 == 0) break;
       know = true;
     }
-    ctx->report_tag = ctx->report_tag == 0xFFFFFFFFu ? 2 : ctx->report_tag + 1;       // (0 means "no report"; turns kept)
-    int rc = step_impl(ctx, k, imp, B, s, nullptr, ctx->report_tag);
-    if (rc == BPD_OK && s > 0 && !know) rc = await(before);
+    // Slots of this step: the sequences that had not ended after step s - 2 (live2); of the next: not after s - 1 (live1),
+    // which the host waits for while the GPU has this step's layers to do
+    use_slots(ctx, ctx->live2);
+    int rc = step_forward(ctx, k, imp, B, s);
+    if (rc == BPD_OK && !know) rc = await(before, ctx->live1);
     if (rc) return rc;
+    if (ctx->live1 == 0) { ctx->x_ready_k = 0; break; }      // step s - 1 was the last: this one accepts nothing
+    ctx->report_tag = ctx->report_tag == 0xFFFFFFFFu ? 2 : ctx->report_tag + 1;       // (0 means "no report"; turns kept)
+    const bool exact = slots_used(ctx) && ctx->live1 > 0;
+    rc = step_accept(ctx, k, nullptr, exact ? ctx->live1 : B, ctx->report_tag);
+    if (rc) return rc;
+    ctx->live2 = ctx->live1; ctx->live1 = -1;
+    if (s + 1 == max_steps) { rc = await(ctx->report_tag, ctx->live1); if (rc) return rc; }
   }
   return output_and_stats(ctx, out_ids, out_len, stats);
 }
@@ -1471,6 +1527,7 @@ int bpd_debug_step_logits(bpd_ctx* ctx, int k, float* logits) {
   if (!ctx || !logits) return fail(ctx, BPD_E_ARG, "bpd_debug_step_logits: null argument");
   if (!ctx->encoded) return fail(ctx, BPD_E_STATE, "bpd_debug_step_logits: call bpd_encode first");
   if (k < 1 || k > ctx->cfg.k_max) return fail(ctx, BPD_E_ARG, "bpd_debug_step_logits: k outside 1..k_max");
+  use_slots(ctx, ctx->B);                         // every sequence, ended or not
   int rc = forward(ctx, k, k, 0, logits);
   if (rc) return rc;
   hipLaunchKernelGGL(accept_kernel, dim3(ctx->B), dim3(64), 0, ctx->stream, state_params(ctx), ctx->lay.keys, k, ctx->B, 0, 0, nullptr, 0);

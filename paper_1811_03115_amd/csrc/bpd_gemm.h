@@ -644,7 +644,7 @@ __global__ __launch_bounds__(512) void stream_gemm_kernel(GemmP p, Epi e) {
 //     one 64-bit atomic max per row and workgroup goes to keys[]
 // Dynamic LDS: 8 * 16 * MT * 8 bytes (keys) + rows * (K + 8) * 2 bytes (X).
 template <int MT, int NT, int UPT, bool STREAM>
-__global__ __launch_bounds__(512) void stream_vocab_kernel(GemmP p, unsigned long long* keys, float* logits) {
+__global__ __launch_bounds__(512) void stream_vocab_kernel(GemmP p, unsigned long long* keys, float* logits, LiveP live) {
   constexpr int WAVES = 8, BM = 16 * MT, UK = 16 / NT;      // UK k-steps per unit
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   unsigned long long* wb = (unsigned long long*)smem_raw;  // [WAVES][BM]
@@ -654,7 +654,9 @@ __global__ __launch_bounds__(512) void stream_vocab_kernel(GemmP p, unsigned lon
   const int lr = lane & 15, lq = lane >> 4;
   const int ntiles = p.N >> 4, ksteps = p.K >> 5;          // ksteps == UK * UPT
   const int m0 = blockIdx.y * BM;
-  const int nrows = min(BM, p.M - m0);
+  const int M = rows_in_use(live, p.M);
+  if (m0 >= M) return;
+  const int nrows = min(BM, M - m0);
   const int t0 = (int)(blockIdx.x * (unsigned)ntiles / gridDim.x), t1 = (int)((blockIdx.x + 1) * (unsigned)ntiles / gridDim.x);
   {   // X: whole wave-loads of 64 pieces (512 columns) inside one row
     const bf16_t* xg = (const bf16_t*)p.X + (long)m0 * p.ldx;
@@ -729,7 +731,7 @@ __global__ __launch_bounds__(512) void stream_vocab_kernel(GemmP p, unsigned lon
             best[t] = key_ > best[t] ? key_ : best[t];                                          \
           }                                                                                     \
           const int m_ = m0 + t * 16 + lr;                                                      \
-          if (logits && m_ < p.M) *(float4*)(logits + (long)m_ * p.N + n_) = make_float4(acc[t][n][0], acc[t][n][1], acc[t][n][2], acc[t][n][3]); \
+          if (logits && m_ < M) *(float4*)(logits + (long)m_ * p.N + n_) = make_float4(acc[t][n][0], acc[t][n][1], acc[t][n][2], acc[t][n][3]); \
         }                                                                                       \
       }                                                                                         \
     }                                                                                           \
@@ -826,7 +828,7 @@ constexpr size_t ldsx_lds_bytes() { return (size_t)(ldsx_deep<MT, NT, KC>() ? 3 
 // producer's partial statistics (requested before everything else, reduced while the first chunk arrives), applied in
 // the epilogue.  X comes through the direct loads like any bf16 operand: no LayerNorm kernel and no normalisation here.
 template <int MT, int NT, int KC, bool ARGMAX, bool XLN, bool STATS, bool ROWAFF = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_min<MT, NT, KC>(), ldsx_waves_max<MT, NT, KC>()))) void gemm_ldsx_kernel(GemmP p, Epi e, unsigned long long* keys, float* logits, LnP ln) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_min<MT, NT, KC>(), ldsx_waves_max<MT, NT, KC>()))) void gemm_ldsx_kernel(GemmP p, Epi e, unsigned long long* keys, float* logits, LnP ln, LiveP live) {
   constexpr int BM = 16 * MT, KS = KC / 32, SEG = KC / 8;
   static_assert(!ROWAFF || (BM <= 64 && !XLN && !ARGMAX), "row statistics: one pass over at most 64 rows");
   __shared__ float2 ra_part[ROWAFF ? 4 * 64 : 1];
@@ -844,6 +846,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
   int bx, by;                                    // (the map: bpd_tile_map.h)
   ldsx_tile_of(p.lx, gridDim.x, gridDim.y, blockIdx.x, blockIdx.y, blockIdx.z, g, by, bx);
   const int m0 = by * BM;
+  // Row blocks past the rows in use end at once.  Large tiles only: the look costs 0.3 us, which the small tiles, whose
+  // launches live for a few microseconds whatever their rows, would not get back.  (Rows past the end in the last block
+  // are computed for nothing, like all dead rows of the small tiles.)
+  if (MT * NT >= 8 && m0 >= rows_in_use(live, p.M)) return;
+  const int M = p.M;
   const int nt0 = (bx * 4 + wave) * NT;
   const int lr = lane & 15, lq = lane >> 4;
   const bf16_t* X = (const bf16_t*)p.X + g * p.x_g;
@@ -862,7 +869,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
     const int slot = tid + 256 * i;
     const int r = slot / SEG;
     int row = m0 + r;
-    row = row < p.M ? row : p.M - 1;
+    row = row < M ? row : M - 1;
     xoff[i] = (row * p.ldx + (((slot % SEG) ^ (r & 7)) * 8)) * 2;      // bytes
   }
 #define BPD_X_TO_LDS(buf, chunk)                                                            \
@@ -882,7 +889,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
     for (int i = 0; i < XI; ++i) {
       const int r = rbase + RPI * i;             // may pass BM when BM * SEG is not a multiple of 256: never read back
       rcl[i] = r < BM ? r : BM - 1;
-      int row = m0 + rcl[i]; row = row < p.M ? row : p.M - 1;
+      int row = m0 + rcl[i]; row = row < M ? row : M - 1;
       xp[i] = ln.x + (long)row * p.K + seg * 8;
       lo[i] = (r * SEG + (seg ^ (r & 7))) * 8;
     }
@@ -942,7 +949,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
       // (one partial per 64-column block; 16 rows: thread = (block tid / 16, row tid % 16): one load per thread)
       constexpr int RL = MT == 1 ? 1 : 4;
       const int tiles = p.K >> 6;                // 64-column blocks of the producer, <= 16
-      int row = m0 + (MT == 1 ? (tid & 15) : lane); row = row < p.M ? row : p.M - 1;
+      int row = m0 + (MT == 1 ? (tid & 15) : lane); row = row < M ? row : M - 1;
       float2 pv[RL];
 #pragma unroll
       for (int i = 0; i < RL; ++i) {             // branch-free: all loads in flight together
@@ -958,7 +965,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
           xpre_b[u] = *(const float4*)(e.bias + n);
 #pragma unroll
           for (int t = 0; t < MT; ++t) {
-            int m = m0 + t * 16 + lr; m = m < p.M ? m : p.M - 1;
+            int m = m0 + t * 16 + lr; m = m < M ? m : M - 1;
             xpre_r[t * NT + u] = *(const float4*)(e.R + (long)m * e.ldr + n);
           }
         }
@@ -998,7 +1005,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
 #undef BPD_NORM1
 #undef BPD_LOAD_X
     if (nt0 >= ntiles) return;
-    store_tiles<MT, NT, STATS>(e, g, acc, m0, nt0, ntiles, p.M, lane, nullptr, nullptr, nullptr, XPREF ? xpre_b : nullptr, XPREF ? xpre_r : nullptr, smem_raw + wave * 2048);
+    store_tiles<MT, NT, STATS>(e, g, acc, m0, nt0, ntiles, M, lane, nullptr, nullptr, nullptr, XPREF ? xpre_b : nullptr, XPREF ? xpre_r : nullptr, smem_raw + wave * 2048);
     return;
   }
   // The direct-to-LDS loads of the loop are issued from inline assembly (lds_dma16) and waited for by hand (s_waitcnt
@@ -1037,7 +1044,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
         pre_b[u] = *(const float4*)(e.bias + g * e.bias_g + n);
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
-          int m = m0 + t * 16 + lr; m = m < p.M ? m : p.M - 1;
+          int m = m0 + t * 16 + lr; m = m < M ? m : M - 1;
           pre_r[t * NT + u] = *(const float4*)(e.R + g * e.r_g + (long)m * e.ldr + n);
         }
       }
@@ -1049,7 +1056,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
   float2 rpv[ROWAFF ? RL : 1];
   float4 ra_c4[NT], ra_d4[NT];
   if constexpr (ROWAFF) {
-    int row = m0 + (MT == 1 ? (tid & 15) : lane); row = row < p.M ? row : p.M - 1;
+    int row = m0 + (MT == 1 ? (tid & 15) : lane); row = row < M ? row : M - 1;
     const int tiles = p.K >> 6;                  // 64-column blocks of the producer, <= 16
 #pragma unroll
     for (int i = 0; i < RL; ++i) {
@@ -1213,7 +1220,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
           const unsigned long long key = argmax_key(acc[t][u][r], (unsigned)(n + r));
           best = key > best ? key : best;
         }
-        if (logits && m < p.M)
+        if (logits && m < M)
           *(float4*)(logits + (long)m * p.N + n) = make_float4(acc[t][u][0], acc[t][u][1], acc[t][u][2], acc[t][u][3]);
       }
       unsigned long long o = __shfl_xor(best, 16, 64); best = o > best ? o : best;
@@ -1221,7 +1228,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
       if (lane < 16) wb[wave * BM + t * 16 + lane] = best;
     }
     __syncthreads();
-    if (tid < BM && m0 + tid < p.M) {
+    if (tid < BM && m0 + tid < M) {
       unsigned long long best = wb[tid];
 #pragma unroll
       for (int w = 1; w < 4; ++w) { const unsigned long long o = wb[w * BM + tid]; best = o > best ? o : best; }
@@ -1235,7 +1242,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
       const int m = m0 + t * 16 + lr;
-      if (m >= p.M) continue;
+      if (m >= M) continue;
 #pragma unroll
       for (int u = 0; u < NT; ++u) {
         if (nt0 + u >= ntiles) continue;
@@ -1244,5 +1251,5 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
     }
     return;
   }
-  store_tiles<MT, NT, STATS, ROWAFF>(e, g, acc, m0, nt0, ntiles, p.M, lane, ra_ms, ra_c4, ra_d4, PREF ? pre_b : nullptr, PREF ? pre_r : nullptr, smem_raw + wave * 2048);
+  store_tiles<MT, NT, STATS, ROWAFF>(e, g, acc, m0, nt0, ntiles, M, lane, ra_ms, ra_c4, ra_d4, PREF ? pre_b : nullptr, PREF ? pre_r : nullptr, smem_raw + wave * 2048);
 }

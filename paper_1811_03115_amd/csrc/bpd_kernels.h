@@ -48,7 +48,8 @@ __device__ __forceinline__ float wave_sum(float v) {
 // mode 1:  the N axis is cut into chunks of `dsplit` columns; chunk c = n/dsplit + chunk0
 //          c == 0 -> Qf[m][n%dsplit] (fp32),  c == 1 -> Ka,  c == 2 -> Va  (act type) at row
 //          (m / rows_per_seq) * cap + (base ? base[m / rows_per_seq] : 0) + m % rows_per_seq
-//          (a K/V cache write at the sequence's current length).
+//          (a K/V cache write at the sequence's current length; with slots cap is 0 and base holds whole cache rows,
+//          StateP::slot_row).
 struct Epi {
   int mode;
   int relu;
@@ -153,6 +154,15 @@ struct GemmP {
   int ksplit; float* part;
   LdsxMap lx;          // gemm_ldsx_kernel: its workgroup -> tile map and K walk (bpd_tile_map.h; set by the launcher)
 };
+
+// Rows in use of a step of a batch some of whose sequences may have ended: *n slots of `per` rows (n null: all).  A kernel's
+// last argument: in the middle of the others it moved them across cache lines, 0.1 .. 0.3 us for each small kernel.
+struct LiveP { const int* n; int per; };
+__device__ __forceinline__ int rows_in_use(const LiveP& live, int M) {
+  if (!live.n) return M;
+  const int m = *live.n * live.per;
+  return m < M ? m : M;
+}
 
 // ---------------------------------------------------------------------------------------
 // bf16 MFMA GEMM.  One workgroup = 4 wavefronts.
@@ -420,19 +430,22 @@ __global__ __launch_bounds__(64) void fold_layernorm_kernel(const bf16_t* Wp, bf
 // Embedding of the k proposed tokens (decoder side) or of the source tokens.
 //   x[row][c] = sqrt(d) * E[tok][c] + pos[position][c];  tok < 0 -> zero vector (the shifted
 //   decoder input at position 0).  E is the packed vocabulary matrix in bf16 mode.
+// seq (decoder side, may be null): the sequence of every slot of rows_per_seq rows (base: indexed by slot), -1: not in use.
 template <bool BF16>
 __global__ void embed_kernel(const int* tok, int tok_ld, const int* base, int rows_per_seq, int M,
                              int d, const void* E, int V, const float* pos, float scale, float* x,
-                             int zero_input, unsigned long long* keys, int nkeys) {
+                             int zero_input, unsigned long long* keys, int nkeys, const int* seq) {
   const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx < nkeys) keys[idx] = 0ull;          // argmax keys of this invocation start at "nothing"
   if (idx >= (long)M * d) return;
   const int row = (int)(idx / d), c = (int)(idx % d);
   const int b = row / rows_per_seq, i = row % rows_per_seq;
+  const int q = seq ? seq[b] : b;
+  if (q < 0) return;
   const int position = (base ? base[b] : 0) + i;
   float v = pos[(long)position * d + c];
   if (!zero_input) {
-    int t = tok[b * tok_ld + i];
+    int t = tok[q * tok_ld + i];
     t = t < 0 ? 0 : (t >= V ? V - 1 : t);      // ids are validated on the host; never index outside E
     float ev;
     if (BF16) {
@@ -454,17 +467,19 @@ __global__ void embed_kernel(const int* tok, int tok_ld, const int* base, int ro
 __global__ __launch_bounds__(64) void embed_stats_kernel(const int* tok, int tok_ld, const int* base, int rows_per_seq,
                                                          int M, int d, const bf16_t* E, int V, const float* pos,
                                                          float scale, float* x, int zero_input, float* stats,
-                                                         unsigned long long* keys, int nkeys) {
+                                                         unsigned long long* keys, int nkeys, const int* seq) {
   const int tile = blockIdx.x, lane = threadIdx.x;
   for (int i = tile * 64 + lane; i < nkeys; i += gridDim.x * 64) keys[i] = 0ull;
   const int row = lane & 15, c0 = tile * 16 + (lane >> 4) * 4;
   const int r = row < M ? row : M - 1;
   const int b = r / rows_per_seq, i = r % rows_per_seq;
+  int sq = seq ? seq[b] : b;
+  sq = sq < 0 ? 0 : sq;                          // (a slot not in use, of length 0: any row will do)
   const int position = (base ? base[b] : 0) + i;
   const float4 pv = *(const float4*)(pos + (long)position * d + c0);
   float v[4] = {pv.x, pv.y, pv.z, pv.w};
   if (!zero_input) {
-    int t = tok[b * tok_ld + i];
+    int t = tok[sq * tok_ld + i];
     t = t < 0 ? 0 : (t >= V ? V - 1 : t);
     const int ksteps = d >> 5;
     const long tl = (long)(t >> 4) * ksteps + (c0 >> 5);
@@ -645,6 +660,8 @@ struct AttnP {
   float scale;
   int local_q, local_m;   // causal only, local_q > 0: 1D local attention (Section 7.2): the row at position t sees keys
                           // floor(t / local_q) * local_q - local_m .. t; the chunks then start at the first row's bound
+  const int* seq;         // null: Q, out, limit and the K/V buffer are all indexed by sequence.  Otherwise Q, out and limit by
+                          // slot, and seq[slot] is the sequence in the K/V buffer (-1: slot not in use)
   int nsplit;             // key chunks are dealt round-robin to nsplit workgroups per (head, sequence, row tile)
   float* part;            // nsplit > 1: partial results [b][h][tile][split][16*DH acc | 16 max | 16 sum]
 };
@@ -667,14 +684,16 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnP p) {
   __shared__ __attribute__((aligned(16))) ACT vs[CH][DH];
   __shared__ float m_s[RT], l_s[RT], alpha_s[RT];
   const int h = blockIdx.x, b = blockIdx.y;
+  const int sb = p.seq ? p.seq[b] : b;
+  if (sb < 0) return;
   const int split = blockIdx.z % p.nsplit, tile = blockIdx.z / p.nsplit, r0 = tile * RT;
   int kbeg = 0;                                  // local attention: the length decides where the keys start (read first)
   if (p.causal && p.local_q > 0) { const int l0 = p.limit[b]; kbeg = attn_first_key(p, (l0 < 0 ? 0 : l0) + r0); }
   const int first = kbeg + split * CH, hop = p.nsplit * CH;
   const int nrows = min(RT, p.R - r0);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const ACT* Kb = (const ACT*)p.Kc + b * p.kv_seq_stride + h * DH;
-  const ACT* Vb = (const ACT*)p.Vc + b * p.kv_seq_stride + h * DH;
+  const ACT* Kb = (const ACT*)p.Kc + sb * p.kv_seq_stride + h * DH;
+  const ACT* Vb = (const ACT*)p.Vc + sb * p.kv_seq_stride + h * DH;
   // first chunk's K and V rows are requested before anything else: one memory round trip
   constexpr int VW = DH * sizeof(ACT) / 16;               // 16-byte words per row
   uint4 kraw[VW], vraw[VW];
@@ -887,12 +906,12 @@ struct AttnLds {
     return s;
   }
 };
-// One (head h, sequence b, z = row tile * nsplit + split) item of the attention, run by 256 threads (tid 0..255, four
+// One (head h, sequence b (in the K/V buffer: sb), z = row tile * nsplit + split) item of the attention, run by 256 threads (tid 0..255, four
 // whole waves) that share `sm`; nheads / nz: the extents the partial-result layout is indexed with.  Every
 // __syncthreads() inside is reached by all 256 threads; a caller whose workgroup has more waves makes those arrive at
 // as many barriers (one with QU == 0, three with QU > 0).
 template <bool KVNT, bool LIMF, int QU>
-__device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP& qp, const AttnLds& sm, int h, int b, int z,
+__device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP& qp, const AttnLds& sm, int h, int b, int sb, int z,
                                                     int nheads, int nz, int tid) {
   constexpr int RT = 16, CH = 256, DH = 64, WK = 64, VLD = DH + 4;
   bf16_t (*vs)[WK][VLD] = sm.vs;
@@ -904,8 +923,8 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
   const int nrows = min(RT, p.R - r0);
   const int lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 15, lq = lane >> 4;
-  const bf16_t* Kb = (const bf16_t*)p.Kc + b * p.kv_seq_stride + h * DH;
-  const bf16_t* Vb = (const bf16_t*)p.Vc + b * p.kv_seq_stride + h * DH;
+  const bf16_t* Kb = (const bf16_t*)p.Kc + sb * p.kv_seq_stride + h * DH;
+  const bf16_t* Vb = (const bf16_t*)p.Vc + sb * p.kv_seq_stride + h * DH;
   int kmax = p.cap;                              // rows that may be fetched
   int kbeg = 0;                                  // first key of the first chunk (local attention: LIMF only)
   if (LIMF) {
@@ -1167,8 +1186,10 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
     if (tid < RT) { part[RT * DH + tid] = M; part[RT * DH + RT + tid] = L; }
   }
 }
-template <bool KVNT, bool LIMF, int QU>
-__global__ __launch_bounds__(256) void attention_mfma_kernel(AttnP p, QProjP qp) {
+// SLOTS: a step of a batch some of whose sequences may have ended (AttnP::seq); a kernel of its own, since looking the
+// sequence up is one more round trip ahead of the K/V loads.
+template <bool KVNT, bool LIMF, int QU, bool SLOTS>
+__device__ __forceinline__ void attention_mfma_entry(const AttnP& p, const QProjP& qp) {
   constexpr int RT = 16, DH = 64, WK = 64, VLD = DH + 4;
   __shared__ __attribute__((aligned(16))) bf16_t vs[4][WK][VLD];
   __shared__ f32x4 o_s[4][4][64];
@@ -1176,8 +1197,14 @@ __global__ __launch_bounds__(256) void attention_mfma_kernel(AttnP p, QProjP qp)
   __shared__ __attribute__((aligned(16))) float q_s[QU > 0 ? RT * (DH + 4) : 4];
   AttnLds sm;
   sm.vs = vs; sm.o_s = o_s; sm.m_s = m_s; sm.l_s = l_s; sm.q_s = q_s;
-  attention_mfma_body<KVNT, LIMF, QU>(p, qp, sm, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.x, gridDim.z, threadIdx.x);
+  const int sb = SLOTS ? p.seq[blockIdx.y] : blockIdx.y;
+  if (SLOTS && sb < 0) return;
+  attention_mfma_body<KVNT, LIMF, QU>(p, qp, sm, blockIdx.x, blockIdx.y, sb, blockIdx.z, gridDim.x, gridDim.z, threadIdx.x);
 }
+template <bool KVNT, bool LIMF, int QU>
+__global__ __launch_bounds__(256) void attention_mfma_kernel(AttnP p, QProjP qp) { attention_mfma_entry<KVNT, LIMF, QU, false>(p, qp); }
+template <bool KVNT, bool LIMF, int QU>
+__global__ __launch_bounds__(256) void attention_mfma_slots_kernel(AttnP p, QProjP qp) { attention_mfma_entry<KVNT, LIMF, QU, true>(p, qp); }
 
 // Merge of the nsplit partial results of attention_kernel: with M the largest of the partial
 // maxima, output = sum_s acc_s e^(m_s - M) / sum_s l_s e^(m_s - M).  Grid (heads, B, row tiles).
@@ -1239,6 +1266,16 @@ struct StateP {
   // bpd_decode only (null otherwise): host memory, one word per sequence, where the step leaves (report_tag << 32) | tokens
   // still to come (0: ended), so that the host can follow the decode without stopping the stream
   unsigned long long* report; unsigned report_tag;
+  // Slots: the rows of a step belong to the sequences that had not ended when the step before it began, packed in
+  // sequence order, so that a batch of unequal lengths does not compute the rows of those that are done.
+  int* fin_step;       // [B] step (since bpd_encode) that ended the sequence, INT_MAX before
+  int* slot_seq;       // [B] sequence of each slot of the next step, -1 behind the last
+  int* slot_L; int* slot_src;   // [B] cache length and source length of that sequence
+  int* slot_row;       // [B] its next cache row, counted over all sequences (behind the last slot: of one that has ended, where
+                       // rows past its length may be overwritten)
+  int cache_rows;      // cache rows of a sequence
+  int* n_live;         // [1] slots in use
+  const int* src_len;
 };
 
 __device__ __forceinline__ void report_remaining(const StateP& s, int b, int remaining) {
@@ -1264,7 +1301,9 @@ __global__ __launch_bounds__(256) void encode_init_kernel(StateP s, const int* s
     d_len[q] = sl < 1 ? 1 : (sl > S ? S : sl);
     s.max_len[q] = m < 1 ? 1 : (m > s.max_out ? s.max_out : m);
     s.L[q] = 0; s.j[q] = 0; s.finished[q] = 0; s.accepted[q] = 0;
+    s.fin_step[q] = 0x7FFFFFFF; s.slot_seq[q] = q; s.slot_L[q] = 1; s.slot_src[q] = d_len[q]; s.slot_row[q] = q * s.cache_rows + 1;
   }
+  if (i == 0) *s.n_live = B;
   __syncthreads();                               // (every argument this workgroup reads has arrived: it has been stored)
   if (threadIdx.x == 0 && atomicAdd(counter, 1u) == gridDim.x - 1) {
     *counter = 0;
@@ -1314,9 +1353,10 @@ __global__ void prime_kernel(StateP s, const unsigned long long* keys, int B) {
 // proposal is the number of tokens that beat it in the (value, lower index first) order of the
 // arg-max keys.  Grid (k - 1, B), one workgroup per tested row.
 __global__ __launch_bounds__(256) void topn_rank_kernel(const float* logits, int V, const int* P, int kmax, int k, int n,
-                                                        int* ok) {
-  const int i = blockIdx.x, b = blockIdx.y;
-  const float* z = logits + ((long)b * k + i) * V;
+                                                        int* ok, const int* seq) {
+  const int i = blockIdx.x, b = seq ? seq[blockIdx.y] : blockIdx.y;
+  if (b < 0) return;
+  const float* z = logits + ((long)blockIdx.y * k + i) * V;
   int t = P[b * kmax + i + 1];
   t = t < 0 ? 0 : (t >= V ? V - 1 : t);
   const unsigned long long kt = argmax_key(z[t], (unsigned)t);
@@ -1374,20 +1414,22 @@ __device__ __forceinline__ int cut_length(const StateP& s, int b, int lane, int 
 // heads 2..k.  Grid B, 256 threads (the first wavefront verifies).
 __global__ __launch_bounds__(256) void select_row_kernel(StateP s, const unsigned long long* keys_h1, int k, int step,
                                                          const bf16_t* hn, const float* h, int d, int* sel,
-                                                         bf16_t* hn2, float* h2) {
-  const int b = blockIdx.x, lane = threadIdx.x & 63;
+                                                         bf16_t* hn2, float* h2, const int* seq) {
+  const int c_ = blockIdx.x, lane = threadIdx.x & 63;      // slot; b: its sequence
+  const int b = seq ? seq[c_] : c_;
+  if (b < 0) return;
   __shared__ int row_s;
   if (threadIdx.x < 64) {
     const int myP = lane < k ? s.P[b * s.kmax + lane] : -1;
-    const int a1 = (lane >= 1 && lane < k) ? key_index(keys_h1[(long)b * k + lane - 1]) : 0;
+    const int a1 = (lane >= 1 && lane < k) ? key_index(keys_h1[(long)c_ * k + lane - 1]) : 0;
     bool eos;
     int khat = verified_length(s, b, k, lane, myP, a1, step);
     khat = cut_length(s, b, lane, myP, khat, eos);   // the row the accept kernel will read
     khat = khat < 1 ? 1 : khat;                      // (a sequence that has already ended keeps its state)
-    if (lane == 0) { row_s = khat - 1; sel[b] = khat - 1; }
+    if (lane == 0) { row_s = khat - 1; sel[c_] = khat - 1; }
   }
   __syncthreads();
-  const long src = ((long)b * k + row_s) * d, dst = (long)b * d;
+  const long src = ((long)c_ * k + row_s) * d, dst = (long)c_ * d;
   for (int c = threadIdx.x; c < d; c += 256) { hn2[dst + c] = hn[src + c]; h2[dst + c] = h[src + c]; }
 }
 
@@ -1395,8 +1437,10 @@ __global__ __launch_bounds__(256) void select_row_kernel(StateP s, const unsigne
 // Column 0 (head 1) of every block row comes from the first phase, columns 1..k-1 of row sel[b]
 // from the second; the other entries stay empty (key 0 reads back as token -1).  Grid B, 256 threads.
 __global__ __launch_bounds__(256) void assemble_keys_kernel(const unsigned long long* keys_h1, const unsigned long long* keys2,
-                                                            const int* sel, int k, unsigned long long* keys) {
-  const int b = blockIdx.x, r = sel[b];
+                                                            const int* sel, int k, unsigned long long* keys, const int* seq) {
+  const int b = blockIdx.x;                      // slot
+  if (seq && seq[b] < 0) return;
+  const int r = sel[b];
   for (int e = threadIdx.x; e < k * k; e += 256) {
     const int ip = e / k, i = e % k;
     unsigned long long v = 0ull;
@@ -1459,25 +1503,59 @@ __global__ __launch_bounds__(64) void accept_kernel(StateP s, const unsigned lon
 // the sequence's k next rows (token i = new proposal i, position = new L + i) with their partial LayerNorm statistics,
 // exactly as embed_stats_kernel would at the start of the next step, and the sequence's k*k arg-max keys are cleared
 // for the next vocabulary projection.
-// stats: srows = 16: [(tile * 16 + row) * 2] per 16-column tile; otherwise srows = B * k rows and one entry per
+// stats: srows = 16: [(tile * 16 + row) * 2] per 16-column tile; otherwise srows = the rows of the next block and one entry per
 // 64-column block, [(block * srows + row) * 2]; xb (may be null):
 // bf16 copy of the rows as well.
+// slots != 0: the next step's slots are dealt here (StateP::slot_seq); 2: this step's rows and keys are indexed by slot too.
 __global__ __launch_bounds__(1024) void accept_embed_kernel(StateP s, unsigned long long* keys, int k, int B, int step,
                                                             int* accepted_out, int d, const bf16_t* E, int V,
                                                             const float* pos, float scale, float* x, float* stats,
-                                                            int srows, bf16_t* xb, int live_step) {
+                                                            int srows, bf16_t* xb, int live_step, int slots) {
   __shared__ int tok_s[16];
   __shared__ int L_s;
+  __shared__ int slot_s[2];                      // this sequence's slot in this step and in the next (-1: none)
   __shared__ int A_s[256];                       // the sequence's k x k arg-max table
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (b >= B) return;
+  // Slots of this step (sequences not ended before step live_step - 1) and of the next (not before this one).  (The
+  // workgroups of this launch write fin_step too: live_step, which both tests let pass.)  With all of the batch in this
+  // step (slots == 1) the slot is the sequence and only the next step's is worked out, by a wave of its own.
+  if (slots && wave == (slots == 1 ? 1 : 0)) {
+    int cur = 0, nxt = 0, all_cur = 0, all_nxt = 0, mine = 0;
+    for (int q0 = 0; q0 < B; q0 += 64) {
+      const int q = q0 + lane, f = q < B ? s.fin_step[q] : -2;
+      const unsigned long long bc = __ballot(f >= live_step - 1), bn = __ballot(f >= live_step);
+      const unsigned long long below = b >= q0 + 64 ? ~0ull : (b > q0 ? (1ull << (b - q0)) - 1ull : 0ull);
+      cur += __popcll(bc & below); nxt += __popcll(bn & below);
+      all_cur += __popcll(bc); all_nxt += __popcll(bn);
+      if (b >= q0 && b < q0 + 64) mine = (int)((bc >> (b - q0)) & 1) | ((int)((bn >> (b - q0)) & 1) << 1);
+    }
+    if (lane == 0) {
+      slot_s[0] = mine & 1 ? cur : -1; slot_s[1] = mine & 2 ? nxt : -1;
+      if (mine & 2) { s.slot_seq[nxt] = b; s.slot_src[nxt] = s.src_len[b]; }
+      else if (mine & 1) {                       // leaves: the last slots, as many as sequences leave, fall free
+        const int q = all_nxt + cur - nxt;
+        s.slot_seq[q] = -1; s.slot_L[q] = 0; s.slot_row[q] = b * s.cache_rows + s.L[b];
+      }
+      if (b == 0) *s.n_live = all_nxt;
+    }
+  }
+  int slot = b;
+  if (slots == 2) {
+    __syncthreads();
+    slot = slot_s[0];
+    if (slot < 0) {                              // ended before the step began: no rows, nothing to do
+      if (tid == 0) { s.accepted[b] = 0; if (accepted_out) accepted_out[b] = 0; report_remaining(s, b, 0); }
+      return;
+    }
+  }
   if (wave == 0) {
     // one round trip for all the state the decision reads (the chain of dependent loads of accept_kernel costs more
     // than its arithmetic); the table then passes through LDS, so row k-hat needs no second trip
     const int kk = k * k;
     unsigned long long kv[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) kv[q] = keys[(long)b * kk + (lane + 64 * q < kk ? lane + 64 * q : 0)];
+    for (int q = 0; q < 4; ++q) kv[q] = keys[(long)slot * kk + (lane + 64 * q < kk ? lane + 64 * q : 0)];
     const int myP_raw = s.P[b * s.kmax + (lane < k ? lane : 0)];
     const int fin0 = s.finished[b], j = s.j[b], max_len = s.max_len[b], L0 = s.L[b];
     const int imp_raw = s.imposed ? s.imposed[(long)step * s.imposed_stride + b] : 0;
@@ -1512,6 +1590,7 @@ __global__ __launch_bounds__(1024) void accept_embed_kernel(StateP s, unsigned l
         s.L[b] = Ln;
         L_s = Ln;
         s.finished[b] = fin;
+        if (fin) s.fin_step[b] = live_step;
         s.accepted[b] = khat;
         if (accepted_out) accepted_out[b] = khat;
         report_remaining(s, b, fin ? 0 : max_len - j - khat);
@@ -1524,13 +1603,16 @@ __global__ __launch_bounds__(1024) void accept_embed_kernel(StateP s, unsigned l
     }
   }
   __syncthreads();
-  for (int e = tid; e < k * k; e += 1024) keys[(long)b * k * k + e] = 0ull;
-  // rows b*k .. b*k + k - 1 of the next block
+  for (int e = tid; e < k * k; e += 1024) keys[(long)slot * k * k + e] = 0ull;
+  const int slot_next = slots ? slot_s[1] : b;
+  if (slot_next < 0) return;
+  if (slots && tid == 0) { s.slot_L[slot_next] = L_s; s.slot_row[slot_next] = b * s.cache_rows + L_s; }
+  // rows slot_next * k .. + k - 1 of the next block
   const int i = lane & 15, ic = i < k ? i : k - 1;
   int t = tok_s[ic];
   t = t < 0 ? 0 : (t >= V ? V - 1 : t);
   const int position = L_s + ic;
-  const int row = b * k + ic;
+  const int row = slot_next * k + ic;
   const int ksteps = d >> 5, ntiles = d >> 4;
   // srows == 16: statistics per 16-column tile (tiles wave, wave + 16, ..); otherwise per 64-column block: the wave's
   // four tiles are block `wave` and their sums are added up here
