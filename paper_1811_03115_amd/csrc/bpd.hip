@@ -268,8 +268,9 @@ void use_slots(bpd_ctx* ctx, int exact) {
 LiveP live_rows(const bpd_ctx* ctx, int M) { return ctx->live ? LiveP{ctx->live, M / ctx->Bs} : LiveP{nullptr, 0}; }
 // LayerNorm statistics ride along with the residual stream when the whole block is one MFMA row tile and every GEMM
 // that updates the stream is one the skinny kernel takes (it is the one that writes them: K = d_ff must fit it)
+bool lean_ok(const bpd_config& c, int M);
 bool stats_path(const bpd_ctx* ctx, int M) {
-  return ctx->cfg.dtype == BPD_BF16 && M <= 16 && ctx->cfg.d_model <= 1024 && ctx->cfg.d_ff <= 4096;
+  return !lean_ok(ctx->cfg, M) && ctx->cfg.dtype == BPD_BF16 && M <= 16 && ctx->cfg.d_model <= 1024 && ctx->cfg.d_ff <= 4096;
 }
 
 // ---- ldsx path: many rows ---------------------------------------------------------------
@@ -510,6 +511,30 @@ Epi split(float* Qf, void* Ka, void* Va, int dsplit, int chunk0, int rows_per_se
   e.rows_per_seq = rows_per_seq; e.cap = cap; e.base = base;
   return e;
 }
+// Where a block's keys and values go: `rows` cache rows per sequence, R new ones for each slot at base (null: from the first)
+Epi kv_split(const bpd_ctx* ctx, float* Qf, void* Ka, void* Va, int chunk0, int R, int rows, const int* lens, const int* seq) {
+  const bool grouped = kv_grouped(ctx->cfg);
+  Epi e = split(Qf, Ka, Va, ctx->cfg.d_model, chunk0, R, seq && !grouped ? 0 : rows, seq && !grouped ? ctx->lay.slot_row : lens);
+  if (grouped) { e.capg = (rows + 31) / 32; e.seq = seq; }
+  return e;
+}
+
+template <int D>
+void launch_ln_row(bpd_ctx* ctx, float* x, LnW w, int M, void* ya, float* yf, int nsl, const float* bias) {
+#define BPD_LN(NSL) hipLaunchKernelGGL((ln_row_kernel<D, NSL>), dim3(M), dim3(ln_row_threads(D)), 0, ctx->stream, x, w.g, w.b, M, ctx->cfg.ln_eps, \
+                                       (bf16_t*)ya, yf, (const float*)ctx->lay.kpart, bias)
+  switch (nsl) {
+    case 0: BPD_LN(0); break;
+    case 2: BPD_LN(2); break;
+    case 3: BPD_LN(3); break;
+    case 4: BPD_LN(4); break;
+    case 8: BPD_LN(8); break;
+    default: BPD_LN(16); break;
+  }
+#undef BPD_LN
+}
+// Widths that the kernels of bpd_row_gemm.h are built for
+bool lean_width(int d) { return d == 128 || d == 256 || d == 512 || d == 768 || d == 1024; }
 
 void layernorm(bpd_ctx* ctx, float* x, LnW w, int M, void* ya, float* yf) {
   const int d = ctx->cfg.d_model;
@@ -517,6 +542,16 @@ void layernorm(bpd_ctx* ctx, float* x, LnW w, int M, void* ya, float* yf) {
   int nsl = 0;
   const float* bias = nullptr;
   if (ctx->pend_slices && ctx->pend_x == x) { nsl = ctx->pend_slices; bias = ctx->pend_bias; ctx->pend_slices = 0; }
+  if (ctx->cfg.dtype == BPD_BF16 && lean_width(d) && (nsl == 0 || nsl == 2 || nsl == 3 || nsl == 4 || nsl == 8 || nsl == 16)) {
+    switch (d) {
+      case 128: launch_ln_row<128>(ctx, x, w, M, ya, yf, nsl, bias); break;
+      case 256: launch_ln_row<256>(ctx, x, w, M, ya, yf, nsl, bias); break;
+      case 512: launch_ln_row<512>(ctx, x, w, M, ya, yf, nsl, bias); break;
+      case 768: launch_ln_row<768>(ctx, x, w, M, ya, yf, nsl, bias); break;
+      default: launch_ln_row<1024>(ctx, x, w, M, ya, yf, nsl, bias); break;
+    }
+    return;
+  }
 #define BPD_LN(ACT_, V_) hipLaunchKernelGGL((layernorm_kernel<ACT_, V_>), grid, dim3(256), 0, ctx->stream, x, w.g, w.b, M, d, \
                                             ctx->cfg.ln_eps, (ACT_*)ya, yf, (const float*)ctx->lay.kpart, nsl, bias)
   if (ctx->cfg.dtype == BPD_BF16) {
@@ -553,10 +588,11 @@ bool attention_qproj_ok(const bpd_ctx* ctx, int B, int R) {
 void attention(bpd_ctx* ctx, const float* Q, const void* Kc, const void* Vc, void* out, int cap,
                int B, int R, const int* limit, int causal, const int* seq, const QProjP* qproj = nullptr) {
   const long kv_seq_stride = (long)cap * ctx->cfg.d_model;
+  const int capg = (cap + 31) / 32;
   const bpd_config& c = ctx->cfg;
   const int dh = c.d_model / c.n_heads;
   AttnP p{};
-  p.Q = Q; p.Kc = Kc; p.Vc = Vc; p.out = out; p.kv_seq_stride = kv_seq_stride; p.cap = cap; p.d = c.d_model; p.R = R;
+  p.Q = Q; p.Kc = Kc; p.Vc = Vc; p.out = out; p.kv_seq_stride = kv_seq_stride; p.cap = cap; p.capg = capg; p.d = c.d_model; p.R = R;
   p.limit = limit; p.causal = causal; p.seq = seq; p.scale = 1.0f / sqrtf((float)dh);
   const bool local = causal && ctx->local_q > 0;
   p.local_q = local ? ctx->local_q : 0; p.local_m = local ? ctx->local_m : 0;
@@ -572,8 +608,8 @@ void attention(bpd_ctx* ctx, const float* Q, const void* Kc, const void* Vc, voi
       // (a split launch walks a long cache, where nearly all fetched rows are in use: measured slower with the extra round trip)
       // (local attention: where the keys start depends on the length, so it is always read first)
       const bool limf = (nsplit == 1 && wgs >= ATTN_LIMF_MIN_WGS) || local;
-#define BPD_ATTN(...) { if (seq) hipLaunchKernelGGL((attention_mfma_slots_kernel<__VA_ARGS__>), grid, dim3(256), 0, ctx->stream, p, qp_); \
-                        else hipLaunchKernelGGL((attention_mfma_kernel<__VA_ARGS__>), grid, dim3(256), 0, ctx->stream, p, qp_); }
+#define BPD_ATTN(A_, B_, QU_) { if (seq) hipLaunchKernelGGL((attention_mfma_slots_kernel<A_, B_, QU_>), grid, dim3(64 * attn_waves(QU_)), 0, ctx->stream, p, qp_); \
+                                else hipLaunchKernelGGL((attention_mfma_kernel<A_, B_, QU_>), grid, dim3(64 * attn_waves(QU_)), 0, ctx->stream, p, qp_); }
       const QProjP qp_ = qproj ? *qproj : QProjP{};
       if (qproj) {                               // queries projected in the kernel (attention_qproj_ok() holds)
         switch (c.d_model / 128) {
@@ -773,6 +809,91 @@ void refresh_folded_weights(bpd_ctx* ctx) {
   ctx->fold_ready = true;
 }
 
+// ------------------------------------------------------------------------------- blocks of few rows (bpd_row_gemm.h)
+constexpr int LEAN_M_MAX = 128;
+// The residual GEMM of K = d_ff runs as one kernel up to this K, beyond in K slices of 1024 that the next LayerNorm adds up
+// (4096 x 1024 at 10 rows: 5.5 us whole, 3.4 us in slices, and the LayerNorm kernel with them 2.0 us, which takes the LayerNorm
+// out of the next GEMM: 4.2 -> 3.05 us.  2048 x 512: 3.3 us whole, and 2.1 + 1.9 - 0.8 us in slices).
+constexpr int LEAN_K_WHOLE = 2048;
+bool lean_ok(const bpd_config& c, int M) {
+  return c.dtype == BPD_BF16 && M <= LEAN_M_MAX && lean_width(c.d_model) &&
+         (c.d_ff == 512 || c.d_ff == 1024 || c.d_ff == 2048 || c.d_ff == 3072 || c.d_ff == 4096);
+}
+int lean_slices(const bpd_config& c) { return c.d_ff > LEAN_K_WHOLE ? c.d_ff / 1024 : 1; }
+// LayerNorm inside the GEMM that follows, or in a kernel of its own?  (with K = 1024 every column block of 64 KB of x costs: 24 rows
+// 5.05 us against 1.9 + 3.6, 40 rows 6.6 against 2.0 + 4.3; with K = 512 80 rows 3.3 against 1.9 + 2.5, 128 rows 4.4 against 1.9 + 2.9)
+bool lean_fuse(int d, int M) { return d <= 512 || M <= 32; }
+
+template <int WAVES, int U, bool LN, int EPI>
+void launch_row_gemm(const bpd_ctx* ctx, const RowGemmP& p, int slices) {
+  // the smallest tile that needs no more workgroups than there are CUs: a second round of workgroups costs more than the wider tile
+  auto wgs = [&](int mt, int nt) { return (long)((p.ntiles + nt - 1) / nt) * ((p.M + 16 * mt - 1) / (16 * mt)) * slices; };
+#define BPD_RG(MT_, NT_) hipLaunchKernelGGL((row_gemm_kernel<WAVES, U, MT_, NT_, LN, EPI>), dim3((p.ntiles + NT_ - 1) / NT_, (p.M + 16 * MT_ - 1) / (16 * MT_), slices), \
+                                            dim3(64 * WAVES), 0, ctx->stream, p)
+  if (wgs(1, 1) <= ctx->num_cus) BPD_RG(1, 1);
+  else if (wgs(1, 2) <= ctx->num_cus) BPD_RG(1, 2);
+  else if (LN || wgs(1, 4) <= ctx->num_cus) BPD_RG(1, 4);
+  else BPD_RG(2, 4);
+#undef BPD_RG
+}
+template <bool LN, int EPI>
+void row_gemm(const bpd_ctx* ctx, const RowGemmP& p, int K) {
+  switch (K) {
+    case 128: launch_row_gemm<4, 1, LN, EPI>(ctx, p, 1); break;
+    case 256: launch_row_gemm<4, 2, LN, EPI>(ctx, p, 1); break;
+    case 512: launch_row_gemm<4, 4, LN, EPI>(ctx, p, 1); break;
+    case 768: launch_row_gemm<8, 3, LN, EPI>(ctx, p, 1); break;
+    case 1024: launch_row_gemm<8, 4, LN, EPI>(ctx, p, 1); break;
+    default: if constexpr (EPI == RG_RES) launch_row_gemm<8, 8, LN, EPI>(ctx, p, 1); break;      // 2048
+  }
+}
+// Y = relu(LayerNorm(x) W + b), or queries / K / V from LayerNorm(x) W.  xn: room for the normalised rows
+template <int EPI>
+void lean_ln_gemm(bpd_ctx* ctx, float* x, LnW w, void* xn, RowGemmP p) {
+  const int d = ctx->cfg.d_model;
+  p.eps = ctx->cfg.ln_eps; p.ldx = d;
+  if (ctx->pend_slices == 0 && lean_fuse(d, p.M)) {
+    p.X = x; p.g = w.g; p.b = w.b;
+    row_gemm<true, EPI>(ctx, p, d);
+  } else {
+    layernorm(ctx, x, w, p.M, xn, nullptr);
+    p.X = xn;
+    row_gemm<false, EPI>(ctx, p, d);
+  }
+}
+RowGemmP rg(const void* X, int ldx, const void* W, int M, int N) {
+  RowGemmP p{};
+  p.X = X; p.ldx = ldx; p.W = W; p.M = M; p.ntiles = N / 16;
+  return p;
+}
+RowGemmP rg_kv(const bpd_ctx* ctx, const void* X, const void* W, int M, int N, const Epi& e) {
+  RowGemmP p = rg(X, ctx->cfg.d_model, W, M, N);
+  p.Y = e.Qf; p.chunk0 = e.chunk0; p.R = e.rows_per_seq; p.heads = ctx->cfg.n_heads; p.capg = e.capg; p.cap = e.cap;
+  p.Kc = (bf16_t*)e.Ka; p.Vc = (bf16_t*)e.Va; p.base = e.base; p.seq = e.seq;
+  return p;
+}
+// x += X W + bias; K slices of a long K are left for the LayerNorm of x that follows (ctx->pend_*)
+void lean_residual(bpd_ctx* ctx, const void* X, int K, const void* W, const float* bias, int M, float* x) {
+  const int d = ctx->cfg.d_model;
+  RowGemmP p = rg(X, K, W, M, d);
+  p.ldy = d; p.bias = bias;
+  if (K > LEAN_K_WHOLE) {
+    p.Y = ctx->lay.kpart; p.ksteps = K / 32;
+    launch_row_gemm<8, 4, false, RG_PART>(ctx, p, K / 1024);
+    ctx->pend_slices = K / 1024; ctx->pend_bias = bias ? bias : ctx->lay.zeros; ctx->pend_x = x;
+  } else {
+    p.Y = x;
+    row_gemm<false, RG_RES>(ctx, p, K);
+  }
+}
+void lean_ffn(bpd_ctx* ctx, float* x, LnW ln, void* xn, const void* w1, const float* b1, void* hidden, const void* w2, const float* b2, int M) {
+  const int F = ctx->cfg.d_ff;
+  RowGemmP p = rg(nullptr, 0, w1, M, F);
+  p.bias = b1; p.Y = hidden; p.ldy = F;
+  lean_ln_gemm<RG_RELU>(ctx, x, ln, xn, p);
+  lean_residual(ctx, hidden, F, w2, b2, M, x);
+}
+
 // One invocation of the combined model on R new rows per sequence (R = 1 for the first call
 // on the empty prefix, R = k afterwards) with the first k heads; fills keys[B*R*k].
 int forward(bpd_ctx* ctx, int R, int k, int zero_input, float* logits) {
@@ -782,13 +903,14 @@ int forward(bpd_ctx* ctx, int R, int k, int zero_input, float* logits) {
   const int slots = c.max_out_len + c.k_max + 1;
   const size_t as = act_size(c);
   const long nk = (long)M * k;
-  const bool sp = stats_path(ctx, M);
+  const bool lean = lean_ok(c, M), sp = stats_path(ctx, M);
+  const size_t self_layer = (size_t)c.max_batch * kv_rows(c, slots) * d * as, src_layer = (size_t)c.max_batch * kv_rows(c, c.max_src_len) * d * as;
   const int* seq = ctx->seq;
   const int *base = seq ? L.slot_L : L.L, *srcs = seq ? L.slot_src : L.src_len;
   // residual update x += ...; on the statistics path the kernel also leaves LayerNorm partial sums
   // with more rows the LDS-staged kernel leaves them per tile in L.stats_big for the LayerNorm-fused GEMM that follows
   // (up to 128 rows: with more, every column block repeating the normalisation of its rows costs more than the kernel saved)
-  const bool bigs = !sp && c.dtype == BPD_BF16 && M > 16 && M <= LDSX_LN_M_MAX && d % 64 == 0 && d <= 1024;
+  const bool bigs = !sp && !lean && c.dtype == BPD_BF16 && M > 16 && M <= LDSX_LN_M_MAX && d % 64 == 0 && d <= 1024;
   // more than 128 rows: the GEMMs that update x also leave its bf16 copy in L.xn, and the LayerNorm + GEMM that follows
   // runs as one GEMM on folded weights (unless that update is split over K: its slices are summed by a LayerNorm kernel)
   const bool folds = !sp && !bigs && c.dtype == BPD_BF16 && M > LDSX_LN_M_MAX && L.dec[0].f_qkv.W != nullptr;
@@ -808,21 +930,38 @@ int forward(bpd_ctx* ctx, int R, int k, int zero_input, float* logits) {
     ctx->x_ready_k = 0;
     xs = have_x && !sp;
     if (!have_x) embed(ctx, L.P, c.k_max, base, R, M, L.pos_tgt, L.x, zero_input, L.keys, (int)nk, seq);
-    const bool stack = sp && stack_usable(ctx, B, R);
+    const bool stack = M <= 16 && (lean || sp) && stack_usable(ctx, B, R);
     if (stack) launch_stack(ctx, R);
     for (int l = 0; l < (stack ? 0 : c.n_dec_layers); ++l) {
       DecL& w = L.dec[l];
-      char* Kl = (char*)L.selfK + (size_t)l * c.max_batch * slots * d * as;
-      char* Vl = (char*)L.selfV + (size_t)l * c.max_batch * slots * d * as;
-      char* cK = (char*)L.crossK + (size_t)l * c.max_batch * c.max_src_len * d * as;
-      char* cV = (char*)L.crossV + (size_t)l * c.max_batch * c.max_src_len * d * as;
+      char* Kl = (char*)L.selfK + self_layer * l;
+      char* Vl = (char*)L.selfV + self_layer * l;
+      char* cK = (char*)L.crossK + src_layer * l;
+      char* cV = (char*)L.crossV + src_layer * l;
+      const Epi kv = kv_split(ctx, L.q, Kl, Vl, 0, R, slots, base, seq);
+      const bool qproj = attention_qproj_ok(ctx, B, R);
+      if (lean) {
+        lean_ln_gemm<RG_QKV>(ctx, L.x, w.ln1, L.xn, rg_kv(ctx, nullptr, w.wqkv, M, 3 * d, kv));
+        attention(ctx, L.q, Kl, Vl, L.attn, slots, B, R, base, 1, seq);
+        lean_residual(ctx, L.attn, d, w.wo, nullptr, M, L.x);
+        if (qproj) {
+          const QProjP qp{L.x, w.ln2.g, w.ln2.b, w.cq, c.ln_eps};
+          attention(ctx, nullptr, cK, cV, L.attn, c.max_src_len, B, R, srcs, 0, seq, &qp);
+        } else {
+          lean_ln_gemm<RG_QKV>(ctx, L.x, w.ln2, L.xn, rg_kv(ctx, nullptr, w.cq, M, d, kv));
+          attention(ctx, L.q, cK, cV, L.attn, c.max_src_len, B, R, srcs, 0, seq);
+        }
+        lean_residual(ctx, L.attn, d, w.co, nullptr, M, L.x);
+        lean_ffn(ctx, L.x, w.ln3, L.xn, w.w1, w.b1, L.ffh, w.w2, w.b2, M);
+        continue;
+      }
       // self-attention sublayer: K/V of the block rows go straight into the cache at L_b + i'
-      gemm_ln(ctx, L.x, w.ln1, L.xn, nullptr, gp(L.xn, d, w.wqkv, 3 * d, M, 3 * d, d), split(L.q, Kl, Vl, d, 0, R, seq ? 0 : slots, seq ? L.slot_row : L.L), sp, xs, folds ? &w.f_qkv : nullptr);
+      gemm_ln(ctx, L.x, w.ln1, L.xn, nullptr, gp(L.xn, d, w.wqkv, 3 * d, M, 3 * d, d), kv, sp, xs, folds ? &w.f_qkv : nullptr);
       attention(ctx, L.q, Kl, Vl, L.attn, slots, B, R, base, 1, seq);
       xs = gemm(ctx, gp(L.attn, d, w.wo, d, M, d, d), residual(nullptr, d));
       // cross-attention sublayer over the encoder memory
-      if ((sp || xs) && attention_qproj_ok(ctx, B, R)) {
-        const QProjP qp{L.x, w.ln2.g, w.ln2.b, sp ? L.stats_ln : L.stats_big, sp ? 16 : M, w.cq, c.ln_eps};
+      if (qproj) {
+        const QProjP qp{L.x, w.ln2.g, w.ln2.b, w.cq, c.ln_eps};
         attention(ctx, nullptr, cK, cV, L.attn, c.max_src_len, B, R, srcs, 0, seq, &qp);
       } else {
         gemm_ln(ctx, L.x, w.ln2, L.xn, nullptr, gp(L.xn, d, w.cq, d, M, d, d), plain(nullptr, 0, nullptr, 0, L.q, d, nullptr, 0), sp, xs, folds ? &w.f_cq : nullptr);
@@ -840,7 +979,10 @@ int forward(bpd_ctx* ctx, int R, int k, int zero_input, float* logits) {
   // for the residual), then one output layer per head
   {
     PhaseTimer t(ctx, BPD_PHASE_HEAD_HIDDEN);
-    gemm_ln(ctx, L.x, L.dec_lnf, L.hn, L.h, gp(L.hn, d, L.hw1, c.k_max * F, M, k * F, d),
+    if (lean) {
+      layernorm(ctx, L.x, L.dec_lnf, M, L.hn, L.h);
+      gemm(ctx, gp(L.hn, d, L.hw1, c.k_max * F, M, k * F, d), plain(L.hb1, 1, nullptr, 0, nullptr, 0, L.H, k * F));
+    } else gemm_ln(ctx, L.x, L.dec_lnf, L.hn, L.h, gp(L.hn, d, L.hw1, c.k_max * F, M, k * F, d),
             plain(L.hb1, 1, nullptr, 0, nullptr, 0, L.H, k * F), sp);
   }
   {
@@ -899,17 +1041,26 @@ int encoder(bpd_ctx* ctx) {
   const int B = ctx->B, S = ctx->S, d = c.d_model, F = c.d_ff, M = B * S;
   const size_t as = act_size(c);
   embed(ctx, L.src_ids, S, nullptr, S, M, L.pos_src, L.xe, 0);
-  // 17 .. 128 source rows: the residual GEMMs leave LayerNorm statistics for the LayerNorm-fused GEMM that follows
-  const bool bigs = c.dtype == BPD_BF16 && M > 16 && M <= LDSX_LN_M_MAX && d % 64 == 0 && d <= 1024;
+  // 17 .. 128 source rows of a width that bpd_row_gemm.h is not built for: the residual GEMMs leave LayerNorm statistics for the LayerNorm-fused GEMM that follows
+  const bool bigs = !lean_ok(c, M) && c.dtype == BPD_BF16 && M > 16 && M <= LDSX_LN_M_MAX && d % 64 == 0 && d <= 1024;
   auto residual = [&](const float* bias) {
     Epi e = plain(bias, 0, L.xe, d, L.xe, d, nullptr, 0);
     if (bigs) e.stats_out = L.stats_big;
     return e;
   };
   bool xs = false;      // L.stats_big describes the current L.xe
+  const bool lean = lean_ok(c, M);
   for (int l = 0; l < c.n_enc_layers; ++l) {
     EncL& w = L.enc[l];
-    gemm_ln(ctx, L.xe, w.ln1, L.xen, nullptr, gp(L.xen, d, w.wqkv, 3 * d, M, 3 * d, d), split(L.qe, L.ke, L.ve, d, 0, S, S, nullptr), false, xs);
+    const Epi kv = kv_split(ctx, L.qe, L.ke, L.ve, 0, S, S, nullptr, nullptr);
+    if (lean) {
+      lean_ln_gemm<RG_QKV>(ctx, L.xe, w.ln1, L.xen, rg_kv(ctx, nullptr, w.wqkv, M, 3 * d, kv));
+      attention(ctx, L.qe, L.ke, L.ve, L.attne, S, B, S, L.src_len, 0, nullptr);
+      lean_residual(ctx, L.attne, d, w.wo, nullptr, M, L.xe);
+      lean_ffn(ctx, L.xe, w.ln2, L.xen, w.w1, w.b1, L.ffhe, w.w2, w.b2, M);
+      continue;
+    }
+    gemm_ln(ctx, L.xe, w.ln1, L.xen, nullptr, gp(L.xen, d, w.wqkv, 3 * d, M, 3 * d, d), kv, false, xs);
     attention(ctx, L.qe, L.ke, L.ve, L.attne, S, B, S, L.src_len, 0, nullptr);
     xs = gemm(ctx, gp(L.attne, d, w.wo, d, M, d, d), residual(nullptr));
     gemm_ln(ctx, L.xe, w.ln2, L.xen, nullptr, gp(L.xen, d, w.w1, F, M, F, d), plain(w.b1, 1, nullptr, 0, nullptr, 0, L.ffhe, F), false, xs);
@@ -917,9 +1068,10 @@ int encoder(bpd_ctx* ctx) {
   }
   layernorm(ctx, L.xe, L.enc_lnf, M, L.mem, nullptr);
   for (int l = 0; l < c.n_dec_layers; ++l) {
-    char* cK = (char*)L.crossK + (size_t)l * c.max_batch * c.max_src_len * d * as;
-    char* cV = (char*)L.crossV + (size_t)l * c.max_batch * c.max_src_len * d * as;
-    gemm(ctx, gp(L.mem, d, L.dec[l].ckv, 2 * d, M, 2 * d, d), split(nullptr, cK, cV, d, 1, S, c.max_src_len, nullptr));
+    const size_t at = (size_t)l * c.max_batch * kv_rows(c, c.max_src_len) * d * as;
+    const Epi kv = kv_split(ctx, nullptr, (char*)L.crossK + at, (char*)L.crossV + at, 1, S, c.max_src_len, nullptr, nullptr);
+    if (lean) row_gemm<false, RG_QKV>(ctx, rg_kv(ctx, L.mem, L.dec[l].ckv, M, 2 * d, kv), d);
+    else gemm(ctx, gp(L.mem, d, L.dec[l].ckv, 2 * d, M, 2 * d, d), kv);
   }
   LAUNCHCHK();
   return BPD_OK;
@@ -1043,10 +1195,10 @@ int bpd_create(const bpd_config* cfg, void* workspace, size_t workspace_bytes, v
         q.wqkv = w.wqkv; q.wo = w.wo; q.cq = w.cq; q.co = w.co; q.w1 = w.w1; q.w2 = w.w2;
         q.ln1g = w.ln1.g; q.ln1b = w.ln1.b; q.ln2g = w.ln2.g; q.ln2b = w.ln2.b; q.ln3g = w.ln3.g; q.ln3b = w.ln3.b;
         q.b1 = w.b1; q.b2 = w.b2;
-        q.selfK = (char*)L.selfK + (size_t)l * c.max_batch * slots * d * as;
-        q.selfV = (char*)L.selfV + (size_t)l * c.max_batch * slots * d * as;
-        q.crossK = (char*)L.crossK + (size_t)l * c.max_batch * c.max_src_len * d * as;
-        q.crossV = (char*)L.crossV + (size_t)l * c.max_batch * c.max_src_len * d * as;
+        q.selfK = (char*)L.selfK + (size_t)l * c.max_batch * kv_rows(c, slots) * d * as;
+        q.selfV = (char*)L.selfV + (size_t)l * c.max_batch * kv_rows(c, slots) * d * as;
+        q.crossK = (char*)L.crossK + (size_t)l * c.max_batch * kv_rows(c, c.max_src_len) * d * as;
+        q.crossV = (char*)L.crossV + (size_t)l * c.max_batch * kv_rows(c, c.max_src_len) * d * as;
       }
       (void)hipMemcpyAsync(ctx->lay.stack_layers, table.data(), sizeof(StackLayerP) * STACK_MAX_LAYERS, hipMemcpyHostToDevice, ctx->stream);
     }
@@ -1321,7 +1473,8 @@ int bpd_step_static(bpd_ctx* ctx, int k, const int32_t* imposed_accept, int32_t*
     if (ns > 1) attn_b = std::max(attn_b, up(ns * wgs * 16 * (d / c.n_heads + 2) * 4));
   }
   size_t slices = 1;
-  if (c.dtype == BPD_BF16 && M > 16)
+  if (lean_ok(c, (int)M)) slices = lean_slices(c);
+  else if (c.dtype == BPD_BF16 && M > 16)
     for (int K : {c.d_model, c.d_ff}) {
       const int ns = residual_k_slices(ctx, gp(nullptr, K, nullptr, c.d_model, (int)M, c.d_model, K));
       if ((size_t)ns > slices) slices = ns;

@@ -1,0 +1,356 @@
+// Attention of 64-wide bf16 heads on the matrix cores, over keys and values kept in operand order.  Included by
+// bpd_kernels.h (after AttnP).
+#pragma once
+
+// K and V of one sequence and head, 64-wide heads in bf16: `capg` groups of 32 keys, 4 KiB of each per group, as the
+// operands of v_mfma_f32_16x16x32_bf16 that the attention feeds them to, so that every fragment is one coalesced 1 KiB
+// load and nothing passes through LDS:
+//   K group: [key tile t][dimensions 32 s .. + 31][lane][8]: lane 16 q' + row holds dimensions 32 s + 8 q' .. + 7 of the key
+//            8 (row / 4) + 4 t + row % 4 of the group: the scores that a lane of the product holds are then those of
+//            keys 8 (lane / 16) .. + 7 (tiles 0 and 1 in turn), which is what the second product takes from it.
+//   V group: [dimensions 16 t .. + 15][lane][8]: lane 16 q + c holds dimension 16 t + c of keys 8 q .. + 7.
+constexpr int KV_GROUP = 2048;                   // elements of a group of 32 keys x 64 dimensions
+__device__ __forceinline__ unsigned k_frag_at(int key, int c) {        // c % 4 == 0: four dimensions lie side by side
+  return (unsigned)(key >> 5) * KV_GROUP + ((key >> 2) & 1) * 1024 + (c >> 5) * 512 + (((c >> 3) & 3) * 16 + ((key >> 3) & 3) * 4 + (key & 3)) * 8 + (c & 7);
+}
+__device__ __forceinline__ unsigned v_frag_at(int key, int c) {        // dimension c + 1 lies 8 elements on
+  return (unsigned)(key >> 5) * KV_GROUP + (c >> 4) * 512 + (((key >> 3) & 3) * 16 + (c & 15)) * 8 + (key & 7);
+}
+// Columns col .. col + 3 (col % 4 == 0) of key row `key` of sequence sb
+__device__ __forceinline__ void kv_frag_store(bf16_t* cache, bool is_v, int sb, int heads, int capg, int key, int col, unsigned lo, unsigned hi) {
+  bf16_t* dst = cache + ((size_t)sb * heads + (col >> 6)) * capg * KV_GROUP;
+  if (!is_v) {
+    *(u32x2*)(dst + k_frag_at(key, col & 63)) = u32x2{lo, hi};
+  } else {
+    bf16_t* v = dst + v_frag_at(key, col & 63);
+    v[0] = (bf16_t)lo; v[8] = (bf16_t)(lo >> 16); v[16] = (bf16_t)hi; v[24] = (bf16_t)(hi >> 16);
+  }
+}
+
+// fp32 operands (queries, probabilities) go to the matrix cores as a bf16 pair hi + lo, which keeps them to ~2^-17.
+__device__ __forceinline__ void split_bf16x8(const float (&v)[8], bf16x8& hi, bf16x8& lo) {
+  unsigned h[4], l[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    h[j] = cvt_pk_bf16(v[2 * j], v[2 * j + 1]);
+    l[j] = cvt_pk_bf16(v[2 * j] - __uint_as_float(h[j] << 16), v[2 * j + 1] - __uint_as_float(h[j] & 0xFFFF0000u));
+  }
+  hi = __builtin_bit_cast(bf16x8, (u32x4{h[0], h[1], h[2], h[3]}));
+  lo = __builtin_bit_cast(bf16x8, (u32x4{l[0], l[1], l[2], l[3]}));
+}
+
+// QU > 0 (at most 16 rows per sequence, d = 128 * QU): the queries are projected inside the kernel,
+//   Q = LayerNorm(x) Wq[:, 64 h .. 64 h + 63]   (x: fp32 residual stream),
+// instead of being read from p.Q: the waves split the contraction, their partial sums meet in LDS, and the K/V loads of
+// the first chunk are already in flight meanwhile.  Saves the projection's kernel and its round trip.
+struct QProjP {
+  const float* x;       // [M][d] residual stream
+  const float* g;       // LayerNorm gain, bias
+  const float* b;
+  const void* W;        // packed [d/16 column tiles][d/32 k-steps][64 lanes][8]
+  float eps;
+};
+
+// LDS of one attention workgroup: the kernel below declares it; a caller that runs the body from inside another kernel
+// carves it out of its own LDS.
+template <int NW>
+struct AttnLdsT {
+  static constexpr int RT = 16, DH = 64;
+  f32x4 (*o_s)[4][64];        // [NW][4][64]  per wave and output tile: un-normalised out^T
+  float (*m_s)[RT];           // [NW][RT]     per wave: running maximum per query row
+  float (*l_s)[RT];           // [NW][RT]     ... and sum
+  float* q_s;                 // QU > 0: [RT * (DH + 4)] projected queries
+  float* gb_s;                // QU > 0: per wave, gain and bias of its columns; and the row sums of x
+  float2* st_s;
+  static constexpr size_t OS_BYTES = (size_t)NW * 4 * 64 * 16, ML_BYTES = (size_t)NW * RT * 4;
+  static constexpr size_t BYTES = OS_BYTES + 2 * ML_BYTES;        // QU == 0
+  __device__ static AttnLdsT carve(unsigned char* base) {         // (16-byte aligned base), QU == 0 layout
+    AttnLdsT s;
+    s.o_s = (f32x4 (*)[4][64])base;
+    s.m_s = (float (*)[RT])(base + OS_BYTES);
+    s.l_s = (float (*)[RT])(base + OS_BYTES + ML_BYTES);
+    s.q_s = nullptr; s.gb_s = nullptr; s.st_s = nullptr;
+    return s;
+  }
+};
+typedef AttnLdsT<4> AttnLds;
+
+// One (head h, sequence b (in the K/V buffer: sb), z = row tile * nsplit + split) item of the attention, run by NW whole
+// waves (tid 0 .. 64 NW - 1) that share `sm`; nheads / nz: the extents the partial-result layout is indexed with.  Every
+// __syncthreads() inside is reached by all of them; a caller whose workgroup has more waves makes those arrive at as many
+// barriers (one with QU == 0, four with QU > 0).
+// The waves split the keys: of every chunk of 256 keys wave w takes the groups w, w + NW, .. of 32 keys (interleaved, so
+// that short caches keep all waves busy) and keeps its own running maximum, sum and weighted values in registers; the
+// waves' results meet once, in LDS, at the end.  Per group
+//   scores^T = K Q^T     keys are the 16-wide "feature" side of the MFMA, the <= 16 query rows the other
+//   softmax              maximum and sum in the lane, then across the 4 lanes of a row; the probabilities stay in
+//                        registers: as they lie they are the second MFMA operand of a contraction over the 32 keys
+//   out^T += V^T P^T     64 head dimensions = 4 output tiles
+// What bounds it at the step's sizes is the chain of latencies (launch, one trip for K, V and Q together, two products, the
+// waves' meeting).  With K and V as rows of d (V staged and transposed through LDS, 64 two-byte reads per wave and 64 keys)
+// a decoder layer's self-attention took 5.6 us at 8 rows, 8 heads, 30 keys.
+// KVNT: K and V are fetched with non-temporal loads (a cache too large for the last-level cache is a stream that should
+// not evict the weights).
+// LIMF: the sequence's length is fetched first and only groups that hold keys are fetched: one more dependent round trip
+// (many sequences: the traffic is what counts; local attention: where the keys start depends on it).
+template <int NW, bool KVNT, bool LIMF, int QU>
+__device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP& qp, const AttnLdsT<NW>& sm, int h, int b, int sb, int z,
+                                                    int nheads, int nz, int tid) {
+  constexpr int RT = 16, DH = 64, G = 8 / NW;
+  const int split = z % p.nsplit, tile = z / p.nsplit, r0 = tile * RT;
+  const int nrows = min(RT, p.R - r0);
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lq = lane >> 4;
+  const size_t head_at = ((size_t)sb * nheads + h) * p.capg * KV_GROUP;
+  int glim = p.capg;                             // groups that may be fetched
+  int gbeg = 0;                                  // group of the first key (local attention: LIMF only)
+  if (LIMF) {
+    int l0 = p.limit[b];
+    l0 = l0 < 0 ? 0 : l0;
+    const int g0 = ((p.causal ? l0 + r0 + nrows : l0) + 31) >> 5;
+    glim = g0 < glim ? g0 : glim;
+    gbeg = attn_first_key(p, l0 + r0) >> 5;
+  }
+  const int first = gbeg + split * 8, hop = p.nsplit * 8;
+  const rsrc_t kr = rsrc_of((const bf16_t*)p.Kc + head_at, (unsigned)glim * (KV_GROUP * 2));
+  const rsrc_t vr = rsrc_of((const bf16_t*)p.Vc + head_at, (unsigned)glim * (KV_GROUP * 2));
+  u32x4 kf[G][4], vf[G][4];                      // K: [tile][half of the dimensions], V: [16 dimensions]
+#define BPD_LOAD_KV(c)                                                                          \
+  _Pragma("unroll") for (int gg = 0; gg < G; ++gg) {                                            \
+    const unsigned at_ = (unsigned)((c) + wave + NW * gg) * (KV_GROUP * 2);                     \
+    _Pragma("unroll") for (int x = 0; x < 4; ++x)                                               \
+      kf[gg][x] = __builtin_amdgcn_raw_buffer_load_b128(kr, lane * 16 + x * 1024, at_, KVNT ? 2 : 0); \
+    _Pragma("unroll") for (int x = 0; x < 4; ++x)                                               \
+      vf[gg][x] = __builtin_amdgcn_raw_buffer_load_b128(vr, lane * 16 + x * 1024, at_, KVNT ? 2 : 0); \
+  }
+  // queries: row lr (zeros beyond the last), head dimensions 32s + 8*lq .. +8, scaled, as bf16 hi + lo
+  bf16x8 qhi[2], qlo[2];
+  int lim;
+  if constexpr (QU > 0) {
+    static_assert(NW == 8, "k-steps over eight waves");
+    constexpr int K = 128 * QU, KSTEPS = K / 32, U = (KSTEPS + NW - 1) / NW;
+    const bool mine = wave * U < KSTEPS;         // (K = 128: four waves have k-steps)
+    const int ks0 = mine ? wave * U : 0;
+    // every global load of the kernel is issued before the first wait
+    u32x4 wf[4][U], xv[U][2];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int i = 0; i < U; ++i) wf[j][i] = *(const u32x4*)((const char*)qp.W + ((size_t)(4 * h + j) * KSTEPS + ks0 + i) * 1024 + lane * 16);
+    {
+      const rsrc_t xr = rsrc_of(qp.x + (size_t)b * p.R * K, mine ? (unsigned)p.R * K * 4 : 0);
+      const unsigned off = (lr * K + ks0 * 32 + lq * 8) * 4;
+#pragma unroll
+      for (int i = 0; i < U; ++i) { xv[i][0] = buf_load16(xr, off + i * 128, 0); xv[i][1] = buf_load16(xr, off + i * 128 + 16, 0); }
+    }
+    const f32x4 gbv = *(const f32x4*)((lane % (U * 16) < U * 8 ? qp.g : qp.b) + ks0 * 32 + (lane % (U * 8)) * 4);
+    BPD_LOAD_KV(first)
+    lim = p.limit[b];
+    __builtin_amdgcn_sched_barrier(0);
+    float* gw = sm.gb_s + wave * (U * 64);
+    if (lane < U * 16) *(f32x4*)(gw + lane * 4) = gbv;
+    {
+      float s = 0.f, q = 0.f;
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+          const f32x4 v = __builtin_bit_cast(f32x4, xv[i][hh]);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) { s += v[r]; q = fmaf(v[r], v[r], q); }
+        }
+      s = sum_rows(s); q = sum_rows(q);
+      if (lq == 0) sm.st_s[wave * 16 + lr] = make_float2(s, q);
+    }
+    __syncthreads();
+    f32x4 qa[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) qa[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    {
+      float s = 0.f, q = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) { const float2 v = sm.st_s[w * 16 + lr]; s += v.x; q += v.y; }
+      float mu, rs;
+      row_moments(s, q, 1.f / K, qp.eps, mu, rs);
+      const float nmr = -mu * rs;
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        float y[8];
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+          const f32x4 v = __builtin_bit_cast(f32x4, xv[i][hh]);
+          const f32x4 g4 = *(const f32x4*)(gw + i * 32 + lq * 8 + 4 * hh), b4 = *(const f32x4*)(gw + U * 32 + i * 32 + lq * 8 + 4 * hh);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) y[4 * hh + r] = fmaf(fmaf(v[r], rs, nmr), g4[r], b4[r]);
+        }
+        u32x4 yb = u32x4{cvt_pk_bf16(y[0], y[1]), cvt_pk_bf16(y[2], y[3]), cvt_pk_bf16(y[4], y[5]), cvt_pk_bf16(y[6], y[7])};
+        if (U * NW != KSTEPS && !mine) yb = u32x4{0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          qa[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[j][i]), __builtin_bit_cast(bf16x8, yb), qa[j], 0, 0, 0);
+      }
+    }
+    f32x4* red = &sm.o_s[0][0][0];               // [wave][column tile][lane], before the final merge uses it
+#pragma unroll
+    for (int j = 0; j < 4; ++j) red[(wave * 4 + j) * 64 + lane] = qa[j];
+    __syncthreads();
+    if (wave < 4) {                              // wave w finishes column tile w: a lane holds row lr, columns 16w + 4lq ..
+      f32x4 sum = red[wave * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) sum += red[(w * 4 + wave) * 64 + lane];
+      *(f32x4*)&sm.q_s[lr * (DH + 4) + 16 * wave + 4 * lq] = sum * p.scale;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2) {
+      const f32x4 q0 = *(const f32x4*)&sm.q_s[lr * (DH + 4) + 32 * s2 + 8 * lq], q1 = *(const f32x4*)&sm.q_s[lr * (DH + 4) + 32 * s2 + 8 * lq + 4];
+      const float v[8] = {q0[0], q0[1], q0[2], q0[3], q1[0], q1[1], q1[2], q1[3]};
+      split_bf16x8(v, qhi[s2], qlo[s2]);
+    }
+  } else {
+    const rsrc_t qr = rsrc_of(p.Q + ((size_t)b * p.R + r0) * p.d, (unsigned)nrows * p.d * 4);
+    const unsigned off = (lr * p.d + h * DH + 8 * lq) * 4;
+    u32x4 qa[2][2];
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2) { qa[s2][0] = buf_load16(qr, off + s2 * 128, 0); qa[s2][1] = buf_load16(qr, off + s2 * 128 + 16, 0); }
+    BPD_LOAD_KV(first)
+    lim = p.limit[b];
+    __builtin_amdgcn_sched_barrier(0);            // every global load above is in flight before the first wait
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2) {
+      const f32x4 q0 = __builtin_bit_cast(f32x4, qa[s2][0]) * p.scale, q1 = __builtin_bit_cast(f32x4, qa[s2][1]) * p.scale;
+      const float v[8] = {q0[0], q0[1], q0[2], q0[3], q1[0], q1[1], q1[2], q1[3]};
+      split_bf16x8(v, qhi[s2], qlo[s2]);
+    }
+  }
+  lim = lim < 0 ? 0 : lim;
+  int nkeys = p.causal ? lim + r0 + nrows : lim;
+  nkeys = nkeys < p.capg * 32 ? nkeys : p.capg * 32;
+  const int ngr = (nkeys + 31) >> 5;
+  const int nvis = lr < nrows ? (p.causal ? lim + r0 + lr + 1 : lim) : 0;     // keys row lr may see: nlo .. nvis - 1
+  const int nlo = LIMF ? attn_first_key(p, lim + r0 + lr) : 0;
+  float m_run = -INFINITY, l_run = 0.f;          // of query row lr over this wave's keys (the 4 lanes of a row agree)
+  f32x4 acc[4];                                  // out^T tile dt: head dimensions 16*dt + 4*lq + r, row lr
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c = first; c + wave < ngr; c += hop) {
+    // scores of the wave's groups: sacc[gg][t][r] = key 32 (c + wave + NW gg) + 8 lq + 4 t + r against query row lr
+    f32x4 sacc[G][2];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) {
+      const int kb = 32 * (c + wave + NW * gg) + 8 * lq;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+          const bf16x8 ka = __builtin_bit_cast(bf16x8, kf[gg][2 * t + s2]);
+          a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qhi[s2], a, 0, 0, 0);
+          a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qlo[s2], a, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int key = kb + 4 * t + r;
+          a[r] = (key < nvis && (!LIMF || key >= nlo)) ? a[r] : -INFINITY;
+          mx = fmaxf(mx, a[r]);
+        }
+        sacc[gg][t] = a;
+      }
+    }
+    mx = max_rows(mx);
+    const float m_new = fmaxf(m_run, mx);
+    const float alpha = (m_new == -INFINITY) ? 1.f : __expf(m_run - m_new);
+    float sum = 0.f;
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float pv = (m_new == -INFINITY) ? 0.f : __expf(sacc[gg][t][r] - m_new);
+          sacc[gg][t][r] = pv;
+          sum += pv;
+        }
+    sum = sum_rows(sum);
+    l_run = l_run * alpha + sum;
+    m_run = m_new;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) acc[dt] *= alpha;
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) {
+      const int g0 = 32 * (c + wave + NW * gg);
+      if (g0 >= nkeys) continue;                 // (the same for the whole wave)
+      if (g0 + 32 > nkeys) {                     // values of keys past the last one: their probabilities are zero, their bits unknown
+        const int left = nkeys - g0 - 8 * lq;    // of this lane's eight
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+          for (int w = 0; w < 4; ++w)
+            vf[gg][dt][w] = left > 2 * w + 1 ? vf[gg][dt][w] : (left > 2 * w ? vf[gg][dt][w] & 0xFFFFu : 0u);
+      }
+      const float pv[8] = {sacc[gg][0][0], sacc[gg][0][1], sacc[gg][0][2], sacc[gg][0][3], sacc[gg][1][0], sacc[gg][1][1], sacc[gg][1][2], sacc[gg][1][3]};
+      bf16x8 phi, plo;
+      split_bf16x8(pv, phi, plo);
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt) {
+        const bf16x8 va = __builtin_bit_cast(bf16x8, vf[gg][dt]);
+        acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, phi, acc[dt], 0, 0, 0);
+        acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, plo, acc[dt], 0, 0, 0);
+      }
+    }
+    if (c + hop + wave < ngr) BPD_LOAD_KV(c + hop)
+  }
+#undef BPD_LOAD_KV
+  // the waves meet: wave w (of the first four) finishes head dimensions 16w .. 16w+15
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt) sm.o_s[wave][dt][lane] = acc[dt];
+  if (lq == 0) { sm.m_s[wave][lr] = m_run; sm.l_s[wave][lr] = l_run; }
+  __syncthreads();
+  if (wave >= 4) return;
+  float mw[NW], M = -INFINITY;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) { mw[w] = sm.m_s[w][lr]; M = fmaxf(M, mw[w]); }
+  float L = 0.f;
+  f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const float wgt = (mw[w] == -INFINITY) ? 0.f : __expf(mw[w] - M);
+    L = fmaf(sm.l_s[w][lr], wgt, L);
+    const f32x4 ow = sm.o_s[w][wave][lane];
+    o[0] = fmaf(ow[0], wgt, o[0]); o[1] = fmaf(ow[1], wgt, o[1]); o[2] = fmaf(ow[2], wgt, o[2]); o[3] = fmaf(ow[3], wgt, o[3]);
+  }
+  const int dim = 16 * wave + 4 * lq;
+  if (p.nsplit == 1) {
+    if (lr < nrows) {
+      const float inv = 1.0f / L;
+      *(u32x2*)((bf16_t*)p.out + ((size_t)b * p.R + r0 + lr) * p.d + h * DH + dim) = u32x2{cvt_pk_bf16(o[0] * inv, o[1] * inv), cvt_pk_bf16(o[2] * inv, o[3] * inv)};
+    }
+  } else {
+    const int tiles = nz / p.nsplit;
+    float* part = p.part + ((((long)b * nheads + h) * tiles + tile) * p.nsplit + split) * (RT * (DH + 2));
+    *(f32x4*)(part + lr * DH + dim) = o;
+    if (tid < RT) { part[RT * DH + tid] = M; part[RT * DH + RT + tid] = L; }
+  }
+}
+// SLOTS: a step of a batch some of whose sequences may have ended (AttnP::seq); a kernel of its own, since looking the
+// sequence up is one more round trip ahead of the K/V loads.
+constexpr int attn_waves(int QU) { return QU > 0 ? 8 : 4; }
+template <bool KVNT, bool LIMF, int QU, bool SLOTS>
+__device__ __forceinline__ void attention_mfma_entry(const AttnP& p, const QProjP& qp) {
+  constexpr int NW = attn_waves(QU), RT = 16, DH = 64;
+  __shared__ f32x4 o_s[NW][4][64];
+  __shared__ float m_s[NW][RT], l_s[NW][RT];
+  __shared__ __attribute__((aligned(16))) float q_s[QU > 0 ? RT * (DH + 4) : 4];
+  __shared__ __attribute__((aligned(16))) float gb_s[QU > 0 ? NW * ((4 * QU + NW - 1) / NW) * 64 : 4];
+  __shared__ float2 st_s[QU > 0 ? NW * 16 : 1];
+  AttnLdsT<NW> sm;
+  sm.o_s = o_s; sm.m_s = m_s; sm.l_s = l_s; sm.q_s = q_s; sm.gb_s = gb_s; sm.st_s = st_s;
+  const int sb = SLOTS ? p.seq[blockIdx.y] : blockIdx.y;
+  if (SLOTS && sb < 0) return;
+  attention_mfma_body<NW, KVNT, LIMF, QU>(p, qp, sm, blockIdx.x, blockIdx.y, sb, blockIdx.z, gridDim.x, gridDim.z, threadIdx.x);
+}
+template <bool KVNT, bool LIMF, int QU>
+__global__ __launch_bounds__(64 * attn_waves(QU)) void attention_mfma_kernel(AttnP p, QProjP qp) { attention_mfma_entry<KVNT, LIMF, QU, false>(p, qp); }
+template <bool KVNT, bool LIMF, int QU>
+__global__ __launch_bounds__(64 * attn_waves(QU)) void attention_mfma_slots_kernel(AttnP p, QProjP qp) { attention_mfma_entry<KVNT, LIMF, QU, true>(p, qp); }

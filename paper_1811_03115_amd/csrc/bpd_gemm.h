@@ -62,14 +62,14 @@ __device__ __forceinline__ void store_tiles(const Epi& e_in, int g, const f32x4 
         if (m < M) {
           if (e.Yf) *(float4*)(e.Yf + g * e.yf_g + (long)m * e.ldyf + n) = make_float4(v[0], v[1], v[2], v[3]);
           if (e.Ya) *(uint2*)((bf16_t*)e.Ya + g * e.ya_g + (long)m * e.ldya + n) =
-                        make_uint2((unsigned)f2bf(v[0]) | ((unsigned)f2bf(v[1]) << 16), (unsigned)f2bf(v[2]) | ((unsigned)f2bf(v[3]) << 16));
+                        make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
           fin[0] = v[0]; fin[1] = v[1]; fin[2] = v[2]; fin[3] = v[3];
         }
       } else if (m < M) epi_store4f(e, g, m, n, v, fin);
       if (wide) {                                 // (the direct stores above saw e.Ya == nullptr: see the copy of e below)
         const int lr_ = lane & 15, sg = (u * 2 + (lane >> 5)) ^ (lr_ & 7);
         *(uint2*)(stage + lr_ * 128 + sg * 16 + ((lane >> 4) & 1) * 8) =
-            make_uint2((unsigned)f2bf(fin[0]) | ((unsigned)f2bf(fin[1]) << 16), (unsigned)f2bf(fin[2]) | ((unsigned)f2bf(fin[3]) << 16));
+            make_uint2(cvt_pk_bf16(fin[0], fin[1]), cvt_pk_bf16(fin[2], fin[3]));
       }
       if (stats) {
         float sv = (fin[0] + fin[1]) + (fin[2] + fin[3]);
@@ -182,8 +182,6 @@ struct LnP {
   const float* stats;   // partial sums written by the producer of x
   float eps;
 };
-
-__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) { return (unsigned)f2bf(lo) | ((unsigned)f2bf(hi) << 16); }
 
 // Skinny GEMM: blocks of 16*MT rows (blockIdx.y), all rows of a block resident in registers.  Workgroup = WAVES waves
 // sharing NT column tiles, K split WAVES ways (wave w takes k-steps w, w+WAVES, ...; at most U
@@ -329,7 +327,7 @@ __global__ __launch_bounds__(WAVES * 64) void skinny_gemm_kernel(GemmP p, Epi e,
         y[4 * hh + 2] = (xv[i][hh].z - mu) * rstd * gv[i][hh].z + bv[i][hh].z;
         y[4 * hh + 3] = (xv[i][hh].w - mu) * rstd * gv[i][hh].w + bv[i][hh].w;
       }
-      const uint4 yb = make_uint4(pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3]), pack_bf16(y[4], y[5]), pack_bf16(y[6], y[7]));
+      const uint4 yb = make_uint4(cvt_pk_bf16(y[0], y[1]), cvt_pk_bf16(y[2], y[3]), cvt_pk_bf16(y[4], y[5]), cvt_pk_bf16(y[6], y[7]));
       b[0][i] = (wave + WAVES * i) < ksteps ? yb : zero4;
     }
   } else {
@@ -436,7 +434,7 @@ __global__ __launch_bounds__(WAVES * 64) void skinny_gemm_kernel(GemmP p, Epi e,
         if (m < p.M) {
           if (e.Yf) *(float4*)(e.Yf + g * e.yf_g + (long)m * e.ldyf + n) = make_float4(v[0], v[1], v[2], v[3]);
           if (e.Ya) *(uint2*)((bf16_t*)e.Ya + g * e.ya_g + (long)m * e.ldya + n) =
-                        make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+                        make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
         }
       }
     }
@@ -566,7 +564,7 @@ __global__ __launch_bounds__(512) void stream_gemm_kernel(GemmP p, Epi e) {
     const int n = (tile) * 16 + lq * 4;                                                         \
     if (lr < p.M) {                                                                             \
       if (e.Yf) *(float4*)(e.Yf + g * e.yf_g + (long)lr * e.ldyf + n) = make_float4(v[0], v[1], v[2], v[3]); \
-      if (e.Ya) *(uint2*)((bf16_t*)e.Ya + g * e.ya_g + (long)lr * e.ldya + n) = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])); \
+      if (e.Ya) *(uint2*)((bf16_t*)e.Ya + g * e.ya_g + (long)lr * e.ldya + n) = make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])); \
     }                                                                                           \
   }
 #define ST_MULT(A)                                                                              \
@@ -911,10 +909,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
 #define BPD_NORM1(v, gq, bq, i) ((v - mu[i]) * rs[i] * gq + bq)
 #define BPD_NORM_STORE(buf)                                                                  \
     _Pragma("unroll") for (int i = 0; i < XI; ++i) {                                         \
-      const unsigned w0 = pack_bf16(BPD_NORM1(xa[i][0].x, ga[0].x, ba[0].x, i), BPD_NORM1(xa[i][0].y, ga[0].y, ba[0].y, i)); \
-      const unsigned w1 = pack_bf16(BPD_NORM1(xa[i][0].z, ga[0].z, ba[0].z, i), BPD_NORM1(xa[i][0].w, ga[0].w, ba[0].w, i)); \
-      const unsigned w2 = pack_bf16(BPD_NORM1(xa[i][1].x, ga[1].x, ba[1].x, i), BPD_NORM1(xa[i][1].y, ga[1].y, ba[1].y, i)); \
-      const unsigned w3 = pack_bf16(BPD_NORM1(xa[i][1].z, ga[1].z, ba[1].z, i), BPD_NORM1(xa[i][1].w, ga[1].w, ba[1].w, i)); \
+      const unsigned w0 = cvt_pk_bf16(BPD_NORM1(xa[i][0].x, ga[0].x, ba[0].x, i), BPD_NORM1(xa[i][0].y, ga[0].y, ba[0].y, i)); \
+      const unsigned w1 = cvt_pk_bf16(BPD_NORM1(xa[i][0].z, ga[0].z, ba[0].z, i), BPD_NORM1(xa[i][0].w, ga[0].w, ba[0].w, i)); \
+      const unsigned w2 = cvt_pk_bf16(BPD_NORM1(xa[i][1].x, ga[1].x, ba[1].x, i), BPD_NORM1(xa[i][1].y, ga[1].y, ba[1].y, i)); \
+      const unsigned w3 = cvt_pk_bf16(BPD_NORM1(xa[i][1].z, ga[1].z, ba[1].z, i), BPD_NORM1(xa[i][1].w, ga[1].w, ba[1].w, i)); \
       *(uint4*)((buf) + lo[i]) = make_uint4(w0, w1, w2, w3);                                 \
     }
 #define BPD_LOAD_WX(dst, chunk)                                                              \

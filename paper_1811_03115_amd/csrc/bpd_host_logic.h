@@ -55,7 +55,7 @@ struct Layout {
   std::vector<DecL> dec; LnW dec_lnf;
   void *hw1, *hw2; float *hb1, *hb2;
   // caches
-  void *selfK, *selfV, *crossK, *crossV;        // [n_dec][B][slots|max_src][d]
+  void *selfK, *selfV, *crossK, *crossV;        // [n_dec][B][kv_rows(slots | max_src)][d]
   // decoder activations (M = max_batch * k_max rows)
   float *x, *q, *h, *stats_ln, *stats_big, *zeros, *attn_part, *kpart; size_t n_zeros, n_kpart; void *xn, *attn, *ffh, *hn, *H, *O;
   unsigned long long* keys; unsigned long long* keys_h1; float* logits_h1; int* topn_ok;
@@ -74,6 +74,10 @@ struct Layout {
 };
 
 size_t act_size(const bpd_config& c) { return c.dtype == BPD_BF16 ? 2 : 4; }
+
+// 64-wide heads in bf16: K and V are kept in operand order, in groups of 32 keys (bpd_attention.h)
+bool kv_grouped(const bpd_config& c) { return c.dtype == BPD_BF16 && c.d_model == 64 * c.n_heads; }
+size_t kv_rows(const bpd_config& c, size_t rows) { return kv_grouped(c) ? (rows + 31) / 32 * 32 : rows; }
 
 bool config_ok(const bpd_config& c) {
   if (c.n_enc_layers < 1 || c.n_dec_layers < 1 || c.d_model < 32 || c.n_heads < 1) return false;
@@ -134,8 +138,9 @@ size_t build_layout(const bpd_config& c, char* base, Layout& L, std::vector<std:
   }
   L.hw1 = mat(d, k * F); L.hb1 = vec(k * F); L.hw2 = mat(k * F, d); L.hb2 = vec(k * d);
   const size_t B = c.max_batch, nd = c.n_dec_layers, S = c.max_src_len;
-  L.selfK = a.take(nd * B * slots * d * as); L.selfV = a.take(nd * B * slots * d * as);
-  L.crossK = a.take(nd * B * S * d * as);    L.crossV = a.take(nd * B * S * d * as);
+  const size_t self_rows = kv_rows(c, slots), src_rows = kv_rows(c, S);
+  L.selfK = a.take(nd * B * self_rows * d * as); L.selfV = a.take(nd * B * self_rows * d * as);
+  L.crossK = a.take(nd * B * src_rows * d * as); L.crossV = a.take(nd * B * src_rows * d * as);
   const size_t M = B * k;
   L.x = vec(M * d); L.q = vec(M * d); L.h = vec(M * d); L.stats_ln = vec(64 * 16 * 2);
   L.n_zeros = k * F; if (V > L.n_zeros) L.n_zeros = V; if (3 * d > L.n_zeros) L.n_zeros = 3 * d;
@@ -152,7 +157,7 @@ size_t build_layout(const bpd_config& c, char* base, Layout& L, std::vector<std:
   const size_t Me = B * S;
   L.stats_big = vec((size_t)(d / 64 + 1) * (M > Me ? M : Me) * 2);   // per 64-column block and row: sum, sum of squares
   L.xe = vec(Me * d); L.qe = vec(Me * d);
-  L.xen = a.take(Me * d * as); L.ke = a.take(Me * d * as); L.ve = a.take(Me * d * as);
+  L.xen = a.take(Me * d * as); L.ke = a.take(B * src_rows * d * as); L.ve = a.take(B * src_rows * d * as);
   L.attne = a.take(Me * d * as); L.ffhe = a.take(Me * F * as); L.mem = a.take(Me * d * as);
   auto ints = [&](size_t n) { return (int*)a.take(n * 4); };
   L.L = ints(B); L.j = ints(B); L.finished = ints(B); L.max_len = ints(B); L.src_len = ints(B);

@@ -21,11 +21,19 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 __device__ __forceinline__ float bf2f(bf16_t v) { return __uint_as_float(((unsigned)v) << 16); }
-__device__ __forceinline__ bf16_t f2bf(float f) {          // round to nearest even
-  unsigned u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (bf16_t)(u >> 16);
+__device__ __forceinline__ bf16_t f2bf(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }      // round to nearest even (one instruction)
+__device__ __forceinline__ unsigned cvt_pk_bf16(float lo, float hi) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
 }
+// Descriptor of `bytes` bytes from p (both the same for the whole wave): loads past the end return zeros without a memory
+// access, so that rows beyond a block's last one cost nothing and need no branch.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ rsrc_t rsrc_of(const void* p, unsigned bytes) { return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)bytes, 0x00027000); }
+__device__ __forceinline__ u32x4 buf_load16(rsrc_t r, unsigned off, unsigned soff) { return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, (int)soff, 0); }
 template <typename T> __device__ __forceinline__ float to_f(T v);
 template <> __device__ __forceinline__ float to_f<float>(float v) { return v; }
 template <> __device__ __forceinline__ float to_f<bf16_t>(bf16_t v) { return bf2f(v); }
@@ -37,9 +45,36 @@ __device__ __forceinline__ float wave_max(float v) {
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
   return v;
 }
+// Sum and maximum over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (one row of an MFMA operand), in all of them.  The swaps
+// exchange every second 16-lane row (the upper half) of one register with the others (the lower half) of another: no trip
+// through LDS.
+__device__ __forceinline__ float sum_rows(float v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+__device__ __forceinline__ float max_rows(float v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+// ... and over the whole wave: lanes of a 16-lane row first (data-parallel-primitive moves), then the rows
+template <int CTRL> __device__ __forceinline__ float dpp_move(float v) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true)); }
 __device__ __forceinline__ float wave_sum(float v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  v += dpp_move<0xB1>(v);                        // quad_perm 1 0 3 2
+  v += dpp_move<0x4E>(v);                        // quad_perm 2 3 0 1
+  v += dpp_move<0x141>(v);                       // row_half_mirror
+  v += dpp_move<0x140>(v);                       // row_mirror
+  return sum_rows(v);
+}
+// Mean and 1 / sqrt(variance + eps) of a row from its sum and its sum of squares (inv_n = 1 / columns); one Newton step
+// brings the hardware's reciprocal root to fp32.
+__device__ __forceinline__ void row_moments(float s, float q, float inv_n, float eps, float& mu, float& rstd) {
+  mu = s * inv_n;
+  const float v = fmaxf(fmaf(-mu, mu, q * inv_n), 0.f) + eps, r = __builtin_amdgcn_rsqf(v);
+  rstd = r * fmaf(-0.5f * v * r, r, 1.5f);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -49,7 +84,9 @@ __device__ __forceinline__ float wave_sum(float v) {
 //          c == 0 -> Qf[m][n%dsplit] (fp32),  c == 1 -> Ka,  c == 2 -> Va  (act type) at row
 //          (m / rows_per_seq) * cap + (base ? base[m / rows_per_seq] : 0) + m % rows_per_seq
 //          (a K/V cache write at the sequence's current length; with slots cap is 0 and base holds whole cache rows,
-//          StateP::slot_row).
+//          StateP::slot_row).  capg > 0: 64-wide heads, whose caches lie in operand order (bpd_attention.h), capg groups of 32
+//          keys per sequence; base is then always the sequence's length, and seq (null: the slot; -1: none) its place.
+__device__ __forceinline__ void kv_frag_store(bf16_t* cache, bool is_v, int sb, int heads, int capg, int key, int col, unsigned lo, unsigned hi);   // bpd_attention.h
 struct Epi {
   int mode;
   int relu;
@@ -76,6 +113,7 @@ struct Epi {
   float* Qf; void* Ka; void* Va;
   int dsplit, chunk0, rows_per_seq, cap;
   const int* base;
+  int capg; const int* seq;
 };
 
 template <typename ACT>
@@ -122,7 +160,7 @@ __device__ __forceinline__ void epi_store4f(const Epi& e, int g, int m, int n, c
     }
     if (e.Yf) *(float4*)(e.Yf + g * e.yf_g + (long)m * e.ldyf + n) = make_float4(v[0], v[1], v[2], v[3]);
     if (e.Ya) *(uint2*)((bf16_t*)e.Ya + g * e.ya_g + (long)m * e.ldya + n) =
-                  make_uint2((unsigned)f2bf(v[0]) | ((unsigned)f2bf(v[1]) << 16), (unsigned)f2bf(v[2]) | ((unsigned)f2bf(v[3]) << 16));
+                  make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
     fin[0] = v[0]; fin[1] = v[1]; fin[2] = v[2]; fin[3] = v[3];
   } else {
     const int c = n / e.dsplit + e.chunk0;
@@ -131,10 +169,15 @@ __device__ __forceinline__ void epi_store4f(const Epi& e, int g, int m, int n, c
       *(float4*)(e.Qf + (long)m * e.dsplit + col) = make_float4(v[0], v[1], v[2], v[3]);
     } else {
       const int b = m / e.rows_per_seq, i = m % e.rows_per_seq;
-      const long row = (long)b * e.cap + (e.base ? e.base[b] : 0) + i;
       bf16_t* dst = (bf16_t*)(c == 1 ? e.Ka : e.Va);
-      *(uint2*)(dst + row * e.dsplit + col) =
-          make_uint2((unsigned)f2bf(v[0]) | ((unsigned)f2bf(v[1]) << 16), (unsigned)f2bf(v[2]) | ((unsigned)f2bf(v[3]) << 16));
+      const unsigned lo = cvt_pk_bf16(v[0], v[1]), hi = cvt_pk_bf16(v[2], v[3]);
+      if (e.capg) {
+        const int sb = e.seq ? e.seq[b] : b;
+        if (sb >= 0) kv_frag_store(dst, c == 2, sb, e.dsplit >> 6, e.capg, (e.base ? e.base[b] : 0) + i, col, lo, hi);
+      } else {
+        const long row = (long)b * e.cap + (e.base ? e.base[b] : 0) + i;
+        *(uint2*)(dst + row * e.dsplit + col) = make_uint2(lo, hi);
+      }
     }
   }
 }
@@ -587,7 +630,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(float* x, const float* g
       if (ya) {
         ACT* o = ya + (long)row * d + 4 * c4;
         if constexpr (sizeof(ACT) == 2) {          // bf16: one 8-byte store
-          *(uint2*)o = make_uint2((unsigned)f2bf(y0) | ((unsigned)f2bf(y1) << 16), (unsigned)f2bf(y2) | ((unsigned)f2bf(y3) << 16));
+          *(uint2*)o = make_uint2(cvt_pk_bf16(y0, y1), cvt_pk_bf16(y2, y3));
         } else {
           o[0] = from_f<ACT>(y0); o[1] = from_f<ACT>(y1); o[2] = from_f<ACT>(y2); o[3] = from_f<ACT>(y3);
         }
@@ -604,7 +647,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(float* x, const float* g
 // self-attention.  Keys are visited in chunks of 256 with a running (max, sum) per row so
 // the LDS footprint does not depend on the cache length.
 //   Q    fp32 [B*R][d]                 out  act [B*R][d]
-//   Kc,Vc act, sequence b at Kc + b*kv_seq_stride, key s at + s*d, head h at + h*DH
+//   Kc,Vc act, sequence b at Kc + b*kv_seq_stride, key s at + s*d, head h at + h*DH (64-wide bf16 heads: bpd_attention.h)
 template <typename ACT, int DH> struct RowLoader;
 template <int DH> struct RowLoader<float, DH> {
   static __device__ __forceinline__ void unpack(const uint4* raw, float* out) {
@@ -654,6 +697,7 @@ struct AttnP {
   void* out;
   long kv_seq_stride;
   int cap;                // rows per sequence in the K/V buffer (loads are clamped to it)
+  int capg;               // 64-wide bf16 heads (bpd_attention.h): groups of 32 keys per sequence instead
   int d, R;
   const int* limit;       // [B]: base (causal) or len (non-causal)
   int causal;
@@ -836,375 +880,8 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnP p) {
   }
 }
 
-// bf16, 64-wide heads: the same computation on the matrix cores, one barrier per workgroup.  The four waves split
-// the keys: of every 256-key chunk wave w takes keys 64w .. 64w+63 and keeps its own running maximum, sum and weighted
-// values in registers; the waves' results meet once, in LDS, at the end.  Per chunk and wave
-//   scores^T = K Q^T     keys are the 16-wide "feature" side of the MFMA, the <= 16 query rows the other; K fragments
-//                        come straight from the cache (a key row is contiguous along the contracted head dimension);
-//                        a lane then holds, for its query row, the scores of 4 keys of each of the 4 key tiles
-//   softmax              maximum and sum over the wave's 64 keys: in the lane, then across the 4 lanes of a row;
-//                        the probabilities stay in registers: the scores of two key tiles are, as they lie, the
-//                        second MFMA operand for a contraction over those 32 keys (in a permuted key order)
-//   out^T += V^T P^T     contracted over keys, 64 head dimensions = 4 output tiles; the V^T fragments (same key
-//                        order) are gathered from the wave's own 64 V rows staged in LDS (row stride 68 elements,
-//                        so the four key groups of a fragment read disjoint banks; no barrier: a wave's LDS
-//                        accesses execute in order)
-// fp32 operands (Q, the probabilities) are fed as a bf16 pair hi + lo, which keeps them to ~2^-17: the result matches
-// the scalar kernel to fp32 rounding.  Same arguments, grid and partial-result layout as attention_kernel.
-__device__ __forceinline__ void split_bf16x8(const float (&v)[8], bf16x8& hi, bf16x8& lo) {
-  unsigned h[4], l[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const bf16_t h0 = f2bf(v[2 * j]), h1 = f2bf(v[2 * j + 1]);
-    const bf16_t l0 = f2bf(v[2 * j] - bf2f(h0)), l1 = f2bf(v[2 * j + 1] - bf2f(h1));
-    h[j] = (unsigned)h0 | ((unsigned)h1 << 16);
-    l[j] = (unsigned)l0 | ((unsigned)l1 << 16);
-  }
-  hi = __builtin_bit_cast(bf16x8, make_uint4(h[0], h[1], h[2], h[3]));
-  lo = __builtin_bit_cast(bf16x8, make_uint4(l[0], l[1], l[2], l[3]));
-}
-
-__device__ __forceinline__ unsigned pack_bf16_pair(float lo, float hi) { return (unsigned)f2bf(lo) | ((unsigned)f2bf(hi) << 16); }
-
-// KVNT: K and V are fetched with non-temporal loads (a cache too large for the last-level cache is a
-// stream that should not evict the weights).
-typedef unsigned int u32x4_kv __attribute__((ext_vector_type(4)));
-// LIMF: the sequence's length is fetched first and the K/V loads are clamped to it instead of to the buffer's rows: one
-// more dependent round trip, but rows past the end are not fetched (many sequences: the traffic is what counts).
-// QU > 0 (at most 16 rows per sequence, d = 128 * QU): the queries are projected inside the kernel,
-//   Q = LayerNorm(x) Wq[:, 64 h .. 64 h + 63]   (x: fp32 residual stream with its partial LayerNorm statistics),
-// instead of being read from p.Q: the four waves split the contraction, their partial sums meet in LDS, and the K/V
-// loads of the first chunk are already in flight meanwhile.  Saves the projection's kernel and its round trip.
-struct QProjP {
-  const float* x;       // [M][d] residual stream
-  const float* g;       // LayerNorm gain, bias
-  const float* b;
-  const float* stats;   // partial statistics of x: [(part * srows + row) * 2]
-  int srows;            // 16: single-tile path, one part per 16 columns; otherwise M rows, one part per 64 columns
-  const void* W;        // packed [d/16 column tiles][d/32 k-steps][64 lanes][8]
-  float eps;
-};
-// LDS of one attention workgroup (4 waves): the kernel below declares it; a caller that runs the body from inside
-// another kernel carves it out of its own LDS.
-struct AttnLds {
-  static constexpr int RT = 16, DH = 64, WK = 64, VLD = DH + 4;
-  bf16_t (*vs)[WK][VLD];      // [4][WK][VLD] per wave: its 64 V rows of the chunk
-  f32x4 (*o_s)[4][64];        // [4][4][64]   per wave and output tile: un-normalised out^T
-  float (*m_s)[RT];           // [4][RT]      per wave: running maximum per query row
-  float (*l_s)[RT];           // [4][RT]      ... and sum
-  float* q_s;                 // QU > 0: [RT * (DH + 4)] projected queries
-  static constexpr size_t VS_BYTES = (size_t)4 * WK * VLD * 2, OS_BYTES = (size_t)4 * 4 * 64 * 16, ML_BYTES = (size_t)4 * RT * 4;
-  static constexpr size_t BYTES = VS_BYTES + OS_BYTES + 2 * ML_BYTES;        // without q_s
-  // carve (16-byte aligned base), QU == 0 layout
-  __device__ static AttnLds carve(unsigned char* base) {
-    AttnLds s;
-    s.vs = (bf16_t (*)[WK][VLD])base;
-    s.o_s = (f32x4 (*)[4][64])(base + VS_BYTES);
-    s.m_s = (float (*)[RT])(base + VS_BYTES + OS_BYTES);
-    s.l_s = (float (*)[RT])(base + VS_BYTES + OS_BYTES + ML_BYTES);
-    s.q_s = nullptr;
-    return s;
-  }
-};
-// One (head h, sequence b (in the K/V buffer: sb), z = row tile * nsplit + split) item of the attention, run by 256 threads (tid 0..255, four
-// whole waves) that share `sm`; nheads / nz: the extents the partial-result layout is indexed with.  Every
-// __syncthreads() inside is reached by all 256 threads; a caller whose workgroup has more waves makes those arrive at
-// as many barriers (one with QU == 0, three with QU > 0).
-template <bool KVNT, bool LIMF, int QU>
-__device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP& qp, const AttnLds& sm, int h, int b, int sb, int z,
-                                                    int nheads, int nz, int tid) {
-  constexpr int RT = 16, CH = 256, DH = 64, WK = 64, VLD = DH + 4;
-  bf16_t (*vs)[WK][VLD] = sm.vs;
-  f32x4 (*o_s)[4][64] = sm.o_s;
-  float (*m_s)[RT] = sm.m_s;
-  float (*l_s)[RT] = sm.l_s;
-  float* q_s = sm.q_s;
-  const int split = z % p.nsplit, tile = z / p.nsplit, r0 = tile * RT;
-  const int nrows = min(RT, p.R - r0);
-  const int lane = tid & 63, wave = tid >> 6;
-  const int lr = lane & 15, lq = lane >> 4;
-  const bf16_t* Kb = (const bf16_t*)p.Kc + sb * p.kv_seq_stride + h * DH;
-  const bf16_t* Vb = (const bf16_t*)p.Vc + sb * p.kv_seq_stride + h * DH;
-  int kmax = p.cap;                              // rows that may be fetched
-  int kbeg = 0;                                  // first key of the first chunk (local attention: LIMF only)
-  if (LIMF) {
-    int l0 = p.limit[b];
-    l0 = l0 < 0 ? 0 : l0;
-    const int nk0 = p.causal ? l0 + r0 + nrows : l0;
-    kmax = nk0 < p.cap ? (nk0 > 0 ? nk0 : 1) : p.cap;
-    kbeg = attn_first_key(p, l0 + r0);
-  }
-  const int first = kbeg + split * CH, hop = p.nsplit * CH;
-  // K fragments (4 key tiles x 2 halves of the head dimension) and this lane's 8 pieces of the wave's V rows
-  uint4 kf[4][2], vraw[8];
-#define BPD_LOAD_KV(c0)                                                                         \
-  {                                                                                             \
-    _Pragma("unroll") for (int kt = 0; kt < 4; ++kt) {                                          \
-      int key = (c0) + wave * WK + kt * 16 + lr;                                                \
-      key = key < kmax ? key : kmax - 1;                                                        \
-      const bf16_t* kp = Kb + (long)key * p.d + 8 * lq;                                         \
-      if (KVNT) {                                                                               \
-        kf[kt][0] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4_kv*)kp));     \
-        kf[kt][1] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4_kv*)(kp + 32))); \
-      } else {                                                                                  \
-        kf[kt][0] = *(const uint4*)kp; kf[kt][1] = *(const uint4*)(kp + 32);                    \
-      }                                                                                         \
-    }                                                                                           \
-    _Pragma("unroll") for (int x = 0; x < 8; ++x) {       /* 8 lanes per V row: a wave-load covers 8 whole rows */ \
-      int vkey = (c0) + wave * WK + 8 * x + (lane >> 3);                                        \
-      vkey = vkey < kmax ? vkey : kmax - 1;                                                     \
-      const bf16_t* vp_ = Vb + (long)vkey * p.d + 8 * (lane & 7);                               \
-      if (KVNT) vraw[x] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4_kv*)vp_)); \
-      else vraw[x] = *(const uint4*)vp_;                                                        \
-    }                                                                                           \
-  }
-  // queries: row lr (clamped), head dimensions 32s + 8*lq .. +8, scaled, as bf16 hi + lo
-  bf16x8 qhi[2], qlo[2];
-  if constexpr (QU > 0) {
-    constexpr int K = 128 * QU, KSTEPS = K / 32, NV4 = 64 * QU, J = QU > 4 ? 2 : 1;
-    // LDS that the key loop and the final merge use later: statistics and gain / bias in vs, the waves' partial sums in o_s
-    float* st_s = (float*)&vs[0][0][0];          // [K/16][16][2]   (<= 8 KB)
-    float* gb_s = st_s + 2048;                   // gain at 0, bias at 1024   (8 KB)
-    f32x4* red = &o_s[0][0][0];                  // [wave][column tile][lane]
-    static_assert(AttnLds::VS_BYTES >= 4 * 4096, "prologue operands fit the V staging area");
-    // every global load of the kernel is issued before the first wait: small operands, x, weights, then K / V
-    // (named registers: indexed arrays of these were placed in LDS by the compiler)
-    const int i0 = tid < NV4 ? tid : 0, i1 = tid + 256 < NV4 ? tid + 256 : 0;
-    const float4 gb0 = ((const float4*)(i0 < NV4 / 2 ? qp.g : qp.b))[i0 < NV4 / 2 ? i0 : i0 - NV4 / 2];
-    float4 gb1 = gb0;
-    if constexpr (J > 1) gb1 = ((const float4*)(i1 < NV4 / 2 ? qp.g : qp.b))[i1 < NV4 / 2 ? i1 : i1 - NV4 / 2];
-    // statistics of this sequence's rows: element e = 16 * tile + local row
-    // (srows == 16: one partial per 16-column tile, 8 QU of them; otherwise per 64-column block, 2 QU)
-    constexpr int JS = QU >= 2 ? QU / 2 : 1;
-    const int nparts = qp.srows == 16 ? 8 * QU : 2 * QU, NS2 = 16 * nparts;
-    const int row_first = b * p.R + r0;
-#define BPD_ST_SRC(e) ((const float2*)qp.stats)[(e) < NS2 ? ((e) >> 4) * qp.srows + row_first + (((e) & 15) < nrows ? ((e) & 15) : nrows - 1) : 0]
-    const float2 s0 = BPD_ST_SRC(tid);
-    float2 s1 = s0, s2 = s0, s3 = s0;
-    if constexpr (JS > 1) s1 = BPD_ST_SRC(tid + 256);
-    if constexpr (JS > 2) { s2 = BPD_ST_SRC(tid + 512); s3 = BPD_ST_SRC(tid + 768); }
-#undef BPD_ST_SRC
-    const int lrc = lr < nrows ? lr : nrows - 1;
-    const int grow = row_first + lrc;
-    float4 xv[QU][2];
-#pragma unroll
-    for (int i = 0; i < QU; ++i) {
-      const float* xp = qp.x + (long)grow * K + (wave + 4 * i) * 32 + 8 * lq;
-      xv[i][0] = *(const float4*)xp; xv[i][1] = *(const float4*)(xp + 4);
-    }
-    uint4 wf[QU][4];
-#pragma unroll
-    for (int i = 0; i < QU; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        wf[i][j] = ((const uint4*)qp.W)[((long)(4 * h + j) * KSTEPS + wave + 4 * i) * 64 + lane];
-    BPD_LOAD_KV(first)
-    __builtin_amdgcn_sched_barrier(0);
-    if (tid < NV4) *(float4*)&gb_s[tid < NV4 / 2 ? 4 * tid : 1024 + 4 * (tid - NV4 / 2)] = gb0;
-    if (J > 1 && tid + 256 < NV4) {
-      const int idx = tid + 256;
-      *(float4*)&gb_s[idx < NV4 / 2 ? 4 * idx : 1024 + 4 * (idx - NV4 / 2)] = gb1;
-    }
-    if (tid < NS2) ((float2*)st_s)[tid] = s0;
-    if constexpr (JS > 1) ((float2*)st_s)[tid + 256] = s1;
-    if constexpr (JS > 2) { ((float2*)st_s)[tid + 512] = s2; ((float2*)st_s)[tid + 768] = s3; }
-    __syncthreads();
-    float sm = 0.f, sq = 0.f;                    // row statistics: this lane adds partials lq, lq + 4, ...
-#pragma unroll
-    for (int i = 0; i < 2 * QU; ++i) {
-      const int part = lq + 4 * i;
-      const float2 v = ((const float2*)st_s)[(part < nparts ? part : 0) * 16 + lrc];
-      sm += part < nparts ? v.x : 0.f; sq += part < nparts ? v.y : 0.f;
-    }
-    sm += __shfl_xor(sm, 16, 64); sm += __shfl_xor(sm, 32, 64);
-    sq += __shfl_xor(sq, 16, 64); sq += __shfl_xor(sq, 32, 64);
-    const float mu = sm / K;
-    const float rstd = 1.0f / sqrtf(fmaxf(sq / K - mu * mu, 0.f) + qp.eps);
-    f32x4 qa[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) qa[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < QU; ++i) {
-      const int col = (wave + 4 * i) * 32 + 8 * lq;
-      const float4 g0 = *(const float4*)&gb_s[col], g1 = *(const float4*)&gb_s[col + 4];
-      const float4 b0 = *(const float4*)&gb_s[1024 + col], b1 = *(const float4*)&gb_s[1024 + col + 4];
-      const uint4 yb = make_uint4(pack_bf16_pair((xv[i][0].x - mu) * rstd * g0.x + b0.x, (xv[i][0].y - mu) * rstd * g0.y + b0.y),
-                                  pack_bf16_pair((xv[i][0].z - mu) * rstd * g0.z + b0.z, (xv[i][0].w - mu) * rstd * g0.w + b0.w),
-                                  pack_bf16_pair((xv[i][1].x - mu) * rstd * g1.x + b1.x, (xv[i][1].y - mu) * rstd * g1.y + b1.y),
-                                  pack_bf16_pair((xv[i][1].z - mu) * rstd * g1.z + b1.z, (xv[i][1].w - mu) * rstd * g1.w + b1.w));
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        qa[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[i][j]), __builtin_bit_cast(bf16x8, yb), qa[j], 0, 0, 0);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) red[(wave * 4 + j) * 64 + lane] = qa[j];
-    __syncthreads();
-    {                                            // wave w finishes column tile w: a lane holds row lr, columns 16w + 4lq ..
-      f32x4 sum = red[wave * 64 + lane];
-#pragma unroll
-      for (int w = 1; w < 4; ++w) sum += red[(w * 4 + wave) * 64 + lane];
-      *(float4*)&q_s[lr * (DH + 4) + 16 * wave + 4 * lq] = make_float4(sum[0], sum[1], sum[2], sum[3]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) {
-      const float4 q0 = *(const float4*)&q_s[lr * (DH + 4) + 32 * s2 + 8 * lq], q1 = *(const float4*)&q_s[lr * (DH + 4) + 32 * s2 + 8 * lq + 4];
-      const float v[8] = {q0.x * p.scale, q0.y * p.scale, q0.z * p.scale, q0.w * p.scale,
-                          q1.x * p.scale, q1.y * p.scale, q1.z * p.scale, q1.w * p.scale};
-      split_bf16x8(v, qhi[s2], qlo[s2]);
-    }
-  } else {
-    BPD_LOAD_KV(first)
-    const int row = r0 + (lr < nrows ? lr : nrows - 1);
-    const float* qp = p.Q + ((long)b * p.R + row) * p.d + h * DH + 8 * lq;
-    float4 qa[2][2];
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) { qa[s2][0] = *(const float4*)(qp + 32 * s2); qa[s2][1] = *(const float4*)(qp + 32 * s2 + 4); }
-    int lim0 = p.limit[b];
-    __builtin_amdgcn_sched_barrier(0);            // every global load above is in flight before the first wait
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) {
-      const float v[8] = {qa[s2][0].x * p.scale, qa[s2][0].y * p.scale, qa[s2][0].z * p.scale, qa[s2][0].w * p.scale,
-                          qa[s2][1].x * p.scale, qa[s2][1].y * p.scale, qa[s2][1].z * p.scale, qa[s2][1].w * p.scale};
-      split_bf16x8(v, qhi[s2], qlo[s2]);
-    }
-    (void)lim0;
-  }
-  int lim = p.limit[b];
-  lim = lim < 0 ? 0 : lim;
-  int nkeys = p.causal ? lim + r0 + nrows : lim;
-  nkeys = nkeys < p.cap ? nkeys : p.cap;
-  const int nvis = lr < nrows ? (p.causal ? lim + r0 + lr + 1 : lim) : 0;     // keys row lr may see: nlo .. nvis - 1
-  const int nlo = LIMF ? attn_first_key(p, lim + r0 + lr) : 0;
-  float m_run = -INFINITY, l_run = 0.f;          // of query row lr over this wave's keys (the 4 lanes of a row agree)
-  f32x4 acc[4];                                  // out^T tile dt: head dimensions 16*dt + 4*lq + r, row lr
-#pragma unroll
-  for (int dt = 0; dt < 4; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int c0 = first; c0 < nkeys; c0 += hop) {
-    const int k0 = c0 + wave * WK;               // first key of this wave in this chunk
-    // V rows of the wave -> LDS (rows past the last key as zeros: their probabilities are zero, their bits unknown)
-#pragma unroll
-    for (int x = 0; x < 8; ++x) {
-      const int kl = 8 * x + (lane >> 3);
-      const uint4 v = k0 + kl < nkeys ? vraw[x] : make_uint4(0, 0, 0, 0);
-      *(uint2*)&vs[wave][kl][8 * (lane & 7)] = make_uint2(v.x, v.y);
-      *(uint2*)&vs[wave][kl][8 * (lane & 7) + 4] = make_uint2(v.z, v.w);
-    }
-    // scores of the wave's 64 keys: sacc[kt][r] = key k0 + 16*kt + 4*lq + r against query row lr
-    f32x4 sacc[4];
-    float mx = -INFINITY;
-#pragma unroll
-    for (int kt = 0; kt < 4; ++kt) {
-      f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) {
-        const bf16x8 ka = __builtin_bit_cast(bf16x8, kf[kt][s2]);
-        a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qhi[s2], a, 0, 0, 0);
-        a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qlo[s2], a, 0, 0, 0);
-      }
-      const int kb = k0 + kt * 16 + 4 * lq;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        a[r] = (kb + r < nvis && kb + r >= nlo) ? a[r] : -INFINITY;
-        mx = fmaxf(mx, a[r]);
-      }
-      sacc[kt] = a;
-    }
-    // K fragments and V rows of this chunk have been used: the next chunk's are requested now and arrive during the
-    // softmax and the weighted-value products
-    if (c0 + hop < nkeys) BPD_LOAD_KV(c0 + hop)
-    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float m_new = fmaxf(m_run, mx);
-    const float alpha = (m_new == -INFINITY) ? 1.f : __expf(m_run - m_new);
-    float sum = 0.f;
-#pragma unroll
-    for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float pv = (m_new == -INFINITY) ? 0.f : __expf(sacc[kt][r] - m_new);
-        sacc[kt][r] = pv;
-        sum += pv;
-      }
-    sum += __shfl_xor(sum, 16, 64);
-    sum += __shfl_xor(sum, 32, 64);
-    l_run = l_run * alpha + sum;
-    m_run = m_new;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) { acc[dt][0] *= alpha; acc[dt][1] *= alpha; acc[dt][2] *= alpha; acc[dt][3] *= alpha; }
-    // weighted values: two contractions over 32 keys each.  Position 8*lq + e of the contraction is key
-    // 32*j + 4*lq + e (e < 4) or 32*j + 16 + 4*lq + e - 4 (e >= 4): what the score tiles 2j and 2j+1 hold in this lane
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const float pvv[8] = {sacc[2 * j][0], sacc[2 * j][1], sacc[2 * j][2], sacc[2 * j][3],
-                            sacc[2 * j + 1][0], sacc[2 * j + 1][1], sacc[2 * j + 1][2], sacc[2 * j + 1][3]};
-      bf16x8 phi, plo;
-      split_bf16x8(pvv, phi, plo);
-#pragma unroll
-      for (int dt = 0; dt < 4; ++dt) {
-        unsigned short vv[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) vv[e] = vs[wave][32 * j + (e < 4 ? 4 * lq + e : 16 + 4 * lq + e - 4)][16 * dt + lr];
-        const bf16x8 va = __builtin_bit_cast(bf16x8, make_uint4((unsigned)vv[0] | ((unsigned)vv[1] << 16), (unsigned)vv[2] | ((unsigned)vv[3] << 16),
-                                                                 (unsigned)vv[4] | ((unsigned)vv[5] << 16), (unsigned)vv[6] | ((unsigned)vv[7] << 16)));
-        acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, phi, acc[dt], 0, 0, 0);
-        acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, plo, acc[dt], 0, 0, 0);
-      }
-    }
-  }
-#undef BPD_LOAD_KV
-  // the four waves meet: wave w finishes head dimensions 16w .. 16w+15
-#pragma unroll
-  for (int dt = 0; dt < 4; ++dt) o_s[wave][dt][lane] = acc[dt];
-  if (lq == 0) { m_s[wave][lr] = m_run; l_s[wave][lr] = l_run; }
-  __syncthreads();
-  float M = -INFINITY;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) M = fmaxf(M, m_s[w][lr]);
-  float L = 0.f;
-  f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const float mw = m_s[w][lr];
-    const float wgt = (mw == -INFINITY) ? 0.f : __expf(mw - M);
-    L = fmaf(l_s[w][lr], wgt, L);
-    const f32x4 ow = o_s[w][wave][lane];
-    o[0] = fmaf(ow[0], wgt, o[0]); o[1] = fmaf(ow[1], wgt, o[1]); o[2] = fmaf(ow[2], wgt, o[2]); o[3] = fmaf(ow[3], wgt, o[3]);
-  }
-  const int dim = 16 * wave + 4 * lq;
-  if (p.nsplit == 1) {
-    if (lr < nrows) {
-      const float inv = 1.0f / L;
-      bf16_t* op = (bf16_t*)p.out + ((long)b * p.R + r0 + lr) * p.d + h * DH + dim;
-      *(uint2*)op = make_uint2((unsigned)f2bf(o[0] * inv) | ((unsigned)f2bf(o[1] * inv) << 16),
-                               (unsigned)f2bf(o[2] * inv) | ((unsigned)f2bf(o[3] * inv) << 16));
-    }
-  } else {
-    const int tiles = nz / p.nsplit;
-    float* part = p.part + ((((long)b * nheads + h) * tiles + tile) * p.nsplit + split) * (RT * (DH + 2));
-    *(float4*)(part + lr * DH + dim) = make_float4(o[0], o[1], o[2], o[3]);
-    if (tid < RT) { part[RT * DH + tid] = M; part[RT * DH + RT + tid] = L; }
-  }
-}
-// SLOTS: a step of a batch some of whose sequences may have ended (AttnP::seq); a kernel of its own, since looking the
-// sequence up is one more round trip ahead of the K/V loads.
-template <bool KVNT, bool LIMF, int QU, bool SLOTS>
-__device__ __forceinline__ void attention_mfma_entry(const AttnP& p, const QProjP& qp) {
-  constexpr int RT = 16, DH = 64, WK = 64, VLD = DH + 4;
-  __shared__ __attribute__((aligned(16))) bf16_t vs[4][WK][VLD];
-  __shared__ f32x4 o_s[4][4][64];
-  __shared__ float m_s[4][RT], l_s[4][RT];
-  __shared__ __attribute__((aligned(16))) float q_s[QU > 0 ? RT * (DH + 4) : 4];
-  AttnLds sm;
-  sm.vs = vs; sm.o_s = o_s; sm.m_s = m_s; sm.l_s = l_s; sm.q_s = q_s;
-  const int sb = SLOTS ? p.seq[blockIdx.y] : blockIdx.y;
-  if (SLOTS && sb < 0) return;
-  attention_mfma_body<KVNT, LIMF, QU>(p, qp, sm, blockIdx.x, blockIdx.y, sb, blockIdx.z, gridDim.x, gridDim.z, threadIdx.x);
-}
-template <bool KVNT, bool LIMF, int QU>
-__global__ __launch_bounds__(256) void attention_mfma_kernel(AttnP p, QProjP qp) { attention_mfma_entry<KVNT, LIMF, QU, false>(p, qp); }
-template <bool KVNT, bool LIMF, int QU>
-__global__ __launch_bounds__(256) void attention_mfma_slots_kernel(AttnP p, QProjP qp) { attention_mfma_entry<KVNT, LIMF, QU, true>(p, qp); }
+#include "bpd_attention.h"
+#include "bpd_row_gemm.h"
 
 // Merge of the nsplit partial results of attention_kernel: with M the largest of the partial
 // maxima, output = sum_s acc_s e^(m_s - M) / sum_s l_s e^(m_s - M).  Grid (heads, B, row tiles).
@@ -1239,8 +916,8 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(AttnP p) {
   }
   ACT* o = (ACT*)p.out + ((long)b * p.R + r0 + i) * p.d + h * DH + 4 * c4;
   if constexpr (sizeof(ACT) == 2) {
-    *(uint2*)o = make_uint2((unsigned)f2bf(num.x / den) | ((unsigned)f2bf(num.y / den) << 16),
-                            (unsigned)f2bf(num.z / den) | ((unsigned)f2bf(num.w / den) << 16));
+    *(uint2*)o = make_uint2(cvt_pk_bf16(num.x / den, num.y / den),
+                            cvt_pk_bf16(num.z / den, num.w / den));
   } else {
     o[0] = from_f<ACT>(num.x / den); o[1] = from_f<ACT>(num.y / den); o[2] = from_f<ACT>(num.z / den); o[3] = from_f<ACT>(num.w / den);
   }
@@ -1638,7 +1315,7 @@ __global__ __launch_bounds__(1024) void accept_embed_kernel(StateP s, unsigned l
     if (!per_block && lane < 16 && i < k) ((float2*)stats)[(long)tile * srows + row] = make_float2(sv, qv);
     if (i < k) {
       *(float4*)(x + (long)row * d + c0) = make_float4(v[0], v[1], v[2], v[3]);
-      if (xb) *(uint2*)(xb + (long)row * d + c0) = make_uint2((unsigned)f2bf(v[0]) | ((unsigned)f2bf(v[1]) << 16), (unsigned)f2bf(v[2]) | ((unsigned)f2bf(v[3]) << 16));
+      if (xb) *(uint2*)(xb + (long)row * d + c0) = make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
     }
   }
   if (per_block && 4 * wave < ntiles && lane < 16 && i < k) ((float2*)stats)[(long)wave * srows + row] = make_float2(bs, bq);

@@ -1,0 +1,236 @@
+// GEMMs and LayerNorms of blocks of up to 128 rows, one memory round trip per kernel.  Included by bpd_kernels.h.
+//
+// A decoding step is a chain of small dependent kernels.  A kernel that does nothing costs 1.7 us in such a chain, and
+// what the step's kernels took beyond that (2.2 .. 5.3 us) was mostly not data: four rounds of argument loads, 64-bit
+// group arithmetic and index work for epilogues not in use stood between the launch and the first load (0.75 us), the
+// LayerNorm prologue passed through two more barriers, and the LDS-staged kernel walks K in chunks, one trip each.  Here K
+// is a compile-time constant, all of it is in flight at once, addresses are one register plus constants (buffer loads, whose
+// bounds check also takes care of rows past the last one), and each epilogue is a kernel of its own.
+#pragma once
+
+enum { RG_RELU, RG_RES, RG_QKV, RG_PART };
+struct RowGemmP {
+  const void* W;                       // packed tiles
+  const void* X;                       // LN: fp32 residual stream [M][K];  otherwise bf16 [M][ldx]
+  const float* g; const float* b;      // LN: gain, bias
+  int M, ntiles, ldx, ldy;
+  const float* bias;                   // RELU, RES (null: none)
+  void* Y;                             // RELU: bf16 [M][ldy];  RES: fp32 [M][ldy], added to;  PART: fp32 [slice][M][ldy];  QKV: fp32 queries [M][K]
+  float eps;
+  int ksteps;                          // PART: k-steps of all slices
+  // QKV: columns of K each go to the queries (chunk 0), K cache (1), V cache (2), counted from chunk0
+  int chunk0, R, heads;                // R: rows per sequence
+  int capg, cap;                       // 64-wide heads: groups of 32 keys per sequence (bpd_attention.h); otherwise 0, and rows per sequence
+  bf16_t* Kc; bf16_t* Vc;
+  const int* base; const int* seq;     // first key row of each slot (null: 0) and its sequence (null: the slot; -1: none)
+};
+
+// Y = epilogue(X W) for 16 MT rows x 16 NT columns per workgroup, K = 32 * WAVES * U (PART: of one slice, grid z).  The waves
+// split K (wave w takes k-steps w U .. w U + U - 1), every load of the kernel is issued at its entry, and the waves' partial
+// sums meet in LDS once.
+// LN: X = LayerNorm(x): every wave adds up its columns of the rows, the sums meet in LDS, and the wave normalises in
+// registers the fragments it already holds.  One barrier more than without, and twice the bytes for x: 0.8 us at K = 512,
+// 1.2 us at K = 1024, against 1.9 us for a LayerNorm kernel of its own; but every column block repeats it, so that with
+// K = 1024 and more than 32 rows the kernel of its own is the faster one (lean_fuse() in bpd.hip).
+// 8 x 512 x 1536 with LayerNorm: 3.95 -> 2.84 us per kernel of a chain;  10 x 1024 x 3072: 5.6 -> 4.2;  8 x 512 x 512: 3.2 -> 2.1;
+// 10 x 1024 x 1024: 3.7 -> 2.6.  More waves (16), fewer columns per workgroup (8, 4 of a tile) and more rows (MT = 2, 3) are slower
+// except for MT = 2 with NT = 4 where one row tile would need more workgroups than there are CUs.
+template <int WAVES, int U, int MT, int NT, bool LN, int EPI>
+__global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
+  constexpr int KSTEPS = WAVES * U, K = 32 * KSTEPS, TILES = MT * NT, OWN = (TILES + WAVES - 1) / WAVES, XB = LN ? 4 : 2;
+  __shared__ f32x4 red[WAVES * TILES * 64];
+  __shared__ float2 st[LN ? WAVES * 16 * MT : 1];
+  __shared__ __attribute__((aligned(16))) float gb[LN ? WAVES * U * 64 : 4];       // per wave: gain, bias of its columns
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 15, lq = lane >> 4;
+  const int m0 = blockIdx.y * (16 * MT), tile0 = blockIdx.x * NT;
+  const int ksteps = EPI == RG_PART ? p.ksteps : KSTEPS, ks0 = (EPI == RG_PART ? (int)blockIdx.z * KSTEPS : 0) + wave * U;
+  u32x4 a[NT][U];
+#pragma unroll
+  for (int u = 0; u < NT; ++u) {
+    const int tile = NT > 1 && tile0 + u >= p.ntiles ? p.ntiles - 1 : tile0 + u;
+    const char* Wb = (const char*)p.W + ((size_t)tile * ksteps + ks0) * 1024;
+#pragma unroll
+    for (int i = 0; i < U; ++i) a[u][i] = *(const u32x4*)(Wb + i * 1024 + lane * 16);
+  }
+  const int ldx = LN ? K : p.ldx;
+  const rsrc_t xr = rsrc_of(p.X, (unsigned)p.M * ldx * XB);
+  u32x4 xv[MT][U][LN ? 2 : 1];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    const unsigned off = ((m0 + t * 16 + lr) * ldx + ks0 * 32 + lq * 8) * XB;
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      xv[t][i][0] = buf_load16(xr, off + i * (32 * XB), 0);
+      if constexpr (LN) xv[t][i][1] = buf_load16(xr, off + i * (32 * XB) + 16, 0);
+    }
+  }
+  f32x4 gbv;
+  if constexpr (LN) gbv = *(const f32x4*)((lane % (U * 16) < U * 8 ? p.g : p.b) + ks0 * 32 + (lane % (U * 8)) * 4);
+  // operands of the epilogue, for the tiles that this wave finishes
+  f32x4 bias[OWN], res[OWN];
+  int key0[OWN], sb[OWN];
+#pragma unroll
+  for (int j = 0; j < OWN; ++j) {
+    const int id = wave + WAVES * j;
+    if (id >= TILES) continue;
+    const int tile = tile0 + id % NT, n = (NT > 1 && tile >= p.ntiles ? p.ntiles - 1 : tile) * 16 + lq * 4, m = m0 + (id / NT) * 16 + lr;
+    if constexpr (EPI == RG_RELU || EPI == RG_RES) bias[j] = p.bias ? *(const f32x4*)(p.bias + n) : f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (EPI == RG_RES) res[j] = __builtin_bit_cast(f32x4, buf_load16(rsrc_of(p.Y, (unsigned)p.M * p.ldy * 4), (m * p.ldy + n) * 4, 0));
+    if constexpr (EPI == RG_QKV) {
+      const int mm = m < p.M ? m : 0, q = (int)(((float)mm + 0.5f) * __builtin_amdgcn_rcpf((float)p.R));      // mm / R (mm < 2^16: exact)
+      sb[j] = p.seq ? p.seq[q] : q;
+      key0[j] = (p.base ? p.base[q] : 0) + mm - q * p.R;
+      if (!p.capg) key0[j] += q * p.cap;         // (slots: cap is 0 and base counts rows over all sequences)
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  f32x4 acc[MT][NT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t)
+#pragma unroll
+    for (int u = 0; u < NT; ++u) acc[t][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if constexpr (LN) {
+    float* gw = gb + wave * (U * 64);            // written and read by this wave alone: no barrier
+    if (lane < U * 16) *(f32x4*)(gw + lane * 4) = gbv;
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      float s = 0.f, q = 0.f;
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const f32x4 v = __builtin_bit_cast(f32x4, xv[t][i][h]);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) { s += v[r]; q = fmaf(v[r], v[r], q); }
+        }
+      s = sum_rows(s); q = sum_rows(q);
+      if (lq == 0) st[(wave * MT + t) * 16 + lr] = make_float2(s, q);
+    }
+    __syncthreads();
+    f32x4 g4[U][2], b4[U][2];
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        g4[i][h] = *(const f32x4*)(gw + i * 32 + lq * 8 + 4 * h);
+        b4[i][h] = *(const f32x4*)(gw + U * 32 + i * 32 + lq * 8 + 4 * h);
+      }
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      float s = 0.f, q = 0.f;
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) { const float2 v = st[(w * MT + t) * 16 + lr]; s += v.x; q += v.y; }
+      float mu, rs;
+      row_moments(s, q, 1.f / K, p.eps, mu, rs);
+      const float nmr = -mu * rs;
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        float y[8];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const f32x4 v = __builtin_bit_cast(f32x4, xv[t][i][h]);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) y[4 * h + r] = fmaf(fmaf(v[r], rs, nmr), g4[i][h][r], b4[i][h][r]);
+        }
+        const u32x4 yb = u32x4{cvt_pk_bf16(y[0], y[1]), cvt_pk_bf16(y[2], y[3]), cvt_pk_bf16(y[4], y[5]), cvt_pk_bf16(y[6], y[7])};
+#pragma unroll
+        for (int u = 0; u < NT; ++u)
+          acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[u][i]), __builtin_bit_cast(bf16x8, yb), acc[t][u], 0, 0, 0);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+#pragma unroll
+      for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int u = 0; u < NT; ++u)
+          acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[u][i]), __builtin_bit_cast(bf16x8, xv[t][i][0]), acc[t][u], 0, 0, 0);
+  }
+#pragma unroll
+  for (int t = 0; t < MT; ++t)
+#pragma unroll
+    for (int u = 0; u < NT; ++u) red[(wave * TILES + t * NT + u) * 64 + lane] = acc[t][u];
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < OWN; ++j) {
+    const int id = wave + WAVES * j;
+    if (id >= TILES) continue;
+    f32x4 v = red[id * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) v += red[(w * TILES + id) * 64 + lane];
+    const int tile = tile0 + id % NT, n = tile * 16 + lq * 4, m = m0 + (id / NT) * 16 + lr;
+    if (NT > 1 && tile >= p.ntiles) continue;
+    if (m >= p.M) continue;
+    if constexpr (EPI == RG_RELU) {
+      v += bias[j];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.f);
+      *(u32x2*)((bf16_t*)p.Y + (size_t)m * p.ldy + n) = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
+    } else if constexpr (EPI == RG_RES) {
+      v += bias[j];
+      v += res[j];
+      *(f32x4*)((float*)p.Y + (size_t)m * p.ldy + n) = v;
+    } else if constexpr (EPI == RG_PART) {
+      *(f32x4*)((float*)p.Y + ((size_t)blockIdx.z * p.M + m) * p.ldy + n) = v;
+    } else {
+      const int c = tile / (K / 16), col = n - c * K;
+      if (c + p.chunk0 == 0) {
+        *(f32x4*)((float*)p.Y + (size_t)m * K + col) = v;
+      } else if (sb[j] >= 0) {                   // (a slot behind the last one has no cache rows)
+        bf16_t* cache = c + p.chunk0 == 1 ? p.Kc : p.Vc;
+        const unsigned lo = cvt_pk_bf16(v[0], v[1]), hi = cvt_pk_bf16(v[2], v[3]);
+        if (p.capg) kv_frag_store(cache, c + p.chunk0 == 2, sb[j], p.heads, p.capg, key0[j], col, lo, hi);
+        else *(u32x2*)(cache + (size_t)key0[j] * K + col) = u32x2{lo, hi};
+      }
+    }
+  }
+}
+
+// LayerNorm of one row of D columns per workgroup.  NSL > 0: x is the sum of itself, a bias and NSL raw K slices of a split
+// GEMM, in this order of slices, and is stored.  One load of everything, one barrier: 1.9 us in a chain of kernels where one
+// wave per row took 4.2 us (D = 512, 80 rows) .. 5.2 us (D = 1024, 8 slices).
+constexpr int ln_row_threads(int D) { return D < 256 ? 64 : D / 4; }
+template <int D, int NSL>
+__global__ __launch_bounds__(ln_row_threads(D)) void ln_row_kernel(float* x, const float* g, const float* b, int M, float eps, bf16_t* ya, float* yf,
+                                                                   const float* part, const float* pbias) {
+  constexpr int WAVES = ln_row_threads(D) / 64;
+  __shared__ float2 st[WAVES];
+  const int tid = threadIdx.x;
+  const bool in = 4 * tid < D;                   // (D < 256: the last lanes hold zeros)
+  const size_t at = (size_t)blockIdx.x * D + (in ? 4 * tid : 0);
+  f32x4 v = *(const f32x4*)(x + at);
+  f32x4 pv[NSL > 0 ? NSL : 1], pb;
+  if constexpr (NSL > 0) {
+#pragma unroll
+    for (int i = 0; i < NSL; ++i) pv[i] = *(const f32x4*)(part + (size_t)i * M * D + at);
+    pb = *(const f32x4*)(pbias + (in ? 4 * tid : 0));
+  }
+  const f32x4 gv = *(const f32x4*)(g + (in ? 4 * tid : 0)), bv = *(const f32x4*)(b + (in ? 4 * tid : 0));
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (NSL > 0) {
+#pragma unroll
+    for (int i = 1; i < NSL; ++i) pv[0] += pv[i];
+    v += pv[0] + pb;
+    if (in) *(f32x4*)(x + at) = v;
+  }
+  if (!in) v = f32x4{0.f, 0.f, 0.f, 0.f};
+  float s = (v[0] + v[1]) + (v[2] + v[3]), q = (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
+  s = wave_sum(s); q = wave_sum(q);
+  if constexpr (WAVES > 1) {
+    if ((tid & 63) == 0) st[tid >> 6] = make_float2(s, q);
+    __syncthreads();
+    s = 0.f; q = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) { s += st[w].x; q += st[w].y; }
+  }
+  float mu, rs;
+  row_moments(s, q, 1.f / D, eps, mu, rs);
+  const float nmr = -mu * rs;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) v[r] = fmaf(fmaf(v[r], rs, nmr), gv[r], bv[r]);
+  if (!in) return;
+  if (ya) *(u32x2*)(ya + at) = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
+  if (yf) *(f32x4*)(yf + at) = v;
+}

@@ -33,8 +33,8 @@ struct StackLayerP {
   const void *wqkv, *wo, *cq, *co, *w1, *w2;             // packed bf16 tiles [n/16][k/32][64][8]
   const float *ln1g, *ln1b, *ln2g, *ln2b, *ln3g, *ln3b;
   const float *b1, *b2;
-  void *selfK, *selfV;                                    // [B][slots][d] bf16
-  const void *crossK, *crossV;                            // [B][max_src][d] bf16
+  void *selfK, *selfV;                                    // caches in operand order (bpd_attention.h)
+  const void *crossK, *crossV;
 };
 struct StackP {
   const StackLayerP* L;                                   // [n_layers], in device memory (a table in the kernel arguments
@@ -225,7 +225,7 @@ __device__ __forceinline__ void stack_stage_ln(const StackP& p, const float* x, 
         if (idx < n4) {
           const float y0 = (xv[rs][i].x - mu) * rstd * gv[i].x + bv[i].x, y1 = (xv[rs][i].y - mu) * rstd * gv[i].y + bv[i].y;
           const float y2 = (xv[rs][i].z - mu) * rstd * gv[i].z + bv[i].z, y3 = (xv[rs][i].w - mu) * rstd * gv[i].w + bv[i].w;
-          *(uint2*)(xs + (long)r * (d + 8) + 4 * idx) = make_uint2((unsigned)f2bf(y0) | ((unsigned)f2bf(y1) << 16), (unsigned)f2bf(y2) | ((unsigned)f2bf(y3) << 16));
+          *(uint2*)(xs + (long)r * (d + 8) + 4 * idx) = make_uint2(cvt_pk_bf16(y0, y1), cvt_pk_bf16(y2, y3));
         }
       }
     }
@@ -301,12 +301,12 @@ struct StackHelperV {
     stamp(inst, 1);
     AttnP ap{};
     ap.Q = (const float*)(e + (self ? ex.q : ex.q2)); ap.Kc = self ? l.selfK : l.crossK; ap.Vc = self ? l.selfV : l.crossV;
-    ap.out = e + (self ? ex.attn : ex.attn2); ap.cap = self ? p.slots : p.max_src; ap.kv_seq_stride = (long)ap.cap * p.d;
+    ap.out = e + (self ? ex.attn : ex.attn2); ap.cap = self ? p.slots : p.max_src; ap.capg = (ap.cap + 31) >> 5;
     ap.d = p.d; ap.R = p.R; ap.limit = self ? p.Lbase : p.src_len; ap.causal = self ? 1 : 0; ap.scale = p.scale;
     ap.local_q = 0; ap.local_m = 0; ap.nsplit = 1; ap.part = nullptr;
     const AttnLds sm = AttnLds::carve(smem);
     for (int item = rank; item < p.heads * p.B; item += p.workers)       // one workgroup barrier inside each
-      attention_mfma_body<false, false, 0>(ap, QProjP{}, sm, item % p.heads, item / p.heads, item / p.heads, 0, p.heads, 1, helper_tid());
+      attention_mfma_body<4, false, false, 0>(ap, QProjP{}, sm, item % p.heads, item / p.heads, item / p.heads, 0, p.heads, 1, helper_tid());
     stamp(inst, 5);
     signal(inst);
     stamp(inst, 6);
@@ -375,9 +375,7 @@ struct StackHelperV {
           if (n < d) *(float4*)((float*)(e + ex.q) + (long)m * d + n) = make_float4(v[0], v[1], v[2], v[3]);
           else {
             const int b = m / p.R, i = m - b * p.R, col = n < 2 * d ? n - d : n - 2 * d;
-            const long row = (long)b * p.slots + p.Lbase[b] + i;
-            bf16_t* dst = (bf16_t*)(n < 2 * d ? l.selfK : l.selfV);
-            *(uint2*)(dst + row * d + col) = make_uint2((unsigned)f2bf(v[0]) | ((unsigned)f2bf(v[1]) << 16), (unsigned)f2bf(v[2]) | ((unsigned)f2bf(v[3]) << 16));
+            kv_frag_store((bf16_t*)(n < 2 * d ? l.selfK : l.selfV), n >= 2 * d, b, p.heads, (p.slots + 31) >> 5, p.Lbase[b] + i, col, cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
           }
         }
       } else if (op == 3) {
@@ -386,8 +384,8 @@ struct StackHelperV {
         const float4 bs = pre_bias[j];
         if (live)
           *(uint2*)((bf16_t*)(e + ex.ffh) + (long)m * F + n) =
-              make_uint2((unsigned)f2bf(fmaxf(v[0] + bs.x, 0.f)) | ((unsigned)f2bf(fmaxf(v[1] + bs.y, 0.f)) << 16),
-                         (unsigned)f2bf(fmaxf(v[2] + bs.z, 0.f)) | ((unsigned)f2bf(fmaxf(v[3] + bs.w, 0.f)) << 16));
+              make_uint2(cvt_pk_bf16(fmaxf(v[0] + bs.x, 0.f), fmaxf(v[1] + bs.y, 0.f)),
+                         cvt_pk_bf16(fmaxf(v[2] + bs.z, 0.f), fmaxf(v[3] + bs.w, 0.f)));
       } else {                                             // residual updates
         float* Y = op == 2 ? (float*)(e + ex.x1) : (op == 5 ? (float*)(e + ex.x2) : x_after(layer));
         const float4 rv = pre_res[j];
