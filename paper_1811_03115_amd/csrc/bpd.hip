@@ -574,6 +574,11 @@ int attention_nsplit(const bpd_ctx* ctx, int cap, int B, int R, int causal) {
   return attention_nsplit_of(ctx->cfg, (long)ctx->steps, ctx->local_q, ctx->local_m, cap, B, R, causal);
 }
 
+// keys of a sequence as far as the host knows a bound
+long attention_keys(const bpd_ctx* ctx, int cap, int R, int causal) {
+  return causal ? std::min<long>(cap, (long)ctx->steps * ctx->cfg.k_max + 1 + R) : cap;
+}
+
 // Cross-attention whose query projection runs inside the attention kernel: LayerNorm statistics of x at hand (the
 // caller checks), at most 16 rows per sequence, 64-wide heads, d = 128 / 256 / 512 / 1024, one workgroup per (head,
 // sequence) and few enough of them that each streaming its head's 128 d bytes of weights beats one GEMM doing it once.
@@ -608,8 +613,12 @@ void attention(bpd_ctx* ctx, const float* Q, const void* Kc, const void* Vc, voi
       // (a split launch walks a long cache, where nearly all fetched rows are in use: measured slower with the extra round trip)
       // (local attention: where the keys start depends on the length, so it is always read first)
       const bool limf = (nsplit == 1 && wgs >= ATTN_LIMF_MIN_WGS) || local;
-#define BPD_ATTN(A_, B_, QU_) { if (seq) hipLaunchKernelGGL((attention_mfma_slots_kernel<A_, B_, QU_>), grid, dim3(64 * attn_waves(QU_)), 0, ctx->stream, p, qp_); \
-                                else hipLaunchKernelGGL((attention_mfma_kernel<A_, B_, QU_>), grid, dim3(64 * attn_waves(QU_)), 0, ctx->stream, p, qp_); }
+#define BPD_ATTN(A_, B_, QU_) { if (seq) hipLaunchKernelGGL((attention_mfma_slots_kernel<A_, B_, QU_>), grid, dim3(64 * (QU_ > 0 ? ATTN_WAVES : waves)), 0, ctx->stream, p, qp_); \
+                                else hipLaunchKernelGGL((attention_mfma_kernel<A_, B_, QU_>), grid, dim3(64 * (QU_ > 0 ? ATTN_WAVES : waves)), 0, ctx->stream, p, qp_); }
+      // up to 128 keys: four waves; more: eight, or four with two groups each where there are many workgroups or where the keys
+      // are dealt to several of them (8 x 8 heads, 3072 keys: 97 ms per decode, 110 with one group each)
+      const bool few = attention_keys(ctx, cap, R, causal) <= 128, two = !few && (limf || nsplit > 1);
+      const int waves = few || two ? 4 : ATTN_WAVES;
       const QProjP qp_ = qproj ? *qproj : QProjP{};
       if (qproj) {                               // queries projected in the kernel (attention_qproj_ok() holds)
         switch (c.d_model / 128) {
@@ -620,10 +629,11 @@ void attention(bpd_ctx* ctx, const float* Q, const void* Kc, const void* Vc, voi
         }
         return;
       }
-      if (causal && kv_bytes > ((size_t)128 << 20)) {
-        if (limf) BPD_ATTN(true, true, 0) else BPD_ATTN(true, false, 0)
+      const bool nt = causal && kv_bytes > ((size_t)128 << 20);
+      if (two) {
+        if (nt && limf) BPD_ATTN(true, true, -1) else if (nt) BPD_ATTN(true, false, -1) else if (limf) BPD_ATTN(false, true, -1) else BPD_ATTN(false, false, -1)
       } else {
-        if (limf) BPD_ATTN(false, true, 0) else BPD_ATTN(false, false, 0)
+        if (nt && limf) BPD_ATTN(true, true, 0) else if (nt) BPD_ATTN(true, false, 0) else if (limf) BPD_ATTN(false, true, 0) else BPD_ATTN(false, false, 0)
       }
 #undef BPD_ATTN
       if (nsplit > 1) launch_combine<bf16_t, 64>(p, cgrid, ctx->stream);

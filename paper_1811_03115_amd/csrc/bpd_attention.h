@@ -51,21 +51,21 @@ struct QProjP {
   float eps;
 };
 
-// LDS of one attention workgroup: the kernel below declares it; a caller that runs the body from inside another kernel
-// carves it out of its own LDS.
-template <int NW>
-struct AttnLdsT {
+// LDS of one attention workgroup of up to ATTN_WAVES waves: the kernel below declares it; a caller that runs the body from
+// inside another kernel carves it out of its own LDS (four waves, QU == 0).
+constexpr int ATTN_WAVES = 8;
+struct AttnLds {
   static constexpr int RT = 16, DH = 64;
-  f32x4 (*o_s)[4][64];        // [NW][4][64]  per wave and output tile: un-normalised out^T
-  float (*m_s)[RT];           // [NW][RT]     per wave: running maximum per query row
-  float (*l_s)[RT];           // [NW][RT]     ... and sum
-  float* q_s;                 // QU > 0: [RT * (DH + 4)] projected queries
+  f32x4 (*o_s)[4][64];        // [waves][4][64]  per wave and output tile: un-normalised out^T
+  float (*m_s)[RT];           // [waves][RT]     per wave: running maximum per query row
+  float (*l_s)[RT];           // [waves][RT]     ... and sum
+  u32x2* q_s;                 // QU > 0: [hi, lo][2][64][2] projected queries as MFMA operands
   float* gb_s;                // QU > 0: per wave, gain and bias of its columns; and the row sums of x
   float2* st_s;
-  static constexpr size_t OS_BYTES = (size_t)NW * 4 * 64 * 16, ML_BYTES = (size_t)NW * RT * 4;
-  static constexpr size_t BYTES = OS_BYTES + 2 * ML_BYTES;        // QU == 0
-  __device__ static AttnLdsT carve(unsigned char* base) {         // (16-byte aligned base), QU == 0 layout
-    AttnLdsT s;
+  static constexpr size_t OS_BYTES = (size_t)4 * 4 * 64 * 16, ML_BYTES = (size_t)4 * RT * 4;
+  static constexpr size_t BYTES = OS_BYTES + 2 * ML_BYTES;        // four waves, QU == 0
+  __device__ static AttnLds carve(unsigned char* base) {          // (16-byte aligned base)
+    AttnLds s;
     s.o_s = (f32x4 (*)[4][64])base;
     s.m_s = (float (*)[RT])(base + OS_BYTES);
     s.l_s = (float (*)[RT])(base + OS_BYTES + ML_BYTES);
@@ -73,15 +73,30 @@ struct AttnLdsT {
     return s;
   }
 };
-typedef AttnLdsT<4> AttnLds;
 
-// One (head h, sequence b (in the K/V buffer: sb), z = row tile * nsplit + split) item of the attention, run by NW whole
-// waves (tid 0 .. 64 NW - 1) that share `sm`; nheads / nz: the extents the partial-result layout is indexed with.  Every
+// Largest maximum M, sum L and values o (both relative to M) of NW waves' results for row lane % 16, output tile dt
+template <int NW>
+__device__ __forceinline__ void attention_merge(const AttnLds& sm, int dt, int lane, float& M, float& L, f32x4& o) {
+  float mw[NW];
+  M = -INFINITY; L = 0.f;
+  o = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < NW; ++w) { mw[w] = sm.m_s[w][lane & 15]; M = fmaxf(M, mw[w]); }
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const float wgt = (mw[w] == -INFINITY) ? 0.f : __expf(mw[w] - M);
+    L = fmaf(sm.l_s[w][lane & 15], wgt, L);
+    o += sm.o_s[w][dt][lane] * wgt;
+  }
+}
+
+// One (head h, sequence b (in the K/V buffer: sb), z = row tile * nsplit + split) item of the attention, run by nw whole
+// waves (tid 0 .. 64 nw - 1) that share `sm`; nheads / nz: the extents the partial-result layout is indexed with.  Every
 // __syncthreads() inside is reached by all of them; a caller whose workgroup has more waves makes those arrive at as many
 // barriers (one with QU == 0, four with QU > 0).
-// The waves split the keys: of every chunk of 256 keys wave w takes the groups w, w + NW, .. of 32 keys (interleaved, so
-// that short caches keep all waves busy) and keeps its own running maximum, sum and weighted values in registers; the
-// waves' results meet once, in LDS, at the end.  Per group
+// The waves split the keys: of every nw groups of 32 keys each takes one (QU < 0: two of every 2 nw, for long caches: fewer rounds,
+// more loads in flight), and keeps its own running maximum, sum and
+// weighted values in registers; the results of the waves that had keys meet once, in LDS, at the end.  Per group
 //   scores^T = K Q^T     keys are the 16-wide "feature" side of the MFMA, the <= 16 query rows the other
 //   softmax              maximum and sum in the lane, then across the 4 lanes of a row; the probabilities stay in
 //                        registers: as they lie they are the second MFMA operand of a contraction over the 32 keys
@@ -93,11 +108,14 @@ typedef AttnLdsT<4> AttnLds;
 // not evict the weights).
 // LIMF: the sequence's length is fetched first and only groups that hold keys are fetched: one more dependent round trip
 // (many sequences: the traffic is what counts; local attention: where the keys start depends on it).
-template <int NW, bool KVNT, bool LIMF, int QU>
-__device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP& qp, const AttnLdsT<NW>& sm, int h, int b, int sb, int z,
-                                                    int nheads, int nz, int tid) {
-  constexpr int RT = 16, DH = 64, G = 8 / NW;
-  const int split = z % p.nsplit, tile = z / p.nsplit, r0 = tile * RT;
+// ARGS: p lies in the kernel's arguments.
+template <bool KVNT, bool LIMF, int QU, bool ARGS>
+__device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP& qp, const AttnLds& sm, int h, int b, int sb, int z,
+                                                    int nheads, int nz, int tid, int nw) {
+  constexpr int RT = 16, DH = 64, G = QU < 0 ? 2 : 1;       // groups of keys per wave and round
+  int split = 0, tile = z;
+  if (p.nsplit > 1) { tile = z / p.nsplit; split = z - tile * p.nsplit; }
+  const int r0 = tile * RT;
   const int nrows = min(RT, p.R - r0);
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lq = lane >> 4;
@@ -111,13 +129,13 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
     glim = g0 < glim ? g0 : glim;
     gbeg = attn_first_key(p, l0 + r0) >> 5;
   }
-  const int first = gbeg + split * 8, hop = p.nsplit * 8;
+  const int first = gbeg + split * (G * nw), hop = p.nsplit * (G * nw);
   const rsrc_t kr = rsrc_of((const bf16_t*)p.Kc + head_at, (unsigned)glim * (KV_GROUP * 2));
   const rsrc_t vr = rsrc_of((const bf16_t*)p.Vc + head_at, (unsigned)glim * (KV_GROUP * 2));
   u32x4 kf[G][4], vf[G][4];                      // K: [tile][half of the dimensions], V: [16 dimensions]
 #define BPD_LOAD_KV(c)                                                                          \
   _Pragma("unroll") for (int gg = 0; gg < G; ++gg) {                                            \
-    const unsigned at_ = (unsigned)((c) + wave + NW * gg) * (KV_GROUP * 2);                     \
+    const unsigned at_ = (unsigned)((c) + wave + gg * nw) * (KV_GROUP * 2);                     \
     _Pragma("unroll") for (int x = 0; x < 4; ++x)                                               \
       kf[gg][x] = __builtin_amdgcn_raw_buffer_load_b128(kr, lane * 16 + x * 1024, at_, KVNT ? 2 : 0); \
     _Pragma("unroll") for (int x = 0; x < 4; ++x)                                               \
@@ -126,17 +144,13 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
   // queries: row lr (zeros beyond the last), head dimensions 32s + 8*lq .. +8, scaled, as bf16 hi + lo
   bf16x8 qhi[2], qlo[2];
   int lim;
+  bf16_t* out;
   if constexpr (QU > 0) {
-    static_assert(NW == 8, "k-steps over eight waves");
-    constexpr int K = 128 * QU, KSTEPS = K / 32, U = (KSTEPS + NW - 1) / NW;
+    constexpr int NW = ATTN_WAVES, K = 128 * QU, KSTEPS = K / 32, U = (KSTEPS + NW - 1) / NW;
     const bool mine = wave * U < KSTEPS;         // (K = 128: four waves have k-steps)
     const int ks0 = mine ? wave * U : 0;
-    // every global load of the kernel is issued before the first wait
+    // every global load of the kernel is issued before the first wait, in the order in which they are used
     u32x4 wf[4][U], xv[U][2];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int i = 0; i < U; ++i) wf[j][i] = *(const u32x4*)((const char*)qp.W + ((size_t)(4 * h + j) * KSTEPS + ks0 + i) * 1024 + lane * 16);
     {
       const rsrc_t xr = rsrc_of(qp.x + (size_t)b * p.R * K, mine ? (unsigned)p.R * K * 4 : 0);
       const unsigned off = (lr * K + ks0 * 32 + lq * 8) * 4;
@@ -144,8 +158,14 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
       for (int i = 0; i < U; ++i) { xv[i][0] = buf_load16(xr, off + i * 128, 0); xv[i][1] = buf_load16(xr, off + i * 128 + 16, 0); }
     }
     const f32x4 gbv = *(const f32x4*)((lane % (U * 16) < U * 8 ? qp.g : qp.b) + ks0 * 32 + (lane % (U * 8)) * 4);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int i = 0; i < U; ++i) wf[j][i] = *(const u32x4*)((const char*)qp.W + ((size_t)(4 * h + j) * KSTEPS + ks0 + i) * 1024 + lane * 16);
     BPD_LOAD_KV(first)
     lim = p.limit[b];
+    out = (bf16_t*)p.out;
+    if (ARGS) out = arg_now(out);
     __builtin_amdgcn_sched_barrier(0);
     float* gw = sm.gb_s + wave * (U * 64);
     if (lane < U * 16) *(f32x4*)(gw + lane * 4) = gbv;
@@ -198,14 +218,20 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
       f32x4 sum = red[wave * 64 + lane];
 #pragma unroll
       for (int w = 1; w < NW; ++w) sum += red[(w * 4 + wave) * 64 + lane];
-      *(f32x4*)&sm.q_s[lr * (DH + 4) + 16 * wave + 4 * lq] = sum * p.scale;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sum[r] *= p.scale;       // (one by one: as a vector product the compiler keeps p.scale in scratch memory)
+      const u32x2 hi = u32x2{cvt_pk_bf16(sum[0], sum[1]), cvt_pk_bf16(sum[2], sum[3])};
+      const u32x2 lo = u32x2{cvt_pk_bf16(sum[0] - __uint_as_float(hi[0] << 16), sum[1] - __uint_as_float(hi[0] & 0xFFFF0000u)),
+                             cvt_pk_bf16(sum[2] - __uint_as_float(hi[1] << 16), sum[3] - __uint_as_float(hi[1] & 0xFFFF0000u))};
+      // operand lane 16 q + lr of half s holds columns 32 s + 8 q .. + 7
+      const int at = ((wave >> 1) * 64 + ((wave & 1) * 2 + (lq >> 1)) * 16 + lr) * 2 + (lq & 1);
+      sm.q_s[at] = hi; sm.q_s[256 + at] = lo;
     }
     __syncthreads();
 #pragma unroll
     for (int s2 = 0; s2 < 2; ++s2) {
-      const f32x4 q0 = *(const f32x4*)&sm.q_s[lr * (DH + 4) + 32 * s2 + 8 * lq], q1 = *(const f32x4*)&sm.q_s[lr * (DH + 4) + 32 * s2 + 8 * lq + 4];
-      const float v[8] = {q0[0], q0[1], q0[2], q0[3], q1[0], q1[1], q1[2], q1[3]};
-      split_bf16x8(v, qhi[s2], qlo[s2]);
+      qhi[s2] = __builtin_bit_cast(bf16x8, *(const u32x4*)&sm.q_s[(s2 * 64 + lane) * 2]);
+      qlo[s2] = __builtin_bit_cast(bf16x8, *(const u32x4*)&sm.q_s[256 + (s2 * 64 + lane) * 2]);
     }
   } else {
     const rsrc_t qr = rsrc_of(p.Q + ((size_t)b * p.R + r0) * p.d, (unsigned)nrows * p.d * 4);
@@ -215,11 +241,13 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
     for (int s2 = 0; s2 < 2; ++s2) { qa[s2][0] = buf_load16(qr, off + s2 * 128, 0); qa[s2][1] = buf_load16(qr, off + s2 * 128 + 16, 0); }
     BPD_LOAD_KV(first)
     lim = p.limit[b];
+    out = (bf16_t*)p.out;
+    if (ARGS) out = arg_now(out);
     __builtin_amdgcn_sched_barrier(0);            // every global load above is in flight before the first wait
 #pragma unroll
     for (int s2 = 0; s2 < 2; ++s2) {
-      const f32x4 q0 = __builtin_bit_cast(f32x4, qa[s2][0]) * p.scale, q1 = __builtin_bit_cast(f32x4, qa[s2][1]) * p.scale;
-      const float v[8] = {q0[0], q0[1], q0[2], q0[3], q1[0], q1[1], q1[2], q1[3]};
+      const f32x4 q0 = __builtin_bit_cast(f32x4, qa[s2][0]), q1 = __builtin_bit_cast(f32x4, qa[s2][1]);
+      const float v[8] = {q0[0] * p.scale, q0[1] * p.scale, q0[2] * p.scale, q0[3] * p.scale, q1[0] * p.scale, q1[1] * p.scale, q1[2] * p.scale, q1[3] * p.scale};
       split_bf16x8(v, qhi[s2], qlo[s2]);
     }
   }
@@ -234,12 +262,11 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
 #pragma unroll
   for (int dt = 0; dt < 4; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int c = first; c + wave < ngr; c += hop) {
-    // scores of the wave's groups: sacc[gg][t][r] = key 32 (c + wave + NW gg) + 8 lq + 4 t + r against query row lr
+    // scores: sacc[gg][t][r] = key 32 (c + wave + gg nw) + 8 lq + 4 t + r against query row lr
     f32x4 sacc[G][2];
     float mx = -INFINITY;
 #pragma unroll
-    for (int gg = 0; gg < G; ++gg) {
-      const int kb = 32 * (c + wave + NW * gg) + 8 * lq;
+    for (int gg = 0; gg < G; ++gg)
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -251,13 +278,12 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int key = kb + 4 * t + r;
+          const int key = 32 * (c + wave + gg * nw) + 8 * lq + 4 * t + r;
           a[r] = (key < nvis && (!LIMF || key >= nlo)) ? a[r] : -INFINITY;
           mx = fmaxf(mx, a[r]);
         }
         sacc[gg][t] = a;
       }
-    }
     mx = max_rows(mx);
     const float m_new = fmaxf(m_run, mx);
     const float alpha = (m_new == -INFINITY) ? 1.f : __expf(m_run - m_new);
@@ -279,15 +305,14 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
     for (int dt = 0; dt < 4; ++dt) acc[dt] *= alpha;
 #pragma unroll
     for (int gg = 0; gg < G; ++gg) {
-      const int g0 = 32 * (c + wave + NW * gg);
-      if (g0 >= nkeys) continue;                 // (the same for the whole wave)
+      const int g0 = 32 * (c + wave + gg * nw);
+      if (G > 1 && g0 >= nkeys) continue;        // (the same for the whole wave)
       if (g0 + 32 > nkeys) {                     // values of keys past the last one: their probabilities are zero, their bits unknown
         const int left = nkeys - g0 - 8 * lq;    // of this lane's eight
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-          for (int w = 0; w < 4; ++w)
-            vf[gg][dt][w] = left > 2 * w + 1 ? vf[gg][dt][w] : (left > 2 * w ? vf[gg][dt][w] & 0xFFFFu : 0u);
+          for (int w = 0; w < 4; ++w) vf[gg][dt][w] = left > 2 * w + 1 ? vf[gg][dt][w] : (left > 2 * w ? vf[gg][dt][w] & 0xFFFFu : 0u);
       }
       const float pv[8] = {sacc[gg][0][0], sacc[gg][0][1], sacc[gg][0][2], sacc[gg][0][3], sacc[gg][1][0], sacc[gg][1][1], sacc[gg][1][2], sacc[gg][1][3]};
       bf16x8 phi, plo;
@@ -302,29 +327,23 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
     if (c + hop + wave < ngr) BPD_LOAD_KV(c + hop)
   }
 #undef BPD_LOAD_KV
-  // the waves meet: wave w (of the first four) finishes head dimensions 16w .. 16w+15
+  // the waves meet (those without keys bring zeros): wave w of the first four finishes head dimensions 16w .. 16w+15
 #pragma unroll
   for (int dt = 0; dt < 4; ++dt) sm.o_s[wave][dt][lane] = acc[dt];
   if (lq == 0) { sm.m_s[wave][lr] = m_run; sm.l_s[wave][lr] = l_run; }
   __syncthreads();
   if (wave >= 4) return;
-  float mw[NW], M = -INFINITY;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) { mw[w] = sm.m_s[w][lr]; M = fmaxf(M, mw[w]); }
-  float L = 0.f;
-  f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    const float wgt = (mw[w] == -INFINITY) ? 0.f : __expf(mw[w] - M);
-    L = fmaf(sm.l_s[w][lr], wgt, L);
-    const f32x4 ow = sm.o_s[w][wave][lane];
-    o[0] = fmaf(ow[0], wgt, o[0]); o[1] = fmaf(ow[1], wgt, o[1]); o[2] = fmaf(ow[2], wgt, o[2]); o[3] = fmaf(ow[3], wgt, o[3]);
-  }
+  float M, L;
+  f32x4 o;
+  if (QU <= 0 && (QU < 0 || nw == 4)) attention_merge<4>(sm, wave, lane, M, L, o);
+  else if (QU > 0 && ngr - first <= 1) { M = sm.m_s[0][lr]; L = sm.l_s[0][lr]; o = sm.o_s[0][wave][lane]; }
+  else attention_merge<ATTN_WAVES>(sm, wave, lane, M, L, o);
   const int dim = 16 * wave + 4 * lq;
   if (p.nsplit == 1) {
     if (lr < nrows) {
-      const float inv = 1.0f / L;
-      *(u32x2*)((bf16_t*)p.out + ((size_t)b * p.R + r0 + lr) * p.d + h * DH + dim) = u32x2{cvt_pk_bf16(o[0] * inv, o[1] * inv), cvt_pk_bf16(o[2] * inv, o[3] * inv)};
+      float inv = __builtin_amdgcn_rcpf(L);
+      inv = inv * fmaf(-L, inv, 2.f);            // (one Newton step: the quotient to fp32)
+      *(u32x2*)(out + ((size_t)b * p.R + r0 + lr) * p.d + h * DH + dim) = u32x2{cvt_pk_bf16(o[0] * inv, o[1] * inv), cvt_pk_bf16(o[2] * inv, o[3] * inv)};
     }
   } else {
     const int tiles = nz / p.nsplit;
@@ -335,22 +354,22 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
 }
 // SLOTS: a step of a batch some of whose sequences may have ended (AttnP::seq); a kernel of its own, since looking the
 // sequence up is one more round trip ahead of the K/V loads.
-constexpr int attn_waves(int QU) { return QU > 0 ? 8 : 4; }
 template <bool KVNT, bool LIMF, int QU, bool SLOTS>
 __device__ __forceinline__ void attention_mfma_entry(const AttnP& p, const QProjP& qp) {
-  constexpr int NW = attn_waves(QU), RT = 16, DH = 64;
+  constexpr int NW = ATTN_WAVES, RT = 16;
   __shared__ f32x4 o_s[NW][4][64];
   __shared__ float m_s[NW][RT], l_s[NW][RT];
-  __shared__ __attribute__((aligned(16))) float q_s[QU > 0 ? RT * (DH + 4) : 4];
+  __shared__ __attribute__((aligned(16))) u32x2 q_s[QU > 0 ? 512 : 1];
   __shared__ __attribute__((aligned(16))) float gb_s[QU > 0 ? NW * ((4 * QU + NW - 1) / NW) * 64 : 4];
   __shared__ float2 st_s[QU > 0 ? NW * 16 : 1];
-  AttnLdsT<NW> sm;
+  AttnLds sm;
   sm.o_s = o_s; sm.m_s = m_s; sm.l_s = l_s; sm.q_s = q_s; sm.gb_s = gb_s; sm.st_s = st_s;
   const int sb = SLOTS ? p.seq[blockIdx.y] : blockIdx.y;
   if (SLOTS && sb < 0) return;
-  attention_mfma_body<NW, KVNT, LIMF, QU>(p, qp, sm, blockIdx.x, blockIdx.y, sb, blockIdx.z, gridDim.x, gridDim.z, threadIdx.x);
+  attention_mfma_body<KVNT, LIMF, QU, true>(p, qp, sm, blockIdx.x, blockIdx.y, sb, blockIdx.z, gridDim.x, gridDim.z, threadIdx.x, QU > 0 ? NW : blockDim.x >> 6);
 }
+// (QU == 0: four or eight waves; QU < 0: four; otherwise eight)
 template <bool KVNT, bool LIMF, int QU>
-__global__ __launch_bounds__(64 * attn_waves(QU)) void attention_mfma_kernel(AttnP p, QProjP qp) { attention_mfma_entry<KVNT, LIMF, QU, false>(p, qp); }
+__global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_kernel(AttnP p, QProjP qp) { attention_mfma_entry<KVNT, LIMF, QU, false>(p, qp); }
 template <bool KVNT, bool LIMF, int QU>
-__global__ __launch_bounds__(64 * attn_waves(QU)) void attention_mfma_slots_kernel(AttnP p, QProjP qp) { attention_mfma_entry<KVNT, LIMF, QU, true>(p, qp); }
+__global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_slots_kernel(AttnP p, QProjP qp) { attention_mfma_entry<KVNT, LIMF, QU, true>(p, qp); }

@@ -22,6 +22,9 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 __device__ __forceinline__ float bf2f(bf16_t v) { return __uint_as_float(((unsigned)v) << 16); }
 __device__ __forceinline__ bf16_t f2bf(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }      // round to nearest even (one instruction)
+// An argument that only a kernel's end reads, loaded where this stands: left to itself the compiler loads it there, and the trip
+// (0.2 .. 0.4 us) is exposed.
+template <typename T> __device__ __forceinline__ T* arg_now(T* v) { asm volatile("" ::"s"(v)); return v; }
 __device__ __forceinline__ unsigned cvt_pk_bf16(float lo, float hi) {
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -692,22 +695,23 @@ template <int DH> struct RowLoader<bf16_t, DH> {
 };
 
 struct AttnP {
-  const float* Q;
+  // (what the first loads need comes first: one scalar load)
   const void* Kc; const void* Vc;
-  void* out;
-  long kv_seq_stride;
-  int cap;                // rows per sequence in the K/V buffer (loads are clamped to it)
-  int capg;               // 64-wide bf16 heads (bpd_attention.h): groups of 32 keys per sequence instead
-  int d, R;
+  const float* Q;
   const int* limit;       // [B]: base (causal) or len (non-causal)
-  int causal;
-  float scale;
-  int local_q, local_m;   // causal only, local_q > 0: 1D local attention (Section 7.2): the row at position t sees keys
-                          // floor(t / local_q) * local_q - local_m .. t; the chunks then start at the first row's bound
   const int* seq;         // null: Q, out, limit and the K/V buffer are all indexed by sequence.  Otherwise Q, out and limit by
                           // slot, and seq[slot] is the sequence in the K/V buffer (-1: slot not in use)
+  int capg;               // 64-wide bf16 heads (bpd_attention.h): groups of 32 keys per sequence in the K/V buffer
+  int d, R;
   int nsplit;             // key chunks are dealt round-robin to nsplit workgroups per (head, sequence, row tile)
+  int causal;
+  float scale;
+  void* out;
+  int local_q, local_m;   // causal only, local_q > 0: 1D local attention (Section 7.2): the row at position t sees keys
+                          // floor(t / local_q) * local_q - local_m .. t; the chunks then start at the first row's bound
   float* part;            // nsplit > 1: partial results [b][h][tile][split][16*DH acc | 16 max | 16 sum]
+  int cap;                // other heads: rows per sequence in the K/V buffer (loads are clamped to it)
+  long kv_seq_stride;
 };
 
 // first key that the row at position t may see

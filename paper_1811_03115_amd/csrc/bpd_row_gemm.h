@@ -69,7 +69,7 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
   if constexpr (LN) gbv = *(const f32x4*)((lane % (U * 16) < U * 8 ? p.g : p.b) + ks0 * 32 + (lane % (U * 8)) * 4);
   // operands of the epilogue, for the tiles that this wave finishes
   f32x4 bias[OWN], res[OWN];
-  int key0[OWN], sb[OWN];
+  int key0[OWN], sb[OWN], row0[OWN];
 #pragma unroll
   for (int j = 0; j < OWN; ++j) {
     const int id = wave + WAVES * j;
@@ -79,11 +79,15 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
     if constexpr (EPI == RG_RES) res[j] = __builtin_bit_cast(f32x4, buf_load16(rsrc_of(p.Y, (unsigned)p.M * p.ldy * 4), (m * p.ldy + n) * 4, 0));
     if constexpr (EPI == RG_QKV) {
       const int mm = m < p.M ? m : 0, q = (int)(((float)mm + 0.5f) * __builtin_amdgcn_rcpf((float)p.R));      // mm / R (mm < 2^16: exact)
-      sb[j] = p.seq ? p.seq[q] : q;
-      key0[j] = (p.base ? p.base[q] : 0) + mm - q * p.R;
-      if (!p.capg) key0[j] += q * p.cap;         // (slots: cap is 0 and base counts rows over all sequences)
+      row0[j] = mm - q * p.R + (p.capg ? 0 : q * p.cap);       // (slots: cap is 0 and base counts rows over all sequences)
+      sb[j] = q; key0[j] = 0;
+      if (p.seq) sb[j] = p.seq[q];
+      if (p.base) key0[j] = p.base[q];
     }
   }
+  void* Y = arg_now(p.Y);
+  bf16_t *Kc = nullptr, *Vc = nullptr;
+  if constexpr (EPI == RG_QKV) { Kc = arg_now(p.Kc); Vc = arg_now(p.Vc); }
   __builtin_amdgcn_sched_barrier(0);
   f32x4 acc[MT][NT];
 #pragma unroll
@@ -167,22 +171,22 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
       v += bias[j];
 #pragma unroll
       for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.f);
-      *(u32x2*)((bf16_t*)p.Y + (size_t)m * p.ldy + n) = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
+      *(u32x2*)((bf16_t*)Y + (size_t)m * p.ldy + n) = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
     } else if constexpr (EPI == RG_RES) {
       v += bias[j];
       v += res[j];
-      *(f32x4*)((float*)p.Y + (size_t)m * p.ldy + n) = v;
+      *(f32x4*)((float*)Y + (size_t)m * p.ldy + n) = v;
     } else if constexpr (EPI == RG_PART) {
-      *(f32x4*)((float*)p.Y + ((size_t)blockIdx.z * p.M + m) * p.ldy + n) = v;
+      *(f32x4*)((float*)Y + ((size_t)blockIdx.z * p.M + m) * p.ldy + n) = v;
     } else {
       const int c = tile / (K / 16), col = n - c * K;
       if (c + p.chunk0 == 0) {
-        *(f32x4*)((float*)p.Y + (size_t)m * K + col) = v;
+        *(f32x4*)((float*)Y + (size_t)m * K + col) = v;
       } else if (sb[j] >= 0) {                   // (a slot behind the last one has no cache rows)
-        bf16_t* cache = c + p.chunk0 == 1 ? p.Kc : p.Vc;
+        bf16_t* cache = c + p.chunk0 == 1 ? Kc : Vc;
         const unsigned lo = cvt_pk_bf16(v[0], v[1]), hi = cvt_pk_bf16(v[2], v[3]);
-        if (p.capg) kv_frag_store(cache, c + p.chunk0 == 2, sb[j], p.heads, p.capg, key0[j], col, lo, hi);
-        else *(u32x2*)(cache + (size_t)key0[j] * K + col) = u32x2{lo, hi};
+        if (p.capg) kv_frag_store(cache, c + p.chunk0 == 2, sb[j], p.heads, p.capg, key0[j] + row0[j], col, lo, hi);
+        else *(u32x2*)(cache + (size_t)(key0[j] + row0[j]) * K + col) = u32x2{lo, hi};
       }
     }
   }

@@ -306,7 +306,7 @@ struct StackHelperV {
     ap.local_q = 0; ap.local_m = 0; ap.nsplit = 1; ap.part = nullptr;
     const AttnLds sm = AttnLds::carve(smem);
     for (int item = rank; item < p.heads * p.B; item += p.workers)       // one workgroup barrier inside each
-      attention_mfma_body<4, false, false, 0>(ap, QProjP{}, sm, item % p.heads, item / p.heads, item / p.heads, 0, p.heads, 1, helper_tid());
+      attention_mfma_body<false, false, 0, false>(ap, QProjP{}, sm, item % p.heads, item / p.heads, item / p.heads, 0, p.heads, 1, helper_tid(), 4);
     stamp(inst, 5);
     signal(inst);
     stamp(inst, 6);
