@@ -1041,8 +1041,81 @@ StateP state_params(bpd_ctx* ctx) {
   s.kmax = ctx->cfg.k_max; s.max_out = ctx->cfg.max_out_len;
   s.eos_id = ctx->cfg.eos_id; s.distance_eps = ctx->distance_eps; s.min_block = ctx->min_block;
   s.topn_ok = ctx->top_n > 1 ? ctx->lay.topn_ok : nullptr;
-  s.fin_step = L.fin_step; s.slot_seq = L.slot_seq; s.slot_L = L.slot_L; s.slot_src = L.slot_src; s.slot_row = L.slot_row; s.cache_rows = ctx->cfg.max_out_len + ctx->cfg.k_max + 1; s.n_live = L.n_live; s.src_len = L.src_len;
+  s.steps_done = L.steps_done; s.fin_step = L.fin_step; s.slot_seq = L.slot_seq; s.slot_L = L.slot_L; s.slot_src = L.slot_src; s.slot_row = L.slot_row; s.cache_rows = ctx->cfg.max_out_len + ctx->cfg.k_max + 1; s.n_live = L.n_live; s.src_len = L.src_len;
   return s;
+}
+
+// ------------------------------------------------------------------------------- small fp32 models (bpd_small.h)
+constexpr size_t SMALL_LDS_MAX = 160 * 1024;
+SmallLds small_decode_lds(const bpd_config& c, int rows, int k, int hgroup, bool topn) {
+  return small_lds(c.d_model, c.d_ff, c.vocab, rows, k, hgroup, 0, topn, small_decoder_phases(c.d_model, c.n_dec_layers, k, hgroup));
+}
+// heads whose hidden layers fit the LDS together (0: not even one does)
+int small_hgroup(const bpd_ctx* ctx, int k) {
+  const bpd_config& c = ctx->cfg;
+  if (!small_shape(c)) return 0;
+  int h = k;
+  while (h > 0 && (size_t)small_decode_lds(c, k, k, h, ctx->top_n > 1 && k > 1).total * 4 > SMALL_LDS_MAX) --h;
+  return h;
+}
+SmallLds small_encode_lds(const bpd_config& c, int S) {
+  return small_lds(c.d_model, c.d_ff, c.vocab, 16, 1, 1, (S + 15) / 16 * 16, false, small_encoder_phases(c.d_model, c.n_enc_layers, c.n_dec_layers));
+}
+SmallLds small_prime_lds(const bpd_config& c) { return small_lds(c.d_model, c.d_ff, c.vocab, 4, 4, c.k_max, 0, false, small_decoder_phases(c.d_model, c.n_dec_layers, c.k_max, c.k_max)); }
+bool small_encode_ok(const bpd_ctx* ctx) {
+  return small_shape(ctx->cfg) && ctx->prof_phase == 0 && (size_t)small_encode_lds(ctx->cfg, ctx->S).total * 4 <= SMALL_LDS_MAX &&
+         (size_t)small_prime_lds(ctx->cfg).total * 4 <= SMALL_LDS_MAX;
+}
+SmallP small_params(bpd_ctx* ctx) {
+  const bpd_config& c = ctx->cfg;
+  Layout& L = ctx->lay;
+  SmallP p{};
+  p.s = state_params(ctx);
+  p.d = c.d_model; p.F = c.d_ff; p.V = c.vocab; p.heads = c.n_heads; p.n_enc = c.n_enc_layers; p.n_dec = c.n_dec_layers; p.max_src = c.max_src_len;
+  p.slots = c.max_out_len + c.k_max + 1; p.S = ctx->S;
+  p.eps = c.ln_eps; p.escale = sqrtf((float)c.d_model); p.qscale = 1.0f / sqrtf((float)(c.d_model / c.n_heads));
+  p.local_q = ctx->local_q; p.local_m = ctx->local_m;
+  const EncL& e = L.enc[0];
+  const DecL& w = L.dec[0];
+  p.enc.wqkv = (const float*)e.wqkv; p.enc.wo = (const float*)e.wo; p.enc.w1 = (const float*)e.w1; p.enc.w2 = (const float*)e.w2; p.enc.b1 = e.b1; p.enc.b2 = e.b2;
+  p.enc.ln1g = e.ln1.g; p.enc.ln1b = e.ln1.b; p.enc.ln2g = e.ln2.g; p.enc.ln2b = e.ln2.b;
+  p.enc.cq = p.enc.co = p.enc.ckv = p.enc.ln3g = p.enc.ln3b = p.enc.wqkv;                    // (not used by the encoder)
+  p.dec.wqkv = (const float*)w.wqkv; p.dec.wo = (const float*)w.wo; p.dec.cq = (const float*)w.cq; p.dec.co = (const float*)w.co; p.dec.ckv = (const float*)w.ckv;
+  p.dec.w1 = (const float*)w.w1; p.dec.w2 = (const float*)w.w2; p.dec.b1 = w.b1; p.dec.b2 = w.b2;
+  p.dec.ln1g = w.ln1.g; p.dec.ln1b = w.ln1.b; p.dec.ln2g = w.ln2.g; p.dec.ln2b = w.ln2.b; p.dec.ln3g = w.ln3.g; p.dec.ln3b = w.ln3.b;
+  // (build_layout takes every layer's arrays in the same order)
+  p.enc_stride = c.n_enc_layers > 1 ? (const float*)L.enc[1].wqkv - (const float*)e.wqkv : 0;
+  p.dec_stride = c.n_dec_layers > 1 ? (const float*)L.dec[1].wqkv - (const float*)w.wqkv : 0;
+  p.enc_g = L.enc_lnf.g; p.enc_b = L.enc_lnf.b; p.dec_g = L.dec_lnf.g; p.dec_b = L.dec_lnf.b;
+  p.hw1 = (const float*)L.hw1; p.hb1 = L.hb1; p.hw2 = (const float*)L.hw2; p.hb2 = L.hb2; p.emb = (const float*)L.emb; p.emb_t = L.emb_t; p.pos_src = L.pos_src; p.pos_tgt = L.pos_tgt;
+  p.selfK = (float*)L.selfK; p.selfV = (float*)L.selfV; p.crossK = (float*)L.crossK; p.crossV = (float*)L.crossV; p.qe = L.qe; p.ke = (float*)L.ke; p.ve = (float*)L.ve;
+  p.self_layer = (long)c.max_batch * p.slots * c.d_model; p.src_layer = (long)c.max_batch * c.max_src_len * c.d_model;
+  p.src_ids = L.src_ids;
+  return p;
+}
+template <void (*kernel)(SmallP)>
+void small_launch(bpd_ctx* ctx, const SmallP& p, const SmallLds& n) {
+  const int lds = n.total * 4;
+  static bool attr = false;                       // per kernel: allow more than 64 KiB of LDS
+  if (!attr) { (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SMALL_LDS_MAX); attr = true; }
+  hipLaunchKernelGGL(kernel, dim3(ctx->B), dim3(SMALL_T), lds, ctx->stream, p);
+}
+void small_encode(bpd_ctx* ctx) {
+  SmallP p = small_params(ctx);
+  p.k = p.hgroup = ctx->cfg.k_max;
+  small_launch<small_encode_kernel>(ctx, p, small_encode_lds(ctx->cfg, ctx->S));
+  small_launch<small_prime_kernel>(ctx, p, small_prime_lds(ctx->cfg));
+}
+// `steps` steps of every sequence (hgroup: of small_hgroup()), or with logits one invocation's scores
+void small_decode(bpd_ctx* ctx, int k, int hgroup, int steps, const int* imposed, int imposed_stride, int* accepted, float* logits) {
+  SmallP p = small_params(ctx);
+  p.s.imposed = imposed; p.s.imposed_stride = imposed_stride;
+  p.k = k; p.hgroup = hgroup; p.steps = steps; p.top_n = ctx->top_n; p.accepted_out = accepted; p.logits = logits;
+  const SmallLds n = small_decode_lds(ctx->cfg, k, k, hgroup, p.top_n > 1 && k > 1);
+  ctx->x_ready_k = 0;
+  if (k <= 4) small_launch<small_decode_kernel<1>>(ctx, p, n);
+  else if (k <= 8) small_launch<small_decode_kernel<2>>(ctx, p, n);
+  else small_launch<small_decode_kernel<4>>(ctx, p, n);
 }
 
 int encoder(bpd_ctx* ctx) {
@@ -1321,7 +1394,10 @@ int bpd_load_weights(bpd_ctx* ctx, const bpd_tensor* tensors, int n) {
       case MAT: conv_mat(src, e.dst, e.K, e.N, 0, e.ldw, e.n_off); break;
       case EMB:
         if (bf) conv_mat(src, e.dst, e.K, e.N, 1, e.ldw, 0);      // as the projection matrix W[d][V] = E^T
-        else conv_vec(src, (float*)e.dst, count);                  // fp32 kernels read E[V][d] directly
+        else {
+          conv_vec(src, (float*)e.dst, count);                      // fp32 kernels read E[V][d] directly
+          if (ctx->lay.emb_t) conv_mat(src, ctx->lay.emb_t, e.K, e.N, 1, e.ldw, 0);
+        }
         break;
       case MATK_CAT:
         for (int i = 0; i < (int)e.shape[0]; ++i)
@@ -1381,12 +1457,16 @@ int bpd_encode(bpd_ctx* ctx, const int32_t* src_ids, const int32_t* src_len, con
     ++ctx->encode_tag;
   }
   use_slots(ctx, B);
-  int rc = encoder(ctx);
-  if (rc) return rc;
-  // first invocation: position 0 only, all heads -> first proposals
-  rc = forward(ctx, 1, c.k_max, 1, nullptr);
-  if (rc) return rc;
-  hipLaunchKernelGGL(prime_kernel, dim3(B), dim3(64), 0, ctx->stream, state_params(ctx), L.keys, B);
+  if (small_encode_ok(ctx)) {
+    small_encode(ctx);
+  } else {
+    int rc = encoder(ctx);
+    if (rc) return rc;
+    // first invocation: position 0 only, all heads -> first proposals
+    rc = forward(ctx, 1, c.k_max, 1, nullptr);
+    if (rc) return rc;
+    hipLaunchKernelGGL(prime_kernel, dim3(B), dim3(64), 0, ctx->stream, state_params(ctx), L.keys, B);
+  }
   LAUNCHCHK();
   ctx->steps = 0;
   ctx->live1 = ctx->live2 = B;
@@ -1436,6 +1516,13 @@ static int step_impl(bpd_ctx* ctx, int k, const int* imposed_dev, int* accepted_
   std::fill(ctx->remaining.begin(), ctx->remaining.end(), -1);
   ctx->live1 = ctx->live2 = -1;
   use_slots(ctx, -1);
+  const int hgroup = ctx->prof_phase == 0 || ctx->prof_phase == BPD_PHASE_STEP ? small_hgroup(ctx, k) : 0;
+  if (hgroup > 0) {
+    small_decode(ctx, k, hgroup, 1, imposed_dev, 0, accepted_dev, nullptr);
+    LAUNCHCHK();
+    ctx->steps++;
+    return BPD_OK;
+  }
   const int rc = step_forward(ctx, k, imposed_dev, 0, 0);
   if (rc) return rc;
   return step_accept(ctx, k, accepted_dev, ctx->B, 0);
@@ -1566,12 +1653,13 @@ int bpd_get_stats(bpd_ctx* ctx, bpd_stats* st) {
   return BPD_OK;
 }
 
-static int output_and_stats(bpd_ctx* ctx, int32_t* out_ids, int32_t* out_len, bpd_stats* st) {
+static int output_and_stats(bpd_ctx* ctx, int32_t* out_ids, int32_t* out_len, bpd_stats* st, bool count_steps = false) {
   Layout& L = ctx->lay;
   long long raw[32];
   const int rc = fetch(ctx, {{L.out_ids, (size_t)ctx->B * ctx->cfg.max_out_len, out_ids}, {L.j, (size_t)ctx->B, out_len},
-                             {(const int*)L.stats, 64, st ? raw : nullptr}});
+                             {(const int*)L.stats, 64, st || count_steps ? raw : nullptr}});
   if (rc) return rc;
+  if (count_steps) ctx->steps = raw[20];
   if (st) stats_of(ctx, raw, st);
   return stack_check(ctx);
 }
@@ -1612,6 +1700,14 @@ int bpd_decode(bpd_ctx* ctx, int k, const int32_t* schedule, int max_steps, int3
     }
   }
   auto& rem = ctx->remaining;
+  if (const int hgroup = ctx->prof_phase == 0 ? small_hgroup(ctx, k) : 0) {      // the whole decode as one kernel
+    if (max_steps > 0) {
+      std::fill(rem.begin(), rem.end(), -1);
+      small_decode(ctx, k, hgroup, max_steps, imp, B, nullptr, nullptr);
+      LAUNCHCHK();
+    }
+    return output_and_stats(ctx, out_ids, out_len, stats, true);
+  }
   // may step s end the last sequence by its budget, as far as the reports before s tell?
   auto may_be_last = [&](int s) {
     for (int b = 0; b < B; ++b) {
@@ -1691,6 +1787,11 @@ int bpd_debug_step_logits(bpd_ctx* ctx, int k, float* logits) {
   if (!ctx->encoded) return fail(ctx, BPD_E_STATE, "bpd_debug_step_logits: call bpd_encode first");
   if (k < 1 || k > ctx->cfg.k_max) return fail(ctx, BPD_E_ARG, "bpd_debug_step_logits: k outside 1..k_max");
   use_slots(ctx, ctx->B);                         // every sequence, ended or not
+  if (const int hgroup = ctx->prof_phase == 0 ? small_hgroup(ctx, k) : 0) {
+    small_decode(ctx, k, hgroup, 1, nullptr, 0, nullptr, logits);
+    LAUNCHCHK();
+    return BPD_OK;
+  }
   int rc = forward(ctx, k, k, 0, logits);
   if (rc) return rc;
   hipLaunchKernelGGL(accept_kernel, dim3(ctx->B), dim3(64), 0, ctx->stream, state_params(ctx), ctx->lay.keys, k, ctx->B, 0, 0, nullptr, 0);

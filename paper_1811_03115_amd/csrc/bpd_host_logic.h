@@ -50,7 +50,7 @@ struct DecL { LnW ln1, ln2, ln3; void *wqkv, *wo, *cq, *co, *ckv, *w1, *w2; floa
 
 struct Layout {
   // weights
-  void* emb; float *pos_src, *pos_tgt;
+  void* emb; float *emb_t, *pos_src, *pos_tgt;            // (emb_t: the embedding transposed, small fp32 models)
   std::vector<EncL> enc; LnW enc_lnf;
   std::vector<DecL> dec; LnW dec_lnf;
   void *hw1, *hw2; float *hb1, *hb2;
@@ -67,7 +67,7 @@ struct Layout {
   float *xe, *qe; void *xen, *ke, *ve, *attne, *ffhe, *mem;
   // state
   int *L, *j, *finished, *max_len, *src_len, *src_ids, *P, *A, *accepted, *out_ids, *step_counter, *imposed1, *sched;
-  int *fin_step, *slot_seq, *slot_L, *slot_src, *slot_row, *n_live;
+  int *steps_done, *fin_step, *slot_seq, *slot_L, *slot_src, *slot_row, *n_live;
   long long* stats;
   void* staging; size_t staging_bytes;
   size_t total;
@@ -94,6 +94,14 @@ bool config_ok(const bpd_config& c) {
   return true;
 }
 
+// Small fp32 models run with a workgroup per sequence (bpd_small.h): one CU reading the step's weights (64 bytes per clock) still
+// takes far less than a step's launches (27 of 4.6 us each with two layers).
+constexpr size_t SMALL_WEIGHTS_MAX = (size_t)8 << 20;
+bool small_shape(const bpd_config& c) {
+  const size_t d = c.d_model, F = c.d_ff, V = c.vocab, k = c.k_max;
+  return c.dtype == BPD_F32 && d <= 256 && V <= 4096 && c.n_dec_layers <= 8 && c.n_enc_layers <= 8 && (c.n_dec_layers * (6 * d * d + 2 * d * F) + 2 * k * d * F + V * d) * 4 <= SMALL_WEIGHTS_MAX;
+}
+
 // Decoder blocks of more than 128 rows run their LayerNorm-then-GEMM pairs as one GEMM on weights with the LayerNorm
 // folded in (ROWAFF in bpd_gemm.h); contexts that can see such blocks keep a folded copy of those matrices.
 bool fold_kept(const bpd_config& c) {
@@ -117,6 +125,7 @@ size_t build_layout(const bpd_config& c, char* base, Layout& L, std::vector<std:
   auto mat = [&](size_t kk, size_t nn) { return a.take(kk * nn * ws); };
   auto ln = [&]() { LnW w; w.g = vec(d); w.b = vec(d); return w; };
   L.emb = mat(V, d);
+  L.emb_t = small_shape(c) ? vec(V * d) : nullptr;
   L.pos_src = vec((size_t)c.max_src_len * d);
   L.pos_tgt = vec(slots * d);
   L.enc.resize(c.n_enc_layers);
@@ -164,7 +173,7 @@ size_t build_layout(const bpd_config& c, char* base, Layout& L, std::vector<std:
   L.src_ids = ints(Me); L.P = ints(B * k); L.A = ints(B * k * k); L.accepted = ints(B); L.topn_ok = ints(B * k); L.sel = ints(B);
   L.out_ids = ints(B * (size_t)c.max_out_len); L.step_counter = ints(1); L.imposed1 = ints(B);
   L.sched = ints(B * (size_t)c.max_out_len);
-  L.fin_step = ints(B); L.slot_seq = ints(B); L.slot_L = ints(B); L.slot_src = ints(B); L.slot_row = ints(B); L.n_live = ints(1);
+  L.steps_done = ints(B); L.fin_step = ints(B); L.slot_seq = ints(B); L.slot_L = ints(B); L.slot_src = ints(B); L.slot_row = ints(B); L.n_live = ints(1);
   L.stats = (long long*)a.take(32 * 8);
   L.xcc_map = (unsigned*)a.take(XCC_MAP_MAX * 4);
   L.stack_err = (unsigned*)a.take(256);

@@ -949,6 +949,7 @@ struct StateP {
   unsigned long long* report; unsigned report_tag;
   // Slots: the rows of a step belong to the sequences that had not ended when the step before it began, packed in
   // sequence order, so that a batch of unequal lengths does not compute the rows of those that are done.
+  int* steps_done;     // [B] steps that the sequence has made since bpd_encode
   int* fin_step;       // [B] step (since bpd_encode) that ended the sequence, INT_MAX before
   int* slot_seq;       // [B] sequence of each slot of the next step, -1 behind the last
   int* slot_L; int* slot_src;   // [B] cache length and source length of that sequence
@@ -982,7 +983,7 @@ __global__ __launch_bounds__(256) void encode_init_kernel(StateP s, const int* s
     d_len[q] = sl < 1 ? 1 : (sl > S ? S : sl);
     s.max_len[q] = m < 1 ? 1 : (m > s.max_out ? s.max_out : m);
     s.L[q] = 0; s.j[q] = 0; s.finished[q] = 0; s.accepted[q] = 0;
-    s.fin_step[q] = 0x7FFFFFFF; s.slot_seq[q] = q; s.slot_L[q] = 1; s.slot_src[q] = d_len[q]; s.slot_row[q] = q * s.cache_rows + 1;
+    s.steps_done[q] = 0; s.fin_step[q] = 0x7FFFFFFF; s.slot_seq[q] = q; s.slot_L[q] = 1; s.slot_src[q] = d_len[q]; s.slot_row[q] = q * s.cache_rows + 1;
   }
   if (i == 0) *s.n_live = B;
   __syncthreads();                               // (every argument this workgroup reads has arrived: it has been stored)
@@ -1168,6 +1169,7 @@ __global__ __launch_bounds__(64) void accept_kernel(StateP s, const unsigned lon
     s.L[b] = s.L[b] + khat;
     s.finished[b] = fin;
     s.accepted[b] = khat;
+    s.steps_done[b] = live_step + 1;
     if (accepted_out) accepted_out[b] = khat;
     report_remaining(s, b, fin ? 0 : s.max_len[b] - j - khat);
     atomicAdd((unsigned long long*)&s.stats[0], 1ull);
@@ -1324,6 +1326,8 @@ __global__ __launch_bounds__(1024) void accept_embed_kernel(StateP s, unsigned l
   }
   if (per_block && 4 * wave < ntiles && lane < 16 && i < k) ((float2*)stats)[(long)wave * srows + row] = make_float2(bs, bq);
 }
+
+#include "bpd_small.h"
 
 // ---------------------------------------------------------------------------------------
 // Machine peaks, measured the way the step's kernels use the machine (bpd_measure_*).
