@@ -11,6 +11,8 @@
 #include <cstdlib>
 #include <cstring>
 #include <algorithm>
+#include <array>
+#include <atomic>
 #include <initializer_list>
 #include <map>
 #include <string>
@@ -31,6 +33,9 @@ struct WEntry {
   int K, N, ldw, n_off;      // matrices: source K x N, destination row length, column offset
   bool loaded;
 };
+
+// A sequence of launches that depends on nothing but `key`
+struct Plan { std::array<long, 8> key; int seen; bool failed; hipGraphExec_t exec; unsigned long long used; };
 
 }  // namespace
 
@@ -72,6 +77,8 @@ struct bpd_ctx {
   unsigned long long fetch_tag = 0, encode_tag = 0;
   unsigned report_tag = 0;
   std::vector<int> remaining;                  // tokens still to come per sequence as far as the host knows (-1: it does not)
+  std::vector<Plan> plans;                     // launches seen before, as graphs (run_planned)
+  hipStream_t plan_stream = nullptr;           // where they are recorded
   int prof_phase = 0;
   std::vector<hipEvent_t> prof_ev;
   size_t prof_used = 0;
@@ -1041,7 +1048,7 @@ StateP state_params(bpd_ctx* ctx) {
   s.kmax = ctx->cfg.k_max; s.max_out = ctx->cfg.max_out_len;
   s.eos_id = ctx->cfg.eos_id; s.distance_eps = ctx->distance_eps; s.min_block = ctx->min_block;
   s.topn_ok = ctx->top_n > 1 ? ctx->lay.topn_ok : nullptr;
-  s.steps_done = L.steps_done; s.fin_step = L.fin_step; s.slot_seq = L.slot_seq; s.slot_L = L.slot_L; s.slot_src = L.slot_src; s.slot_row = L.slot_row; s.cache_rows = ctx->cfg.max_out_len + ctx->cfg.k_max + 1; s.n_live = L.n_live; s.src_len = L.src_len;
+  s.dyn = nullptr; s.tick = L.tick; s.imp_next = L.imp_next; s.steps_done = L.steps_done; s.fin_step = L.fin_step; s.slot_seq = L.slot_seq; s.slot_L = L.slot_L; s.slot_src = L.slot_src; s.slot_row = L.slot_row; s.cache_rows = ctx->cfg.max_out_len + ctx->cfg.k_max + 1; s.n_live = L.n_live; s.src_len = L.src_len;
   return s;
 }
 
@@ -1174,6 +1181,60 @@ bool is_host_ptr_cached(bpd_ctx* ctx, const void* p) {
   ctx->kind_ptr[ctx->kind_next] = p; ctx->kind_host[ctx->kind_next] = h;
   ctx->kind_next = (ctx->kind_next + 1) & 3;
   return h;
+}
+
+// Launches of one kind (a decode's step, an encode) that come again and again with the same arguments: from the second time on
+// they are recorded and replayed as a graph.  A launch costs the host 3 us (its arguments go to device memory), which is
+// what a sentence's encode took (90 launches: 0.6 ms, the GPU 0.3) and most of what a step of the base model took (43).  `enqueue`
+// launches on ctx->stream and may only depend on the key.  Graphs are kept for the last PLANS_MAX keys (source lengths, mostly).
+constexpr size_t PLANS_MAX = 24;
+enum { PLAN_ENCODE, PLAN_STEP };
+template <class F>
+int run_planned(bpd_ctx* ctx, const std::array<long, 8>& key, F enqueue) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  // (not while phases are timed, nor inside a graph of the caller's, nor with the decoder stack kernel, whose flags count its launches)
+  if (ctx->prof_phase != 0 || (ctx->stack_workers > 0 && !ctx->stack_off) || hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return enqueue();
+  }
+  static std::atomic<unsigned long long> clock{0};
+  Plan* p = nullptr;
+  for (auto& q : ctx->plans)
+    if (q.key == key) { p = &q; break; }
+  if (!p) {
+    if (ctx->plans.size() >= PLANS_MAX) {        // the one not used for longest goes
+      auto old = std::min_element(ctx->plans.begin(), ctx->plans.end(), [](const Plan& a, const Plan& b) { return a.used < b.used; });
+      if (old->exec) (void)hipGraphExecDestroy(old->exec);
+      ctx->plans.erase(old);
+    }
+    ctx->plans.push_back(Plan{key, 0, false, nullptr, 0});
+    p = &ctx->plans.back();
+  }
+  p->used = ++clock;
+  if (p->exec) {
+    HIPCHK(hipGraphLaunch(p->exec, ctx->stream));
+    return BPD_OK;
+  }
+  if (p->failed || ++p->seen < 2) return enqueue();
+  if (!ctx->plan_stream && hipStreamCreateWithFlags(&ctx->plan_stream, hipStreamNonBlocking) != hipSuccess) ctx->plan_stream = nullptr;
+  hipGraph_t graph = nullptr;
+  bool ok = ctx->plan_stream && hipStreamBeginCapture(ctx->plan_stream, hipStreamCaptureModeThreadLocal) == hipSuccess;
+  if (ok) {
+    const hipStream_t user = ctx->stream;
+    ctx->stream = ctx->plan_stream;
+    const int rc = enqueue();
+    ctx->stream = user;
+    ok = hipStreamEndCapture(ctx->plan_stream, &graph) == hipSuccess && rc == BPD_OK && graph;
+  }
+  ok = ok && hipGraphInstantiate(&p->exec, graph, nullptr, nullptr, 0) == hipSuccess;
+  if (graph) (void)hipGraphDestroy(graph);
+  if (!ok) {                                     // (nothing has run: launch by launch, from now on)
+    (void)hipGetLastError();
+    p->exec = nullptr; p->failed = true;
+    return enqueue();
+  }
+  HIPCHK(hipGraphLaunch(p->exec, ctx->stream));
+  return BPD_OK;
 }
 
 unsigned long long* report_of(bpd_ctx* ctx, unsigned tag) { return ctx->report + (size_t)(tag & 1) * ctx->cfg.max_batch; }
@@ -1333,6 +1394,9 @@ int bpd_destroy(bpd_ctx* ctx) {
         if (FILE* f = fopen(path, "wb")) { fwrite(t.data(), 8, n, f); fclose(f); }
     }
   }
+  for (auto& q : ctx->plans)
+    if (q.exec) (void)hipGraphExecDestroy(q.exec);
+  if (ctx->plan_stream) (void)hipStreamDestroy(ctx->plan_stream);
   for (auto e : ctx->prof_ev) (void)hipEventDestroy(e);
   if (ctx->report) (void)hipHostFree(ctx->report);
   delete ctx;
@@ -1460,12 +1524,18 @@ int bpd_encode(bpd_ctx* ctx, const int32_t* src_ids, const int32_t* src_len, con
   if (small_encode_ok(ctx)) {
     small_encode(ctx);
   } else {
-    int rc = encoder(ctx);
+    ctx->steps = 0;
+    const int rc = run_planned(ctx, {PLAN_ENCODE, B, S, ctx->local_q, ctx->local_m, 0, 0, 0}, [&]() -> int {
+      int rc = encoder(ctx);
+      if (rc) return rc;
+      // first invocation: position 0 only, all heads -> first proposals
+      rc = forward(ctx, 1, c.k_max, 1, nullptr);
+      if (rc) return rc;
+      hipLaunchKernelGGL(prime_kernel, dim3(B), dim3(64), 0, ctx->stream, state_params(ctx), L.keys, B);
+      LAUNCHCHK();
+      return BPD_OK;
+    });
     if (rc) return rc;
-    // first invocation: position 0 only, all heads -> first proposals
-    rc = forward(ctx, 1, c.k_max, 1, nullptr);
-    if (rc) return rc;
-    hipLaunchKernelGGL(prime_kernel, dim3(B), dim3(64), 0, ctx->stream, state_params(ctx), L.keys, B);
   }
   LAUNCHCHK();
   ctx->steps = 0;
@@ -1481,14 +1551,14 @@ static int step_forward(bpd_ctx* ctx, int k, const int* imposed_dev, int imposed
   ctx->cur_imposed = imposed_dev; ctx->cur_imposed_stride = imposed_stride; ctx->cur_imposed_step = imposed_step;
   return forward(ctx, k, k, 0, nullptr);
 }
-// report_tag: bpd_decode's tag of this step (0: the step reports nothing to the host)
+// report_tag: bpd_decode's tag of this step (0: not a step of bpd_decode)
 static int step_accept(bpd_ctx* ctx, int k, int* accepted_dev, int next_slots, unsigned report_tag) {
   Layout& L = ctx->lay;
   {
     PhaseTimer t(ctx, BPD_PHASE_ACCEPT);
     StateP s = state_params(ctx);
     s.imposed = ctx->cur_imposed; s.imposed_stride = ctx->cur_imposed_stride;
-    if (report_tag) { s.report = report_of(ctx, report_tag); s.report_tag = report_tag; }
+    if (report_tag) s.dyn = (const StepDyn*)L.dyn;
     const bpd_config& c = ctx->cfg;
     const int imposed_step = ctx->cur_imposed_step;
     if (embed_in_accept(ctx)) {
@@ -1687,17 +1757,23 @@ int bpd_decode(bpd_ctx* ctx, int k, const int32_t* schedule, int max_steps, int3
   const int* host_sched = nullptr;
   if (schedule) {
     // a live sequence takes at least one token per step, so max_out_len rows always suffice
-    const int rows = max_steps < ctx->cfg.max_out_len ? max_steps : ctx->cfg.max_out_len;
-    if (max_steps > rows) max_steps = rows;
+    if (max_steps > ctx->cfg.max_out_len) max_steps = ctx->cfg.max_out_len;
     imp = L.sched;
+  }
+  {
+    const int rows = schedule ? max_steps : 0;
+    const int* src = schedule;
     if (rows > 0 && is_host_ptr(schedule)) {     // (the decode before this one has ended: its copy has been made)
       memcpy(ctx->stage_sched, schedule, (size_t)rows * B * 4);
-      hipLaunchKernelGGL(copy_i32_kernel, dim3((unsigned)(((size_t)rows * B + 255) / 256)), dim3(256), 0, ctx->stream, ctx->stage_sched, L.sched, (long)rows * B);
-      LAUNCHCHK();
-      host_sched = ctx->stage_sched;
-    } else if (rows > 0) {
-      HIPCHK(hipMemcpyAsync(L.sched, schedule, (size_t)rows * B * 4, hipMemcpyDefault, ctx->stream));
+      src = host_sched = ctx->stage_sched;
     }
+    if (ctx->report_tag > 0x7FFFFFFFu) ctx->report_tag = 2;        // (turns kept; far from the tags that old words hold)
+    const long n = (long)rows * B;
+    const StepDyn dyn{imp, B, rows, ctx->report_tag, (int)ctx->steps, ctx->report, ctx->cfg.max_batch};
+    if (max_steps > 0)
+      hipLaunchKernelGGL(decode_init_kernel, dim3((unsigned)((std::max<long>(n, B) + 255) / 256)), dim3(256), 0, ctx->stream, state_params(ctx), dyn, (StepDyn*)L.dyn,
+                         src, L.sched, n, B);
+    LAUNCHCHK();
   }
   auto& rem = ctx->remaining;
   if (const int hgroup = ctx->prof_phase == 0 ? small_hgroup(ctx, k) : 0) {      // the whole decode as one kernel
@@ -1742,6 +1818,31 @@ int bpd_decode(bpd_ctx* ctx, int k, const int32_t* schedule, int max_steps, int3
       if (ctx->live1 == 0) break;
       know = true;
     }
+    // A step like the one before, of all sequences and for all of them (one sentence; images before the first ends): recorded once, replayed
+    // from then on.  All sequences go on after step s - 1 for certain: there is one, or only budgets end them and none is that short.
+    bool planned = s > 0 && !ctx->two_phase && embed_in_accept(ctx) && ctx->x_ready_k == k && ctx->x_ready_slots == B && (B == 1 || (ctx->cfg.eos_id < 0 && ctx->live2 == B));
+    for (int b = 0; planned && B > 1 && b < B; ++b) planned = rem[b] > (know ? 0 : k);
+    if (planned) {
+      use_slots(ctx, B);
+      const bool few = attention_keys(ctx, ctx->cfg.max_out_len + ctx->cfg.k_max + 1, k, 1) <= 128;
+      const int rc = run_planned(ctx, {PLAN_STEP, B, k, attention_nsplit(ctx, ctx->cfg.max_out_len + ctx->cfg.k_max + 1, B, k, 1) * 2 + few, ctx->top_n, ctx->local_q * 4096L + ctx->distance_eps, ctx->local_m * 32L + ctx->min_block, 0},
+                                 [&]() -> int {
+                                   const int ready = ctx->x_ready_k;
+                                   const int64_t steps = ctx->steps;
+                                   int rc = step_forward(ctx, k, nullptr, B, 0);
+                                   if (rc == BPD_OK) rc = step_accept(ctx, k, nullptr, B, 1);
+                                   ctx->x_ready_k = ready; ctx->steps = steps;       // (what a replay leaves as well)
+                                   return rc;
+                                 });
+      if (rc) return rc;
+      ctx->steps++;
+      ++ctx->report_tag;
+      if (!know) { const int rc2 = await(before, ctx->live1); if (rc2) return rc2; }
+      if (ctx->live1 == 0) { ctx->x_ready_k = 0; break; }      // step s - 1 was the last: this one finds nothing to do
+      ctx->live2 = ctx->live1; ctx->live1 = -1;
+      if (s + 1 == max_steps) { const int rc2 = await(ctx->report_tag, ctx->live1); if (rc2) return rc2; }
+      continue;
+    }
     // Slots of this step: the sequences that had not ended after step s - 2 (live2); of the next: not after s - 1 (live1),
     // which the host waits for while the GPU has this step's layers to do
     use_slots(ctx, ctx->live2);
@@ -1749,7 +1850,7 @@ int bpd_decode(bpd_ctx* ctx, int k, const int32_t* schedule, int max_steps, int3
     if (rc == BPD_OK && !know) rc = await(before, ctx->live1);
     if (rc) return rc;
     if (ctx->live1 == 0) { ctx->x_ready_k = 0; break; }      // step s - 1 was the last: this one accepts nothing
-    ctx->report_tag = ctx->report_tag == 0xFFFFFFFFu ? 2 : ctx->report_tag + 1;       // (0 means "no report"; turns kept)
+    ++ctx->report_tag;
     const bool exact = slots_used(ctx) && ctx->live1 > 0;
     rc = step_accept(ctx, k, nullptr, exact ? ctx->live1 : B, ctx->report_tag);
     if (rc) return rc;

@@ -67,7 +67,7 @@ struct Layout {
   float *xe, *qe; void *xen, *ke, *ve, *attne, *ffhe, *mem;
   // state
   int *L, *j, *finished, *max_len, *src_len, *src_ids, *P, *A, *accepted, *out_ids, *step_counter, *imposed1, *sched;
-  int *steps_done, *fin_step, *slot_seq, *slot_L, *slot_src, *slot_row, *n_live;
+  void* dyn; int *tick, *imp_next; int *steps_done, *fin_step, *slot_seq, *slot_L, *slot_src, *slot_row, *n_live;
   long long* stats;
   void* staging; size_t staging_bytes;
   size_t total;
@@ -173,7 +173,7 @@ size_t build_layout(const bpd_config& c, char* base, Layout& L, std::vector<std:
   L.src_ids = ints(Me); L.P = ints(B * k); L.A = ints(B * k * k); L.accepted = ints(B); L.topn_ok = ints(B * k); L.sel = ints(B);
   L.out_ids = ints(B * (size_t)c.max_out_len); L.step_counter = ints(1); L.imposed1 = ints(B);
   L.sched = ints(B * (size_t)c.max_out_len);
-  L.steps_done = ints(B); L.fin_step = ints(B); L.slot_seq = ints(B); L.slot_L = ints(B); L.slot_src = ints(B); L.slot_row = ints(B); L.n_live = ints(1);
+  L.dyn = a.take(64); L.tick = ints(B); L.imp_next = ints(B); L.steps_done = ints(B); L.fin_step = ints(B); L.slot_seq = ints(B); L.slot_L = ints(B); L.slot_src = ints(B); L.slot_row = ints(B); L.n_live = ints(1);
   L.stats = (long long*)a.take(32 * 8);
   L.xcc_map = (unsigned*)a.take(XCC_MAP_MAX * 4);
   L.stack_err = (unsigned*)a.take(256);

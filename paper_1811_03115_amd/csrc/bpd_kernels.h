@@ -928,6 +928,14 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(AttnP p) {
 }
 
 // ---------------------------------------------------------------------------------------
+// What changes from step to step of a bpd_decode, in device memory: the steps' launches are then all alike and can be replayed as a
+// graph.  Set by decode_init_kernel; the steps are counted by StateP::tick.
+struct StepDyn {
+  const int* imposed; int imposed_stride, rows;      // the schedule (null: none), its rows
+  unsigned tag0; int live0;                          // report tag and number of steps made before the first step
+  unsigned long long* report; int report_stride;     // two turns of report words
+};
+
 // Decode state (all arrays on the device, one entry per sequence).
 struct StateP {
   int* L;            // committed decoder-cache rows = j + 1
@@ -944,11 +952,14 @@ struct StateP {
   int kmax, max_out, eos_id;
   int distance_eps, min_block;
   const int* topn_ok;  // [B][kmax]: proposal i+1 is among the n best of p_1 at row i (null: criterion off)
-  // bpd_decode only (null otherwise): host memory, one word per sequence, where the step leaves (report_tag << 32) | tokens
-  // still to come (0: ended), so that the host can follow the decode without stopping the stream
+  // (bpd_decode: host memory, one word per sequence, where the step leaves (report_tag << 32) | tokens still to come (0: ended), so
+  // that the host can follow the decode without stopping the stream; set from dyn)
   unsigned long long* report; unsigned report_tag;
   // Slots: the rows of a step belong to the sequences that had not ended when the step before it began, packed in
   // sequence order, so that a batch of unequal lengths does not compute the rows of those that are done.
+  const StepDyn* dyn;  // steps of a bpd_decode: imposed, report and the step counters come from here
+  int* tick;           // [B] ... its steps so far
+  int* imp_next;       // [B] ... and the value imposed on the next (looked up by the step before: no chain of loads)
   int* steps_done;     // [B] steps that the sequence has made since bpd_encode
   int* fin_step;       // [B] step (since bpd_encode) that ended the sequence, INT_MAX before
   int* slot_seq;       // [B] sequence of each slot of the next step, -1 behind the last
@@ -959,6 +970,20 @@ struct StateP {
   int* n_live;         // [1] slots in use
   const int* src_len;
 };
+
+// A step of a bpd_decode: fills the fields that come from dyn, returns the number of steps since bpd_encode
+__device__ __forceinline__ int step_from_dyn(StateP& s, int tick) {
+  const StepDyn d = *s.dyn;
+  const unsigned tag = d.tag0 + 1u + (unsigned)tick;
+  s.imposed = d.imposed; s.imposed_stride = d.imposed_stride;
+  s.report = d.report + (size_t)(tag & 1) * d.report_stride; s.report_tag = tag;
+  return d.live0 + tick;
+}
+// ... and, once everybody has read the counter: on to the next step
+__device__ __forceinline__ void step_tick(const StateP& s, int b, int tick) {
+  s.tick[b] = tick + 1;
+  if (s.imposed) s.imp_next[b] = tick + 1 < s.dyn->rows ? s.imposed[(long)(tick + 1) * s.imposed_stride + b] : 1;
+}
 
 __device__ __forceinline__ void report_remaining(const StateP& s, int b, int remaining) {
   if (s.report) __hip_atomic_store(&s.report[b], ((unsigned long long)s.report_tag << 32) | (unsigned)remaining, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -1013,9 +1038,12 @@ __global__ __launch_bounds__(1024) void fetch_kernel(FetchP f) {
   if (threadIdx.x == 0) __hip_atomic_store(f.done, f.tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-__global__ __launch_bounds__(256) void copy_i32_kernel(const int* src, int* dst, long n) {
+// Start of a bpd_decode: the schedule (pinned host or device memory) into place, and what its steps share
+__global__ __launch_bounds__(256) void decode_init_kernel(StateP s, StepDyn d, StepDyn* dyn, const int* src, int* dst, long n, int B) {
   const long i = (long)blockIdx.x * 256 + threadIdx.x;
   if (i < n) dst[i] = src[i];
+  if (i < B) { s.tick[i] = 0; s.imp_next[i] = n > 0 ? src[i] : 1; }
+  if (i == 0) *dyn = d;
 }
 
 // After the first invocation on the empty prefix: P <- heads at position 0, j = 0, L = 1.
@@ -1145,18 +1173,23 @@ __global__ __launch_bounds__(64) void accept_kernel(StateP s, const unsigned lon
                                                     int commit, int step, int* accepted_out, int live_step) {
   const int b = blockIdx.x, lane = threadIdx.x;
   if (b >= B) return;
+  const int tick = s.dyn && commit ? s.tick[b] : 0;
+  int imp = 0;
+  if (s.dyn && commit) { live_step = step_from_dyn(s, tick); imp = s.imp_next[b]; if (lane == 0) step_tick(s, b, tick); }
+  else if (s.imposed) imp = s.imposed[(long)step * s.imposed_stride + b];
+  if (commit && s.finished[b]) {
+    if (lane == 0) { s.accepted[b] = 0; if (accepted_out) accepted_out[b] = 0; report_remaining(s, b, 0); }
+    return;
+  }
   for (int e = lane; e < k * k; e += 64) {
     const int ip = e / k, i = e % k;
     s.A[(b * s.kmax + ip) * s.kmax + i] = key_index(keys[(long)b * k * k + e]);
   }
   if (!commit) return;
-  if (s.finished[b]) {
-    if (lane == 0) { s.accepted[b] = 0; if (accepted_out) accepted_out[b] = 0; report_remaining(s, b, 0); }
-    return;
-  }
   const int myP = lane < k ? s.P[b * s.kmax + lane] : -1;
   const int a1 = (lane >= 1 && lane < k) ? key_index(keys[(long)b * k * k + (lane - 1) * k + 0]) : 0;
-  int khat = verified_length(s, b, k, lane, myP, a1, step);
+  const int topn = (s.topn_ok && lane >= 1 && lane < k) ? s.topn_ok[b * s.kmax + lane - 1] : 0;
+  int khat = verified_length_v(s, k, lane, myP, a1, topn, imp);
   bool eos = false;
   const int j = s.j[b];
   khat = cut_length(s, b, lane, myP, khat, eos);
@@ -1200,6 +1233,8 @@ __global__ __launch_bounds__(1024) void accept_embed_kernel(StateP s, unsigned l
   __shared__ int A_s[256];                       // the sequence's k x k arg-max table
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (b >= B) return;
+  const int tick = s.dyn ? s.tick[b] : 0;
+  if (s.dyn) live_step = step_from_dyn(s, tick);
   // Slots of this step (sequences not ended before step live_step - 1) and of the next (not before this one).  (The
   // workgroups of this launch write fin_step too: live_step, which both tests let pass.)  With all of the batch in this
   // step (slots == 1) the slot is the sequence and only the next step's is worked out, by a wave of its own.
@@ -1228,7 +1263,7 @@ __global__ __launch_bounds__(1024) void accept_embed_kernel(StateP s, unsigned l
     __syncthreads();
     slot = slot_s[0];
     if (slot < 0) {                              // ended before the step began: no rows, nothing to do
-      if (tid == 0) { s.accepted[b] = 0; if (accepted_out) accepted_out[b] = 0; report_remaining(s, b, 0); }
+      if (tid == 0) { s.accepted[b] = 0; if (accepted_out) accepted_out[b] = 0; report_remaining(s, b, 0); if (s.dyn) step_tick(s, b, tick); }
       return;
     }
   }
@@ -1241,7 +1276,7 @@ __global__ __launch_bounds__(1024) void accept_embed_kernel(StateP s, unsigned l
     for (int q = 0; q < 4; ++q) kv[q] = keys[(long)slot * kk + (lane + 64 * q < kk ? lane + 64 * q : 0)];
     const int myP_raw = s.P[b * s.kmax + (lane < k ? lane : 0)];
     const int fin0 = s.finished[b], j = s.j[b], max_len = s.max_len[b], L0 = s.L[b];
-    const int imp_raw = s.imposed ? s.imposed[(long)step * s.imposed_stride + b] : 0;
+    const int imp_raw = s.dyn ? s.imp_next[b] : (s.imposed ? s.imposed[(long)step * s.imposed_stride + b] : 0);
     const int topn_raw = s.topn_ok ? s.topn_ok[b * s.kmax + ((lane >= 1 && lane < k) ? lane - 1 : 0)] : 0;
     __builtin_amdgcn_sched_barrier(0);
     const int myP = lane < k ? myP_raw : -1;
@@ -1251,7 +1286,7 @@ __global__ __launch_bounds__(1024) void accept_embed_kernel(StateP s, unsigned l
       if (e < kk) {
         const int a = key_index(kv[q]);
         A_s[e] = a;
-        s.A[(b * s.kmax + e / k) * s.kmax + e % k] = a;
+        if (!fin0) s.A[(b * s.kmax + e / k) * s.kmax + e % k] = a;
       }
     }
     if (fin0) {
@@ -1273,6 +1308,7 @@ __global__ __launch_bounds__(1024) void accept_embed_kernel(StateP s, unsigned l
         s.L[b] = Ln;
         L_s = Ln;
         s.finished[b] = fin;
+        s.steps_done[b] = live_step + 1;
         if (fin) s.fin_step[b] = live_step;
         s.accepted[b] = khat;
         if (accepted_out) accepted_out[b] = khat;
@@ -1286,6 +1322,7 @@ __global__ __launch_bounds__(1024) void accept_embed_kernel(StateP s, unsigned l
     }
   }
   __syncthreads();
+  if (s.dyn && tid == 0) step_tick(s, b, tick);
   for (int e = tid; e < k * k; e += 1024) keys[(long)slot * k * k + e] = 0ull;
   const int slot_next = slots ? slot_s[1] : b;
   if (slot_next < 0) return;

@@ -1,0 +1,70 @@
+"""Kernels and launch paths of small blocks: GEMMs with a constant K at the edges of their row and column tiles, attention at
+the edges of its key groups, whole decodes in one workgroup, and steps that are recorded and replayed as graphs."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from harness import LockStep, gpu_context
+
+pytestmark = pytest.mark.gpu
+
+
+def lockstep(cfg, steps, sched=None, std=0.02):
+    weights = wl.make_weights(cfg, std=std)
+    ctx = gpu_context(cfg, weights)
+    src, n = wl.make_sources(cfg)
+    ls = LockStep(cfg, weights, ctx, src, n, np.full(cfg.batch, cfg.max_out, np.int32), sample=sorted({0, cfg.batch // 2, cfg.batch - 1}))
+    for s in range(steps):
+        ls.step(imposed=np.full(cfg.batch, cfg.k, np.int32) if sched is None else sched[s])
+    return ls
+
+
+# (d, F, k, batch): rows 1, 15 .. 17, 33, 127 .. 129 of each width; F = 3072 and 4096 leave K slices; 768 columns are three quarters of 1024
+@pytest.mark.parametrize("d,F,k,B", [(128, 512, 1, 1), (256, 1024, 5, 3), (512, 2048, 16, 1), (512, 512, 1, 17), (768, 3072, 11, 3), (1024, 4096, 16, 2), (1024, 4096, 3, 11),
+                                     (512, 2048, 1, 127), (256, 512, 8, 16), (1024, 1024, 3, 43)])
+def test_row_blocks(d, F, k, B):
+    cfg = wl.Config("rows", 70, 1, 2, d, d // 64, F, 272, k, B, 3, 2 * k + 4, "bf16", 2, src_len_kind="lognormal")
+    lockstep(cfg, 2)
+
+
+# lengths of the caches on both sides of 32, 128 and 256 keys (a group, four waves, eight waves), sources likewise
+@pytest.mark.parametrize("k,S,out", [(1, 1, 34), (7, 31, 40), (5, 33, 135), (16, 129, 150), (13, 200, 270)])
+def test_key_groups(k, S, out):
+    cfg = wl.Config("keys", 71, 1, 1, 128, 2, 512, 272, k, 2, S, out, "bf16", 2)
+    lockstep(cfg, max(3, out // k))
+
+
+# fp32, one workgroup: widths with and without a LayerNorm of its own, vocabularies of one block to more than a workgroup's columns, row
+# counts past a quad, heads that do not fit LDS together
+@pytest.mark.parametrize("d,F,V,k,S,L", [(32, 32, 16, 1, 1, 1), (64, 256, 272, 4, 17, 2), (96, 384, 832, 9, 33, 2), (64, 512, 1040, 16, 5, 1), (128, 512, 2000, 5, 16, 1)])
+def test_small_models(d, F, V, k, S, L):
+    cfg = wl.Config("small", 72, L, L, d, d // 16, F, V, k, 2, S, 3 * k + 70, "f32", 2, src_kind="uniform3", src_len_kind="lognormal")
+    lockstep(cfg, 5, std=0.08)
+
+
+@pytest.mark.parametrize("B,eos,local", [(1, 2, 0), (3, -1, 0), (2, -1, 40)])
+def test_replayed_steps(B, eos, local):
+    """Decodes and encodes on one context, over and over with other sources and schedules, against steps launched one by one."""
+    cfg = wl.Config("replay", 73, 2, 2, 128, 2, 512, 272, 4, B, 9, 150, "bf16", eos, local_q=local, local_m=local)
+    weights = wl.make_weights(cfg)
+    ctx, ref = gpu_context(cfg, weights), gpu_context(cfg, weights)
+    rng = np.random.default_rng(B)
+    for rep in range(6):
+        S = 9 - rep % 2
+        src = rng.integers(3, cfg.vocab, (B, S)).astype(np.int32)
+        n = np.full(B, S, np.int32)
+        sched = rng.integers(1, cfg.k + 1, (cfg.max_out, B)).astype(np.int32) if rep != 3 else None
+        eps = 1 if rep == 4 else 0
+        for c in (ctx, ref):
+            c.bpd_set_acceptance(eps, 1)
+            c.bpd_encode(src, n)
+        ids, lens, st = ctx.bpd_decode(cfg.k, sched)
+        steps = 0
+        while not np.all(ref.bpd_get_state()[3]):
+            ref.bpd_step(cfg.k, None if sched is None else sched[steps])
+            steps += 1
+        ids2, lens2 = ref.bpd_get_output()
+        assert lens.tolist() == lens2.tolist() and (np.asarray(ids) == np.asarray(ids2)).all()
+        assert st.steps == steps
+        for a, b in zip(ctx.bpd_get_state(), ref.bpd_get_state()):
+            assert (np.asarray(a) == np.asarray(b)).all()
