@@ -827,7 +827,7 @@ void refresh_folded_weights(bpd_ctx* ctx) {
 }
 
 // ------------------------------------------------------------------------------- blocks of few rows (bpd_row_gemm.h)
-constexpr int LEAN_M_MAX = 128;
+constexpr int LEAN_M_MAX = 640;
 // The residual GEMM of K = d_ff runs as one kernel up to this K, beyond in K slices of 1024 that the next LayerNorm adds up
 // (4096 x 1024 at 10 rows: 5.5 us whole, 3.4 us in slices, and the LayerNorm kernel with them 2.0 us, which takes the LayerNorm
 // out of the next GEMM: 4.2 -> 3.05 us.  2048 x 512: 3.3 us whole, and 2.1 + 1.9 - 0.8 us in slices).
@@ -836,32 +836,45 @@ bool lean_ok(const bpd_config& c, int M) {
   return c.dtype == BPD_BF16 && M <= LEAN_M_MAX && lean_width(c.d_model) &&
          (c.d_ff == 512 || c.d_ff == 1024 || c.d_ff == 2048 || c.d_ff == 3072 || c.d_ff == 4096);
 }
-int lean_slices(const bpd_config& c) { return c.d_ff > LEAN_K_WHOLE ? c.d_ff / 1024 : 1; }
+constexpr int LEAN_PART_M = 192;        // more rows: the slices of the LDS-staged kernel (192 rows 6.8 against 7.25 us, 256 rows 8.0 against 7.3)
+constexpr int LEAN_WHOLE_M = 256;       // ... as well for K = 2048 (256 rows 4.6 against 4.3 us, 320 rows 5.6 against 5.2)
+int lean_slices(const bpd_ctx* ctx, int M) {
+  const bpd_config& c = ctx->cfg;
+  if (c.d_ff > LEAN_K_WHOLE && M <= LEAN_PART_M) return c.d_ff / 1024;
+  return c.d_ff > LEAN_K_WHOLE || (c.d_ff == LEAN_K_WHOLE && M > LEAN_WHOLE_M) ? residual_k_slices(ctx, gp(nullptr, c.d_ff, nullptr, c.d_model, M, c.d_model, c.d_ff)) : 1;
+}
 // LayerNorm inside the GEMM that follows, or in a kernel of its own?  (with K = 1024 every column block of 64 KB of x costs: 24 rows
-// 5.05 us against 1.9 + 3.6, 40 rows 6.6 against 2.0 + 4.3; with K = 512 80 rows 3.3 against 1.9 + 2.5, 128 rows 4.4 against 1.9 + 2.9)
-bool lean_fuse(int d, int M) { return d <= 512 || M <= 32; }
+// 5.05 us against 1.9 + 3.6, 40 rows 6.6 against 2.0 + 4.3; with K = 512 80 rows 3.3 against 1.9 + 2.5, 256 rows 5.4 against 1.9 + 3.9, 320 rows 6.8
+// against 1.9 + 4.3)
+bool lean_fuse(int d, int M) { return d <= 512 ? M <= 256 : M <= 32; }
 
 template <int WAVES, int U, bool LN, int EPI>
 void launch_row_gemm(const bpd_ctx* ctx, const RowGemmP& p, int slices) {
   // the smallest tile that needs no more workgroups than there are CUs: a second round of workgroups costs more than the wider tile
+  // (no tile gets there: two rows of tiles, many workgroups)
   auto wgs = [&](int mt, int nt) { return (long)((p.ntiles + nt - 1) / nt) * ((p.M + 16 * mt - 1) / (16 * mt)) * slices; };
 #define BPD_RG(MT_, NT_) hipLaunchKernelGGL((row_gemm_kernel<WAVES, U, MT_, NT_, LN, EPI>), dim3((p.ntiles + NT_ - 1) / NT_, (p.M + 16 * MT_ - 1) / (16 * MT_), slices), \
                                             dim3(64 * WAVES), 0, ctx->stream, p)
   if (wgs(1, 1) <= ctx->num_cus) BPD_RG(1, 1);
   else if (wgs(1, 2) <= ctx->num_cus) BPD_RG(1, 2);
-  else if (LN || wgs(1, 4) <= ctx->num_cus) BPD_RG(1, 4);
-  else BPD_RG(2, 4);
+  else if (LN || U > 4 || wgs(1, 4) <= ctx->num_cus) BPD_RG(1, 4);
+  else if constexpr (!LN && U <= 4) {      // (U = 8: K = 2048, at most 256 rows)
+    if (wgs(2, 4) <= ctx->num_cus) BPD_RG(2, 4);
+    else if (wgs(3, 4) <= ctx->num_cus) BPD_RG(3, 4);
+    else if (wgs(4, 4) <= ctx->num_cus) BPD_RG(4, 4);
+    else BPD_RG(2, 4);
+  }
 #undef BPD_RG
 }
 template <bool LN, int EPI>
-void row_gemm(const bpd_ctx* ctx, const RowGemmP& p, int K) {
+void row_gemm(const bpd_ctx* ctx, const RowGemmP& p, int K, int z = 1) {
   switch (K) {
-    case 128: launch_row_gemm<4, 1, LN, EPI>(ctx, p, 1); break;
-    case 256: launch_row_gemm<4, 2, LN, EPI>(ctx, p, 1); break;
-    case 512: launch_row_gemm<4, 4, LN, EPI>(ctx, p, 1); break;
-    case 768: launch_row_gemm<8, 3, LN, EPI>(ctx, p, 1); break;
-    case 1024: launch_row_gemm<8, 4, LN, EPI>(ctx, p, 1); break;
-    default: if constexpr (EPI == RG_RES) launch_row_gemm<8, 8, LN, EPI>(ctx, p, 1); break;      // 2048
+    case 128: launch_row_gemm<4, 1, LN, EPI>(ctx, p, z); break;
+    case 256: launch_row_gemm<4, 2, LN, EPI>(ctx, p, z); break;
+    case 512: launch_row_gemm<4, 4, LN, EPI>(ctx, p, z); break;
+    case 768: launch_row_gemm<8, 3, LN, EPI>(ctx, p, z); break;
+    case 1024: launch_row_gemm<8, 4, LN, EPI>(ctx, p, z); break;
+    default: if constexpr (EPI == RG_RES) launch_row_gemm<8, 8, LN, EPI>(ctx, p, z); break;      // 2048
   }
 }
 // Y = relu(LayerNorm(x) W + b), or queries / K / V from LayerNorm(x) W.  xn: room for the normalised rows
@@ -894,7 +907,9 @@ void lean_residual(bpd_ctx* ctx, const void* X, int K, const void* W, const floa
   const int d = ctx->cfg.d_model;
   RowGemmP p = rg(X, K, W, M, d);
   p.ldy = d; p.bias = bias;
-  if (K > LEAN_K_WHOLE) {
+  if (K >= LEAN_K_WHOLE && M > (K > LEAN_K_WHOLE ? LEAN_PART_M : LEAN_WHOLE_M)) {
+    gemm(ctx, gp(X, K, W, d, M, d, K), plain(bias, 0, x, d, x, d, nullptr, 0));
+  } else if (K > LEAN_K_WHOLE) {
     p.Y = ctx->lay.kpart; p.ksteps = K / 32;
     launch_row_gemm<8, 4, false, RG_PART>(ctx, p, K / 1024);
     ctx->pend_slices = K / 1024; ctx->pend_bias = bias ? bias : ctx->lay.zeros; ctx->pend_x = x;
@@ -958,8 +973,14 @@ int forward(bpd_ctx* ctx, int R, int k, int zero_input, float* logits) {
       const Epi kv = kv_split(ctx, L.q, Kl, Vl, 0, R, slots, base, seq);
       const bool qproj = attention_qproj_ok(ctx, B, R);
       if (lean) {
-        lean_ln_gemm<RG_QKV>(ctx, L.x, w.ln1, L.xn, rg_kv(ctx, nullptr, w.wqkv, M, 3 * d, kv));
-        attention(ctx, L.q, Kl, Vl, L.attn, slots, B, R, base, 1, seq);
+        if (zero_input && R == 1) {              // on the empty prefix: a row sees one key, its own, and its attention is that key's value
+          RowGemmP q = rg_kv(ctx, nullptr, (const char*)w.wqkv + (size_t)d * d * as, M, 2 * d, kv);
+          q.chunk0 = 1; q.vout = (bf16_t*)L.attn;
+          lean_ln_gemm<RG_QKV>(ctx, L.x, w.ln1, L.xn, q);
+        } else {
+          lean_ln_gemm<RG_QKV>(ctx, L.x, w.ln1, L.xn, rg_kv(ctx, nullptr, w.wqkv, M, 3 * d, kv));
+          attention(ctx, L.q, Kl, Vl, L.attn, slots, B, R, base, 1, seq);
+        }
         lean_residual(ctx, L.attn, d, w.wo, nullptr, M, L.x);
         if (qproj) {
           const QProjP qp{L.x, w.ln2.g, w.ln2.b, w.cq, c.ln_eps};
@@ -1157,11 +1178,21 @@ int encoder(bpd_ctx* ctx) {
     xs = gemm(ctx, gp(L.ffhe, F, w.w2, d, M, d, F), residual(w.b2));
   }
   layernorm(ctx, L.xe, L.enc_lnf, M, L.mem, nullptr);
-  for (int l = 0; l < c.n_dec_layers; ++l) {
-    const size_t at = (size_t)l * c.max_batch * kv_rows(c, c.max_src_len) * d * as;
-    const Epi kv = kv_split(ctx, nullptr, (char*)L.crossK + at, (char*)L.crossV + at, 1, S, c.max_src_len, nullptr, nullptr);
-    if (lean) row_gemm<false, RG_QKV>(ctx, rg_kv(ctx, L.mem, L.dec[l].ckv, M, 2 * d, kv), d);
-    else gemm(ctx, gp(L.mem, d, L.dec[l].ckv, 2 * d, M, 2 * d, d), kv);
+  // cross keys and values of all decoder layers in one launch (fp32 and shapes without a tiled kernel: one each)
+  const size_t src_layer = (size_t)c.max_batch * kv_rows(c, c.max_src_len) * d;
+  const long wz = c.n_dec_layers > 1 ? ((const char*)L.dec[1].ckv - (const char*)L.dec[0].ckv) / (long)as : 0;      // (every layer's arrays are laid out alike)
+  const bool together = lean || (c.dtype == BPD_BF16 && d % 64 == 0 && M > 16);
+  for (int l = 0; l < (together ? 1 : c.n_dec_layers); ++l) {
+    Epi kv = kv_split(ctx, nullptr, (char*)L.crossK + src_layer * l * as, (char*)L.crossV + src_layer * l * as, 1, S, c.max_src_len, nullptr, nullptr);
+    if (lean) {
+      RowGemmP p = rg_kv(ctx, L.mem, L.dec[l].ckv, M, 2 * d, kv);
+      p.wz = wz; p.kvz = (long)src_layer;
+      row_gemm<false, RG_QKV>(ctx, p, d, c.n_dec_layers);
+    } else {
+      GemmP p = gp(L.mem, d, L.dec[l].ckv, 2 * d, M, 2 * d, d);
+      if (together) { p.w_g = wz; kv.kv_g = (long)src_layer; }
+      gemm(ctx, p, kv, together ? c.n_dec_layers : 1);
+    }
   }
   LAUNCHCHK();
   return BPD_OK;
@@ -1565,10 +1596,10 @@ static int step_accept(bpd_ctx* ctx, int k, int* accepted_dev, int next_slots, u
       // the accept kernel also embeds the next block (same k assumed; checked by forward); its LayerNorm statistics go
       // where the first layer will look for them: the single-tile layout for at most 16 rows, per-tile rows otherwise
       const int rows = next_slots * k;
-      const bool sp = stats_path(ctx, rows);
+      const bool sp = stats_path(ctx, rows), lean = lean_ok(c, rows);
       hipLaunchKernelGGL(accept_embed_kernel, dim3(ctx->B), dim3(1024), 0, ctx->stream, s, L.keys, k, ctx->B, imposed_step, accepted_dev,
                          c.d_model, (const bf16_t*)L.emb, c.vocab, (const float*)L.pos_tgt, sqrtf((float)c.d_model), L.x,
-                         sp ? L.stats_ln : L.stats_big, sp ? 16 : rows, sp ? (bf16_t*)nullptr : (bf16_t*)L.xn, (int)ctx->steps,
+                         lean ? nullptr : (sp ? L.stats_ln : L.stats_big), sp ? 16 : rows, sp || lean ? (bf16_t*)nullptr : (bf16_t*)L.xn, (int)ctx->steps,
                          !slots_used(ctx) ? 0 : (ctx->seq ? 2 : 1));
       ctx->x_ready_k = k; ctx->x_ready_slots = next_slots;
     } else {
@@ -1640,7 +1671,7 @@ int bpd_step_static(bpd_ctx* ctx, int k, const int32_t* imposed_accept, int32_t*
     if (ns > 1) attn_b = std::max(attn_b, up(ns * wgs * 16 * (d / c.n_heads + 2) * 4));
   }
   size_t slices = 1;
-  if (lean_ok(c, (int)M)) slices = lean_slices(c);
+  if (lean_ok(c, (int)M)) slices = lean_slices(ctx, (int)M);
   else if (c.dtype == BPD_BF16 && M > 16)
     for (int K : {c.d_model, c.d_ff}) {
       const int ns = residual_k_slices(ctx, gp(nullptr, K, nullptr, c.d_model, (int)M, c.d_model, K));

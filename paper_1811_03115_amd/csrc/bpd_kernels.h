@@ -117,6 +117,7 @@ struct Epi {
   int dsplit, chunk0, rows_per_seq, cap;
   const int* base;
   int capg; const int* seq;
+  long kv_g;           // elements between the caches of two groups
 };
 
 template <typename ACT>
@@ -135,7 +136,7 @@ __device__ __forceinline__ void epi_store(const Epi& e, int g, int m, int n, flo
     } else {
       const int b = m / e.rows_per_seq, i = m % e.rows_per_seq;
       const long row = (long)b * e.cap + (e.base ? e.base[b] : 0) + i;
-      ACT* dst = (ACT*)(c == 1 ? e.Ka : e.Va);
+      ACT* dst = (ACT*)(c == 1 ? e.Ka : e.Va) + g * e.kv_g;
       dst[row * e.dsplit + col] = from_f<ACT>(v);
     }
   }
@@ -172,7 +173,7 @@ __device__ __forceinline__ void epi_store4f(const Epi& e, int g, int m, int n, c
       *(float4*)(e.Qf + (long)m * e.dsplit + col) = make_float4(v[0], v[1], v[2], v[3]);
     } else {
       const int b = m / e.rows_per_seq, i = m % e.rows_per_seq;
-      bf16_t* dst = (bf16_t*)(c == 1 ? e.Ka : e.Va);
+      bf16_t* dst = (bf16_t*)(c == 1 ? e.Ka : e.Va) + g * e.kv_g;
       const unsigned lo = cvt_pk_bf16(v[0], v[1]), hi = cvt_pk_bf16(v[2], v[3]);
       if (e.capg) {
         const int sb = e.seq ? e.seq[b] : b;
@@ -1219,7 +1220,7 @@ __global__ __launch_bounds__(64) void accept_kernel(StateP s, const unsigned lon
 // the sequence's k next rows (token i = new proposal i, position = new L + i) with their partial LayerNorm statistics,
 // exactly as embed_stats_kernel would at the start of the next step, and the sequence's k*k arg-max keys are cleared
 // for the next vocabulary projection.
-// stats: srows = 16: [(tile * 16 + row) * 2] per 16-column tile; otherwise srows = the rows of the next block and one entry per
+// stats (null: not wanted): srows = 16: [(tile * 16 + row) * 2] per 16-column tile; otherwise srows = the rows of the next block and one entry per
 // 64-column block, [(block * srows + row) * 2]; xb (may be null):
 // bf16 copy of the rows as well.
 // slots != 0: the next step's slots are dealt here (StateP::slot_seq); 2: this step's rows and keys are indexed by slot too.
@@ -1350,18 +1351,19 @@ __global__ __launch_bounds__(1024) void accept_embed_kernel(StateP s, unsigned l
     float v[4] = {pv.x, pv.y, pv.z, pv.w};
     v[0] += scale * __uint_as_float(raw.x << 16); v[1] += scale * __uint_as_float(raw.x & 0xFFFF0000u);
     v[2] += scale * __uint_as_float(raw.y << 16); v[3] += scale * __uint_as_float(raw.y & 0xFFFF0000u);
-    float sv = (v[0] + v[1]) + (v[2] + v[3]);
-    float qv = (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
-    sv += __shfl_xor(sv, 16, 64); sv += __shfl_xor(sv, 32, 64);
-    qv += __shfl_xor(qv, 16, 64); qv += __shfl_xor(qv, 32, 64);
-    bs += sv; bq += qv;
-    if (!per_block && lane < 16 && i < k) ((float2*)stats)[(long)tile * srows + row] = make_float2(sv, qv);
+    float sv = 0.f, qv = 0.f;
+    if (stats) {
+      sv = sum_rows((v[0] + v[1]) + (v[2] + v[3]));
+      qv = sum_rows((v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]));
+      bs += sv; bq += qv;
+    }
+    if (stats && !per_block && lane < 16 && i < k) ((float2*)stats)[(long)tile * srows + row] = make_float2(sv, qv);
     if (i < k) {
       *(float4*)(x + (long)row * d + c0) = make_float4(v[0], v[1], v[2], v[3]);
       if (xb) *(uint2*)(xb + (long)row * d + c0) = make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
     }
   }
-  if (per_block && 4 * wave < ntiles && lane < 16 && i < k) ((float2*)stats)[(long)wave * srows + row] = make_float2(bs, bq);
+  if (stats && per_block && 4 * wave < ntiles && lane < 16 && i < k) ((float2*)stats)[(long)wave * srows + row] = make_float2(bs, bq);
 }
 
 #include "bpd_small.h"

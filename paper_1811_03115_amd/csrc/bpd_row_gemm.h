@@ -1,4 +1,4 @@
-// GEMMs and LayerNorms of blocks of up to 128 rows, one memory round trip per kernel.  Included by bpd_kernels.h.
+// GEMMs and LayerNorms of blocks of up to 640 rows, one memory round trip per kernel.  Included by bpd_kernels.h.
 //
 // A decoding step is a chain of small dependent kernels.  A kernel that does nothing costs 1.7 us in such a chain, and
 // what the step's kernels took beyond that (2.2 .. 5.3 us) was mostly not data: four rounds of argument loads, 64-bit
@@ -23,6 +23,8 @@ struct RowGemmP {
   int capg, cap;                       // 64-wide heads: groups of 32 keys per sequence (bpd_attention.h); otherwise 0, and rows per sequence
   bf16_t* Kc; bf16_t* Vc;
   const int* base; const int* seq;     // first key row of each slot (null: 0) and its sequence (null: the slot; -1: none)
+  long wz, kvz;                        // several matrices and caches side by side (grid z; cross keys and values of all layers): elements between them
+  bf16_t* vout;                        // not null: values also to [M][K] (a row that sees one key: its attention is that key's value)
 };
 
 // Y = epilogue(X W) for 16 MT rows x 16 NT columns per workgroup, K = 32 * WAVES * U (PART: of one slice, grid z).  The waves
@@ -31,10 +33,11 @@ struct RowGemmP {
 // LN: X = LayerNorm(x): every wave adds up its columns of the rows, the sums meet in LDS, and the wave normalises in
 // registers the fragments it already holds.  One barrier more than without, and twice the bytes for x: 0.8 us at K = 512,
 // 1.2 us at K = 1024, against 1.9 us for a LayerNorm kernel of its own; but every column block repeats it, so that with
-// K = 1024 and more than 32 rows the kernel of its own is the faster one (lean_fuse() in bpd.hip).
+// K = 1024 and more than 32 rows (K = 512: 256) the kernel of its own is the faster one (lean_fuse() in bpd.hip).
 // 8 x 512 x 1536 with LayerNorm: 3.95 -> 2.84 us per kernel of a chain;  10 x 1024 x 3072: 5.6 -> 4.2;  8 x 512 x 512: 3.2 -> 2.1;
-// 10 x 1024 x 1024: 3.7 -> 2.6.  More waves (16), fewer columns per workgroup (8, 4 of a tile) and more rows (MT = 2, 3) are slower
-// except for MT = 2 with NT = 4 where one row tile would need more workgroups than there are CUs.
+// 10 x 1024 x 1024: 3.7 -> 2.6.  More waves (16) and fewer columns per workgroup (8, 4 of a tile) are slower; more columns (NT), then more
+// rows (MT), pay once the workgroups would outnumber the CUs: 192 x 1024 x 3072 8.1 us with MT = 1, 7.05 with 3 (the LDS-staged kernel 10.2), 320 x 1024 x
+// 1024 5.1 with 2 (5.85).
 template <int WAVES, int U, int MT, int NT, bool LN, int EPI>
 __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
   constexpr int KSTEPS = WAVES * U, K = 32 * KSTEPS, TILES = MT * NT, OWN = (TILES + WAVES - 1) / WAVES, XB = LN ? 4 : 2;
@@ -49,7 +52,7 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
 #pragma unroll
   for (int u = 0; u < NT; ++u) {
     const int tile = NT > 1 && tile0 + u >= p.ntiles ? p.ntiles - 1 : tile0 + u;
-    const char* Wb = (const char*)p.W + ((size_t)tile * ksteps + ks0) * 1024;
+    const char* Wb = (const char*)p.W + ((size_t)tile * ksteps + ks0) * 1024 + (EPI == RG_QKV ? blockIdx.z * p.wz * 2 : 0);
 #pragma unroll
     for (int i = 0; i < U; ++i) a[u][i] = *(const u32x4*)(Wb + i * 1024 + lane * 16);
   }
@@ -183,8 +186,9 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
       if (c + p.chunk0 == 0) {
         *(f32x4*)((float*)Y + (size_t)m * K + col) = v;
       } else if (sb[j] >= 0) {                   // (a slot behind the last one has no cache rows)
-        bf16_t* cache = c + p.chunk0 == 1 ? Kc : Vc;
+        bf16_t* cache = (c + p.chunk0 == 1 ? Kc : Vc) + blockIdx.z * p.kvz;
         const unsigned lo = cvt_pk_bf16(v[0], v[1]), hi = cvt_pk_bf16(v[2], v[3]);
+        if (p.vout && c + p.chunk0 == 2) *(u32x2*)(p.vout + (size_t)m * K + col) = u32x2{lo, hi};
         if (p.capg) kv_frag_store(cache, c + p.chunk0 == 2, sb[j], p.heads, p.capg, key0[j] + row0[j], col, lo, hi);
         else *(u32x2*)(cache + (size_t)(key0[j] + row0[j]) * K + col) = u32x2{lo, hi};
       }
