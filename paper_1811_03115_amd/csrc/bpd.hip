@@ -48,7 +48,7 @@ struct bpd_ctx {
   int B = 0, S = 0;
   bool encoded = false;
   bool fold_ready = false;        // the folded copies match the loaded weights
-  int64_t steps = 0;
+  int64_t steps = 0;              // steps enqueued since bpd_encode: bounds the cache lengths (the count itself is on the device, StateP::steps_done)
   int distance_eps = 0, min_block = 1, top_n = 1, two_phase = 0;
   int local_q = 0, local_m = 0;   // 1D local self-attention in the decoder (0: full causal), bpd_set_local_attention
   int num_cus = 256;                   // compute units of the device the context was created on
@@ -1599,11 +1599,11 @@ static int step_accept(bpd_ctx* ctx, int k, int* accepted_dev, int next_slots, u
       const bool sp = stats_path(ctx, rows), lean = lean_ok(c, rows);
       hipLaunchKernelGGL(accept_embed_kernel, dim3(ctx->B), dim3(1024), 0, ctx->stream, s, L.keys, k, ctx->B, imposed_step, accepted_dev,
                          c.d_model, (const bf16_t*)L.emb, c.vocab, (const float*)L.pos_tgt, sqrtf((float)c.d_model), L.x,
-                         lean ? nullptr : (sp ? L.stats_ln : L.stats_big), sp ? 16 : rows, sp || lean ? (bf16_t*)nullptr : (bf16_t*)L.xn, (int)ctx->steps,
+                         lean ? nullptr : (sp ? L.stats_ln : L.stats_big), sp ? 16 : rows, sp || lean ? (bf16_t*)nullptr : (bf16_t*)L.xn,
                          !slots_used(ctx) ? 0 : (ctx->seq ? 2 : 1));
       ctx->x_ready_k = k; ctx->x_ready_slots = next_slots;
     } else {
-      hipLaunchKernelGGL(accept_kernel, dim3(ctx->B), dim3(64), 0, ctx->stream, s, L.keys, k, ctx->B, 1, imposed_step, accepted_dev, (int)ctx->steps);
+      hipLaunchKernelGGL(accept_kernel, dim3(ctx->B), dim3(64), 0, ctx->stream, s, L.keys, k, ctx->B, 1, imposed_step, accepted_dev);
       ctx->x_ready_k = 0;
     }
   }
@@ -1800,7 +1800,7 @@ int bpd_decode(bpd_ctx* ctx, int k, const int32_t* schedule, int max_steps, int3
     }
     if (ctx->report_tag > 0x7FFFFFFFu) ctx->report_tag = 2;        // (turns kept; far from the tags that old words hold)
     const long n = (long)rows * B;
-    const StepDyn dyn{imp, B, rows, ctx->report_tag, (int)ctx->steps, ctx->report, ctx->cfg.max_batch};
+    const StepDyn dyn{imp, B, rows, ctx->report_tag, ctx->report, ctx->cfg.max_batch};
     if (max_steps > 0)
       hipLaunchKernelGGL(decode_init_kernel, dim3((unsigned)((std::max<long>(n, B) + 255) / 256)), dim3(256), 0, ctx->stream, state_params(ctx), dyn, (StepDyn*)L.dyn,
                          src, L.sched, n, B);
@@ -1926,7 +1926,7 @@ int bpd_debug_step_logits(bpd_ctx* ctx, int k, float* logits) {
   }
   int rc = forward(ctx, k, k, 0, logits);
   if (rc) return rc;
-  hipLaunchKernelGGL(accept_kernel, dim3(ctx->B), dim3(64), 0, ctx->stream, state_params(ctx), ctx->lay.keys, k, ctx->B, 0, 0, nullptr, 0);
+  hipLaunchKernelGGL(accept_kernel, dim3(ctx->B), dim3(64), 0, ctx->stream, state_params(ctx), ctx->lay.keys, k, ctx->B, 0, 0, nullptr);
   LAUNCHCHK();
   return BPD_OK;
 }

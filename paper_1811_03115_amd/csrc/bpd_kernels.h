@@ -933,7 +933,7 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(AttnP p) {
 // graph.  Set by decode_init_kernel; the steps are counted by StateP::tick.
 struct StepDyn {
   const int* imposed; int imposed_stride, rows;      // the schedule (null: none), its rows
-  unsigned tag0; int live0;                          // report tag and number of steps made before the first step
+  unsigned tag0;                                     // report tag before the first step
   unsigned long long* report; int report_stride;     // two turns of report words
 };
 
@@ -958,10 +958,12 @@ struct StateP {
   unsigned long long* report; unsigned report_tag;
   // Slots: the rows of a step belong to the sequences that had not ended when the step before it began, packed in
   // sequence order, so that a batch of unequal lengths does not compute the rows of those that are done.
-  const StepDyn* dyn;  // steps of a bpd_decode: imposed, report and the step counters come from here
+  const StepDyn* dyn;  // steps of a bpd_decode: imposed and report come from here
   int* tick;           // [B] ... its steps so far
   int* imp_next;       // [B] ... and the value imposed on the next (looked up by the step before: no chain of loads)
-  int* steps_done;     // [B] steps that the sequence has made since bpd_encode
+  int* steps_done;     // [B] steps since bpd_encode (of a sequence that has not ended: its own; accept_embed_kernel, which deals the slots
+                       // by it, counts on in the others).  Kept here and not by the host: a step that was captured is replayed
+                       // without it.
   int* fin_step;       // [B] step (since bpd_encode) that ended the sequence, INT_MAX before
   int* slot_seq;       // [B] sequence of each slot of the next step, -1 behind the last
   int* slot_L; int* slot_src;   // [B] cache length and source length of that sequence
@@ -972,13 +974,12 @@ struct StateP {
   const int* src_len;
 };
 
-// A step of a bpd_decode: fills the fields that come from dyn, returns the number of steps since bpd_encode
-__device__ __forceinline__ int step_from_dyn(StateP& s, int tick) {
+// A step of a bpd_decode: fills the fields that come from dyn
+__device__ __forceinline__ void step_from_dyn(StateP& s, int tick) {
   const StepDyn d = *s.dyn;
   const unsigned tag = d.tag0 + 1u + (unsigned)tick;
   s.imposed = d.imposed; s.imposed_stride = d.imposed_stride;
   s.report = d.report + (size_t)(tag & 1) * d.report_stride; s.report_tag = tag;
-  return d.live0 + tick;
 }
 // ... and, once everybody has read the counter: on to the next step
 __device__ __forceinline__ void step_tick(const StateP& s, int b, int tick) {
@@ -1169,14 +1170,14 @@ __global__ __launch_bounds__(256) void assemble_keys_kernel(const unsigned long 
 //   value; then cut at the first EOS (inclusive) and at max_len; append; L += k-hat commits
 //   the cache rows of the accepted tokens (rejected rows are simply overwritten next step);
 //   P <- row k-hat of the table.
-//   step: row of the imposed schedule; live_step: steps made since the last bpd_encode (for the step counter).
+//   step: row of the imposed schedule.
 __global__ __launch_bounds__(64) void accept_kernel(StateP s, const unsigned long long* keys, int k, int B,
-                                                    int commit, int step, int* accepted_out, int live_step) {
+                                                    int commit, int step, int* accepted_out) {
   const int b = blockIdx.x, lane = threadIdx.x;
   if (b >= B) return;
-  const int tick = s.dyn && commit ? s.tick[b] : 0;
+  const int tick = s.dyn && commit ? s.tick[b] : 0, live_step = s.steps_done[b];
   int imp = 0;
-  if (s.dyn && commit) { live_step = step_from_dyn(s, tick); imp = s.imp_next[b]; if (lane == 0) step_tick(s, b, tick); }
+  if (s.dyn && commit) { step_from_dyn(s, tick); imp = s.imp_next[b]; if (lane == 0) step_tick(s, b, tick); }
   else if (s.imposed) imp = s.imposed[(long)step * s.imposed_stride + b];
   if (commit && s.finished[b]) {
     if (lane == 0) { s.accepted[b] = 0; if (accepted_out) accepted_out[b] = 0; report_remaining(s, b, 0); }
@@ -1227,15 +1228,15 @@ __global__ __launch_bounds__(64) void accept_kernel(StateP s, const unsigned lon
 __global__ __launch_bounds__(1024) void accept_embed_kernel(StateP s, unsigned long long* keys, int k, int B, int step,
                                                             int* accepted_out, int d, const bf16_t* E, int V,
                                                             const float* pos, float scale, float* x, float* stats,
-                                                            int srows, bf16_t* xb, int live_step, int slots) {
+                                                            int srows, bf16_t* xb, int slots) {
   __shared__ int tok_s[16];
   __shared__ int L_s;
   __shared__ int slot_s[2];                      // this sequence's slot in this step and in the next (-1: none)
   __shared__ int A_s[256];                       // the sequence's k x k arg-max table
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (b >= B) return;
-  const int tick = s.dyn ? s.tick[b] : 0;
-  if (s.dyn) live_step = step_from_dyn(s, tick);
+  const int live_step = s.steps_done[b], tick = s.dyn ? s.tick[b] : 0;      // (the same for every sequence: each launch moves all on by one)
+  if (s.dyn) step_from_dyn(s, tick);
   // Slots of this step (sequences not ended before step live_step - 1) and of the next (not before this one).  (The
   // workgroups of this launch write fin_step too: live_step, which both tests let pass.)  With all of the batch in this
   // step (slots == 1) the slot is the sequence and only the next step's is worked out, by a wave of its own.
@@ -1264,7 +1265,7 @@ __global__ __launch_bounds__(1024) void accept_embed_kernel(StateP s, unsigned l
     __syncthreads();
     slot = slot_s[0];
     if (slot < 0) {                              // ended before the step began: no rows, nothing to do
-      if (tid == 0) { s.accepted[b] = 0; if (accepted_out) accepted_out[b] = 0; report_remaining(s, b, 0); if (s.dyn) step_tick(s, b, tick); }
+      if (tid == 0) { s.accepted[b] = 0; if (accepted_out) accepted_out[b] = 0; report_remaining(s, b, 0); s.steps_done[b] = live_step + 1; if (s.dyn) step_tick(s, b, tick); }
       return;
     }
   }
@@ -1309,7 +1310,6 @@ __global__ __launch_bounds__(1024) void accept_embed_kernel(StateP s, unsigned l
         s.L[b] = Ln;
         L_s = Ln;
         s.finished[b] = fin;
-        s.steps_done[b] = live_step + 1;
         if (fin) s.fin_step[b] = live_step;
         s.accepted[b] = khat;
         if (accepted_out) accepted_out[b] = khat;
@@ -1323,7 +1323,7 @@ __global__ __launch_bounds__(1024) void accept_embed_kernel(StateP s, unsigned l
     }
   }
   __syncthreads();
-  if (s.dyn && tid == 0) step_tick(s, b, tick);
+  if (tid == 0) { s.steps_done[b] = live_step + 1; if (s.dyn) step_tick(s, b, tick); }
   for (int e = tid; e < k * k; e += 1024) keys[(long)slot * k * k + e] = 0ull;
   const int slot_next = slots ? slot_s[1] : b;
   if (slot_next < 0) return;

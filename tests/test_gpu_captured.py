@@ -1,0 +1,77 @@
+"""Calls that the caller captures into a HIP graph and replays: what a replay does may not depend on what the host knew when
+the call was recorded."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def context(cfg, weights, stream=None):
+    from paper_1811_03115_amd import binding
+    ctx = binding.Context(binding.config_from_workload(cfg), stream=stream)
+    ctx.bpd_load_weights(weights)
+    return ctx
+
+
+def capture(stream, call):
+    """A graph of what `call` enqueues on `stream`."""
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream, capture_error_mode="thread_local"):
+        call()
+    return g
+
+
+def replay(g, stream):
+    with torch.cuda.stream(stream):
+        g.replay()
+
+
+def snapshot(ctx):
+    st = ctx.bpd_get_stats()
+    return [np.array(v) for v in ctx.bpd_get_state()] + [np.array(v) for v in ctx.bpd_get_output()] + [np.array([st.steps, st.seq_steps, st.accepted_total, st.finished])]
+
+
+def same(a, b, what):
+    for u, v in zip(a, b):
+        np.testing.assert_array_equal(u, v, err_msg=what)
+
+
+def job(cfg, seed):
+    """Sources and budgets: one sequence ends in every other step from the second on, at two tokens a step."""
+    src, n = wl.make_sources(cfg)
+    budget = np.minimum(4 * np.arange(1, cfg.batch + 1), cfg.max_out).astype(np.int32)
+    return src, n, np.random.default_rng(seed).permutation(budget)
+
+
+# one row tile; several, of a width without and with kernels of a constant K; two-phase scoring
+@pytest.mark.parametrize("d,F,k,B,two_phase", [(128, 512, 3, 4, False), (192, 384, 5, 6, False), (128, 512, 4, 9, False), (128, 512, 5, 7, True)])
+def test_step_captured_after_a_sequence_has_ended(d, F, k, B, two_phase):
+    cfg = wl.Config("captured", 80, 1, 2, d, d // 64, F, 272, k, B, 7, 4 * B, "bf16", -1, src_len_kind="lognormal")
+    weights = wl.make_weights(cfg)
+    stream = torch.cuda.Stream()
+    ref, cap = context(cfg, weights), context(cfg, weights, stream)
+    src, n, budget = job(cfg, B)
+    two = torch.full((B,), 2, dtype=torch.int32, device="cuda")
+    acc = torch.zeros((2, B), dtype=torch.int32, device="cuda")
+    for c in (ref, cap):
+        c.bpd_set_two_phase(two_phase)
+        c.bpd_encode(src, n, budget)
+        for _ in range(2):
+            c.bpd_step(k, two)
+    assert ref.bpd_get_state()[3].sum() == 1
+    same(snapshot(ref), snapshot(cap), "before the capture")
+    g = capture(stream, lambda: cap.bpd_step_static(k, two, acc[1]))
+    same(snapshot(ref), snapshot(cap), "recorded, not run")
+    for s in range(2 * B - 1):
+        ref.bpd_step(k, two, acc[0])
+        replay(g, stream)
+        same(snapshot(ref), snapshot(cap), f"replay {s}")
+        torch.cuda.synchronize()
+        assert acc[0].tolist() == acc[1].tolist()
+        if s == B:                                         # a direct step in between
+            ref.bpd_step(k, two)
+            cap.bpd_step_static(k, two)
+    assert ref.bpd_get_state()[3].all()
