@@ -34,8 +34,9 @@ struct WEntry {
   bool loaded;
 };
 
-// A sequence of launches that depends on nothing but `key`
-struct Plan { std::array<long, 8> key; int seen; bool failed; hipGraphExec_t exec; unsigned long long used; };
+// A sequence of launches that depends on nothing but `key`: one word for each setting (packed into one word, settings of any size collide)
+typedef std::array<long, 10> PlanKey;
+struct Plan { PlanKey key; int seen; bool failed; hipGraphExec_t exec; unsigned long long used; };
 
 }  // namespace
 
@@ -1221,7 +1222,7 @@ bool is_host_ptr_cached(bpd_ctx* ctx, const void* p) {
 constexpr size_t PLANS_MAX = 24;
 enum { PLAN_ENCODE, PLAN_STEP };
 template <class F>
-int run_planned(bpd_ctx* ctx, const std::array<long, 8>& key, F enqueue) {
+int run_planned(bpd_ctx* ctx, const PlanKey& key, F enqueue) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   // (not while phases are timed, nor inside a graph of the caller's, nor with the decoder stack kernel, whose flags count its launches)
   if (ctx->prof_phase != 0 || (ctx->stack_workers > 0 && !ctx->stack_off) || hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
@@ -1556,7 +1557,7 @@ int bpd_encode(bpd_ctx* ctx, const int32_t* src_ids, const int32_t* src_len, con
     small_encode(ctx);
   } else {
     ctx->steps = 0;
-    const int rc = run_planned(ctx, {PLAN_ENCODE, B, S, ctx->local_q, ctx->local_m, 0, 0, 0}, [&]() -> int {
+    const int rc = run_planned(ctx, {PLAN_ENCODE, B, S, ctx->local_q, ctx->local_m}, [&]() -> int {
       int rc = encoder(ctx);
       if (rc) return rc;
       // first invocation: position 0 only, all heads -> first proposals
@@ -1855,8 +1856,9 @@ int bpd_decode(bpd_ctx* ctx, int k, const int32_t* schedule, int max_steps, int3
     for (int b = 0; planned && B > 1 && b < B; ++b) planned = rem[b] > (know ? 0 : k);
     if (planned) {
       use_slots(ctx, B);
-      const bool few = attention_keys(ctx, ctx->cfg.max_out_len + ctx->cfg.k_max + 1, k, 1) <= 128;
-      const int rc = run_planned(ctx, {PLAN_STEP, B, k, attention_nsplit(ctx, ctx->cfg.max_out_len + ctx->cfg.k_max + 1, B, k, 1) * 2 + few, ctx->top_n, ctx->local_q * 4096L + ctx->distance_eps, ctx->local_m * 32L + ctx->min_block, 0},
+      const int cap = ctx->cfg.max_out_len + ctx->cfg.k_max + 1;
+      const bool few = attention_keys(ctx, cap, k, 1) <= 128;
+      const int rc = run_planned(ctx, {PLAN_STEP, B, k, attention_nsplit(ctx, cap, B, k, 1), few, ctx->top_n, ctx->local_q, ctx->local_m, ctx->distance_eps, ctx->min_block},
                                  [&]() -> int {
                                    const int ready = ctx->x_ready_k;
                                    const int64_t steps = ctx->steps;

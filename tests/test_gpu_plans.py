@@ -1,0 +1,37 @@
+"""Steps of a bpd_decode that are recorded once and replayed: every setting that a step depends on has a recording of its own."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from harness import gpu_context
+
+pytestmark = pytest.mark.gpu
+
+
+def test_settings_do_not_share_recorded_steps():
+    """(distance_eps, min_block, top_n, query block, memory): each after one that a narrower key took for the same."""
+    cfg = wl.Config("plans", 81, 1, 2, 128, 2, 512, 272, 4, 1, 9, 80, "bf16", -1)
+    weights = wl.make_weights(cfg, std=0.12)                # tokens that depend on what is seen and accepted
+    ctx, ref = gpu_context(cfg, weights), gpu_context(cfg, weights)
+    src, n = wl.make_sources(cfg)
+    settings = [(4096 * 8, 1, 1, 0, 0), (0, 1, 1, 8, 0), (4096 * 8, 1, 1, 8, 0), (0, 1, 1, 16, 0), (0, 1, 1, 8, 1), (0, 3, 1, 8, 0), (0, 1, 3, 8, 0), (0, 1, 1, 0, 0)]
+    seen = {}
+    for rep in range(2):
+        for eps, least, top, q, mem in settings:
+            for c in (ctx, ref):
+                c.bpd_set_acceptance(eps, least)
+                c.bpd_set_top_n(top)
+                c.bpd_set_local_attention(q, mem)
+                c.bpd_encode(src, n)
+            ids, lens, st = ctx.bpd_decode(cfg.k)
+            steps = 0
+            while not ref.bpd_get_state()[3].all():
+                ref.bpd_step(cfg.k)
+                steps += 1
+            what = f"eps {eps} min {least} top {top} local {q}, {mem}"
+            assert st.steps == steps, what
+            for a, b in zip([ids, lens, *ctx.bpd_get_state()], [*ref.bpd_get_output(), *ref.bpd_get_state()]):
+                np.testing.assert_array_equal(a, b, err_msg=what)
+            seen[what] = (ids.tobytes(), steps)
+    first, second = list(seen.values())[:2]
+    assert first != second and len(set(seen.values())) >= 4  # (otherwise nothing would show)
