@@ -35,7 +35,7 @@ struct WEntry {
 };
 
 // A sequence of launches that depends on nothing but `key`: one word for each setting (packed into one word, settings of any size collide)
-typedef std::array<long, 10> PlanKey;
+typedef std::array<long, 9> PlanKey;
 struct Plan { PlanKey key; int seen; bool failed; hipGraphExec_t exec; unsigned long long used; };
 
 }  // namespace
@@ -78,7 +78,8 @@ struct bpd_ctx {
   unsigned long long fetch_tag = 0, encode_tag = 0;
   unsigned report_tag = 0;
   std::vector<int> remaining;                  // tokens still to come per sequence as far as the host knows (-1: it does not)
-  std::vector<Plan> plans;                     // launches seen before, as graphs (run_planned)
+  std::vector<Plan> plans[2];                  // launches seen before, as graphs (run_planned): encodes, steps
+  std::vector<hipGraphExec_t> retired;         // ... given up, but perhaps still running (release_retired)
   hipStream_t plan_stream = nullptr;           // where they are recorded
   int prof_phase = 0;
   std::vector<hipEvent_t> prof_ev;
@@ -1215,14 +1216,30 @@ bool is_host_ptr_cached(bpd_ctx* ctx, const void* p) {
   return h;
 }
 
-// Launches of one kind (a decode's step, an encode) that come again and again with the same arguments: from the second time on
-// they are recorded and replayed as a graph.  A launch costs the host 3 us (its arguments go to device memory), which is
-// what a sentence's encode took (90 launches: 0.6 ms, the GPU 0.3) and most of what a step of the base model took (43).  `enqueue`
-// launches on ctx->stream and may only depend on the key.  Graphs are kept for the last PLANS_MAX keys (source lengths, mostly).
+// Graphs given up by run_planned are destroyed once the stream has been waited for past their last launch (run_planned waits for it
+// itself when PLANS_MAX of them have come together: encodes that nobody waits for).
+void release_retired(bpd_ctx* ctx) {
+  for (auto g : ctx->retired) (void)hipGraphExecDestroy(g);
+  ctx->retired.clear();
+}
+
+// Launches of one kind (an encode, a decode's step) that come again and again with the same arguments are recorded and replayed as
+// a graph, since a launch costs the host 3 us: a step of the base model has 43, an encode some 90.  `enqueue` launches on
+// ctx->stream and may only depend on the key.  Of each kind the last PLANS_MAX keys are kept, and a key is recorded when it comes
+// for the PLAN_SIGHTS'th time while it is among them.  Recording costs 0.2 .. 0.6 ms.
+//   Steps (keys: batch sizes and cache lengths) at the second sight.  Without: base model, one sentence 4.09 instead of 3.83 ms, big
+//   model, greedy 8.11 instead of 7.13, eight images 102.4 instead of 96.5.
+//   Encodes (keys: batch sizes and source lengths) at the eighth.  The GPU is no sooner done with a recorded one (base model, one
+//   sentence of 64 tokens: 282 us launch by launch, 289), but the host is (50 instead of 220 us), which steps that go out launch by launch then
+//   have as a lead (five sentences in steps of the big model 5.58 instead of 5.93 ms, thirteen of the base model 3.62 instead of
+//   3.87).  At the second sight source lengths as they come cost more than that: 100 lengths in turn are recorded, given up and
+//   recorded again (base model 318 -> 368 us per sentence, big 448 -> 521); eight sights among the last 24 keys are what lengths
+//   that do recur have.
 constexpr size_t PLANS_MAX = 24;
 enum { PLAN_ENCODE, PLAN_STEP };
+constexpr int PLAN_SIGHTS[2] = {8, 2};
 template <class F>
-int run_planned(bpd_ctx* ctx, const PlanKey& key, F enqueue) {
+int run_planned(bpd_ctx* ctx, int kind, const PlanKey& key, F enqueue) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   // (not while phases are timed, nor inside a graph of the caller's, nor with the decoder stack kernel, whose flags count its launches)
   if (ctx->prof_phase != 0 || (ctx->stack_workers > 0 && !ctx->stack_off) || hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
@@ -1230,24 +1247,26 @@ int run_planned(bpd_ctx* ctx, const PlanKey& key, F enqueue) {
     return enqueue();
   }
   static std::atomic<unsigned long long> clock{0};
+  auto& plans = ctx->plans[kind];
   Plan* p = nullptr;
-  for (auto& q : ctx->plans)
+  for (auto& q : plans)
     if (q.key == key) { p = &q; break; }
   if (!p) {
-    if (ctx->plans.size() >= PLANS_MAX) {        // the one not used for longest goes
-      auto old = std::min_element(ctx->plans.begin(), ctx->plans.end(), [](const Plan& a, const Plan& b) { return a.used < b.used; });
-      if (old->exec) (void)hipGraphExecDestroy(old->exec);
-      ctx->plans.erase(old);
+    if (plans.size() >= PLANS_MAX) {             // the one not used for longest goes
+      auto old = std::min_element(plans.begin(), plans.end(), [](const Plan& a, const Plan& b) { return a.used < b.used; });
+      if (old->exec) ctx->retired.push_back(old->exec);
+      plans.erase(old);
+      if (ctx->retired.size() >= PLANS_MAX) { HIPCHK(hipStreamSynchronize(ctx->stream)); release_retired(ctx); }
     }
-    ctx->plans.push_back(Plan{key, 0, false, nullptr, 0});
-    p = &ctx->plans.back();
+    plans.push_back(Plan{key, 0, false, nullptr, 0});
+    p = &plans.back();
   }
   p->used = ++clock;
   if (p->exec) {
     HIPCHK(hipGraphLaunch(p->exec, ctx->stream));
     return BPD_OK;
   }
-  if (p->failed || ++p->seen < 2) return enqueue();
+  if (p->failed || ++p->seen < PLAN_SIGHTS[kind]) return enqueue();
   if (!ctx->plan_stream && hipStreamCreateWithFlags(&ctx->plan_stream, hipStreamNonBlocking) != hipSuccess) ctx->plan_stream = nullptr;
   hipGraph_t graph = nullptr;
   bool ok = ctx->plan_stream && hipStreamBeginCapture(ctx->plan_stream, hipStreamCaptureModeThreadLocal) == hipSuccess;
@@ -1305,6 +1324,7 @@ int fetch(bpd_ctx* ctx, std::initializer_list<Fetch> list) {
     LAUNCHCHK();
     const int rc = wait_word(ctx, &ctx->done[0], f.tag);
     if (rc) return rc;
+    release_retired(ctx);
     const int* from = ctx->stage_out;
     for (const Fetch& a : list)
       if (a.dst && a.n) { memcpy(a.dst, from, a.n * 4); from += a.n; }
@@ -1313,6 +1333,7 @@ int fetch(bpd_ctx* ctx, std::initializer_list<Fetch> list) {
   for (const Fetch& a : list)
     if (a.dst && a.n) HIPCHK(hipMemcpyAsync(a.dst, a.src, a.n * 4, hipMemcpyDefault, ctx->stream));
   HIPCHK(hipStreamSynchronize(ctx->stream));
+  release_retired(ctx);
   return BPD_OK;
 }
 
@@ -1426,8 +1447,10 @@ int bpd_destroy(bpd_ctx* ctx) {
         if (FILE* f = fopen(path, "wb")) { fwrite(t.data(), 8, n, f); fclose(f); }
     }
   }
-  for (auto& q : ctx->plans)
-    if (q.exec) (void)hipGraphExecDestroy(q.exec);
+  release_retired(ctx);
+  for (auto& kind : ctx->plans)
+    for (auto& q : kind)
+      if (q.exec) (void)hipGraphExecDestroy(q.exec);
   if (ctx->plan_stream) (void)hipStreamDestroy(ctx->plan_stream);
   for (auto e : ctx->prof_ev) (void)hipEventDestroy(e);
   if (ctx->report) (void)hipHostFree(ctx->report);
@@ -1557,7 +1580,7 @@ int bpd_encode(bpd_ctx* ctx, const int32_t* src_ids, const int32_t* src_len, con
     small_encode(ctx);
   } else {
     ctx->steps = 0;
-    const int rc = run_planned(ctx, {PLAN_ENCODE, B, S, ctx->local_q, ctx->local_m}, [&]() -> int {
+    const int rc = run_planned(ctx, PLAN_ENCODE, {B, S, ctx->local_q, ctx->local_m}, [&]() -> int {
       int rc = encoder(ctx);
       if (rc) return rc;
       // first invocation: position 0 only, all heads -> first proposals
@@ -1858,7 +1881,7 @@ int bpd_decode(bpd_ctx* ctx, int k, const int32_t* schedule, int max_steps, int3
       use_slots(ctx, B);
       const int cap = ctx->cfg.max_out_len + ctx->cfg.k_max + 1;
       const bool few = attention_keys(ctx, cap, k, 1) <= 128;
-      const int rc = run_planned(ctx, {PLAN_STEP, B, k, attention_nsplit(ctx, cap, B, k, 1), few, ctx->top_n, ctx->local_q, ctx->local_m, ctx->distance_eps, ctx->min_block},
+      const int rc = run_planned(ctx, PLAN_STEP, {B, k, attention_nsplit(ctx, cap, B, k, 1), few, ctx->top_n, ctx->local_q, ctx->local_m, ctx->distance_eps, ctx->min_block},
                                  [&]() -> int {
                                    const int ready = ctx->x_ready_k;
                                    const int64_t steps = ctx->steps;
