@@ -72,10 +72,10 @@ struct bpd_ctx {
   // bpd_encode / a host schedule, and results on their way to the caller
   unsigned long long* report = nullptr;       // [2][max_batch] bpd_decode: tokens still to come, tagged with the step; steps
                                               // take turns (the next one may report before the host has looked)
-  unsigned long long* done = nullptr;         // [0]: last finished fetch, [1]: last encode whose arguments have been read
+  unsigned long long* done = nullptr;         // [0]: last finished fetch, [1]: last encode whose staged arguments have been read
   int *stage_in = nullptr, *stage_sched = nullptr, *stage_out = nullptr;
   size_t n_stage_out = 0;
-  unsigned long long fetch_tag = 0, encode_tag = 0;
+  unsigned long long fetch_tag = 0, encode_tag = 0;        // encode_tag: of the last encode whose arguments were staged
   unsigned report_tag = 0;
   std::vector<int> remaining;                  // tokens still to come per sequence as far as the host knows (-1: it does not)
   std::vector<Plan> plans[2];                  // launches seen before, as graphs (run_planned): encodes, steps
@@ -814,8 +814,8 @@ int heads_two_phase(bpd_ctx* ctx, int k) {
   return BPD_OK;
 }
 
-// The folded copies of the decoder's LayerNorm + GEMM pairs follow the loaded weights: bpd_load_weights marks them stale
-// (and asks for a new bpd_encode, which calls this).
+// The folded copies of the decoder's LayerNorm + GEMM pairs follow the loaded weights: bpd_load_weights marks them stale, and
+// once every tensor is there calls this.
 void refresh_folded_weights(bpd_ctx* ctx) {
   Layout& L = ctx->lay;
   if (ctx->fold_ready || !L.dec[0].f_qkv.W) return;
@@ -1216,6 +1216,13 @@ bool is_host_ptr_cached(bpd_ctx* ctx, const void* p) {
   return h;
 }
 
+// Is the caller recording the context's stream into a graph of its own?
+bool capturing(const bpd_ctx* ctx) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) { (void)hipGetLastError(); return false; }
+  return cap != hipStreamCaptureStatusNone;
+}
+
 // Graphs given up by run_planned are destroyed once the stream has been waited for past their last launch (run_planned waits for it
 // itself when PLANS_MAX of them have come together: encodes that nobody waits for).
 void release_retired(bpd_ctx* ctx) {
@@ -1240,12 +1247,8 @@ enum { PLAN_ENCODE, PLAN_STEP };
 constexpr int PLAN_SIGHTS[2] = {8, 2};
 template <class F>
 int run_planned(bpd_ctx* ctx, int kind, const PlanKey& key, F enqueue) {
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   // (not while phases are timed, nor inside a graph of the caller's, nor with the decoder stack kernel, whose flags count its launches)
-  if (ctx->prof_phase != 0 || (ctx->stack_workers > 0 && !ctx->stack_off) || hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return enqueue();
-  }
+  if (ctx->prof_phase != 0 || (ctx->stack_workers > 0 && !ctx->stack_off) || capturing(ctx)) return enqueue();
   static std::atomic<unsigned long long> clock{0};
   auto& plans = ctx->plans[kind];
   Plan* p = nullptr;
@@ -1290,9 +1293,10 @@ int run_planned(bpd_ctx* ctx, int kind, const PlanKey& key, F enqueue) {
 
 unsigned long long* report_of(bpd_ctx* ctx, unsigned tag) { return ctx->report + (size_t)(tag & 1) * ctx->cfg.max_batch; }
 
-// Waits until a kernel of the context's stream has stored `tag` in a word of pinned memory (shifted up by `shift`).  Ends also when the stream has nothing left to run: then the word is there, or the launch failed.
-int wait_word(bpd_ctx* ctx, const unsigned long long* word, unsigned long long tag, int shift = 0) {
-  auto there = [&] { return (__atomic_load_n(word, __ATOMIC_ACQUIRE) >> shift) == tag; };
+// Waits (on the CPU, which polls) until a kernel of the context's stream has stored what `there` looks for in pinned memory.
+// Ends also when the stream has nothing left to run: then it is there, or the launch failed.
+template <class There>
+int wait_until(bpd_ctx* ctx, There there) {
   for (unsigned spin = 1; !there(); ++spin) {
     __builtin_ia32_pause();
     if (spin % 8192) continue;
@@ -1302,6 +1306,13 @@ int wait_word(bpd_ctx* ctx, const unsigned long long* word, unsigned long long t
     if (!there()) return fail(ctx, BPD_E_HIP, "waiting for the stream: it ended without the awaited result");
   }
   return BPD_OK;
+}
+// ... a counter that only grows, or the report of a step (its tag in the upper half)
+int wait_done(bpd_ctx* ctx, const unsigned long long* word, unsigned long long tag) {
+  return wait_until(ctx, [&] { return __atomic_load_n(word, __ATOMIC_ACQUIRE) >= tag; });
+}
+int wait_report(bpd_ctx* ctx, const unsigned long long* word, unsigned tag) {
+  return wait_until(ctx, [&] { return __atomic_load_n(word, __ATOMIC_ACQUIRE) >> 32 == tag; });
 }
 
 // Copies up to four arrays of ints to the caller (host or device memory; null: not wanted) and waits for them.
@@ -1322,7 +1333,7 @@ int fetch(bpd_ctx* ctx, std::initializer_list<Fetch> list) {
     f.dst = ctx->stage_out; f.done = &ctx->done[0]; f.tag = ++ctx->fetch_tag;
     hipLaunchKernelGGL(fetch_kernel, dim3(1), dim3(1024), 0, ctx->stream, f);
     LAUNCHCHK();
-    const int rc = wait_word(ctx, &ctx->done[0], f.tag);
+    const int rc = wait_done(ctx, &ctx->done[0], f.tag);
     if (rc) return rc;
     release_retired(ctx);
     const int* from = ctx->stage_out;
@@ -1533,6 +1544,9 @@ int bpd_load_weights(bpd_ctx* ctx, const bpd_tensor* tensors, int n) {
     ctx->fold_ready = false;
   }
   ctx->encoded = false;
+  bool all = true;
+  for (auto& kv : ctx->table) all = all && kv.second.loaded;
+  if (all) { refresh_folded_weights(ctx); LAUNCHCHK(); }      // (here and not in bpd_encode: a captured one would fold at its replays only)
   return BPD_OK;
 }
 
@@ -1543,8 +1557,9 @@ int bpd_encode(bpd_ctx* ctx, const int32_t* src_ids, const int32_t* src_len, con
   if (B > c.max_batch || S > c.max_src_len) return fail(ctx, BPD_E_CAPACITY, "bpd_encode: batch or source length over the configured maximum");
   for (auto& kv : ctx->table)
     if (!kv.second.loaded) return fail(ctx, BPD_E_STATE, "bpd_encode: tensor not loaded: " + kv.first);
-  // host arrays are validated here and pass through the pinned staging area (free again once the encode before this one
-  // has read its own); the kernel that takes them clamps, so device arrays are safe as well
+  // Host arrays are validated here and pass through the pinned staging area (free again once the last encode that used it has
+  // read its own); the kernel that takes them clamps, so device arrays are safe as well.  In a graph of the caller's the area
+  // would be read at every replay, whatever lies there by then: host arrays are copied from where they are instead.
   int *h_ids = ctx->stage_in, *h_len = h_ids + (size_t)c.max_batch * c.max_src_len, *h_max = h_len + c.max_batch;
   const bool host_ids = is_host_ptr(src_ids), host_len = is_host_ptr(src_len), host_max = max_len && is_host_ptr(max_len);
   if (host_len) {
@@ -1561,19 +1576,28 @@ int bpd_encode(bpd_ctx* ctx, const int32_t* src_ids, const int32_t* src_len, con
   }
   Layout& L = ctx->lay;
   ctx->B = B; ctx->S = S; ctx->encoded = false; ctx->x_ready_k = 0;
-  refresh_folded_weights(ctx);                    // (every tensor is loaded: checked above)
-  { const int rc = wait_word(ctx, &ctx->done[1], ctx->encode_tag); if (rc) return rc; }
-  if (host_ids) memcpy(h_ids, src_ids, (size_t)B * S * 4);
-  if (host_len) memcpy(h_len, src_len, (size_t)B * 4);
-  if (host_max) memcpy(h_max, max_len, (size_t)B * 4);
+  refresh_folded_weights(ctx);                    // (every tensor is loaded: checked above; nothing to do unless bpd_load_weights failed halfway)
+  const int *from_ids = src_ids, *from_len = src_len, *from_max = max_len;
+  const bool host = host_ids || host_len || host_max, staged = host && !capturing(ctx);
+  if (staged) {
+    const int rc = wait_done(ctx, &ctx->done[1], ctx->encode_tag);
+    if (rc) return rc;
+    if (host_ids) { memcpy(h_ids, src_ids, (size_t)B * S * 4); from_ids = h_ids; }
+    if (host_len) { memcpy(h_len, src_len, (size_t)B * 4); from_len = h_len; }
+    if (host_max) { memcpy(h_max, max_len, (size_t)B * 4); from_max = h_max; }
+  } else if (host) {
+    if (host_ids) { HIPCHK(hipMemcpyAsync(L.src_ids, src_ids, (size_t)B * S * 4, hipMemcpyHostToDevice, ctx->stream)); from_ids = L.src_ids; }
+    if (host_len) { HIPCHK(hipMemcpyAsync(L.src_len, src_len, (size_t)B * 4, hipMemcpyHostToDevice, ctx->stream)); from_len = L.src_len; }
+    if (host_max) { HIPCHK(hipMemcpyAsync(L.max_len, max_len, (size_t)B * 4, hipMemcpyHostToDevice, ctx->stream)); from_max = L.max_len; }
+  }
   for (int b = 0; b < B; ++b) ctx->remaining[b] = !max_len ? c.max_out_len : (host_max ? max_len[b] : -1);
   {
     const size_t most = std::max((size_t)B * S, (size_t)B * std::max(c.max_out_len, c.k_max * c.k_max));
     hipLaunchKernelGGL(encode_init_kernel, dim3((unsigned)std::min<size_t>(256, (most + 255) / 256)), dim3(256), 0, ctx->stream, state_params(ctx),
-                       host_ids ? h_ids : src_ids, host_len ? h_len : src_len, host_max ? h_max : max_len, L.src_ids, L.src_len, B, S, c.vocab, c.pad_id,
-                       (unsigned*)L.step_counter, &ctx->done[1], ctx->encode_tag + 1);
+                       from_ids, from_len, from_max, L.src_ids, L.src_len, B, S, c.vocab, c.pad_id,
+                       (unsigned*)L.step_counter, staged ? &ctx->done[1] : nullptr, ctx->encode_tag + 1);
     LAUNCHCHK();
-    ++ctx->encode_tag;
+    if (staged) ++ctx->encode_tag;
   }
   use_slots(ctx, B);
   if (small_encode_ok(ctx)) {
@@ -1854,7 +1878,7 @@ int bpd_decode(bpd_ctx* ctx, int k, const int32_t* schedule, int max_steps, int3
     const unsigned long long* words = report_of(ctx, tag);
     going = 0;
     for (int b = 0; b < B; ++b) {
-      const int rc = wait_word(ctx, &words[b], tag, 32);
+      const int rc = wait_report(ctx, &words[b], tag);
       if (rc) return rc;
       rem[b] = (int)(unsigned)words[b];
       going += rem[b] > 0;

@@ -998,8 +998,9 @@ __global__ void fill_i32_kernel(int* p, long n, int v) {
 
 // Start of bpd_encode, one launch for what took twelve (three copies out of pageable memory, a sanitising kernel, eight
 // fills: 60 us of a 0.7 ms encode at batch 1): takes the call's arrays (device memory, or the library's pinned staging
-// area, which the kernel reads directly) and empties the decode state.  `taken` (host memory) is set to `tag` by the last
-// workgroup: the staging area may be written again.  counter: a zero in device memory, zero again afterwards.
+// area, which the kernel reads directly, or the state's own arrays) and empties the decode state.  `taken` (host memory; null:
+// nothing was staged) is set to `tag` by the last workgroup: the staging area may be written again.  counter: a zero in device
+// memory, zero again afterwards.
 __global__ __launch_bounds__(256) void encode_init_kernel(StateP s, const int* src_ids, const int* src_len, const int* max_len, int* d_ids, int* d_len,
                                                           int B, int S, int V, int pad, unsigned* counter, unsigned long long* taken,
                                                           unsigned long long tag) {
@@ -1013,10 +1014,12 @@ __global__ __launch_bounds__(256) void encode_init_kernel(StateP s, const int* s
     s.steps_done[q] = 0; s.fin_step[q] = 0x7FFFFFFF; s.slot_seq[q] = q; s.slot_L[q] = 1; s.slot_src[q] = d_len[q]; s.slot_row[q] = q * s.cache_rows + 1;
   }
   if (i == 0) *s.n_live = B;
-  __syncthreads();                               // (every argument this workgroup reads has arrived: it has been stored)
-  if (threadIdx.x == 0 && atomicAdd(counter, 1u) == gridDim.x - 1) {
-    *counter = 0;
-    __hip_atomic_store(taken, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (taken) {
+    __syncthreads();                             // (every argument this workgroup reads has arrived: it has been stored)
+    if (threadIdx.x == 0 && atomicAdd(counter, 1u) == gridDim.x - 1) {
+      *counter = 0;
+      __hip_atomic_store(taken, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
   }
   for (int q = i; q < B * s.max_out; q += n) s.out_ids[q] = pad;
   for (int q = i; q < 32; q += n) s.stats[q] = 0;

@@ -75,3 +75,45 @@ def test_step_captured_after_a_sequence_has_ended(d, F, k, B, two_phase):
             ref.bpd_step(k, two)
             cap.bpd_step_static(k, two)
     assert ref.bpd_get_state()[3].all()
+
+
+@pytest.mark.parametrize("dtype,d,F,host", [("bf16", 128, 512, False), ("bf16", 192, 384, False), ("bf16", 128, 512, True), ("f32", 64, 256, False), ("f32", 64, 1024, True)])
+def test_captured_encode(dtype, d, F, host):
+    """A captured encode takes what its arrays hold at each replay, and direct encodes go on before the first replay and
+    between replays."""
+    cfg = wl.Config("captured", 84, 1, 2, d, d // (64 if dtype == "bf16" else 16), F, 272, 4, 3, 20, 12, dtype, 2)
+    weights = wl.make_weights(cfg, std=0.1)
+    stream = torch.cuda.Stream()
+    ref, cap = context(cfg, weights), context(cfg, weights, stream)
+    rng = np.random.default_rng(d)
+    arrays = [np.zeros((3, 20), np.int32), np.ones(3, np.int32), np.ones(3, np.int32)]
+    if not host:
+        arrays = [torch.from_numpy(a).cuda() for a in arrays]
+
+    def fill():
+        n = rng.integers(1, 21, 3).astype(np.int32)
+        new = [rng.integers(3, cfg.vocab, (3, 20)).astype(np.int32), n, rng.integers(1, 13, 3).astype(np.int32)]
+        for a, v in zip(arrays, new):
+            if host:
+                a[...] = v
+            else:
+                a.copy_(torch.from_numpy(v))
+        torch.cuda.synchronize()
+        return new
+
+    fill()
+    g = capture(stream, lambda: cap.bpd_encode(*arrays))
+    for s in range(6):
+        new = fill()
+        if s in (0, 1, 3):                                 # direct encodes of other sources, from host memory
+            other = [np.roll(new[0], 1, 0), np.roll(new[1], 1), np.roll(new[2], 1)]
+            for c in (ref, cap):
+                c.bpd_encode(*other)
+            same(snapshot(ref), snapshot(cap), f"direct encode before replay {s}")
+        ref.bpd_encode(*new)
+        replay(g, stream)
+        same(snapshot(ref), snapshot(cap), f"replay {s}")
+        for t in range(2):
+            ref.bpd_step(3)
+            cap.bpd_step_static(3)                         # (its scratch is one array per GPU: not both contexts at a time)
+            same(snapshot(ref), snapshot(cap), f"step {t} after replay {s}")
