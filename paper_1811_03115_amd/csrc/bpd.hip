@@ -77,6 +77,7 @@ struct bpd_ctx {
   size_t n_stage_out = 0;
   unsigned long long fetch_tag = 0, encode_tag = 0;        // encode_tag: of the last encode whose arguments were staged
   unsigned report_tag = 0;
+  bool replayable = false;                     // a call has been captured by the caller: forget_replayed()
   std::vector<int> remaining;                  // tokens still to come per sequence as far as the host knows (-1: it does not)
   std::vector<Plan> plans[2];                  // launches seen before, as graphs (run_planned): encodes, steps
   std::vector<hipGraphExec_t> retired;         // ... given up, but perhaps still running (release_retired)
@@ -694,7 +695,7 @@ int stack_lds_bytes(const bpd_ctx* ctx, int B, int R) { return stack_lds_need(st
 bool stack_usable(const bpd_ctx* ctx, int B, int R) {
   const bpd_config& c = ctx->cfg;
   const int M = B * R;
-  return ctx->stack_workers > 0 && !ctx->stack_off && ctx->lay.stack_ex != nullptr && M >= 1 && M <= 16 && ctx->local_q == 0 && ctx->seq == nullptr &&
+  return ctx->stack_workers > 0 && !ctx->stack_off && !ctx->replayable && ctx->lay.stack_ex != nullptr && M >= 1 && M <= 16 && ctx->local_q == 0 && ctx->seq == nullptr &&
          attention_nsplit(ctx, c.max_out_len + c.k_max + 1, B, R, 1) == 1 && attention_nsplit(ctx, c.max_src_len, B, R, 0) == 1 &&
          stack_lds_bytes(ctx, B, R) <= 160 * 1024 &&
          (std::max(3 * c.d_model, c.d_ff) / 16 + ctx->stack_workers - 1) / ctx->stack_workers <= 8;     // tiles a helper wave finishes: two
@@ -1223,6 +1224,19 @@ bool capturing(const bpd_ctx* ctx) {
   return cap != hipStreamCaptureStatusNone;
 }
 
+// Start of every call that reads or changes the decode: once a call has been captured, its replays may have encoded or stepped
+// unseen since the last call, so nothing is left of what the host knew of the decode: tokens to come, sequences in use, the block
+// embedded ahead of time, the bound on the cache lengths.  (The decoder stack kernel counts its launches on the host: not used.)
+void forget_replayed(bpd_ctx* ctx) {
+  if (!ctx->replayable) ctx->replayable = capturing(ctx);
+  if (!ctx->replayable) return;
+  std::fill(ctx->remaining.begin(), ctx->remaining.end(), -1);
+  ctx->live1 = ctx->live2 = -1;
+  ctx->budget_min = 0;
+  ctx->x_ready_k = 0;
+  ctx->steps = std::max<int64_t>(ctx->steps, ctx->cfg.max_out_len);
+}
+
 // Graphs given up by run_planned are destroyed once the stream has been waited for past their last launch (run_planned waits for it
 // itself when PLANS_MAX of them have come together: encodes that nobody waits for).
 void release_retired(bpd_ctx* ctx) {
@@ -1575,6 +1589,7 @@ int bpd_encode(bpd_ctx* ctx, const int32_t* src_ids, const int32_t* src_len, con
       if (max_len[b] < 1 || max_len[b] > c.max_out_len) return fail(ctx, BPD_E_ARG, "bpd_encode: max_len out of range");
   }
   Layout& L = ctx->lay;
+  forget_replayed(ctx);
   ctx->B = B; ctx->S = S; ctx->encoded = false; ctx->x_ready_k = 0;
   refresh_folded_weights(ctx);                    // (every tensor is loaded: checked above; nothing to do unless bpd_load_weights failed halfway)
   const int *from_ids = src_ids, *from_len = src_len, *from_max = max_len;
@@ -1682,6 +1697,7 @@ int bpd_step(bpd_ctx* ctx, int k, const int32_t* imposed_accept, int32_t* accept
   if (!ctx->encoded) return fail(ctx, BPD_E_STATE, "bpd_step: call bpd_encode first");
   if (k < 1 || k > ctx->cfg.k_max) return fail(ctx, BPD_E_ARG, "bpd_step: k outside 1..k_max");
   Layout& L = ctx->lay;
+  forget_replayed(ctx);
   // device pointers are used in place by the accept kernel; host arrays go through a copy
   const int* imp = nullptr;
   if (imposed_accept) {
@@ -1705,6 +1721,7 @@ int bpd_step_static(bpd_ctx* ctx, int k, const int32_t* imposed_accept, int32_t*
   if (k < 1 || k > ctx->cfg.k_max) return fail(ctx, BPD_E_ARG, "bpd_step_static: k outside 1..k_max");
   Layout& L = ctx->lay;
   const bpd_config& c = ctx->cfg;
+  forget_replayed(ctx);
   char* sp = (char*)g_scratch_ptr[ctx->device];
   if (!sp) return fail(ctx, BPD_E_STATE, "bpd_step_static: no scratch address for this device");
   // what this step needs: its k x k keys per sequence, the head-1 / second-phase keys, the attention partials, and as
@@ -1830,6 +1847,7 @@ int bpd_decode(bpd_ctx* ctx, int k, const int32_t* schedule, int max_steps, int3
   if (!ctx) return BPD_E_ARG;
   if (!ctx->encoded) return fail(ctx, BPD_E_STATE, "bpd_decode: call bpd_encode first");
   if (k < 1 || k > ctx->cfg.k_max || max_steps < 0) return fail(ctx, BPD_E_ARG, "bpd_decode: bad k or max_steps");
+  forget_replayed(ctx);
   Layout& L = ctx->lay;
   const int B = ctx->B;
   const int* imp = nullptr;
@@ -1967,6 +1985,7 @@ int bpd_debug_step_logits(bpd_ctx* ctx, int k, float* logits) {
   if (!ctx || !logits) return fail(ctx, BPD_E_ARG, "bpd_debug_step_logits: null argument");
   if (!ctx->encoded) return fail(ctx, BPD_E_STATE, "bpd_debug_step_logits: call bpd_encode first");
   if (k < 1 || k > ctx->cfg.k_max) return fail(ctx, BPD_E_ARG, "bpd_debug_step_logits: k outside 1..k_max");
+  forget_replayed(ctx);
   use_slots(ctx, ctx->B);                         // every sequence, ended or not
   if (const int hgroup = ctx->prof_phase == 0 ? small_hgroup(ctx, k) : 0) {
     small_decode(ctx, k, hgroup, 1, nullptr, 0, nullptr, logits);

@@ -117,3 +117,56 @@ def test_captured_encode(dtype, d, F, host):
             ref.bpd_step(3)
             cap.bpd_step_static(3)                         # (its scratch is one array per GPU: not both contexts at a time)
             same(snapshot(ref), snapshot(cap), f"step {t} after replay {s}")
+
+
+@pytest.mark.parametrize("dtype,d,F,eos,B", [("bf16", 128, 512, 2, 1), ("bf16", 128, 512, -1, 3), ("bf16", 192, 384, 2, 6), ("f32", 64, 256, 2, 2)])
+def test_direct_calls_between_replays(dtype, d, F, eos, B):
+    """Decodes and steps that are called directly find what replays have left, not what the host last knew: tokens to come, the
+    sequences still in use, a block embedded ahead of time."""
+    cfg = wl.Config("captured", 85, 1, 2, d, d // (64 if dtype == "bf16" else 16), F, 272, 4, B, 9, 24, dtype, eos)
+    weights = wl.make_weights(cfg, std=0.1)
+    stream = torch.cuda.Stream()
+    ref, cap = context(cfg, weights), context(cfg, weights, stream)
+    rng = np.random.default_rng(d + B)
+    src = torch.zeros((B, 9), dtype=torch.int32, device="cuda")
+    n = torch.full((B,), 9, dtype=torch.int32, device="cuda")
+    budget = torch.from_numpy(rng.integers(9, 25, B).astype(np.int32)).cuda()
+    two = torch.full((B,), 2, dtype=torch.int32, device="cuda")
+
+    def fill():
+        src.copy_(torch.from_numpy(rng.integers(3, cfg.vocab, (B, 9)).astype(np.int32)))
+        torch.cuda.synchronize()
+
+    fill()
+    encode = capture(stream, lambda: cap.bpd_encode(src, n, budget))
+    replay(encode, stream)
+    step = capture(stream, lambda: cap.bpd_step(3, two))
+
+    def decode(c, sched=None):
+        ids, lens, st = c.bpd_decode(3, sched)
+        return [ids, lens, np.array([st.steps, st.accepted_total, st.finished])]
+
+    for rep in range(4):
+        for c in (ref, cap):                               # a whole decode: the host knows that all sequences have ended
+            c.bpd_encode(src, n, budget)
+        same(decode(ref), decode(cap), "direct")
+        fill()
+        ref.bpd_encode(src, n, budget)
+        replay(encode, stream)
+        for s in range(rep):                               # replayed and direct steps in turn
+            ref.bpd_step(3, two)
+            if s % 2:
+                cap.bpd_step(3, two)
+            else:
+                replay(step, stream)
+            same(snapshot(ref), snapshot(cap), f"step {s}, time {rep}")
+        P = ref.bpd_get_state()[0]
+        if rep % 2:                                        # other proposals, then a replayed step
+            P = ((P + 7) % cfg.vocab).astype(np.int32)
+            for c in (ref, cap):
+                c.bpd_set_proposals(P)
+            ref.bpd_step(3, two)
+            replay(step, stream)
+            same(snapshot(ref), snapshot(cap), f"after new proposals, time {rep}")
+        same(decode(ref), decode(cap), f"after replays, time {rep}")
+        same(snapshot(ref), snapshot(cap), f"after replays, time {rep}")
