@@ -169,17 +169,25 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
     __builtin_amdgcn_sched_barrier(0);
     float* gw = sm.gb_s + wave * (U * 64);
     if (lane < U * 16) *(f32x4*)(gw + lane * 4) = gbv;
+    float mw;                                    // mean of the wave's own columns; the registers then hold the distances to it
     {
-      float s = 0.f, q = 0.f;
+      f32x4 s4 = f32x4{0.f, 0.f, 0.f, 0.f}, q4 = s4;
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) s4 += __builtin_bit_cast(f32x4, xv[i][hh]);
+      const float s = sum_rows((s4[0] + s4[1]) + (s4[2] + s4[3]));
+      mw = s * (1.f / (32 * U));
 #pragma unroll
       for (int i = 0; i < U; ++i)
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
-          const f32x4 v = __builtin_bit_cast(f32x4, xv[i][hh]);
+          const f32x4 c = __builtin_bit_cast(f32x4, xv[i][hh]) - mw;
+          xv[i][hh] = __builtin_bit_cast(u32x4, c);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) { s += v[r]; q = fmaf(v[r], v[r], q); }
+          for (int r = 0; r < 4; ++r) q4[r] = fmaf(c[r], c[r], q4[r]);
         }
-      s = sum_rows(s); q = sum_rows(q);
+      const float q = sum_rows((q4[0] + q4[1]) + (q4[2] + q4[3]));
       if (lq == 0) sm.st_s[wave * 16 + lr] = make_float2(s, q);
     }
     __syncthreads();
@@ -187,12 +195,9 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
 #pragma unroll
     for (int j = 0; j < 4; ++j) qa[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     {
-      float s = 0.f, q = 0.f;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) { const float2 v = sm.st_s[w * 16 + lr]; s += v.x; q += v.y; }
       float mu, rs;
-      row_moments(s, q, 1.f / K, qp.eps, mu, rs);
-      const float nmr = -mu * rs;
+      row_moments<KSTEPS / U, 32 * U>(sm.st_s + lr, 16, qp.eps, mu, rs);      // (of the waves that have k-steps)
+      const float off = (mw - mu) * rs;
 #pragma unroll
       for (int i = 0; i < U; ++i) {
         float y[8];
@@ -201,7 +206,7 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
           const f32x4 v = __builtin_bit_cast(f32x4, xv[i][hh]);
           const f32x4 g4 = *(const f32x4*)(gw + i * 32 + lq * 8 + 4 * hh), b4 = *(const f32x4*)(gw + U * 32 + i * 32 + lq * 8 + 4 * hh);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) y[4 * hh + r] = fmaf(fmaf(v[r], rs, nmr), g4[r], b4[r]);
+          for (int r = 0; r < 4; ++r) y[4 * hh + r] = fmaf(fmaf(v[r], rs, off), g4[r], b4[r]);
         }
         u32x4 yb = u32x4{cvt_pk_bf16(y[0], y[1]), cvt_pk_bf16(y[2], y[3]), cvt_pk_bf16(y[4], y[5]), cvt_pk_bf16(y[6], y[7])};
         if (U * NW != KSTEPS && !mine) yb = u32x4{0, 0, 0, 0};

@@ -30,8 +30,8 @@ struct RowGemmP {
 // Y = epilogue(X W) for 16 MT rows x 16 NT columns per workgroup, K = 32 * WAVES * U (PART: of one slice, grid z).  The waves
 // split K (wave w takes k-steps w U .. w U + U - 1), every load of the kernel is issued at its entry, and the waves' partial
 // sums meet in LDS once.
-// LN: X = LayerNorm(x): every wave adds up its columns of the rows, the sums meet in LDS, and the wave normalises in
-// registers the fragments it already holds.  One barrier more than without, and twice the bytes for x: 0.8 us at K = 512,
+// LN: X = LayerNorm(x): every wave takes mean and squared distances of its columns of the rows, these meet in LDS (row_moments), and
+// the wave normalises in registers the fragments it already holds.  One barrier more than without, and twice the bytes for x: 0.8 us at K = 512,
 // 1.2 us at K = 1024, against 1.9 us for a LayerNorm kernel of its own; but every column block repeats it, so that with
 // K = 1024 and more than 32 rows (K = 512: 256) the kernel of its own is the faster one (lean_fuse() in bpd.hip).
 // 8 x 512 x 1536 with LayerNorm: 3.95 -> 2.84 us per kernel of a chain;  10 x 1024 x 3072: 5.6 -> 4.2;  8 x 512 x 512: 3.2 -> 2.1;
@@ -99,19 +99,28 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
     for (int u = 0; u < NT; ++u) acc[t][u] = f32x4{0.f, 0.f, 0.f, 0.f};
   if constexpr (LN) {
     float* gw = gb + wave * (U * 64);            // written and read by this wave alone: no barrier
+    float mw[MT];                                // mean of the wave's own columns
     if (lane < U * 16) *(f32x4*)(gw + lane * 4) = gbv;
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
-      float s = 0.f, q = 0.f;
+      // (sums in four chains; the registers then hold the distances to that mean)
+      f32x4 s4 = f32x4{0.f, 0.f, 0.f, 0.f}, q4 = s4;
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) s4 += __builtin_bit_cast(f32x4, xv[t][i][h]);
+      const float s = sum_rows((s4[0] + s4[1]) + (s4[2] + s4[3]));
+      mw[t] = s * (1.f / (32 * U));
 #pragma unroll
       for (int i = 0; i < U; ++i)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const f32x4 v = __builtin_bit_cast(f32x4, xv[t][i][h]);
+          const f32x4 c = __builtin_bit_cast(f32x4, xv[t][i][h]) - mw[t];
+          xv[t][i][h] = __builtin_bit_cast(u32x4, c);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) { s += v[r]; q = fmaf(v[r], v[r], q); }
+          for (int r = 0; r < 4; ++r) q4[r] = fmaf(c[r], c[r], q4[r]);
         }
-      s = sum_rows(s); q = sum_rows(q);
+      const float q = sum_rows((q4[0] + q4[1]) + (q4[2] + q4[3]));
       if (lq == 0) st[(wave * MT + t) * 16 + lr] = make_float2(s, q);
     }
     __syncthreads();
@@ -125,12 +134,9 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
       }
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
-      float s = 0.f, q = 0.f;
-#pragma unroll
-      for (int w = 0; w < WAVES; ++w) { const float2 v = st[(w * MT + t) * 16 + lr]; s += v.x; q += v.y; }
       float mu, rs;
-      row_moments(s, q, 1.f / K, p.eps, mu, rs);
-      const float nmr = -mu * rs;
+      row_moments<WAVES, 32 * U>(st + t * 16 + lr, MT * 16, p.eps, mu, rs);
+      const float off = (mw[t] - mu) * rs;
 #pragma unroll
       for (int i = 0; i < U; ++i) {
         float y[8];
@@ -138,7 +144,7 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
         for (int h = 0; h < 2; ++h) {
           const f32x4 v = __builtin_bit_cast(f32x4, xv[t][i][h]);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) y[4 * h + r] = fmaf(fmaf(v[r], rs, nmr), g4[i][h][r], b4[i][h][r]);
+          for (int r = 0; r < 4; ++r) y[4 * h + r] = fmaf(fmaf(v[r], rs, off), g4[i][h][r], b4[i][h][r]);
         }
         const u32x4 yb = u32x4{cvt_pk_bf16(y[0], y[1]), cvt_pk_bf16(y[2], y[3]), cvt_pk_bf16(y[4], y[5]), cvt_pk_bf16(y[6], y[7])};
 #pragma unroll
@@ -197,7 +203,8 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
 }
 
 // LayerNorm of one row of D columns per workgroup.  NSL > 0: x is the sum of itself, a bias and NSL raw K slices of a split
-// GEMM, in this order of slices, and is stored.  One load of everything, one barrier: 1.9 us in a chain of kernels where one
+// GEMM, in this order of slices, and is stored.  One load of everything, one barrier (each wave takes the squares about the mean of its
+// own columns, row_moments puts the waves together; against sums of squares about zero this costs 0.5 % of a sentence's decode): 1.9 us in a chain of kernels where one
 // wave per row took 4.2 us (D = 512, 80 rows) .. 5.2 us (D = 1024, 8 slices).
 constexpr int ln_row_threads(int D) { return D < 256 ? 64 : D / 4; }
 template <int D, int NSL>
@@ -224,20 +231,19 @@ __global__ __launch_bounds__(ln_row_threads(D)) void ln_row_kernel(float* x, con
     if (in) *(f32x4*)(x + at) = v;
   }
   if (!in) v = f32x4{0.f, 0.f, 0.f, 0.f};
-  float s = (v[0] + v[1]) + (v[2] + v[3]), q = (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
-  s = wave_sum(s); q = wave_sum(q);
+  const float s = wave_sum((v[0] + v[1]) + (v[2] + v[3])), mw = s * ((float)WAVES / D);
+  f32x4 c = v - mw;                              // distances to the mean of the wave's own columns
+  if (!in) c = f32x4{0.f, 0.f, 0.f, 0.f};
+  const float q = wave_sum((c[0] * c[0] + c[1] * c[1]) + (c[2] * c[2] + c[3] * c[3]));
+  float mu = mw, rs, off = 0.f;
   if constexpr (WAVES > 1) {
     if ((tid & 63) == 0) st[tid >> 6] = make_float2(s, q);
     __syncthreads();
-    s = 0.f; q = 0.f;
+    row_moments<WAVES, D / WAVES>(st, 1, eps, mu, rs);
+    off = (mw - mu) * rs;
+  } else rs = inv_sqrt(fmaf(q, 1.f / D, eps));
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) { s += st[w].x; q += st[w].y; }
-  }
-  float mu, rs;
-  row_moments(s, q, 1.f / D, eps, mu, rs);
-  const float nmr = -mu * rs;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) v[r] = fmaf(fmaf(v[r], rs, nmr), gv[r], bv[r]);
+  for (int r = 0; r < 4; ++r) v[r] = fmaf(fmaf(c[r], rs, off), gv[r], bv[r]);
   if (!in) return;
   if (ya) *(u32x2*)(ya + at) = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
   if (yf) *(f32x4*)(yf + at) = v;
