@@ -98,9 +98,10 @@ typedef struct {
 } bpd_stats;
 
 /* Bytes of device workspace bpd_create needs for this configuration (weights in kernel
- * layout -- with max_batch * k_max > 128 in bf16 mode also copies of three decoder matrices
- * per layer with their LayerNorm folded in --, K/V caches, activations, decode state, a
- * staging area for host weights).
+ * layout -- in bf16 mode with max_batch * k_max > 640, or > 128 if d_model is none of 128, 256,
+ * 512, 768, 1024 or d_ff none of 512, 1024, 2048, 3072, 4096, also copies of three decoder
+ * matrices per layer with their LayerNorm folded in --, K/V caches, activations, decode state,
+ * a staging area for host weights).
  * Returns 0 if the configuration is invalid. */
 size_t bpd_workspace_bytes(const bpd_config* cfg);
 

@@ -278,7 +278,6 @@ void use_slots(bpd_ctx* ctx, int exact) {
 LiveP live_rows(const bpd_ctx* ctx, int M) { return ctx->live ? LiveP{ctx->live, M / ctx->Bs} : LiveP{nullptr, 0}; }
 // LayerNorm statistics ride along with the residual stream when the whole block is one MFMA row tile and every GEMM
 // that updates the stream is one the skinny kernel takes (it is the one that writes them: K = d_ff must fit it)
-bool lean_ok(const bpd_config& c, int M);
 bool stats_path(const bpd_ctx* ctx, int M) {
   return !lean_ok(ctx->cfg, M) && ctx->cfg.dtype == BPD_BF16 && M <= 16 && ctx->cfg.d_model <= 1024 && ctx->cfg.d_ff <= 4096;
 }
@@ -543,9 +542,6 @@ void launch_ln_row(bpd_ctx* ctx, float* x, LnW w, int M, void* ya, float* yf, in
   }
 #undef BPD_LN
 }
-// Widths that the kernels of bpd_row_gemm.h are built for
-bool lean_width(int d) { return d == 128 || d == 256 || d == 512 || d == 768 || d == 1024; }
-
 void layernorm(bpd_ctx* ctx, float* x, LnW w, int M, void* ya, float* yf) {
   const int d = ctx->cfg.d_model;
   dim3 grid((M + 3) / 4);
@@ -830,15 +826,10 @@ void refresh_folded_weights(bpd_ctx* ctx) {
 }
 
 // ------------------------------------------------------------------------------- blocks of few rows (bpd_row_gemm.h)
-constexpr int LEAN_M_MAX = 640;
 // The residual GEMM of K = d_ff runs as one kernel up to this K, beyond in K slices of 1024 that the next LayerNorm adds up
 // (4096 x 1024 at 10 rows: 5.5 us whole, 3.4 us in slices, and the LayerNorm kernel with them 2.0 us, which takes the LayerNorm
 // out of the next GEMM: 4.2 -> 3.05 us.  2048 x 512: 3.3 us whole, and 2.1 + 1.9 - 0.8 us in slices).
 constexpr int LEAN_K_WHOLE = 2048;
-bool lean_ok(const bpd_config& c, int M) {
-  return c.dtype == BPD_BF16 && M <= LEAN_M_MAX && lean_width(c.d_model) &&
-         (c.d_ff == 512 || c.d_ff == 1024 || c.d_ff == 2048 || c.d_ff == 3072 || c.d_ff == 4096);
-}
 constexpr int LEAN_PART_M = 192;        // more rows: the slices of the LDS-staged kernel (192 rows 6.8 against 7.25 us, 256 rows 8.0 against 7.3)
 constexpr int LEAN_WHOLE_M = 256;       // ... as well for K = 2048 (256 rows 4.6 against 4.3 us, 320 rows 5.6 against 5.2)
 int lean_slices(const bpd_ctx* ctx, int M) {
@@ -1156,14 +1147,13 @@ int encoder(bpd_ctx* ctx) {
   const size_t as = act_size(c);
   embed(ctx, L.src_ids, S, nullptr, S, M, L.pos_src, L.xe, 0);
   // 17 .. 128 source rows of a width that bpd_row_gemm.h is not built for: the residual GEMMs leave LayerNorm statistics for the LayerNorm-fused GEMM that follows
-  const bool bigs = !lean_ok(c, M) && c.dtype == BPD_BF16 && M > 16 && M <= LDSX_LN_M_MAX && d % 64 == 0 && d <= 1024;
+  const bool lean = lean_ok(c, M), bigs = !lean && c.dtype == BPD_BF16 && M > 16 && M <= LDSX_LN_M_MAX && d % 64 == 0 && d <= 1024;
   auto residual = [&](const float* bias) {
     Epi e = plain(bias, 0, L.xe, d, L.xe, d, nullptr, 0);
     if (bigs) e.stats_out = L.stats_big;
     return e;
   };
   bool xs = false;      // L.stats_big describes the current L.xe
-  const bool lean = lean_ok(c, M);
   for (int l = 0; l < c.n_enc_layers; ++l) {
     EncL& w = L.enc[l];
     const Epi kv = kv_split(ctx, L.qe, L.ke, L.ve, 0, S, S, nullptr, nullptr);

@@ -102,10 +102,26 @@ bool small_shape(const bpd_config& c) {
   return c.dtype == BPD_F32 && d <= 256 && V <= 4096 && c.n_dec_layers <= 8 && c.n_enc_layers <= 8 && (c.n_dec_layers * (6 * d * d + 2 * d * F) + 2 * k * d * F + V * d) * 4 <= SMALL_WEIGHTS_MAX;
 }
 
-// Decoder blocks of more than 128 rows run their LayerNorm-then-GEMM pairs as one GEMM on weights with the LayerNorm
+// Shapes and row counts that run on the kernels with a constant K (bpd_row_gemm.h).
+// Decoder layers, us with them and without (the LDS-staged GEMMs on folded weights), by block rows:
+//   d = 1024, d_ff 4096   160: 348, 375   200: 380, 389   260: 461, 483   320: 458, 430   400: 538, 531   480: 531, 497   560: 669, 701   640: 622, 597
+//   d = 512, d_ff 2048    160: 206, 234   256: 230, 251   320: 276, 281   448: 291, 295   512: 304, 301   576: 341, 343   640: 344, 334
+// They cross at 300 and at 500 rows.  From there to 640 the constant K costs up to 6 % of the layers and stays: folded weights round
+// the residual stream to bf16 before its LayerNorm and not after, and contexts of up to 640 rows need no second copy of three
+// matrices per layer (Transformer-big: 96 MB).
+constexpr int LEAN_M_MAX = 640;
+bool lean_width(int d) { return d == 128 || d == 256 || d == 512 || d == 768 || d == 1024; }
+bool lean_ok(const bpd_config& c, long M) {
+  return c.dtype == BPD_BF16 && M <= LEAN_M_MAX && lean_width(c.d_model) &&
+         (c.d_ff == 512 || c.d_ff == 1024 || c.d_ff == 2048 || c.d_ff == 3072 || c.d_ff == 4096);
+}
+
+// Other decoder blocks of more than 128 rows run their LayerNorm-then-GEMM pairs as one GEMM on weights with the LayerNorm
 // folded in (ROWAFF in bpd_gemm.h); contexts that can see such blocks keep a folded copy of those matrices.
+constexpr int LDSX_LN_M_MAX = 128;     // LayerNorm-fused consumers and statistics-writing producers: blocks of at most 128 rows
 bool fold_kept(const bpd_config& c) {
-  return c.dtype == BPD_BF16 && (long)c.max_batch * c.k_max > 128 && c.d_model % 64 == 0 && c.d_model <= 1024;
+  const long rows = (long)c.max_batch * c.k_max;
+  return c.dtype == BPD_BF16 && rows > LDSX_LN_M_MAX && !lean_ok(c, rows) && c.d_model % 64 == 0 && c.d_model <= 1024;
 }
 
 // Shapes the decoder stack kernel is built for (what a step additionally needs is checked per launch)
@@ -195,7 +211,6 @@ size_t build_layout(const bpd_config& c, char* base, Layout& L, std::vector<std:
 }
 
 constexpr int LDSX_LN_MT_MAX = 3;      // LayerNorm-fused consumers and statistics-writing producers: tiles of at most 48 rows
-constexpr int LDSX_LN_M_MAX = 128;     // and blocks of at most 128 rows
 constexpr long LDSX_MIN_WGS = 440;
 constexpr long LDSX_MIN_WGS_LONGK = 400;   // K >= 2048, fewer than 1024 rows: a workgroup lives long enough that about 1.5 per CU suffice
                                            // (the encoder's 4096-row FFN output: 64-row tiles, 512 workgroups, beat 80-row tiles, 416: encode -2%)

@@ -44,6 +44,10 @@ static void check_config(const bpd_config& c) {
   EXPECT((size_t)((char*)L.keys_h1 - (char*)L.keys) >= M * k * 8, "keys");
   EXPECT((size_t)((char*)L.hn2 - (char*)L.keys_h1) >= 2 * M * 8, "head-1 and second-phase keys");
   EXPECT(L.n_zeros >= std::max({k * F, V, 3 * d}), "zero vector");
+  // folded copies of the decoder's matrices: there whenever a block of the context needs them, and only then
+  bool needed = false;
+  for (long rows = 1; rows <= (long)M; ++rows) needed = needed || (c.dtype == BPD_BF16 && rows > LDSX_LN_M_MAX && !lean_ok(c, rows) && d % 64 == 0 && d <= 1024);
+  EXPECT((L.dec[0].f_qkv.W != nullptr) == needed && (L.dec[0].f_w1.W != nullptr) == needed, "folded copies d=%zu F=%zu rows=%zu", d, F, M);
   // split factors stay inside their buffers for every block the context may see
   for (int b = 1; b <= c.max_batch; b += (c.max_batch > 8 ? 3 : 1))
     for (int kk = 1; kk <= c.k_max; kk += (c.k_max > 6 ? 2 : 1)) {
@@ -76,7 +80,7 @@ int main() {
     const int dh = (c.dtype == BPD_F32 || U(0, 2) == 0) ? 16 : 64;
     c.n_heads = U(1, dh == 16 ? 16 : 32);
     c.d_model = dh * c.n_heads;
-    c.d_ff = 32 * U(1, 160);
+    c.d_ff = U(0, 1) ? 32 * U(1, 160) : 512 * U(1, 9);
     c.vocab = 16 * U(1, 2200);
     c.k_max = U(1, 16);
     c.n_enc_layers = U(1, 6); c.n_dec_layers = U(1, 8);

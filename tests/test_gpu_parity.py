@@ -453,9 +453,13 @@ ODD_SHAPES = [
     wl.Config("loc-bf16", 32, 1, 2, 128, 2, 256, 528, 5, 3, 7, 40, "bf16", 2, src_len_kind="lognormal", local_q=8, local_m=5),
     wl.Config("loc-f32", 33, 1, 2, 64, 4, 128, 272, 4, 2, 6, 36, "f32", 2, local_q=6, local_m=3),
     wl.Config("loc-dh16", 34, 1, 1, 128, 8, 256, 528, 3, 2, 7, 30, "bf16", 2, local_q=4, local_m=9),
-    # more than 128 block rows: LayerNorm folded into the weights of the GEMM that follows it (row-affine epilogue on
-    # the raw bf16 copy of the residual stream); 153 rows = nine 16-row tiles and a ragged one
+    # more than 128 block rows, 153 = nine 16-row tiles and a ragged one: kernels with a constant K at this width and
+    # depth; at others LayerNorm folded into the weights of the GEMM that follows it (row-affine epilogue on the raw bf16
+    # copy of the residual stream): odd-fold192 (width), odd-fold640 (depth), odd-b66 (more than 640 rows)
     wl.Config("odd-fold153", 37, 1, 3, 256, 4, 512, 528, 9, 17, 6, 24, "bf16", 2, src_len_kind="lognormal"),
+    wl.Config("odd-fold192", 43, 1, 3, 192, 3, 384, 528, 9, 17, 6, 24, "bf16", 2, src_len_kind="lognormal"),
+    wl.Config("odd-fold640", 44, 1, 2, 256, 4, 640, 528, 10, 14, 6, 24, "bf16", 2, src_len_kind="lognormal"),
+    wl.Config("odd-b66", 45, 1, 2, 128, 2, 512, 272, 10, 66, 5, 22, "bf16", 2, src_len_kind="lognormal"),
     wl.Config("loc-b20", 35, 1, 1, 128, 2, 256, 528, 4, 20, 7, 30, "bf16", 2, src_len_kind="lognormal", local_q=5, local_m=0),
     # the widest model bpd_create accepts (d = 2048) on one row tile, and d = 1536 on 30 rows with a 2048-deep FFN
     # output: beyond d = 1024 LayerNorm is a kernel of its own (a row of up to 2048 floats per wavefront), the accept
@@ -617,11 +621,12 @@ def test_accept_kernel_embedding_next_block_changes_nothing(which):
 
 
 @pytest.mark.gpu
-def test_reloaded_layernorm_weights_reach_the_folded_copies():
-    """Blocks of more than 128 rows multiply by copies of the decoder matrices with the LayerNorm in front of them
-    folded in.  LayerNorm gains and biases loaded later (a new bpd_encode is then required) must reach those
+@pytest.mark.parametrize("which", ["odd-fold153", "odd-fold192", "odd-fold640", "odd-b66"])
+def test_reloaded_layernorm_weights_reach_the_folded_copies(which):
+    """Blocks of more than 128 rows (odd-fold153: where no kernels with a constant K take them) multiply by copies of the
+    decoder matrices with the LayerNorm in front of them folded in.  LayerNorm gains and biases loaded later (a new bpd_encode is then required) must reach those
     copies: the state after the same steps equals that of a fresh context given the new weights from the start."""
-    cfg = {c.name: c for c in ODD_SHAPES}["odd-fold153"]
+    cfg = {c.name: c for c in ODD_SHAPES}[which]
     w1 = wl.make_weights(cfg, std=0.02)
     rng = np.random.default_rng(3)
     new_ln = {n: (a + rng.normal(0, 0.05, a.shape)).astype(np.float32) for n, a in w1.items()
