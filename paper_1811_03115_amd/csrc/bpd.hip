@@ -1147,7 +1147,7 @@ int encoder(bpd_ctx* ctx) {
   const size_t as = act_size(c);
   embed(ctx, L.src_ids, S, nullptr, S, M, L.pos_src, L.xe, 0);
   // 17 .. 128 source rows of a width that bpd_row_gemm.h is not built for: the residual GEMMs leave LayerNorm statistics for the LayerNorm-fused GEMM that follows
-  const bool lean = lean_ok(c, M), bigs = !lean && c.dtype == BPD_BF16 && M > 16 && M <= LDSX_LN_M_MAX && d % 64 == 0 && d <= 1024;
+  const bool lean = lean_encoder_ok(c, M), bigs = !lean && c.dtype == BPD_BF16 && M > 16 && M <= LDSX_LN_M_MAX && d % 64 == 0 && d <= 1024;
   auto residual = [&](const float* bias) {
     Epi e = plain(bias, 0, L.xe, d, L.xe, d, nullptr, 0);
     if (bigs) e.stats_out = L.stats_big;

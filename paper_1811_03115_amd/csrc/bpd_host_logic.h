@@ -109,12 +109,17 @@ bool small_shape(const bpd_config& c) {
 // They cross at 300 and at 500 rows.  From there to 640 the constant K costs up to 6 % of the layers and stays: folded weights round
 // the residual stream to bf16 before its LayerNorm and not after, and contexts of up to 640 rows need no second copy of three
 // matrices per layer (Transformer-big: 96 MB).
+// Encodes (without: LayerNorm kernels and LDS-staged GEMMs, the same roundings), by source rows:
+//   d = 1024   128: 471, 472   256: 553, 575   384: 644, 629   512: 703, 679   640: 791, 749        -> up to 320 rows
+//   d = 512    128: 293, 292   256: 332, 357   384: 374, 394   512: 401, 408   640: 447, 450        -> up to 640
 constexpr int LEAN_M_MAX = 640;
+constexpr int LEAN_ENC_WIDE_M_MAX = 320;      // encoder, d > 512
 bool lean_width(int d) { return d == 128 || d == 256 || d == 512 || d == 768 || d == 1024; }
 bool lean_ok(const bpd_config& c, long M) {
   return c.dtype == BPD_BF16 && M <= LEAN_M_MAX && lean_width(c.d_model) &&
          (c.d_ff == 512 || c.d_ff == 1024 || c.d_ff == 2048 || c.d_ff == 3072 || c.d_ff == 4096);
 }
+bool lean_encoder_ok(const bpd_config& c, long M) { return lean_ok(c, M) && (c.d_model <= 512 || M <= LEAN_ENC_WIDE_M_MAX); }
 
 // Other decoder blocks of more than 128 rows run their LayerNorm-then-GEMM pairs as one GEMM on weights with the LayerNorm
 // folded in (ROWAFF in bpd_gemm.h); contexts that can see such blocks keep a folded copy of those matrices.

@@ -27,6 +27,13 @@ def test_row_blocks(d, F, k, B):
     lockstep(cfg, 2)
 
 
+# source rows on both sides of where the encoder leaves the kernels with a constant K: 320 (beyond d = 512) and 640
+@pytest.mark.parametrize("d,F,B,S", [(1024, 1024, 10, 32), (1024, 1024, 11, 30), (512, 512, 20, 32), (512, 512, 21, 31), (768, 512, 9, 36)])
+def test_encoder_rows(d, F, B, S):
+    cfg = wl.Config("rows", 74, 2, 1, d, d // 64, F, 272, 2, B, S, 8, "bf16", 2)
+    lockstep(cfg, 1)
+
+
 # lengths of the caches on both sides of 32, 128 and 256 keys (a group, four waves, eight waves), sources likewise
 @pytest.mark.parametrize("k,S,out", [(1, 1, 34), (7, 31, 40), (5, 33, 135), (16, 129, 150), (13, 200, 270)])
 def test_key_groups(k, S, out):
