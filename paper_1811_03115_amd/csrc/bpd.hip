@@ -1653,7 +1653,7 @@ static int step_accept(bpd_ctx* ctx, int k, int* accepted_dev, int next_slots, u
       hipLaunchKernelGGL(accept_embed_kernel, dim3(ctx->B), dim3(1024), 0, ctx->stream, s, L.keys, k, ctx->B, imposed_step, accepted_dev,
                          c.d_model, (const bf16_t*)L.emb, c.vocab, (const float*)L.pos_tgt, sqrtf((float)c.d_model), L.x,
                          lean ? nullptr : (sp ? L.stats_ln : L.stats_big), sp ? 16 : rows, sp || lean ? (bf16_t*)nullptr : (bf16_t*)L.xn,
-                         !slots_used(ctx) ? 0 : (ctx->seq ? 2 : 1));
+                         !slots_used(ctx) ? 0 : (ctx->seq ? 2 : 1), ctx->two_phase && k > 1 && ctx->B * k > 16);
       ctx->x_ready_k = k; ctx->x_ready_slots = next_slots;
     } else {
       hipLaunchKernelGGL(accept_kernel, dim3(ctx->B), dim3(64), 0, ctx->stream, s, L.keys, k, ctx->B, 1, imposed_step, accepted_dev);

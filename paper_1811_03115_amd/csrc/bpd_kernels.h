@@ -1240,10 +1240,12 @@ __global__ __launch_bounds__(64) void accept_kernel(StateP s, const unsigned lon
 // 64-column block, [(block * srows + row) * 2]; xb (may be null):
 // bf16 copy of the rows as well.
 // slots != 0: the next step's slots are dealt here (StateP::slot_seq); 2: this step's rows and keys are indexed by slot too.
+// partial: the step is one of two-phase scoring, whose table is column 1 and row k-hat: also where so few sequences are left that
+// the keys are the full table's.
 __global__ __launch_bounds__(1024) void accept_embed_kernel(StateP s, unsigned long long* keys, int k, int B, int step,
                                                             int* accepted_out, int d, const bf16_t* E, int V,
                                                             const float* pos, float scale, float* x, float* stats,
-                                                            int srows, bf16_t* xb, int slots) {
+                                                            int srows, bf16_t* xb, int slots, int partial) {
   __shared__ int tok_s[16];
   __shared__ int L_s;
   __shared__ int slot_s[2];                      // this sequence's slot in this step and in the next (-1: none)
@@ -1315,6 +1317,13 @@ __global__ __launch_bounds__(1024) void accept_embed_kernel(StateP s, unsigned l
       int khat = verified_length_v(s, k, lane, myP, a1, topn_raw, imp_raw);
       bool eos = false;
       khat = cut_length_v(s, lane, myP, khat, max_len - j, eos);
+      if (partial) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int e = lane + 64 * q;
+          if (e < kk && e % k != 0 && e / k != khat - 1) s.A[(b * s.kmax + e / k) * s.kmax + e % k] = -1;
+        }
+      }
       if (lane < khat) s.out_ids[(long)b * s.max_out + j + lane] = myP;
       const int nextP = lane < k ? A_s[(khat > 0 ? khat - 1 : 0) * k + lane] : 0;
       if (lane < k) { s.P[b * s.kmax + lane] = nextP; tok_s[lane] = nextP; }

@@ -74,3 +74,30 @@ def test_ragged_batches(B, d, k, two_phase, top_n):
     ids, lens, st = ctx.bpd_decode(k, sched[6:])
     check(ids, lens, whole)
     assert st.finished == B
+
+
+@pytest.mark.parametrize("B,k", [(6, 4), (9, 2), (5, 5)])
+def test_two_phase_table_when_few_sequences_are_left(B, k):
+    """The table of two-phase scoring is column 1 and row k-hat, all else -1, for every batch of more than 16 block rows: also in
+    steps that sequences have left until the live ones have 16 rows or fewer."""
+    cfg = wl.Config("slots", 61, 1, 2, 128, 2, 512, 528, k, B, 7, 40, "bf16", 2, src_len_kind="lognormal")
+    w, said = saying(cfg, B)
+    src, n = wl.make_sources(cfg)
+    budget = np.array([4 + 6 * b for b in range(B)], np.int32).clip(1, cfg.max_out)
+    sched = np.random.default_rng(B).integers(1, k + 1, (cfg.max_out, B)).astype(np.int32)
+    ctx = gpu_context(cfg, w)
+    ctx.bpd_set_two_phase(True)
+    steps = 0
+    ctx.bpd_encode(src, n, budget)
+    while steps < cfg.max_out:
+        ctx.bpd_decode(k, sched[steps:steps + 3])
+        steps += 3
+        P, A, j, fin = ctx.bpd_get_state()
+        for b in range(B):
+            rows = [r for r in range(k) if (A[b, r, 1:k] >= 0).all()]
+            assert len(rows) == 1, (steps, b, A[b])
+            assert (A[b, :k, 0] >= 0).all() and (np.delete(A[b, :k, 1:k], rows[0], 0) == -1).all(), (steps, b, A[b])
+            assert P[b, :k].tolist() == A[b, rows[0], :k].tolist()
+        if fin.all():
+            break
+    assert fin.all()
