@@ -1072,10 +1072,15 @@ constexpr size_t SMALL_LDS_MAX = 160 * 1024;
 SmallLds small_decode_lds(const bpd_config& c, int rows, int k, int hgroup, bool topn) {
   return small_lds(c.d_model, c.d_ff, c.vocab, rows, k, hgroup, 0, topn, small_decoder_phases(c.d_model, c.n_dec_layers, k, hgroup));
 }
-// heads whose hidden layers fit the LDS together (0: not even one does)
-int small_hgroup(const bpd_ctx* ctx, int k) {
+// Heads whose hidden layers fit the LDS together; 0: not even one does, or steps over caches between as many rows as the host knows
+// there may be and `more` others are faster launch by launch (about the mean of those lengths)
+int small_hgroup(const bpd_ctx* ctx, int k, long more) {
   const bpd_config& c = ctx->cfg;
   if (!small_shape(c)) return 0;
+  const long cap = c.max_out_len + c.k_max + 1, from = std::min(cap, (long)ctx->steps * c.k_max + 1 + k);
+  long keys = (from + std::min(cap, from + more)) / 2;
+  if (ctx->local_q > 0) keys = std::min(keys, (long)ctx->local_q + ctx->local_m + k);
+  if (!small_step_pays(c, k, keys, ctx->S)) return 0;
   int h = k;
   while (h > 0 && (size_t)small_decode_lds(c, k, k, h, ctx->top_n > 1 && k > 1).total * 4 > SMALL_LDS_MAX) --h;
   return h;
@@ -1085,7 +1090,7 @@ SmallLds small_encode_lds(const bpd_config& c, int S) {
 }
 SmallLds small_prime_lds(const bpd_config& c) { return small_lds(c.d_model, c.d_ff, c.vocab, 4, 4, c.k_max, 0, false, small_decoder_phases(c.d_model, c.n_dec_layers, c.k_max, c.k_max)); }
 bool small_encode_ok(const bpd_ctx* ctx) {
-  return small_shape(ctx->cfg) && ctx->prof_phase == 0 && (size_t)small_encode_lds(ctx->cfg, ctx->S).total * 4 <= SMALL_LDS_MAX &&
+  return small_shape(ctx->cfg) && ctx->prof_phase == 0 && small_encode_pays(ctx->cfg, ctx->S) && (size_t)small_encode_lds(ctx->cfg, ctx->S).total * 4 <= SMALL_LDS_MAX &&
          (size_t)small_prime_lds(ctx->cfg).total * 4 <= SMALL_LDS_MAX;
 }
 SmallP small_params(bpd_ctx* ctx) {
@@ -1670,7 +1675,7 @@ static int step_impl(bpd_ctx* ctx, int k, const int* imposed_dev, int* accepted_
   std::fill(ctx->remaining.begin(), ctx->remaining.end(), -1);
   ctx->live1 = ctx->live2 = -1;
   use_slots(ctx, -1);
-  const int hgroup = ctx->prof_phase == 0 || ctx->prof_phase == BPD_PHASE_STEP ? small_hgroup(ctx, k) : 0;
+  const int hgroup = ctx->prof_phase == 0 || ctx->prof_phase == BPD_PHASE_STEP ? small_hgroup(ctx, k, 0) : 0;
   if (hgroup > 0) {
     small_decode(ctx, k, hgroup, 1, imposed_dev, 0, accepted_dev, nullptr);
     LAUNCHCHK();
@@ -1863,7 +1868,9 @@ int bpd_decode(bpd_ctx* ctx, int k, const int32_t* schedule, int max_steps, int3
     LAUNCHCHK();
   }
   auto& rem = ctx->remaining;
-  if (const int hgroup = ctx->prof_phase == 0 ? small_hgroup(ctx, k) : 0) {      // the whole decode as one kernel
+  long more = (long)max_steps * k;               // rows that the caches may grow by
+  if (std::find(rem.begin(), rem.begin() + B, -1) == rem.begin() + B) more = std::min(more, (long)*std::max_element(rem.begin(), rem.begin() + B));
+  if (const int hgroup = ctx->prof_phase == 0 ? small_hgroup(ctx, k, more) : 0) {      // the whole decode as one kernel
     if (max_steps > 0) {
       std::fill(rem.begin(), rem.end(), -1);
       small_decode(ctx, k, hgroup, max_steps, imp, B, nullptr, nullptr);
@@ -1977,7 +1984,7 @@ int bpd_debug_step_logits(bpd_ctx* ctx, int k, float* logits) {
   if (k < 1 || k > ctx->cfg.k_max) return fail(ctx, BPD_E_ARG, "bpd_debug_step_logits: k outside 1..k_max");
   forget_replayed(ctx);
   use_slots(ctx, ctx->B);                         // every sequence, ended or not
-  if (const int hgroup = ctx->prof_phase == 0 ? small_hgroup(ctx, k) : 0) {
+  if (const int hgroup = ctx->prof_phase == 0 ? small_hgroup(ctx, k, 0) : 0) {
     small_decode(ctx, k, hgroup, 1, nullptr, 0, nullptr, logits);
     LAUNCHCHK();
     return BPD_OK;

@@ -102,6 +102,37 @@ int main() {
     check_config(c);
     ++configs;
   }
+  // one workgroup per sequence or launches: measured us of both (d, d_ff, vocab, layers, rows, keys: one, launches), and the
+  // rule takes the faster one wherever they differ by more than a tenth
+  const int STEPS[][8] = {{64, 256, 256, 2, 4, 1, 68, 134}, {64, 256, 256, 2, 4, 64, 71, 157}, {64, 256, 256, 2, 4, 512, 102, 163}, {64, 256, 256, 2, 4, 1000, 135, 158},
+                          {64, 256, 256, 2, 4, 1900, 197, 164}, {64, 256, 256, 2, 4, 3900, 364, 175}, {64, 1024, 1024, 8, 4, 1, 279, 715}, {64, 256, 256, 8, 16, 1, 563, 498},
+                          {64, 256, 256, 8, 16, 1000, 1698, 537}, {128, 512, 256, 2, 4, 1, 118, 180}, {128, 512, 256, 2, 4, 512, 195, 200}, {128, 512, 256, 2, 4, 1000, 272, 197},
+                          {128, 512, 256, 4, 4, 1, 192, 369}, {256, 512, 256, 1, 4, 1, 154, 144}, {256, 256, 256, 3, 1, 1, 169, 252}, {256, 256, 256, 3, 1, 512, 252, 352},
+                          {256, 256, 256, 3, 1, 1000, 337, 366}, {256, 256, 256, 3, 1, 1900, 497, 378}, {32, 64, 64, 1, 16, 1, 95, 74}, {64, 256, 256, 2, 8, 1, 105, 141},
+                          {64, 256, 256, 4, 8, 1, 158, 245}, {128, 512, 256, 2, 8, 1, 209, 216}, {64, 256, 4096, 2, 4, 1, 115, 166}, {64, 256, 256, 2, 16, 1, 255, 146},
+                          {64, 256, 256, 2, 12, 1, 185, 143}, {32, 128, 256, 2, 8, 1, 75, 117}, {64, 256, 256, 2, 1, 1, 50, 121}};
+  const int ENCODES[][8] = {{64, 256, 256, 2, 4, 16, 134, 231}, {64, 256, 256, 2, 4, 33, 235, 234}, {64, 256, 256, 2, 4, 64, 334, 209}, {64, 256, 256, 2, 4, 128, 736, 239},
+                            {64, 256, 256, 2, 4, 300, 2549, 242}, {64, 1024, 1024, 8, 4, 16, 567, 1280}, {64, 1024, 1024, 8, 4, 64, 1595, 1307}, {64, 1024, 1024, 8, 4, 128, 3545, 1451},
+                            {64, 256, 256, 8, 16, 16, 433, 796}, {128, 512, 256, 2, 4, 16, 233, 283}, {128, 512, 256, 2, 4, 32, 353, 284}, {128, 512, 256, 4, 4, 16, 397, 640},
+                            {256, 512, 256, 1, 4, 16, 272, 223}, {256, 256, 256, 3, 1, 16, 488, 573}, {32, 64, 64, 1, 16, 16, 75, 120}, {32, 64, 64, 1, 16, 128, 276, 130},
+                            {64, 256, 256, 2, 8, 16, 141, 219}, {64, 256, 256, 4, 8, 16, 227, 419}, {128, 512, 256, 2, 8, 16, 261, 301}, {64, 256, 4096, 2, 4, 16, 166, 263},
+                            {64, 256, 256, 2, 16, 16, 155, 226}, {64, 256, 256, 2, 1, 16, 128, 220}, {32, 128, 256, 2, 8, 16, 110, 191}};
+  auto fp32_model = [](const int* m) {
+    bpd_config c{};
+    c.n_enc_layers = c.n_dec_layers = m[3]; c.d_model = m[0]; c.n_heads = m[0] / 16; c.d_ff = m[1]; c.vocab = m[2]; c.k_max = m[4];
+    c.max_batch = 1; c.max_src_len = 300; c.max_out_len = 4000; c.dtype = BPD_F32; c.eos_id = 2; c.ln_eps = 1e-6f;
+    return c;
+  };
+  for (auto& m : STEPS) {
+    const bpd_config c = fp32_model(m);
+    EXPECT(config_ok(c) && small_shape(c), "measured shape d %d", m[0]);
+    if (10 * std::min(m[6], m[7]) < 9 * std::max(m[6], m[7]))
+      EXPECT(small_step_pays(c, m[4], m[5] + m[4], 16) == (m[6] < m[7]), "step d %d F %d L %d rows %d keys %d: %.0f %.0f", m[0], m[1], m[3], m[4], m[5], small_step_us(c, m[4], m[4], m[5] + m[4], 16), launched_step_us(c));
+  }
+  for (auto& m : ENCODES) {
+    const bpd_config c = fp32_model(m);
+    if (10 * std::min(m[6], m[7]) < 9 * std::max(m[6], m[7])) EXPECT(small_encode_pays(c, m[5]) == (m[6] < m[7]), "encode d %d F %d L %d S %d", m[0], m[1], m[3], m[5]);
+  }
   // the tile rule: every answer is a tile the library has, K is a multiple of the chunk depth, the cap on rows is kept
   long tiles = 0;
   for (int M : {17, 20, 33, 48, 64, 80, 100, 128, 153, 252, 320, 512, 1000, 3200, 4096})

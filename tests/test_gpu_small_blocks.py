@@ -75,3 +75,36 @@ def test_replayed_steps(B, eos, local):
         assert st.steps == steps
         for a, b in zip(ctx.bpd_get_state(), ref.bpd_get_state()):
             assert (np.asarray(a) == np.asarray(b)).all()
+
+
+# d, F, k, S, longest output: caches past which steps go out launch by launch (about 1000 keys); sources of two tiles, which one
+# workgroup encodes, and of three, which it does not; 16 rows, launch by launch from the start
+@pytest.mark.parametrize("d,F,k,S,out", [(64, 256, 4, 32, 1300), (64, 256, 8, 33, 500), (32, 64, 16, 16, 120)])
+def test_small_models_leave_the_one_workgroup(d, F, k, S, out):
+    """Small fp32 models by the rule against launches throughout (what timing a phase makes of it): same tokens, scores to
+    fp32 rounding, in steps that change over in mid-sequence and in whole decodes."""
+    from paper_1811_03115_amd import binding
+    from test_gpu_slots import saying
+    cfg = wl.Config("small", 75, 2, 2, d, d // 16, F, 256, k, 2, S, out, "f32", -1)
+    w, said = saying(cfg, 9)
+    ctx, ref = gpu_context(cfg, w), gpu_context(cfg, w)
+    ref.bpd_profile_enable(binding.PHASE_ACCEPT)
+    src, n = wl.make_sources(cfg)
+    n[-1] = max(1, S - 5)
+    full = np.full(2, k, np.int32)
+    for c in (ctx, ref):
+        c.bpd_encode(src, n)
+    for s in range((out - k) // k):
+        for c in (ctx, ref):
+            c.bpd_step(k, full)
+        if s % 60 == 3:
+            a, b = ctx.bpd_debug_step_logits(k), ref.bpd_debug_step_logits(k)
+            assert float((a - b).abs().max()) <= 1e-4, s
+            for u, v in zip(ctx.bpd_get_state(), ref.bpd_get_state()):
+                assert (np.asarray(u) == np.asarray(v)).all(), s
+    for budget in (out, 20):
+        for c in (ctx, ref):
+            c.bpd_encode(src, n, np.full(2, budget, np.int32))
+        got, want = ctx.bpd_decode(k), ref.bpd_decode(k)
+        assert got[1].tolist() == want[1].tolist() == [budget] * 2 and (got[0] == want[0]).all()
+        assert got[2].steps == want[2].steps
