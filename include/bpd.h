@@ -13,15 +13,27 @@
  *   and row k-hat of A becomes the next block of proposals.
  *
  * All device work is enqueued on the HIP stream given at creation; unless stated otherwise a
- * call does not synchronise.  Every function returns 0 (BPD_OK) or a negative error code and
+ * call does not synchronise.  Where a call waits for the GPU to report through pinned host memory
+ * (bpd_decode, bpd_get_*, bpd_encode with host arrays) it polls: one CPU core is busy meanwhile.
+ * Every function returns 0 (BPD_OK) or a negative error code and
  * never throws or aborts; bpd_last_error() gives a message.  On an argument error the decode
  * state is left unchanged.
  *
  * Calls on one context must not overlap (one thread at a time, or external locking), and all
  * contexts of a process must live on one device: kernel attributes are set once per process.
  *
- * Pointer arguments marked [host|device] may be either (they are copied with
- * hipMemcpyDefault); arguments marked [device] are dereferenced by kernels.
+ * Pointer arguments marked [host|device] may be either; arguments marked [device] are
+ * dereferenced by kernels.
+ *
+ * Capture.  bpd_encode, bpd_step, bpd_step_static, bpd_set_proposals and bpd_debug_step_logits can
+ * be captured into a HIP graph on the context's stream and replayed any number of times, with
+ * direct calls in between (the calls that wait cannot).  Settings (bpd_set_*), B, S and k are
+ * those of the capture; arrays are read and written where they were: device arrays by the kernels,
+ * host arrays by copies in the graph, so both must stay valid.  A replayed encode takes the place
+ * of a direct one with the same B and S (the last direct or captured call must have had them); a
+ * replayed step that of a direct one.  From its first captured call on a context takes nothing
+ * from earlier calls for granted that a replay may have changed, which costs later direct steps
+ * the embedding of their block (one kernel) and bpd_decode the knowledge of how much is left.
  */
 #ifndef BPD_H
 #define BPD_H
@@ -43,7 +55,15 @@ extern "C" {
 #define BPD_F32  0
 #define BPD_BF16 1
 
-typedef struct bpd_ctx bpd_ctx;   /* opaque; owns small host structs only */
+/* Opaque.  Beside host structs a context owns
+ *   - pinned host memory: 4 * (max_batch * (max_src_len + max_out_len + 6) + 16) bytes and room for
+ *     results on their way to the caller (as many ints as outputs or state have, at most 32768);
+ *   - recorded launches: up to 24 encodes and 24 steps of bpd_decode that came again and again, as
+ *     HIP graphs (no device memory of its own, but the runtime keeps the arguments of a graph's
+ *     kernels in device memory: some 100 launches of up to 400 bytes each), and a non-blocking
+ *     stream that only records them.  At most 24 more wait for the stream to have passed them.
+ * All of it is given back by bpd_destroy. */
+typedef struct bpd_ctx bpd_ctx;
 
 /* Model and capacity description.  k_max counts all heads p_1..p_k (Section 3: p_1 is the
  * base model, p_2..p_k the proposal models; Section 6: p_1 passes through a head as well).
@@ -106,8 +126,9 @@ typedef struct {
 size_t bpd_workspace_bytes(const bpd_config* cfg);
 
 /* Create a context on the current device.  workspace [device] is caller-owned, 256-byte
- * aligned, at least bpd_workspace_bytes(cfg) bytes, and must outlive the context; the
- * library allocates no device memory itself.  hip_stream is a hipStream_t (NULL = the
+ * aligned, at least bpd_workspace_bytes(cfg) bytes, and must outlive the context; apart from
+ * what the runtime does for recorded launches (see bpd_ctx) and bpd_step_static's array the library
+ * takes no device memory.  hip_stream is a hipStream_t (NULL = the
  * default stream).  Errors: BPD_E_ARG, BPD_E_CAPACITY. */
 int bpd_create(const bpd_config* cfg, void* workspace, size_t workspace_bytes,
                void* hip_stream, bpd_ctx** out);
@@ -134,6 +155,9 @@ int bpd_load_weights(bpd_ctx* ctx, const bpd_tensor* tensors, int n);
  *   src_ids [host|device]  int32 [B, S] row-major, rows padded beyond src_len[b]
  *   src_len [host|device]  int32 [B], 1 <= src_len[b] <= S
  *   max_len [host|device]  int32 [B] output budget per sequence (1..max_out_len), or NULL
+ * Host arrays are checked and copied to a pinned staging area before the call returns; a call with
+ * host arrays waits until the last such call's have been read from there.  With device arrays
+ * (out-of-range values are clamped) the call only enqueues.
  * Errors: BPD_E_STATE (weights missing), BPD_E_CAPACITY (B, S over the limits), BPD_E_ARG. */
 int bpd_encode(bpd_ctx* ctx, const int32_t* src_ids, const int32_t* src_len,
                const int32_t* max_len, int B, int S);
@@ -183,7 +207,9 @@ int bpd_set_top_n(bpd_ctx* ctx, int n);
  * heads 2..k only at block row k-hat, the one row whose proposals the next step uses: 2k - 1
  * vocabulary-projection rows per sequence instead of k^2, at the price of a second, dependent
  * pass over the head and embedding weights.  Pays off when the step is compute bound (large
- * batch); applies to bf16 contexts with more than 16 block rows per step, otherwise ignored.
+ * batch); applies to bf16 contexts with more than 16 block rows per step (k times the batch given
+ * to bpd_encode), otherwise ignored.  (Steps of bpd_decode with so few sequences left that their
+ * rows are 16 or fewer compute the full table, which is faster there; what they report is the same.)
  * The table returned by bpd_get_state then holds column 1 of every row and row k-hat only
  * (other entries -1).  Default off.  Errors: BPD_E_ARG (null ctx). */
 int bpd_set_two_phase(bpd_ctx* ctx, int on);
@@ -200,7 +226,9 @@ int bpd_set_two_phase(bpd_ctx* ctx, int on);
 int bpd_set_local_attention(bpd_ctx* ctx, int query_block, int memory_len);
 
 /* The decoding loop of Section 3 with the merged verify / predict invocation of Section 4:
- * repeat bpd_step until every sequence has ended or max_steps steps were made; synchronises.
+ * repeat bpd_step until every sequence has ended or max_steps steps were made; waits for the end
+ * (following the decode step by step, on one CPU core).  The rows of sequences that have ended
+ * leave the steps of the others.
  * A sequence ends as greedy decoding does (Section 2): when the end-of-sequence token has been
  * accepted, or at its length budget max_len (the only rule when eos_id < 0: a fixed number of
  * tokens, as for the images of Section 7.2).

@@ -1968,6 +1968,7 @@ int bpd_get_state(bpd_ctx* ctx, int32_t* P, int32_t* A, int32_t* j, int32_t* fin
 int bpd_set_proposals(bpd_ctx* ctx, const int32_t* P) {
   if (!ctx || !P) return fail(ctx, BPD_E_ARG, "bpd_set_proposals: null argument");
   if (!ctx->encoded) return fail(ctx, BPD_E_STATE, "bpd_set_proposals: call bpd_encode first");
+  forget_replayed(ctx);
   const size_t n = (size_t)ctx->B * ctx->cfg.k_max;
   if (is_host_ptr(P)) {
     for (size_t i = 0; i < n; ++i)

@@ -141,6 +141,8 @@ def test_direct_calls_between_replays(dtype, d, F, eos, B):
     encode = capture(stream, lambda: cap.bpd_encode(src, n, budget))
     replay(encode, stream)
     step = capture(stream, lambda: cap.bpd_step(3, two))
+    P_dev = torch.zeros((B, 4), dtype=torch.int32, device="cuda")
+    proposals = capture(stream, lambda: cap.bpd_set_proposals(P_dev))
 
     def decode(c, sched=None):
         ids, lens, st = c.bpd_decode(3, sched)
@@ -163,8 +165,13 @@ def test_direct_calls_between_replays(dtype, d, F, eos, B):
         P = ref.bpd_get_state()[0]
         if rep % 2:                                        # other proposals, then a replayed step
             P = ((P + 7) % cfg.vocab).astype(np.int32)
-            for c in (ref, cap):
-                c.bpd_set_proposals(P)
+            ref.bpd_set_proposals(P)
+            if rep == 3:
+                P_dev.copy_(torch.from_numpy(P))
+                torch.cuda.synchronize()
+                replay(proposals, stream)
+            else:
+                cap.bpd_set_proposals(P)
             ref.bpd_step(3, two)
             replay(step, stream)
             same(snapshot(ref), snapshot(cap), f"after new proposals, time {rep}")
