@@ -1,6 +1,7 @@
 """Summaries of rocprofv3 runs of bench.py: writes the text tables under profiles/ and profiles/traffic.json.
 
     python -m paper_1811_03115_amd.profsum --trace DIR --fetch DIR --write DIR [--sq DIR] [--c4-fetch DIR --c4-write DIR]
+    python -m paper_1811_03115_amd.profsum --case NAME=DIR [--case NAME=DIR ...]       (traces of the cases of perf/cases.py)
 
 Each DIR is the `-d` output directory of one rocprofv3 run (a rocpd sqlite database somewhere below it).  The commands
 that produce the runs are printed into the headers of the files written, so that every number can be reproduced from
@@ -22,15 +23,20 @@ BENCH_PMC = "python3 bench.py --steps 30 --warmup 5 --no-cpu-baseline --no-batch
 BENCH_SQ = "python3 bench.py --steps 10 --warmup 3 --no-cpu-baseline --no-other-configs --no-k-sweep --no-peaks"
 BENCH_C4 = "python3 bench.py --only C4 --copy-calibration"
 
-# kernels of one C2 step (batch 1, 10 block rows) by phase: (substring of the kernel name, grid x, launches per step)
+BENCH_CASE = ("python3 -c \"import sys, torch; from perf import cases as p; c = {x['name']: x for x in p.listed()}[sys.argv[1]]; s = p.prepare(c, 1); "
+              "[p.run(s) for _ in range(int(sys.argv[2]))]; torch.cuda.synchronize()\" NAME 12        (image cases: 2)")
+
+# kernels of one C2 step (batch 1, 10 block rows) by phase: (substring of the kernel name, grid x or several, launches per step)
 C2_STEP = {
-    "layers": [("skinny_gemm_kernel<1, 1, true, false, 8, 4, 0, false>", 98304, 6),        # LayerNorm + QKV
-               ("attention_mfma_kernel<false, false, 0>", 4096, 6),                       # self-attention
-               ("skinny_gemm_kernel<1, 1, false, false, 4, 8, 0, false>", 16384, 12),      # attention output projections
-               ("attention_mfma_kernel<false, false, 8>", 4096, 6),                       # LayerNorm + query projection + cross-attention
-               ("skinny_gemm_kernel<1, 1, true, false, 8, 4, 0, false>", 131072, 6),       # LayerNorm + FFN in
-               ("skinny_gemm_kernel<1, 1, false, false, 8, 16, 0, false>", 32768, 6)],     # FFN out
-    "head_hidden": [("skinny_gemm_kernel<1, 2, true, false, 8, 4, 2, true>", 131072, 1)],
+    "layers": [("row_gemm_kernel<8, 4, 1, 1, true, 2>", 98304, 1),                         # LayerNorm + QKV of the first layer
+               ("ln_row_kernel<1024, 4>", 2560, 5),                                       # K slices of the FFN output + LayerNorm
+               ("row_gemm_kernel<8, 4, 1, 1, false, 2>", 98304, 5),                        # QKV
+               ("attention_mfma_kernel<false, false, 0>", (4096, 8192), 6),               # self-attention (four or eight waves)
+               ("row_gemm_kernel<8, 4, 1, 1, false, 1>", 32768, 12),                       # attention output projections
+               ("attention_mfma_kernel<false, false, 8>", 8192, 6),                       # LayerNorm + query projection + cross-attention
+               ("row_gemm_kernel<8, 4, 1, 1, true, 0>", 131072, 6),                        # LayerNorm + FFN in
+               ("row_gemm_kernel<8, 4, 1, 1, false, 3>", 32768, 6)],                       # FFN out, four K slices
+    "head_hidden": [("ln_row_kernel<1024, 4>", 2560, 1), ("skinny_gemm_kernel<1, 2, false, false, 4, 8, 2, true>", 65536, 1)],
     "head_out": [("stream_gemm_kernel<16, true>", 12800, 1)],
     "vocab": [("stream_vocab_kernel<4, 1, 2, false>", 65536, 1)],
     "accept": [("accept_embed_kernel", 1024, 1)],
@@ -65,6 +71,21 @@ def trace_table(rows, top):
     return "\n".join(out)
 
 
+def case_table(cur, name, top=16):
+    k = cur.execute("select name, start, end, grid_x, grid_y, grid_z from kernels order by start").fetchall()
+    first = [i for i, x in enumerate(k) if x[0].startswith("encode_init_kernel")][-1]       # (a pass starts with an encode)
+    acc = {}
+    for x in k[first:]:
+        t = acc.setdefault((x[0],) + x[3:], [0, 0])
+        t[0] += 1
+        t[1] += x[2] - x[1]
+    busy = sum(t[1] for t in acc.values())
+    out = [f"{name}: {len(k) - first} kernels, {busy / 1e3:.1f} us"]
+    for key, t in sorted(acc.items(), key=lambda q: -q[1][1])[:top]:
+        out.append(f"  {short(key[0], 86):86s} {t[0]:6d} x {t[1] / t[0] / 1e3:8.2f} = {t[1] / 1e3:10.1f} {100 * t[1] / busy:5.1f} %  {key[1]}x{key[2]}x{key[3]}")
+    return out
+
+
 def pmc_rows(cur):
     return cur.execute("select kernel_name, grid_size_x, counter_name, count(*), avg(value), min(value), max(value), avg(end-start) "
                        "from counters_collection group by kernel_name, grid_size_x, counter_name order by avg(value)*count(*) desc").fetchall()
@@ -78,7 +99,7 @@ def pmc_table(rows, top):
 
 
 def avg_of(rows, sub, grid=None, col=4):
-    m = [r for r in rows if sub in r[0] and (grid is None or r[1] == grid)]
+    m = [r for r in rows if sub in r[0] and (grid is None or r[1] in (grid if isinstance(grid, tuple) else (grid,)))]
     return sum(r[col] * r[3] for r in m) / max(1, sum(r[3] for r in m)) if m else 0.0
 
 
@@ -102,6 +123,7 @@ def main():
     ap.add_argument("--sq")
     ap.add_argument("--c4-fetch")
     ap.add_argument("--c4-write")
+    ap.add_argument("--case", action="append", default=[])
     args = ap.parse_args()
     traffic = {}
     tpath = os.path.join(PROFILES, "traffic.json")
@@ -109,10 +131,21 @@ def main():
         with open(tpath) as f:
             traffic = json.load(f)
 
+    if args.case:
+        out = ["# rocprofv3 kernel traces of the cases of perf/cases.py: the kernels of the last of a dozen passes (images: of two)",
+               f"# command: rocprofv3 --kernel-trace --stats -d prof_out/case_NAME -o t -- {BENCH_CASE}",
+               "# summarised by: python -m paper_1811_03115_amd.profsum " + " ".join(f"--case {c.split('=')[0]}=prof_out/case_{c.split('=')[0]}" for c in args.case),
+               "# durations in microseconds (profiled: a few per cent above unprofiled ones); grid = threads in x, y, z.  The passes' own times",
+               "# are not in here: under the profiler launches take longer than the kernels."]
+        for c in args.case:
+            name, d = c.split("=", 1)
+            out += ["", *case_table(db_of(d), name)]
+        write("case_kernel_traces.txt", "\n".join(out) + "\n")
+
     if args.trace:
         rows = trace_rows(db_of(args.trace))
         def kavg(sub, grid):          # average duration (ns) over the dispatches of that kernel and grid
-            m = [r for r in rows if sub in r[0] and r[6] == grid]
+            m = [r for r in rows if sub in r[0] and r[6] in (grid if isinstance(grid, tuple) else (grid,))]
             return sum(r[2] for r in m) / max(1, sum(r[1] for r in m))
         per_step = {ph: sum(kavg(sub, grid) * n for sub, grid, n in ks) / 1e3 for ph, ks in C2_STEP.items()}
         hdr = [
@@ -124,13 +157,14 @@ def main():
             "# C2 step (batch 1, 10 block rows), average kernel durations x launches per step:",
         ] + [f"#   {ph:12s} {us:8.2f} us" for ph, us in per_step.items()] + [
             f"#   whole step   {sum(per_step.values()):8.2f} us (sum of kernel durations)",
-            "# C2 kernels: skinny_gemm_kernel<1,..> = layer GEMMs and the heads' hidden layers (XLN variants apply LayerNorm from",
-            "#   the partial statistics), stream_gemm_kernel<16,true> = heads' output layers, attention_mfma_kernel<..,0> self-attention,",
-            "#   <..,8> cross-attention with its query projection, stream_vocab_kernel = vocabulary projection + arg-max (100 rows)",
+            "# C2 kernels: row_gemm_kernel<waves, k-steps per wave, row tiles, column tiles, LayerNorm inside, epilogue> = layer GEMMs",
+            "#   (epilogue 0 ReLU, 1 residual, 2 queries / K / V, 3 K slice), ln_row_kernel<columns, slices>, skinny_gemm_kernel = heads'",
+            "#   hidden layers, stream_gemm_kernel = heads' output layers, attention_mfma_kernel<..,0> self-attention, <..,8>",
+            "#   cross-attention with its query projection, stream_vocab_kernel = vocabulary projection + arg-max (100 rows)",
             "# C3 step (batch 32, 320 block rows): gemm_ldsx_kernel<8,4,64,true,..> = vocabulary projection + arg-max (3200 rows),",
-            "#   <7,4,64,false,..> = heads' hidden layers, <4,2,128,false> = heads' output layers (10 groups), <3,1,256> / <2,1,256> /",
-            "#   <1,1,256> = layer GEMMs (the 4096-deep FFN output split 4 ways over K, summed by layernorm_kernel); two-phase mode adds",
-            "#   gemm_ldsx_kernel<5,4,64,true> (320 and 288 rows), select_row_kernel, assemble_keys_kernel",
+            "#   <7,4,64,false,..> = heads' hidden layers, <4,2,128,false> = heads' output layers (10 groups), row_gemm_kernel<8,4,2..4,4,..> =",
+            "#   layer GEMMs, <3,1,256,..> x 4 slices = FFN output, attention_mfma_slots_kernel = attention of the sequences that go on;",
+            "#   two-phase mode adds gemm_ldsx_kernel<5,4,64,true> (320 and 288 rows), select_row_kernel, assemble_keys_kernel",
         ]
         write("bench_c2_c3_kernel_trace.txt", "\n".join(hdr) + "\n" + trace_table(rows, 48) + "\n")
         traffic.setdefault("C2", {})["kernel_us_per_step"] = per_step
@@ -155,7 +189,7 @@ def main():
             "# against the algorithmic bytes (weights read once):",
         ] + [f"#   {ph:12s} {c2[ph] / 1e6:8.1f} MB measured, {alg[ph]:6.1f} MB algorithmic" for ph in c2] + [
             "# (FETCH_SIZE counts what the L2s request from the fabric: it sits in front of the Infinity Cache and cannot tell its hits",
-            "#  from HBM reads.  The decoder layers' 42 kernels each fetch their activations once per XCD on top of the weights.)",
+            "#  from HBM reads.  The decoder layers' 47 kernels each fetch their activations once per XCD on top of the weights.)",
         ]
         write("c2_step_hbm_traffic_pmc.txt", "\n".join(hdr) + "\n\n" + pmc_table(fetch, 14) + "\n\n" + pmc_table(wr, 12) + "\n")
 
@@ -183,7 +217,7 @@ def main():
         ]
         for r in att:
             hdr.append(f"#   {short(r[0], 60)} grid {r[1]}: avg {1024 * fs * r[4] / 1e6:.1f} MB, max {1024 * fs * r[6] / 1e6:.1f} MB per launch "
-                       f"(max: L = 3000+, algorithmic 49.5 MB), avg duration {r[7] / 1e3:.1f} us")
+                       + ("(max: L = 3000+, algorithmic 49.5 MB), " if r is max(att, key=lambda q: q[6]) else "") + f"avg duration {r[7] / 1e3:.1f} us")
         if top:
             tb = 1024 * fs * sum(t[0] for t in top) / len(top)
             tus = sum(t[1] for t in top) / len(top) / 1e3

@@ -18,19 +18,25 @@ ALLOWED = [
     r"skinny_gemm_kernel<1, 1, false, false, 8, 16, 1, (false|true)>",
     r"decoder_stack_kernel<\d+>",
 ]
-# kernels of the batch-1 and batch-32 steps that must be there and scratch-free
+# kernels that must be there and scratch-free: first those that the steps, encodes and decodes of the workloads run
+# (profiles/case_kernel_traces.txt), then those that other widths and depths run in their place
 REQUIRED = [
-    "skinny_gemm_kernel<1, 1, false, false, 8, 16, 0, false>",
-    "skinny_gemm_kernel<1, 1, false, false, 4, 8, 0, false>",
-    "stream_gemm_kernel<16, true>",
-    "stream_vocab_kernel<4, 1, 2, false>",
-    "attention_mfma_kernel<false, false, 8>",
-    "attention_mfma_kernel<false, false, 0>",
-    "gemm_ldsx_kernel<8, 4, 64, true, false, false, false>",
-    "gemm_ldsx_kernel<7, 4, 64, false, false, false, false>",
+    "row_gemm_kernel<8, 4, 1, 1, true, 0>", "row_gemm_kernel<8, 4, 1, 1, true, 2>", "row_gemm_kernel<8, 4, 1, 1, false, 1>",
+    "row_gemm_kernel<8, 4, 1, 1, false, 2>", "row_gemm_kernel<8, 4, 1, 1, false, 3>", "row_gemm_kernel<8, 4, 2, 4, false, 0>",
+    "row_gemm_kernel<8, 4, 4, 4, false, 2>", "row_gemm_kernel<4, 4, 1, 1, true, 0>", "row_gemm_kernel<4, 4, 1, 1, true, 2>",
+    "row_gemm_kernel<4, 4, 1, 1, false, 1>", "row_gemm_kernel<8, 8, 1, 1, false, 1>",
+    "ln_row_kernel<1024, 4>", "ln_row_kernel<1024, 0>", "ln_row_kernel<512, 0>",
+    "attention_mfma_kernel<false, false, 8>", "attention_mfma_kernel<false, false, 4>", "attention_mfma_kernel<false, false, 0>",
+    "attention_mfma_kernel<false, true, -1>", "attention_mfma_kernel<true, false, -1>", "attention_mfma_slots_kernel<false, true, 0>",
+    "attention_mfma_slots_kernel<false, true, -1>",
+    "skinny_gemm_kernel<1, 2, false, false, 4, 8, 2, true>", "skinny_gemm_kernel<1, 1, false, false, 8, 8, 0, false>",
+    "stream_gemm_kernel<16, true>", "stream_vocab_kernel<4, 1, 2, false>", "stream_vocab_kernel<4, 1, 1, false>",
+    "gemm_ldsx_kernel<8, 4, 64, true, false, false, false>", "gemm_ldsx_kernel<7, 4, 64, false, false, false, false>",
     "gemm_ldsx_kernel<4, 2, 128, false, false, false, false>",
-    "gemm_ldsx_kernel<1, 1, 256, false, false, true, false>",
-    "accept_embed_kernel",
+    "small_decode_kernel<1>", "small_encode_kernel", "small_prime_kernel", "accept_embed_kernel", "encode_init_kernel", "decode_init_kernel", "fetch_kernel",
+    "skinny_gemm_kernel<1, 1, false, false, 8, 16, 0, false>", "skinny_gemm_kernel<1, 1, false, false, 4, 8, 0, false>",
+    "gemm_ldsx_kernel<1, 1, 256, false, false, true, false>", "gemm_ldsx_kernel<1, 1, 256, false, true, false, false>", "gemm_ldsx_kernel<1, 1, 256, false, false, false, true>",
+    "layernorm_kernel<unsigned short, 4>",
 ]
 
 
