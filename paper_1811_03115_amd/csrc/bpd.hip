@@ -86,9 +86,6 @@ struct bpd_ctx {
   std::vector<hipEvent_t> prof_ev;
   size_t prof_used = 0;
   int64_t prof_launches = 0;
-  // host / device classification of the pointers bpd_step was last given (a virtual address keeps its kind in the
-  // unified address space, so the runtime is asked once per distinct pointer, not once per step)
-  const void* kind_ptr[4] = {nullptr, nullptr, nullptr, nullptr}; bool kind_host[4] = {false, false, false, false}; int kind_next = 0;
   // a split-K residual update whose slices the next LayerNorm of `pend_x` still has to add
   int pend_slices = 0; const float* pend_bias = nullptr; const float* pend_x = nullptr;
 };
@@ -1202,16 +1199,6 @@ bool is_host_ptr(const void* p) {
   return a.type != hipMemoryTypeDevice && a.type != hipMemoryTypeManaged;
 }
 
-// is_host_ptr with the answers for the last four distinct pointers remembered in the context
-bool is_host_ptr_cached(bpd_ctx* ctx, const void* p) {
-  for (int i = 0; i < 4; ++i)
-    if (ctx->kind_ptr[i] == p) return ctx->kind_host[i];
-  const bool h = is_host_ptr(p);
-  ctx->kind_ptr[ctx->kind_next] = p; ctx->kind_host[ctx->kind_next] = h;
-  ctx->kind_next = (ctx->kind_next + 1) & 3;
-  return h;
-}
-
 // Is the caller recording the context's stream into a graph of its own?
 bool capturing(const bpd_ctx* ctx) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -1696,14 +1683,14 @@ int bpd_step(bpd_ctx* ctx, int k, const int32_t* imposed_accept, int32_t* accept
   // device pointers are used in place by the accept kernel; host arrays go through a copy
   const int* imp = nullptr;
   if (imposed_accept) {
-    if (is_host_ptr_cached(ctx, imposed_accept)) {
+    if (is_host_ptr(imposed_accept)) {
       HIPCHK(hipMemcpyAsync(L.imposed1, imposed_accept, (size_t)ctx->B * 4, hipMemcpyHostToDevice, ctx->stream));
       imp = L.imposed1;
     } else {
       imp = imposed_accept;
     }
   }
-  const bool out_host = accepted_len && is_host_ptr_cached(ctx, accepted_len);
+  const bool out_host = accepted_len && is_host_ptr(accepted_len);
   int rc = step_impl(ctx, k, imp, out_host ? nullptr : accepted_len);
   if (rc) return rc;
   if (out_host) HIPCHK(hipMemcpyAsync(accepted_len, L.accepted, (size_t)ctx->B * 4, hipMemcpyDeviceToHost, ctx->stream));
@@ -1743,14 +1730,14 @@ int bpd_step_static(bpd_ctx* ctx, int k, const int32_t* imposed_accept, int32_t*
                                      " bytes of scratch, the static array holds " + std::to_string(STATIC_SCRATCH_BYTES));
   const int* imp = nullptr;
   if (imposed_accept) {
-    if (is_host_ptr_cached(ctx, imposed_accept)) {
+    if (is_host_ptr(imposed_accept)) {
       HIPCHK(hipMemcpyAsync(L.imposed1, imposed_accept, (size_t)ctx->B * 4, hipMemcpyHostToDevice, ctx->stream));
       imp = L.imposed1;
     } else {
       imp = imposed_accept;
     }
   }
-  const bool out_host = accepted_len && is_host_ptr_cached(ctx, accepted_len);
+  const bool out_host = accepted_len && is_host_ptr(accepted_len);
   // the step's kernels take their scratch from the layout: point it at the static array for this call
   unsigned long long* const keys0 = L.keys; unsigned long long* const keys_h10 = L.keys_h1;
   float* const attn0 = L.attn_part; float* const kpart0 = L.kpart;
