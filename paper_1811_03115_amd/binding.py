@@ -56,6 +56,7 @@ def lib() -> C.CDLL:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is missing: build it with `python -m paper_1811_03115_amd.build` "
                                "(there is no CPU fallback)")
+        import torch  # noqa: F401  (first: the library then uses the HIP runtime that torch brings, not a second one)
         L = C.CDLL(LIB_PATH)
         vp, i32p = C.c_void_p, C.c_void_p
         L.bpd_workspace_bytes.restype = C.c_size_t
