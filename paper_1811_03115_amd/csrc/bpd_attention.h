@@ -77,16 +77,23 @@ struct AttnLds {
 // Largest maximum M, sum L and values o (both relative to M) of NW waves' results for row lane % 16, output tile dt
 template <int NW>
 __device__ __forceinline__ void attention_merge(const AttnLds& sm, int dt, int lane, float& M, float& L, f32x4& o) {
-  float mw[NW];
+  // (every LDS read under way before the first is waited for: left alone the compiler reads and waits wave by wave, 0.4 us for four)
+  float mw[NW], lw[NW];
+  f32x4 ow[NW];
+#pragma unroll
+  for (int w = 0; w < NW; ++w) mw[w] = sm.m_s[w][lane & 15];
+#pragma unroll
+  for (int w = 0; w < NW; ++w) { lw[w] = sm.l_s[w][lane & 15]; ow[w] = sm.o_s[w][dt][lane]; }
+  __builtin_amdgcn_sched_barrier(0);
   M = -INFINITY; L = 0.f;
   o = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int w = 0; w < NW; ++w) { mw[w] = sm.m_s[w][lane & 15]; M = fmaxf(M, mw[w]); }
+  for (int w = 0; w < NW; ++w) M = fmaxf(M, mw[w]);
 #pragma unroll
   for (int w = 0; w < NW; ++w) {
     const float wgt = (mw[w] == -INFINITY) ? 0.f : __expf(mw[w] - M);
-    L = fmaf(sm.l_s[w][lane & 15], wgt, L);
-    o += sm.o_s[w][dt][lane] * wgt;
+    L = fmaf(lw[w], wgt, L);
+    o += ow[w] * wgt;
   }
 }
 
@@ -150,6 +157,7 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
     const bool mine = wave * U < KSTEPS;         // (K = 128: four waves have k-steps)
     const int ks0 = mine ? wave * U : 0;
     // every global load of the kernel is issued before the first wait, in the order in which they are used
+    const f32x4 gbv = *(const f32x4*)((lane % (U * 16) < U * 8 ? qp.g : qp.b) + ks0 * 32 + (lane % (U * 8)) * 4);
     u32x4 wf[4][U], xv[U][2];
     {
       const rsrc_t xr = rsrc_of(qp.x + (size_t)b * p.R * K, mine ? (unsigned)p.R * K * 4 : 0);
@@ -157,7 +165,6 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
 #pragma unroll
       for (int i = 0; i < U; ++i) { xv[i][0] = buf_load16(xr, off + i * 128, 0); xv[i][1] = buf_load16(xr, off + i * 128 + 16, 0); }
     }
-    const f32x4 gbv = *(const f32x4*)((lane % (U * 16) < U * 8 ? qp.g : qp.b) + ks0 * 32 + (lane % (U * 8)) * 4);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -169,6 +176,15 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
     __builtin_amdgcn_sched_barrier(0);
     float* gw = sm.gb_s + wave * (U * 64);
     if (lane < U * 16) *(f32x4*)(gw + lane * 4) = gbv;
+    f32x4 g4[U][2], b4[U][2];
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        g4[i][hh] = *(const f32x4*)(gw + i * 32 + lq * 8 + 4 * hh);
+        b4[i][hh] = *(const f32x4*)(gw + U * 32 + i * 32 + lq * 8 + 4 * hh);
+      }
+    __builtin_amdgcn_sched_barrier(0);
     float mw;                                    // mean of the wave's own columns; the registers then hold the distances to it
     {
       f32x4 s4 = f32x4{0.f, 0.f, 0.f, 0.f}, q4 = s4;
@@ -204,9 +220,8 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
           const f32x4 v = __builtin_bit_cast(f32x4, xv[i][hh]);
-          const f32x4 g4 = *(const f32x4*)(gw + i * 32 + lq * 8 + 4 * hh), b4 = *(const f32x4*)(gw + U * 32 + i * 32 + lq * 8 + 4 * hh);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) y[4 * hh + r] = fmaf(fmaf(v[r], rs, off), g4[r], b4[r]);
+          for (int r = 0; r < 4; ++r) y[4 * hh + r] = fmaf(fmaf(v[r], rs, off), g4[i][hh][r], b4[i][hh][r]);
         }
         u32x4 yb = u32x4{cvt_pk_bf16(y[0], y[1]), cvt_pk_bf16(y[2], y[3]), cvt_pk_bf16(y[4], y[5]), cvt_pk_bf16(y[6], y[7])};
         if (U * NW != KSTEPS && !mine) yb = u32x4{0, 0, 0, 0};
@@ -220,9 +235,13 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
     for (int j = 0; j < 4; ++j) red[(wave * 4 + j) * 64 + lane] = qa[j];
     __syncthreads();
     if (wave < 4) {                              // wave w finishes column tile w: a lane holds row lr, columns 16w + 4lq ..
-      f32x4 sum = red[wave * 64 + lane];
+      f32x4 part[NW];                            // (all reads under way before the first is waited for)
 #pragma unroll
-      for (int w = 1; w < NW; ++w) sum += red[(w * 4 + wave) * 64 + lane];
+      for (int w = 0; w < NW; ++w) part[w] = red[(w * 4 + wave) * 64 + lane];
+      __builtin_amdgcn_sched_barrier(0);
+      f32x4 sum = part[0];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) sum += part[w];
 #pragma unroll
       for (int r = 0; r < 4; ++r) sum[r] *= p.scale;       // (one by one: as a vector product the compiler keeps p.scale in scratch memory)
       const u32x2 hi = u32x2{cvt_pk_bf16(sum[0], sum[1]), cvt_pk_bf16(sum[2], sum[3])};
@@ -340,8 +359,8 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
   if (wave >= 4) return;
   float M, L;
   f32x4 o;
-  if (QU <= 0 && (QU < 0 || nw == 4)) attention_merge<4>(sm, wave, lane, M, L, o);
-  else if (QU > 0 && ngr - first <= 1) { M = sm.m_s[0][lr]; L = sm.l_s[0][lr]; o = sm.o_s[0][wave][lane]; }
+  if (QU >= 0 && ngr - first <= 1) { M = sm.m_s[0][lr]; L = sm.l_s[0][lr]; o = sm.o_s[0][wave][lane]; }         // (the first wave has all keys)
+  else if (QU <= 0 && (QU < 0 || nw == 4)) attention_merge<4>(sm, wave, lane, M, L, o);
   else attention_merge<ATTN_WAVES>(sm, wave, lane, M, L, o);
   const int dim = 16 * wave + 4 * lq;
   if (p.nsplit == 1) {

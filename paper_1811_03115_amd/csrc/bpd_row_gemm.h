@@ -48,6 +48,8 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
   const int lr = lane & 15, lq = lane >> 4;
   const int m0 = blockIdx.y * (16 * MT), tile0 = blockIdx.x * NT;
   const int ksteps = EPI == RG_PART ? p.ksteps : KSTEPS, ks0 = (EPI == RG_PART ? (int)blockIdx.z * KSTEPS : 0) + wave * U;
+  f32x4 gbv;                                     // (first: it passes through LDS while x is on its way)
+  if constexpr (LN) gbv = *(const f32x4*)((lane % (U * 16) < U * 8 ? p.g : p.b) + ks0 * 32 + (lane % (U * 8)) * 4);
   u32x4 a[NT][U];
 #pragma unroll
   for (int u = 0; u < NT; ++u) {
@@ -68,8 +70,6 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
       if constexpr (LN) xv[t][i][1] = buf_load16(xr, off + i * (32 * XB) + 16, 0);
     }
   }
-  f32x4 gbv;
-  if constexpr (LN) gbv = *(const f32x4*)((lane % (U * 16) < U * 8 ? p.g : p.b) + ks0 * 32 + (lane % (U * 8)) * 4);
   // operands of the epilogue, for the tiles that this wave finishes
   f32x4 bias[OWN], res[OWN];
   int key0[OWN], sb[OWN], row0[OWN];
@@ -101,6 +101,15 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
     float* gw = gb + wave * (U * 64);            // written and read by this wave alone: no barrier
     float mw[MT];                                // mean of the wave's own columns
     if (lane < U * 16) *(f32x4*)(gw + lane * 4) = gbv;
+    f32x4 g4[U][2], b4[U][2];
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        g4[i][h] = *(const f32x4*)(gw + i * 32 + lq * 8 + 4 * h);
+        b4[i][h] = *(const f32x4*)(gw + U * 32 + i * 32 + lq * 8 + 4 * h);
+      }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
       // (sums in four chains; the registers then hold the distances to that mean)
@@ -124,14 +133,6 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
       if (lq == 0) st[(wave * MT + t) * 16 + lr] = make_float2(s, q);
     }
     __syncthreads();
-    f32x4 g4[U][2], b4[U][2];
-#pragma unroll
-    for (int i = 0; i < U; ++i)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        g4[i][h] = *(const f32x4*)(gw + i * 32 + lq * 8 + 4 * h);
-        b4[i][h] = *(const f32x4*)(gw + U * 32 + i * 32 + lq * 8 + 4 * h);
-      }
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
       float mu, rs;
@@ -170,9 +171,14 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
   for (int j = 0; j < OWN; ++j) {
     const int id = wave + WAVES * j;
     if (id >= TILES) continue;
-    f32x4 v = red[id * 64 + lane];
+    // (all reads under way before the first is waited for: left alone the compiler reads and waits two by two, 130 cycles each time)
+    f32x4 part[WAVES];
 #pragma unroll
-    for (int w = 1; w < WAVES; ++w) v += red[(w * TILES + id) * 64 + lane];
+    for (int w = 0; w < WAVES; ++w) part[w] = red[(w * TILES + id) * 64 + lane];
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 v = part[0];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) v += part[w];
     const int tile = tile0 + id % NT, n = tile * 16 + lq * 4, m = m0 + (id / NT) * 16 + lr;
     if (NT > 1 && tile >= p.ntiles) continue;
     if (m >= p.M) continue;
