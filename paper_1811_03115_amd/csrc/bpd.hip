@@ -66,6 +66,8 @@ struct bpd_ctx {
   int Bs = 0; const int* seq = nullptr; const int* live = nullptr;
   int live1 = -1, live2 = -1;            // sequences that had not ended after the last step and after the one before (-1: not known)
   int budget_min = 0;                    // smallest length budget of the batch as far as the host knows
+  int layers_group = LK_PLACES;        // workgroups per XCD that layers_kernel waits for (for tests, BPD_LAYERS_GROUP at creation: fewer; 33: waits in vain; 0: the kernel is not used)
+  bool layers_ran = false;             // layers_kernel has been launched and the LayerNorm behind it has not (layernorm() has it clear layers_sync)
   bool weights_exceed_llc = false;     // decoder-side weights read per step > 192 MB (the Infinity Cache holds 256 MB)
   const int* cur_imposed = nullptr; int cur_imposed_stride = 0, cur_imposed_step = 0;   // of the step being run
   // pinned host memory, read and written by kernels directly: the words that say what has happened, the arguments of
@@ -528,7 +530,9 @@ Epi kv_split(const bpd_ctx* ctx, float* Qf, void* Ka, void* Va, int chunk0, int 
 template <int D>
 void launch_ln_row(bpd_ctx* ctx, float* x, LnW w, int M, void* ya, float* yf, int nsl, const float* bias) {
 #define BPD_LN(NSL) hipLaunchKernelGGL((ln_row_kernel<D, NSL>), dim3(M), dim3(ln_row_threads(D)), 0, ctx->stream, x, w.g, w.b, M, ctx->cfg.ln_eps, \
-                                       (bf16_t*)ya, yf, (const float*)ctx->lay.kpart, bias)
+                                       (bf16_t*)ya, yf, (const float*)ctx->lay.kpart, bias, clear, clear ? LK_WORDS / 4 : 0)
+  u32x4* clear = ctx->layers_ran ? (u32x4*)ctx->lay.layers_sync : nullptr;
+  ctx->layers_ran = false;
   switch (nsl) {
     case 0: BPD_LN(0); break;
     case 2: BPD_LN(2); break;
@@ -736,6 +740,47 @@ int stack_check(bpd_ctx* ctx) {
   HIPCHK(hipMemsetAsync(ctx->lay.stack_err, 0, 4, ctx->stream));
   return fail(ctx, BPD_E_HIP, "decoder stack kernel: a bounded wait ran out (code " + std::to_string(e) +
                               "); the results of this decode are invalid, later steps use the per-operator kernels");
+}
+
+// ------------------------------------------------------------------------------- all layers in one kernel (bpd_layers.h)
+bool layers_usable(const bpd_ctx* ctx, int slots, int R) {
+  return ctx->lay.layers_sync && ctx->layers_group > 0 && ctx->num_cus >= LK_JOBS * LK_PLACES && layers_fit(slots, R);
+}
+int layers_split_of(const bpd_ctx* ctx, int slots, int R) {
+  const bpd_config& c = ctx->cfg;
+  long keys = attention_keys(ctx, c.max_out_len + c.k_max + 1, R, 1);
+  if (ctx->local_q > 0) keys = std::min(keys, (long)ctx->local_q + ctx->local_m + R);
+  return layers_split(slots, keys);
+}
+template <bool KVNT>
+void launch_layers_kernel(const bpd_ctx* ctx, const LayersP& p) {
+  static bool attr_set = false;                 // per instantiation: allow more than 64 KiB of LDS
+  if (!attr_set) { (void)hipFuncSetAttribute((const void*)layers_kernel<2048, KVNT>, hipFuncAttributeMaxDynamicSharedMemorySize, LkLds<2048>::BYTES); attr_set = true; }
+  hipLaunchKernelGGL((layers_kernel<2048, KVNT>), dim3(LK_JOBS * LK_PLACES), dim3(512), LkLds<2048>::BYTES, ctx->stream, p);
+}
+void launch_layers(bpd_ctx* ctx, int R) {
+  const bpd_config& c = ctx->cfg;
+  Layout& L = ctx->lay;
+  const size_t d = c.d_model, slots = (size_t)c.max_out_len + c.k_max + 1;
+  const DecL& w = L.dec[0];
+  LayersP p{};
+  p.wqkv = (const char*)w.wqkv; p.wo = (const char*)w.wo; p.cq = (const char*)w.cq; p.co = (const char*)w.co; p.w1 = (const char*)w.w1; p.w2 = (const char*)w.w2;
+  p.ln1 = w.ln1.g; p.ln2 = w.ln2.g; p.ln3 = w.ln3.g; p.b1 = w.b1; p.b2 = w.b2;      // (a bias follows its gain: both are d floats, whole units of ALIGN)
+  p.stride = c.n_dec_layers > 1 ? (long)((const char*)L.dec[1].wqkv - (const char*)w.wqkv) : 0;      // (every layer's arrays are laid out alike)
+  p.n_layers = c.n_dec_layers; p.R = R; p.slots = ctx->Bs; p.per_job = layers_per_job(ctx->Bs); p.jobs = (ctx->Bs + p.per_job - 1) / p.per_job;
+  p.split = layers_split_of(ctx, ctx->Bs, R);
+  p.few = attention_keys(ctx, (int)slots, R, 1) <= 128;
+  p.x = L.x; p.q = (bf16_t*)L.q; p.part = L.attn_part; p.attn = (bf16_t*)L.attn; p.ffh = (bf16_t*)L.ffh;
+  p.selfK = (bf16_t*)L.selfK; p.selfV = (bf16_t*)L.selfV; p.crossK = (const bf16_t*)L.crossK; p.crossV = (const bf16_t*)L.crossV;
+  p.self_layer = (long)c.max_batch * kv_rows(c, slots) * d; p.src_layer = (long)c.max_batch * kv_rows(c, c.max_src_len) * d;
+  p.self_groups = (int)((slots + 31) / 32); p.src_groups = (c.max_src_len + 31) / 32;
+  p.seq = ctx->seq; p.base = ctx->seq ? L.slot_L : L.L; p.src_len = ctx->seq ? L.slot_src : L.src_len;
+  p.eps = c.ln_eps; p.scale = 1.0f / sqrtf(64.f); p.local_q = ctx->local_q; p.local_m = ctx->local_m;
+  p.group = ctx->layers_group;
+  p.sync = L.layers_sync; p.error = L.stats + 31;
+  const bool nt = (size_t)2 * c.n_dec_layers * ctx->Bs * slots * d * 2 > ((size_t)128 << 20);       // (as in attention())
+  if (nt) launch_layers_kernel<true>(ctx, p); else launch_layers_kernel<false>(ctx, p);
+  ctx->layers_ran = true;
 }
 
 // ------------------------------------------------------------------------------- profiling
@@ -954,8 +999,10 @@ int forward(bpd_ctx* ctx, int R, int k, int zero_input, float* logits) {
     xs = have_x && !sp;
     if (!have_x) embed(ctx, L.P, c.k_max, base, R, M, L.pos_tgt, L.x, zero_input, L.keys, (int)nk, seq);
     const bool stack = M <= 16 && (lean || sp) && stack_usable(ctx, B, R);
+    const bool one = !stack && lean && layers_usable(ctx, B, R);
     if (stack) launch_stack(ctx, R);
-    for (int l = 0; l < (stack ? 0 : c.n_dec_layers); ++l) {
+    else if (one) launch_layers(ctx, R);
+    for (int l = 0; l < (stack || one ? 0 : c.n_dec_layers); ++l) {
       DecL& w = L.dec[l];
       char* Kl = (char*)L.selfK + self_layer * l;
       char* Vl = (char*)L.selfV + self_layer * l;
@@ -1421,6 +1468,8 @@ int bpd_create(const bpd_config* cfg, void* workspace, size_t workspace_bytes, v
     }
     (void)hipGetLastError();
   }
+  if (const char* env = getenv("BPD_LAYERS_GROUP")) ctx->layers_group = std::min(LK_PLACES + 1, std::max(0, atoi(env)));
+  if (ctx->lay.layers_sync) (void)hipMemsetAsync(ctx->lay.layers_sync, 0, (size_t)LK_WORDS * 4, ctx->stream);
   (void)hipMemsetAsync(ctx->lay.zeros, 0, ctx->lay.n_zeros * 4, ctx->stream);
   (void)hipMemsetAsync(ctx->lay.step_counter, 0, 4, ctx->stream);
   (void)hipMemsetAsync(ctx->lay.stats_ln, 0, 64 * 16 * 2 * 4, ctx->stream);
@@ -1717,6 +1766,7 @@ int bpd_step_static(bpd_ctx* ctx, int k, const int32_t* imposed_accept, int32_t*
     const size_t wgs = (size_t)c.n_heads * ctx->B * ((k + 15) / 16);
     if (ns > 1) attn_b = std::max(attn_b, up(ns * wgs * 16 * (d / c.n_heads + 2) * 4));
   }
+  if (layers_usable(ctx, ctx->B, k) && layers_split_of(ctx, ctx->B, k) > 1) attn_b = std::max(attn_b, up((size_t)layers_split_of(ctx, ctx->B, k) * c.n_heads * ctx->B * 16 * 66 * 4));
   size_t slices = 1;
   if (lean_ok(c, (int)M)) slices = lean_slices(ctx, (int)M);
   else if (c.dtype == BPD_BF16 && M > 16)
@@ -1805,8 +1855,9 @@ static int output_and_stats(bpd_ctx* ctx, int32_t* out_ids, int32_t* out_len, bp
   Layout& L = ctx->lay;
   long long raw[32];
   const int rc = fetch(ctx, {{L.out_ids, (size_t)ctx->B * ctx->cfg.max_out_len, out_ids}, {L.j, (size_t)ctx->B, out_len},
-                             {(const int*)L.stats, 64, st || count_steps ? raw : nullptr}});
+                             {(const int*)L.stats, 64, raw}});
   if (rc) return rc;
+  if (raw[31]) return fail(ctx, BPD_E_HIP, "decoder layers: a bounded wait ran out; the results of this decode are invalid");
   if (count_steps) ctx->steps = raw[20];
   if (st) stats_of(ctx, raw, st);
   return stack_check(ctx);
@@ -1907,7 +1958,8 @@ int bpd_decode(bpd_ctx* ctx, int k, const int32_t* schedule, int max_steps, int3
       use_slots(ctx, B);
       const int cap = ctx->cfg.max_out_len + ctx->cfg.k_max + 1;
       const bool few = attention_keys(ctx, cap, k, 1) <= 128;
-      const int rc = run_planned(ctx, PLAN_STEP, {B, k, attention_nsplit(ctx, cap, B, k, 1), few, ctx->top_n, ctx->local_q, ctx->local_m, ctx->distance_eps, ctx->min_block},
+      const int nsplit = layers_usable(ctx, B, k) ? layers_split_of(ctx, B, k) : attention_nsplit(ctx, cap, B, k, 1);
+      const int rc = run_planned(ctx, PLAN_STEP, {B, k, nsplit, few, ctx->top_n, ctx->local_q, ctx->local_m, ctx->distance_eps, ctx->min_block},
                                  [&]() -> int {
                                    const int ready = ctx->x_ready_k;
                                    const int64_t steps = ctx->steps;

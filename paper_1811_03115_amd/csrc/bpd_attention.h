@@ -97,6 +97,128 @@ __device__ __forceinline__ void attention_merge(const AttnLds& sm, int dt, int l
   }
 }
 
+// K and V of the groups c, c + nw, .. (G of them) as operands
+template <bool KVNT, int G>
+__device__ __forceinline__ void attn_load_kv(rsrc_t kr, rsrc_t vr, int c, int nw, int lane, u32x4 (&kf)[G][4], u32x4 (&vf)[G][4]) {
+#pragma unroll
+  for (int gg = 0; gg < G; ++gg) {
+    const unsigned at = (unsigned)__builtin_amdgcn_readfirstlane(c + gg * nw) * (KV_GROUP * 2);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) kf[gg][x] = __builtin_amdgcn_raw_buffer_load_b128(kr, lane * 16 + x * 1024, at, KVNT ? 2 : 0);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) vf[gg][x] = __builtin_amdgcn_raw_buffer_load_b128(vr, lane * 16 + x * 1024, at, KVNT ? 2 : 0);
+  }
+}
+// The item's work from the point where its queries (qhi + qlo) and the first groups of K and V are at hand or under way (parameters as in
+// attention_mfma_body; first, hop: this split's first group and the distance to its next round; lim: limit[b]).
+template <bool KVNT, bool LIMF, int QU, int G>
+__device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLds& sm, int h, int b, int tile, int split, int r0, int nrows,
+                                                    int nheads, int nz, int tid, int nw, int first, int hop, rsrc_t kr, rsrc_t vr,
+                                                    u32x4 (&kf)[G][4], u32x4 (&vf)[G][4], const bf16x8 (&qhi)[2], const bf16x8 (&qlo)[2], int lim, bf16_t* out) {
+  constexpr int RT = 16, DH = 64;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lq = lane >> 4;
+  lim = lim < 0 ? 0 : lim;
+  int nkeys = p.causal ? lim + r0 + nrows : lim;
+  nkeys = nkeys < p.capg * 32 ? nkeys : p.capg * 32;
+  const int ngr = (nkeys + 31) >> 5;
+  const int nvis = lr < nrows ? (p.causal ? lim + r0 + lr + 1 : lim) : 0;     // keys row lr may see: nlo .. nvis - 1
+  const int nlo = LIMF ? attn_first_key(p, lim + r0 + lr) : 0;
+  float m_run = -INFINITY, l_run = 0.f;          // of query row lr over this wave's keys (the 4 lanes of a row agree)
+  f32x4 acc[4];                                  // out^T tile dt: head dimensions 16*dt + 4*lq + r, row lr
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c = first; c + wave < ngr; c += hop) {
+    // scores: sacc[gg][t][r] = key 32 (c + wave + gg nw) + 8 lq + 4 t + r against query row lr
+    f32x4 sacc[G][2];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f}, al = a;       // (two chains)
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+          const bf16x8 ka = __builtin_bit_cast(bf16x8, kf[gg][2 * t + s2]);
+          a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qhi[s2], a, 0, 0, 0);
+          al = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qlo[s2], al, 0, 0, 0);
+        }
+        a += al;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int key = 32 * (c + wave + gg * nw) + 8 * lq + 4 * t + r;
+          a[r] = (key < nvis && (!LIMF || key >= nlo)) ? a[r] : -INFINITY;
+          mx = fmaxf(mx, a[r]);
+        }
+        sacc[gg][t] = a;
+      }
+    mx = max_rows(mx);
+    const float m_new = fmaxf(m_run, mx);
+    const float alpha = (m_new == -INFINITY) ? 1.f : __expf(m_run - m_new);
+    float sum = 0.f;
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float pv = (m_new == -INFINITY) ? 0.f : __expf(sacc[gg][t][r] - m_new);
+          sacc[gg][t][r] = pv;
+          sum += pv;
+        }
+    sum = sum_rows(sum);
+    l_run = l_run * alpha + sum;
+    m_run = m_new;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) acc[dt] *= alpha;
+#pragma unroll
+    for (int gg = 0; gg < G; ++gg) {
+      const int g0 = 32 * (c + wave + gg * nw);
+      if (G > 1 && g0 >= nkeys) continue;        // (the same for the whole wave)
+      if (g0 + 32 > nkeys) {                     // values of keys past the last one: their probabilities are zero, their bits unknown
+        const int left = nkeys - g0 - 8 * lq;    // of this lane's eight
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+          for (int w = 0; w < 4; ++w) vf[gg][dt][w] = left > 2 * w + 1 ? vf[gg][dt][w] : (left > 2 * w ? vf[gg][dt][w] & 0xFFFFu : 0u);
+      }
+      const float pv[8] = {sacc[gg][0][0], sacc[gg][0][1], sacc[gg][0][2], sacc[gg][0][3], sacc[gg][1][0], sacc[gg][1][1], sacc[gg][1][2], sacc[gg][1][3]};
+      bf16x8 phi, plo;
+      split_bf16x8(pv, phi, plo);
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt) {
+        const bf16x8 va = __builtin_bit_cast(bf16x8, vf[gg][dt]);
+        acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, phi, acc[dt], 0, 0, 0);
+        acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, plo, acc[dt], 0, 0, 0);
+      }
+    }
+    if (c + hop + wave < ngr) attn_load_kv<KVNT, G>(kr, vr, c + hop + wave, nw, lane, kf, vf);
+  }
+  // the waves meet (those without keys bring zeros): wave w of the first four finishes head dimensions 16w .. 16w+15
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt) sm.o_s[wave][dt][lane] = acc[dt];
+  if (lq == 0) { sm.m_s[wave][lr] = m_run; sm.l_s[wave][lr] = l_run; }
+  __syncthreads();
+  if (wave >= 4) return;
+  float M, L;
+  f32x4 o;
+  if (QU >= 0 && ngr - first <= 1) { M = sm.m_s[0][lr]; L = sm.l_s[0][lr]; o = sm.o_s[0][wave][lane]; }         // (the first wave has all keys)
+  else if (QU <= 0 && (QU < 0 || nw == 4)) attention_merge<4>(sm, wave, lane, M, L, o);
+  else attention_merge<ATTN_WAVES>(sm, wave, lane, M, L, o);
+  const int dim = 16 * wave + 4 * lq;
+  if (p.nsplit == 1) {
+    if (lr < nrows) {
+      float inv = __builtin_amdgcn_rcpf(L);
+      inv = inv * fmaf(-L, inv, 2.f);            // (one Newton step: the quotient to fp32)
+      *(u32x2*)(out + ((size_t)b * p.R + r0 + lr) * p.d + h * DH + dim) = u32x2{cvt_pk_bf16(o[0] * inv, o[1] * inv), cvt_pk_bf16(o[2] * inv, o[3] * inv)};
+    }
+  } else {
+    const int tiles = nz / p.nsplit;
+    float* part = p.part + ((((long)b * nheads + h) * tiles + tile) * p.nsplit + split) * (RT * (DH + 2));
+    *(f32x4*)(part + lr * DH + dim) = o;
+    if (tid < RT) { part[RT * DH + tid] = M; part[RT * DH + RT + tid] = L; }
+  }
+}
 // One (head h, sequence b (in the K/V buffer: sb), z = row tile * nsplit + split) item of the attention, run by nw whole
 // waves (tid 0 .. 64 nw - 1) that share `sm`; nheads / nz: the extents the partial-result layout is indexed with.  Every
 // __syncthreads() inside is reached by all of them; a caller whose workgroup has more waves makes those arrive at as many
@@ -115,8 +237,8 @@ __device__ __forceinline__ void attention_merge(const AttnLds& sm, int dt, int l
 // not evict the weights).
 // LIMF: the sequence's length is fetched first and only groups that hold keys are fetched: one more dependent round trip
 // (many sequences: the traffic is what counts; local attention: where the keys start depends on it).
-// ARGS: p lies in the kernel's arguments.
-template <bool KVNT, bool LIMF, int QU, bool ARGS>
+// ARGS: p lies in the kernel's arguments.  AUX: cache policy of the loads of Q (16: past the L1, for queries that this very kernel has written).
+template <bool KVNT, bool LIMF, int QU, bool ARGS, int AUX = 0>
 __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP& qp, const AttnLds& sm, int h, int b, int sb, int z,
                                                     int nheads, int nz, int tid, int nw) {
   constexpr int RT = 16, DH = 64, G = QU < 0 ? 2 : 1;       // groups of keys per wave and round
@@ -140,14 +262,6 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
   const rsrc_t kr = rsrc_of((const bf16_t*)p.Kc + head_at, (unsigned)glim * (KV_GROUP * 2));
   const rsrc_t vr = rsrc_of((const bf16_t*)p.Vc + head_at, (unsigned)glim * (KV_GROUP * 2));
   u32x4 kf[G][4], vf[G][4];                      // K: [tile][half of the dimensions], V: [16 dimensions]
-#define BPD_LOAD_KV(c)                                                                          \
-  _Pragma("unroll") for (int gg = 0; gg < G; ++gg) {                                            \
-    const unsigned at_ = (unsigned)((c) + wave + gg * nw) * (KV_GROUP * 2);                     \
-    _Pragma("unroll") for (int x = 0; x < 4; ++x)                                               \
-      kf[gg][x] = __builtin_amdgcn_raw_buffer_load_b128(kr, lane * 16 + x * 1024, at_, KVNT ? 2 : 0); \
-    _Pragma("unroll") for (int x = 0; x < 4; ++x)                                               \
-      vf[gg][x] = __builtin_amdgcn_raw_buffer_load_b128(vr, lane * 16 + x * 1024, at_, KVNT ? 2 : 0); \
-  }
   // queries: row lr (zeros beyond the last), head dimensions 32s + 8*lq .. +8, scaled, as bf16 hi + lo
   bf16x8 qhi[2], qlo[2];
   int lim;
@@ -169,7 +283,7 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int i = 0; i < U; ++i) wf[j][i] = *(const u32x4*)((const char*)qp.W + ((size_t)(4 * h + j) * KSTEPS + ks0 + i) * 1024 + lane * 16);
-    BPD_LOAD_KV(first)
+    attn_load_kv<KVNT, G>(kr, vr, first + wave, nw, lane, kf, vf);
     lim = p.limit[b];
     out = (bf16_t*)p.out;
     if (ARGS) out = arg_now(out);
@@ -262,8 +376,8 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
     const unsigned off = (lr * p.d + h * DH + 8 * lq) * 4;
     u32x4 qa[2][2];
 #pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) { qa[s2][0] = buf_load16(qr, off + s2 * 128, 0); qa[s2][1] = buf_load16(qr, off + s2 * 128 + 16, 0); }
-    BPD_LOAD_KV(first)
+    for (int s2 = 0; s2 < 2; ++s2) { qa[s2][0] = __builtin_amdgcn_raw_buffer_load_b128(qr, off + s2 * 128, 0, AUX); qa[s2][1] = __builtin_amdgcn_raw_buffer_load_b128(qr, off + s2 * 128 + 16, 0, AUX); }
+    attn_load_kv<KVNT, G>(kr, vr, first + wave, nw, lane, kf, vf);
     lim = p.limit[b];
     out = (bf16_t*)p.out;
     if (ARGS) out = arg_now(out);
@@ -275,106 +389,7 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
       split_bf16x8(v, qhi[s2], qlo[s2]);
     }
   }
-  lim = lim < 0 ? 0 : lim;
-  int nkeys = p.causal ? lim + r0 + nrows : lim;
-  nkeys = nkeys < p.capg * 32 ? nkeys : p.capg * 32;
-  const int ngr = (nkeys + 31) >> 5;
-  const int nvis = lr < nrows ? (p.causal ? lim + r0 + lr + 1 : lim) : 0;     // keys row lr may see: nlo .. nvis - 1
-  const int nlo = LIMF ? attn_first_key(p, lim + r0 + lr) : 0;
-  float m_run = -INFINITY, l_run = 0.f;          // of query row lr over this wave's keys (the 4 lanes of a row agree)
-  f32x4 acc[4];                                  // out^T tile dt: head dimensions 16*dt + 4*lq + r, row lr
-#pragma unroll
-  for (int dt = 0; dt < 4; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int c = first; c + wave < ngr; c += hop) {
-    // scores: sacc[gg][t][r] = key 32 (c + wave + gg nw) + 8 lq + 4 t + r against query row lr
-    f32x4 sacc[G][2];
-    float mx = -INFINITY;
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg)
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-          const bf16x8 ka = __builtin_bit_cast(bf16x8, kf[gg][2 * t + s2]);
-          a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qhi[s2], a, 0, 0, 0);
-          a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qlo[s2], a, 0, 0, 0);
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int key = 32 * (c + wave + gg * nw) + 8 * lq + 4 * t + r;
-          a[r] = (key < nvis && (!LIMF || key >= nlo)) ? a[r] : -INFINITY;
-          mx = fmaxf(mx, a[r]);
-        }
-        sacc[gg][t] = a;
-      }
-    mx = max_rows(mx);
-    const float m_new = fmaxf(m_run, mx);
-    const float alpha = (m_new == -INFINITY) ? 1.f : __expf(m_run - m_new);
-    float sum = 0.f;
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg)
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float pv = (m_new == -INFINITY) ? 0.f : __expf(sacc[gg][t][r] - m_new);
-          sacc[gg][t][r] = pv;
-          sum += pv;
-        }
-    sum = sum_rows(sum);
-    l_run = l_run * alpha + sum;
-    m_run = m_new;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) acc[dt] *= alpha;
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg) {
-      const int g0 = 32 * (c + wave + gg * nw);
-      if (G > 1 && g0 >= nkeys) continue;        // (the same for the whole wave)
-      if (g0 + 32 > nkeys) {                     // values of keys past the last one: their probabilities are zero, their bits unknown
-        const int left = nkeys - g0 - 8 * lq;    // of this lane's eight
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-          for (int w = 0; w < 4; ++w) vf[gg][dt][w] = left > 2 * w + 1 ? vf[gg][dt][w] : (left > 2 * w ? vf[gg][dt][w] & 0xFFFFu : 0u);
-      }
-      const float pv[8] = {sacc[gg][0][0], sacc[gg][0][1], sacc[gg][0][2], sacc[gg][0][3], sacc[gg][1][0], sacc[gg][1][1], sacc[gg][1][2], sacc[gg][1][3]};
-      bf16x8 phi, plo;
-      split_bf16x8(pv, phi, plo);
-#pragma unroll
-      for (int dt = 0; dt < 4; ++dt) {
-        const bf16x8 va = __builtin_bit_cast(bf16x8, vf[gg][dt]);
-        acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, phi, acc[dt], 0, 0, 0);
-        acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, plo, acc[dt], 0, 0, 0);
-      }
-    }
-    if (c + hop + wave < ngr) BPD_LOAD_KV(c + hop)
-  }
-#undef BPD_LOAD_KV
-  // the waves meet (those without keys bring zeros): wave w of the first four finishes head dimensions 16w .. 16w+15
-#pragma unroll
-  for (int dt = 0; dt < 4; ++dt) sm.o_s[wave][dt][lane] = acc[dt];
-  if (lq == 0) { sm.m_s[wave][lr] = m_run; sm.l_s[wave][lr] = l_run; }
-  __syncthreads();
-  if (wave >= 4) return;
-  float M, L;
-  f32x4 o;
-  if (QU >= 0 && ngr - first <= 1) { M = sm.m_s[0][lr]; L = sm.l_s[0][lr]; o = sm.o_s[0][wave][lane]; }         // (the first wave has all keys)
-  else if (QU <= 0 && (QU < 0 || nw == 4)) attention_merge<4>(sm, wave, lane, M, L, o);
-  else attention_merge<ATTN_WAVES>(sm, wave, lane, M, L, o);
-  const int dim = 16 * wave + 4 * lq;
-  if (p.nsplit == 1) {
-    if (lr < nrows) {
-      float inv = __builtin_amdgcn_rcpf(L);
-      inv = inv * fmaf(-L, inv, 2.f);            // (one Newton step: the quotient to fp32)
-      *(u32x2*)(out + ((size_t)b * p.R + r0 + lr) * p.d + h * DH + dim) = u32x2{cvt_pk_bf16(o[0] * inv, o[1] * inv), cvt_pk_bf16(o[2] * inv, o[3] * inv)};
-    }
-  } else {
-    const int tiles = nz / p.nsplit;
-    float* part = p.part + ((((long)b * nheads + h) * tiles + tile) * p.nsplit + split) * (RT * (DH + 2));
-    *(f32x4*)(part + lr * DH + dim) = o;
-    if (tid < RT) { part[RT * DH + tid] = M; part[RT * DH + RT + tid] = L; }
-  }
+  attention_mfma_core<KVNT, LIMF, QU>(p, sm, h, b, tile, split, r0, nrows, nheads, nz, tid, nw, first, hop, kr, vr, kf, vf, qhi, qlo, lim, out);
 }
 // SLOTS: a step of a batch some of whose sequences may have ended (AttnP::seq); a kernel of its own, since looking the
 // sequence up is one more round trip ahead of the K/V loads.

@@ -1,0 +1,14 @@
+// How decoder blocks are dealt to the jobs of layers_kernel (bpd_layers.h), for the kernel and for the host.
+#pragma once
+
+constexpr int LK_PLACES = 32, LK_XCDS = 16, LK_JOBS = 8;
+constexpr int LK_CTL = 32, LK_FLAGS = 64, LK_AREA = 192;        // words of an XCD's area: [0] registered; members, then jobs; flags [wave][member]
+constexpr int LK_NEXT_JOB = LK_XCDS * LK_AREA, LK_WORDS = LK_NEXT_JOB + 32;
+// Slots of a job: they are dealt evenly to at most LK_JOBS of them, and a job holds at most 16 rows of four slots
+inline int layers_per_job(int slots) { return (slots + LK_JOBS - 1) / LK_JOBS; }
+inline bool layers_fit(int slots, int R) { return layers_per_job(slots) <= LK_PLACES / 8 && layers_per_job(slots) * R <= 16; }
+// Workgroups that share the self-attention of a (head, slot): one per 256 keys (a round of its four waves), as far as there are any
+inline int layers_split(int slots, long keys) {
+  const long want = (keys + 255) / 256, most = LK_PLACES / 8 / layers_per_job(slots);
+  return (int)(want < most ? want : most);
+}

@@ -208,14 +208,14 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
   }
 }
 
-// LayerNorm of one row of D columns per workgroup.  NSL > 0: x is the sum of itself, a bias and NSL raw K slices of a split
+// LayerNorm of one row of D columns per workgroup.  clear: behind layers_kernel, the words it counts in (nclear pieces of 16 bytes).  NSL > 0: x is the sum of itself, a bias and NSL raw K slices of a split
 // GEMM, in this order of slices, and is stored.  One load of everything, one barrier (each wave takes the squares about the mean of its
 // own columns, row_moments puts the waves together; against sums of squares about zero this costs 0.5 % of a sentence's decode): 1.9 us in a chain of kernels where one
 // wave per row took 4.2 us (D = 512, 80 rows) .. 5.2 us (D = 1024, 8 slices).
 constexpr int ln_row_threads(int D) { return D < 256 ? 64 : D / 4; }
 template <int D, int NSL>
 __global__ __launch_bounds__(ln_row_threads(D)) void ln_row_kernel(float* x, const float* g, const float* b, int M, float eps, bf16_t* ya, float* yf,
-                                                                   const float* part, const float* pbias) {
+                                                                   const float* part, const float* pbias, u32x4* clear, int nclear) {
   constexpr int WAVES = ln_row_threads(D) / 64;
   __shared__ float2 st[WAVES];
   const int tid = threadIdx.x;
@@ -230,6 +230,9 @@ __global__ __launch_bounds__(ln_row_threads(D)) void ln_row_kernel(float* x, con
   }
   const f32x4 gv = *(const f32x4*)(g + (in ? 4 * tid : 0)), bv = *(const f32x4*)(b + (in ? 4 * tid : 0));
   __builtin_amdgcn_sched_barrier(0);
+  if (clear && blockIdx.x == 0) {
+    for (int i = tid; i < nclear; i += WAVES * 64) clear[i] = u32x4{0, 0, 0, 0};
+  }
   if constexpr (NSL > 0) {
 #pragma unroll
     for (int i = 1; i < NSL; ++i) pv[0] += pv[i];

@@ -1,0 +1,94 @@
+"""All decoder layers as one kernel, a job of up to 16 rows per XCD (d = 512, d_ff = 2048): rows and slots of a job at their limits, long caches
+whose attention several workgroups share, groups that are not full, and sequences that end."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+from harness import TOL, LockStep, gpu_context
+
+pytestmark = pytest.mark.gpu
+
+
+def config(k, B, S, out, layers=2, **kw):
+    return wl.Config("layers", 75, 1, layers, 512, 8, 2048, 272, k, B, S, out, "bf16", 2, src_len_kind="lognormal", **kw)
+
+
+def lockstep(cfg, steps, budgets=None):
+    weights = wl.make_weights(cfg)
+    ctx = gpu_context(cfg, weights)
+    src, n = wl.make_sources(cfg)
+    budgets = np.full(cfg.batch, cfg.max_out, np.int32) if budgets is None else budgets
+    ls = LockStep(cfg, weights, ctx, src, n, budgets, sample=sorted({0, cfg.batch // 2, cfg.batch - 1}))
+    for _ in range(steps):
+        ls.step(imposed=np.full(cfg.batch, cfg.k, np.int32))
+
+
+# (k, batch): one row; 16 rows of one sequence, of two and of three with one to spare; a last job that is not full; four slots per job
+@pytest.mark.parametrize("k,B,S", [(1, 1, 1), (16, 1, 33), (16, 8, 3), (8, 16, 5), (8, 9, 40), (5, 24, 3), (4, 32, 3), (1, 27, 5), (3, 5, 140)])
+def test_rows_and_slots(k, B, S):
+    lockstep(config(k, B, S, 3 * k + 4), 3)
+
+
+# groups of fewer workgroups than places, and one that waits until its time is up
+@pytest.mark.parametrize("group,k,B", [(1, 7, 2), (5, 8, 16), (31, 10, 3), (33, 4, 9)])
+def test_groups(group, k, B, monkeypatch):
+    monkeypatch.setenv("BPD_LAYERS_GROUP", str(group))
+    lockstep(config(k, B, 5, 3 * k + 4), 3)
+
+
+@pytest.mark.parametrize("k,B", [(4, 9), (6, 13)])
+def test_ended_sequences(k, B):
+    lockstep(config(k, B, 4, 4 * k + 1), 4, np.array([1 + (5 * b) % (4 * k + 1) for b in range(B)], np.int32))
+
+
+# caches of more keys than a workgroup takes in one round: two, three and four workgroups per head, two slots per job, a window.  Both ways the logits
+# are within TOL of the oracle's (shown above and for the kernel chain elsewhere), so within twice that of each other.
+@pytest.mark.parametrize("k,B,out,steps,local", [(16, 1, 400, 20, 0), (10, 3, 700, 60, 0), (16, 8, 1100, 66, 0), (8, 16, 600, 60, 0), (9, 2, 700, 70, 256), (16, 2, 300, 9, 40)])
+def test_long_caches(k, B, out, steps, local, monkeypatch):
+    cfg = config(k, B, 35, out, layers=1, local_q=local, local_m=local)
+    weights = wl.make_weights(cfg)
+    ctx = gpu_context(cfg, weights)
+    monkeypatch.setenv("BPD_LAYERS_GROUP", "0")
+    ref = gpu_context(cfg, weights)
+    src, n = wl.make_sources(cfg)
+    rng = np.random.default_rng(k)
+    whole = torch.full((B,), k, dtype=torch.int32, device="cuda")
+    for c in (ctx, ref):
+        c.bpd_encode(src, n, np.full(B, out, np.int32))
+    for s in range(steps):
+        tok = torch.from_numpy(rng.integers(3, 272, (B, cfg.k)).astype(np.int32)).cuda()
+        for c in (ctx, ref):
+            c.bpd_set_proposals(tok)
+            if s + 1 < steps:
+                c.bpd_step(k, whole)
+    a, b = (c.bpd_debug_step_logits(k).double().cpu().numpy() for c in (ctx, ref))
+    assert np.isfinite(a).all() and np.abs(a - b).max() <= 2 * TOL["bf16"], np.abs(a - b).max()
+
+
+def test_two_streams():
+    """Contexts on streams of their own, decoding at the same time: the workgroups of both launches share the CUs."""
+    import threading
+    cfg = config(8, 8, 9, 60)
+    weights = wl.make_weights(cfg)
+    src, n = wl.make_sources(cfg)
+    budgets = np.full(8, 60, np.int32)
+    sched = np.random.default_rng(3).integers(1, 9, (60, 8)).astype(np.int32)
+    torch.cuda.synchronize()
+    out = [None, None, None]
+
+    def run(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            ctx = gpu_context(cfg, weights)
+            for _ in range(4):
+                ctx.bpd_encode(src, n, budgets)
+                ids, lens, stats = ctx.bpd_decode(8, sched)
+            out[i] = (np.asarray(ids).tolist(), np.asarray(lens).tolist(), stats.steps)
+
+    run(2)
+    threads = [threading.Thread(target=run, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert out[0] == out[2] and out[1] == out[2]
