@@ -868,12 +868,7 @@ void refresh_folded_weights(bpd_ctx* ctx) {
 }
 
 // ------------------------------------------------------------------------------- blocks of few rows (bpd_row_gemm.h)
-// The residual GEMM of K = d_ff runs as one kernel up to this K, beyond in K slices of 1024 that the next LayerNorm adds up
-// (4096 x 1024 at 10 rows: 5.5 us whole, 3.4 us in slices, and the LayerNorm kernel with them 2.0 us, which takes the LayerNorm
-// out of the next GEMM: 4.2 -> 3.05 us.  2048 x 512: 3.3 us whole, and 2.1 + 1.9 - 0.8 us in slices).
-constexpr int LEAN_K_WHOLE = 2048;
-constexpr int LEAN_PART_M = 192;        // more rows: the slices of the LDS-staged kernel (192 rows 6.8 against 7.25 us, 256 rows 8.0 against 7.3)
-constexpr int LEAN_WHOLE_M = 256;       // ... as well for K = 2048 (256 rows 4.6 against 4.3 us, 320 rows 5.6 against 5.2)
+constexpr int LEAN_WHOLE_M = 256;       // more rows: the slices of the LDS-staged kernel for K = 2048, too (256 rows 4.6 against 4.3 us, 320 rows 5.6 against 5.2)
 int lean_slices(const bpd_ctx* ctx, int M) {
   const bpd_config& c = ctx->cfg;
   if (c.d_ff > LEAN_K_WHOLE && M <= LEAN_PART_M) return c.d_ff / 1024;

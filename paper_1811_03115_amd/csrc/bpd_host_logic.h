@@ -149,6 +149,11 @@ bool lean_ok(const bpd_config& c, long M) {
   return c.dtype == BPD_BF16 && M <= LEAN_M_MAX && lean_width(c.d_model) &&
          (c.d_ff == 512 || c.d_ff == 1024 || c.d_ff == 2048 || c.d_ff == 3072 || c.d_ff == 4096);
 }
+// The residual GEMM of K = d_ff runs as one kernel up to this K, beyond in K slices of 1024 that the next LayerNorm adds up
+// (4096 x 1024 at 10 rows: 5.5 us whole, 3.4 us in slices, and the LayerNorm kernel with them 2.0 us, which takes the LayerNorm
+// out of the next GEMM: 4.2 -> 3.05 us.  2048 x 512: 3.3 us whole, and 2.1 + 1.9 - 0.8 us in slices).
+constexpr int LEAN_K_WHOLE = 2048;
+constexpr int LEAN_PART_M = 192;        // more rows: the slices of the LDS-staged kernel (192 rows 6.8 against 7.25 us, 256 rows 8.0 against 7.3)
 bool lean_encoder_ok(const bpd_config& c, long M) { return lean_ok(c, M) && (c.d_model <= 512 || M <= LEAN_ENC_WIDE_M_MAX); }
 
 // Other decoder blocks of more than 128 rows run their LayerNorm-then-GEMM pairs as one GEMM on weights with the LayerNorm
@@ -210,7 +215,10 @@ size_t build_layout(const bpd_config& c, char* base, Layout& L, std::vector<std:
   L.zeros = vec(L.n_zeros);
   L.attn_part = vec((size_t)ATTN_PART_SLOTS * 16 * (d / c.n_heads + 2));
   L.n_kpart = (size_t)KSPLIT_MAX * M * d;      // K slices of one residual update of the decoder block
-  L.kpart = vec(L.n_kpart);
+  // ... and the encoder's d_ff / 1024 slices of up to LEAN_PART_M source rows, which may be more than that
+  size_t enc_part = 0;
+  if (c.d_ff > LEAN_K_WHOLE && lean_encoder_ok(c, 1)) enc_part = F / 1024 * (B * S < (size_t)LEAN_PART_M ? B * S : (size_t)LEAN_PART_M) * d;
+  L.kpart = vec(L.n_kpart > enc_part ? L.n_kpart : enc_part);
   L.xn = a.take(M * d * as); L.attn = a.take(M * d * as); L.ffh = a.take(M * F * as);
   L.hn = a.take(M * d * as); L.H = a.take(M * k * F * as); L.O = a.take(M * k * d * as);
   L.keys = (unsigned long long*)a.take(M * k * 8);

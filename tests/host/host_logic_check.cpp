@@ -41,6 +41,9 @@ static void check_config(const bpd_config& c) {
   // distances between neighbouring regions that launches rely on
   EXPECT((char*)L.kpart - (char*)L.attn_part >= (long)((size_t)ATTN_PART_SLOTS * 16 * (d / c.n_heads + 2) * 4), "attention partials");
   EXPECT((size_t)((char*)L.xn - (char*)L.kpart) >= L.n_kpart * 4, "K slices");
+  // the encoder's slices of a long K, of as many source rows as leave any
+  const size_t sliced = std::min(B * S, (size_t)LEAN_PART_M);
+  if (c.d_ff > LEAN_K_WHOLE && lean_encoder_ok(c, (long)sliced)) EXPECT((size_t)((char*)L.xn - (char*)L.kpart) >= F / 1024 * sliced * d * 4, "the encoder's K slices, %zu rows, d=%zu F=%zu k=%zu B=%zu", sliced, d, F, k, B);
   EXPECT((size_t)((char*)L.keys_h1 - (char*)L.keys) >= M * k * 8, "keys");
   EXPECT((size_t)((char*)L.hn2 - (char*)L.keys_h1) >= 2 * M * 8, "head-1 and second-phase keys");
   EXPECT(L.n_zeros >= std::max({k * F, V, 3 * d}), "zero vector");

@@ -34,6 +34,13 @@ def test_encoder_rows(d, F, B, S):
     lockstep(cfg, 1)
 
 
+# K slices of the encoder (F > 2048) of more source rows than the decoder ever has: up to 192 rows leave some
+@pytest.mark.parametrize("d,F,B,S", [(1024, 4096, 1, 17), (1024, 4096, 4, 48), (768, 3072, 1, 70), (512, 4096, 1, 193)])
+def test_encoder_slices(d, F, B, S):
+    cfg = wl.Config("rows", 76, 2, 1, d, d // 64, F, 272, 1, B, S, 8, "bf16", 2)
+    lockstep(cfg, 1)
+
+
 # lengths of the caches on both sides of 32, 128 and 256 keys (a group, four waves, eight waves), sources likewise
 @pytest.mark.parametrize("k,S,out", [(1, 1, 34), (7, 31, 40), (5, 33, 135), (16, 129, 150), (13, 200, 270)])
 def test_key_groups(k, S, out):
