@@ -66,7 +66,9 @@ struct bpd_ctx {
   int Bs = 0; const int* seq = nullptr; const int* live = nullptr;
   int live1 = -1, live2 = -1;            // sequences that had not ended after the last step and after the one before (-1: not known)
   int budget_min = 0;                    // smallest length budget of the batch as far as the host knows
-  int layers_group = LK_PLACES;        // workgroups per XCD that layers_kernel waits for (for tests, BPD_LAYERS_GROUP at creation: fewer; 33: waits in vain; 0: the kernel is not used)
+  // workgroups per XCD that layers_kernel and wide_layers_kernel wait for (for tests, BPD_LAYERS_GROUP at creation: fewer; 33: they wait in vain; 64 n
+  // added: the second one is left to n XCDs; 0: neither is used)
+  int layers_group = LK_PLACES;
   bool layers_ran = false;             // layers_kernel has been launched and the LayerNorm behind it has not (layernorm() has it clear layers_sync)
   bool weights_exceed_llc = false;     // decoder-side weights read per step > 192 MB (the Infinity Cache holds 256 MB)
   const int* cur_imposed = nullptr; int cur_imposed_stride = 0, cur_imposed_step = 0;   // of the step being run
@@ -743,8 +745,12 @@ int stack_check(bpd_ctx* ctx) {
 }
 
 // ------------------------------------------------------------------------------- all layers in one kernel (bpd_layers.h)
-bool layers_usable(const bpd_ctx* ctx, int slots, int R) {
-  return ctx->lay.layers_sync && ctx->layers_group > 0 && ctx->num_cus >= LK_JOBS * LK_PLACES && layers_fit(slots, R);
+enum { LAYERS_CHAIN, LAYERS_JOBS, LAYERS_WIDE };         // kernels one by one, layers_kernel, wide_layers_kernel
+int layers_way(const bpd_ctx* ctx, int slots, int R) {
+  const bpd_config& c = ctx->cfg;
+  if (!ctx->lay.layers_sync || ctx->layers_group == 0 || ctx->num_cus < LK_JOBS * LK_PLACES) return LAYERS_CHAIN;
+  if (layers_shape(c)) return layers_fit(slots, R) ? LAYERS_JOBS : LAYERS_CHAIN;
+  return wide_layers_fit(slots, R, attention_keys(ctx, c.max_out_len + c.k_max + 1, R, 1), c.max_src_len) ? LAYERS_WIDE : LAYERS_CHAIN;
 }
 int layers_split_of(const bpd_ctx* ctx, int slots, int R) {
   const bpd_config& c = ctx->cfg;
@@ -758,7 +764,7 @@ void launch_layers_kernel(const bpd_ctx* ctx, const LayersP& p) {
   if (!attr_set) { (void)hipFuncSetAttribute((const void*)layers_kernel<2048, KVNT>, hipFuncAttributeMaxDynamicSharedMemorySize, LkLds<2048>::BYTES); attr_set = true; }
   hipLaunchKernelGGL((layers_kernel<2048, KVNT>), dim3(LK_JOBS * LK_PLACES), dim3(512), LkLds<2048>::BYTES, ctx->stream, p);
 }
-void launch_layers(bpd_ctx* ctx, int R) {
+void launch_layers(bpd_ctx* ctx, int R, int way) {
   const bpd_config& c = ctx->cfg;
   Layout& L = ctx->lay;
   const size_t d = c.d_model, slots = (size_t)c.max_out_len + c.k_max + 1;
@@ -776,11 +782,18 @@ void launch_layers(bpd_ctx* ctx, int R) {
   p.self_groups = (int)((slots + 31) / 32); p.src_groups = (c.max_src_len + 31) / 32;
   p.seq = ctx->seq; p.base = ctx->seq ? L.slot_L : L.L; p.src_len = ctx->seq ? L.slot_src : L.src_len;
   p.eps = c.ln_eps; p.scale = 1.0f / sqrtf(64.f); p.local_q = ctx->local_q; p.local_m = ctx->local_m;
-  p.group = ctx->layers_group;
+  p.group = way == LAYERS_WIDE ? ctx->layers_group : ctx->layers_group & 63;
   p.sync = L.layers_sync; p.error = L.stats + 31;
+  ctx->layers_ran = true;
+  if (way == LAYERS_WIDE) {
+    p.jobs = p.per_job = p.split = 0;
+    static bool attr_set = false;
+    if (!attr_set) { (void)hipFuncSetAttribute((const void*)wide_layers_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, WkLds::BYTES); attr_set = true; }
+    hipLaunchKernelGGL(wide_layers_kernel, dim3(WK_XCDS * LK_PLACES), dim3(512), WkLds::BYTES, ctx->stream, p);
+    return;
+  }
   const bool nt = (size_t)2 * c.n_dec_layers * ctx->Bs * slots * d * 2 > ((size_t)128 << 20);       // (as in attention())
   if (nt) launch_layers_kernel<true>(ctx, p); else launch_layers_kernel<false>(ctx, p);
-  ctx->layers_ran = true;
 }
 
 // ------------------------------------------------------------------------------- profiling
@@ -994,9 +1007,10 @@ int forward(bpd_ctx* ctx, int R, int k, int zero_input, float* logits) {
     xs = have_x && !sp;
     if (!have_x) embed(ctx, L.P, c.k_max, base, R, M, L.pos_tgt, L.x, zero_input, L.keys, (int)nk, seq);
     const bool stack = M <= 16 && (lean || sp) && stack_usable(ctx, B, R);
-    const bool one = !stack && lean && layers_usable(ctx, B, R);
+    const int way = stack || !lean ? LAYERS_CHAIN : layers_way(ctx, B, R);
+    const bool one = way != LAYERS_CHAIN;
     if (stack) launch_stack(ctx, R);
-    else if (one) launch_layers(ctx, R);
+    else if (one) launch_layers(ctx, R, way);
     for (int l = 0; l < (stack || one ? 0 : c.n_dec_layers); ++l) {
       DecL& w = L.dec[l];
       char* Kl = (char*)L.selfK + self_layer * l;
@@ -1463,7 +1477,7 @@ int bpd_create(const bpd_config* cfg, void* workspace, size_t workspace_bytes, v
     }
     (void)hipGetLastError();
   }
-  if (const char* env = getenv("BPD_LAYERS_GROUP")) ctx->layers_group = std::min(LK_PLACES + 1, std::max(0, atoi(env)));
+  if (const char* env = getenv("BPD_LAYERS_GROUP")) ctx->layers_group = std::max(0, atoi(env));
   if (ctx->lay.layers_sync) (void)hipMemsetAsync(ctx->lay.layers_sync, 0, (size_t)LK_WORDS * 4, ctx->stream);
   (void)hipMemsetAsync(ctx->lay.zeros, 0, ctx->lay.n_zeros * 4, ctx->stream);
   (void)hipMemsetAsync(ctx->lay.step_counter, 0, 4, ctx->stream);
@@ -1761,7 +1775,7 @@ int bpd_step_static(bpd_ctx* ctx, int k, const int32_t* imposed_accept, int32_t*
     const size_t wgs = (size_t)c.n_heads * ctx->B * ((k + 15) / 16);
     if (ns > 1) attn_b = std::max(attn_b, up(ns * wgs * 16 * (d / c.n_heads + 2) * 4));
   }
-  if (layers_usable(ctx, ctx->B, k) && layers_split_of(ctx, ctx->B, k) > 1) attn_b = std::max(attn_b, up((size_t)layers_split_of(ctx, ctx->B, k) * c.n_heads * ctx->B * 16 * 66 * 4));
+  if (layers_way(ctx, ctx->B, k) == LAYERS_JOBS && layers_split_of(ctx, ctx->B, k) > 1) attn_b = std::max(attn_b, up((size_t)layers_split_of(ctx, ctx->B, k) * c.n_heads * ctx->B * 16 * 66 * 4));
   size_t slices = 1;
   if (lean_ok(c, (int)M)) slices = lean_slices(ctx, (int)M);
   else if (c.dtype == BPD_BF16 && M > 16)
@@ -1953,8 +1967,8 @@ int bpd_decode(bpd_ctx* ctx, int k, const int32_t* schedule, int max_steps, int3
       use_slots(ctx, B);
       const int cap = ctx->cfg.max_out_len + ctx->cfg.k_max + 1;
       const bool few = attention_keys(ctx, cap, k, 1) <= 128;
-      const int nsplit = layers_usable(ctx, B, k) ? layers_split_of(ctx, B, k) : attention_nsplit(ctx, cap, B, k, 1);
-      const int rc = run_planned(ctx, PLAN_STEP, {B, k, nsplit, few, ctx->top_n, ctx->local_q, ctx->local_m, ctx->distance_eps, ctx->min_block},
+      const int way = layers_way(ctx, B, k), nsplit = way == LAYERS_JOBS ? layers_split_of(ctx, B, k) : attention_nsplit(ctx, cap, B, k, 1);
+      const int rc = run_planned(ctx, PLAN_STEP, {B, k, nsplit * 4 + way, few, ctx->top_n, ctx->local_q, ctx->local_m, ctx->distance_eps, ctx->min_block},
                                  [&]() -> int {
                                    const int ready = ctx->x_ready_k;
                                    const int64_t steps = ctx->steps;

@@ -110,8 +110,9 @@ __device__ __forceinline__ void attn_load_kv(rsrc_t kr, rsrc_t vr, int c, int nw
   }
 }
 // The item's work from the point where its queries (qhi + qlo) and the first groups of K and V are at hand or under way (parameters as in
-// attention_mfma_body; first, hop: this split's first group and the distance to its next round; lim: limit[b]).
-template <bool KVNT, bool LIMF, int QU, int G>
+// attention_mfma_body; first, hop: this split's first group and the distance to its next round; lim: limit[b]).  THROUGH: results are written through
+// the L2.
+template <bool KVNT, bool LIMF, int QU, int G, bool THROUGH = false>
 __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLds& sm, int h, int b, int tile, int split, int r0, int nrows,
                                                     int nheads, int nz, int tid, int nw, int first, int hop, rsrc_t kr, rsrc_t vr,
                                                     u32x4 (&kf)[G][4], u32x4 (&vf)[G][4], const bf16x8 (&qhi)[2], const bf16x8 (&qlo)[2], int lim, bf16_t* out) {
@@ -210,7 +211,10 @@ __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLd
     if (lr < nrows) {
       float inv = __builtin_amdgcn_rcpf(L);
       inv = inv * fmaf(-L, inv, 2.f);            // (one Newton step: the quotient to fp32)
-      *(u32x2*)(out + ((size_t)b * p.R + r0 + lr) * p.d + h * DH + dim) = u32x2{cvt_pk_bf16(o[0] * inv, o[1] * inv), cvt_pk_bf16(o[2] * inv, o[3] * inv)};
+      const u32x2 w = u32x2{cvt_pk_bf16(o[0] * inv, o[1] * inv), cvt_pk_bf16(o[2] * inv, o[3] * inv)};
+      bf16_t* to = out + ((size_t)b * p.R + r0 + lr) * p.d + h * DH + dim;
+      if constexpr (THROUGH) asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(to), "v"(w) : "memory");      // (to memory, for other XCDs)
+      else *(u32x2*)to = w;
     }
   } else {
     const int tiles = nz / p.nsplit;

@@ -164,8 +164,9 @@ bool fold_kept(const bpd_config& c) {
   return c.dtype == BPD_BF16 && rows > LDSX_LN_M_MAX && !lean_ok(c, rows) && c.d_model % 64 == 0 && c.d_model <= 1024;
 }
 
-// All decoder layers as one kernel (bpd_layers.h): the shape it is built for
+// All decoder layers as one kernel: the shapes that those of bpd_layers.h and bpd_wide_layers.h are built for
 bool layers_shape(const bpd_config& c) { return c.dtype == BPD_BF16 && c.d_model == 512 && c.n_heads == 8 && c.d_ff == 2048; }
+bool wide_layers_shape(const bpd_config& c) { return c.dtype == BPD_BF16 && c.d_model == 1024 && c.n_heads == 16 && c.d_ff == 4096; }
 
 // Shapes the decoder stack kernel is built for (what a step additionally needs is checked per launch)
 bool stack_shape_ok(const bpd_config& c) {
@@ -237,7 +238,7 @@ size_t build_layout(const bpd_config& c, char* base, Layout& L, std::vector<std:
   L.sched = ints(B * (size_t)c.max_out_len);
   L.dyn = a.take(64); L.tick = ints(B); L.imp_next = ints(B); L.steps_done = ints(B); L.fin_step = ints(B); L.slot_seq = ints(B); L.slot_L = ints(B); L.slot_src = ints(B); L.slot_row = ints(B); L.n_live = ints(1);
   L.stats = (long long*)a.take(32 * 8);
-  L.layers_sync = layers_shape(c) ? (unsigned*)a.take((size_t)LK_WORDS * 4) : nullptr;
+  L.layers_sync = layers_shape(c) || wide_layers_shape(c) ? (unsigned*)a.take((size_t)LK_WORDS * 4) : nullptr;
   L.xcc_map = (unsigned*)a.take(XCC_MAP_MAX * 4);
   L.stack_err = (unsigned*)a.take(256);
   if (stack_shape_ok(c)) {

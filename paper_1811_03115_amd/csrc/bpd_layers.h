@@ -117,6 +117,7 @@ __device__ __forceinline__ void lk_multiply(const u32x4 (&a)[N][U], const bf16_t
     const bf16x8 b = __builtin_bit_cast(bf16x8, *(const u32x4*)(row + i * 32));
 #pragma unroll
     for (int t = 0; t < N; ++t) acc[t][i % CH] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[t][i]), b, acc[t][i % CH], 0, 0, 0);
+    if (U > 16 && i % 8 == 7) __builtin_amdgcn_sched_barrier(0);       // (reads of eight steps at most ahead: no registers for more)
   }
 #pragma unroll
   for (int t = 0; t < N; ++t) {
@@ -213,7 +214,8 @@ __device__ __forceinline__ void lk_copy(const bf16_t* src, int rows, bf16_t* xs,
   const rsrc_t r = rsrc_of(src, (unsigned)rows * K * 2);
   if (rows <= 8) lk_copy_rows<K, 2>(r, rows, xs, hw, lane);
   else if (rows <= 12) lk_copy_rows<K, 3>(r, rows, xs, hw, lane);
-  else lk_copy_rows<K, 4>(r, rows, xs, hw, lane);
+  else if constexpr (K <= 2048) lk_copy_rows<K, 4>(r, rows, xs, hw, lane);
+  else { lk_copy_rows<K, 2>(r, rows, xs, hw, lane); lk_copy_rows<K, 2>(r, rows, xs, hw + 8, lane); }         // (registers)
 }
 // Rows of the attention left by `split` workgroups per (head, slot) (attention_mfma_core) put together, into LDS like lk_copy<512>
 __device__ __forceinline__ void lk_merge(const float* part, int split, int slot0, int R, int rows, bf16_t* xs, int hw, int lane) {

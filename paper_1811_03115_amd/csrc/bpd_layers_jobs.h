@@ -12,3 +12,6 @@ inline int layers_split(int slots, long keys) {
   const long want = (keys + 255) / 256, most = LK_PLACES / 8 / layers_per_job(slots);
   return (int)(want < most ? want : most);
 }
+// ... and of wide_layers_kernel: one block of at most 16 rows of four slots, caches that a workgroup walks in four rounds
+constexpr long WIDE_LAYERS_KEYS = 1024;
+inline bool wide_layers_fit(int slots, int R, long keys, long src) { return slots <= 4 && slots * R <= 16 && keys <= WIDE_LAYERS_KEYS && src <= WIDE_LAYERS_KEYS; }

@@ -1,5 +1,5 @@
-"""All decoder layers as one kernel, a job of up to 16 rows per XCD (d = 512, d_ff = 2048): rows and slots of a job at their limits, long caches
-whose attention several workgroups share, groups that are not full, and sequences that end."""
+"""All decoder layers as one kernel: a job of up to 16 rows per XCD (d = 512, d_ff = 2048), or one block of up to 16 rows on the whole chip (d = 1024, d_ff =
+4096).  Rows and slots at their limits, long caches, whose attention several workgroups may share, groups that are not full, and sequences that end."""
 import numpy as np
 import pytest
 import torch
@@ -10,8 +10,8 @@ from harness import TOL, LockStep, gpu_context
 pytestmark = pytest.mark.gpu
 
 
-def config(k, B, S, out, layers=2, **kw):
-    return wl.Config("layers", 75, 1, layers, 512, 8, 2048, 272, k, B, S, out, "bf16", 2, src_len_kind="lognormal", **kw)
+def config(k, B, S, out, layers=2, d=512, **kw):
+    return wl.Config("layers", 75, 1, layers, d, d // 64, 4 * d, 272, k, B, S, out, "bf16", 2, src_len_kind="lognormal", **kw)
 
 
 def lockstep(cfg, steps, budgets=None):
@@ -30,23 +30,31 @@ def test_rows_and_slots(k, B, S):
     lockstep(config(k, B, S, 3 * k + 4), 3)
 
 
-# groups of fewer workgroups than places, and one that waits until its time is up
-@pytest.mark.parametrize("group,k,B", [(1, 7, 2), (5, 8, 16), (31, 10, 3), (33, 4, 9)])
-def test_groups(group, k, B, monkeypatch):
+# one row, rows of one wave, of two and of three of a helper's rounds; two to four slots, which the attentions share places for from three on
+@pytest.mark.parametrize("k,B,S", [(1, 1, 1), (4, 1, 33), (10, 1, 3), (16, 1, 140), (8, 2, 5), (5, 3, 40), (4, 4, 3), (1, 4, 70)])
+def test_wide_rows_and_slots(k, B, S):
+    lockstep(config(k, B, S, 3 * k + 4, d=1024), 3)
+
+
+# groups of fewer workgroups than places, and one that waits until its time is up; d = 1024: fewer XCDs, too
+@pytest.mark.parametrize("group,k,B,d", [(1, 7, 2, 512), (5, 8, 16, 512), (31, 10, 3, 512), (33, 4, 9, 512),
+                                         (5, 10, 1, 1024), (31, 4, 4, 1024), (33, 7, 2, 1024), (32 + 64 * 3, 5, 3, 1024), (3 + 64, 3, 1, 1024)])
+def test_groups(group, k, B, d, monkeypatch):
     monkeypatch.setenv("BPD_LAYERS_GROUP", str(group))
-    lockstep(config(k, B, 5, 3 * k + 4), 3)
+    lockstep(config(k, B, 5, 3 * k + 4, d=d), 3)
 
 
-@pytest.mark.parametrize("k,B", [(4, 9), (6, 13)])
-def test_ended_sequences(k, B):
-    lockstep(config(k, B, 4, 4 * k + 1), 4, np.array([1 + (5 * b) % (4 * k + 1) for b in range(B)], np.int32))
+@pytest.mark.parametrize("k,B,d", [(4, 9, 512), (6, 13, 512), (4, 4, 1024)])
+def test_ended_sequences(k, B, d):
+    lockstep(config(k, B, 4, 4 * k + 1, d=d), 4, np.array([1 + (5 * b) % (4 * k + 1) for b in range(B)], np.int32))
 
 
 # caches of more keys than a workgroup takes in one round: two, three and four workgroups per head, two slots per job, a window.  Both ways the logits
 # are within TOL of the oracle's (shown above and for the kernel chain elsewhere), so within twice that of each other.
-@pytest.mark.parametrize("k,B,out,steps,local", [(16, 1, 400, 20, 0), (10, 3, 700, 60, 0), (16, 8, 1100, 66, 0), (8, 16, 600, 60, 0), (9, 2, 700, 70, 256), (16, 2, 300, 9, 40)])
-def test_long_caches(k, B, out, steps, local, monkeypatch):
-    cfg = config(k, B, 35, out, layers=1, local_q=local, local_m=local)
+@pytest.mark.parametrize("k,B,out,steps,local,d", [(16, 1, 400, 20, 0, 512), (10, 3, 700, 60, 0, 512), (16, 8, 1100, 66, 0, 512), (8, 16, 600, 60, 0, 512), (9, 2, 700, 70, 256, 512),
+                                                   (16, 2, 300, 9, 40, 512), (16, 1, 900, 50, 0, 1024), (8, 2, 1100, 125, 0, 1024), (10, 1, 300, 25, 64, 1024)])
+def test_long_caches(k, B, out, steps, local, d, monkeypatch):
+    cfg = config(k, B, 35, out, layers=1, d=d, local_q=local, local_m=local)
     weights = wl.make_weights(cfg)
     ctx = gpu_context(cfg, weights)
     monkeypatch.setenv("BPD_LAYERS_GROUP", "0")
@@ -66,14 +74,15 @@ def test_long_caches(k, B, out, steps, local, monkeypatch):
     assert np.isfinite(a).all() and np.abs(a - b).max() <= 2 * TOL["bf16"], np.abs(a - b).max()
 
 
-def test_two_streams():
+@pytest.mark.parametrize("k,B,d", [(8, 8, 512), (8, 2, 1024)])
+def test_two_streams(k, B, d):
     """Contexts on streams of their own, decoding at the same time: the workgroups of both launches share the CUs."""
     import threading
-    cfg = config(8, 8, 9, 60)
+    cfg = config(k, B, 9, 60, d=d)
     weights = wl.make_weights(cfg)
     src, n = wl.make_sources(cfg)
-    budgets = np.full(8, 60, np.int32)
-    sched = np.random.default_rng(3).integers(1, 9, (60, 8)).astype(np.int32)
+    budgets = np.full(B, 60, np.int32)
+    sched = np.random.default_rng(3).integers(1, k + 1, (60, B)).astype(np.int32)
     torch.cuda.synchronize()
     out = [None, None, None]
 
@@ -82,7 +91,7 @@ def test_two_streams():
             ctx = gpu_context(cfg, weights)
             for _ in range(4):
                 ctx.bpd_encode(src, n, budgets)
-                ids, lens, stats = ctx.bpd_decode(8, sched)
+                ids, lens, stats = ctx.bpd_decode(k, sched)
             out[i] = (np.asarray(ids).tolist(), np.asarray(lens).tolist(), stats.steps)
 
     run(2)
