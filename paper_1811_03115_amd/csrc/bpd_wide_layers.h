@@ -4,7 +4,8 @@
 // A layer of this shape has 29 MB of weights, more than one XCD streams in the time that the chain of operators takes (25 us at 1.2 TB/s), so all
 // XCDs work on one block: 256 members, one per CU, hold a layer's weights in their registers, fetched while they have no part in
 // an operator, and hand the block over between XCDs: results are written through to memory (sc1) and read past the L1; when they are
-// acknowledged a member raises a flag on its XCD, the XCD's first member gathers these and raises a flag on every XCD.
+// acknowledged a member raises a flag on its XCD, the XCD's first member (behind the second FFN layer, when that one's compute waves fetch weights, its
+// last: 0.8 us sooner) gathers these and raises a flag on every XCD.  An attention of few heads per XCD does without the gathering.
 // (Grid-wide hand-overs of a 40 KB block, a chain with nothing else: 3.0 us with atomic counters per XCD, 5.0 us with one flag per workgroup that all
 // poll, 2.7 us this way; one kernel per operator 4.2 us.)
 //
@@ -18,7 +19,8 @@
 // they go and hand everything over through memory.
 #pragma once
 
-constexpr int WK_XCDS = 8, WK_CENSUS = 32, WK_GLOBAL = 64, WK_LOCAL = 96, WK_AREA = 224;      // words of an XCD's area: [0] registered; members of each XCD; its operators done; flags [wave][member]
+constexpr int WK_HOLD = 40, WK_GAP = 1;           // pauses of the compute waves, as LK_HOLD and LK_GAP (six layers of 10 rows: hold 12: 151 us, 24: 150, 40: 147, 64: 149, 90: 150)
+constexpr int WK_XCDS = 8, WK_CENSUS = 32, WK_GLOBAL = 64, WK_LOCAL = 96, WK_HEADS = 224, WK_AREA = 480;      // words of an XCD's area: [0] registered; members of each XCD; its operators done; flags [wave][member]; heads [XCD] [slot][head], a line each XCD
 static_assert(WK_XCDS * WK_AREA <= LK_WORDS, "both kernels count in the same words");
 
 __device__ __forceinline__ void wk_store4(unsigned* p, unsigned v) { asm volatile("global_store_dword %0, %1, off sc1" ::"v"(p), "v"(v) : "memory"); }
@@ -108,27 +110,32 @@ struct WkHelper {
   bool broken = false;
 
   __device__ __forceinline__ unsigned* area() const { return lk_args().sync + j.xcd * WK_AREA; }
-  // every XCD has done operator `target`
-  __device__ __forceinline__ void wait_all(unsigned target) {
+  // One or two slots: the members of a head tell all XCDs themselves (0.8 us until they see it, 1.25 through the first member; with eight heads
+  // per XCD, whose flags lie in one line, 1.8)
+  __device__ __forceinline__ bool heads_tell() const { return j.full && j.slots <= 2; }
+  // Operator `target` is done: a product, or an attention of n heads
+  __device__ __forceinline__ void wait(unsigned target, int n = 0) {
     if (broken || target == 0) return;
-    const unsigned* g = area() + WK_GLOBAL;
     const int lane = lk_lane();
+    const bool heads = n > 0 && heads_tell();
+    const unsigned* g = area() + (heads ? WK_HEADS + (lane >> 3) * 32 + (lane & 7) : WK_GLOBAL + (lane & 7));
+    const bool of = heads ? (lane & 7) * 8 < n : (j.xcds >> (lane & 7) & 1);
 #pragma unroll 1
     for (int s = 0; s < LK_SPINS; ++s) {
-      const unsigned v = lk_load(g + (lane & 7));
-      if (__all(v >= target || !(j.xcds >> (lane & 7) & 1))) return;
+      const unsigned v = lk_load(g);
+      if (__all(!of || v >= target)) return;
     }
     broken = true;
     if (lane == 0) *lk_args().error = 1;
   }
-  // This wave's part of the operator is in memory; the XCD's first member passes it on when all members' parts are: those of waves < NF of members from ..
+  // This wave's part of the operator is in memory; a member of the XCD passes it on when all members' parts are: those of waves < NF of members from ..
   // from + count - 1 (not full: of all waves of all)
   template <int NF>
-  __device__ __forceinline__ void done(bool mine, int from, int count, bool pass_on = true) {
+  __device__ __forceinline__ void done(bool mine, int from, int count, bool pass_on, int passer = 0) {
     const int lane = lk_lane();
     unsigned* flags = area() + WK_LOCAL;
     if (!j.full || (mine && hw < NF)) lk_raise(flags + hw * 32 + j.rank, op, lane);
-    if (hw != 3 || j.rank != 0 || !(pass_on || !j.full)) return;
+    if (hw != 3 || j.rank != (j.full ? passer : 0) || !(pass_on || !j.full)) return;
     if (j.full) lk_wait<NF>(flags, op, from, count, lane, broken, lk_args().error);
     else lk_wait<4>(flags, op, 0, j.here, lane, broken, lk_args().error);
     if (lane < WK_XCDS) wk_store4(lk_args().sync + lane * WK_AREA + WK_GLOBAL + j.xcd, op);
@@ -146,7 +153,7 @@ struct WkHelper {
   }
 
   template <int OP, int K, bool LN, bool BIAS>
-  __device__ __forceinline__ void product(int l, const float* LayersP::*lnp, const float* LayersP::*biasp, int from, int count) {
+  __device__ __forceinline__ void product(int l, const float* LayersP::*lnp, const float* LayersP::*biasp, int from, int count, int heads = 0) {
     const LayersP& p = lk_args();
     const int lane = lk_lane(), lr = lane & 15, lq = lane >> 4;
     ++op;
@@ -161,7 +168,7 @@ struct WkHelper {
       f32x4 g[4], b[4];
       if (!staged) {
         if constexpr (LN) load_norm((const float*)((const char*)(p.*lnp) + l * p.stride), g, b, lane);
-        wait_all(op - 1);
+        wait(op - 1, heads);
       }
       // (behind the wait: another member wrote the tile, O's, CO's or DOWN's)
       if constexpr (OP == WK_O || OP == WK_CO || OP == WK_DOWN) if (hw == 0) res = __builtin_bit_cast(f32x4, lk_load16(rsrc_of(p.x, (unsigned)j.rows * D * 4), (lr * D + n) * 4));
@@ -207,7 +214,7 @@ struct WkHelper {
         wk_store16(p.x + (size_t)lr * D + n, v);
       }
     }
-    done<1>(staged, from, count, OP != WK_QKV);
+    done<1>(staged, from, count, OP != WK_QKV, OP == WK_DOWN ? LK_PLACES - 1 : 0);
   }
 
   __device__ __forceinline__ static AttnP attn_args(bool self) {
@@ -243,7 +250,7 @@ struct WkHelper {
 #pragma unroll
       for (int g = 0; g < G; ++g) asm volatile("" ::"v"(t[g]));
     } else {
-      wait_all(op - 1);
+      wait(op - 1);
     }
     if (s < 0) { lk_barrier(); return; }         // (as the attention's own)
     const unsigned off = lr * (4 * D) + (h * 64 + 8 * lq) * 2;
@@ -258,6 +265,14 @@ struct WkHelper {
     __builtin_amdgcn_sched_barrier(0);
     attention_mfma_core<false, true, G == 2 ? -1 : 0, G, true>(a, sm, h, slot, 0, 0, 0, p.R, H, 1, hw * 64 + lane, 4, first, 4 * G, kr, vr, kf, vf, qhi, qlo, lim, out);
   }
+  __device__ __forceinline__ void heads_done(int which, bool mine) {
+    if (!heads_tell()) { done<4>(mine, 24 + (which == WK_CROSS ? j.cross_first() : 0), 2 * j.slots, true); return; }
+    if (!mine) return;
+    lk_stores_done();
+    lk_barrier();
+    const int lane = lk_lane(), item = j.item(which, j.place);
+    if (hw == 0 && lane < WK_XCDS) wk_store4(lk_args().sync + lane * WK_AREA + WK_HEADS + j.xcd * 32 + (item >> 4) * 2 + (item & 1), op);
+  }
   __device__ __forceinline__ void self_attention(int l) {
     ++op;
     const bool few = lk_args().few;
@@ -269,7 +284,7 @@ struct WkHelper {
       if (few) self_item<1>(l, item, !mine); else self_item<2>(l, item, !mine);
       mine = true;
     }
-    done<4>(mine, 24, 2 * j.slots);
+    heads_done(WK_SELF, mine);
   }
   __device__ __forceinline__ void cross_attention(int l) {
     const LayersP& p = lk_args();
@@ -289,7 +304,7 @@ struct WkHelper {
       load_norm((const float*)((const char*)p.ln2 + l * p.stride), g, b, lane);
       attn_load_kv<false, 1>(kr, vr, hw, 4, lane, kf, vf);
       const int lim = lk_const(p.src_len, slot);
-      if (!mine) wait_all(op - 1);
+      if (!mine) wait(op - 1);
       else lk_barrier();                         // the results of the item before are out of LDS
       mine = true;
       wk_norm(p.x + (size_t)slot * p.R * D, p.R, g, b, p.eps, xs, hw, lane);
@@ -316,7 +331,7 @@ struct WkHelper {
       if (s < 0) { lk_barrier(); continue; }     // (as the attention's own)
       attention_mfma_core<false, false, 0, 1, true>(a, sm, h, slot, 0, 0, 0, p.R, H, 1, hw * 64 + lane, 4, 0, 4, kr, vr, kf, vf, qhi, qlo, lim, p.attn);
     }
-    done<4>(mine, 24 + j.cross_first(), 2 * j.slots);
+    heads_done(WK_CROSS, mine);
   }
 
   __device__ __forceinline__ void run() {
@@ -331,9 +346,9 @@ struct WkHelper {
     for (int l = 0; l < layers; ++l) {
       product<WK_QKV, D, true, false>(l, &LayersP::ln1, nullptr, 8, 24);
       self_attention(l);
-      product<WK_O, D, false, false>(l, nullptr, nullptr, 8, 8);
+      product<WK_O, D, false, false>(l, nullptr, nullptr, 8, 8, 16 * j.slots);
       cross_attention(l);
-      product<WK_CO, D, false, false>(l, nullptr, nullptr, 16, 8);
+      product<WK_CO, D, false, false>(l, nullptr, nullptr, 16, 8, 16 * j.slots);
       product<WK_UP, D, true, true>(l, &LayersP::ln3, &LayersP::b1, 0, 32);
       product<WK_DOWN, F, false, true>(l, nullptr, &LayersP::b2, 0, 8);
     }
@@ -377,10 +392,10 @@ struct WkCompute {
       const int next = l + 1 < layers ? l + 1 : l;                   // (past the last layer: once more, read by nobody)
       product<WK_QKV>(aq, &LayersP::wqkv, l);
       if (qkv && !self) {
-        __builtin_amdgcn_s_sleep(LK_HOLD);       // (the operator's own results first)
-        if (cross) load<LK_GAP>(ax, &LayersP::cq, l, (j.item(WK_CROSS, j.place) & 15) * 4);
-        if (co) load<LK_GAP>(one(), &LayersP::co, l, WkMember::tile(WK_CO, j.place));
-        if (!o) load<LK_GAP>(aq, &LayersP::wqkv, next, WkMember::tile(WK_QKV, j.place));
+        __builtin_amdgcn_s_sleep(WK_HOLD);       // (the operator's own results first)
+        if (cross) load<WK_GAP>(ax, &LayersP::cq, l, (j.item(WK_CROSS, j.place) & 15) * 4);
+        if (co) load<WK_GAP>(one(), &LayersP::co, l, WkMember::tile(WK_CO, j.place));
+        if (!o) load<WK_GAP>(aq, &LayersP::wqkv, next, WkMember::tile(WK_QKV, j.place));
       }
 #pragma unroll 1
       for (int place = j.place, mine = 0; place < 256; place += j.members) {
@@ -389,12 +404,13 @@ struct WkCompute {
         mine = 1;
         lk_barrier();
       }
+      if (self && j.slots <= 2) lk_barrier();      // (heads_done)
       product<WK_O>(one(), &LayersP::wo, l);
       if (o || self) {
-        __builtin_amdgcn_s_sleep(LK_HOLD);
+        __builtin_amdgcn_s_sleep(WK_HOLD);
         if (self && cross) load(ax, &LayersP::cq, l, (j.item(WK_CROSS, j.place) & 15) * 4);
-        load<LK_GAP>(aq, &LayersP::wqkv, next, WkMember::tile(WK_QKV, j.place));
-        if (o) load<LK_GAP>(one(), &LayersP::wo, next, WkMember::tile(WK_O, j.place));
+        load<WK_GAP>(aq, &LayersP::wqkv, next, WkMember::tile(WK_QKV, j.place));
+        if (o) load<WK_GAP>(one(), &LayersP::wo, next, WkMember::tile(WK_O, j.place));
       }
 #pragma unroll 1
       for (int place = j.place, mine = 0; place < 256; place += j.members) {
@@ -409,14 +425,15 @@ struct WkCompute {
         lk_barrier();
         lk_barrier();
       }
+      if (cross && j.slots <= 2) lk_barrier();
       product<WK_CO>(one(), &LayersP::co, l);
       product<WK_UP>(a1, &LayersP::w1, l);
-      if (qkv) { __builtin_amdgcn_s_sleep(LK_HOLD); load<LK_GAP>(a1, &LayersP::w1, next, j.place); }
+      if (qkv) { __builtin_amdgcn_s_sleep(WK_HOLD); load<WK_GAP>(a1, &LayersP::w1, next, j.place); }
       product<WK_DOWN>(deep(), &LayersP::w2, l);
       if (down) {
-        __builtin_amdgcn_s_sleep(LK_HOLD);
-        load<LK_GAP>(deep(), &LayersP::w2, next, WkMember::tile(WK_DOWN, j.place));
-        load<LK_GAP>(a1, &LayersP::w1, next, j.place);
+        __builtin_amdgcn_s_sleep(WK_HOLD);
+        load<WK_GAP>(deep(), &LayersP::w2, next, WkMember::tile(WK_DOWN, j.place));
+        load<WK_GAP>(a1, &LayersP::w1, next, j.place);
       }
     }
   }
