@@ -70,19 +70,27 @@ __device__ __forceinline__ const SmallP& small_args() {
   asm volatile("" : "+s"(q));
   return *(const SmallP*)q;
 }
-__device__ __forceinline__ float wave_max_f(float v) {
-  v = fmaxf(v, dpp_move<0xB1>(v)); v = fmaxf(v, dpp_move<0x4E>(v)); v = fmaxf(v, dpp_move<0x141>(v)); v = fmaxf(v, dpp_move<0x140>(v));
-  return max_rows(v);
+// Reductions over the wave of four values at once.  First over the four 16-lane rows, which leaves value i in row i (three exchanges instead of eight)
+template <typename T, typename Op>
+__device__ __forceinline__ T small_rows4(T v0, T v1, T v2, T v3, Op op) {
+  auto pair = [&](bool half, T a, T b) {
+    const unsigned x = __builtin_bit_cast(unsigned, a), y = __builtin_bit_cast(unsigned, b);
+    const auto r = half ? __builtin_amdgcn_permlane32_swap(x, y, false, false) : __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    return op(__builtin_bit_cast(T, (unsigned)r[0]), __builtin_bit_cast(T, (unsigned)r[1]));
+  };
+  const T a = pair(true, v0, v2), b = pair(true, v1, v3);
+  return pair(false, a, b);
 }
-__device__ __forceinline__ unsigned wave_max_u(unsigned v) {
-#define BPD_STEP(C) { const unsigned o = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, C, 0xF, 0xF, true); v = o > v ? o : v; }
-  BPD_STEP(0xB1) BPD_STEP(0x4E) BPD_STEP(0x141) BPD_STEP(0x140)
-#undef BPD_STEP
-  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-  v = a[0] > a[1] ? a[0] : a[1];
-  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return b[0] > b[1] ? b[0] : b[1];
+template <int CTRL, typename T> __device__ __forceinline__ T small_dpp(T v) { return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true)); }
+template <typename T, typename Op>
+__device__ __forceinline__ void small_wave4(T (&v)[4], Op op) {
+  T r = small_rows4(v[0], v[1], v[2], v[3], op);
+  r = op(r, small_dpp<0xB1>(r)); r = op(r, small_dpp<0x4E>(r)); r = op(r, small_dpp<0x141>(r)); r = op(r, small_dpp<0x140>(r));
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, r), 16 * i));
 }
+struct SmallAdd { template <typename T> __device__ __forceinline__ T operator()(T a, T b) const { return a + b; } };
+struct SmallMax { template <typename T> __device__ __forceinline__ T operator()(T a, T b) const { return a > b ? a : b; } };
 
 // Fills a table entry (one thread)
 struct SmallEntry {
@@ -91,7 +99,7 @@ struct SmallEntry {
   __device__ __forceinline__ void gemm(int mode, const float* W, int ldw, int N, int K, const float* bias, int X, int ldx, int dst, int ldo) {
     const int ncb = (N + 63) / 64, per = ncb < SMALL_W ? ncb : SMALL_W;
     int slices = SMALL_W / per;
-    while (slices > 1 && K % (4 * slices)) --slices;
+    while (slices > 1 && K % (16 * slices)) --slices;
     ptr(SD_W, W); ptr(SD_BIAS, bias); ptr(SD_G, nullptr); ptr(SD_GB, nullptr); ptr(SD_P0, nullptr); ptr(SD_P1, nullptr); ptr(SD_P2, nullptr);
     e[SD_N] = N; e[SD_K] = K; e[SD_LDW] = ldw; e[SD_X] = X; e[SD_LDX] = ldx; e[SD_DST] = dst; e[SD_LDO] = ldo; e[SD_MODE] = mode;
     e[SD_NCB] = ncb; e[SD_INV] = 65536 / per + 1; e[SD_SLICES] = slices; e[SD_KN] = K / slices; e[SD_GW] = 0; e[SD_WG] = 0; e[SD_XG] = 0; e[SD_XN] = -1;
@@ -127,211 +135,321 @@ __device__ __forceinline__ void small_norm_row(const float (&v)[4], float* out, 
 // kv_at: cache row of the block's first row; x_at: where the tile being worked on lies in x (encoder)
 struct SmallCtx { float* lds; int red, xn, d, k, heads, L, src, local_q, local_m, kv_at, x_at; float eps, qscale; };
 
-// Four rows (4 q ..) of one column, finished: v = X W
-__device__ __forceinline__ void small_finish(const SmallCtx& m, int dv, int mode, int rows, int q, int col, float bias, f32x4 v, int lane) {
+// How a wave's 64 columns x 16 rows of weights lie in its registers: load t of four brings, 16 bytes a lane, row 4 (lane / 16) + t of columns
+// 4 (lane % 16) ..  An instruction multiplies one column of every lane: its sixteen blocks of four lanes have different k, so the rows' operand is
+// one 16-byte LDS read per lane for all sixteen k, and the row of 16 lanes g has the sums over k = 4 g ..; the exchange that adds the four up leaves
+// column 4 (lane % 16) + lane / 16 in the lane.  (A load of one row of 64 columns, 4 bytes a lane, at a time: 16 loads and 4 LDS reads for the same,
+// 1000 instead of 250 cycles.)
+__device__ __forceinline__ int small_col(int lane) { return (lane & 15) * 4 + (lane >> 4); }
+
+// What a wave brings along into a phase, requested while the phase before still meets in LDS: its row of the table, its first sixteen rows of
+// weights, where they lie, and bias and gains of the column that it will finish
+struct SmallFetch { int dv, s, cb, xo; unsigned at; f32x4 w[4]; float bias, g, b; };
+
+__device__ __forceinline__ void small_load(const rsrc_t& wr, unsigned at, int ldw, f32x4 (&w)[4]) {
+#pragma unroll
+  for (int t = 0; t < 4; ++t) w[t] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(wr, at, t * ldw * 4, 0));
+}
+// Slice s of column block cb of an entry's matrix: the lane's first byte, and where its part of x lies behind the row's start
+__device__ __forceinline__ unsigned small_column(int dv, int cb, int s, int lane, int& xo) {
+  const int N = BPD_SD(SD_N), gw = BPD_SD(SD_GW), k = s * BPD_SD(SD_KN) + (lane >> 4) * 4, col = cb * 64 + (lane & 15) * 4;
+  int c = col < N ? col : N - 4;
+  xo = k;
+  if (gw) { const int h = (int)(((float)c + 0.5f) * __builtin_amdgcn_rcpf((float)gw)); c += h * (BPD_SD(SD_WG) - gw); xo += h * BPD_SD(SD_XG); }
+  return (unsigned)(c + k * BPD_SD(SD_LDW)) * 4;
+}
+// The pair (column block, row quad) that a wave finishes first, counted from the last wave: where the product leaves waves idle they finish
+__device__ __forceinline__ int small_pair(int wave) { return SMALL_W - 1 - wave; }
+template <int RQ>
+__device__ __forceinline__ void small_fetch(const SmallCtx& m, int dv, SmallFetch& f) {
+  const int tid = small_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  f.dv = dv;
+  if (BPD_SD(SD_MODE) >= SM_SELF) return;
+  const int N = BPD_SD(SD_N), slices = BPD_SD(SD_SLICES), ncb = BPD_SD(SD_NCB);
+  f.s = slices == 1 ? 0 : (wave * BPD_SD(SD_INV)) >> 16;
+  f.cb = wave - f.s * ncb;
+  if (f.s < slices && f.cb < ncb) {
+    f.at = small_column(dv, f.cb, f.s, lane, f.xo);
+    small_load(rsrc_of((const void*)BPD_SDP(SD_W), 0x7FFFFFFF), f.at, BPD_SD(SD_LDW), f.w);
+  }
+  const int col = (slices == 1 ? f.cb : small_pair(wave) / RQ) * 64 + small_col(lane), c = col < N ? col : 0;
+  const gfloat* bias = BPD_SDP(SD_BIAS);
+  f.bias = 0.f;
+  if (bias) f.bias = bias[c];
+  if (BPD_SD(SD_XN) >= 0) { f.g = BPD_SDP(SD_G)[c]; f.b = BPD_SDP(SD_GB)[c]; }
+}
+
+// Four rows (4 q ..) of one column, finished: v = X W.  (Rows past the last: there is room for whole quads everywhere but in the caches and in o.)
+__device__ __forceinline__ void small_finish(const SmallCtx& m, int dv, int mode, int rows, int q, int col, float bias, float gv, float bv, f32x4 v, int lane) {
   float* lds = m.lds;
   const int d = m.d, N = BPD_SD(SD_N), dst = BPD_SD(SD_DST), ldo = BPD_SD(SD_LDO), xn = BPD_SD(SD_XN);
   const bool in = col < N;
   if (mode == SM_QKV || mode == SM_KV) {
     const int c = mode == SM_KV ? col + d : col;
     gfloat *q2 = BPD_SDP(SD_P2), *k0 = BPD_SDP(SD_P0), *v0 = BPD_SDP(SD_P1);
-    if (in) {
+    if (c < d && !q2) {
+      float* at = lds + dst + 4 * q * ldo + c;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = 4 * q + i;
-        if (r >= rows) break;
-        if (c < d) { if (q2) q2[(long)(m.kv_at + r) * d + c] = v[i]; else lds[dst + r * ldo + c] = v[i]; }
-        else if (c < 2 * d) k0[(long)(m.kv_at + r) * d + c - d] = v[i];
-        else v0[(long)(m.kv_at + r) * d + c - 2 * d] = v[i];
-      }
+      for (int i = 0; i < 4; ++i) at[i * ldo] = v[i];
+    } else if (in) {
+      gfloat* at = (c < d ? q2 + c : (c < 2 * d ? k0 + (c - d) : v0 + (c - 2 * d))) + (long)(m.kv_at + 4 * q) * d;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (4 * q + i < rows) at[i * d] = v[i];
     }
     return;
   }
-  int at = dst + (mode == SM_ADD ? m.x_at : 0) + col;
-  if (mode == SM_HEAD) { const int h = (int)(((float)col + 0.5f) * __builtin_amdgcn_rcpf((float)d)), c = col - h * d; at = dst + h * ldo + c; col = c; }
-  f32x4 t;
+  f32x4 t = v + bias;
+  if (mode == SM_HEAD) {
+    const int h = (int)(((float)col + 0.5f) * __builtin_amdgcn_rcpf((float)d)), c = col - h * d;
+    const float* x = lds + m.xn + 4 * q * (d + 4) + c;
+    float xv[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int r = 4 * q + i;
-    t[i] = v[i] + bias;
-    if (mode == SM_RELU) t[i] = fmaxf(t[i], 0.f);
-    if (!in || r >= rows) { t[i] = 0.f; continue; }
-    if (mode == SM_HEAD) lds[at + r * m.k * ldo] = t[i] + lds[m.xn + r * (d + 4) + col];
-    else {
-      if (mode == SM_ADD) t[i] += lds[at + r * ldo];
-      lds[at + r * ldo] = t[i];
+    for (int i = 0; i < 4; ++i) xv[i] = x[i * (d + 4)];
+    float* at = lds + dst + (4 * q * m.k + h) * ldo + c;
+    if (in) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (4 * q + i < rows) at[i * m.k * ldo] = t[i] + xv[i];
     }
+    return;
+  }
+  float* at = lds + dst + (mode == SM_ADD ? m.x_at : 0) + 4 * q * ldo + (in ? col : 0);
+  if (mode == SM_RELU) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t[i] = fmaxf(t[i], 0.f);
+  }
+  if (mode == SM_ADD) {
+    f32x4 x;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = at[i * ldo];
+    t += x;
+  }
+  if (in) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) at[i * ldo] = t[i];
   }
   if (xn >= 0) {                                 // four rows at once: their reductions overlap
-    const gfloat *g = BPD_SDP(SD_G), *b = BPD_SDP(SD_GB);
-    const float gv = g[in ? col : 0], bv = b[in ? col : 0], inv = 1.0f / d;
+    const float inv = 1.0f / d;
     float mu[4], va[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) mu[i] = wave_sum(t[i]) * inv;
+    for (int i = 0; i < 4; ++i) mu[i] = in ? t[i] : 0.f;
+    small_wave4(mu, SmallAdd());
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { const float c = in ? t[i] - mu[i] : 0.f; va[i] = wave_sum(c * c); }
+    for (int i = 0; i < 4; ++i) { mu[i] = fmaf(-mu[i], inv, t[i]); va[i] = in ? mu[i] * mu[i] : 0.f; }
+    small_wave4(va, SmallAdd());
+    float* out = lds + xn + 4 * q * (d + 4) + (in ? col : 0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float x = fmaf(va[i], inv, m.eps), r0 = __builtin_amdgcn_rsqf(x), rs = r0 * fmaf(-0.5f * x * r0, r0, 1.5f);
-      if (in && 4 * q + i < rows) lds[xn + (4 * q + i) * (d + 4) + col] = (t[i] - mu[i]) * rs * gv + bv;
+      va[i] = mu[i] * rs * gv + bv;
+    }
+    if (in) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) out[i * (d + 4)] = va[i];
     }
   }
 }
 
-// X W of one wave: 64 columns (col: this lane's) and kn of the k, 4 RQ rows
+// X W of one wave: 64 columns and kn (sixteens) of the k, 4 RQ rows.  w: the first sixteen rows of weights, which `at` (small_column) starts at;
+// x: the lane's row and k
 template <int RQ>
-__device__ __forceinline__ void small_product(const SmallCtx& m, int dv, int col, int s, int lane, f32x4 (&acc)[RQ]) {
-  const int N = BPD_SD(SD_N), ldw = BPD_SD(SD_LDW), ldx = BPD_SD(SD_LDX), kn = BPD_SD(SD_KN), gw = BPD_SD(SD_GW);
-  int c = col < N ? col : N - 1, xo = 0;
-  if (gw) { const int h = (int)(((float)c + 0.5f) * __builtin_amdgcn_rcpf((float)gw)); c += h * (BPD_SD(SD_WG) - gw); xo = h * BPD_SD(SD_XG); }
-  // (rows of W are scalar offsets: one register of address for all loads)
-  const rsrc_t wr = rsrc_of((const void*)BPD_SDP(SD_W), 0x7FFFFFFF);
-  unsigned at = (unsigned)(c + s * kn * ldw) * 4;
-  const float* x = m.lds + BPD_SD(SD_X) + xo + (lane & 3) * ldx + s * kn;
-  f32x4 a2[RQ];
+__device__ __forceinline__ void small_product(const rsrc_t& wr, unsigned at, int ldw, const float* x, int ldx, int kn, f32x4 (&w)[4], f32x4 (&out)[RQ]) {
+  f32x4 acc[RQ][4];
 #pragma unroll
-  for (int q = 0; q < RQ; ++q) { acc[q] = f32x4{0.f, 0.f, 0.f, 0.f}; a2[q] = acc[q]; }
-  // sixteen k at a time, the next sixteen weights on their way meanwhile
-  float wa[16], wb[16];
-#define BPD_SLOAD(w, left)                                                                      \
-  {                                                                                             \
-    _Pragma("unroll") for (int j = 0; j < 16; ++j) w[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wr, at, (j < (left) ? j : 0) * ldw * 4, 0)); \
-    at += 64 * ldw;                                                                             \
-  }
-#define BPD_SMULT(w, left)                                                                      \
-  {                                                                                             \
-    _Pragma("unroll") for (int j = 0; j < 16; j += 4) {                                         \
-      if (j >= (left)) break;                    /* (the same for the whole wave) */            \
-      _Pragma("unroll") for (int q = 0; q < RQ; ++q) {                                          \
-        const f32x4 xv = *(const f32x4*)(x + 4 * q * ldx + j);                                  \
-        acc[q] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[0], w[j], acc[q], 0, 0, 0);              \
-        a2[q] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[1], w[j + 1], a2[q], 0, 0, 0);            \
-        acc[q] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[2], w[j + 2], acc[q], 0, 0, 0);          \
-        a2[q] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[3], w[j + 3], a2[q], 0, 0, 0);            \
-      }                                                                                         \
-    }                                                                                           \
-    x += 16;                                                                                    \
-  }
-  BPD_SLOAD(wa, kn)
-  if (kn <= 16) {                                // (one batch: no loop around it, which would wait for the loads at its head)
-    BPD_SMULT(wa, kn)
-  } else {
-    int left = kn;
+  for (int q = 0; q < RQ; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[q][i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-    for (;;) {
-      BPD_SLOAD(wb, left - 16)
-      BPD_SMULT(wa, 16)
-      left -= 16;
-      if (left <= 16) { BPD_SMULT(wb, left) break; }
-      BPD_SLOAD(wa, left - 16)
-      BPD_SMULT(wb, 16)
-      left -= 16;
-      if (left <= 16) { BPD_SMULT(wa, left) break; }
-    }
-  }
-#undef BPD_SMULT
-#undef BPD_SLOAD
+  for (int left = kn;;) {
+    f32x4 next[4], xv[RQ];                       // (the next sixteen rows on their way meanwhile)
+    left -= 16;
+    at += 64 * ldw;
+    if (left > 0) small_load(wr, at, ldw, next);
 #pragma unroll
-  for (int q = 0; q < RQ; ++q) acc[q] += a2[q];
+    for (int q = 0; q < RQ; ++q) xv[q] = *(const f32x4*)(x + 4 * q * ldx);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int q = 0; q < RQ; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[q][i] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[q][t], w[t][i], acc[q][i], 0, 0, 0);
+    if (left <= 0) break;
+    x += 16;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) w[t] = next[t];
+  }
+#pragma unroll
+  for (int q = 0; q < RQ; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out[q][r] = small_rows4(acc[q][0][r], acc[q][1][r], acc[q][2][r], acc[q][3][r], SmallAdd());
+}
+// The sum of the slices' partial results at red[at], `step` apart
+__device__ __forceinline__ f32x4 small_partials(const f32x4* red, int slices, int step) {
+  f32x4 v[4];                                    // (all reads of four under way together)
+#pragma unroll
+  for (int t = 0; t < 4; ++t) v[t] = red[(t < slices ? t : 0) * step];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int t = 1; t < 4; ++t)
+    if (t < slices) v[0] += v[t];
+#pragma unroll 1
+  for (int t = 4; t < slices; ++t) v[0] += red[t * step];
+  return v[0];
 }
 
-// One phase for up to 4 RQ rows.  Ends with a barrier.
+// Attention of 16-wide heads, a wave per two (head, row) pairs, whose chains overlap.  64 keys at a time: four lanes have a key's sixteen numbers, load
+// i brings keys 16 i + lane / 4, and a lane keeps the probabilities of its four keys for its four dimensions of their values.  (A lane per key and 16
+// bytes of it a load: 64 lines each, 4400 cycles for the 16 pairs of four rows and 20 keys.)
+__device__ __forceinline__ void small_attention(const SmallCtx& m, int dv, int rows, int wave, int lane) {
+  const int d = m.d, pairs = m.heads * rows;
+  const bool self = BPD_SD(SD_MODE) == SM_SELF;
+  const gfloat* qg = BPD_SDP(SD_P2);
+  const int X = BPD_SD(SD_X), ldx = BPD_SD(SD_LDX), dim = (lane & 3) * 4;
+  const rsrc_t kr = rsrc_of((const void*)BPD_SDP(SD_P0), 0x7FFFFFFF), vr = rsrc_of((const void*)BPD_SDP(SD_P1), 0x7FFFFFFF);
+#pragma unroll 1
+  for (int p0 = wave; p0 < pairs; p0 += 2 * SMALL_W) {
+    int h[2], r[2], k0[2], k1[2];
+    f32x4 qv[2], acc[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int pr = p0 + u * SMALL_W < pairs ? p0 + u * SMALL_W : p0;
+      h[u] = (int)(((float)pr + 0.5f) * __builtin_amdgcn_rcpf((float)rows)); r[u] = pr - h[u] * rows;
+      k1[u] = self ? m.L + r[u] + 1 : m.src;
+      k0[u] = 0;
+      if (self && m.local_q > 0) { k0[u] = (m.L + r[u]) / m.local_q * m.local_q - m.local_m; k0[u] = k0[u] > 0 ? k0[u] : 0; }
+      qv[u] = qg ? *(const gfloat4*)(qg + (long)(m.kv_at + r[u]) * d + h[u] * 16 + dim) : *(const f32x4*)(m.lds + X + r[u] * ldx + h[u] * 16 + dim);
+      acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const int n0 = k1[0] - k0[0], n1 = k1[1] - k0[1], span = n0 > n1 ? n0 : n1;
+    float mx[2] = {-INFINITY, -INFINITY}, l[2] = {0.f, 0.f};
+#pragma unroll 1
+    for (int s0 = 0; s0 < span; s0 += 64) {
+      f32x4 kv[2][4], vv[2][4];
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int key = k0[u] + s0 + 16 * i + (lane >> 2);
+          const unsigned at = (unsigned)((key < k1[u] ? key : k1[u] - 1) * d + h[u] * 16 + dim) * 4;
+          kv[u][i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(kr, at, 0, 0));
+          vv[u][i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(vr, at, 0, 0));
+        }
+      __builtin_amdgcn_sched_barrier(0);
+      float sc[2][4], top[2];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          float v = qv[u][0] * kv[u][i][0];
+#pragma unroll
+          for (int e = 1; e < 4; ++e) v = fmaf(qv[u][e], kv[u][i][e], v);
+          v += small_dpp<0xB1>(v);
+          v += small_dpp<0x4E>(v);
+          sc[u][i] = k0[u] + s0 + 16 * i + (lane >> 2) < k1[u] ? v * m.qscale : -INFINITY;      // (a pair that is done: nothing but these, and its maximum stays)
+        }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        top[u] = fmaxf(fmaxf(sc[u][0], sc[u][1]), fmaxf(sc[u][2], sc[u][3]));
+        top[u] = fmaxf(top[u], small_dpp<0x124>(top[u]));         // (row_ror: the other quads of the row)
+        top[u] = fmaxf(top[u], small_dpp<0x128>(top[u]));
+        top[u] = max_rows(top[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const float mn = fmaxf(mx[u], top[u]), a = __expf(mx[u] - mn);
+        mx[u] = mn;
+        l[u] *= a; acc[u] *= a;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float p = __expf(sc[u][i] - mn);
+          l[u] += p;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[u][e] = fmaf(p, vv[u][i][e], acc[u][e]);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      // over the rows of 16 lanes (dimension e of the four in row e), then over the quads
+      float o = small_rows4(acc[u][0], acc[u][1], acc[u][2], acc[u][3], SmallAdd());
+      o += small_dpp<0x124>(o); o += small_dpp<0x128>(o);
+      l[u] += small_dpp<0x124>(l[u]); l[u] += small_dpp<0x128>(l[u]);
+      l[u] = sum_rows(l[u]);
+      if ((lane & 12) == 0 && p0 + u * SMALL_W < pairs) m.lds[BPD_SD(SD_DST) + r[u] * BPD_SD(SD_LDO) + h[u] * 16 + dim + (lane >> 4)] = o / l[u];
+    }
+  }
+}
+
+// One phase for up to 4 RQ rows: the one f was fetched for; that of entry `next` (-1: none) is fetched on the way.  Ends with a barrier.
 template <int RQ>
-__device__ __forceinline__ void small_phase(const SmallCtx& m, int entry, int rows) {
+__device__ __forceinline__ void small_phase(const SmallCtx& m, SmallFetch& f, int next, int rows) {
   const int tid = small_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int dv = ((const int*)m.lds)[entry + (lane & 31)];
-  const int mode = BPD_SD(SD_MODE), d = m.d;
-  if (mode == SM_NORM) {
+  const int dv = f.dv, mode = BPD_SD(SD_MODE), d = m.d;
+  const int dn = next >= 0 ? ((const int*)m.lds)[next + (lane & 31)] : 0;
+  const int ncb = BPD_SD(SD_NCB), N = BPD_SD(SD_N), slices = BPD_SD(SD_SLICES);
+  const gfloat* bias = BPD_SDP(SD_BIAS);
+  const float bs0 = f.bias, gv = f.g, bv = f.b;
+  f32x4* red = (f32x4*)(m.lds + m.red);
+  if (mode < SM_SELF && f.s < slices) {
+    const int ldw = BPD_SD(SD_LDW), ldx = BPD_SD(SD_LDX), kn = BPD_SD(SD_KN);
+    const rsrc_t wr = rsrc_of((const void*)BPD_SDP(SD_W), 0x7FFFFFFF);
+    const float* x = m.lds + BPD_SD(SD_X) + (lane & 3) * ldx;
+    f32x4 acc[RQ];
+#pragma unroll 1
+    for (int cb = f.cb; cb < ncb; cb += SMALL_W) {
+      small_product<RQ>(wr, f.at, ldw, x + f.xo, ldx, kn, f.w, acc);
+      if (slices > 1) {                          // (at most SMALL_W column blocks)
+#pragma unroll
+        for (int q = 0; q < RQ; ++q) red[(wave * RQ + q) * 64 + lane] = acc[q];
+        break;
+      }
+      // a wave finishes what it multiplied
+      if (cb + SMALL_W < ncb) { f.at = small_column(dv, cb + SMALL_W, 0, lane, f.xo); small_load(wr, f.at, ldw, f.w); }
+      const int col = cb * 64 + small_col(lane);
+      float bs = bs0;
+      if (cb != wave && bias) bs = bias[col < N ? col : N - 1];
+#pragma unroll 1
+      for (int q = 0; q < RQ && 4 * q < rows; ++q) {
+        f32x4 v = acc[0];
+#pragma unroll
+        for (int i = 1; i < RQ; ++i) v = q == i ? acc[i] : v;
+        small_finish(m, dv, mode, rows, q, col, bs, gv, bv, v, lane);
+      }
+    }
+  }
+  if (next >= 0) small_fetch<RQ>(m, dn, f);
+  if (mode < SM_SELF) {
+    if (slices > 1) {
+      const int pair = small_pair(wave), step = ncb * RQ * 64;
+      __syncthreads();
+#pragma unroll 1
+      for (int pr = pair; pr < ncb * RQ; pr += SMALL_W) {
+        const int c = pr / RQ, q = pr - c * RQ, col = c * 64 + small_col(lane);
+        if (4 * q >= rows) continue;
+        const float bs = pr == pair ? bs0 : (bias ? bias[col < N ? col : N - 1] : 0.f);
+        small_finish(m, dv, mode, rows, q, col, bs, gv, bv, small_partials(red + (c * RQ + q) * 64 + lane, slices, step), lane);
+      }
+    }
+  } else if (mode == SM_NORM) {
     for (int r = wave; r < rows; r += SMALL_W) {
       float v[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[i] = lane + 64 * i < d ? m.lds[BPD_SD(SD_X) + m.x_at + r * (d + 4) + lane + 64 * i] : 0.f;
       small_norm_row(v, m.lds + BPD_SD(SD_XN) + r * (d + 4), d, lane, BPD_SDP(SD_G), BPD_SDP(SD_GB), m.eps);
     }
-  } else if (mode >= SM_SELF) {
-    // Attention of 16-wide heads, a wave per (head, row): scores with a lane per key, then values with a lane per dimension and 16 of 64 keys
-    const bool self = mode == SM_SELF;
-    const gfloat *Kc = BPD_SDP(SD_P0), *Vc = BPD_SDP(SD_P1), *qg = BPD_SDP(SD_P2);
-    float* pb = m.lds + m.red + wave * 64;
-    for (int pr = wave; pr < m.heads * rows; pr += SMALL_W) {
-      const int h = (int)(((float)pr + 0.5f) * __builtin_amdgcn_rcpf((float)rows)), r = pr - h * rows;
-      const int k1 = self ? m.L + r + 1 : m.src;
-      int k0 = 0;
-      if (self && m.local_q > 0) { k0 = (m.L + r) / m.local_q * m.local_q - m.local_m; k0 = k0 > 0 ? k0 : 0; }
-      f32x4 qv[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) qv[j] = qg ? *(const gfloat4*)(qg + (long)(m.kv_at + r) * d + h * 16 + 4 * j) : *(const f32x4*)(m.lds + BPD_SD(SD_X) + r * BPD_SD(SD_LDX) + h * 16 + 4 * j);
-      float mx = -INFINITY, l = 0.f, acc = 0.f;
-      for (int s0 = k0; s0 < k1; s0 += 64) {
-        const int key = s0 + lane < k1 ? s0 + lane : k1 - 1;
-        const gfloat4* kp = (const gfloat4*)(Kc + (long)key * d + h * 16);
-        f32x4 kv[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) kv[j] = kp[j];
-        float vv[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int kk = s0 + 16 * (lane >> 4) + i;
-          vv[i] = Vc[(long)(kk < k1 ? kk : k1 - 1) * d + h * 16 + (lane & 15)];
-        }
-        float sc = 0.f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) sc = fmaf(qv[j][i], kv[j][i], sc);
-        sc = s0 + lane < k1 ? sc * m.qscale : -INFINITY;
-        const float mn = fmaxf(mx, wave_max_f(sc)), a = __expf(mx - mn), p = __expf(sc - mn);
-        mx = mn;
-        l = fmaf(l, a, p);
-        pb[lane] = p;                            // (a wave's LDS accesses execute in order)
-        acc *= a;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const f32x4 pv = *(const f32x4*)(pb + 16 * (lane >> 4) + 4 * i);
-          acc = fmaf(pv[0], vv[4 * i], acc); acc = fmaf(pv[1], vv[4 * i + 1], acc); acc = fmaf(pv[2], vv[4 * i + 2], acc); acc = fmaf(pv[3], vv[4 * i + 3], acc);
-        }
-      }
-      l = wave_sum(l);
-      acc = sum_rows(acc);
-      if (lane < 16) m.lds[BPD_SD(SD_DST) + r * BPD_SD(SD_LDO) + h * 16 + lane] = acc / l;
-    }
   } else {
-    const int ncb = BPD_SD(SD_NCB), N = BPD_SD(SD_N), slices = BPD_SD(SD_SLICES);
-    const gfloat* bias = BPD_SDP(SD_BIAS);
-    if (slices == 1) {                           // a wave finishes what it multiplied
-      for (int cb = wave; cb < ncb; cb += SMALL_W) {
-        const int col = cb * 64 + lane;
-        const float bs = bias ? bias[col < N ? col : N - 1] : 0.f;
-        f32x4 acc[RQ];
-        small_product<RQ>(m, dv, col, 0, lane, acc);
-#pragma unroll
-        for (int q = 0; q < RQ; ++q) small_finish(m, dv, mode, rows, q, col, bs, acc[q], lane);
-      }
-    } else {                                     // (at most SMALL_W column blocks)
-      f32x4* red = (f32x4*)(m.lds + m.red);
-      const int s = (wave * BPD_SD(SD_INV)) >> 16, cb = wave - s * ncb;
-      // bias of what this wave will finish: (column block, row quad) pairs wave, wave + SMALL_W, ..
-      const int col0 = (wave / RQ) * 64 + lane;
-      const float bs0 = bias ? bias[col0 < N ? col0 : N - 1] : 0.f;
-      if (s < slices) {
-        f32x4 acc[RQ];
-        small_product<RQ>(m, dv, cb * 64 + lane, s, lane, acc);
-#pragma unroll
-        for (int q = 0; q < RQ; ++q) red[(wave * RQ + q) * 64 + lane] = acc[q];
-      }
-      __syncthreads();
-      for (int pr = wave; pr < ncb * RQ; pr += SMALL_W) {
-        const int c = pr / RQ, q = pr - c * RQ, col = c * 64 + lane;
-        const float bs = pr == wave ? bs0 : (bias ? bias[col < N ? col : N - 1] : 0.f);
-        f32x4 v = red[(c * RQ + q) * 64 + lane];
-#pragma unroll
-        for (int t = 1; t < SMALL_W; ++t)        // (a branch each, all reads under way together)
-          if (t < slices) v += red[((t * ncb + c) * RQ + q) * 64 + lane];
-        small_finish(m, dv, mode, rows, q, col, bs, v, lane);
-      }
-    }
+    small_attention(m, dv, rows, wave, lane);
   }
   __syncthreads();
+}
+// The phases of the entries first .. last - 1 for the same rows
+template <int RQ>
+__device__ __forceinline__ void small_phases(const SmallCtx& m, int table, int first, int last, int rows) {
+  SmallFetch f;
+  small_fetch<RQ>(m, ((const int*)m.lds)[table + first * SD_WORDS + (small_tid() & 31)], f);
+#pragma unroll 1
+  for (int ph = first; ph < last; ++ph) small_phase<RQ>(m, f, ph + 1 < last ? table + (ph + 1) * SD_WORDS : -1, rows);
 }
 
 // Rows of the next block: x = scale E[token] + pos (zero: without token), with the LayerNorm of the first phase (g null: without).  A wave per row, no barrier.
@@ -407,19 +525,27 @@ __device__ __forceinline__ void small_decoder_table(const SmallP& p, const Small
   }
 }
 
+// The lowest column (small_col) among the lanes of a mask
+__device__ __forceinline__ int small_first(unsigned long long lanes) {
+  // columns 4 i + g are lanes 16 g + i: the lowest i of any row of lanes, then the lowest row that has it
+  const unsigned any = (unsigned)((lanes | lanes >> 16 | lanes >> 32 | lanes >> 48) & 0xFFFFu);
+  const int i = __ffs((int)any) - 1;
+  const unsigned long long at = lanes >> (i & 15);
+  return 4 * i + ((at & 1) ? 0 : ((at >> 16 & 1) ? 1 : ((at >> 32 & 1) ? 2 : 3)));
+}
+
 // The decoder's phases, then scores and arg-max: fills best[row * k + head] for the first k heads (and logits, z where wanted).  x and xn hold
 // the block (small_embed).
 template <int RQ>
 __device__ __forceinline__ void small_forward(const SmallCtx& m, const SmallLds& n, int rows, float* logits, bool want_z) {
   const SmallP& p = small_args();
   const int count = small_decoder_phases(p), k = p.k, V = p.V, d = p.d;
-#pragma unroll 1
-  for (int ph = 0; ph < count; ++ph) small_phase<RQ>(m, n.table + ph * SD_WORDS, rows);
+  small_phases<RQ>(m, n.table, 0, count, rows);
   // sixteen rows at a time; column blocks of 64, up to SMALL_W of them with K in slices, else one wave each
   const int tid = small_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int M = rows * k, ncb = (V + 63) / 64, per = ncb < SMALL_W ? ncb : SMALL_W;
   int slices = SMALL_W / per;
-  while (slices > 1 && d % (4 * slices)) --slices;
+  while (slices > 1 && d % (16 * slices)) --slices;
   const int kn = d / slices, s = wave / per, cb0 = wave - s * per, ld = d + 4;
   f32x4* red = (f32x4*)(m.lds + m.red);
   unsigned long long* best = (unsigned long long*)(m.lds + n.best);
@@ -430,31 +556,17 @@ __device__ __forceinline__ void small_forward(const SmallCtx& m, const SmallLds&
     unsigned bu = 0, bi = 0;                     // lane r < 16: best of row r over the columns this wave finished
 #pragma unroll 1
     for (int cbase = 0; cbase < ncb; cbase += SMALL_W) {
+      const int lane = small_tid() & 63;
       f32x4 acc[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
       const int cb = cbase + cb0;
       if (s < slices && cb < ncb) {
-        const int col = cb * 64 + lane;
-        unsigned at = (unsigned)((col < V ? col : V - 1) + s * kn * V) * 4;
-        const float* x = m.lds + n.o + (m0 + (lane & 3)) * ld + s * kn;
-        for (int left = kn; left > 0; left -= 16) {
-          float w[16];
-#pragma unroll
-          for (int j = 0; j < 16; ++j) w[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wr, at, (j < left ? j : 0) * V * 4, 0));
-          at += 64 * V;
-#pragma unroll
-          for (int j = 0; j < 16; j += 4) {
-            if (j >= left) break;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const f32x4 xv = *(const f32x4*)(x + 4 * q * ld + j);
-#pragma unroll
-              for (int i = 0; i < 4; ++i) acc[q] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[i], w[j + i], acc[q], 0, 0, 0);
-            }
-          }
-          x += 16;
-        }
+        const int col = cb * 64 + (lane & 15) * 4, kk = s * kn + (lane >> 4) * 4;
+        const unsigned at = (unsigned)((col < V ? col : V - 4) + kk * V) * 4;
+        f32x4 w[4];
+        small_load(wr, at, V, w);
+        small_product<4>(wr, at, V, m.lds + n.o + (m0 + (lane & 3)) * ld + kk, ld, kn, w, acc);
       }
       if (slices > 1) {
         if (s < slices) {
@@ -464,39 +576,39 @@ __device__ __forceinline__ void small_forward(const SmallCtx& m, const SmallLds&
         __syncthreads();
       }
       // (column block, row quad) pairs: with slices a wave takes the pairs wave, wave + SMALL_W, .., without it has all four quads of its block
+#pragma unroll 1
       for (int pr = slices > 1 ? wave : 0; pr < (slices > 1 ? per * 4 : 4); pr += slices > 1 ? SMALL_W : 1) {
-        const int c = slices > 1 ? pr >> 2 : cb, q = pr & 3, col = c * 64 + lane;
-        f32x4 v;
-        if (slices > 1) {
-          v = red[(c * 4 + q) * 64 + lane];
+        const int c = slices > 1 ? pr >> 2 : cb, q = pr & 3, col = c * 64 + small_col(lane);
+        if (slices == 1 && (cb >= ncb || s > 0)) break;         // (not a block of this wave)
+        const f32x4 v = slices > 1 ? small_partials(red + (c * 4 + q) * 64 + lane, slices, per * 256) : (q == 0 ? acc[0] : (q == 1 ? acc[1] : (q == 2 ? acc[2] : acc[3])));
+        unsigned key[4], top[4];
 #pragma unroll
-          for (int t = 1; t < SMALL_W; ++t)
-            if (t < slices) v += red[((t * per + c) * 4 + q) * 64 + lane];
-        } else {
-          v = q == 0 ? acc[0] : (q == 1 ? acc[1] : (q == 2 ? acc[2] : acc[3]));
-          if (cb >= ncb || s > 0) break;         // (not a block of this wave)
-        }
+        for (int i = 0; i < 4; ++i) top[i] = key[i] = col < V ? (unsigned)(argmax_key(v[i], 0u) >> 32) : 0u;
+        small_wave4(top, SmallMax());
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int r = 4 * q + i, mm = m0 + r;
-          if (mm >= M) break;
-          const unsigned key = col < V ? (unsigned)(argmax_key(v[i], 0u) >> 32) : 0u, top = wave_max_u(key);
-          const int first = __ffsll((long long)__ballot(key == top && col < V)) - 1;
+          const int r = 4 * q + i, mm = m0 + r, first = small_first(__ballot(key[i] == top[i] && col < V));
           // (columns ascend from pair to pair and pass to pass: an equal later one loses)
-          if (lane == r && top > bu) { bu = top; bi = (unsigned)(c * 64 + first); }
+          const bool better = lane == r && top[i] > bu;
+          bi = better ? (unsigned)(c * 64 + first) : bi; bu = better ? top[i] : bu;
+          if (mm >= M) continue;
           if (logits && col < V) logits[(long)mm * V + col] = v[i];
           if (want_z && col < V && mm % k == 0) m.lds[n.z + mm / k * V + col] = v[i];
         }
       }
       if (slices > 1) __syncthreads();
     }
-    if (lane < 16) { cand[(wave * 16 + lane) * 2] = bu; cand[(wave * 16 + lane) * 2 + 1] = bi; }
+    if (lane < 16) *(u32x2*)(cand + (wave * 16 + lane) * 2) = u32x2{bu, bi};
     __syncthreads();
     if (tid < 16 && m0 + tid < M) {
+      u32x2 c[SMALL_W];
+#pragma unroll
+      for (int w = 0; w < SMALL_W; ++w) c[w] = *(const u32x2*)(cand + (w * 16 + tid) * 2);
+      __builtin_amdgcn_sched_barrier(0);
       unsigned long long top = 0ull;
+#pragma unroll
       for (int w = 0; w < SMALL_W; ++w) {
-        const unsigned u = cand[(w * 16 + tid) * 2], i = cand[(w * 16 + tid) * 2 + 1];
-        const unsigned long long key = u ? ((unsigned long long)u << 32) | (0xFFFFFFFFu - i) : 0ull;
+        const unsigned long long key = c[w][0] ? ((unsigned long long)c[w][0] << 32) | (0xFFFFFFFFu - c[w][1]) : 0ull;
         top = key > top ? key : top;
       }
       best[m0 + tid] = top;
@@ -635,8 +747,7 @@ __global__ __launch_bounds__(SMALL_T) void small_encode_kernel(SmallP p) {
 #pragma unroll 1
     for (int t = 0; t < tiles; ++t) {
       m.kv_at = t * 16; m.x_at = t * 16 * ld;
-#pragma unroll 1
-      for (int ph = first; ph < last; ++ph) small_phase<4>(m, n.table + ph * SD_WORDS, S - t * 16 < 16 ? S - t * 16 : 16);
+      small_phases<4>(m, n.table, first, last, S - t * 16 < 16 ? S - t * 16 : 16);
     }
   }
 }
