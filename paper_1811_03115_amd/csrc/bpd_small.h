@@ -298,8 +298,63 @@ __device__ __forceinline__ f32x4 small_partials(const f32x4* red, int slices, in
   return v[0];
 }
 
-// Attention of 16-wide heads, a wave per two (head, row) pairs, whose chains overlap.  64 keys at a time: four lanes have a key's sixteen numbers, load
-// i brings keys 16 i + lane / 4, and a lane keeps the probabilities of its four keys for its four dimensions of their values.  (A lane per key and 16
+// The keys of small_attention
+template <int NI>
+__device__ __forceinline__ void small_keys(const SmallCtx& m, const rsrc_t& kr, const rsrc_t& vr, int span, const int (&k0)[2], const int (&k1)[2], const int (&h)[2], int lane,
+                                           const f32x4 (&qv)[2], f32x4 (&acc)[2], float (&l)[2]) {
+  const int d = m.d, dim = (lane & 3) * 4;
+  float mx[2] = {-INFINITY, -INFINITY};
+#pragma unroll 1
+  for (int s0 = 0; s0 < span; s0 += 16 * NI) {
+    f32x4 kv[2][NI], vv[2][NI];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int key = k0[u] + s0 + 16 * i + (lane >> 2);
+        const unsigned at = (unsigned)((key < k1[u] ? key : k1[u] - 1) * d + h[u] * 16 + dim) * 4;
+        kv[u][i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(kr, at, 0, 0));
+        vv[u][i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(vr, at, 0, 0));
+      }
+    __builtin_amdgcn_sched_barrier(0);
+    float sc[2][NI], top[2];
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        float v = qv[u][0] * kv[u][i][0];
+#pragma unroll
+        for (int e = 1; e < 4; ++e) v = fmaf(qv[u][e], kv[u][i][e], v);
+        v += small_dpp<0xB1>(v);
+        v += small_dpp<0x4E>(v);
+        sc[u][i] = k0[u] + s0 + 16 * i + (lane >> 2) < k1[u] ? v * m.qscale : -INFINITY;      // (a pair that is done: nothing but these, and its maximum stays)
+      }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      top[u] = sc[u][0];
+#pragma unroll
+      for (int i = 1; i < NI; ++i) top[u] = fmaxf(top[u], sc[u][i]);
+      top[u] = fmaxf(top[u], small_dpp<0x124>(top[u]));         // (row_ror: the other quads of the row)
+      top[u] = fmaxf(top[u], small_dpp<0x128>(top[u]));
+      top[u] = max_rows(top[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const float mn = fmaxf(mx[u], top[u]), a = __expf(mx[u] - mn);
+      mx[u] = mn;
+      l[u] *= a; acc[u] *= a;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const float p = __expf(sc[u][i] - mn);
+        l[u] += p;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[u][e] = fmaf(p, vv[u][i][e], acc[u][e]);
+      }
+    }
+  }
+}
+// Attention of 16-wide heads, a wave per two (head, row) pairs, whose chains overlap.  16 NI keys at a time: four lanes have a key's sixteen numbers, load
+// i brings keys 16 i + lane / 4, and a lane keeps the probabilities of its NI keys for its four dimensions of their values.  (A lane per key and 16
 // bytes of it a load: 64 lines each, 4400 cycles for the 16 pairs of four rows and 20 keys.)
 __device__ __forceinline__ void small_attention(const SmallCtx& m, int dv, int rows, int wave, int lane) {
   const int d = m.d, pairs = m.heads * rows;
@@ -322,53 +377,10 @@ __device__ __forceinline__ void small_attention(const SmallCtx& m, int dv, int r
       acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     const int n0 = k1[0] - k0[0], n1 = k1[1] - k0[1], span = n0 > n1 ? n0 : n1;
-    float mx[2] = {-INFINITY, -INFINITY}, l[2] = {0.f, 0.f};
-#pragma unroll 1
-    for (int s0 = 0; s0 < span; s0 += 64) {
-      f32x4 kv[2][4], vv[2][4];
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int key = k0[u] + s0 + 16 * i + (lane >> 2);
-          const unsigned at = (unsigned)((key < k1[u] ? key : k1[u] - 1) * d + h[u] * 16 + dim) * 4;
-          kv[u][i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(kr, at, 0, 0));
-          vv[u][i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(vr, at, 0, 0));
-        }
-      __builtin_amdgcn_sched_barrier(0);
-      float sc[2][4], top[2];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          float v = qv[u][0] * kv[u][i][0];
-#pragma unroll
-          for (int e = 1; e < 4; ++e) v = fmaf(qv[u][e], kv[u][i][e], v);
-          v += small_dpp<0xB1>(v);
-          v += small_dpp<0x4E>(v);
-          sc[u][i] = k0[u] + s0 + 16 * i + (lane >> 2) < k1[u] ? v * m.qscale : -INFINITY;      // (a pair that is done: nothing but these, and its maximum stays)
-        }
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        top[u] = fmaxf(fmaxf(sc[u][0], sc[u][1]), fmaxf(sc[u][2], sc[u][3]));
-        top[u] = fmaxf(top[u], small_dpp<0x124>(top[u]));         // (row_ror: the other quads of the row)
-        top[u] = fmaxf(top[u], small_dpp<0x128>(top[u]));
-        top[u] = max_rows(top[u]);
-      }
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const float mn = fmaxf(mx[u], top[u]), a = __expf(mx[u] - mn);
-        mx[u] = mn;
-        l[u] *= a; acc[u] *= a;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float p = __expf(sc[u][i] - mn);
-          l[u] += p;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[u][e] = fmaf(p, vv[u][i][e], acc[u][e]);
-        }
-      }
-    }
+    float l[2] = {0.f, 0.f};
+    if (span <= 16) small_keys<1>(m, kr, vr, span, k0, k1, h, lane, qv, acc, l);
+    else if (span <= 32) small_keys<2>(m, kr, vr, span, k0, k1, h, lane, qv, acc, l);
+    else small_keys<4>(m, kr, vr, span, k0, k1, h, lane, qv, acc, l);
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       // over the rows of 16 lanes (dimension e of the four in row e), then over the quads
@@ -525,13 +537,32 @@ __device__ __forceinline__ void small_decoder_table(const SmallP& p, const Small
   }
 }
 
-// The lowest column (small_col) among the lanes of a mask
-__device__ __forceinline__ int small_first(unsigned long long lanes) {
-  // columns 4 i + g are lanes 16 g + i: the lowest i of any row of lanes, then the lowest row that has it
-  const unsigned any = (unsigned)((lanes | lanes >> 16 | lanes >> 32 | lanes >> 48) & 0xFFFFu);
-  const int i = __ffs((int)any) - 1;
-  const unsigned long long at = lanes >> (i & 15);
-  return 4 * i + ((at & 1) ? 0 : ((at >> 16 & 1) ? 1 : ((at >> 32 & 1) ? 2 : 3)));
+// First weights of column block cb from row k0 of the transposed table on; returns where they lie
+__device__ __forceinline__ unsigned small_vocab_load(const rsrc_t& wr, int V, int cb, int k0, int lane, f32x4 (&w)[4]) {
+  const int col = cb * 64 + (lane & 15) * 4;
+  const unsigned at = (unsigned)((col < V ? col : V - 4) + (k0 + (lane >> 4) * 4) * V) * 4;
+  small_load(wr, at, V, w);
+  return at;
+}
+// As small_product, for sixteen rows: with v_mfma_f32_16x16x4 the same loads need no exchange; acc[i]: columns 4 (lane % 16) + i of rows
+// 4 (lane / 16) ..
+__device__ __forceinline__ void small_product16(const rsrc_t& wr, unsigned at, int ldw, const float* x, int kn, f32x4 (&w)[4], f32x4 (&acc)[4]) {
+#pragma unroll 1
+  for (int left = kn;;) {
+    f32x4 next[4];
+    left -= 16;
+    at += 64 * ldw;
+    if (left > 0) small_load(wr, at, ldw, next);
+    const f32x4 xv = *(const f32x4*)x;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[t], w[t][i], acc[i], 0, 0, 0);
+    if (left <= 0) break;
+    x += 16;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) w[t] = next[t];
+  }
 }
 
 // The decoder's phases, then scores and arg-max: fills best[row * k + head] for the first k heads (and logits, z where wanted).  x and xn hold
@@ -540,8 +571,7 @@ template <int RQ>
 __device__ __forceinline__ void small_forward(const SmallCtx& m, const SmallLds& n, int rows, float* logits, bool want_z) {
   const SmallP& p = small_args();
   const int count = small_decoder_phases(p), k = p.k, V = p.V, d = p.d;
-  small_phases<RQ>(m, n.table, 0, count, rows);
-  // sixteen rows at a time; column blocks of 64, up to SMALL_W of them with K in slices, else one wave each
+  // scores: sixteen rows at a time; column blocks of 64, up to SMALL_W of them with K in slices, else one wave each
   const int tid = small_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int M = rows * k, ncb = (V + 63) / 64, per = ncb < SMALL_W ? ncb : SMALL_W;
   int slices = SMALL_W / per;
@@ -551,54 +581,75 @@ __device__ __forceinline__ void small_forward(const SmallCtx& m, const SmallLds&
   unsigned long long* best = (unsigned long long*)(m.lds + n.best);
   unsigned* cand = (unsigned*)(m.lds + n.best + 512);                // [wave][16][2]
   const rsrc_t wr = rsrc_of(p.emb_t, 0x7FFFFFFF);
+  f32x4 w[4];                                    // (the first ones come while the phases run)
+  unsigned at = 0;
+  if (s < slices && cb0 < ncb) at = small_vocab_load(wr, V, cb0, s * kn, lane, w);
+  small_phases<RQ>(m, n.table, 0, count, rows);
 #pragma unroll 1
   for (int m0 = 0; m0 < M; m0 += 16) {
-    unsigned bu = 0, bi = 0;                     // lane r < 16: best of row r over the columns this wave finished
+    unsigned bu[4] = {0, 0, 0, 0}, bi[4] = {0, 0, 0, 0};           // best of rows 4 (lane / 16) .. over the columns this wave finished
 #pragma unroll 1
     for (int cbase = 0; cbase < ncb; cbase += SMALL_W) {
-      const int lane = small_tid() & 63;
+      const int lane = small_tid() & 63, cb = cbase + cb0;
       f32x4 acc[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-      const int cb = cbase + cb0;
+      for (int i = 0; i < 4; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
       if (s < slices && cb < ncb) {
-        const int col = cb * 64 + (lane & 15) * 4, kk = s * kn + (lane >> 4) * 4;
-        const unsigned at = (unsigned)((col < V ? col : V - 4) + kk * V) * 4;
-        f32x4 w[4];
-        small_load(wr, at, V, w);
-        small_product<4>(wr, at, V, m.lds + n.o + (m0 + (lane & 3)) * ld + kk, ld, kn, w, acc);
+        if (m0 > 0 || cbase > 0) at = small_vocab_load(wr, V, cb, s * kn, lane, w);
+        small_product16(wr, at, V, m.lds + n.o + (m0 + (lane & 15)) * ld + s * kn + (lane >> 4) * 4, kn, w, acc);
       }
       if (slices > 1) {
         if (s < slices) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) red[(wave * 4 + q) * 64 + lane] = acc[q];
+          for (int i = 0; i < 4; ++i) red[(wave * 4 + i) * 64 + lane] = acc[i];
         }
         __syncthreads();
       }
-      // (column block, row quad) pairs: with slices a wave takes the pairs wave, wave + SMALL_W, .., without it has all four quads of its block
+      // two of a lane's four columns at a time: with slices (column block, half) pairs wave, wave + SMALL_W, .., without the wave's own block
 #pragma unroll 1
-      for (int pr = slices > 1 ? wave : 0; pr < (slices > 1 ? per * 4 : 4); pr += slices > 1 ? SMALL_W : 1) {
-        const int c = slices > 1 ? pr >> 2 : cb, q = pr & 3, col = c * 64 + small_col(lane);
-        if (slices == 1 && (cb >= ncb || s > 0)) break;         // (not a block of this wave)
-        const f32x4 v = slices > 1 ? small_partials(red + (c * 4 + q) * 64 + lane, slices, per * 256) : (q == 0 ? acc[0] : (q == 1 ? acc[1] : (q == 2 ? acc[2] : acc[3])));
+      for (int pr = slices > 1 ? wave : 2 * cb; pr < (slices > 1 ? 2 * per : 2 * cb + 2); pr += slices > 1 ? SMALL_W : 1) {
+        const int c = pr >> 1, i0 = (pr & 1) * 2, col = c * 64 + (lane & 15) * 4 + i0, g = lane >> 4;
+        if (c >= ncb || (slices == 1 && s > 0)) break;         // (not a block of this wave)
+        f32x4 v[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) v[e] = slices > 1 ? small_partials(red + (c * 4 + i0 + e) * 64 + lane, slices, per * 256) : (i0 ? acc[2 + e] : acc[e]);
+        const bool in = col < V;
         unsigned key[4], top[4];
+        bool second[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) top[i] = key[i] = col < V ? (unsigned)(argmax_key(v[i], 0u) >> 32) : 0u;
-        small_wave4(top, SmallMax());
+        for (int r = 0; r < 4; ++r) {
+          const unsigned k0 = (unsigned)(argmax_key(v[0][r], 0u) >> 32), k1 = (unsigned)(argmax_key(v[1][r], 0u) >> 32);
+          second[r] = k1 > k0;
+          top[r] = key[r] = in ? (second[r] ? k1 : k0) : 0u;
+        }
+        auto over_lanes = [&](auto step) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int r = 4 * q + i, mm = m0 + r, first = small_first(__ballot(key[i] == top[i] && col < V));
-          // (columns ascend from pair to pair and pass to pass: an equal later one loses)
-          const bool better = lane == r && top[i] > bu;
-          bi = better ? (unsigned)(c * 64 + first) : bi; bu = better ? top[i] : bu;
-          if (mm >= M) continue;
-          if (logits && col < V) logits[(long)mm * V + col] = v[i];
-          if (want_z && col < V && mm % k == 0) m.lds[n.z + mm / k * V + col] = v[i];
+          for (int r = 0; r < 4; ++r) { const unsigned o = step(top[r]); top[r] = o > top[r] ? o : top[r]; }
+        };
+        over_lanes([](unsigned x) { return small_dpp<0xB1>(x); });
+        over_lanes([](unsigned x) { return small_dpp<0x4E>(x); });
+        over_lanes([](unsigned x) { return small_dpp<0x141>(x); });
+        over_lanes([](unsigned x) { return small_dpp<0x140>(x); });
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          // (of equal ones the lowest column: the lowest lane's, and of two pairs' or passes' the lower)
+          const unsigned long long has = __ballot(in && key[r] == top[r]) >> (16 * g), odd = __ballot(second[r]) >> (16 * g);
+          const int first = __ffs((int)((unsigned)has & 0xFFFFu)) - 1;
+          const unsigned at = (unsigned)(c * 64 + first * 4 + i0) + ((unsigned)odd >> (first & 15) & 1u);
+          const bool better = top[r] > bu[r] || (top[r] == bu[r] && at < bi[r]);
+          bi[r] = better ? at : bi[r];
+          bu[r] = better ? top[r] : bu[r];
+          const int mm = m0 + 4 * g + r;
+          if (logits && in && mm < M) { logits[(long)mm * V + col] = v[0][r]; logits[(long)mm * V + col + 1] = v[1][r]; }
+          if (want_z && in && mm < M && mm % k == 0) { m.lds[n.z + mm / k * V + col] = v[0][r]; m.lds[n.z + mm / k * V + col + 1] = v[1][r]; }
         }
       }
       if (slices > 1) __syncthreads();
     }
-    if (lane < 16) *(u32x2*)(cand + (wave * 16 + lane) * 2) = u32x2{bu, bi};
+    if ((lane & 15) == 0) {
+      u32x4* to = (u32x4*)(cand + (wave * 16 + (lane >> 4) * 4) * 2);
+      to[0] = u32x4{bu[0], bi[0], bu[1], bi[1]}; to[1] = u32x4{bu[2], bi[2], bu[3], bi[3]};
+    }
     __syncthreads();
     if (tid < 16 && m0 + tid < M) {
       u32x2 c[SMALL_W];
