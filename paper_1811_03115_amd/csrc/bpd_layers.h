@@ -225,10 +225,10 @@ __device__ __forceinline__ void lk_merge(const float* part, int split, int slot0
   for (int m = hw; m < rows; m += 4) {
     const int s = m / R, r = m - s * R;
     const rsrc_t pr = rsrc_of(part + (size_t)(slot0 + s) * H * split * REC, (unsigned)(H * split * REC) * 4);
-    f32x4 o[4][2];
-    float M[4], L[4];
+    f32x4 o[LK_SPLITS][2];
+    float M[LK_SPLITS], L[LK_SPLITS];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < LK_SPLITS; ++i) {
       const unsigned at = i < split ? (unsigned)((h * split + i) * REC) * 4 : 0x40000000u;         // (past the end: zeros)
       o[i][0] = __builtin_bit_cast(f32x4, lk_load16(pr, at + (r * 64 + dim) * 4));
       o[i][1] = __builtin_bit_cast(f32x4, lk_load16(pr, at + (r * 64 + dim + 4) * 4));
@@ -238,10 +238,10 @@ __device__ __forceinline__ void lk_merge(const float* part, int split, int slot0
     __builtin_amdgcn_sched_barrier(0);
     float top = M[0], l = 0.f;
 #pragma unroll
-    for (int i = 1; i < 4; ++i) top = i < split ? fmaxf(top, M[i]) : top;
+    for (int i = 1; i < LK_SPLITS; ++i) top = i < split ? fmaxf(top, M[i]) : top;
     f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f}, b = a;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < LK_SPLITS; ++i) {
       const float w = i < split && M[i] != -INFINITY ? __expf(M[i] - top) : 0.f;
       l = fmaf(L[i], w, l);
       a += o[i][0] * w; b += o[i][1] * w;

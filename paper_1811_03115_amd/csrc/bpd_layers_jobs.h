@@ -7,11 +7,13 @@ constexpr int LK_NEXT_JOB = LK_XCDS * LK_AREA, LK_WORDS = LK_NEXT_JOB + 768;    
 // Slots of a job: they are dealt evenly to at most LK_JOBS of them, and a job holds at most 16 rows of four slots
 inline int layers_per_job(int slots) { return (slots + LK_JOBS - 1) / LK_JOBS; }
 inline bool layers_fit(int slots, int R) { return layers_per_job(slots) <= LK_PLACES / 8 && layers_per_job(slots) * R <= 16; }
-// Workgroups that share the self-attention of a (head, slot): one per 256 keys (a round of its four waves), as far as there are any
-inline int layers_split(int slots, long keys) {
-  const long want = (keys + 255) / 256, most = LK_PLACES / 8 / layers_per_job(slots);
-  return (int)(want < most ? want : most);
-}
+// Workgroups that share the self-attention of a (head, slot): sharing costs the next operator the merging of their results, and members that fetch weights
+// meanwhile.  Six layers in us, by keys:
+//   one slot per job, 8 jobs of 10 rows   500: 127 alone, 136 .. 137 shared   1000: 141, 143   1300: 153, 149 (three)   1500: 155, 150 (three), 154 (two), 156 (four)   3000: 220, 187
+//   1 job of 10 rows                      600: 124, 130   1000: 133, 137   1300: 145, 140   3000: 188, 159
+//   two slots, 8 jobs of 16 rows          500: 140, 154   1000: 158, 172   2000: 205, 212 (two)
+constexpr int LK_SPLITS = 3;
+inline int layers_split(int slots, long keys) { return keys > 1024 && layers_per_job(slots) == 1 ? LK_SPLITS : 1; }
 // ... and of wide_layers_kernel: one block of at most 16 rows of four slots, caches that a workgroup walks in four rounds
 constexpr long WIDE_LAYERS_KEYS = 1024;
 inline bool wide_layers_fit(int slots, int R, long keys, long src) { return slots <= 4 && slots * R <= 16 && keys <= WIDE_LAYERS_KEYS && src <= WIDE_LAYERS_KEYS; }

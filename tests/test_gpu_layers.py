@@ -49,7 +49,7 @@ def test_ended_sequences(k, B, d):
     lockstep(config(k, B, 4, 4 * k + 1, d=d), 4, np.array([1 + (5 * b) % (4 * k + 1) for b in range(B)], np.int32))
 
 
-# caches of more keys than a workgroup takes in one round: two, three and four workgroups per head, two slots per job, a window.  Both ways the logits
+# caches of more keys than a workgroup takes in one round, of more than 1024, which three workgroups share, two slots per job, a window.  Both ways the logits
 # are within TOL of the oracle's (shown above and for the kernel chain elsewhere), so within twice that of each other.
 @pytest.mark.parametrize("k,B,out,steps,local,d", [(16, 1, 400, 20, 0, 512), (10, 3, 700, 60, 0, 512), (16, 8, 1100, 66, 0, 512), (8, 16, 600, 60, 0, 512), (9, 2, 700, 70, 256, 512),
                                                    (16, 2, 300, 9, 40, 512), (16, 1, 900, 50, 0, 1024), (8, 2, 1100, 125, 0, 1024), (10, 1, 300, 25, 64, 1024)])
