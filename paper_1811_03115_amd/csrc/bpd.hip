@@ -745,12 +745,14 @@ int stack_check(bpd_ctx* ctx) {
 }
 
 // ------------------------------------------------------------------------------- all layers in one kernel (bpd_layers.h)
-enum { LAYERS_CHAIN, LAYERS_JOBS, LAYERS_WIDE };         // kernels one by one, layers_kernel, wide_layers_kernel
+enum { LAYERS_CHAIN, LAYERS_JOBS, LAYERS_WIDE, LAYERS_TALL };         // kernels one by one, layers_kernel, wide_layers_kernel, tall_layers_kernel
 int layers_way(const bpd_ctx* ctx, int slots, int R) {
   const bpd_config& c = ctx->cfg;
   if (!ctx->lay.layers_sync || ctx->layers_group == 0 || ctx->num_cus < LK_JOBS * LK_PLACES) return LAYERS_CHAIN;
   if (layers_shape(c)) return layers_fit(slots, R) ? LAYERS_JOBS : LAYERS_CHAIN;
-  return wide_layers_fit(slots, R, attention_keys(ctx, c.max_out_len + c.k_max + 1, R, 1), c.max_src_len) ? LAYERS_WIDE : LAYERS_CHAIN;
+  const long keys = attention_keys(ctx, c.max_out_len + c.k_max + 1, R, 1);
+  if (wide_layers_fit(slots, R, keys, c.max_src_len)) return LAYERS_WIDE;
+  return ctx->lay.layers_xn && tall_layers_fit(slots, R, keys, c.max_src_len) ? LAYERS_TALL : LAYERS_CHAIN;
 }
 int layers_split_of(const bpd_ctx* ctx, int slots, int R) {
   const bpd_config& c = ctx->cfg;
@@ -782,7 +784,7 @@ void launch_layers(bpd_ctx* ctx, int R, int way) {
   p.self_groups = (int)((slots + 31) / 32); p.src_groups = (c.max_src_len + 31) / 32;
   p.seq = ctx->seq; p.base = ctx->seq ? L.slot_L : L.L; p.src_len = ctx->seq ? L.slot_src : L.src_len;
   p.eps = c.ln_eps; p.scale = 1.0f / sqrtf(64.f); p.local_q = ctx->local_q; p.local_m = ctx->local_m;
-  p.group = way == LAYERS_WIDE ? ctx->layers_group : ctx->layers_group & 63;
+  p.group = way == LAYERS_JOBS ? ctx->layers_group & 63 : ctx->layers_group;
   p.sync = L.layers_sync; p.error = L.stats + 31;
   ctx->layers_ran = true;
   if (way == LAYERS_WIDE) {
@@ -790,6 +792,15 @@ void launch_layers(bpd_ctx* ctx, int R, int way) {
     static bool attr_set = false;
     if (!attr_set) { (void)hipFuncSetAttribute((const void*)wide_layers_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, WkLds::BYTES); attr_set = true; }
     hipLaunchKernelGGL(wide_layers_kernel, dim3(WK_XCDS * LK_PLACES), dim3(512), WkLds::BYTES, ctx->stream, p);
+    return;
+  }
+  if (way == LAYERS_TALL) {
+    p.jobs = p.per_job = p.split = 0;
+    p.xn = (bf16_t*)L.layers_xn; p.x2 = L.layers_x2; p.part = L.kpart;
+    static bool attr_set = false;
+    if (!attr_set) { (void)hipFuncSetAttribute((const void*)tall_layers_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, TkLds::BYTES); attr_set = true; }
+    hipLaunchKernelGGL(tall_layers_kernel, dim3(WK_XCDS * LK_PLACES), dim3(512), TkLds::BYTES, ctx->stream, p);
+    ctx->pend_slices = 4; ctx->pend_bias = L.dec[c.n_dec_layers - 1].b2; ctx->pend_x = L.x;
     return;
   }
   const bool nt = (size_t)2 * c.n_dec_layers * ctx->Bs * slots * d * 2 > ((size_t)128 << 20);       // (as in attention())

@@ -901,6 +901,7 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnP p) {
 #include "bpd_row_gemm.h"
 #include "bpd_layers.h"
 #include "bpd_wide_layers.h"
+#include "bpd_tall_layers.h"
 
 // Merge of the nsplit partial results of attention_kernel: with M the largest of the partial
 // maxima, output = sum_s acc_s e^(m_s - M) / sum_s l_s e^(m_s - M).  Grid (heads, B, row tiles).

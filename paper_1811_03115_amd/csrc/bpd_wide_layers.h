@@ -227,7 +227,7 @@ struct WkHelper {
   }
   __device__ __forceinline__ static int sequence(int slot) { const LayersP& p = lk_args(); return p.seq ? lk_const(p.seq, slot) : slot; }
 
-  template <int G>
+  template <int G, int NF>
   __device__ __forceinline__ void self_item(int l, int item, bool first_item) {
     const LayersP& p = lk_args();
     const int lane = lk_lane(), lr = lane & 15, lq = lane >> 4;
@@ -246,7 +246,7 @@ struct WkHelper {
       unsigned t[G];
 #pragma unroll
       for (int g = 0; g < G; ++g) t[g] = __builtin_amdgcn_raw_buffer_load_b32(lane < 32 ? kr : vr, (lane & 31) * 128, (first + hw + g * 4) * (KV_GROUP * 2), 16);
-      lk_wait<1>(area() + WK_LOCAL, op - 1, 8, 24, lane, broken, p.error);
+      lk_wait<NF>(area() + WK_LOCAL, op - 1, 8, 24, lane, broken, p.error);
 #pragma unroll
       for (int g = 0; g < G; ++g) asm volatile("" ::"v"(t[g]));
     } else {
@@ -281,55 +281,58 @@ struct WkHelper {
     for (int place = j.place; place < 256; place += j.members) {
       const int item = j.item(WK_SELF, place);
       if (item < 0) continue;
-      if (few) self_item<1>(l, item, !mine); else self_item<2>(l, item, !mine);
+      if (few) self_item<1, 1>(l, item, !mine); else self_item<2, 1>(l, item, !mine);
       mine = true;
     }
     heads_done(WK_SELF, mine);
   }
-  __device__ __forceinline__ void cross_attention(int l) {
+  __device__ __forceinline__ void cross_item(int l, int item, const float* x, bool first_item) {
     const LayersP& p = lk_args();
     const int lane = lk_lane(), lr = lane & 15, lq = lane >> 4;
     const AttnP a = attn_args(false);
+    const int h = item & 15, slot = item >> 4, s = sequence(slot);
+    const size_t at = l * p.src_layer + ((size_t)(s < 0 ? 0 : s) * H + h) * p.src_groups * KV_GROUP;
+    const rsrc_t kr = rsrc_of(p.crossK + at, (unsigned)p.src_groups * (KV_GROUP * 2)), vr = rsrc_of(p.crossV + at, (unsigned)p.src_groups * (KV_GROUP * 2));
+    u32x4 kf[1][4], vf[1][4];
+    f32x4 g[4], b[4];
+    load_norm((const float*)((const char*)p.ln2 + l * p.stride), g, b, lane);
+    attn_load_kv<false, 1>(kr, vr, hw, 4, lane, kf, vf);
+    const int lim = lk_const(p.src_len, slot);
+    if (first_item) wait(op - 1);
+    else lk_barrier();                         // the results of the item before are out of LDS
+      wk_norm(x + (size_t)slot * p.R * D, p.R, g, b, p.eps, xs, hw, lane);
+    lk_barrier();
+    lk_barrier();
+    {
+      f32x4 v = partial_sums(4, hw, lane);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] *= p.scale;
+      const u32x2 hi = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
+      const u32x2 lo = u32x2{cvt_pk_bf16(v[0] - __uint_as_float(hi[0] << 16), v[1] - __uint_as_float(hi[0] & 0xFFFF0000u)),
+                             cvt_pk_bf16(v[2] - __uint_as_float(hi[1] << 16), v[3] - __uint_as_float(hi[1] & 0xFFFF0000u))};
+      // operand lane 16 q + lr of half s holds columns 32 s + 8 q .. + 7
+      const int to = ((hw >> 1) * 64 + ((hw & 1) * 2 + (lq >> 1)) * 16 + lr) * 2 + (lq & 1);
+      q_s[to] = hi; q_s[256 + to] = lo;
+    }
+    lk_barrier();
+    bf16x8 qhi[2], qlo[2];
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2) {
+      qhi[s2] = __builtin_bit_cast(bf16x8, *(const u32x4*)&q_s[(s2 * 64 + lane) * 2]);
+      qlo[s2] = __builtin_bit_cast(bf16x8, *(const u32x4*)&q_s[256 + (s2 * 64 + lane) * 2]);
+    }
+    if (s < 0) { lk_barrier(); return; }     // (as the attention's own)
+    attention_mfma_core<false, false, 0, 1, true>(a, sm, h, slot, 0, 0, 0, p.R, H, 1, hw * 64 + lane, 4, 0, 4, kr, vr, kf, vf, qhi, qlo, lim, p.attn);
+  }
+  __device__ __forceinline__ void cross_attention(int l) {
     ++op;
     bool mine = false;
 #pragma unroll 1
     for (int place = j.place; place < 256; place += j.members) {
       const int item = j.item(WK_CROSS, place);
       if (item < 0) continue;
-      const int h = item & 15, slot = item >> 4, s = sequence(slot);
-      const size_t at = l * p.src_layer + ((size_t)(s < 0 ? 0 : s) * H + h) * p.src_groups * KV_GROUP;
-      const rsrc_t kr = rsrc_of(p.crossK + at, (unsigned)p.src_groups * (KV_GROUP * 2)), vr = rsrc_of(p.crossV + at, (unsigned)p.src_groups * (KV_GROUP * 2));
-      u32x4 kf[1][4], vf[1][4];
-      f32x4 g[4], b[4];
-      load_norm((const float*)((const char*)p.ln2 + l * p.stride), g, b, lane);
-      attn_load_kv<false, 1>(kr, vr, hw, 4, lane, kf, vf);
-      const int lim = lk_const(p.src_len, slot);
-      if (!mine) wait(op - 1);
-      else lk_barrier();                         // the results of the item before are out of LDS
+      cross_item(l, item, lk_args().x, !mine);
       mine = true;
-      wk_norm(p.x + (size_t)slot * p.R * D, p.R, g, b, p.eps, xs, hw, lane);
-      lk_barrier();
-      lk_barrier();
-      {
-        f32x4 v = partial_sums(4, hw, lane);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] *= p.scale;
-        const u32x2 hi = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
-        const u32x2 lo = u32x2{cvt_pk_bf16(v[0] - __uint_as_float(hi[0] << 16), v[1] - __uint_as_float(hi[0] & 0xFFFF0000u)),
-                               cvt_pk_bf16(v[2] - __uint_as_float(hi[1] << 16), v[3] - __uint_as_float(hi[1] & 0xFFFF0000u))};
-        // operand lane 16 q + lr of half s holds columns 32 s + 8 q .. + 7
-        const int to = ((hw >> 1) * 64 + ((hw & 1) * 2 + (lq >> 1)) * 16 + lr) * 2 + (lq & 1);
-        q_s[to] = hi; q_s[256 + to] = lo;
-      }
-      lk_barrier();
-      bf16x8 qhi[2], qlo[2];
-#pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) {
-        qhi[s2] = __builtin_bit_cast(bf16x8, *(const u32x4*)&q_s[(s2 * 64 + lane) * 2]);
-        qlo[s2] = __builtin_bit_cast(bf16x8, *(const u32x4*)&q_s[256 + (s2 * 64 + lane) * 2]);
-      }
-      if (s < 0) { lk_barrier(); continue; }     // (as the attention's own)
-      attention_mfma_core<false, false, 0, 1, true>(a, sm, h, slot, 0, 0, 0, p.R, H, 1, hw * 64 + lane, 4, 0, 4, kr, vr, kf, vf, qhi, qlo, lim, p.attn);
     }
     heads_done(WK_CROSS, mine);
   }
@@ -445,18 +448,11 @@ struct WkLds {
   static_assert(ATTN + (int)AttnLds::BYTES + 512 * 8 <= XS && BYTES <= 160 * 1024, "LDS");
 };
 
-__global__ __launch_bounds__(512, 2) void wide_layers_kernel(LayersP p) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char lk_smem[];
-  bf16_t* xs = (bf16_t*)lk_smem;
-  f32x4* red = (f32x4*)(lk_smem + WkLds::XS);
-  unsigned char* attn = lk_smem + WkLds::ATTN;
-  u32x2* q_s = (u32x2*)(attn + AttnLds::BYTES);
-  int* word = (int*)(lk_smem + WkLds::XS + WkLds::RED);
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int xcd = __builtin_amdgcn_readfirstlane((int)lk_xcd());
+// Registers the workgroup: its part in j, or false if it has none
+__device__ __forceinline__ bool wk_register(const LayersP& p, int* word, int wave, int lane, int xcd, WkMember& j) {
   const int group = p.group & 63, most_xcds = p.group >> 6 ? p.group >> 6 : WK_XCDS;
   unsigned* area = p.sync + xcd * WK_AREA;
-  if (xcd >= most_xcds) return;
+  if (xcd >= most_xcds) return false;
   if (wave == 0) {
     unsigned old = 0;
     if (lane == 0) old = __hip_atomic_fetch_add(area, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -507,13 +503,26 @@ __global__ __launch_bounds__(512, 2) void wide_layers_kernel(LayersP p) {
     if (lane == 0) word[0] = rank;
   }
   lk_barrier();
-  WkMember j;
   j.rank = __builtin_amdgcn_readfirstlane(word[0]);
-  if (j.rank < 0) return;
+  if (j.rank < 0) return false;
   j.members = __builtin_amdgcn_readfirstlane(word[1]); j.place = __builtin_amdgcn_readfirstlane(word[2]);
   j.here = __builtin_amdgcn_readfirstlane(word[3]); j.xcds = (unsigned)__builtin_amdgcn_readfirstlane(word[4]);
   j.xcd = xcd; j.full = j.members == WK_XCDS * LK_PLACES;
   j.slots = p.slots; j.rows = p.slots * p.R;
+  return true;
+}
+
+__global__ __launch_bounds__(512, 2) void wide_layers_kernel(LayersP p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lk_smem[];
+  bf16_t* xs = (bf16_t*)lk_smem;
+  f32x4* red = (f32x4*)(lk_smem + WkLds::XS);
+  unsigned char* attn = lk_smem + WkLds::ATTN;
+  u32x2* q_s = (u32x2*)(attn + AttnLds::BYTES);
+  int* word = (int*)(lk_smem + WkLds::XS + WkLds::RED);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int xcd = __builtin_amdgcn_readfirstlane((int)lk_xcd());
+  WkMember j;
+  if (!wk_register(p, word, wave, lane, xcd, j)) return;
   if (wave >= 4) {
     WkCompute c{xs, red, wave - 4, j};
     c.run();

@@ -1,5 +1,5 @@
-"""All decoder layers as one kernel: a job of up to 16 rows per XCD (d = 512, d_ff = 2048), or one block of up to 16 rows on the whole chip (d = 1024, d_ff =
-4096).  Rows and slots at their limits, long caches, whose attention several workgroups may share, groups that are not full, and sequences that end."""
+"""All decoder layers as one kernel: a job of up to 16 rows per XCD (d = 512, d_ff = 2048), or one block of up to 16 or of 17 .. 48 rows on the whole chip (d =
+1024, d_ff = 4096).  Rows and slots at their limits, long caches, whose attention several workgroups may share, groups that are not full, and sequences that end."""
 import numpy as np
 import pytest
 import torch
@@ -36,15 +36,22 @@ def test_wide_rows_and_slots(k, B, S):
     lockstep(config(k, B, S, 3 * k + 4, d=1024), 3)
 
 
+# two and three row tiles, one row of the second and of the third, all slots and rows there can be; up to four slots the attentions have members of their own
+@pytest.mark.parametrize("k,B,S", [(16, 3, 33), (9, 2, 5), (8, 5, 50), (11, 3, 3), (6, 8, 140), (10, 4, 20), (3, 6, 1), (5, 7, 70)])
+def test_tall_rows_and_slots(k, B, S):
+    lockstep(config(k, B, S, 3 * k + 4, d=1024), 3)
+
+
 # groups of fewer workgroups than places, and one that waits until its time is up; d = 1024: fewer XCDs, too
 @pytest.mark.parametrize("group,k,B,d", [(1, 7, 2, 512), (5, 8, 16, 512), (31, 10, 3, 512), (33, 4, 9, 512),
-                                         (5, 10, 1, 1024), (31, 4, 4, 1024), (33, 7, 2, 1024), (32 + 64 * 3, 5, 3, 1024), (3 + 64, 3, 1, 1024)])
+                                         (5, 10, 1, 1024), (31, 4, 4, 1024), (33, 7, 2, 1024), (32 + 64 * 3, 5, 3, 1024), (3 + 64, 3, 1, 1024),
+                                         (5, 10, 4, 1024), (33, 6, 8, 1024), (32 + 64 * 3, 8, 5, 1024), (3 + 64, 9, 2, 1024)])
 def test_groups(group, k, B, d, monkeypatch):
     monkeypatch.setenv("BPD_LAYERS_GROUP", str(group))
     lockstep(config(k, B, 5, 3 * k + 4, d=d), 3)
 
 
-@pytest.mark.parametrize("k,B,d", [(4, 9, 512), (6, 13, 512), (4, 4, 1024)])
+@pytest.mark.parametrize("k,B,d", [(4, 9, 512), (6, 13, 512), (4, 4, 1024), (6, 8, 1024)])
 def test_ended_sequences(k, B, d):
     lockstep(config(k, B, 4, 4 * k + 1, d=d), 4, np.array([1 + (5 * b) % (4 * k + 1) for b in range(B)], np.int32))
 
@@ -52,7 +59,7 @@ def test_ended_sequences(k, B, d):
 # caches of more keys than a workgroup takes in one round, of more than 1024, which three workgroups share, two slots per job, a window.  Both ways the logits
 # are within TOL of the oracle's (shown above and for the kernel chain elsewhere), so within twice that of each other.
 @pytest.mark.parametrize("k,B,out,steps,local,d", [(16, 1, 400, 20, 0, 512), (10, 3, 700, 60, 0, 512), (16, 8, 1100, 66, 0, 512), (8, 16, 600, 60, 0, 512), (9, 2, 700, 70, 256, 512),
-                                                   (16, 2, 300, 9, 40, 512), (16, 1, 900, 50, 0, 1024), (8, 2, 1100, 125, 0, 1024), (10, 1, 300, 25, 64, 1024)])
+                                                   (16, 2, 300, 9, 40, 512), (16, 1, 900, 50, 0, 1024), (8, 2, 1100, 125, 0, 1024), (10, 1, 300, 25, 64, 1024), (10, 3, 700, 60, 0, 1024), (6, 8, 300, 40, 64, 1024)])
 def test_long_caches(k, B, out, steps, local, d, monkeypatch):
     cfg = config(k, B, 35, out, layers=1, d=d, local_q=local, local_m=local)
     weights = wl.make_weights(cfg)
@@ -74,7 +81,7 @@ def test_long_caches(k, B, out, steps, local, d, monkeypatch):
     assert np.isfinite(a).all() and np.abs(a - b).max() <= 2 * TOL["bf16"], np.abs(a - b).max()
 
 
-@pytest.mark.parametrize("k,B,d", [(8, 8, 512), (8, 2, 1024)])
+@pytest.mark.parametrize("k,B,d", [(8, 8, 512), (8, 2, 1024), (8, 5, 1024)])
 def test_two_streams(k, B, d):
     """Contexts on streams of their own, decoding at the same time: the workgroups of both launches share the CUs."""
     import threading
