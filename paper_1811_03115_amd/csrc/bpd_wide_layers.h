@@ -25,7 +25,8 @@ static_assert(WK_XCDS * WK_AREA <= LK_WORDS, "both kernels count in the same wor
 
 __device__ __forceinline__ void wk_store4(unsigned* p, unsigned v) { asm volatile("global_store_dword %0, %1, off sc1" ::"v"(p), "v"(v) : "memory"); }
 __device__ __forceinline__ void wk_store8(void* p, u32x2 v) { asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory"); }
-__device__ __forceinline__ void wk_store16(void* p, f32x4 v) { asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory"); }
+// (more than 64 bits: two wait states until an instruction may write the data registers, which the compiler cannot see to here)
+__device__ __forceinline__ void wk_store16(void* p, f32x4 v) { asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory"); }
 __device__ __forceinline__ void wk_store2(bf16_t* p, unsigned v) { asm volatile("global_store_short %0, %1, off sc1" ::"v"(p), "v"(v) : "memory"); }
 
 // LayerNorm of up to 16 rows of 1024 into LDS as bf16, rows 1032 apart; wave hw takes rows hw, hw + 4, ..
