@@ -56,30 +56,36 @@ struct TkHelper : WkHelper {
     if (lane < WK_XCDS) wk_store4(lk_args().sync + lane * WK_AREA + WK_GLOBAL + j.xcd, op);
   }
 
-  // Row m of layer l's residual stream, with the slices of the layer before (merge); writes it on where `keep`, and its LayerNorm as bf16 to `to`
-  __device__ __forceinline__ void norm_row(int l, int m, bool merge, bool keep, const f32x4 (&g)[4], const f32x4 (&b)[4], const f32x4 (&bias)[4], bf16_t* to) {
+  // Row m of layer l's residual stream: of its buffer or, first, what the layer before left (merge)
+  __device__ __forceinline__ void load_row(int l, int m, bool merge, f32x4 (&v)[4]) {
     const LayersP& p = lk_args();
     const int lane = lk_lane();
     const float* from = merge ? (l > 0 ? residual(l - 1) : p.x) : residual(l);
     const rsrc_t xr = rsrc_of(from, (unsigned)j.rows * D * 4), pr = rsrc_of(p.part, (unsigned)j.rows * D * 16);
-    f32x4 v[4], s[4][4];
+    f32x4 s[4][4], bias[4];
 #pragma unroll
     for (int h = 0; h < 4; ++h) v[h] = __builtin_bit_cast(f32x4, lk_load16(xr, (m * D + h * 256 + lane * 4) * 4));
     if (merge && l > 0) {
+      const float* b2 = (const float*)((const char*)p.b2 + (l - 1) * p.stride);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int h = 0; h < 4; ++h) s[i][h] = __builtin_bit_cast(f32x4, lk_load16(pr, ((i * j.rows + m) * D + h * 256 + lane * 4) * 4));
+#pragma unroll
+      for (int h = 0; h < 4; ++h) bias[h] = *(const f32x4*)(b2 + h * 256 + lane * 4);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int h = 0; h < 4; ++h) v[h] += (((s[0][h] + s[1][h]) + s[2][h]) + s[3][h]) + bias[h];
     }
     __builtin_amdgcn_sched_barrier(0);
-    if (keep) {
-      float* x = (float*)residual(l) + (size_t)m * D;
+  }
+  __device__ __forceinline__ void keep_row(int l, int m, const f32x4 (&v)[4]) {
+    float* x = (float*)residual(l) + (size_t)m * D;
 #pragma unroll
-      for (int h = 0; h < 4; ++h) wk_store16(x + h * 256 + lane * 4, v[h]);
-    }
+    for (int h = 0; h < 4; ++h) wk_store16(x + h * 256 + lk_lane() * 4, v[h]);
+  }
+  __device__ __forceinline__ void norm_row(f32x4 (&v)[4], const f32x4 (&g)[4], const f32x4 (&b)[4], bf16_t* to) {
+    const int lane = lk_lane();
     const f32x4 t = (v[0] + v[1]) + (v[2] + v[3]);
     const float mu = wave_sum((t[0] + t[1]) + (t[2] + t[3])) * (1.f / D);
     f32x4 q = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -89,7 +95,7 @@ struct TkHelper : WkHelper {
 #pragma unroll
       for (int r = 0; r < 4; ++r) q[r] = fmaf(v[h][r], v[h][r], q[r]);
     }
-    const float rs = inv_sqrt(fmaf(wave_sum((q[0] + q[1]) + (q[2] + q[3])), 1.f / D, p.eps));
+    const float rs = inv_sqrt(fmaf(wave_sum((q[0] + q[1]) + (q[2] + q[3])), 1.f / D, lk_args().eps));
 #pragma unroll
     for (int h = 0; h < 4; ++h) {
       f32x4 y;
@@ -98,6 +104,8 @@ struct TkHelper : WkHelper {
       *(u32x2*)(to + h * 256 + lane * 4) = u32x2{cvt_pk_bf16(y[0], y[1]), cvt_pk_bf16(y[2], y[3])};
     }
   }
+  // Does layer l's first LayerNorm find its rows in another buffer than its own?
+  __device__ __forceinline__ bool moved(int l) const { return l > 0 || residual(0) != lk_args().x; }
   // bf16 rows of 1024 (ld: bytes between them) into LDS, 1032 apart
   __device__ __forceinline__ void stage(const bf16_t* src, unsigned ld) {
     const int lane = lk_lane();
@@ -119,24 +127,23 @@ struct TkHelper : WkHelper {
   __device__ __forceinline__ void stage_norm(int l, const float* ln, bool merge) {
     const LayersP& p = lk_args();
     const int lane = lk_lane(), m = hw < 2 && j.rank >= 8 ? hw * 24 + j.rank - 8 : TK_ROWS;         // (full: the members with queries, keys and values)
-    f32x4 g[4], b[4], bias[4];
+    f32x4 g[4], b[4], v[4];
     load_norm(ln, g, b, lane);
-    if (merge && l > 0) {
-      const float* b2 = (const float*)((const char*)p.b2 + (l - 1) * p.stride);
-#pragma unroll
-      for (int h = 0; h < 4; ++h) bias[h] = *(const f32x4*)(b2 + h * 256 + lane * 4);
-    }
     wait(op - 1);
-    const bool moved = merge && (l > 0 || residual(0) != p.x);
     if (!j.full) {
 #pragma unroll 1
-      for (int r = hw; r < j.rows; r += 4) norm_row(l, r, merge, moved && j.place == 8 % j.members, g, b, bias, xs + r * (D + 8));      // (place 8: the first with a tile here)
+      for (int r = hw; r < j.rows; r += 4) {
+        load_row(l, r, merge, v);
+        if (merge && moved(l) && j.place == 8 % j.members) keep_row(l, r, v);      // (place 8: the first with a tile here)
+        norm_row(v, g, b, xs + r * (D + 8));
+      }
       return;
     }
     bf16_t* mine = p.xn + (size_t)j.xcd * TK_ROWS * D;
     unsigned* flags = area() + WK_NORM;
     if (m < j.rows) {
-      norm_row(l, m, merge, moved && j.xcd == 0, g, b, bias, mine + (size_t)m * D);
+      load_row(l, m, merge, v);
+      norm_row(v, g, b, mine + (size_t)m * D);
       lk_raise(flags + m, op, lane);
     }
     if (!broken) {
@@ -214,6 +221,14 @@ struct TkHelper : WkHelper {
         wk_store16((float*)residual(l) + (size_t)m * D + n, v);
       }
     }
+    // Members without queries, keys and values carry the residual stream over to the layer's own buffer (one of those that normalise it took 1.2 us
+    // longer for it, and all waited).  Their flags count with the self-attention's: the next operator that reads it follows that
+    if (OP == WK_QKV && j.full && j.rank < 8 && hw == 0 && moved(l) && j.rank * 8 + j.xcd < j.rows) {
+      f32x4 v[4];
+      wait(op - 1);
+      load_row(l, j.rank * 8 + j.xcd, true, v);
+      keep_row(l, j.rank * 8 + j.xcd, v);
+    }
     constexpr unsigned MASK = OP == WK_QKV ? 0xFFFFFF00u : (OP == WK_O ? 0xFF00u : (OP == WK_CO ? 0xFF0000u : 0xFFFFFFFFu));
     done<TK_MT>(staged, MASK, OP != WK_QKV);
   }
@@ -231,7 +246,7 @@ struct TkHelper : WkHelper {
       else self_item<2, TK_MT>(l, item, !mine);
       mine = true;
     }
-    done<4>(mine, TkPlaces::item_mask(OP, j.slots), true);
+    done<4>(mine || (OP == WK_SELF && j.rank < 8), TkPlaces::item_mask(OP, j.slots) | (OP == WK_SELF ? 0xFFu : 0u), true);
   }
   __device__ __forceinline__ void run() {
     const int layers = lk_args().n_layers;
