@@ -107,7 +107,8 @@ bool small_shape(const bpd_config& c) {
 
 // Does one workgroup per sequence beat the launches?  It walks the phases of the layers one after the other, with weights at the rate
 // one CU gets and keys 64 at a time by eight waves; the launches cost 4.4 us each and their products walk K serially.  Estimates in
-// us, their constants fitted to 27 steps and 21 encodes, which they are within 30 % of (one, launches; tests/host checks all):
+// us, their constants fitted to 27 steps and 21 encodes, which they are within 30 % of (one, launches; tests/host checks all; the steps of one
+// workgroup have become a quarter to a third shorter since, so that the rule errs towards the launches):
 //   steps    d = 64, 2 layers, 4 rows   64 keys: 71, 157   512: 102, 163   1000: 135, 158   1900: 197, 164   3900: 364, 175
 //            d = 64, 8 layers, 16 rows  1 key: 563, 498    1000: 1698, 537         d = 64, 2 layers, 12 rows  1 key: 185, 143
 //            d = 128, 2 layers, 4 rows  1: 118, 180        1000: 272, 197          d = 256, 1 layer, 4 rows   1: 154, 144

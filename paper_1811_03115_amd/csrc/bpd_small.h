@@ -3,10 +3,12 @@
 // A step of a two-layer, 64-wide model is some 27 dependent kernels of 2 .. 10 us, 125 us in all, for 1 MB of weights and 1.2
 // million multiply-adds: launches and nothing else.  Sequences do not depend on each other, so one workgroup of eight waves
 // takes a sequence through all its steps: activations in LDS, weights out of the L2 (they stay there), barriers instead
-// of launches.  What bounds it is the number of dependent phases (eight per layer: one trip to the L2, the partial sums'
-// meeting in LDS) and, within them, instructions: every phase is one copy of the same code, driven by a table in LDS, and
-// the products run on v_mfma_f32_4x4x1_16b: 4 rows x 64 columns per instruction and k, fp32, the lane's column of weights as it
-// comes from memory (plain multiply-adds, with 16 LDS reads of the rows for 64 of them, took 80 us per step).
+// of launches.  What bounds it is the number of dependent phases (eight per layer: the partial sums' meeting in LDS, two barriers) and, within
+// them, instructions at two waves per SIMD: every phase is one copy of the same code, driven by a table in LDS.  The products run on
+// v_mfma_f32_4x4x1_16b, fp32, with weights as they come from memory 16 bytes a lane, requested a phase ahead (small_load, SmallFetch).  A
+// step of 4 rows at d = 64, two layers, takes 88,000 cycles: 2,200 .. 5,300 a phase, 8,400 and 7,000 the heads' two (512 KB of weights at the
+// 64 bytes a cycle that a CU gets: 8,200 together), 8,300 the scores (fp32 matrix rate: 2,000).  (Loads of 4 bytes a lane behind the barrier: 125,000.  Plain
+// multiply-adds, with 16 LDS reads of the rows for 64 of them, took 80 us instead of 68 before that.)
 #pragma once
 
 constexpr int SMALL_T = 512, SMALL_W = SMALL_T / 64;      // threads and waves of the workgroup

@@ -14,6 +14,10 @@
 // this hand-over stays inside it: plain stores, local flags);  8 .. 15, 16 .. 23: output projections of the self- and the cross-attention;  24 ..:
 // cross-attention, beside the self-attention where there is room.
 //
+// Six layers of 10 rows, 40 keys, 32 source tokens: 204 us as a chain of 60 kernels, 147 here (with no weights fetched: 142), of one row 124, of 16 rows
+// in four slots 157.  What bounds it is the hand-over, six times a layer between XCDs: results acknowledged 0.2 .. 0.5 us, flags gathered 0.3 .. 0.5,
+// seen elsewhere 0.5 .. 0.8; then the input's staging (0.5 us, with LayerNorm of ten rows 1.35) and 0.7 from there to the stores.
+//
 // Members register as in bpd_layers.h.  The first on each XCD closes its list when 32 have come or LK_CLOSE_TICKS have passed, and tells all XCDs
 // how many there are; an XCD where nobody has come is closed by others.  Fewer than 256 members share the places out, fetch weights as
 // they go and hand everything over through memory.
