@@ -257,10 +257,13 @@ enum { LK_QKV, LK_RELU, LK_RES };
 // What a member knows of its group and job
 struct LkJob {
   int rank, members, slot0, slots, rows, row0;
-  // The cross-attention's places (slot, head) start behind the self-attention's first ones where there is room: a member that idles
+  // The cross-attention's places (slot, head) start behind the self-attention's where there is room: a member that idles
   // in one of the two fetches weights then
   __device__ __forceinline__ int cross_places() const { return 8 * slots; }
-  __device__ __forceinline__ int cross_first() const { return members == LK_PLACES && slots <= 2 ? 8 * slots : 0; }
+  __device__ __forceinline__ int cross_first() const {
+    const int first = 8 * slots * lk_args().split;
+    return members == LK_PLACES && first + 8 * slots <= LK_PLACES ? first : 0;
+  }
   __device__ __forceinline__ int cross() const { const int c = rank - cross_first(); return c < 0 ? c + LK_PLACES : c; }
 };
 

@@ -9,7 +9,7 @@ inline int layers_per_job(int slots) { return (slots + LK_JOBS - 1) / LK_JOBS; }
 inline bool layers_fit(int slots, int R) { return layers_per_job(slots) <= LK_PLACES / 8 && layers_per_job(slots) * R <= 16; }
 // Workgroups that share the self-attention of a (head, slot): sharing costs the next operator the merging of their results, and members that fetch weights
 // meanwhile.  Six layers in us, by keys:
-//   one slot per job, 8 jobs of 10 rows   500: 127 alone, 136 .. 137 shared   1000: 141, 143   1300: 153, 149 (three)   1500: 155, 150 (three), 154 (two), 156 (four)   3000: 220, 187
+//   one slot per job, 8 jobs of 10 rows   500: 127 alone, 130 (two), 133 (three)   1000: 141, 142 (two), 144 (three)   1300: 153, 149 (three)   1500: 155, 150 (two, three), 156 (four)   3000: 220, 178 (three), 188 (two)
 //   1 job of 10 rows                      600: 124, 130   1000: 133, 137   1300: 145, 140   3000: 188, 159
 //   two slots, 8 jobs of 16 rows          500: 140, 154   1000: 158, 172   2000: 205, 212 (two)
 constexpr int LK_SPLITS = 3;
