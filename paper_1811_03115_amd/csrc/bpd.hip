@@ -766,6 +766,12 @@ void launch_layers_kernel(const bpd_ctx* ctx, const LayersP& p) {
   if (!attr_set) { (void)hipFuncSetAttribute((const void*)layers_kernel<2048, KVNT>, hipFuncAttributeMaxDynamicSharedMemorySize, LkLds<2048>::BYTES); attr_set = true; }
   hipLaunchKernelGGL((layers_kernel<2048, KVNT>), dim3(LK_JOBS * LK_PLACES), dim3(512), LkLds<2048>::BYTES, ctx->stream, p);
 }
+template <int MT>
+void launch_tall_layers(const bpd_ctx* ctx, const LayersP& p) {
+  static bool attr_set = false;
+  if (!attr_set) { (void)hipFuncSetAttribute((const void*)tall_layers_kernel<MT>, hipFuncAttributeMaxDynamicSharedMemorySize, TkLds<MT>::BYTES); attr_set = true; }
+  hipLaunchKernelGGL(tall_layers_kernel<MT>, dim3(WK_XCDS * LK_PLACES), dim3(512), TkLds<MT>::BYTES, ctx->stream, p);
+}
 void launch_layers(bpd_ctx* ctx, int R, int way) {
   const bpd_config& c = ctx->cfg;
   Layout& L = ctx->lay;
@@ -797,9 +803,10 @@ void launch_layers(bpd_ctx* ctx, int R, int way) {
   if (way == LAYERS_TALL) {
     p.jobs = p.per_job = p.split = 0;
     p.xn = (bf16_t*)L.layers_xn; p.x2 = L.layers_x2; p.part = L.kpart;
-    static bool attr_set = false;
-    if (!attr_set) { (void)hipFuncSetAttribute((const void*)tall_layers_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, TkLds::BYTES); attr_set = true; }
-    hipLaunchKernelGGL(tall_layers_kernel, dim3(WK_XCDS * LK_PLACES), dim3(512), TkLds::BYTES, ctx->stream, p);
+    const int tiles = (ctx->Bs * R + 15) / 16;
+    if (tiles <= 2) launch_tall_layers<2>(ctx, p);
+    else if (tiles == 3) launch_tall_layers<3>(ctx, p);
+    else launch_tall_layers<4>(ctx, p);
     ctx->pend_slices = 4; ctx->pend_bias = L.dec[c.n_dec_layers - 1].b2; ctx->pend_x = L.x;
     return;
   }

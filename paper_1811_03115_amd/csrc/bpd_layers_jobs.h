@@ -16,7 +16,7 @@ constexpr int LK_SPLITS = 3;
 inline int layers_split(int slots, long keys) { return keys > 1024 && layers_per_job(slots) == 1 ? LK_SPLITS : 1; }
 // ... and of wide_layers_kernel: one block of at most 16 rows of four slots, caches that a workgroup walks in four rounds
 constexpr long WIDE_LAYERS_KEYS = 1024;
-// tall_layers_kernel: more rows, of up to eight slots
-constexpr int TALL_LAYERS_ROWS = 48;
-inline bool tall_layers_fit(int slots, int R, long keys, long src) { return slots <= 8 && R <= 16 && slots * R > 16 && slots * R <= TALL_LAYERS_ROWS && keys <= WIDE_LAYERS_KEYS && src <= WIDE_LAYERS_KEYS; }
+// tall_layers_kernel: more rows, of up to 16 slots
+constexpr int TALL_LAYERS_ROWS = 64;
+inline bool tall_layers_fit(int slots, int R, long keys, long src) { return slots <= 16 && R <= 16 && slots * R > 16 && slots * R <= TALL_LAYERS_ROWS && keys <= WIDE_LAYERS_KEYS && src <= WIDE_LAYERS_KEYS; }
 inline bool wide_layers_fit(int slots, int R, long keys, long src) { return slots <= 4 && slots * R <= 16 && keys <= WIDE_LAYERS_KEYS && src <= WIDE_LAYERS_KEYS; }

@@ -1,37 +1,42 @@
-// As bpd_wide_layers.h, for blocks of 17 .. 48 rows of up to eight slots: three MFMA row tiles.  Included by bpd_kernels.h behind it.
+// As bpd_wide_layers.h, for blocks of 17 .. 64 rows of up to 16 slots: MT = 2 .. 4 MFMA row tiles.  Included by bpd_kernels.h behind it.
 //
 // With one row tile every member normalises all rows of an operator's input itself, which costs 0.42 us a row and wave: here a wave has
 // one row, and the XCD's waves hand their rows on inside the XCD (every XCD normalises all rows: a hand-over between XCDs
 // costs more than the row).  The second FFN layer (four times as long as the others) is split over K among four members per tile, all 256 of
-// them: each multiplies 1024 of 4096, as everywhere else, so that one staging buffer of 48 x 1024 holds any input; the LayerNorm that follows adds the
+// them: each multiplies 1024 of 4096, as everywhere else, so that one staging buffer of 16 MT x 1024 holds any input; the LayerNorm that follows adds the
 // four slices, and so does ln_row_kernel behind the last layer.  Since every XCD reads the residual stream that this LayerNorm writes, two
 // buffers of it take turns; the last layer's is LayersP::x.
 //
-// Six layers of 40 rows in five slots: 264 us as a chain of 60 kernels, 185 here; of 18 rows in two slots 170, of 48 in three 194.  It is bound as the other
-// is, by eight hand-overs a layer, the two of normalised rows inside the XCD (0.6 us), and by 80 KB of staging for each operator (0.9 .. 1.4 us).
+// Six layers of 40 rows in five slots: 264 us as a chain of 60 kernels, 187 here; of 18 rows in two slots 160, of 32 in four 170 (with MT = 3 170 and 180),
+// of 56 in seven 207, of 64 in four 222, in sixteen 240 (chain: 280 .. 300).  It is bound as the other is, by eight hand-overs a layer, the two of
+// normalised rows inside the XCD (0.6 us), and by staging 2 KB a row for each operator (40 rows: 0.9 .. 1.4 us).
 //
 // Places.  r < 8: no queries, keys and values, but the cross-attention's first eight heads of an XCD, 24 .. 31: the self-attention's (the
-// other way round for more); 8 .. 15, 16 .. 23: the output projections; every place has a tile of the first FFN layer and one K slice of a tile of the second.
+// other way round for more; from nine slots on two heads or more per place); 8 .. 15, 16 .. 23: the output projections; every place has a tile of the first FFN layer and one K slice of a tile of the second.
 #pragma once
 
-constexpr int TK_ROWS = TALL_LAYERS_ROWS, TK_MT = TK_ROWS / 16;
+constexpr int TK_ROWS = TALL_LAYERS_ROWS;        // rows of the XCD's copies of normalised rows
 constexpr int WK_NORM = WK_HEADS;                // flags of the rows that the XCD's waves normalise (the heads' words are free: eight slots do not use them)
 enum { TK_DOWN = WK_DOWN };
 
 struct TkPlaces {
-  // attention (slot, head) as slot * 16 + head, or -1
-  __device__ __forceinline__ static int item(int op, int place, int slots) {
-    const int x = place >> 5, r = place & 31, k = r >= 8 && r < 24 ? 32 : (op == WK_SELF ? (r + 8) & 31 : (r < 8 ? r : r - 16));
-    return k < 2 * slots ? (k >> 1) * 16 + 2 * x + (k & 1) : -1;
+  // Attention: items k = order, order + 16, .. < 2 slots of the place's XCD are a place's (one head's), -1: none
+  __device__ __forceinline__ static int order(int op, int place) {
+    const int r = place & 31;
+    return r >= 8 && r < 24 ? -1 : (op == WK_SELF ? (r + 8) & 31 : (r < 8 ? r : r - 16));
   }
+  // (slot, head) as slot * 16 + head
+  __device__ __forceinline__ static int item(int place, int k) { return (k >> 1) * 16 + 2 * (place >> 5) + (k & 1); }
+  __device__ __forceinline__ static bool any(int op, int place, int slots) { const int k = order(op, place); return k >= 0 && k < 2 * slots; }
   // the members of an XCD that have one
-  __device__ __forceinline__ static unsigned item_mask(int op, int slots) {
-    const int n = 2 * slots, a = n < 8 ? n : 8, b = n - a;
+  __device__ __forceinline__ static unsigned mask(int op, int slots) {
+    const int n = slots < 8 ? 2 * slots : 16, a = n < 8 ? n : 8, b = n - a;
     const unsigned first = (1u << a) - 1, rest = (1u << b) - 1;
     return op == WK_SELF ? first << 24 | rest : first | rest << 24;
   }
 };
 
+template <int MT>
 struct TkHelper : WkHelper {
   __device__ __forceinline__ const float* residual(int l) const { const LayersP& p = lk_args(); return (p.n_layers - 1 - l) & 1 ? p.x2 : p.x; }
 
@@ -113,14 +118,14 @@ struct TkHelper : WkHelper {
   __device__ __forceinline__ void stage(const bf16_t* src, unsigned ld) {
     const int lane = lk_lane();
     const rsrc_t r = rsrc_of(src, (unsigned)(j.rows - 1) * ld + D * 2);
-    u32x4 v[TK_ROWS / 4][2];
+    u32x4 v[4 * MT][2];
 #pragma unroll
-    for (int i = 0; i < TK_ROWS / 4; ++i)
+    for (int i = 0; i < 4 * MT; ++i)
 #pragma unroll
       for (int h = 0; h < 2; ++h) v[i][h] = lk_load16(r, (hw + 4 * i) * ld + h * 1024 + lane * 16);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < TK_ROWS / 4; ++i)
+    for (int i = 0; i < 4 * MT; ++i)
       if (hw + 4 * i < j.rows) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) *(u32x4*)(xs + (hw + 4 * i) * (D + 8) + h * 512 + lane * 8) = v[i][h];
@@ -129,7 +134,7 @@ struct TkHelper : WkHelper {
   // LayerNorm of all rows into LDS
   __device__ __forceinline__ void stage_norm(int l, const float* ln, bool merge) {
     const LayersP& p = lk_args();
-    const int lane = lk_lane(), m = hw < 2 && j.rank >= 8 ? hw * 24 + j.rank - 8 : TK_ROWS;         // (full: the members with queries, keys and values)
+    const int lane = lk_lane(), m = hw < 3 && j.rank >= 8 ? hw * 24 + j.rank - 8 : TK_ROWS;         // (full: the members with queries, keys and values)
     f32x4 g[4], b[4], v[4];
     load_norm(ln, g, b, lane);
     wait(op - 1);
@@ -185,10 +190,10 @@ struct TkHelper : WkHelper {
       staged = true;
       lk_barrier();                              // the input is staged, the partial sums of the place before are read
       lk_barrier();                              // the partial sums are there
-      if (hw >= TK_MT) continue;
+      if (hw >= MT) continue;
       f32x4 part[4];
 #pragma unroll
-      for (int w = 0; w < 4; ++w) part[w] = red[(w * TK_MT + hw) * 64 + lane];
+      for (int w = 0; w < 4; ++w) part[w] = red[(w * MT + hw) * 64 + lane];
       __builtin_amdgcn_sched_barrier(0);
       f32x4 v = ((part[0] + part[1]) + part[2]) + part[3];
       if (m >= j.rows) continue;
@@ -233,7 +238,7 @@ struct TkHelper : WkHelper {
       keep_row(l, j.rank * 8 + j.xcd, v);
     }
     constexpr unsigned MASK = OP == WK_QKV ? 0xFFFFFF00u : (OP == WK_O ? 0xFF00u : (OP == WK_CO ? 0xFF0000u : 0xFFFFFFFFu));
-    done<TK_MT>(staged, MASK, OP != WK_QKV);
+    this->template done<MT>(staged, MASK, OP != WK_QKV);
   }
   template <int OP>
   __device__ __forceinline__ void attention(int l) {
@@ -242,14 +247,18 @@ struct TkHelper : WkHelper {
     bool mine = false;
 #pragma unroll 1
     for (int place = j.place; place < 256; place += j.members) {
-      const int item = TkPlaces::item(OP, place, j.slots);
-      if (item < 0) continue;
-      if constexpr (OP == WK_CROSS) cross_item(l, item, residual(l), !mine);
-      else if (few) self_item<1, TK_MT>(l, item, !mine);
-      else self_item<2, TK_MT>(l, item, !mine);
-      mine = true;
+      const int first = TkPlaces::order(OP, place);
+      if (first < 0) continue;
+#pragma unroll 1
+      for (int k = first; k < 2 * j.slots; k += 16) {
+        const int item = TkPlaces::item(place, k);
+        if constexpr (OP == WK_CROSS) cross_item(l, item, residual(l), !mine);
+        else if (few) self_item<1, MT>(l, item, !mine);
+        else self_item<2, MT>(l, item, !mine);
+        mine = true;
+      }
     }
-    done<4>(mine || (OP == WK_SELF && j.rank < 8), TkPlaces::item_mask(OP, j.slots) | (OP == WK_SELF ? 0xFFu : 0u), true);
+    this->template done<4>(mine || (OP == WK_SELF && j.rank < 8), TkPlaces::mask(OP, j.slots) | (OP == WK_SELF ? 0xFFu : 0u), true);
   }
   __device__ __forceinline__ void run() {
     const int layers = lk_args().n_layers;
@@ -261,17 +270,18 @@ struct TkHelper : WkHelper {
     }
 #pragma unroll 1
     for (int l = 0; l < layers; ++l) {
-      product<WK_QKV>(l);
-      attention<WK_SELF>(l);
-      product<WK_O>(l);
-      attention<WK_CROSS>(l);
-      product<WK_CO>(l);
-      product<WK_UP>(l);
-      product<TK_DOWN>(l);
+      this->template product<WK_QKV>(l);
+      this->template attention<WK_SELF>(l);
+      this->template product<WK_O>(l);
+      this->template attention<WK_CROSS>(l);
+      this->template product<WK_CO>(l);
+      this->template product<WK_UP>(l);
+      this->template product<TK_DOWN>(l);
     }
   }
 };
 
+template <int MT>
 struct TkCompute {
   const bf16_t* xs;
   f32x4* red;
@@ -285,32 +295,32 @@ struct TkCompute {
   }
   __device__ __forceinline__ u32x4 (&one())[1][8] { return *reinterpret_cast<u32x4 (*)[1][8]>(&ax[0]); }
   __device__ __forceinline__ u32x4 (&second())[1][8] { return *reinterpret_cast<u32x4 (*)[1][8]>(&ax[1]); }
-  // (two steps of operands for the three row tiles at a time: registers)
+  // (two steps of operands for the row tiles at a time: registers)
   __device__ __forceinline__ void multiply(const u32x4 (&a)[1][8]) {
     const int lane = lk_lane(), lr = lane & 15;
-    const bf16_t* row[TK_MT];
-    f32x4 acc[TK_MT];
+    const bf16_t* row[MT];
+    f32x4 acc[MT];
 #pragma unroll
-    for (int t = 0; t < TK_MT; ++t) {
+    for (int t = 0; t < MT; ++t) {
       const int m = t * 16 + lr;
       row[t] = xs + (m < j.rows ? m : 0) * (1024 + 8) + cw * 256 + (lane >> 4) * 8;
       acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 #pragma unroll
     for (int i = 0; i < 8; i += 2) {
-      bf16x8 b[2][TK_MT];
+      bf16x8 b[2][MT];
 #pragma unroll
       for (int e = 0; e < 2; ++e)
 #pragma unroll
-        for (int t = 0; t < TK_MT; ++t) b[e][t] = __builtin_bit_cast(bf16x8, *(const u32x4*)(row[t] + (i + e) * 32));
+        for (int t = 0; t < MT; ++t) b[e][t] = __builtin_bit_cast(bf16x8, *(const u32x4*)(row[t] + (i + e) * 32));
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int e = 0; e < 2; ++e)
 #pragma unroll
-        for (int t = 0; t < TK_MT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[0][i + e]), b[e][t], acc[t], 0, 0, 0);
+        for (int t = 0; t < MT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[0][i + e]), b[e][t], acc[t], 0, 0, 0);
     }
 #pragma unroll
-    for (int t = 0; t < TK_MT; ++t) red[(cw * TK_MT + t) * 64 + lane] = acc[t];
+    for (int t = 0; t < MT; ++t) red[(cw * MT + t) * 64 + lane] = acc[t];
   }
   template <int OP> __device__ __forceinline__ void product(u32x4 (&a)[1][8], const char* LayersP::*w, int l) {
 #pragma unroll 1
@@ -326,8 +336,8 @@ struct TkCompute {
   // Weights are fetched while a member idles: see the places
   __device__ __forceinline__ void run() {
     const int layers = lk_args().n_layers, r = j.place & 31, slots = j.slots;
-    const int cross_at = TkPlaces::item(WK_CROSS, j.place, slots);
-    const bool full = j.full, self = full && TkPlaces::item(WK_SELF, j.place, slots) >= 0, cross = full && cross_at >= 0;
+    const int cross_tile = (2 * (j.place >> 5) + (TkPlaces::order(WK_CROSS, j.place) & 1)) * 4;      // (of the head's queries)
+    const bool full = j.full, self = full && TkPlaces::any(WK_SELF, j.place, slots), cross = full && TkPlaces::any(WK_CROSS, j.place, slots);
     const bool low = full && r < 8, qkv = full && r >= 8, o = full && r >= 8 && r < 16, co = full && r >= 16 && r < 24;
     if (qkv) load(aq, &LayersP::wqkv, 0, WkMember::tile(WK_QKV, j.place));
     if (o) load(one(), &LayersP::wo, 0, WkMember::tile(WK_O, j.place));
@@ -336,14 +346,14 @@ struct TkCompute {
       const int next = l + 1 < layers ? l + 1 : l;                   // (past the last layer: once more, read by nobody)
       if (low) {
         if (l > 0) __builtin_amdgcn_s_sleep(WK_HOLD);
-        if (cross) load<WK_GAP>(ax, &LayersP::cq, l, (cross_at & 15) * 4);
+        if (cross) load<WK_GAP>(ax, &LayersP::cq, l, cross_tile);
         load<WK_GAP>(a1, &LayersP::w1, l, j.place);
         if (!cross) load<WK_GAP>(second(), &LayersP::w2, l, j.place);
       }
       product<WK_QKV>(aq, &LayersP::wqkv, l);
       if (qkv && !self && !o) {
         __builtin_amdgcn_s_sleep(WK_HOLD);       // (the operator's own results first)
-        if (cross) load<WK_GAP>(ax, &LayersP::cq, l, (cross_at & 15) * 4);
+        if (cross) load<WK_GAP>(ax, &LayersP::cq, l, cross_tile);
         if (co) load<WK_GAP>(one(), &LayersP::co, l, WkMember::tile(WK_CO, j.place));
         load<WK_GAP>(aq, &LayersP::wqkv, next, WkMember::tile(WK_QKV, j.place));
         load<WK_GAP>(a1, &LayersP::w1, l, j.place);
@@ -351,15 +361,17 @@ struct TkCompute {
       }
 #pragma unroll 1
       for (int place = j.place, mine = 0; place < 256; place += j.members) {
-        if (TkPlaces::item(WK_SELF, place, slots) < 0) continue;
-        if (mine) lk_barrier();
-        mine = 1;
-        lk_barrier();
+        const int first = TkPlaces::order(WK_SELF, place);
+        for (int k = first < 0 ? 2 * slots : first; k < 2 * slots; k += 16) {
+          if (mine) lk_barrier();
+          mine = 1;
+          lk_barrier();
+        }
       }
       product<WK_O>(one(), &LayersP::wo, l);
       if (qkv && (self || o)) {
         __builtin_amdgcn_s_sleep(WK_HOLD);
-        if (cross) load(ax, &LayersP::cq, l, (cross_at & 15) * 4);
+        if (cross) load(ax, &LayersP::cq, l, cross_tile);
         load<WK_GAP>(aq, &LayersP::wqkv, next, WkMember::tile(WK_QKV, j.place));
         if (o) load<WK_GAP>(one(), &LayersP::wo, next, WkMember::tile(WK_O, j.place));
         load<WK_GAP>(a1, &LayersP::w1, l, j.place);
@@ -367,16 +379,19 @@ struct TkCompute {
       }
 #pragma unroll 1
       for (int place = j.place, mine = 0; place < 256; place += j.members) {
-        const int item = TkPlaces::item(WK_CROSS, place, slots);
-        if (item < 0) continue;
-        if (!full) load(ax, &LayersP::cq, l, (item & 15) * 4);
-        if (mine) lk_barrier();
-        mine = 1;
-        lk_barrier();
-        lk_multiply(ax, xs, lk_args().R, red, cw, lk_lane());
-        lk_barrier();
-        lk_barrier();
-        lk_barrier();
+        const int first = TkPlaces::order(WK_CROSS, place);
+        if (first < 0 || first >= 2 * slots) continue;
+        if (!full) load(ax, &LayersP::cq, l, (TkPlaces::item(place, first) & 15) * 4);
+#pragma unroll 1
+        for (int k = first; k < 2 * slots; k += 16) {
+          if (mine) lk_barrier();
+          mine = 1;
+          lk_barrier();
+          lk_multiply(ax, xs, lk_args().R, red, cw, lk_lane());
+          lk_barrier();
+          lk_barrier();
+          lk_barrier();
+        }
       }
       if (cross) load<WK_GAP>(second(), &LayersP::w2, l, j.place);
       product<WK_CO>(one(), &LayersP::co, l);
@@ -386,30 +401,33 @@ struct TkCompute {
   }
 };
 
+// (the attention works where the partial sums lie: they are read, and not yet written again)
+template <int MT>
 struct TkLds {
-  static constexpr int XS = TK_ROWS * (1024 + 8) * 2, RED = 4 * 4 * 64 * 16;
-  static constexpr int BYTES = XS + RED + (int)AttnLds::BYTES + 512 * 8 + 64;
+  static constexpr int XS = 16 * MT * (1024 + 8) * 2, RED = 4 * 4 * 64 * 16, ATTN = (int)AttnLds::BYTES > RED ? (int)AttnLds::BYTES : RED;
+  static constexpr int BYTES = XS + ATTN + 512 * 8 + 64;
   static_assert(BYTES <= 160 * 1024, "LDS");
 };
 
+template <int MT>
 __global__ __launch_bounds__(512, 2) void tall_layers_kernel(LayersP p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lk_smem[];
+  using Lds = TkLds<MT>;
   bf16_t* xs = (bf16_t*)lk_smem;
-  f32x4* red = (f32x4*)(lk_smem + TkLds::XS);
-  unsigned char* attn = lk_smem + TkLds::XS + TkLds::RED;
-  u32x2* q_s = (u32x2*)(attn + AttnLds::BYTES);
+  f32x4* red = (f32x4*)(lk_smem + Lds::XS);
+  u32x2* q_s = (u32x2*)(lk_smem + Lds::XS + Lds::ATTN);
   int* word = (int*)(q_s + 512);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int xcd = __builtin_amdgcn_readfirstlane((int)lk_xcd());
   WkMember j;
   if (!wk_register(p, word, wave, lane, xcd, j)) return;
   if (wave >= 4) {
-    TkCompute c{xs, red, wave - 4, j};
+    TkCompute<MT> c{xs, red, wave - 4, j};
     c.run();
   } else {
     __builtin_amdgcn_s_setprio(3);
-    TkHelper h;
-    h.xs = xs; h.red = red; h.sm = AttnLds::carve(attn); h.q_s = q_s; h.hw = wave; h.j = j;
+    TkHelper<MT> h;
+    h.xs = xs; h.red = red; h.sm = AttnLds::carve((unsigned char*)red); h.q_s = q_s; h.hw = wave; h.j = j;
     h.run();
   }
 }

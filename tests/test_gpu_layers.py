@@ -1,4 +1,4 @@
-"""All decoder layers as one kernel: a job of up to 16 rows per XCD (d = 512, d_ff = 2048), or one block of up to 16 or of 17 .. 48 rows on the whole chip (d =
+"""All decoder layers as one kernel: a job of up to 16 rows per XCD (d = 512, d_ff = 2048), or one block of up to 16 or of 17 .. 64 rows on the whole chip (d =
 1024, d_ff = 4096).  Rows and slots at their limits, long caches, whose attention several workgroups may share, groups that are not full, and sequences that end."""
 import numpy as np
 import pytest
@@ -36,8 +36,9 @@ def test_wide_rows_and_slots(k, B, S):
     lockstep(config(k, B, S, 3 * k + 4, d=1024), 3)
 
 
-# two and three row tiles, one row of the second and of the third, all slots and rows there can be; up to four slots the attentions have members of their own
-@pytest.mark.parametrize("k,B,S", [(16, 3, 33), (9, 2, 5), (8, 5, 50), (11, 3, 3), (6, 8, 140), (10, 4, 20), (3, 6, 1), (5, 7, 70)])
+# two to four row tiles, one row of the second, third and fourth, all slots and rows there can be; up to four slots the attentions have members of their own,
+# from nine on a member has two heads or more
+@pytest.mark.parametrize("k,B,S", [(16, 3, 33), (9, 2, 5), (8, 5, 50), (11, 3, 3), (6, 8, 140), (10, 4, 20), (3, 6, 1), (5, 7, 70), (7, 7, 5), (16, 4, 40), (4, 16, 3), (2, 9, 130), (5, 11, 9)])
 def test_tall_rows_and_slots(k, B, S):
     lockstep(config(k, B, S, 3 * k + 4, d=1024), 3)
 
@@ -45,7 +46,7 @@ def test_tall_rows_and_slots(k, B, S):
 # groups of fewer workgroups than places, and one that waits until its time is up; d = 1024: fewer XCDs, too
 @pytest.mark.parametrize("group,k,B,d", [(1, 7, 2, 512), (5, 8, 16, 512), (31, 10, 3, 512), (33, 4, 9, 512),
                                          (5, 10, 1, 1024), (31, 4, 4, 1024), (33, 7, 2, 1024), (32 + 64 * 3, 5, 3, 1024), (3 + 64, 3, 1, 1024),
-                                         (5, 10, 4, 1024), (33, 6, 8, 1024), (32 + 64 * 3, 8, 5, 1024), (3 + 64, 9, 2, 1024)])
+                                         (5, 10, 4, 1024), (33, 6, 8, 1024), (32 + 64 * 3, 8, 5, 1024), (3 + 64, 9, 2, 1024), (7, 4, 14, 1024)])
 def test_groups(group, k, B, d, monkeypatch):
     monkeypatch.setenv("BPD_LAYERS_GROUP", str(group))
     lockstep(config(k, B, 5, 3 * k + 4, d=d), 3)
