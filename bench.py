@@ -262,8 +262,8 @@ def main():
     bracket_ms = profile_phase(ctx, binding.PHASE_EMPTY, cfg1, src, n, max_len, sched, k, min(args.steps, 60), torch)
     for name in ("head_hidden", "head_out", "vocab"):
         kern[name]["ms_minus_empty_bracket"] = kern[name]["ms"] - bracket_ms
-    # the roofline entry is for the phase that takes most of the step: the decoder layers (47 kernels, each a small
-    # weight stream), not for the best-behaved kernel; the three big single-kernel streams stay under "kernels"
+    # the roofline entry is for the phase that takes most of the step: the decoder layers (one kernel, a chain of
+    # hand-overs), not for the best-behaved kernel; the three big weight streams stay under "kernels"
     dom = max(("layers", "head_hidden", "head_out", "vocab"), key=lambda q: kern[q]["ms"])
     # HBM bytes per step of that phase measured with rocprofv3 --pmc (FETCH_SIZE + WRITE_SIZE, scaled by a copy kernel of
     # known size), written by `python -m paper_1811_03115_amd.profsum` from the runs named in profiles/
@@ -298,7 +298,7 @@ def main():
     if not args.no_peaks:
         peaks = {"hbm_read_GBps": binding.Context.bpd_measure_hbm_read(1 << 30, 4),
                  "mfma_bf16_TFLOPs": binding.Context.bpd_measure_mfma_bf16(20000)}
-    roofline = {"bound": "hbm", "kernel": dom if dom != "layers" else "layers (the 47 kernels of the 6 decoder layers)",
+    roofline = {"bound": "hbm", "kernel": dom if dom != "layers" else "layers (wide_layers_kernel: the 6 decoder layers)",
                 "share_of_step": kern[dom]["ms"] / ms_step,
                 "achieved": kern[dom]["GBps"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": kern[dom]["GBps"] / HBM_PEAK_GBS, "traffic": traffic,

@@ -28,15 +28,8 @@ BENCH_CASE = ("python3 -c \"import sys, torch; from perf import cases as p; c = 
 
 # kernels of one C2 step (batch 1, 10 block rows) by phase: (substring of the kernel name, grid x or several, launches per step)
 C2_STEP = {
-    "layers": [("row_gemm_kernel<8, 4, 1, 1, true, 2>", 98304, 1),                         # LayerNorm + QKV of the first layer
-               ("ln_row_kernel<1024, 4>", 2560, 5),                                       # K slices of the FFN output + LayerNorm
-               ("row_gemm_kernel<8, 4, 1, 1, false, 2>", 98304, 5),                        # QKV
-               ("attention_mfma_kernel<false, false, 0>", (4096, 8192), 6),               # self-attention (four or eight waves)
-               ("row_gemm_kernel<8, 4, 1, 1, false, 1>", 32768, 12),                       # attention output projections
-               ("attention_mfma_kernel<false, false, 8>", 8192, 6),                       # LayerNorm + query projection + cross-attention
-               ("row_gemm_kernel<8, 4, 1, 1, true, 0>", 131072, 6),                        # LayerNorm + FFN in
-               ("row_gemm_kernel<8, 4, 1, 1, false, 3>", 32768, 6)],                       # FFN out, four K slices
-    "head_hidden": [("ln_row_kernel<1024, 4>", 2560, 1), ("skinny_gemm_kernel<1, 2, false, false, 4, 8, 2, true>", 65536, 1)],
+    "layers": [("wide_layers_kernel", 131072, 1)],                                        # all of them
+    "head_hidden": [("ln_row_kernel<1024, 0>", 2560, 1), ("skinny_gemm_kernel<1, 2, false, false, 4, 8, 2, true>", 65536, 1)],
     "head_out": [("stream_gemm_kernel<16, true>", 12800, 1)],
     "vocab": [("stream_vocab_kernel<4, 1, 2, false>", 65536, 1)],
     "accept": [("accept_embed_kernel", 1024, 1)],
@@ -157,10 +150,11 @@ def main():
             "# C2 step (batch 1, 10 block rows), average kernel durations x launches per step:",
         ] + [f"#   {ph:12s} {us:8.2f} us" for ph, us in per_step.items()] + [
             f"#   whole step   {sum(per_step.values()):8.2f} us (sum of kernel durations)",
-            "# C2 kernels: row_gemm_kernel<waves, k-steps per wave, row tiles, column tiles, LayerNorm inside, epilogue> = layer GEMMs",
-            "#   (epilogue 0 ReLU, 1 residual, 2 queries / K / V, 3 K slice), ln_row_kernel<columns, slices>, skinny_gemm_kernel = heads'",
-            "#   hidden layers, stream_gemm_kernel = heads' output layers, attention_mfma_kernel<..,0> self-attention, <..,8>",
-            "#   cross-attention with its query projection, stream_vocab_kernel = vocabulary projection + arg-max (100 rows)",
+            "# C2 kernels: wide_layers_kernel = decoder layers, ln_row_kernel<columns, slices>, skinny_gemm_kernel = heads' hidden layers,",
+            "#   stream_gemm_kernel = heads' output layers, stream_vocab_kernel = vocabulary projection + arg-max (100 rows)",
+            "# Elsewhere: row_gemm_kernel<waves, k-steps per wave, row tiles, column tiles, LayerNorm inside, epilogue> = layer GEMMs",
+            "#   (epilogue 0 ReLU, 1 residual, 2 queries / K / V, 3 K slice), attention_mfma_kernel<..,0> self-attention, <..,8>",
+            "#   cross-attention with its query projection, tall_layers_kernel = decoder layers of 17 .. 64 rows",
             "# C3 step (batch 32, 320 block rows): gemm_ldsx_kernel<8,4,64,true,..> = vocabulary projection + arg-max (3200 rows),",
             "#   <7,4,64,false,..> = heads' hidden layers, <4,2,128,false> = heads' output layers (10 groups), row_gemm_kernel<8,4,2..4,4,..> =",
             "#   layer GEMMs, <3,1,256,..> x 4 slices = FFN output, attention_mfma_slots_kernel = attention of the sequences that go on;",
@@ -189,7 +183,7 @@ def main():
             "# against the algorithmic bytes (weights read once):",
         ] + [f"#   {ph:12s} {c2[ph] / 1e6:8.1f} MB measured, {alg[ph]:6.1f} MB algorithmic" for ph in c2] + [
             "# (FETCH_SIZE counts what the L2s request from the fabric: it sits in front of the Infinity Cache and cannot tell its hits",
-            "#  from HBM reads.  The decoder layers' 47 kernels each fetch their activations once per XCD on top of the weights.)",
+            "#  from HBM reads.  The decoder layers' kernel hands its activations over between XCDs on top of the weights.)",
         ]
         write("c2_step_hbm_traffic_pmc.txt", "\n".join(hdr) + "\n\n" + pmc_table(fetch, 14) + "\n\n" + pmc_table(wr, 12) + "\n")
 
@@ -197,11 +191,11 @@ def main():
         fetch, wr = pmc_rows(db_of(args.c4_fetch)), pmc_rows(db_of(args.c4_write))
         copy_f, copy_w = avg_of(fetch, COPY_KERNEL), avg_of(wr, COPY_KERNEL)
         fs, ws = COPY_KIB / copy_f, COPY_KIB / copy_w
-        att = [r for r in fetch if "attention_mfma_kernel<true" in r[0]]
-        # the dispatches with the longest cache (largest fetch): bytes and duration of the attention launch alone
+        att = [r for r in fetch if "layers_kernel<2048, true>" in r[0]]
+        # the dispatches with the longest cache (largest fetch)
         cur = db_of(args.c4_fetch)
-        top = cur.execute("select value, end-start from counters_collection where kernel_name like '%attention_mfma_kernel<true%' "
-                          "and counter_name = 'FETCH_SIZE' order by value desc limit 120").fetchall()
+        top = cur.execute("select value, end-start from counters_collection where kernel_name like '%layers_kernel<2048, true>%' "
+                          "and counter_name = 'FETCH_SIZE' order by value desc limit 20").fetchall()
         hdr = [
             "# rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE for the super-resolution workload C4 (batch 8, k = 10, 6 layers, d = 512):",
             "# bpd_step at cache lengths 256, 1536 and 3000 (bench.py --only C4 steps the decode to each length, then times 20 steps",
@@ -210,20 +204,20 @@ def main():
             f"#   rocprofv3 --pmc WRITE_SIZE -d prof_out/pmc_c4_write -o c4 -- {BENCH_C4}",
             "#   python -m paper_1811_03115_amd.profsum --c4-fetch prof_out/pmc_c4_fetch --c4-write prof_out/pmc_c4_write",
             f"# copy kernel: FETCH_SIZE {copy_f:.0f}, WRITE_SIZE {copy_w:.0f} for 262144 KiB each way: scales {fs:.2f} / {ws:.2f}",
-            "# self-attention over the cache = attention_mfma_kernel<true, *, 0> (K/V fetched with non-temporal loads: the 303 MB of",
-            "# caches would evict the weights from the Infinity Cache), its split-KV merge = attention_combine_kernel.",
-            "# Algorithmic K/V bytes of one self-attention launch at cache length L: 2 * 8 sequences * L * 512 * 2 B = 16384 L",
+            "# all decoder layers = layers_kernel<2048, true> (K/V fetched with non-temporal loads: the 303 MB of caches would evict the",
+            "# weights from the Infinity Cache).  Algorithmic bytes of a launch at cache length L: 44 MB of weights, which each of eight",
+            "# XCDs fetches for itself, 19 MB of source keys and values, 6 layers * 2 * 8 sequences * L * 512 * 2 B = 98304 L",
             "# (the average below mixes all lengths the decode passes through; min / max are the ends).",
         ]
         for r in att:
             hdr.append(f"#   {short(r[0], 60)} grid {r[1]}: avg {1024 * fs * r[4] / 1e6:.1f} MB, max {1024 * fs * r[6] / 1e6:.1f} MB per launch "
-                       + ("(max: L = 3000+, algorithmic 49.5 MB), " if r is max(att, key=lambda q: q[6]) else "") + f"avg duration {r[7] / 1e3:.1f} us")
+                       + f"avg duration {r[7] / 1e3:.1f} us")
         if top:
             tb = 1024 * fs * sum(t[0] for t in top) / len(top)
             tus = sum(t[1] for t in top) / len(top) / 1e3
             hdr.append(f"#   the {len(top)} launches with the longest cache: {tb / 1e6:.1f} MB fetched in {tus:.1f} us per launch = {tb / tus / 1e3:.0f} GB/s "
-                       f"({tb / tus / 1e3 / 8000:.2f} of 8 TB/s) for the attention launch alone (profiled run)")
-            traffic["C4"] = {"attention_fetch_bytes_longest": int(tb), "attention_us_longest": tus, "attention_GBps_longest": tb / tus / 1e3,
+                       f"({tb / tus / 1e3 / 8000:.2f} of 8 TB/s), profiled run")
+            traffic["C4"] = {"layers_fetch_bytes_longest": int(tb), "layers_us_longest": tus, "layers_GBps_longest": tb / tus / 1e3,
                              "fetch_scale": fs}
         write("c4_attention_hbm_traffic_pmc.txt", "\n".join(hdr) + "\n\n" + pmc_table(fetch, 14) + "\n\n" + pmc_table(wr, 8) + "\n")
 
