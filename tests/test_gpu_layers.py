@@ -109,3 +109,31 @@ def test_two_streams(k, B, d):
     for t in threads:
         t.join()
     assert out[0] == out[2] and out[1] == out[2]
+
+
+# one kernel per captured step, replayed with other work of the program's between the replays: every replay finds the words that the workgroups count in cleared
+@pytest.mark.parametrize("k,B,d", [(6, 5, 512), (5, 20, 512), (9, 1, 1024), (7, 4, 1024), (8, 7, 1024)])
+def test_captured_steps(k, B, d):
+    from test_gpu_captured import capture, context, replay, same, snapshot
+    cfg = config(k, B, 9, 60, d=d)
+    weights = wl.make_weights(cfg)
+    stream = torch.cuda.Stream()
+    ref, cap = context(cfg, weights), context(cfg, weights, stream)
+    src, n = wl.make_sources(cfg)
+    two = torch.full((B,), 2, dtype=torch.int32, device="cuda")
+    acc = torch.zeros((2, B), dtype=torch.int32, device="cuda")
+    for c in (ref, cap):
+        c.bpd_encode(src, n, np.full(B, 60, np.int32))
+        c.bpd_step(k, two)
+    g = capture(stream, lambda: cap.bpd_step_static(k, two, acc[1]))
+    same(snapshot(ref), snapshot(cap), "recorded, not run")
+    for s in range(6):
+        ref.bpd_step(k, two, acc[0])
+        replay(g, stream)
+        torch.cuda.synchronize()
+        torch.randn(1 << 20, device="cuda").sum().item()
+        same(snapshot(ref), snapshot(cap), f"replay {s}")
+        if s == 3:                                         # a direct step in between
+            ref.bpd_step(k, two)
+            cap.bpd_step(k, two)
+    assert acc[0].tolist() == acc[1].tolist() == [2] * B
