@@ -858,7 +858,7 @@ int heads_two_phase(bpd_ctx* ctx, int k) {
   const bool topn = ctx->top_n > 1;
   vocab_argmax(ctx, gp(L.O, d, L.emb, c.vocab, M, c.vocab, d), L.keys_h1, topn ? L.logits_h1 : nullptr);
   if (topn)
-    hipLaunchKernelGGL(topn_rank_kernel, dim3(k - 1, B), dim3(256), 0, ctx->stream, (const float*)L.logits_h1, c.vocab,
+    hipLaunchKernelGGL(topn_rank_kernel, dim3(k - 1, B), dim3(TOPN_T), 0, ctx->stream, (const float*)L.logits_h1, c.vocab,
                        (const int*)L.P, c.k_max, k, ctx->top_n, L.topn_ok, seq);
   StateP st = state_params(ctx);
   st.imposed = ctx->cur_imposed; st.imposed_stride = ctx->cur_imposed_stride;
@@ -1117,7 +1117,7 @@ int forward(bpd_ctx* ctx, int R, int k, int zero_input, float* logits) {
         hipLaunchKernelGGL(vocab_argmax_f32_kernel, dim3((unsigned)M), dim3(256), 0, ctx->stream, (const float*)L.O, k * d,
                            (const float*)L.emb, M, c.vocab, d, L.keys_h1, L.logits_h1);
       }
-      hipLaunchKernelGGL(topn_rank_kernel, dim3(k - 1, B), dim3(256), 0, ctx->stream, (const float*)L.logits_h1, c.vocab,
+      hipLaunchKernelGGL(topn_rank_kernel, dim3(k - 1, B), dim3(TOPN_T), 0, ctx->stream, (const float*)L.logits_h1, c.vocab,
                          (const int*)L.P, c.k_max, k, ctx->top_n, L.topn_ok, seq);
     }
   }

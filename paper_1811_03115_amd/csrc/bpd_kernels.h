@@ -1081,22 +1081,45 @@ __global__ void prime_kernel(StateP s, const unsigned long long* keys, int B) {
 // Top-n acceptance (Section 5.1): is proposal P[b][i+1] among the n best-scoring tokens of p_1 at
 // block row i?  logits: [B*k][V] fp32, row b*k + i = head 1 at block row i.  The rank of the
 // proposal is the number of tokens that beat it in the (value, lower index first) order of the
-// arg-max keys.  Grid (k - 1, B), one workgroup per tested row.
-__global__ __launch_bounds__(256) void topn_rank_kernel(const float* logits, int V, const int* P, int kmax, int k, int n,
-                                                        int* ok, const int* seq) {
-  const int i = blockIdx.x, b = seq ? seq[blockIdx.y] : blockIdx.y;
+// arg-max keys.  Grid (k - 1, B), one workgroup per tested row, whose 32 floats per thread are under way together, the first ones while the proposal's
+// own score is looked up (32000 tokens: 4.7 us; 256 threads, a float at a time: 36 us).
+constexpr int TOPN_T = 1024;
+__global__ __launch_bounds__(TOPN_T) void topn_rank_kernel(const float* logits, int V, const int* P, int kmax, int k, int n,
+                                                           int* ok, const int* seq) {
+  constexpr int U = 8;
+  const int i = blockIdx.x, b = seq ? seq[blockIdx.y] : blockIdx.y, tid = threadIdx.x;
   if (b < 0) return;
   const float* z = logits + ((long)blockIdx.y * k + i) * V;
+  const int quads = V >> 2;                      // (V is a multiple of 16)
+  f32x4 v[U];
+  auto load = [&](int q0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) { const int q = q0 + u * TOPN_T + tid; v[u] = *(const f32x4*)(z + 4 * (q < quads ? q : 0)); }
+  };
+  load(0);
   int t = P[b * kmax + i + 1];
   t = t < 0 ? 0 : (t >= V ? V - 1 : t);
   const unsigned long long kt = argmax_key(z[t], (unsigned)t);
   int cnt = 0;
-  for (int v = threadIdx.x; v < V; v += 256) cnt += argmax_key(z[v], (unsigned)v) > kt;
-  __shared__ int part[4];
+  for (int q0 = 0; q0 < quads; q0 += U * TOPN_T) {
+    if (q0 > 0) load(q0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int q = q0 + u * TOPN_T + tid;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) cnt += q < quads && argmax_key(v[u][e], (unsigned)(4 * q + e)) > kt;
+    }
+  }
+  __shared__ int part[TOPN_T / 64];
   for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off, 64);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = cnt;
+  if ((tid & 63) == 0) part[tid >> 6] = cnt;
   __syncthreads();
-  if (threadIdx.x == 0) ok[b * kmax + i] = (part[0] + part[1] + part[2] + part[3]) < n;
+  if (tid == 0) {
+    int all = 0;
+#pragma unroll
+    for (int w = 0; w < TOPN_T / 64; ++w) all += part[w];
+    ok[b * kmax + i] = all < n;
+  }
 }
 
 // Verify substep for sequence b, one wavefront: lane i (1 <= i < k) holds proposal P_{i+1} in myP and

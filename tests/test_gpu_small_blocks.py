@@ -41,6 +41,18 @@ def test_encoder_slices(d, F, B, S):
     lockstep(cfg, 1)
 
 
+# rank among vocabularies of less than a thread's first 32 floats each, exactly those, and 16 tokens more
+@pytest.mark.parametrize("V,k,B", [(16, 3, 2), (272, 16, 1), (32768, 4, 2), (32784, 5, 3)])
+def test_top_n_vocabularies(V, k, B):
+    cfg = wl.Config("rank", 77, 1, 1, 128, 2, 512, V, k, B, 7, 4 * k + 8, "bf16", 2, src_len_kind="lognormal")
+    weights = wl.make_weights(cfg)
+    ctx = gpu_context(cfg, weights)
+    src, n = wl.make_sources(cfg)
+    ls = LockStep(cfg, weights, ctx, src, n, np.full(B, cfg.max_out, np.int32), sample=list(range(B)))
+    for top in (2, V // 3, V - 1):
+        ls.step(top_n=top, check_logits=False)
+
+
 # lengths of the caches on both sides of 32, 128 and 256 keys (a group, four waves, eight waves), sources likewise
 @pytest.mark.parametrize("k,S,out", [(1, 1, 34), (7, 31, 40), (5, 33, 135), (16, 129, 150), (13, 200, 270)])
 def test_key_groups(k, S, out):
