@@ -404,7 +404,8 @@ __global__ __launch_bounds__(WAVES * 64) void skinny_gemm_kernel(GemmP p, Epi e,
           const unsigned long long key = argmax_key(sum[r], (unsigned)(n + r));
           best_run[j] = key > best_run[j] ? key : best_run[j];
         }
-        if (logits && m < p.M) *(float4*)(logits + (long)m * p.N + n) = make_float4(sum[0], sum[1], sum[2], sum[3]);
+        const int kept = logit_row(p, logits, m, p.M);
+        if (kept >= 0) *(float4*)(logits + (long)kept * p.N + n) = make_float4(sum[0], sum[1], sum[2], sum[3]);
       } else if (e.mode != 0) {
         if (m < p.M) {
           const float v4[4] = {sum[0], sum[1], sum[2], sum[3]};
@@ -728,8 +729,8 @@ __global__ __launch_bounds__(512) void stream_vocab_kernel(GemmP p, unsigned lon
             const unsigned long long key_ = argmax_key(acc[t][n][r], (unsigned)(n_ + r));       \
             best[t] = key_ > best[t] ? key_ : best[t];                                          \
           }                                                                                     \
-          const int m_ = m0 + t * 16 + lr;                                                      \
-          if (logits && m_ < M) *(float4*)(logits + (long)m_ * p.N + n_) = make_float4(acc[t][n][0], acc[t][n][1], acc[t][n][2], acc[t][n][3]); \
+          const int kept_ = logit_row(p, logits, m0 + t * 16 + lr, M);                          \
+          if (kept_ >= 0) *(float4*)(logits + (long)kept_ * p.N + n_) = make_float4(acc[t][n][0], acc[t][n][1], acc[t][n][2], acc[t][n][3]); \
         }                                                                                       \
       }                                                                                         \
     }                                                                                           \
@@ -1207,7 +1208,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
     unsigned long long* wb = (unsigned long long*)smem_raw;       // [4][BM], the staging buffers are free now
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
-      const int m = m0 + t * 16 + lr;
+      const int kept = logit_row(p, logits, m0 + t * 16 + lr, M);
       unsigned long long best = 0ull;
 #pragma unroll
       for (int u = 0; u < NT; ++u) {
@@ -1218,8 +1219,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
           const unsigned long long key = argmax_key(acc[t][u][r], (unsigned)(n + r));
           best = key > best ? key : best;
         }
-        if (logits && m < M)
-          *(float4*)(logits + (long)m * p.N + n) = make_float4(acc[t][u][0], acc[t][u][1], acc[t][u][2], acc[t][u][3]);
+        if (kept >= 0)
+          *(float4*)(logits + (long)kept * p.N + n) = make_float4(acc[t][u][0], acc[t][u][1], acc[t][u][2], acc[t][u][3]);
       }
       unsigned long long o = __shfl_xor(best, 16, 64); best = o > best ? o : best;
       o = __shfl_xor(best, 32, 64); best = o > best ? o : best;

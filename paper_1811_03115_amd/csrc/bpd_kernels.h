@@ -212,7 +212,15 @@ struct GemmP {
   // goes to part + z*M*N and the consumer (layernorm_kernel) adds the slices in index order
   int ksplit; float* part;
   LdsxMap lx;          // gemm_ldsx_kernel: its workgroup -> tile map and K walk (bpd_tile_map.h; set by the launcher)
+  int lstep;           // vocabulary projections that keep scores: of every lstep-th row only (0: of all)
 };
+// Row m's row among the scores that are kept, -1: none
+__device__ __forceinline__ int logit_row(const GemmP& p, const float* logits, int m, int M) {
+  if (!logits || m >= M) return -1;
+  if (p.lstep <= 1) return m;
+  const int q = m / p.lstep;
+  return q * p.lstep == m ? q : -1;
+}
 
 // Rows in use of a step of a batch some of whose sequences may have ended: *n slots of `per` rows (n null: all).  A kernel's
 // last argument: in the middle of the others it moved them across cache lines, 0.1 .. 0.3 us for each small kernel.
@@ -352,7 +360,7 @@ __global__ __launch_bounds__(256) void vocab_argmax_bf16_kernel(GemmP p, unsigne
   const int ntiles = p.N >> 4;
 #pragma unroll
   for (int t = 0; t < MT; ++t) {
-    const int m = g.m0 + t * 16 + (g.lane & 15);
+    const int m = g.m0 + t * 16 + (g.lane & 15), kept = logit_row(p, logits, m, p.M);
     unsigned long long best = 0ull;
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
@@ -363,7 +371,7 @@ __global__ __launch_bounds__(256) void vocab_argmax_bf16_kernel(GemmP p, unsigne
         const float v = g.acc[t][u][r];
         const unsigned long long key = argmax_key(v, (unsigned)(n + r));
         best = key > best ? key : best;
-        if (logits && m < p.M) logits[(long)m * p.N + n + r] = v;
+        if (kept >= 0) logits[(long)kept * p.N + n + r] = v;
       }
     }
     // lanes l, l^16, l^32, l^48 hold the same row
@@ -398,9 +406,10 @@ __global__ void gemm_f32_kernel(GemmP p, Epi e) {
 
 // fp32 vocabulary projection: E is [V][d] row-major; one workgroup per row of O.
 __global__ __launch_bounds__(256) void vocab_argmax_f32_kernel(const float* O, int ldo, const float* E, int M, int V,
-                                                               int d, unsigned long long* keys, float* logits) {
+                                                               int d, unsigned long long* keys, float* logits, int lstep) {
   const int m = blockIdx.x;
   if (m >= M) return;
+  if (logits) logits = m % lstep == 0 ? logits + (long)(m / lstep) * V : nullptr;      // (as GemmP::lstep)
   const float* o = O + (long)m * ldo;
   unsigned long long best = 0ull;
   for (int v = threadIdx.x; v < V; v += blockDim.x) {
@@ -415,7 +424,7 @@ __global__ __launch_bounds__(256) void vocab_argmax_f32_kernel(const float* O, i
       for (int j = 0; j < 8; ++j) acc = fmaf(ov[j], wv[j], acc);
     }
     for (; c < d; ++c) acc = fmaf(o[c], ev[c], acc);
-    if (logits) logits[(long)m * V + v] = acc;
+    if (logits) logits[v] = acc;
     const unsigned long long key = argmax_key(acc, (unsigned)v);
     best = key > best ? key : best;
   }
@@ -1079,17 +1088,17 @@ __global__ void prime_kernel(StateP s, const unsigned long long* keys, int B) {
 }
 
 // Top-n acceptance (Section 5.1): is proposal P[b][i+1] among the n best-scoring tokens of p_1 at
-// block row i?  logits: [B*k][V] fp32, row b*k + i = head 1 at block row i.  The rank of the
+// block row i?  logits: [B*k][V] fp32 (ld floats from row to row), row b*k + i = head 1 at block row i.  The rank of the
 // proposal is the number of tokens that beat it in the (value, lower index first) order of the
 // arg-max keys.  Grid (k - 1, B), one workgroup per tested row, whose 32 floats per thread are under way together, the first ones while the proposal's
 // own score is looked up (32000 tokens: 4.7 us; 256 threads, a float at a time: 36 us).
 constexpr int TOPN_T = 1024;
-__global__ __launch_bounds__(TOPN_T) void topn_rank_kernel(const float* logits, int V, const int* P, int kmax, int k, int n,
+__global__ __launch_bounds__(TOPN_T) void topn_rank_kernel(const float* logits, long ld, int V, const int* P, int kmax, int k, int n,
                                                            int* ok, const int* seq) {
   constexpr int U = 8;
   const int i = blockIdx.x, b = seq ? seq[blockIdx.y] : blockIdx.y, tid = threadIdx.x;
   if (b < 0) return;
-  const float* z = logits + ((long)blockIdx.y * k + i) * V;
+  const float* z = logits + ((long)blockIdx.y * k + i) * ld;
   const int quads = V >> 2;                      // (V is a multiple of 16)
   f32x4 v[U];
   auto load = [&](int q0) {

@@ -53,6 +53,20 @@ def test_top_n_vocabularies(V, k, B):
         ls.step(top_n=top, check_logits=False)
 
 
+# scores of head 1 out of the one pass over the vocabulary, by each of its kernels: up to 16 rows (2 and 4 heads), 18 and 100
+# streamed, staged in LDS, fp32 past the one-workgroup kernels
+@pytest.mark.parametrize("d,V,k,B,dtype", [(512, 4112, 2, 1, "bf16"), (128, 272, 4, 1, "bf16"), (512, 20496, 3, 2, "bf16"), (1024, 16400, 5, 4, "bf16"),
+                                           (512, 1040, 7, 3, "bf16"), (64, 5008, 3, 3, "f32")])
+def test_top_n_kept_scores(d, V, k, B, dtype):
+    cfg = wl.Config("kept", 78, 1, 1, d, d // (64 if dtype == "bf16" else 16), 2 * d, V, k, B, 7, 4 * k + 8, dtype, 2, src_len_kind="lognormal")
+    weights = wl.make_weights(cfg)
+    ctx = gpu_context(cfg, weights)
+    src, n = wl.make_sources(cfg)
+    ls = LockStep(cfg, weights, ctx, src, n, np.full(B, cfg.max_out, np.int32), sample=list(range(B)))
+    for top in (2, V // 3, V - 1):
+        ls.step(top_n=top, check_logits=False)
+
+
 # lengths of the caches on both sides of 32, 128 and 256 keys (a group, four waves, eight waves), sources likewise
 @pytest.mark.parametrize("k,S,out", [(1, 1, 34), (7, 31, 40), (5, 33, 135), (16, 129, 150), (13, 200, 270)])
 def test_key_groups(k, S, out):
