@@ -113,32 +113,6 @@ __device__ __forceinline__ void store_tiles(const Epi& e_in, int g, const f32x4 
   }
 }
 
-// Row-wise arg-max over this wave's columns, merged into keys[] with a 64-bit atomic max.
-template <int MT, int NT>
-__device__ __forceinline__ void argmax_tiles(const f32x4 (&acc)[MT][NT], int m0, int nt0, int ntiles, int M, int N,
-                                             int lane, unsigned long long* keys, float* logits) {
-#pragma unroll
-  for (int t = 0; t < MT; ++t) {
-    const int m = m0 + t * 16 + (lane & 15);
-    unsigned long long best = 0ull;
-#pragma unroll
-    for (int u = 0; u < NT; ++u) {
-      if (nt0 + u >= ntiles) continue;
-      const int n = (nt0 + u) * 16 + (lane >> 4) * 4;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float v = acc[t][u][r];
-        const unsigned long long key = argmax_key(v, (unsigned)(n + r));
-        best = key > best ? key : best;
-        if (logits && m < M) logits[(long)m * N + n + r] = v;
-      }
-    }
-    unsigned long long o = __shfl_xor(best, 16, 64); best = o > best ? o : best;
-    o = __shfl_xor(best, 32, 64); best = o > best ? o : best;
-    if (lane < 16 && m < M) atomicMax(&keys[m], best);
-  }
-}
-
 // ---------------------------------------------------------------------------------------
 // LayerNorm statistics travel with the residual stream: every kernel that writes x (16-column
 // tile by tile) also writes, per tile and row, the partial sum and sum of squares of its 16

@@ -54,11 +54,12 @@ def test_top_n_vocabularies(V, k, B):
 
 
 # scores of head 1 out of the one pass over the vocabulary, by each of its kernels: up to 16 rows (2 and 4 heads), 18 and 100
-# streamed, staged in LDS, fp32 past the one-workgroup kernels
+# streamed, staged in LDS, a width of no whole 64, fp32 past the
+# one-workgroup kernels
 @pytest.mark.parametrize("d,V,k,B,dtype", [(512, 4112, 2, 1, "bf16"), (128, 272, 4, 1, "bf16"), (512, 20496, 3, 2, "bf16"), (1024, 16400, 5, 4, "bf16"),
-                                           (512, 1040, 7, 3, "bf16"), (64, 5008, 3, 3, "f32")])
+                                           (512, 1040, 7, 3, "bf16"), (96, 272, 5, 2, "bf16"), (64, 5008, 3, 3, "f32")])
 def test_top_n_kept_scores(d, V, k, B, dtype):
-    cfg = wl.Config("kept", 78, 1, 1, d, d // (64 if dtype == "bf16" else 16), 2 * d, V, k, B, 7, 4 * k + 8, dtype, 2, src_len_kind="lognormal")
+    cfg = wl.Config("kept", 78, 1, 1, d, d // (64 if d % 64 == 0 and dtype == "bf16" else 16), 2 * d, V, k, B, 7, 4 * k + 8, dtype, 2, src_len_kind="lognormal")
     weights = wl.make_weights(cfg)
     ctx = gpu_context(cfg, weights)
     src, n = wl.make_sources(cfg)
