@@ -69,7 +69,7 @@ struct bpd_ctx {
   // workgroups per XCD that layers_kernel and wide_layers_kernel wait for (for tests, BPD_LAYERS_GROUP at creation: fewer; 33: they wait in vain; 64 n
   // added: the second one is left to n XCDs; 0: neither is used)
   int layers_group = LK_PLACES;
-  bool layers_ran = false;             // layers_kernel has been launched and the LayerNorm behind it has not (layernorm() has it clear layers_sync)
+  bool layers_ran = false;             // layers_kernel has been launched and the LayerNorm behind it has not (that LayerNorm clears layers_sync)
   bool weights_exceed_llc = false;     // decoder-side weights read per step > 192 MB (the Infinity Cache holds 256 MB)
   const int* cur_imposed = nullptr; int cur_imposed_stride = 0, cur_imposed_step = 0;   // of the step being run
   // pinned host memory, read and written by kernels directly: the words that say what has happened, the arguments of
@@ -177,7 +177,7 @@ void launch_gemm_bf16(const GemmP& p, const Epi& e, int groups, hipStream_t s) {
 }
 
 // ---- skinny path: M <= 16 -------------------------------------------------------------
-template <int MT, int NT, bool XLN, bool ARGMAX, int WAVES, int U, int DEPTH, bool STREAM>
+template <int MT, int NT, int XLN, bool ARGMAX, int WAVES, int U, int DEPTH, bool STREAM>
 void launch_skinny_cfg(const bpd_ctx* ctx, const GemmP& p, const Epi& e_in, const LnP& ln, unsigned long long* keys,
                        float* logits, int groups) {
   hipStream_t s = ctx->stream;
@@ -193,12 +193,12 @@ void launch_skinny_cfg(const bpd_ctx* ctx, const GemmP& p, const Epi& e_in, cons
   dim3 grid(gx, (p.M + 16 * MT - 1) / (16 * MT), groups);
   const size_t lds = (size_t)2 * WAVES * MT * NT * 1024;
   if (ngroups > gx) {
-    auto k = skinny_gemm_kernel<MT, NT, XLN, ARGMAX, WAVES, U, DEPTH, STREAM>;
+    auto k = skinny_gemm_kernel<XLN == 2 ? 0 : MT, NT, XLN != 0, ARGMAX, WAVES, U, DEPTH, STREAM>;
     static bool attr = false;
     if (!attr) { (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); attr = true; }
     hipLaunchKernelGGL(k, grid, dim3(64 * WAVES), lds, s, p, e, ln, keys, logits);
   } else {
-    auto k = skinny_gemm_kernel<MT, NT, XLN, ARGMAX, WAVES, U, 0, STREAM>;
+    auto k = skinny_gemm_kernel<XLN == 2 ? 0 : MT, NT, XLN != 0, ARGMAX, WAVES, U, 0, STREAM>;
     static bool attr = false;
     if (!attr) { (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); attr = true; }
     hipLaunchKernelGGL(k, grid, dim3(64 * WAVES), lds, s, p, e, ln, keys, logits);
@@ -206,19 +206,19 @@ void launch_skinny_cfg(const bpd_ctx* ctx, const GemmP& p, const Epi& e_in, cons
 }
 
 // One 16-row tile (M <= 16): K split over the waves so that each wave holds all its k-steps.
-template <int NT, bool XLN, bool ARGMAX, bool STREAM>
+template <int NT, int XLN, bool ARGMAX, bool STREAM>
 void launch_skinny_s(const bpd_ctx* ctx, const GemmP& p, const Epi& e, const LnP& ln, unsigned long long* keys, float* logits,
                      int groups) {
   // waves x k-steps per wave cover K / 32 without idle slots (an idle slot still costs its clamped load)
   if (XLN && p.K <= 512) launch_skinny_cfg<1, NT, XLN, ARGMAX, 4, 4, 2, STREAM>(ctx, p, e, ln, keys, logits, groups);
   else if (XLN) launch_skinny_cfg<1, NT, XLN, ARGMAX, 8, 4, 2, STREAM>(ctx, p, e, ln, keys, logits, groups);       // K <= 1024
-  else if (p.K <= 512) launch_skinny_cfg<1, NT, false, ARGMAX, 4, 4, 2, STREAM>(ctx, p, e, ln, keys, logits, groups);
-  else if (p.K <= 1024) launch_skinny_cfg<1, NT, false, ARGMAX, 4, 8, 2, STREAM>(ctx, p, e, ln, keys, logits, groups);
-  else if (p.K <= 2048) launch_skinny_cfg<1, NT, false, ARGMAX, 8, 8, 1, STREAM>(ctx, p, e, ln, keys, logits, groups);
-  else launch_skinny_cfg<1, NT, false, ARGMAX, 8, 16, 1, STREAM>(ctx, p, e, ln, keys, logits, groups);             // K <= 4096
+  else if (p.K <= 512) launch_skinny_cfg<1, NT, 0, ARGMAX, 4, 4, 2, STREAM>(ctx, p, e, ln, keys, logits, groups);
+  else if (p.K <= 1024) launch_skinny_cfg<1, NT, 0, ARGMAX, 4, 8, 2, STREAM>(ctx, p, e, ln, keys, logits, groups);
+  else if (p.K <= 2048) launch_skinny_cfg<1, NT, 0, ARGMAX, 8, 8, 1, STREAM>(ctx, p, e, ln, keys, logits, groups);
+  else launch_skinny_cfg<1, NT, 0, ARGMAX, 8, 16, 1, STREAM>(ctx, p, e, ln, keys, logits, groups);             // K <= 4096
 }
 // Streams of at least 32 MB in a model whose per-step weights exceed the last-level cache bypass it.
-template <int NT, bool XLN, bool ARGMAX>
+template <int NT, int XLN, bool ARGMAX>
 void launch_skinny(const bpd_ctx* ctx, const GemmP& p, const Epi& e, const LnP& ln, unsigned long long* keys, float* logits,
                    int groups) {
   const size_t wbytes = (size_t)p.K * p.N * groups * 2;
@@ -393,8 +393,8 @@ bool gemm(bpd_ctx* ctx, const GemmP& p, const Epi& e_in, int groups = 1) {
   if (stream_ok(ctx, p, e, groups)) {
     launch_stream(ctx, p, e, groups);
   } else if (skinny_ok(ctx, p)) {
-    if (p.N / 16 >= 2048) launch_skinny<2, false, false>(ctx, p, e, none, nullptr, nullptr, groups);
-    else launch_skinny<1, false, false>(ctx, p, e, none, nullptr, nullptr, groups);
+    if (p.N / 16 >= 2048) launch_skinny<2, 0, false>(ctx, p, e, none, nullptr, nullptr, groups);
+    else launch_skinny<1, 0, false>(ctx, p, e, none, nullptr, nullptr, groups);
   } else if (p.K % 64 == 0) {
     // In-place residual update with a long K and few output tiles: split K over workgroups.  The
     // slices are added, in a fixed order, by the LayerNorm kernel that reads the residual next.
@@ -440,8 +440,8 @@ void gemm_ln(bpd_ctx* ctx, float* x, LnW w, void* xn, float* yf, GemmP p, const 
   // row tile only; the encoder's kernels do not write them)
   if (with_stats && stats_path(ctx, p.M) && p.K == ctx->cfg.d_model) {
     LnP ln{x, w.g, w.b, ctx->lay.stats_ln, ctx->cfg.ln_eps};
-    if (p.N / 16 >= 2048) launch_skinny<2, true, false>(ctx, p, e, ln, nullptr, nullptr, 1);
-    else launch_skinny<1, true, false>(ctx, p, e, ln, nullptr, nullptr, 1);
+    if (p.N / 16 >= 2048) launch_skinny<2, 1, false>(ctx, p, e, ln, nullptr, nullptr, 1);
+    else launch_skinny<1, 1, false>(ctx, p, e, ln, nullptr, nullptr, 1);
     return;
   }
   // big_stats: more than 16 rows and the GEMM that produced x left per-tile statistics in L.stats_big
@@ -495,7 +495,7 @@ void vocab_argmax(bpd_ctx* ctx, const GemmP& p, unsigned long long* keys, float*
   hipStream_t s = ctx->stream;
   Epi none{};
   LnP noln{};
-  if (skinny_ok(ctx, p)) launch_skinny<2, false, true>(ctx, p, none, noln, keys, logits, 1);
+  if (skinny_ok(ctx, p)) launch_skinny<2, 0, true>(ctx, p, none, noln, keys, logits, 1);
   else if (stream_vocab_ok(ctx, p)) launch_stream_vocab(ctx, p, keys, logits);
   else if (p.K % 64 == 0) dispatch_ldsx<true>(p, none, keys, logits, 1, s, live_rows(ctx, p.M));
   else {
@@ -1082,7 +1082,15 @@ int forward(bpd_ctx* ctx, int R, int k, int zero_input, float* logits) {
   // for the residual), then one output layer per head
   {
     PhaseTimer t(ctx, BPD_PHASE_HEAD_HIDDEN);
-    if (lean) {
+    // behind the layers kernels one row tile is normalised by the GEMM that reads it
+    if (ctx->layers_ran && M <= 16 && !ctx->pend_slices) {
+      GemmP p = gp(nullptr, d, L.hw1, c.k_max * F, M, k * F, d);
+      LnP ln{L.x, L.dec_lnf.g, L.dec_lnf.b, nullptr, c.ln_eps, L.h, (uint4*)L.layers_sync, LK_WORDS / 4};
+      const Epi e = plain(L.hb1, 1, nullptr, 0, nullptr, 0, L.H, k * F);
+      ctx->layers_ran = false;
+      if (p.N / 16 >= 2048) launch_skinny<2, 2, false>(ctx, p, e, ln, nullptr, nullptr, 1);
+      else launch_skinny<1, 2, false>(ctx, p, e, ln, nullptr, nullptr, 1);
+    } else if (lean) {
       layernorm(ctx, L.x, L.dec_lnf, M, L.hn, L.h);
       gemm(ctx, gp(L.hn, d, L.hw1, c.k_max * F, M, k * F, d), plain(L.hb1, 1, nullptr, 0, nullptr, 0, L.H, k * F));
     } else gemm_ln(ctx, L.x, L.dec_lnf, L.hn, L.h, gp(L.hn, d, L.hw1, c.k_max * F, M, k * F, d),

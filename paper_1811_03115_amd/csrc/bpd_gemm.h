@@ -155,6 +155,9 @@ struct LnP {
   const float* b;       // [K]
   const float* stats;   // partial sums written by the producer of x
   float eps;
+  float* yf;            // XLN = 2: the normalised rows in fp32, for a later kernel
+  uint4* clear;         // XLN = 2: as ln_row_kernel's (nclear pieces of 16 bytes; null: none)
+  int nclear;
 };
 
 // Skinny GEMM: blocks of 16*MT rows (blockIdx.y), all rows of a block resident in registers.  Workgroup = WAVES waves
@@ -165,9 +168,15 @@ struct LnP {
 // turn (tile id % WAVES).  A workgroup walks tile groups blockIdx.x, blockIdx.x + gridDim.x,
 // ... with the weights of the next DEPTH groups in flight (DEPTH == 0: one group per
 // workgroup).
-//   XLN = false: X is bf16 [M][K] in global memory.
-//   XLN = true : (MT == 1) X = LayerNorm(x) of the fp32 residual stream, normalised in
-//                registers from the producer's partial statistics.
+//   XLN = 0 (NORM false): X is bf16 [M][K] in global memory.
+//   XLN = 1 (NORM, MT == ROWS == 1): X = LayerNorm(x) of the fp32 residual stream, normalised in
+//           registers from the producer's partial statistics.
+//   XLN = 2 (NORM, ROWS == 0: MT is 1, K = 32 * WAVES * U) the same without statistics at hand: a wave takes mean and squared distances
+//           of its columns of the rows, these meet in LDS (row_moments).  x is asked for in front of the weights, so that all
+//           of this passes while they are on their way.  The heads' hidden layers behind a kernel of all layers: 7.9 us at
+//           8 x 512 x 16384 and 5.8 us at 1 x 1024 x 4096, against 10.9 and 9.5 us with ln_row_kernel in front; a greedy
+//           decode of the big shape 5.81 -> 5.77 ms, a sentence of it, k = 10, 5.37 -> 5.33 ms, one of the base shape, k = 8,
+//           2.765 -> 2.748 ms (in a captured step a launch costs less than in a trace).
 // Every global load of the first group (weights, activations, statistics, bias and residual of
 // the epilogue) is issued before anything is waited for: one memory round trip per kernel.
 // Epilogue (mode 0) additionally supports: R = LayerNorm(R) via e.lnR_* (the heads' residual
@@ -177,9 +186,10 @@ typedef unsigned int u32x4_nt __attribute__((ext_vector_type(4)));
 // STREAM: the weight tiles are fetched with non-temporal loads.  A weight matrix that is read once
 // per step and does not fit the last-level cache together with the rest of the model (the heads of
 // Transformer-big) would otherwise evict the decoder layers' weights from it every step.
-template <int MT, int NT, bool XLN, bool ARGMAX, int WAVES, int U, int DEPTH, bool STREAM>
+template <int ROWS, int NT, bool NORM, bool ARGMAX, int WAVES, int U, int DEPTH, bool STREAM>
 __global__ __launch_bounds__(WAVES * 64) void skinny_gemm_kernel(GemmP p, Epi e, LnP ln, unsigned long long* keys,
                                                                   float* logits) {
+  constexpr int MT = ROWS ? ROWS : 1, XLN = NORM ? (ROWS ? 1 : 2) : 0;
   constexpr int TILES = MT * NT, OWN = (TILES + WAVES - 1) / WAVES;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   f32x4* red = (f32x4*)smem_raw;               // [2][WAVES][TILES][64]
@@ -200,7 +210,7 @@ __global__ __launch_bounds__(WAVES * 64) void skinny_gemm_kernel(GemmP p, Epi e,
   }
   float4 st0 = make_float4(0.f, 0.f, 0.f, 0.f), st1 = st0;   // statistics: (K/16) * 8 float4 in all
   const bool epi_ln = !XLN && !ARGMAX && e.mode == 0 && e.lnR_stats != nullptr;
-  if (XLN || epi_ln) {
+  if (XLN == 1 || epi_ln) {
     const float* sp_ = XLN ? ln.stats : e.lnR_stats;
     const int ns4 = ((XLN ? p.K : e.lnR_K) >> 4) * 8;
     const int i0 = threadIdx.x, i1 = threadIdx.x + WAVES * 64;
@@ -217,6 +227,15 @@ __global__ __launch_bounds__(WAVES * 64) void skinny_gemm_kernel(GemmP p, Epi e,
   if (nt0 >= ntiles) return;
   const int mb0 = blockIdx.y * (16 * MT);       // row block of this workgroup
 
+  float4 xv[XLN ? U : 1][2];
+  if (XLN == 2) {
+    const int mrow = mb0 + lr < p.M ? mb0 + lr : p.M - 1;
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) xv[i][hh] = *(const float4*)(ln.x + (long)mrow * p.K + (wave + WAVES * i) * 32 + lk + 4 * hh);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   constexpr bool PERSIST = DEPTH > 0;
   const int stride = gridDim.x * NT;            // distance between consecutive tile groups of this workgroup
   uint4 a[DEPTH + 1][U][NT];                    // a[0]: current group, a[1..DEPTH]: groups in flight
@@ -233,7 +252,7 @@ __global__ __launch_bounds__(WAVES * 64) void skinny_gemm_kernel(GemmP p, Epi e,
   BPD_LOAD_A(a[0], nt0)                         // weights first: they do not depend on the producer kernel
 #pragma unroll
   for (int dd = 1; dd < DEPTH; ++dd)
-    if (nt0 + dd * stride < ntiles) { BPD_LOAD_A(a[dd], nt0 + dd * stride) }
+    if (XLN == 2 || nt0 + dd * stride < ntiles) { BPD_LOAD_A(a[dd], nt0 + dd * stride) }      // (XLN = 2: no branch between x and its wait)
 
   // operands of the epilogue (bias, residual) for the tiles this wave will finish; the host passes
   // a zero-filled buffer where there is no bias / residual so that the loads are unconditional
@@ -256,9 +275,50 @@ __global__ __launch_bounds__(WAVES * 64) void skinny_gemm_kernel(GemmP p, Epi e,
 
   // activation fragments, kept for all tile groups of this workgroup
   uint4 b[MT][U];
-  if (XLN) {
+  if (XLN == 2) {
+    const int nv = p.K >> 2;
+    const int i0 = threadIdx.x, i1 = threadIdx.x + WAVES * 64;
+    if (i0 < 2 * nv) *(float4*)&gb_s[i0 < nv ? 4 * i0 : 1024 + 4 * (i0 - nv)] = gb0;
+    if (GBL > 1 && i1 < 2 * nv) *(float4*)&gb_s[i1 < nv ? 4 * i1 : 1024 + 4 * (i1 - nv)] = gb1;
+    float s = 0.f, q = 0.f;
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) s += (xv[i][hh].x + xv[i][hh].y) + (xv[i][hh].z + xv[i][hh].w);
+    s += __shfl_xor(s, 16, 64); s += __shfl_xor(s, 32, 64);
+    const float mw = s * (1.f / (32 * U));
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        float4& v = xv[i][hh];                   // (from here on: distances to the mean of the wave's own columns)
+        v.x -= mw; v.y -= mw; v.z -= mw; v.w -= mw;
+        q += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
+      }
+    q += __shfl_xor(q, 16, 64); q += __shfl_xor(q, 32, 64);
+    float2* const st = (float2*)st_s;            // [WAVES][16]
+    if (lane < 16) st[wave * 16 + lr] = make_float2(s, q);
+    __syncthreads();
+    float mu, rs;
+    row_moments<WAVES, 32 * U>(st + lr, 16, ln.eps, mu, rs);
+    const float off = (mw - mu) * rs;
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const int col = (wave + WAVES * i) * 32 + lk;
+      float y[8];
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) {
+        const float4 v = xv[i][hh], gg = *(const float4*)&gb_s[col + 4 * hh], bb = *(const float4*)&gb_s[1024 + col + 4 * hh];
+        y[4 * hh + 0] = fmaf(fmaf(v.x, rs, off), gg.x, bb.x); y[4 * hh + 1] = fmaf(fmaf(v.y, rs, off), gg.y, bb.y);
+        y[4 * hh + 2] = fmaf(fmaf(v.z, rs, off), gg.z, bb.z); y[4 * hh + 3] = fmaf(fmaf(v.w, rs, off), gg.w, bb.w);
+        if (ln.yf && blockIdx.x == 0 && mb0 + lr < p.M)
+          *(float4*)(ln.yf + (long)(mb0 + lr) * p.K + col + 4 * hh) = make_float4(y[4 * hh], y[4 * hh + 1], y[4 * hh + 2], y[4 * hh + 3]);
+      }
+      b[0][i] = make_uint4(cvt_pk_bf16(y[0], y[1]), cvt_pk_bf16(y[2], y[3]), cvt_pk_bf16(y[4], y[5]), cvt_pk_bf16(y[6], y[7]));
+    }
+  } else if (XLN) {
     const int mrow = mb0 + lr < p.M ? mb0 + lr : p.M - 1;
-    float4 xv[U][2], gv[U][2], bv[U][2];
+    float4 gv[U][2], bv[U][2];
 #pragma unroll
     for (int i = 0; i < U; ++i) {
       const int ks = wave + WAVES * i;
@@ -325,6 +385,9 @@ __global__ __launch_bounds__(WAVES * 64) void skinny_gemm_kernel(GemmP p, Epi e,
     }
   }
 
+  if (XLN == 2 && ln.clear && blockIdx.x == 0 && mb0 == 0) {
+    for (int i = threadIdx.x; i < ln.nclear; i += WAVES * 64) ln.clear[i] = zero4;
+  }
   unsigned long long best_run[OWN];
 #pragma unroll
   for (int j = 0; j < OWN; ++j) best_run[j] = 0ull;

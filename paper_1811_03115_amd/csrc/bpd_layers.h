@@ -51,7 +51,7 @@ struct LayersP {
   float eps, scale;
   int local_q, local_m;
   bf16_t* xn; float* x2;                         // tall_layers_kernel: normalised rows, one copy per XCD; the residual stream's second buffer.  Its slices: part
-  unsigned* sync;                                // [LK_WORDS], zero at the start of a launch (ln_row_kernel behind it clears it)
+  unsigned* sync;                                // [LK_WORDS], zero at the start of a launch (the LayerNorm behind it clears it)
   long long* error;                              // set to 1 if a wait ran out
 };
 

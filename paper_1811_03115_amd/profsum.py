@@ -29,7 +29,7 @@ BENCH_CASE = ("python3 -c \"import sys, torch; from perf import cases as p; c = 
 # kernels of one C2 step (batch 1, 10 block rows) by phase: (substring of the kernel name, grid x or several, launches per step)
 C2_STEP = {
     "layers": [("wide_layers_kernel", 131072, 1)],                                        # all of them
-    "head_hidden": [("ln_row_kernel<1024, 0>", 2560, 1), ("skinny_gemm_kernel<1, 2, false, false, 4, 8, 2, true>", 65536, 1)],
+    "head_hidden": [("skinny_gemm_kernel<0, 2, true, false, 8, 4, 2, true>", 131072, 1)],
     "head_out": [("stream_gemm_kernel<16, true>", 12800, 1)],
     "vocab": [("stream_vocab_kernel<4, 1, 2, false>", 65536, 1)],
     "accept": [("accept_embed_kernel", 1024, 1)],
@@ -150,7 +150,7 @@ def main():
             "# C2 step (batch 1, 10 block rows), average kernel durations x launches per step:",
         ] + [f"#   {ph:12s} {us:8.2f} us" for ph, us in per_step.items()] + [
             f"#   whole step   {sum(per_step.values()):8.2f} us (sum of kernel durations)",
-            "# C2 kernels: wide_layers_kernel = decoder layers, ln_row_kernel<columns, slices>, skinny_gemm_kernel = heads' hidden layers,",
+            "# C2 kernels: wide_layers_kernel = decoder layers, ln_row_kernel<columns, slices>, skinny_gemm_kernel = final LayerNorm and heads' hidden layers,",
             "#   stream_gemm_kernel = heads' output layers, stream_vocab_kernel = vocabulary projection + arg-max (100 rows)",
             "# Elsewhere: row_gemm_kernel<waves, k-steps per wave, row tiles, column tiles, LayerNorm inside, epilogue> = layer GEMMs",
             "#   (epilogue 0 ReLU, 1 residual, 2 queries / K / V, 3 K slice), attention_mfma_kernel<..,0> self-attention, <..,8>",
