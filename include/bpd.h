@@ -19,6 +19,11 @@
  * never throws or aborts; bpd_last_error() gives a message.  On an argument error the decode
  * state is left unchanged.
  *
+ * Waits inside kernels are bounded (about a second; only a defect gets there).  If one has run out,
+ * what was computed since the last bpd_encode is invalid: until the next one bpd_decode and
+ * bpd_get_* return BPD_E_HIP, bpd_debug_step_logits leaves NaN, and the context runs its later steps
+ * kernel by kernel.
+ *
  * Calls on one context must not overlap (one thread at a time, or external locking), and all
  * contexts of a process must live on one device: kernel attributes are set once per process.
  *

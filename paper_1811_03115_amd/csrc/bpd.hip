@@ -1390,7 +1390,7 @@ int wait_report(bpd_ctx* ctx, const unsigned long long* word, unsigned tag) {
   return wait_until(ctx, [&] { return __atomic_load_n(word, __ATOMIC_ACQUIRE) >> 32 == tag; });
 }
 
-// Copies up to four arrays of ints to the caller (host or device memory; null: not wanted) and waits for them.
+// Copies up to five arrays of ints to the caller (host or device memory; null: not wanted) and waits for them.
 struct Fetch { const int* src; size_t n; void* dst; };
 constexpr size_t FETCH_KERNEL_MAX = 32768;     // ints: one workgroup's copy, about 10 us; more goes through copies
 int fetch(bpd_ctx* ctx, std::initializer_list<Fetch> list) {
@@ -1504,11 +1504,12 @@ int bpd_create(const bpd_config* cfg, void* workspace, size_t workspace_bytes, v
   if (ctx->lay.layers_sync) (void)hipMemsetAsync(ctx->lay.layers_sync, 0, (size_t)LK_WORDS * 4, ctx->stream);
   (void)hipMemsetAsync(ctx->lay.zeros, 0, ctx->lay.n_zeros * 4, ctx->stream);
   (void)hipMemsetAsync(ctx->lay.step_counter, 0, 4, ctx->stream);
+  (void)hipMemsetAsync(ctx->lay.stats, 0, 32 * 8, ctx->stream);
   (void)hipMemsetAsync(ctx->lay.stats_ln, 0, 64 * 16 * 2 * 4, ctx->stream);
   {
     const size_t B = cfg->max_batch, k = cfg->k_max, S = cfg->max_src_len, T = cfg->max_out_len;
     const size_t n_in = B * S + 2 * B, n_sched = B * T;
-    ctx->n_stage_out = std::min(FETCH_KERNEL_MAX, std::max(B * T + B + 64, B * k * (k + 1) + 2 * B));
+    ctx->n_stage_out = std::min(FETCH_KERNEL_MAX, std::max(B * T + B, B * k * (k + 1) + 2 * B) + 64);      // (64: the statistics)
     const size_t ints = 4 * B + 16 + n_in + n_sched + ctx->n_stage_out;
     if (hipHostMalloc((void**)&ctx->report, ints * sizeof(int), hipHostMallocDefault) != hipSuccess) {
       (void)hipGetLastError();
@@ -1682,7 +1683,7 @@ int bpd_encode(bpd_ctx* ctx, const int32_t* src_ids, const int32_t* src_len, con
     small_encode(ctx);
   } else {
     ctx->steps = 0;
-    const int rc = run_planned(ctx, PLAN_ENCODE, {B, S, ctx->local_q, ctx->local_m}, [&]() -> int {
+    const int rc = run_planned(ctx, PLAN_ENCODE, {B, S, ctx->local_q, ctx->local_m, layers_way(ctx, B, 1)}, [&]() -> int {
       int rc = encoder(ctx);
       if (rc) return rc;
       // first invocation: position 0 only, all heads -> first proposals
@@ -1729,7 +1730,7 @@ static int step_accept(bpd_ctx* ctx, int k, int* accepted_dev, int next_slots, u
                          !slots_used(ctx) ? 0 : (ctx->seq ? 2 : 1), ctx->two_phase && k > 1 && ctx->B * k > 16);
       ctx->x_ready_k = k; ctx->x_ready_slots = next_slots;
     } else {
-      hipLaunchKernelGGL(accept_kernel, dim3(ctx->B), dim3(64), 0, ctx->stream, s, L.keys, k, ctx->B, 1, imposed_step, accepted_dev);
+      hipLaunchKernelGGL(accept_kernel, dim3(ctx->B), dim3(64), 0, ctx->stream, s, L.keys, k, ctx->B, 1, imposed_step, accepted_dev, (float*)nullptr, 0);
       ctx->x_ready_k = 0;
     }
   }
@@ -1874,10 +1875,19 @@ static void stats_of(const bpd_ctx* ctx, const long long* raw, bpd_stats* st) {
   for (int i = 0; i < 17; ++i) st->hist[i] = raw[3 + i];
 }
 
+// Has a wait of a whole-layer kernel run out since the last bpd_encode (which clears the word)?  Everything since is invalid, whoever asks for
+// it, and the context's later steps and encodes go kernel by kernel.
+static int layers_check(bpd_ctx* ctx, const long long* raw) {
+  if (!raw[31]) return BPD_OK;
+  ctx->layers_group = 0;
+  return fail(ctx, BPD_E_HIP, "decoder layers: a bounded wait ran out; results since the last bpd_encode are invalid, later steps use the per-operator kernels");
+}
+
 int bpd_get_stats(bpd_ctx* ctx, bpd_stats* st) {
   if (!ctx || !st) return BPD_E_ARG;
   long long raw[32];
-  const int rc = fetch(ctx, {{(const int*)ctx->lay.stats, 64, raw}});
+  int rc = fetch(ctx, {{(const int*)ctx->lay.stats, 64, raw}});
+  if (rc == BPD_OK) rc = layers_check(ctx, raw);
   if (rc) return rc;
   stats_of(ctx, raw, st);
   return BPD_OK;
@@ -1886,10 +1896,10 @@ int bpd_get_stats(bpd_ctx* ctx, bpd_stats* st) {
 static int output_and_stats(bpd_ctx* ctx, int32_t* out_ids, int32_t* out_len, bpd_stats* st, bool count_steps = false) {
   Layout& L = ctx->lay;
   long long raw[32];
-  const int rc = fetch(ctx, {{L.out_ids, (size_t)ctx->B * ctx->cfg.max_out_len, out_ids}, {L.j, (size_t)ctx->B, out_len},
-                             {(const int*)L.stats, 64, raw}});
+  int rc = fetch(ctx, {{L.out_ids, (size_t)ctx->B * ctx->cfg.max_out_len, out_ids}, {L.j, (size_t)ctx->B, out_len},
+                       {(const int*)L.stats, 64, raw}});
+  if (rc == BPD_OK) rc = layers_check(ctx, raw);
   if (rc) return rc;
-  if (raw[31]) return fail(ctx, BPD_E_HIP, "decoder layers: a bounded wait ran out; the results of this decode are invalid");
   if (count_steps) ctx->steps = raw[20];
   if (st) stats_of(ctx, raw, st);
   return stack_check(ctx);
@@ -2031,7 +2041,9 @@ int bpd_get_state(bpd_ctx* ctx, int32_t* P, int32_t* A, int32_t* j, int32_t* fin
   if (!ctx->encoded) return fail(ctx, BPD_E_STATE, "bpd_get_state: call bpd_encode first");
   Layout& L = ctx->lay;
   const size_t B = ctx->B, k = ctx->cfg.k_max;
-  const int rc = fetch(ctx, {{L.P, B * k, P}, {L.A, B * k * k, A}, {L.j, B, j}, {L.finished, B, finished}});
+  long long raw[32];
+  int rc = fetch(ctx, {{L.P, B * k, P}, {L.A, B * k * k, A}, {L.j, B, j}, {L.finished, B, finished}, {(const int*)L.stats, 64, raw}});
+  if (rc == BPD_OK) rc = layers_check(ctx, raw);
   if (rc) return rc;
   return stack_check(ctx);
 }
@@ -2063,7 +2075,7 @@ int bpd_debug_step_logits(bpd_ctx* ctx, int k, float* logits) {
   }
   int rc = forward(ctx, k, k, 0, logits);
   if (rc) return rc;
-  hipLaunchKernelGGL(accept_kernel, dim3(ctx->B), dim3(64), 0, ctx->stream, state_params(ctx), ctx->lay.keys, k, ctx->B, 0, 0, nullptr);
+  hipLaunchKernelGGL(accept_kernel, dim3(ctx->B), dim3(64), 0, ctx->stream, state_params(ctx), ctx->lay.keys, k, ctx->B, 0, 0, nullptr, logits, ctx->cfg.vocab);
   LAUNCHCHK();
   return BPD_OK;
 }

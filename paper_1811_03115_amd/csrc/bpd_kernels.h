@@ -971,7 +971,7 @@ struct StateP {
   int* A;            // [B][kmax][kmax]
   int* accepted;     // [B] k-hat of the last step
   int* out_ids;      // [B][max_out]
-  long long* stats;  // [0] seq_steps [1] accepted_total [2] finished [3..19] hist[0..16] [20] live steps
+  long long* stats;  // [0] seq_steps [1] accepted_total [2] finished [3..19] hist[0..16] [20] live steps [31] LayersP::error
   const int* imposed;  // k-hat to impose: imposed[step * imposed_stride + b], or null
   int imposed_stride;  // B for a whole schedule, 0 for a single step's vector
   int kmax, max_out, eos_id;
@@ -1054,11 +1054,11 @@ __global__ __launch_bounds__(256) void encode_init_kernel(StateP s, const int* s
 // Up to four arrays of ints from device to pinned host memory, then a word that tells the host they are there.  One
 // workgroup: its barrier orders the word behind every thread's stores.  (Two copies into pageable memory with a stream
 // synchronisation took 50 us at the end of a decode of 128 tokens.)
-struct FetchP { const int* src[4]; int n[4]; int* dst; unsigned long long* done; unsigned long long tag; };
+struct FetchP { const int* src[5]; int n[5]; int* dst; unsigned long long* done; unsigned long long tag; };
 __global__ __launch_bounds__(1024) void fetch_kernel(FetchP f) {
   int at = 0;
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
+  for (int a = 0; a < 5; ++a) {
     for (int q = threadIdx.x; q < f.n[a]; q += 1024) f.dst[at + q] = f.src[a][q];
     at += f.n[a];
   }
@@ -1221,10 +1221,15 @@ __global__ __launch_bounds__(256) void assemble_keys_kernel(const unsigned long 
 //   the cache rows of the accepted tokens (rejected rows are simply overwritten next step);
 //   P <- row k-hat of the table.
 //   step: row of the imposed schedule.
+//   scores (null: none; else [B][k][k][V], what the invocation left for the caller): become NaN if a wait of its layers ran out.
 __global__ __launch_bounds__(64) void accept_kernel(StateP s, const unsigned long long* keys, int k, int B,
-                                                    int commit, int step, int* accepted_out) {
+                                                    int commit, int step, int* accepted_out, float* scores, int V) {
   const int b = blockIdx.x, lane = threadIdx.x;
   if (b >= B) return;
+  if (scores && s.stats[31]) {
+    const size_t n = (size_t)k * k * V;
+    for (size_t i = lane; i < n; i += 64) scores[b * n + i] = __int_as_float(0x7FC00000);
+  }
   const int tick = s.dyn && commit ? s.tick[b] : 0, live_step = s.steps_done[b];
   int imp = 0;
   if (s.dyn && commit) { step_from_dyn(s, tick); imp = s.imp_next[b]; if (lane == 0) step_tick(s, b, tick); }

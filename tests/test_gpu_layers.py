@@ -111,6 +111,48 @@ def test_two_streams(k, B, d):
     assert out[0] == out[2] and out[1] == out[2]
 
 
+# A wait inside a kernel that ran out leaves a word behind the counters; here the test puts it there.  Everything that hands out results says so until the next
+# encode, which (recorded before, or not) and whose steps then go kernel by kernel: the scores are those of a context that always did.
+@pytest.mark.parametrize("k,B,d,encodes", [(8, 3, 512, 1), (10, 1, 1024, 9), (8, 4, 1024, 1)])
+def test_a_wait_that_ran_out(k, B, d, encodes, monkeypatch):
+    from paper_1811_03115_amd import binding
+    cfg = config(k, B, 9, 60, d=d)
+    weights = wl.make_weights(cfg)
+    ctx = gpu_context(cfg, weights)
+    monkeypatch.setenv("BPD_LAYERS_GROUP", "0")
+    ref = gpu_context(cfg, weights)
+    src, n = wl.make_sources(cfg)
+    two = torch.full((B,), 2, dtype=torch.int32, device="cuda")
+    tok = torch.from_numpy(np.random.default_rng(k).integers(3, 272, (B, k)).astype(np.int32)).cuda()
+
+    def scores(c):
+        c.bpd_encode(src, n, np.full(B, 60, np.int32))
+        for _ in range(3):
+            c.bpd_set_proposals(tok)
+            c.bpd_step(k, two)
+        c.bpd_set_proposals(tok)
+        return c.bpd_debug_step_logits(k).cpu()
+
+    want = scores(ref)
+    for _ in range(encodes):
+        assert not torch.equal(scores(ctx), want)
+    st = ctx.bpd_get_stats()
+    counters = torch.tensor([st.seq_steps, st.accepted_total, st.finished, *st.hist, st.steps], device="cuda")
+    start = -ctx.workspace.data_ptr() % 256
+    rows = ctx.workspace[start:start + (ctx.workspace.numel() - start) // 256 * 256].view(torch.int64).view(-1, 32)
+    at = (rows[:, :21] == counters).all(1).nonzero().flatten()
+    assert len(at) == 1
+    rows[at[0], 31] = 1
+    torch.cuda.synchronize()
+    assert torch.isnan(ctx.bpd_debug_step_logits(k)).all()
+    for call in (ctx.bpd_get_stats, ctx.bpd_get_state, ctx.bpd_get_output, lambda: ctx.bpd_decode(k), ctx.bpd_get_state):
+        with pytest.raises(binding.BpdError, match="wait ran out") as e:
+            call()
+        assert e.value.code == -5
+    assert torch.equal(scores(ctx), want)
+    ctx.bpd_get_state()
+
+
 # one kernel per captured step, replayed with other work of the program's between the replays: every replay finds the words that the workgroups count in cleared
 @pytest.mark.parametrize("k,B,d", [(6, 5, 512), (5, 20, 512), (9, 1, 1024), (7, 4, 1024), (8, 7, 1024)])
 def test_captured_steps(k, B, d):
