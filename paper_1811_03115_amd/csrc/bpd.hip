@@ -751,8 +751,8 @@ int layers_way(const bpd_ctx* ctx, int slots, int R) {
   if (!ctx->lay.layers_sync || ctx->layers_group == 0 || ctx->num_cus < LK_JOBS * LK_PLACES) return LAYERS_CHAIN;
   if (layers_shape(c)) return layers_fit(slots, R) ? LAYERS_JOBS : LAYERS_CHAIN;
   const long keys = attention_keys(ctx, c.max_out_len + c.k_max + 1, R, 1);
-  if (wide_layers_fit(slots, R, keys, c.max_src_len)) return LAYERS_WIDE;
-  return ctx->lay.layers_xn && tall_layers_fit(slots, R, keys, c.max_src_len) ? LAYERS_TALL : LAYERS_CHAIN;
+  if (wide_layers_fit(slots, R, keys, ctx->S)) return LAYERS_WIDE;
+  return ctx->lay.layers_xn && tall_layers_fit(slots, R, keys, ctx->S) ? LAYERS_TALL : LAYERS_CHAIN;
 }
 int layers_split_of(const bpd_ctx* ctx, int slots, int R) {
   const bpd_config& c = ctx->cfg;

@@ -14,7 +14,14 @@ inline bool layers_fit(int slots, int R) { return layers_per_job(slots) <= LK_PL
 //   two slots, 8 jobs of 16 rows          500: 140, 154   1000: 158, 172   2000: 205, 212 (two)
 constexpr int LK_SPLITS = 3;
 inline int layers_split(int slots, long keys) { return keys > 1024 && layers_per_job(slots) == 1 ? LK_SPLITS : 1; }
-// ... and of wide_layers_kernel: one block of at most 16 rows of four slots, caches that a workgroup walks in four rounds
+// ... and of wide_layers_kernel: one block of at most 16 rows of four slots.  Keys held and positions of the source that was encoded (not what the context
+// has room for): one workgroup has all of a head's, the chain of kernels deals them out, so that the two cross.  Six layers, us, chain and one kernel:
+//   keys     1 slot x 10 rows   64: 188, 154   1000: 215, 188   1300: 225, 204   2000: 228, 225   3000: 248, 260        1 x 1   1000: 182, 152   1300: 182, 166
+//            4 x 4              64: 211, 169   1000: 248, 207   2000: 251, 241   3000: 266, 277        5 x 8   64: 254, 189   1000: 294, 228   3000: 324, 296
+//            8 x 8              1000: 303, 272   3000: 363, 348       16 x 4   64: 279, 260   1000: 347, 342   1300: 371, 372   2000: 409, 416
+//   source   1 x 10             32: 185, 153   1000: 219, 186   1300: 232, 208   2000: 236, 241        16 x 4  1000: 361, 352   1300: 381, 385
+// (by events around the launches: some 5 us too much each.)  1024 of either is where 16 x 4, the first to, nearly crosses; the others gain 20 .. 65 us there: blocks of up
+// to 16 rows lose that by 1700 .. 2500, taller ones of up to eight slots beyond 3000.
 constexpr long WIDE_LAYERS_KEYS = 1024;
 // tall_layers_kernel: more rows, of up to 16 slots
 constexpr int TALL_LAYERS_ROWS = 64;

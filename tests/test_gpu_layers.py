@@ -111,6 +111,26 @@ def test_two_streams(k, B, d):
     assert out[0] == out[2] and out[1] == out[2]
 
 
+# which kernels run is a matter of the source that was encoded, not of what the context has room for: the same scores to the last bit
+@pytest.mark.parametrize("k,B", [(10, 1), (8, 5)])
+def test_room_for_longer_sources(k, B):
+    import dataclasses
+    cfg = config(k, B, 20, 60, d=1024)
+    weights = wl.make_weights(cfg)
+    src, n = wl.make_sources(cfg)
+    two = torch.full((B,), 2, dtype=torch.int32, device="cuda")
+    scores = []
+    for room in (20, 1100):
+        pos = np.zeros((room, 1024), np.float32)
+        pos[:20] = weights["pos_src"]
+        ctx = gpu_context(dataclasses.replace(cfg, max_src=room), dict(weights, pos_src=pos))
+        ctx.bpd_encode(src, n)
+        for _ in range(3):
+            ctx.bpd_step(k, two)
+        scores.append(ctx.bpd_debug_step_logits(k))
+    assert torch.equal(*scores)
+
+
 # A wait inside a kernel that ran out leaves a word behind the counters; here the test puts it there.  Everything that hands out results says so until the next
 # encode, which (recorded before, or not) and whose steps then go kernel by kernel: the scores are those of a context that always did.
 @pytest.mark.parametrize("k,B,d,encodes", [(8, 3, 512, 1), (10, 1, 1024, 9), (8, 4, 1024, 1)])
