@@ -105,33 +105,34 @@ bool small_shape(const bpd_config& c) {
   return c.dtype == BPD_F32 && d <= 256 && V <= 4096 && c.n_dec_layers <= 8 && c.n_enc_layers <= 8 && (c.n_dec_layers * (6 * d * d + 2 * d * F) + 2 * k * d * F + V * d) * 4 <= SMALL_WEIGHTS_MAX;
 }
 
-// Does one workgroup per sequence beat the launches?  It walks the phases of the layers one after the other, with weights at the rate
-// one CU gets and keys 64 at a time by eight waves; the launches cost 4.4 us each and their products walk K serially.  Estimates in
-// us, their constants fitted to 27 steps and 21 encodes, which they are within 30 % of (one, launches; tests/host checks all; the steps of one
-// workgroup have become a quarter to a third shorter since, so that the rule errs towards the launches):
-//   steps    d = 64, 2 layers, 4 rows   64 keys: 71, 157   512: 102, 163   1000: 135, 158   1900: 197, 164   3900: 364, 175
-//            d = 64, 8 layers, 16 rows  1 key: 563, 498    1000: 1698, 537         d = 64, 2 layers, 12 rows  1 key: 185, 143
-//            d = 128, 2 layers, 4 rows  1: 118, 180        1000: 272, 197          d = 256, 1 layer, 4 rows   1: 154, 144
-//   encodes  d = 64, 2 layers    16 tokens: 134, 231   33: 235, 234   64: 334, 209   128: 736, 239   300: 2549, 242
-//            d = 128, 2 layers   16: 233, 283          32: 353, 284                                  d = 256, 1 layer  16: 272, 223
+// Does one workgroup per sequence beat the launches?  It walks the phases of the layers one after the other, with weights and cache rows
+// at the rate one CU gets and keys 64 at a time by eight waves; the launches cost 3.5 us each, and their products walk K (the vocabulary's: V rows
+// among 256 threads) serially.  Estimates in us, their constants fitted to 273 steps and 345 encodes of 40 shapes, half of them drawn: within a third
+// of all but a hundredth of them, and the faster way wherever the two differ by more than a tenth (tests/host holds a choice of them).  (one, launches):
+//   steps    d = 64, 2 layers, 4 rows    61 keys: 53, 123    632: 70, 126     1120: 84, 126     2020: 110, 131    3620: 203, 132
+//            d = 64, 8 layers, 16 rows   241: 469, 528       960: 706, 517            d = 64, 2 layers, 12 rows   181: 155, 139
+//            d = 128, 2 layers, 4 rows   61: 100, 173        1120: 188, 176           d = 256, 1 layer, 4 rows    61: 130, 135
+//   encodes  d = 64, 2 layers    16 tokens: 104, 199   33: 204, 192   64: 272, 195   128: 548, 196   300: 1611, 226
+//            d = 128, 2 layers   16: 187, 270          32: 282, 264   33: 363, 264
 inline double small_bytes_us(double floats) { return floats * 4 / 65e3; }
 // `rows` rows per sequence with k heads, over `keys` keys of its own and `src` of its source
 inline double small_step_us(const bpd_config& c, int rows, int k, long keys, long src) {
   const double d = c.d_model, F = c.d_ff, V = c.vocab, L = c.n_dec_layers;
   const auto up = [](long a, long b) { return (double)((a + b - 1) / b); };
-  const double phases = L * (c.d_model <= 64 ? 8 : 11) + 2, phase = rows <= 4 ? 2 : (rows <= 8 ? 3 : 4);
-  return phase * phases + small_bytes_us(L * (6 * d * d + 2 * d * F) + 2 * k * d * F + V * d) +
-         1.25 * L * up((long)c.n_heads * rows, 8) * (up(keys, 64) + up(src, 64)) + 3 * up((long)rows * k, 16) * up(c.vocab, 512);
+  const double phases = L * (c.d_model <= 64 ? 8 : 11) + 2, phase = rows <= 4 ? 1.3 : (rows <= 8 ? 2 : 2.8);
+  return phase * phases + small_bytes_us(L * (6 * d * d + 2 * d * F) + 2 * k * d * F + V * d + 2 * L * d * (keys + src)) +
+         0.36 * L * up((long)c.n_heads * rows, 8) * (up(keys, 64) + up(src, 64)) + 4.5 * up((long)rows * k, 16) * up(c.vocab, 512);
 }
 inline double launched_step_us(const bpd_config& c) {
-  const double d = c.d_model, F = c.d_ff, L = c.n_dec_layers;
-  return 4.4 * (11 * L + 6) + 0.022 * (L * (5 * d + F) + d + F);
+  const double d = c.d_model, F = c.d_ff, V = c.vocab, L = c.n_dec_layers;
+  return 3.5 * (11 * L + 6) + 0.032 * (L * (5 * d + F) + d + F) + 0.15e-3 * V * d;
 }
 inline bool small_step_pays(const bpd_config& c, int k, long keys, long src) { return small_step_us(c, k, k, keys, src) < launched_step_us(c); }
+// (a source tile of 16 rows walks the encoder's phases, with the weights at 55 KB/us, and attends to every other)
 inline bool small_encode_pays(const bpd_config& c, int S) {
   const double d = c.d_model, F = c.d_ff, E = c.n_enc_layers, L = c.n_dec_layers, tiles = (S + 15) / 16;
-  const double one = tiles * (5 * (E * (c.d_model <= 64 ? 6 : 7) + 1 + L) + small_bytes_us(E * (4 * d * d + 2 * d * F) + L * 2 * d * d)) + small_step_us(c, 1, c.k_max, 1, S);
-  return one < 4.4 * (7 * E + L + 4) + 0.022 * (E * (3 * d + F) + L * d) + launched_step_us(c);
+  const double one = tiles * (2.7 * (E * (c.d_model <= 64 ? 6 : 7) + 1 + L) + (E * (4 * d * d + 2 * d * F) + L * 2 * d * d) * 4 / 55e3 + 0.8 * E * tiles * d / 64) + small_step_us(c, 1, c.k_max, 1, S);
+  return one < 1.1 * (7 * E + L + 4) + 0.03 * (E * (3 * d + F) + L * d) + launched_step_us(c);
 }
 
 // Shapes and row counts that run on the kernels with a constant K (bpd_row_gemm.h).

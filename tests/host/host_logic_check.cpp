@@ -105,21 +105,87 @@ int main() {
     check_config(c);
     ++configs;
   }
-  // one workgroup per sequence or launches: measured us of both (d, d_ff, vocab, layers, rows, keys: one, launches), and the
-  // rule takes the faster one wherever they differ by more than a tenth
-  const int STEPS[][8] = {{64, 256, 256, 2, 4, 1, 68, 134}, {64, 256, 256, 2, 4, 64, 71, 157}, {64, 256, 256, 2, 4, 512, 102, 163}, {64, 256, 256, 2, 4, 1000, 135, 158},
-                          {64, 256, 256, 2, 4, 1900, 197, 164}, {64, 256, 256, 2, 4, 3900, 364, 175}, {64, 1024, 1024, 8, 4, 1, 279, 715}, {64, 256, 256, 8, 16, 1, 563, 498},
-                          {64, 256, 256, 8, 16, 1000, 1698, 537}, {128, 512, 256, 2, 4, 1, 118, 180}, {128, 512, 256, 2, 4, 512, 195, 200}, {128, 512, 256, 2, 4, 1000, 272, 197},
-                          {128, 512, 256, 4, 4, 1, 192, 369}, {256, 512, 256, 1, 4, 1, 154, 144}, {256, 256, 256, 3, 1, 1, 169, 252}, {256, 256, 256, 3, 1, 512, 252, 352},
-                          {256, 256, 256, 3, 1, 1000, 337, 366}, {256, 256, 256, 3, 1, 1900, 497, 378}, {32, 64, 64, 1, 16, 1, 95, 74}, {64, 256, 256, 2, 8, 1, 105, 141},
-                          {64, 256, 256, 4, 8, 1, 158, 245}, {128, 512, 256, 2, 8, 1, 209, 216}, {64, 256, 4096, 2, 4, 1, 115, 166}, {64, 256, 256, 2, 16, 1, 255, 146},
-                          {64, 256, 256, 2, 12, 1, 185, 143}, {32, 128, 256, 2, 8, 1, 75, 117}, {64, 256, 256, 2, 1, 1, 50, 121}};
-  const int ENCODES[][8] = {{64, 256, 256, 2, 4, 16, 134, 231}, {64, 256, 256, 2, 4, 33, 235, 234}, {64, 256, 256, 2, 4, 64, 334, 209}, {64, 256, 256, 2, 4, 128, 736, 239},
-                            {64, 256, 256, 2, 4, 300, 2549, 242}, {64, 1024, 1024, 8, 4, 16, 567, 1280}, {64, 1024, 1024, 8, 4, 64, 1595, 1307}, {64, 1024, 1024, 8, 4, 128, 3545, 1451},
-                            {64, 256, 256, 8, 16, 16, 433, 796}, {128, 512, 256, 2, 4, 16, 233, 283}, {128, 512, 256, 2, 4, 32, 353, 284}, {128, 512, 256, 4, 4, 16, 397, 640},
-                            {256, 512, 256, 1, 4, 16, 272, 223}, {256, 256, 256, 3, 1, 16, 488, 573}, {32, 64, 64, 1, 16, 16, 75, 120}, {32, 64, 64, 1, 16, 128, 276, 130},
-                            {64, 256, 256, 2, 8, 16, 141, 219}, {64, 256, 256, 4, 8, 16, 227, 419}, {128, 512, 256, 2, 8, 16, 261, 301}, {64, 256, 4096, 2, 4, 16, 166, 263},
-                            {64, 256, 256, 2, 16, 16, 155, 226}, {64, 256, 256, 2, 1, 16, 128, 220}, {32, 128, 256, 2, 8, 16, 110, 191}};
+  // one workgroup per sequence or launches: measured us of both (d, d_ff, vocab, layers, rows, keys or source tokens: one, launches), the shortest of a shape
+  // and those on both sides of where the two cross, and the rule takes the faster one wherever they differ by more than a tenth
+  const int STEPS[][8] = {{64, 256, 256, 2, 4, 61, 53, 123}, {64, 256, 256, 2, 4, 1120, 84, 126}, {64, 256, 256, 2, 4, 2020, 110, 131},
+                          {64, 256, 256, 2, 4, 3620, 203, 132}, {64, 1024, 1024, 8, 4, 61, 221, 741}, {64, 1024, 1024, 8, 4, 1120, 391, 767},
+                          {64, 1024, 1024, 8, 4, 2020, 543, 771}, {64, 1024, 1024, 8, 4, 3620, 822, 788}, {64, 256, 256, 8, 16, 241, 469, 528},
+                          {64, 256, 256, 8, 16, 960, 706, 517}, {64, 256, 256, 8, 16, 2400, 1430, 549}, {128, 512, 256, 2, 4, 61, 100, 173},
+                          {128, 512, 256, 2, 4, 632, 150, 176}, {128, 512, 256, 2, 4, 1120, 188, 176}, {128, 512, 256, 4, 4, 61, 162, 337},
+                          {128, 512, 256, 4, 4, 632, 245, 352}, {128, 512, 256, 4, 4, 1120, 327, 368}, {128, 512, 256, 4, 4, 2020, 475, 370},
+                          {256, 512, 256, 1, 4, 61, 130, 135}, {256, 512, 256, 1, 4, 240, 142, 137}, {256, 512, 256, 1, 4, 1120, 217, 140},
+                          {256, 256, 256, 3, 1, 16, 155, 270}, {256, 256, 256, 3, 1, 1029, 249, 327}, {256, 256, 256, 3, 1, 1929, 336, 329},
+                          {32, 64, 64, 1, 16, 241, 87, 70}, {32, 64, 64, 1, 16, 2400, 141, 71}, {64, 256, 256, 2, 8, 121, 89, 132},
+                          {64, 256, 256, 2, 8, 480, 104, 142}, {64, 256, 256, 2, 8, 960, 131, 138}, {64, 256, 256, 2, 8, 1240, 147, 140},
+                          {64, 256, 256, 4, 8, 121, 133, 241}, {64, 256, 256, 4, 8, 480, 163, 256}, {64, 256, 256, 4, 8, 960, 237, 249},
+                          {64, 256, 256, 4, 8, 1240, 279, 254}, {128, 512, 256, 2, 8, 121, 190, 206}, {128, 512, 256, 2, 8, 480, 223, 219},
+                          {128, 512, 256, 2, 8, 1240, 327, 221}, {64, 256, 4096, 2, 4, 61, 84, 161}, {64, 256, 4096, 2, 4, 1120, 117, 165},
+                          {64, 256, 4096, 2, 4, 2020, 157, 165}, {64, 256, 4096, 2, 4, 3620, 241, 170}, {64, 256, 256, 2, 16, 241, 224, 148},
+                          {64, 256, 256, 2, 16, 2400, 471, 148}, {64, 256, 256, 2, 12, 181, 155, 139}, {64, 256, 256, 2, 12, 1800, 287, 141},
+                          {32, 128, 256, 2, 8, 121, 66, 111}, {32, 128, 256, 2, 8, 960, 88, 116}, {32, 128, 256, 2, 8, 1240, 95, 114},
+                          {32, 128, 256, 2, 8, 2144, 122, 119}, {64, 256, 256, 2, 1, 16, 47, 121}, {64, 256, 256, 2, 1, 1029, 67, 127},
+                          {64, 256, 256, 2, 1, 1929, 83, 122}, {64, 256, 256, 2, 1, 3529, 129, 126}, {128, 256, 1024, 6, 4, 61, 197, 454},
+                          {128, 256, 1024, 6, 4, 632, 322, 469}, {128, 256, 1024, 6, 4, 1120, 442, 477}, {128, 256, 1024, 6, 4, 2020, 668, 480},
+                          {32, 128, 1024, 4, 16, 241, 252, 229}, {32, 128, 1024, 4, 16, 2400, 472, 231}, {256, 256, 256, 1, 8, 121, 187, 120},
+                          {256, 256, 256, 1, 8, 1240, 332, 126}, {128, 64, 4096, 1, 6, 91, 202, 147}, {32, 128, 1024, 4, 13, 196, 208, 211},
+                          {32, 128, 1024, 4, 13, 780, 254, 218}, {192, 32, 2048, 4, 1, 16, 176, 348}, {192, 32, 2048, 4, 1, 1029, 300, 367},
+                          {192, 32, 2048, 4, 1, 1929, 409, 373}, {64, 64, 64, 1, 7, 106, 49, 67}, {64, 64, 64, 1, 7, 420, 57, 72},
+                          {64, 64, 64, 1, 7, 840, 68, 70}, {64, 64, 64, 1, 7, 1211, 78, 70}, {64, 64, 256, 5, 11, 166, 198, 260},
+                          {64, 64, 256, 5, 11, 660, 271, 274}, {64, 64, 256, 5, 11, 990, 355, 272}, {64, 512, 4096, 4, 6, 91, 249, 309},
+                          {64, 512, 4096, 4, 6, 360, 272, 329}, {64, 512, 4096, 4, 6, 720, 320, 326}, {64, 512, 4096, 4, 6, 1182, 385, 334},
+                          {96, 256, 256, 3, 9, 136, 215, 209}, {32, 128, 512, 1, 11, 166, 83, 67}, {32, 128, 512, 5, 16, 241, 228, 287},
+                          {32, 128, 512, 5, 16, 960, 297, 266}, {32, 1024, 256, 4, 4, 61, 96, 318}, {32, 1024, 256, 4, 4, 2020, 234, 327},
+                          {32, 1024, 256, 4, 4, 3620, 356, 334}, {64, 256, 512, 6, 9, 136, 244, 352}, {64, 256, 512, 6, 9, 540, 316, 380},
+                          {64, 256, 512, 6, 9, 810, 385, 368}, {128, 32, 2048, 6, 10, 151, 498, 432}, {32, 256, 64, 4, 11, 166, 159, 218},
+                          {32, 256, 64, 4, 11, 660, 196, 230}, {32, 256, 64, 4, 11, 990, 231, 232}, {32, 256, 64, 4, 11, 1320, 264, 232},
+                          {256, 128, 512, 3, 3, 46, 175, 310}, {256, 128, 512, 3, 3, 339, 227, 322}, {256, 128, 512, 3, 3, 603, 279, 331},
+                          {256, 128, 512, 3, 3, 1089, 377, 336}, {32, 64, 4096, 6, 9, 136, 298, 293}, {128, 1024, 1024, 3, 2, 31, 152, 327},
+                          {128, 1024, 1024, 3, 2, 1060, 228, 365}, {128, 1024, 1024, 3, 2, 1960, 300, 366}, {128, 1024, 1024, 3, 2, 3560, 428, 374},
+                          {32, 64, 1024, 6, 5, 76, 123, 276}, {32, 64, 1024, 6, 5, 665, 171, 281}, {32, 64, 1024, 6, 5, 1150, 209, 286},
+                          {32, 64, 1024, 6, 5, 2050, 289, 283}, {32, 256, 512, 3, 15, 226, 195, 189}, {96, 256, 1024, 3, 4, 61, 98, 203},
+                          {96, 256, 1024, 3, 4, 632, 152, 210}, {96, 256, 1024, 3, 4, 1120, 235, 213}, {64, 32, 1024, 5, 12, 181, 250, 269},
+                          {64, 32, 1024, 5, 12, 720, 328, 278}};
+  const int ENCODES[][8] = {{64, 256, 256, 2, 4, 1, 95, 175}, {64, 256, 256, 2, 4, 32, 157, 193}, {64, 256, 256, 2, 4, 33, 204, 192},
+                          {64, 1024, 1024, 8, 4, 1, 428, 1173}, {64, 1024, 1024, 8, 4, 33, 1002, 1270}, {64, 1024, 1024, 8, 4, 48, 1067, 1258},
+                          {64, 1024, 1024, 8, 4, 64, 1346, 1258}, {64, 256, 256, 8, 16, 1, 324, 651}, {64, 256, 256, 8, 16, 32, 562, 694},
+                          {64, 256, 256, 8, 16, 33, 749, 704}, {128, 512, 256, 2, 4, 1, 165, 244}, {128, 512, 256, 2, 4, 17, 257, 268},
+                          {128, 512, 256, 2, 4, 32, 282, 264}, {128, 512, 256, 4, 4, 1, 279, 543}, {128, 512, 256, 4, 4, 17, 456, 590},
+                          {128, 512, 256, 4, 4, 32, 504, 580}, {128, 512, 256, 4, 4, 33, 663, 582}, {256, 512, 256, 1, 4, 1, 186, 194},
+                          {256, 256, 256, 3, 1, 1, 315, 533}, {32, 64, 64, 1, 16, 1, 57, 87}, {32, 64, 64, 1, 16, 32, 78, 91}, {32, 64, 64, 1, 16, 33, 96, 92},
+                          {64, 256, 256, 2, 8, 1, 100, 179}, {64, 256, 256, 2, 8, 32, 161, 197}, {64, 256, 256, 2, 8, 33, 209, 199},
+                          {64, 256, 256, 4, 8, 1, 163, 351}, {64, 256, 256, 4, 8, 32, 282, 360}, {64, 256, 256, 4, 8, 33, 376, 357},
+                          {128, 512, 256, 2, 8, 1, 192, 249}, {128, 512, 256, 2, 8, 16, 215, 268}, {128, 512, 256, 2, 8, 17, 284, 268},
+                          {64, 256, 4096, 2, 4, 1, 120, 206}, {64, 256, 4096, 2, 4, 32, 182, 230}, {64, 256, 4096, 2, 4, 48, 243, 228},
+                          {64, 256, 256, 2, 16, 1, 111, 172}, {64, 256, 256, 2, 16, 32, 172, 196}, {64, 256, 256, 2, 16, 33, 220, 199},
+                          {64, 256, 256, 2, 12, 1, 107, 174}, {64, 256, 256, 2, 12, 32, 168, 197}, {64, 256, 256, 2, 12, 33, 216, 201},
+                          {32, 128, 256, 2, 8, 1, 84, 143}, {32, 128, 256, 2, 8, 32, 126, 160}, {32, 128, 256, 2, 8, 48, 168, 158},
+                          {64, 256, 256, 2, 1, 1, 91, 176}, {64, 256, 256, 2, 1, 32, 154, 192}, {64, 256, 256, 2, 1, 48, 215, 190},
+                          {128, 256, 1024, 6, 4, 1, 346, 690}, {128, 256, 1024, 6, 4, 17, 584, 759}, {128, 256, 1024, 6, 4, 32, 644, 758},
+                          {128, 256, 1024, 6, 4, 33, 861, 758}, {32, 128, 1024, 4, 16, 1, 141, 261}, {32, 128, 1024, 4, 16, 32, 222, 295},
+                          {32, 128, 1024, 4, 16, 64, 377, 284}, {256, 256, 256, 1, 8, 4, 178, 172}, {128, 64, 4096, 1, 6, 1, 112, 173},
+                          {128, 64, 4096, 1, 6, 17, 149, 182}, {128, 64, 4096, 1, 6, 32, 161, 185}, {128, 64, 4096, 1, 6, 33, 194, 181},
+                          {32, 128, 1024, 4, 13, 1, 141, 266}, {32, 128, 1024, 4, 13, 32, 222, 296}, {32, 128, 1024, 4, 13, 48, 303, 289},
+                          {192, 32, 2048, 4, 1, 1, 329, 543}, {192, 32, 2048, 4, 1, 17, 549, 582}, {192, 32, 2048, 4, 1, 32, 614, 593},
+                          {128, 64, 64, 3, 15, 1, 158, 256}, {128, 64, 64, 3, 15, 17, 268, 278}, {128, 64, 64, 3, 15, 32, 304, 287},
+                          {64, 64, 64, 1, 7, 1, 58, 93}, {64, 64, 64, 1, 7, 32, 87, 101}, {64, 64, 64, 1, 7, 33, 109, 98}, {64, 64, 256, 5, 11, 1, 170, 341},
+                          {64, 64, 256, 5, 11, 32, 306, 378}, {64, 64, 256, 5, 11, 33, 408, 376}, {64, 512, 4096, 4, 6, 1, 224, 424},
+                          {64, 512, 4096, 4, 6, 32, 359, 458}, {64, 512, 4096, 4, 6, 48, 489, 474}, {96, 256, 256, 3, 9, 1, 189, 268},
+                          {96, 256, 256, 3, 9, 16, 215, 302}, {96, 256, 256, 3, 9, 32, 322, 307}, {32, 128, 512, 1, 11, 1, 60, 86},
+                          {32, 128, 512, 1, 11, 32, 83, 92}, {32, 128, 512, 1, 11, 33, 101, 95}, {32, 128, 512, 5, 16, 1, 169, 515},
+                          {32, 128, 512, 5, 16, 32, 265, 349}, {32, 128, 512, 5, 16, 48, 366, 343}, {256, 128, 1024, 1, 14, 1, 181, 191},
+                          {96, 256, 2048, 1, 15, 1, 130, 140}, {96, 256, 2048, 1, 15, 16, 138, 149}, {96, 256, 2048, 1, 15, 17, 168, 144},
+                          {32, 1024, 256, 4, 4, 1, 185, 491}, {32, 1024, 256, 4, 4, 48, 426, 523}, {32, 1024, 256, 4, 4, 64, 534, 516},
+                          {64, 256, 512, 6, 9, 1, 242, 460}, {64, 256, 512, 6, 9, 32, 425, 519}, {64, 256, 512, 6, 9, 33, 565, 527},
+                          {128, 32, 2048, 6, 10, 1, 310, 580}, {128, 32, 2048, 6, 10, 17, 522, 650}, {128, 32, 2048, 6, 10, 32, 587, 649},
+                          {128, 32, 2048, 6, 10, 33, 775, 647}, {32, 256, 64, 4, 11, 1, 149, 283}, {32, 256, 64, 4, 11, 32, 236, 321},
+                          {32, 256, 64, 4, 11, 64, 403, 328}, {256, 128, 512, 3, 3, 1, 304, 491}, {32, 64, 4096, 6, 9, 1, 198, 374},
+                          {32, 64, 4096, 6, 9, 32, 312, 419}, {32, 64, 4096, 6, 9, 64, 533, 416}, {128, 1024, 1024, 3, 2, 1, 280, 564},
+                          {128, 1024, 1024, 3, 2, 17, 446, 597}, {128, 1024, 1024, 3, 2, 32, 485, 603}, {128, 1024, 1024, 3, 2, 33, 635, 603},
+                          {32, 64, 1024, 6, 5, 1, 183, 365}, {32, 64, 1024, 6, 5, 33, 394, 411}, {32, 64, 1024, 6, 5, 64, 516, 411},
+                          {32, 256, 512, 3, 15, 1, 124, 223}, {32, 256, 512, 3, 15, 32, 190, 258}, {32, 256, 512, 3, 15, 64, 316, 257},
+                          {96, 256, 1024, 3, 4, 1, 168, 285}, {96, 256, 1024, 3, 4, 17, 273, 311}, {96, 256, 1024, 3, 4, 32, 303, 317},
+                          {96, 256, 1024, 3, 4, 33, 397, 315}, {64, 32, 1024, 5, 12, 1, 172, 335}, {64, 32, 1024, 5, 12, 32, 307, 379},
+                          {64, 32, 1024, 5, 12, 33, 408, 378}};
   auto fp32_model = [](const int* m) {
     bpd_config c{};
     c.n_enc_layers = c.n_dec_layers = m[3]; c.d_model = m[0]; c.n_heads = m[0] / 16; c.d_ff = m[1]; c.vocab = m[2]; c.k_max = m[4];
