@@ -241,8 +241,8 @@ __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLd
 // not evict the weights).
 // LIMF: the sequence's length is fetched first and only groups that hold keys are fetched: one more dependent round trip
 // (many sequences: the traffic is what counts; local attention: where the keys start depends on it).
-// ARGS: p lies in the kernel's arguments.  AUX: cache policy of the loads of Q (16: past the L1, for queries that this very kernel has written).
-template <bool KVNT, bool LIMF, int QU, bool ARGS, int AUX = 0>
+// ARGS: p lies in the kernel's arguments.
+template <bool KVNT, bool LIMF, int QU, bool ARGS>
 __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP& qp, const AttnLds& sm, int h, int b, int sb, int z,
                                                     int nheads, int nz, int tid, int nw) {
   constexpr int RT = 16, DH = 64, G = QU < 0 ? 2 : 1;       // groups of keys per wave and round
@@ -380,7 +380,7 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
     const unsigned off = (lr * p.d + h * DH + 8 * lq) * 4;
     u32x4 qa[2][2];
 #pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) { qa[s2][0] = __builtin_amdgcn_raw_buffer_load_b128(qr, off + s2 * 128, 0, AUX); qa[s2][1] = __builtin_amdgcn_raw_buffer_load_b128(qr, off + s2 * 128 + 16, 0, AUX); }
+    for (int s2 = 0; s2 < 2; ++s2) { qa[s2][0] = __builtin_amdgcn_raw_buffer_load_b128(qr, off + s2 * 128, 0, 0); qa[s2][1] = __builtin_amdgcn_raw_buffer_load_b128(qr, off + s2 * 128 + 16, 0, 0); }
     attn_load_kv<KVNT, G>(kr, vr, first + wave, nw, lane, kf, vf);
     lim = p.limit[b];
     out = (bf16_t*)p.out;

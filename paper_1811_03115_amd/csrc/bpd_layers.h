@@ -150,6 +150,12 @@ __device__ __forceinline__ void lk_raise(unsigned* flag, unsigned v, int lane) {
   lk_stores_done();
   if (lane == 0) lk_store(flag, v);
 }
+// Four columns of scaled queries as the attention's operands
+__device__ __forceinline__ void lk_halves(const f32x4& v, u32x2& hi, u32x2& lo) {
+  hi = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
+  lo = u32x2{cvt_pk_bf16(v[0] - __uint_as_float(hi[0] << 16), v[1] - __uint_as_float(hi[0] & 0xFFFF0000u)),
+             cvt_pk_bf16(v[2] - __uint_as_float(hi[1] << 16), v[3] - __uint_as_float(hi[1] & 0xFFFF0000u))};
+}
 // LayerNorm of up to 16 rows of 512 into LDS as bf16, rows 520 apart; wave hw takes rows hw, hw + 4, ..
 template <int N>
 __device__ __forceinline__ void lk_norm_rows(const rsrc_t& xr, int rows, const f32x4 (&g)[2], const f32x4 (&b)[2], float eps, bf16_t* xs, int hw, int lane) {
@@ -331,13 +337,11 @@ struct LkHelper {
       const int tile = place * N + hw, n = tile * 16 + lq * 4;
       if constexpr (EPI == LK_QKV) {
         const int c = tile / (D / 16), col = n - c * D;
-        if (c == 0) {                            // queries, scaled, as the attention's operands: hi, and lo D columns on
-          v *= p.scale;
-          const u32x2 hi = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
+        if (c == 0) {                            // (lo: D columns on)
+          u32x2 hi, lo;
+          lk_halves(v * p.scale, hi, lo);
           bf16_t* q = p.q + (size_t)(j.row0 + lr) * (2 * D) + col;
-          *(u32x2*)q = hi;
-          *(u32x2*)(q + D) = u32x2{cvt_pk_bf16(v[0] - __uint_as_float(hi[0] << 16), v[1] - __uint_as_float(hi[0] & 0xFFFF0000u)),
-                                   cvt_pk_bf16(v[2] - __uint_as_float(hi[1] << 16), v[3] - __uint_as_float(hi[1] & 0xFFFF0000u))};
+          *(u32x2*)q = hi; *(u32x2*)(q + D) = lo;
         }
         else if (sb >= 0) kv_frag_store((c == 1 ? p.selfK : p.selfV) + l * p.self_layer, c == 2, sb, D / 64, p.self_groups, key, col, cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
       } else if constexpr (EPI == LK_RELU) {
@@ -442,13 +446,9 @@ struct LkHelper {
       lk_barrier();
       lk_barrier();
       {
-        f32x4 v = partial_sums<4>(lane);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] *= p.scale;
+        u32x2 hi, lo;
+        lk_halves(partial_sums<4>(lane) * p.scale, hi, lo);
         // operand lane 16 q + lr of half s holds columns 32 s + 8 q .. + 7
-        const u32x2 hi = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
-        const u32x2 lo = u32x2{cvt_pk_bf16(v[0] - __uint_as_float(hi[0] << 16), v[1] - __uint_as_float(hi[0] & 0xFFFF0000u)),
-                               cvt_pk_bf16(v[2] - __uint_as_float(hi[1] << 16), v[3] - __uint_as_float(hi[1] & 0xFFFF0000u))};
         const int to = ((hw >> 1) * 64 + ((hw & 1) * 2 + (lq >> 1)) * 16 + lr) * 2 + (lq & 1);
         q_s[to] = hi; q_s[256 + to] = lo;
       }

@@ -198,25 +198,7 @@ struct TkHelper : WkHelper {
       f32x4 v = ((part[0] + part[1]) + part[2]) + part[3];
       if (m >= j.rows) continue;
       if constexpr (OP == WK_QKV) {
-        const int c = tile >> 6, col = n - c * D;
-        if (c == 0) {                            // (as in WkHelper)
-          v *= p.scale;
-          const u32x2 hi = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
-          const u32x2 lo = u32x2{cvt_pk_bf16(v[0] - __uint_as_float(hi[0] << 16), v[1] - __uint_as_float(hi[0] & 0xFFFF0000u)),
-                                 cvt_pk_bf16(v[2] - __uint_as_float(hi[1] << 16), v[3] - __uint_as_float(hi[1] & 0xFFFF0000u))};
-          bf16_t* q = p.q + (size_t)m * (2 * D) + col;
-          if (j.full) { *(u32x2*)q = hi; *(u32x2*)(q + D) = lo; }
-          else { wk_store8(q, hi); wk_store8(q + D, lo); }
-        } else if (sb >= 0) {
-          const unsigned lo = cvt_pk_bf16(v[0], v[1]), hi = cvt_pk_bf16(v[2], v[3]);
-          bf16_t* cache = (c == 1 ? p.selfK : p.selfV) + l * p.self_layer;
-          if (j.full) kv_frag_store(cache, c == 2, sb, H, p.self_groups, key, col, lo, hi);
-          else {
-            bf16_t* dst = cache + ((size_t)sb * H + (col >> 6)) * p.self_groups * KV_GROUP;
-            if (c == 1) wk_store8(dst + k_frag_at(key, col & 63), u32x2{lo, hi});
-            else { dst += v_frag_at(key, col & 63); wk_store2(dst, lo); wk_store2(dst + 8, lo >> 16); wk_store2(dst + 16, hi); wk_store2(dst + 24, hi >> 16); }
-          }
-        }
+        store_qkv(l, tile >> 6, n - (tile >> 6) * D, m, v);
       } else if constexpr (OP == WK_UP) {
         v += bs;
 #pragma unroll

@@ -157,6 +157,27 @@ struct WkHelper {
     for (int h = 0; h < 4; ++h) { g[h] = *(const f32x4*)(ln + h * 256 + lane * 4); b[h] = *(const f32x4*)(ln + D + h * 256 + lane * 4); }
   }
 
+  // Columns col .. col + 3 of a row of queries (c = 0; lo: D columns on), keys (1) or values (2): within the XCD, or (not full) to memory
+  __device__ __forceinline__ void store_qkv(int l, int c, int col, int row, f32x4 v) const {
+    const LayersP& p = lk_args();
+    if (c == 0) {
+      u32x2 hi, lo;
+      lk_halves(v * p.scale, hi, lo);
+      bf16_t* q = p.q + (size_t)row * (2 * D) + col;
+      if (j.full) { *(u32x2*)q = hi; *(u32x2*)(q + D) = lo; }
+      else { wk_store8(q, hi); wk_store8(q + D, lo); }
+    } else if (sb >= 0) {
+      const unsigned lo = cvt_pk_bf16(v[0], v[1]), hi = cvt_pk_bf16(v[2], v[3]);
+      bf16_t* cache = (c == 1 ? p.selfK : p.selfV) + l * p.self_layer;
+      if (j.full) kv_frag_store(cache, c == 2, sb, H, p.self_groups, key, col, lo, hi);
+      else {
+        bf16_t* dst = cache + ((size_t)sb * H + (col >> 6)) * p.self_groups * KV_GROUP;
+        if (c == 1) wk_store8(dst + k_frag_at(key, col & 63), u32x2{lo, hi});
+        else { dst += v_frag_at(key, col & 63); wk_store2(dst, lo); wk_store2(dst + 8, lo >> 16); wk_store2(dst + 16, hi); wk_store2(dst + 24, hi >> 16); }
+      }
+    }
+  }
+
   template <int OP, int K, bool LN, bool BIAS>
   __device__ __forceinline__ void product(int l, const float* LayersP::*lnp, const float* LayersP::*biasp, int from, int count, int heads = 0) {
     const LayersP& p = lk_args();
@@ -189,25 +210,7 @@ struct WkHelper {
       f32x4 v = partial_sums(1, 0, lane);
       if (lr >= j.rows) continue;
       if constexpr (OP == WK_QKV) {
-        const int c = tile >> 6, col = n - c * D;
-        if (c == 0) {                            // queries, scaled, as the attention's operands: hi, and lo D columns on
-          v *= p.scale;
-          const u32x2 hi = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
-          const u32x2 lo = u32x2{cvt_pk_bf16(v[0] - __uint_as_float(hi[0] << 16), v[1] - __uint_as_float(hi[0] & 0xFFFF0000u)),
-                                 cvt_pk_bf16(v[2] - __uint_as_float(hi[1] << 16), v[3] - __uint_as_float(hi[1] & 0xFFFF0000u))};
-          bf16_t* q = p.q + (size_t)lr * (2 * D) + col;
-          if (j.full) { *(u32x2*)q = hi; *(u32x2*)(q + D) = lo; }
-          else { wk_store8(q, hi); wk_store8(q + D, lo); }
-        } else if (sb >= 0) {
-          const unsigned lo = cvt_pk_bf16(v[0], v[1]), hi = cvt_pk_bf16(v[2], v[3]);
-          bf16_t* cache = (c == 1 ? p.selfK : p.selfV) + l * p.self_layer;
-          if (j.full) kv_frag_store(cache, c == 2, sb, H, p.self_groups, key, col, lo, hi);
-          else {
-            bf16_t* dst = cache + ((size_t)sb * H + (col >> 6)) * p.self_groups * KV_GROUP;
-            if (c == 1) wk_store8(dst + k_frag_at(key, col & 63), u32x2{lo, hi});
-            else { dst += v_frag_at(key, col & 63); wk_store2(dst, lo); wk_store2(dst + 8, lo >> 16); wk_store2(dst + 16, hi); wk_store2(dst + 24, hi >> 16); }
-          }
-        }
+        store_qkv(l, tile >> 6, n - (tile >> 6) * D, lr, v);
       } else if constexpr (OP == WK_UP) {
         v += bs;
 #pragma unroll
@@ -305,16 +308,12 @@ struct WkHelper {
     const int lim = lk_const(p.src_len, slot);
     if (first_item) wait(op - 1);
     else lk_barrier();                         // the results of the item before are out of LDS
-      wk_norm(x + (size_t)slot * p.R * D, p.R, g, b, p.eps, xs, hw, lane);
+    wk_norm(x + (size_t)slot * p.R * D, p.R, g, b, p.eps, xs, hw, lane);
     lk_barrier();
     lk_barrier();
     {
-      f32x4 v = partial_sums(4, hw, lane);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) v[r] *= p.scale;
-      const u32x2 hi = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
-      const u32x2 lo = u32x2{cvt_pk_bf16(v[0] - __uint_as_float(hi[0] << 16), v[1] - __uint_as_float(hi[0] & 0xFFFF0000u)),
-                             cvt_pk_bf16(v[2] - __uint_as_float(hi[1] << 16), v[3] - __uint_as_float(hi[1] & 0xFFFF0000u))};
+      u32x2 hi, lo;
+      lk_halves(partial_sums(4, hw, lane) * p.scale, hi, lo);
       // operand lane 16 q + lr of half s holds columns 32 s + 8 q .. + 7
       const int to = ((hw >> 1) * 64 + ((hw & 1) * 2 + (lq >> 1)) * 16 + lr) * 2 + (lq & 1);
       q_s[to] = hi; q_s[256 + to] = lo;
