@@ -64,18 +64,20 @@ def trace_table(rows, top):
     return "\n".join(out)
 
 
-def case_table(cur, name, top=16):
+def case_table(cur, name):
+    """Every kernel of the last pass, by name; one name may have run on grids of several sizes."""
     k = cur.execute("select name, start, end, grid_x, grid_y, grid_z from kernels order by start").fetchall()
     first = [i for i, x in enumerate(k) if x[0].startswith("encode_init_kernel")][-1]       # (a pass starts with an encode)
     acc = {}
     for x in k[first:]:
-        t = acc.setdefault((x[0],) + x[3:], [0, 0])
-        t[0] += 1
-        t[1] += x[2] - x[1]
-    busy = sum(t[1] for t in acc.values())
+        acc.setdefault(x[0], []).append((x[2] - x[1],) + x[3:])
+    busy = sum(t[0] for v in acc.values() for t in v)
     out = [f"{name}: {len(k) - first} kernels, {busy / 1e3:.1f} us"]
-    for key, t in sorted(acc.items(), key=lambda q: -q[1][1])[:top]:
-        out.append(f"  {short(key[0], 86):86s} {t[0]:6d} x {t[1] / t[0] / 1e3:8.2f} = {t[1] / 1e3:10.1f} {100 * t[1] / busy:5.1f} %  {key[1]}x{key[2]}x{key[3]}")
+    for key, v in sorted(acc.items(), key=lambda q: -sum(t[0] for t in q[1])):
+        ns, grids = [t[0] for t in v], sorted({t[1:] for t in v}, key=lambda g: g[0] * g[1] * g[2])
+        spread = f"{min(ns) / 1e3:.1f} .. {max(ns) / 1e3:.1f}"
+        where = "x".join(map(str, grids[0])) + (f" .. {'x'.join(map(str, grids[-1]))} ({len(grids)} grids)" if len(grids) > 1 else "")
+        out.append(f"  {short(key, 86):86s} {len(ns):6d} x {sum(ns) / len(ns) / 1e3:8.2f} = {sum(ns) / 1e3:10.1f} {100 * sum(ns) / busy:5.1f} %  {spread:17s} {where}")
     return out
 
 
@@ -125,10 +127,10 @@ def main():
             traffic = json.load(f)
 
     if args.case:
-        out = ["# rocprofv3 kernel traces of the cases of perf/cases.py: the kernels of the last of a dozen passes (images: of two)",
+        out = ["# rocprofv3 kernel traces of the cases of perf/cases.py: every kernel of the last of a dozen passes (images: of two), by name",
                f"# command: rocprofv3 --kernel-trace --stats -d prof_out/case_NAME -o t -- {BENCH_CASE}",
                "# summarised by: python -m paper_1811_03115_amd.profsum " + " ".join(f"--case {c.split('=')[0]}=prof_out/case_{c.split('=')[0]}" for c in args.case),
-               "# durations in microseconds (profiled: a few per cent above unprofiled ones); grid = threads in x, y, z.  The passes' own times",
+               "# durations in microseconds (profiled: a few per cent above unprofiled ones); shortest .. longest, grid = threads in x, y, z.  The passes' own times",
                "# are not in here: under the profiler launches take longer than the kernels."]
         for c in args.case:
             name, d = c.split("=", 1)
