@@ -18,8 +18,8 @@ ALLOWED = [
     r"skinny_gemm_kernel<1, 1, false, false, 8, 16, 1, (false|true)>",
     r"decoder_stack_kernel<\d+>",
 ]
-# kernels that must be there and scratch-free: first those that the steps, encodes and decodes of the workloads run
-# (profiles/case_kernel_traces.txt), then those that other widths and depths run in their place
+# kernels that must be there and scratch-free, besides those that the traces of the timed cases name (traced()): a choice of the latter, and those that other
+# widths, depths and row counts run in their place
 REQUIRED = [
     "row_gemm_kernel<8, 4, 1, 1, true, 0>", "row_gemm_kernel<8, 4, 1, 1, true, 2>", "row_gemm_kernel<8, 4, 1, 1, false, 1>",
     "row_gemm_kernel<8, 4, 1, 1, false, 2>", "row_gemm_kernel<8, 4, 1, 1, false, 3>", "row_gemm_kernel<8, 4, 2, 4, false, 0>",
@@ -37,7 +37,16 @@ REQUIRED = [
     "skinny_gemm_kernel<1, 1, false, false, 8, 16, 0, false>", "skinny_gemm_kernel<1, 1, false, false, 4, 8, 0, false>",
     "gemm_ldsx_kernel<1, 1, 256, false, false, true, false>", "gemm_ldsx_kernel<1, 1, 256, false, true, false, false>", "gemm_ldsx_kernel<1, 1, 256, false, false, false, true>",
     "layernorm_kernel<unsigned short, 4>",
+    "layers_kernel<2048, false>", "layers_kernel<2048, true>", "wide_layers_kernel", "tall_layers_kernel<2>", "tall_layers_kernel<3>", "tall_layers_kernel<4>", "topn_rank_kernel",
 ]
+
+
+def traced():
+    """The library's kernels in profiles/case_kernel_traces.txt, with their template arguments."""
+    with open(os.path.join(os.path.dirname(__file__), "..", "profiles", "case_kernel_traces.txt")) as f:
+        names = re.findall(r"^  (?:void )?(\w+(?:<[^>]*>)?)\(", f.read(), re.M)
+    assert len(names) > 100
+    return sorted(set(names))
 
 
 def test_no_step_kernel_uses_scratch(tmp_path):
@@ -65,7 +74,7 @@ def test_no_step_kernel_uses_scratch(tmp_path):
     by_name = dict(zip(dem, (scratch[n] for n in names)))
     offenders = [f"{n}: {s} bytes" for n, s in by_name.items() if s > 0 and not any(re.search(a, n) for a in ALLOWED)]
     assert not offenders, "kernels with scratch memory:\n" + "\n".join(offenders)
-    for req in REQUIRED:
-        hits = [n for n in by_name if req in n]
+    for req in REQUIRED + traced():
+        hits = [n for n in by_name if re.search(r"(^|\W)" + re.escape(req) + r"(\W|$)", n)]
         assert hits, f"kernel {req} not found"
         assert all(by_name[n] == 0 for n in hits), f"{req} uses scratch"
