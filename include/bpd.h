@@ -27,6 +27,12 @@
  * Calls on one context must not overlap (one thread at a time, or external locking), and all
  * contexts of a process must live on one device: kernel attributes are set once per process.
  *
+ * Contexts on streams of their own may decode at the same time.  A kernel of all decoder layers
+ * (blocks of few rows, d_model 512 with d_ff 2048 or 1024 with 4096) takes all CUs, so that such
+ * contexts then take turns.  At d_model 1024 kernel by kernel is the faster way for two or more
+ * that are busy at once (one sentence each: two 8.6 instead of 10.2 ms, four 12.3 instead of 18):
+ * a context that is created with BPD_LAYERS_GROUP=0 in the environment goes that way throughout.
+ *
  * Pointer arguments marked [host|device] may be either; arguments marked [device] are
  * dereferenced by kernels.
  *
@@ -202,9 +208,9 @@ int bpd_set_acceptance(bpd_ctx* ctx, int distance_eps, int min_block);
  * imposed_accept == NULL: a proposal is also accepted if it is among the n highest-scoring
  * tokens of p_1 at its block row (ties go to the lower token id, as in the arg-max).  n = 1
  * switches the criterion off (exact match, or whatever bpd_set_acceptance selected; the two
- * criteria are OR-ed).  With n > 1 every step scores p_1 of the k block rows a second time with
- * the logits kept in the workspace ([B*k, vocab] fp32), so a step costs one more pass over the
- * embedding matrix.  Errors: BPD_E_ARG (n outside 1..vocab). */
+ * criteria are OR-ed).  With n > 1 every step keeps p_1's scores of the k block rows in the
+ * workspace ([B*k, vocab] fp32) as it scores the vocabulary, and ranks the proposals among them
+ * (one more kernel).  Errors: BPD_E_ARG (n outside 1..vocab). */
 int bpd_set_top_n(bpd_ctx* ctx, int n);
 
 /* Two-phase scoring (a variant of the combined model of Section 4 that yields the same tokens):
@@ -266,10 +272,11 @@ int bpd_debug_step_logits(bpd_ctx* ctx, int k, float* logits);
  * (BPD_PHASE_*) with HIP events on the context's stream; bpd_profile_read synchronises and
  * returns the accumulated milliseconds and the number of launches since it was enabled. */
 #define BPD_PHASE_NONE         0
-#define BPD_PHASE_LAYERS       1   /* decoder layers (embedding .. final LayerNorm), many kernels */
-#define BPD_PHASE_HEAD_HIDDEN  2   /* heads, hidden layers: one GEMM kernel                       */
+#define BPD_PHASE_LAYERS       1   /* decoder layers, and the embedding where the step before has not
+                                      made it: one kernel, or many                                */
+#define BPD_PHASE_HEAD_HIDDEN  2   /* final LayerNorm, heads' hidden layers: one kernel, or two    */
 #define BPD_PHASE_HEAD_OUT     3   /* heads, k output layers + residual: one grouped GEMM kernel  */
-#define BPD_PHASE_VOCAB        4   /* vocabulary projection + argmax: one kernel                  */
+#define BPD_PHASE_VOCAB        4   /* vocabulary projection + argmax: one kernel (top-n: and ranks) */
 #define BPD_PHASE_ACCEPT       5   /* verify / accept / commit                                    */
 #define BPD_PHASE_STEP         6   /* the whole step                                              */
 #define BPD_PHASE_EMPTY        7   /* nothing: two events back to back, what the bracketing itself costs */

@@ -1,14 +1,16 @@
 // The decoder layers of one step as ONE kernel running on ONE XCD (blocks of at most 16 rows, bf16, 64-wide heads).
 //
-// Why: with a block of <= 16 rows the decoder stack is a chain of ~42 dependent small operators (per layer: QKV
+// The first form of this idea, opt-in (BPD_DECODER_STACK=1 when a context is created): slower than the chain of kernels (Transformer-big, 10 rows:
+// layers 0.49 ms, 0.27 as that chain was when it was measured).  Where it is not asked for, steps of d = 512, d_ff 2048 and of d = 1024, d_ff 4096 have
+// bpd_layers.h and bpd_wide_layers.h, whose weights stay with the workgroups that multiply them and whose flags are plain stores; this one takes
+// other widths and depths (d = 128 .. 1024, d_ff a multiple of 128).
+//
+// Why it was built: with a block of <= 16 rows the decoder stack is a chain of ~42 dependent small operators (per layer: QKV
 // projection, self-attention, output projection, cross-attention query projection, cross-attention, output projection,
-// two FFN layers; Section 6 of the paper adds nothing to the layers themselves).  As separate kernels each link costs
-// 5-7 us (launch, cache write-back / invalidate at the kernel boundary, first memory round trip), and handing the
-// 40 KB block between workgroups of DIFFERENT XCDs inside one kernel costs as much (their L2s are not coherent: the
-// data has to go through memory).  The workgroups of ONE XCD share an L2, and there a hand-over (stores, wait for their
-// acknowledgement, an atomic flag per producer; consumers poll the flags with atomics, then load) measures ~1.3 us.
-// One XCD streams ~1.2 TB/s, which is what this kernel is bound by; the weights of the operators ahead are requested
-// while the current operator waits for its input, so the stream does not stop at the hand-overs.
+// two FFN layers; Section 6 of the paper adds nothing to the layers themselves).  The workgroups of ONE XCD share an L2, and there a
+// hand-over (stores, wait for their acknowledgement, an atomic flag per producer; consumers poll the flags with atomics, then load)
+// measured ~1.3 us.  One XCD streams ~1.2 TB/s, and the weights of the operators ahead are requested while the current operator waits for its
+// input; what it is bound by is the serial part of each operator (poll, staging, multiply, finish, signal: 5 .. 7 us).
 //
 // Structure: grid = one workgroup per CU of the chip; the workgroups that are not on the working XCD exit at once.
 // A worker = 4 compute waves + 4 helper waves.
