@@ -1890,7 +1890,7 @@ int bpd_get_stats(bpd_ctx* ctx, bpd_stats* st) {
   if (rc == BPD_OK) rc = layers_check(ctx, raw);
   if (rc) return rc;
   stats_of(ctx, raw, st);
-  return BPD_OK;
+  return stack_check(ctx);
 }
 
 static int output_and_stats(bpd_ctx* ctx, int32_t* out_ids, int32_t* out_len, bpd_stats* st, bool count_steps = false) {

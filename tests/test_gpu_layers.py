@@ -173,6 +173,29 @@ def test_a_wait_that_ran_out(k, B, d, encodes, monkeypatch):
     ctx.bpd_get_state()
 
 
+# The opt-in kernel's word is one of its own, behind the map of workgroups to XCDs (1024 words, the first 256 of them round and round): told once, then it is off
+def test_a_wait_of_the_stack_kernel_that_ran_out(monkeypatch):
+    from paper_1811_03115_amd import binding
+    monkeypatch.setenv("BPD_DECODER_STACK", "1")
+    cfg = config(4, 1, 9, 20, d=128)
+    ctx = gpu_context(cfg, wl.make_weights(cfg))
+    src, n = wl.make_sources(cfg)
+    ctx.bpd_encode(src, n)
+    ctx.bpd_step(4)
+    ctx.bpd_get_stats()
+    start = -ctx.workspace.data_ptr() % 256
+    words = ctx.workspace[start:start + (ctx.workspace.numel() - start) // 256 * 256].view(torch.int32).view(-1, 64)
+    round_robin = ((words[:, :8].sort(1).values == torch.arange(8, device="cuda")).all(1) & (words[:, 8:] == words[:, :-8]).all(1)).nonzero().flatten().tolist()
+    first = [r for r in round_robin if r + 3 in round_robin and r - 1 not in round_robin]
+    assert len(first) == 1
+    words[first[0] + 16, 0] = 7
+    torch.cuda.synchronize()
+    with pytest.raises(binding.BpdError, match=r"wait ran out \(code 7\)"):
+        ctx.bpd_get_stats()
+    ctx.bpd_get_stats()
+    ctx.bpd_get_output()
+
+
 # one kernel per captured step, replayed with other work of the program's between the replays: every replay finds the words that the workgroups count in cleared
 @pytest.mark.parametrize("k,B,d", [(6, 5, 512), (5, 20, 512), (9, 1, 1024), (7, 4, 1024), (8, 7, 1024)])
 def test_captured_steps(k, B, d):
