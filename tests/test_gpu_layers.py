@@ -131,6 +131,19 @@ def test_room_for_longer_sources(k, B):
     assert torch.equal(*scores)
 
 
+def words_of(ctx, dtype):
+    """The workspace in rows of 256 bytes, at which its arrays start."""
+    start = -ctx.workspace.data_ptr() % 256
+    return ctx.workspace[start:start + (ctx.workspace.numel() - start) // 256 * 256].view(dtype).view(-1, 256 // dtype.itemsize)
+
+
+def cleared_context(cfg, weights, monkeypatch):
+    """A context in a workspace that held nothing of an earlier one's."""
+    with monkeypatch.context() as m:
+        m.setattr(torch, "empty", torch.zeros)
+        return gpu_context(cfg, weights)
+
+
 # A wait inside a kernel that ran out leaves a word behind the counters; here the test puts it there.  Everything that hands out results says so until the next
 # encode, which (recorded before, or not) and whose steps then go kernel by kernel: the scores are those of a context that always did.
 @pytest.mark.parametrize("k,B,d,encodes", [(8, 3, 512, 1), (10, 1, 1024, 9), (8, 4, 1024, 1)])
@@ -138,7 +151,7 @@ def test_a_wait_that_ran_out(k, B, d, encodes, monkeypatch):
     from paper_1811_03115_amd import binding
     cfg = config(k, B, 9, 60, d=d)
     weights = wl.make_weights(cfg)
-    ctx = gpu_context(cfg, weights)
+    ctx = cleared_context(cfg, weights, monkeypatch)
     monkeypatch.setenv("BPD_LAYERS_GROUP", "0")
     ref = gpu_context(cfg, weights)
     src, n = wl.make_sources(cfg)
@@ -158,8 +171,7 @@ def test_a_wait_that_ran_out(k, B, d, encodes, monkeypatch):
         assert not torch.equal(scores(ctx), want)
     st = ctx.bpd_get_stats()
     counters = torch.tensor([st.seq_steps, st.accepted_total, st.finished, *st.hist, st.steps], device="cuda")
-    start = -ctx.workspace.data_ptr() % 256
-    rows = ctx.workspace[start:start + (ctx.workspace.numel() - start) // 256 * 256].view(torch.int64).view(-1, 32)
+    rows = words_of(ctx, torch.int64)
     at = (rows[:, :21] == counters).all(1).nonzero().flatten()
     assert len(at) == 1
     rows[at[0], 31] = 1
@@ -178,13 +190,12 @@ def test_a_wait_of_the_stack_kernel_that_ran_out(monkeypatch):
     from paper_1811_03115_amd import binding
     monkeypatch.setenv("BPD_DECODER_STACK", "1")
     cfg = config(4, 1, 9, 20, d=128)
-    ctx = gpu_context(cfg, wl.make_weights(cfg))
+    ctx = cleared_context(cfg, wl.make_weights(cfg), monkeypatch)
     src, n = wl.make_sources(cfg)
     ctx.bpd_encode(src, n)
     ctx.bpd_step(4)
     ctx.bpd_get_stats()
-    start = -ctx.workspace.data_ptr() % 256
-    words = ctx.workspace[start:start + (ctx.workspace.numel() - start) // 256 * 256].view(torch.int32).view(-1, 64)
+    words = words_of(ctx, torch.int32)
     round_robin = ((words[:, :8].sort(1).values == torch.arange(8, device="cuda")).all(1) & (words[:, 8:] == words[:, :-8]).all(1)).nonzero().flatten().tolist()
     first = [r for r in round_robin if r + 3 in round_robin and r - 1 not in round_robin]
     assert len(first) == 1
