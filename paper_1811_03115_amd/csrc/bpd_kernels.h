@@ -1226,10 +1226,7 @@ __global__ __launch_bounds__(64) void accept_kernel(StateP s, const unsigned lon
                                                     int commit, int step, int* accepted_out, float* scores, int V) {
   const int b = blockIdx.x, lane = threadIdx.x;
   if (b >= B) return;
-  if (scores && s.stats[31]) {
-    const size_t n = (size_t)k * k * V;
-    for (size_t i = lane; i < n; i += 64) scores[b * n + i] = __int_as_float(0x7FC00000);
-  }
+  const long long lost = s.stats[31];
   const int tick = s.dyn && commit ? s.tick[b] : 0, live_step = s.steps_done[b];
   int imp = 0;
   if (s.dyn && commit) { step_from_dyn(s, tick); imp = s.imp_next[b]; if (lane == 0) step_tick(s, b, tick); }
@@ -1241,6 +1238,10 @@ __global__ __launch_bounds__(64) void accept_kernel(StateP s, const unsigned lon
   for (int e = lane; e < k * k; e += 64) {
     const int ip = e / k, i = e % k;
     s.A[(b * s.kmax + ip) * s.kmax + i] = key_index(keys[(long)b * k * k + e]);
+  }
+  if (scores && lost) {
+    const size_t n = (size_t)k * k * V;
+    for (size_t i = lane; i < n; i += 64) scores[b * n + i] = __int_as_float(0x7FC00000);
   }
   if (!commit) return;
   const int myP = lane < k ? s.P[b * s.kmax + lane] : -1;
