@@ -67,7 +67,7 @@ struct bpd_ctx {
   int live1 = -1, live2 = -1;            // sequences that had not ended after the last step and after the one before (-1: not known)
   int budget_min = 0;                    // smallest length budget of the batch as far as the host knows
   // workgroups per XCD that layers_kernel and wide_layers_kernel wait for (for tests, BPD_LAYERS_GROUP at creation: fewer; 33: they wait in vain; 64 n
-  // added: the second one is left to n XCDs; 0: neither is used)
+  // added: the second one is left to n XCDs).  0: none of the kernels of all layers is used
   int layers_group = LK_PLACES;
   bool layers_ran = false;             // layers_kernel has been launched and the LayerNorm behind it has not (that LayerNorm clears layers_sync)
   bool weights_exceed_llc = false;     // decoder-side weights read per step > 192 MB (the Infinity Cache holds 256 MB)

@@ -266,6 +266,8 @@ constexpr int LDSX_LN_MT_MAX = 3;      // LayerNorm-fused consumers and statisti
 constexpr long LDSX_MIN_WGS = 440;
 constexpr long LDSX_MIN_WGS_LONGK = 400;   // K >= 2048, fewer than 1024 rows: a workgroup lives long enough that about 1.5 per CU suffice
                                            // (the encoder's 4096-row FFN output: 64-row tiles, 512 workgroups, beat 80-row tiles, 416: encode -2%)
+// (chosen at 80 .. 320 rows.  Of 64 GEMMs of 700 .. 4096 rows its tile is within 5 % of the best at 37 and within 10 % at 48; worst: 780 x 3072 x 1024 25.8 us, 80 x 128 tiles
+// 15.5; 2240 x 1024 x 4096 50.8, 39.6; 4096 x 1024 x 4096 53.6, 64 x 256 tiles 45.1)
 void pick_tile(int M, int N, int K, long zdim, int& mt, int& nt, int mt_max = 8) {
   const int mts[7] = {8, 7, 5, 4, 3, 2, 1};
   long best_area = 0, best_pad = 0;
