@@ -810,6 +810,7 @@ void launch_layers(bpd_ctx* ctx, int R, int way) {
     ctx->pend_slices = 4; ctx->pend_bias = L.dec[c.n_dec_layers - 1].b2; ctx->pend_x = L.x;
     return;
   }
+  p.x1 = L.layers_x1; p.x3 = L.layers_x3; p.attn2 = (bf16_t*)L.layers_attn2;
   const bool nt = (size_t)2 * c.n_dec_layers * ctx->Bs * slots * d * 2 > ((size_t)128 << 20);       // (as in attention())
   if (nt) launch_layers_kernel<true>(ctx, p); else launch_layers_kernel<false>(ctx, p);
 }

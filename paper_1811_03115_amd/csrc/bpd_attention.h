@@ -27,6 +27,13 @@ __device__ __forceinline__ void kv_frag_store(bf16_t* cache, bool is_v, int sb, 
   }
 }
 
+// What a word holds whose value is still to come, in buffers whose readers wait for the values themselves (bpd_layers.h): no value that is stored there is this
+// one (a NaN of these bits goes as the NaN beside it).
+constexpr unsigned EMPTY_WORD = 0xFFFFFFFFu;
+__device__ __forceinline__ unsigned full_word(unsigned v) { return v < EMPTY_WORD - 1 ? v : EMPTY_WORD - 1; }
+__device__ __forceinline__ u32x2 full_words(u32x2 v) { return u32x2{full_word(v[0]), full_word(v[1])}; }
+__device__ __forceinline__ u32x4 full_words(f32x4 f) { const u32x4 v = __builtin_bit_cast(u32x4, f); return u32x4{full_word(v[0]), full_word(v[1]), full_word(v[2]), full_word(v[3])}; }
+
 // fp32 operands (queries, probabilities) go to the matrix cores as a bf16 pair hi + lo, which keeps them to ~2^-17.
 __device__ __forceinline__ void split_bf16x8(const float (&v)[8], bf16x8& hi, bf16x8& lo) {
   unsigned h[4], l[4];
@@ -110,9 +117,10 @@ __device__ __forceinline__ void attn_load_kv(rsrc_t kr, rsrc_t vr, int c, int nw
   }
 }
 // The item's work from the point where its queries (qhi + qlo) and the first groups of K and V are at hand or under way (parameters as in
-// attention_mfma_body; first, hop: this split's first group and the distance to its next round; lim: limit[b]).  THROUGH: results are written through
-// the L2.
-template <bool KVNT, bool LIMF, int QU, int G, bool THROUGH = false>
+// attention_mfma_body; first, hop: this split's first group and the distance to its next round; lim: limit[b]).  STORE: results are written through the L2
+// (ATTN_THROUGH), or no word of them is EMPTY_WORD (ATTN_WORDS).
+enum { ATTN_PLAIN, ATTN_THROUGH, ATTN_WORDS };
+template <bool KVNT, bool LIMF, int QU, int G, int STORE = ATTN_PLAIN>
 __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLds& sm, int h, int b, int tile, int split, int r0, int nrows,
                                                     int nheads, int nz, int tid, int nw, int first, int hop, rsrc_t kr, rsrc_t vr,
                                                     u32x4 (&kf)[G][4], u32x4 (&vf)[G][4], const bf16x8 (&qhi)[2], const bf16x8 (&qlo)[2], int lim, bf16_t* out) {
@@ -211,16 +219,22 @@ __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLd
     if (lr < nrows) {
       float inv = __builtin_amdgcn_rcpf(L);
       inv = inv * fmaf(-L, inv, 2.f);            // (one Newton step: the quotient to fp32)
-      const u32x2 w = u32x2{cvt_pk_bf16(o[0] * inv, o[1] * inv), cvt_pk_bf16(o[2] * inv, o[3] * inv)};
+      u32x2 w = u32x2{cvt_pk_bf16(o[0] * inv, o[1] * inv), cvt_pk_bf16(o[2] * inv, o[3] * inv)};
+      if constexpr (STORE == ATTN_WORDS) w = full_words(w);
       bf16_t* to = out + ((size_t)b * p.R + r0 + lr) * p.d + h * DH + dim;
-      if constexpr (THROUGH) asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(to), "v"(w) : "memory");      // (to memory, for other XCDs)
+      if constexpr (STORE == ATTN_THROUGH) asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(to), "v"(w) : "memory");      // (to memory, for other XCDs)
       else *(u32x2*)to = w;
     }
   } else {
     const int tiles = nz / p.nsplit;
     float* part = p.part + ((((long)b * nheads + h) * tiles + tile) * p.nsplit + split) * (RT * (DH + 2));
-    *(f32x4*)(part + lr * DH + dim) = o;
-    if (tid < RT) { part[RT * DH + tid] = M; part[RT * DH + RT + tid] = L; }
+    if constexpr (STORE == ATTN_WORDS) {
+      *(u32x4*)(part + lr * DH + dim) = full_words(o);
+      if (tid < RT) { part[RT * DH + tid] = __uint_as_float(full_word(__float_as_uint(M))); part[RT * DH + RT + tid] = __uint_as_float(full_word(__float_as_uint(L))); }
+    } else {
+      *(f32x4*)(part + lr * DH + dim) = o;
+      if (tid < RT) { part[RT * DH + tid] = M; part[RT * DH + RT + tid] = L; }
+    }
   }
 }
 // One (head h, sequence b (in the K/V buffer: sb), z = row tile * nsplit + split) item of the attention, run by nw whole

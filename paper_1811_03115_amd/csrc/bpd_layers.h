@@ -4,9 +4,9 @@
 // A layer is seven dependent operators.  As kernels of their own each costs 2.5 .. 6 us, of which a launch that does nothing is 1.7;
 // the workgroups of one XCD share an L2, and there a hand-over (store, acknowledgement, a flag; a poll that sees it) takes 0.3 us
 // one way (690 cycles; between XCDs 950, with the data written through to memory).  Six layers of 8 rows, 40 keys, 32 source tokens: 156 us
-// as 42 kernels, 90 us here; eight such blocks on eight XCDs 97 us (chain of kernels over 64 rows: 200 us).  What bounds it now is the chain within
-// an operator: a flag, a load of lines that another CU has just written (550 .. 900 cycles), LayerNorm or softmax at one wave
-// per SIMD (4 cycles an instruction), LDS twice, the store's acknowledgement: 1.4 .. 3 us each.
+// as 42 kernels, 82 us here; eight such blocks on eight XCDs 90 us (chain of kernels over 64 rows: 200 us).  What bounds it now is the chain within
+// an operator: a load of lines that another CU has just written (550 .. 900 cycles), LayerNorm or softmax at one wave
+// per SIMD (4 cycles an instruction), LDS twice: 1.1 .. 2.9 us each.
 //
 // Work.  Sequences do not depend on each other: a job is the rows of up to four sequences, at most 16 rows, one MFMA row tile.  A group, the
 // 32 workgroups that run on one XCD, takes a job through all layers, and every XCD streams all the weights (7.3 MB a layer, 0.5 TB/s) for
@@ -20,15 +20,18 @@
 // What launches on several streams do is take turns, since a workgroup fills its CU: decodes of one sentence, ms, chains of kernels and this: one context 3.8,
 // 2.7, two 4.3, 3.1, four 5.9, 5.3; bpd_wide_layers.h, d = 1024: 6.3, 5.5; 8.6, 10.6; 12.3, 18.2 (BPD_LAYERS_GROUP=0 at creation: a context of chains).
 //
-// Inside a workgroup.  Four compute waves hold weights, K split over them; four helper waves poll the flags, stage the operator's input in
-// LDS (through LayerNorm where it has one), add the compute waves' partial sums, store the results, raise their flags and do the
+// Inside a workgroup.  Four compute waves hold weights, K split over them; four helper waves poll for the operator's input, stage it in
+// LDS (through LayerNorm where it has one), add the compute waves' partial sums, store the results and do the
 // attention.  Loads return in order, per wave and, in the L1, per CU: a wave with weights under way can neither poll nor fetch
 // activations without waiting for them too, and the helpers' loads queue behind the compute waves'.  Hence weights are not fetched when their
 // registers fall free (110 us) but, a layer's at a time, while the member idles: in the self-attention or the cross-attention, which eight
 // places each take part in (one sequence per job), others than each other where there is room (90 us; with no weights fetched at all: 88).
 //
-// Memory.  Results are plain stores, in the XCD's L2 when acknowledged; flags are stored behind the acknowledgement; what this kernel has
-// written is read past the L1 (sc1: the L1 may hold the lines as they were an operator or a layer ago).  Keys and values are read
+// Memory.  Results are plain stores into the XCD's L2; what this kernel has written is read past the L1 (sc1: the L1 may hold the lines as they were an
+// operator or a layer ago).  A result tells by itself that it has come: its words hold EMPTY_WORD before, and who needs them loads them until none does.
+// (With a flag stored behind the acknowledgement of the results, and the results loaded behind the flag, a hand-over was two trips to the L2 longer: six layers
+// of 8 rows 89 us instead of 82, eight blocks of 10 rows over up to 3000 keys 150 on average instead of 144.)  The block's keys and values lie among older ones that
+// any word may have: flags, raised by the waves that store queries, keys and values, announce these.  Keys and values are read
 // once per launch, past nothing.
 #pragma once
 
@@ -36,7 +39,7 @@
 
 constexpr unsigned LK_CLOSED = 0x10000u, LK_NO_JOB = 0xFFFFu;
 constexpr long long LK_CLOSE_TICKS = 2000;                      // of the 100 MHz counter: 20 us
-constexpr int LK_HOLD = 12, LK_GAP = 1, LK_PACE = 4;            // pauses of the compute waves, units of 64 cycles: LkCompute::job
+constexpr int LK_HOLD = 12, LK_GAP = 1, LK_PACE = 2;            // pauses of the compute waves, units of 64 cycles: LkCompute::job
 constexpr int LK_SPINS = 1 << 22;                               // (a second: only a defect gets there)
 
 struct LayersP {
@@ -47,6 +50,8 @@ struct LayersP {
   int split, few;                                // workgroups per (head, slot) of the self-attention; few: up to 128 keys
   float *x, *part;
   bf16_t *q, *attn, *ffh, *selfK, *selfV;         // q: a row is 2 d wide (bf16 hi and lo parts)
+  float *x1, *x3;                                // layers_kernel: the residual stream behind the two attentions (x1, then x2) and between layers
+  bf16_t *attn2;                                  // ... and the cross-attention's results
   const bf16_t *crossK, *crossV;
   long self_layer, src_layer;                    // elements of a layer's caches
   int self_groups, src_groups;                   // groups of 32 keys per sequence
@@ -159,16 +164,46 @@ __device__ __forceinline__ void lk_halves(const f32x4& v, u32x2& hi, u32x2& lo) 
   lo = u32x2{cvt_pk_bf16(v[0] - __uint_as_float(hi[0] << 16), v[1] - __uint_as_float(hi[0] & 0xFFFF0000u)),
              cvt_pk_bf16(v[2] - __uint_as_float(hi[1] << 16), v[3] - __uint_as_float(hi[1] & 0xFFFF0000u))};
 }
+// Results that carry their own news (EMPTY_WORD: bpd_attention.h): a buffer is empty in every word until its producers store into it, so that whoever loads it
+// again and again until no word is empty needs no flag, and the producers wait for no acknowledgement.
+constexpr int LK_POLLS = 1 << 20;                               // (as LK_SPINS; a round takes longer)
+__device__ __forceinline__ unsigned lk_top(unsigned top, const u32x4& v) {
+  const unsigned a = v[0] > v[1] ? v[0] : v[1], b = v[2] > v[3] ? v[2] : v[3];
+  top = top > a ? top : a;
+  return top > b ? top : b;
+}
+struct LkPoll {
+  bool* broken;
+  long long* error;
+  bool on;                                       // (off: the data is known to be there)
+  // load: fetches and returns the largest word
+  template <class Load> __device__ __forceinline__ void operator()(Load&& load) const {
+#pragma unroll 1
+    for (int s = 0; s < LK_POLLS; ++s) {
+      const unsigned top = load();
+      if (!on || *broken || !__any(top == EMPTY_WORD)) return;
+      asm volatile("" ::: "memory");
+    }
+    *broken = true;
+    if (lk_lane() == 0) *error = 1;
+  }
+};
 // LayerNorm of up to 16 rows of 512 into LDS as bf16, rows 520 apart; wave hw takes rows hw, hw + 4, ..
 template <int N>
-__device__ __forceinline__ void lk_norm_rows(const rsrc_t& xr, int rows, const f32x4 (&g)[2], const f32x4 (&b)[2], float eps, bf16_t* xs, int hw, int lane) {
+__device__ __forceinline__ void lk_norm_rows(const rsrc_t& xr, int rows, const f32x4 (&g)[2], const f32x4 (&b)[2], float eps, bf16_t* xs, int hw, int lane, LkPoll poll) {
   constexpr int D = 512;
   f32x4 v[N][2];
+  poll([&] {
 #pragma unroll
-  for (int i = 0; i < N; ++i)
+    for (int i = 0; i < N; ++i)
 #pragma unroll
-    for (int h = 0; h < 2; ++h) v[i][h] = __builtin_bit_cast(f32x4, lk_load16(xr, ((hw + 4 * i) * D + lane * 8 + h * 4) * 4));
-  __builtin_amdgcn_sched_barrier(0);
+      for (int h = 0; h < 2; ++h) v[i][h] = __builtin_bit_cast(f32x4, lk_load16(xr, ((hw + 4 * i) * D + lane * 8 + h * 4) * 4));
+    __builtin_amdgcn_sched_barrier(0);
+    unsigned top = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) { top = lk_top(top, __builtin_bit_cast(u32x4, v[i][0])); top = lk_top(top, __builtin_bit_cast(u32x4, v[i][1])); }
+    return top;
+  });
   float mu[N], q[N];
 #pragma unroll
   for (int i = 0; i < N; ++i) { const f32x4 s = v[i][0] + v[i][1]; mu[i] = (s[0] + s[1]) + (s[2] + s[3]); }
@@ -196,22 +231,30 @@ __device__ __forceinline__ void lk_norm_rows(const rsrc_t& xr, int rows, const f
       *(u32x4*)(xs + (hw + 4 * i) * (D + 8) + lane * 8) = u32x4{cvt_pk_bf16(y[0][0], y[0][1]), cvt_pk_bf16(y[0][2], y[0][3]), cvt_pk_bf16(y[1][0], y[1][1]), cvt_pk_bf16(y[1][2], y[1][3])};
   }
 }
-__device__ __forceinline__ void lk_norm(const float* x, int rows, const f32x4 (&g)[2], const f32x4 (&b)[2], float eps, bf16_t* xs, int hw, int lane) {
+__device__ __forceinline__ void lk_norm(const float* x, int rows, const f32x4 (&g)[2], const f32x4 (&b)[2], float eps, bf16_t* xs, int hw, int lane, LkPoll poll) {
   const rsrc_t xr = rsrc_of(x, (unsigned)rows * 512 * 4);
-  if (rows <= 8) lk_norm_rows<2>(xr, rows, g, b, eps, xs, hw, lane);
-  else if (rows <= 12) lk_norm_rows<3>(xr, rows, g, b, eps, xs, hw, lane);
-  else lk_norm_rows<4>(xr, rows, g, b, eps, xs, hw, lane);
+  if (rows <= 8) lk_norm_rows<2>(xr, rows, g, b, eps, xs, hw, lane, poll);
+  else if (rows <= 12) lk_norm_rows<3>(xr, rows, g, b, eps, xs, hw, lane, poll);
+  else lk_norm_rows<4>(xr, rows, g, b, eps, xs, hw, lane, poll);
 }
 // bf16 rows of K into LDS, rows K + 8 apart
 template <int K, int M>
-__device__ __forceinline__ void lk_copy_rows(const rsrc_t& r, int rows, bf16_t* xs, int hw, int lane) {
+__device__ __forceinline__ void lk_copy_rows(const rsrc_t& r, int rows, bf16_t* xs, int hw, int lane, LkPoll poll) {
   constexpr int N = K / 512;
   u32x4 v[M][N];
+  poll([&] {
 #pragma unroll
-  for (int i = 0; i < M; ++i)
+    for (int i = 0; i < M; ++i)
 #pragma unroll
-    for (int j = 0; j < N; ++j) v[i][j] = lk_load16(r, ((hw + 4 * i) * K + j * 512 + lane * 8) * 2);
-  __builtin_amdgcn_sched_barrier(0);
+      for (int j = 0; j < N; ++j) v[i][j] = lk_load16(r, ((hw + 4 * i) * K + j * 512 + lane * 8) * 2);
+    __builtin_amdgcn_sched_barrier(0);
+    unsigned top = 0;
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+#pragma unroll
+      for (int j = 0; j < N; ++j) top = lk_top(top, v[i][j]);
+    return top;
+  });
 #pragma unroll
   for (int i = 0; i < M; ++i)
     if (hw + 4 * i < rows) {
@@ -220,15 +263,15 @@ __device__ __forceinline__ void lk_copy_rows(const rsrc_t& r, int rows, bf16_t* 
     }
 }
 template <int K>
-__device__ __forceinline__ void lk_copy(const bf16_t* src, int rows, bf16_t* xs, int hw, int lane) {
+__device__ __forceinline__ void lk_copy(const bf16_t* src, int rows, bf16_t* xs, int hw, int lane, LkPoll poll = {nullptr, nullptr, false}) {
   const rsrc_t r = rsrc_of(src, (unsigned)rows * K * 2);
-  if (rows <= 8) lk_copy_rows<K, 2>(r, rows, xs, hw, lane);
-  else if (rows <= 12) lk_copy_rows<K, 3>(r, rows, xs, hw, lane);
-  else if constexpr (K <= 2048) lk_copy_rows<K, 4>(r, rows, xs, hw, lane);
-  else { lk_copy_rows<K, 2>(r, rows, xs, hw, lane); lk_copy_rows<K, 2>(r, rows, xs, hw + 8, lane); }         // (registers)
+  if (rows <= 8) lk_copy_rows<K, 2>(r, rows, xs, hw, lane, poll);
+  else if (rows <= 12) lk_copy_rows<K, 3>(r, rows, xs, hw, lane, poll);
+  else if constexpr (K <= 2048) lk_copy_rows<K, 4>(r, rows, xs, hw, lane, poll);
+  else { lk_copy_rows<K, 2>(r, rows, xs, hw, lane, poll); lk_copy_rows<K, 2>(r, rows, xs, hw + 8, lane, poll); }         // (registers)
 }
 // Rows of the attention left by `split` workgroups per (head, slot) (attention_mfma_core) put together, into LDS like lk_copy<512>
-__device__ __forceinline__ void lk_merge(const float* part, int split, int slot0, int R, int rows, bf16_t* xs, int hw, int lane) {
+__device__ __forceinline__ void lk_merge(const float* part, int split, int slot0, int R, int rows, bf16_t* xs, int hw, int lane, LkPoll poll) {
   constexpr int H = 8, REC = 16 * 66;
   const int h = lane >> 3, dim = (lane & 7) * 8;
 #pragma unroll 1
@@ -237,15 +280,25 @@ __device__ __forceinline__ void lk_merge(const float* part, int split, int slot0
     const rsrc_t pr = rsrc_of(part + (size_t)(slot0 + s) * H * split * REC, (unsigned)(H * split * REC) * 4);
     f32x4 o[LK_SPLITS][2];
     float M[LK_SPLITS], L[LK_SPLITS];
+    poll([&] {
 #pragma unroll
-    for (int i = 0; i < LK_SPLITS; ++i) {
-      const unsigned at = i < split ? (unsigned)((h * split + i) * REC) * 4 : 0x40000000u;         // (past the end: zeros)
-      o[i][0] = __builtin_bit_cast(f32x4, lk_load16(pr, at + (r * 64 + dim) * 4));
-      o[i][1] = __builtin_bit_cast(f32x4, lk_load16(pr, at + (r * 64 + dim + 4) * 4));
-      M[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(pr, (int)(at + (1024 + r) * 4), 0, 16));
-      L[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(pr, (int)(at + (1040 + r) * 4), 0, 16));
-    }
-    __builtin_amdgcn_sched_barrier(0);
+      for (int i = 0; i < LK_SPLITS; ++i) {
+        const unsigned at = i < split ? (unsigned)((h * split + i) * REC) * 4 : 0x40000000u;         // (past the end: zeros)
+        o[i][0] = __builtin_bit_cast(f32x4, lk_load16(pr, at + (r * 64 + dim) * 4));
+        o[i][1] = __builtin_bit_cast(f32x4, lk_load16(pr, at + (r * 64 + dim + 4) * 4));
+        M[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(pr, (int)(at + (1024 + r) * 4), 0, 16));
+        L[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(pr, (int)(at + (1040 + r) * 4), 0, 16));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      unsigned top = 0;
+#pragma unroll
+      for (int i = 0; i < LK_SPLITS; ++i) {
+        top = lk_top(top, __builtin_bit_cast(u32x4, o[i][0])); top = lk_top(top, __builtin_bit_cast(u32x4, o[i][1]));
+        const unsigned m = __float_as_uint(M[i]) > __float_as_uint(L[i]) ? __float_as_uint(M[i]) : __float_as_uint(L[i]);
+        top = top > m ? top : m;
+      }
+      return top;
+    });
     float top = M[0], l = 0.f;
 #pragma unroll
     for (int i = 1; i < LK_SPLITS; ++i) top = i < split ? fmaxf(top, M[i]) : top;
@@ -262,7 +315,6 @@ __device__ __forceinline__ void lk_merge(const float* part, int split, int slot0
   }
 }
 
-enum { LK_QKV, LK_RELU, LK_RES };
 // What a member knows of its group and job
 struct LkJob {
   int rank, members, slot0, slots, rows, row0;
@@ -286,11 +338,10 @@ struct LkHelper {
   int hw;
   LkJob j;
   int key, sb;                                   // of row lr: its row in the cache, its sequence
-  unsigned op;
+  unsigned op;                                   // first products done
   bool broken;
 
   __device__ __forceinline__ void raise() { lk_raise(flags + hw * 32 + j.rank, op, lk_lane()); }
-  __device__ __forceinline__ int min_members(int n) const { return n < j.members ? n : j.members; }
 
   // of this wave's tile, of N (all reads under way before the first is waited for)
   template <int N> __device__ __forceinline__ f32x4 partial_sums(int lane) const {
@@ -301,44 +352,108 @@ struct LkHelper {
     return ((part[0] + part[1]) + part[2]) + part[3];
   }
 
-  // One operator with a product.  NF, producers: whose flags it waits for
-  template <int N, int K, int EPI, int NF, bool LN, bool BIAS>
-  __device__ __forceinline__ void product(int l, int producers, const float* LayersP::*lnp, const float* LayersP::*biasp, bool merged = false, int from = 0) {
-    constexpr int D = 512, LD = EPI == LK_RELU ? F : D;
+  __device__ __forceinline__ LkPoll poll(bool on = true) { return LkPoll{&broken, lk_args().error, on}; }
+  // The residual stream on its way through layer l (stage 0: into it, 1, 2: behind its attentions, 3: out of it)
+  __device__ __forceinline__ static float* stream(int l, int stage) {
+    const LayersP& p = lk_args();
+    if (stage == 0) return l == 0 ? p.x : p.x3;
+    if (stage == 3) return l + 1 == p.n_layers ? p.x : p.x3;
+    return stage == 1 ? p.x1 : p.x1 + LK_JOBS * 16 * 512;
+  }
+  // What this member writes is emptied when everybody is known to have read it: by the lanes that wrote it, at the latest an operator ahead of its own
+  // part in what its next reader has waited for.
+  __device__ __forceinline__ void empty_tile(float* x, int place, int lane) const {
+    const int lr = lane & 15;
+    if (hw == 0 && lr < j.rows) *(u32x4*)(x + (size_t)(j.row0 + lr) * 512 + place * 16 + (lane >> 4) * 4) = u32x4{EMPTY_WORD, EMPTY_WORD, EMPTY_WORD, EMPTY_WORD};
+  }
+  __device__ __forceinline__ void empty_hidden(int lane) const {
+    const int lr = lane & 15;
+    if (lr >= j.rows || (F < 2048 && hw >= F / 512)) return;
+#pragma unroll 1
+    for (int place = j.rank; place < LK_PLACES; place += j.members)
+      *(u32x2*)(lk_args().ffh + (size_t)(j.row0 + lr) * F + (place * (F / 512) + hw) * 16 + (lane >> 4) * 4) = u32x2{EMPTY_WORD, EMPTY_WORD};
+  }
+  __device__ __forceinline__ void empty_rows(bf16_t* attn, int slot, int h, u32x2 with, int lane) const {
+    const LayersP& p = lk_args();
+    const int lr = lane & 15;
+    if (lr < p.R) *(u32x2*)(attn + (size_t)(slot * p.R + lr) * 512 + h * 64 + hw * 16 + (lane >> 4) * 4) = with;
+  }
+  __device__ __forceinline__ void part_rows(int slot, int h, int split, f32x4 o, float M, float L, int lane) const {
+    const LayersP& p = lk_args();
+    float* part = p.part + (((long)slot * 8 + h) * p.split + split) * (16 * 66);
+    *(f32x4*)(part + (lane & 15) * 64 + hw * 16 + (lane >> 4) * 4) = o;
+    if (hw == 0 && lane < 16) { part[1024 + lane] = M; part[1040 + lane] = L; }
+  }
+  __device__ __forceinline__ void empty_self(int lane) const {
+    const int items = self_places(), split = lk_args().split;
+    const float e = __uint_as_float(EMPTY_WORD);
+#pragma unroll 1
+    for (int place = j.rank; place < items; place += j.members) {
+      const int ss = place >> 3, sp = split > 1 ? ss / j.slots : 0, slot = j.slot0 + ss - sp * j.slots;
+      if (split > 1) part_rows(slot, place & 7, sp, f32x4{e, e, e, e}, e, e, lane);
+      else empty_rows(lk_args().attn, slot, place & 7, u32x2{EMPTY_WORD, EMPTY_WORD}, lane);
+    }
+  }
+  __device__ __forceinline__ void empty_cross(int lane) const {
+#pragma unroll 1
+    for (int place = j.cross(); place < j.cross_places(); place += j.members) empty_rows(lk_args().attn2, j.slot0 + (place >> 3), place & 7, u32x2{EMPTY_WORD, EMPTY_WORD}, lane);
+  }
+  // Ahead of a job's first hand-over: nothing is assumed of what the buffers hold
+  __device__ __forceinline__ void empty_all(int lane) const {
+    const LayersP& p = lk_args();
+#pragma unroll 1
+    for (int place = j.rank; place < LK_PLACES; place += j.members) {
+      empty_tile(stream(0, 1), place, lane); empty_tile(stream(0, 2), place, lane); empty_tile(p.x3, place, lane);
+    }
+    empty_self(lane); empty_cross(lane);
+  }
+
+  // One operator with a product
+  enum { QKV, O, CO, UP, DOWN };
+  template <int OP, int N, int K>
+  __device__ __forceinline__ void product(int l) {
+    constexpr int D = 512;
+    constexpr bool LN = OP == QKV || OP == UP, RES = !LN;
     const LayersP& p = lk_args();
     const int lane = lk_lane(), lr = lane & 15, lq = lane >> 4;
     const float *ln = nullptr, *bias = nullptr;
-    if constexpr (LN) ln = (const float*)((const char*)(p.*lnp) + l * p.stride);
-    if constexpr (BIAS) bias = (const float*)((const char*)(p.*biasp) + l * p.stride);
+    if constexpr (LN) ln = (const float*)((const char*)(OP == QKV ? p.ln1 : p.ln3) + l * p.stride);
+    if constexpr (OP == UP || OP == DOWN) bias = (const float*)((const char*)(OP == UP ? p.b1 : p.b2) + l * p.stride);
     f32x4 g[2], b[2], bs, res;
-    const rsrc_t xr = rsrc_of(p.x + (size_t)j.row0 * D, (unsigned)j.rows * D * 4);
+    float* const in = stream(l, OP == QKV || OP == O ? 0 : (OP == CO ? 1 : 2));        // LN: the rows; otherwise what the result is added to
+    const rsrc_t xr = rsrc_of(in + (size_t)j.row0 * D, (unsigned)j.rows * D * 4);
     auto operands = [&](int place) {
       const int n = (place * N + hw) * 16 + lq * 4;
       if (N < 4 && hw >= N) return;
-      if constexpr (BIAS) bs = *(const f32x4*)(bias + n);
-      if constexpr (EPI == LK_RES) res = __builtin_bit_cast(f32x4, lk_load16(xr, (lr * D + n) * 4));
+      if constexpr (OP == UP || OP == DOWN) bs = *(const f32x4*)(bias + n);
+      if constexpr (RES) res = __builtin_bit_cast(f32x4, lk_load16(xr, (lr * D + n) * 4));           // (its own: the tile is its place's in all of O, CO and DOWN)
     };
     if constexpr (LN) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) { g[h] = *(const f32x4*)(ln + lane * 8 + h * 4); b[h] = *(const f32x4*)(ln + D + lane * 8 + h * 4); }
     }
     operands(j.rank);
-    if (op > 0) lk_wait<NF>(flags, op, from, producers, lane, broken, p.error);
-    ++op;
-    if constexpr (LN) lk_norm(p.x + (size_t)j.row0 * D, j.rows, g, b, p.eps, xs, hw, lane);
-    else if constexpr (K > D) lk_copy<K>(p.ffh + (size_t)j.row0 * K, j.rows, xs, hw, lane);
-    else if (merged) lk_merge(p.part, p.split, j.slot0, p.R, j.rows, xs, hw, lane);
-    else lk_copy<K>(p.attn + (size_t)j.row0 * K, j.rows, xs, hw, lane);
+    // (everybody has emptied what it writes)
+    if (OP == O && l == 0) lk_wait<4>(flags, op, 0, j.members, lane, broken, p.error);
+    if constexpr (LN) lk_norm(in + (size_t)j.row0 * D, j.rows, g, b, p.eps, xs, hw, lane, poll(OP != QKV || l > 0));
+    else if constexpr (OP == DOWN) lk_copy<K>(p.ffh + (size_t)j.row0 * K, j.rows, xs, hw, lane, poll());
+    else if (OP == O && p.split > 1) lk_merge(p.part, p.split, j.slot0, p.R, j.rows, xs, hw, lane, poll());
+    else lk_copy<K>((OP == O ? p.attn : p.attn2) + (size_t)j.row0 * K, j.rows, xs, hw, lane, poll());
 #pragma unroll 1
     for (int place = j.rank; place < LK_PLACES; place += j.members) {
       if (place != j.rank) operands(place);
       lk_barrier();                              // the input is staged, the partial sums of the place before are read
+      if (place == j.rank) {
+        if constexpr (OP == QKV) { empty_hidden(lane); if (l == 0) empty_all(lane); }         // (read: DOWN's results are there)
+        if constexpr (OP == CO) empty_self(lane);                                                // (O's results were there ahead of the cross-attention's)
+        if constexpr (OP == UP) empty_cross(lane);                                               // (CO's are there)
+      }
       lk_barrier();                              // the partial sums are there
       if (N < 4 && hw >= N) continue;
       f32x4 v = partial_sums<N>(lane);
       if (lr >= j.rows) continue;
       const int tile = place * N + hw, n = tile * 16 + lq * 4;
-      if constexpr (EPI == LK_QKV) {
+      if constexpr (OP == QKV) {
         const int c = tile / (D / 16), col = n - c * D;
         if (c == 0) {                            // (lo: D columns on)
           u32x2 hi, lo;
@@ -347,18 +462,20 @@ struct LkHelper {
           *(u32x2*)q = hi; *(u32x2*)(q + D) = lo;
         }
         else if (sb >= 0) kv_frag_store((c == 1 ? p.selfK : p.selfV) + l * p.self_layer, c == 2, sb, D / 64, p.self_groups, key, col, cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
-      } else if constexpr (EPI == LK_RELU) {
+      } else if constexpr (OP == UP) {
         v += bs;
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.f);
-        *(u32x2*)(p.ffh + (size_t)(j.row0 + lr) * LD + n) = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
+        *(u32x2*)(p.ffh + (size_t)(j.row0 + lr) * F + n) = full_words(u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])});
       } else {
-        if constexpr (BIAS) v += bs;
+        if constexpr (OP == DOWN) v += bs;
         v += res;
-        *(f32x4*)(p.x + (size_t)(j.row0 + lr) * LD + n) = v;
+        float* const out = stream(l, OP == O ? 1 : (OP == CO ? 2 : 3));
+        *(u32x4*)(out + (size_t)(j.row0 + lr) * D + n) = full_words(v);
+        if (OP != O || l > 0) empty_tile(in, place, lane);          // (everybody has read the input: it has led to what this operator waited for)
       }
     }
-    if (N == 4 || hw < N) raise();
+    if constexpr (OP == QKV) { ++op; raise(); }
   }
 
   __device__ __forceinline__ static AttnP attn_args(bool self) {
@@ -394,11 +511,15 @@ struct LkHelper {
       unsigned t[G];
 #pragma unroll
       for (int g = 0; g < G; ++g) t[g] = __builtin_amdgcn_raw_buffer_load_b32(lane < 32 ? kr : vr, (lane & 31) * 128, (first + hw + g * 4) * (KV_GROUP * 2), 16);
-      lk_wait<3>(flags, op - 1, 0, j.members, lane, broken, p.error);
+      lk_wait<3>(flags, op, 0, j.members, lane, broken, p.error);
 #pragma unroll
       for (int g = 0; g < G; ++g) asm volatile("" ::"v"(t[g]));
     }
-    if (s < 0) { lk_barrier(); return; }         // (as the attention's own)
+    if (s < 0) {                                 // (rows of nobody; a barrier as the attention's own)
+      if (p.split > 1) part_rows(slot, h, split, f32x4{0.f, 0.f, 0.f, 0.f}, 0.f, 1.f, lane); else empty_rows(out, slot, h, u32x2{0, 0}, lane);
+      lk_barrier();
+      return;
+    }
     const unsigned off = lr * 2048 + (h * 64 + 8 * lq) * 2;
     bf16x8 qhi[2], qlo[2];
 #pragma unroll
@@ -409,17 +530,15 @@ struct LkHelper {
     u32x4 kf[G][4], vf[G][4];
     attn_load_kv<KVNT, G>(kr, vr, first + hw, 4, lane, kf, vf);
     __builtin_amdgcn_sched_barrier(0);
-    attention_mfma_core<KVNT, true, G == 2 ? -1 : 0, G>(a, sm, h, slot, 0, split, 0, p.R, 8, p.split, hw * 64 + lane, 4, first, hop, kr, vr, kf, vf, qhi, qlo, lim, out);
+    attention_mfma_core<KVNT, true, G == 2 ? -1 : 0, G, ATTN_WORDS>(a, sm, h, slot, 0, split, 0, p.R, 8, p.split, hw * 64 + lane, 4, first, hop, kr, vr, kf, vf, qhi, qlo, lim, out);
   }
   __device__ __forceinline__ void self_attention(int l) {
     const int items = self_places();
     const bool few = lk_args().few;
-    ++op;
 #pragma unroll 1
     for (int place = j.rank; place < items; place += j.members) {
       if (few) self_place<1>(l, place); else self_place<2>(l, place);
     }
-    if (j.rank < items) raise();
   }
   // LayerNorm, queries of one head and attention over the source
   __device__ __forceinline__ void cross_attention(int l) {
@@ -434,7 +553,6 @@ struct LkHelper {
 #pragma unroll
       for (int h = 0; h < 2; ++h) { g[h] = *(const f32x4*)(ln + lane * 8 + h * 4); b[h] = *(const f32x4*)(ln + D + lane * 8 + h * 4); }
     }
-    ++op;
 #pragma unroll 1
     for (int place = mine; place < items; place += j.members) {
       const int h = place & 7, slot = j.slot0 + (place >> 3), s = sequence(slot);
@@ -443,9 +561,8 @@ struct LkHelper {
       u32x4 kf[1][4], vf[1][4];
       attn_load_kv<false, 1>(kr, vr, hw, 4, lane, kf, vf);
       const int lim = lk_const(p.src_len, slot);
-      if (place == mine) lk_wait<1>(flags, op - 1, 0, j.members, lane, broken, p.error);
-      else lk_barrier();                         // the results of the place before are out of LDS
-      lk_norm(p.x + (size_t)slot * p.R * D, p.R, g, b, p.eps, xs, hw, lane);
+      if (place != mine) lk_barrier();           // the results of the place before are out of LDS
+      lk_norm(p.x1 + (size_t)slot * p.R * D, p.R, g, b, p.eps, xs, hw, lane, poll());
       lk_barrier();
       lk_barrier();
       {
@@ -462,10 +579,9 @@ struct LkHelper {
         qhi[s2] = __builtin_bit_cast(bf16x8, *(const u32x4*)&q_s[(s2 * 64 + lane) * 2]);
         qlo[s2] = __builtin_bit_cast(bf16x8, *(const u32x4*)&q_s[256 + (s2 * 64 + lane) * 2]);
       }
-      if (s < 0) { lk_barrier(); continue; }     // (as the attention's own)
-      attention_mfma_core<false, false, 0, 1>(a, sm, h, slot, 0, 0, 0, p.R, 8, 1, hw * 64 + lane, 4, 0, 4, kr, vr, kf, vf, qhi, qlo, lim, p.attn);
+      if (s < 0) { empty_rows(p.attn2, slot, h, u32x2{0, 0}, lane); lk_barrier(); continue; }     // (as the attention's own)
+      attention_mfma_core<false, false, 0, 1, ATTN_WORDS>(a, sm, h, slot, 0, 0, 0, p.R, 8, 1, hw * 64 + lane, 4, 0, 4, kr, vr, kf, vf, qhi, qlo, lim, p.attn2);
     }
-    if (mine < items) raise();
   }
 
   __device__ __forceinline__ void job() {
@@ -480,13 +596,13 @@ struct LkHelper {
 #pragma unroll 1
     for (int l = 0; l < layers; ++l) {
       // (the first operator of a job follows the launch, or the last operator of the job before, whose rows are others)
-      product<3, 512, LK_QKV, 1, true, false>(l, j.members, &LayersP::ln1, nullptr);
+      product<QKV, 3, 512>(l);
       self_attention(l);
-      product<1, 512, LK_RES, 4, false, false>(l, min_members(self_places()), nullptr, nullptr, lk_args().split > 1);
+      product<O, 1, 512>(l);
       cross_attention(l);
-      product<1, 512, LK_RES, 4, false, false>(l, min_members(j.cross_places()), nullptr, nullptr, false, j.cross_first());
-      product<F / 512, 512, LK_RELU, 1, true, true>(l, j.members, &LayersP::ln3, &LayersP::b1);
-      product<1, F, LK_RES, F / 512, false, true>(l, j.members, nullptr, &LayersP::b2);
+      product<CO, 1, 512>(l);
+      product<UP, F / 512, 512>(l);
+      product<DOWN, 1, F>(l);
     }
   }
 };

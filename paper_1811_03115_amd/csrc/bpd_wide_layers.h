@@ -272,7 +272,7 @@ struct WkHelper {
     u32x4 kf[G][4], vf[G][4];
     attn_load_kv<false, G>(kr, vr, first + hw, 4, lane, kf, vf);
     __builtin_amdgcn_sched_barrier(0);
-    attention_mfma_core<false, true, G == 2 ? -1 : 0, G, true>(a, sm, h, slot, 0, 0, 0, p.R, H, 1, hw * 64 + lane, 4, first, 4 * G, kr, vr, kf, vf, qhi, qlo, lim, out);
+    attention_mfma_core<false, true, G == 2 ? -1 : 0, G, ATTN_THROUGH>(a, sm, h, slot, 0, 0, 0, p.R, H, 1, hw * 64 + lane, 4, first, 4 * G, kr, vr, kf, vf, qhi, qlo, lim, out);
   }
   __device__ __forceinline__ void heads_done(int which, bool mine) {
     if (!heads_tell()) { done<4>(mine, 24 + (which == WK_CROSS ? j.cross_first() : 0), 2 * j.slots, true); return; }
@@ -327,7 +327,7 @@ struct WkHelper {
       qlo[s2] = __builtin_bit_cast(bf16x8, *(const u32x4*)&q_s[256 + (s2 * 64 + lane) * 2]);
     }
     if (s < 0) { lk_barrier(); return; }     // (as the attention's own)
-    attention_mfma_core<false, false, 0, 1, true>(a, sm, h, slot, 0, 0, 0, p.R, H, 1, hw * 64 + lane, 4, 0, 4, kr, vr, kf, vf, qhi, qlo, lim, p.attn);
+    attention_mfma_core<false, false, 0, 1, ATTN_THROUGH>(a, sm, h, slot, 0, 0, 0, p.R, H, 1, hw * 64 + lane, 4, 0, 4, kr, vr, kf, vf, qhi, qlo, lim, p.attn);
   }
   __device__ __forceinline__ void cross_attention(int l) {
     ++op;
