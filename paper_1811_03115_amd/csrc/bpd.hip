@@ -752,7 +752,7 @@ int layers_way(const bpd_ctx* ctx, int slots, int R) {
   if (layers_shape(c)) return layers_fit(slots, R) ? LAYERS_JOBS : LAYERS_CHAIN;
   const long keys = attention_keys(ctx, c.max_out_len + c.k_max + 1, R, 1);
   if (wide_layers_fit(slots, R, keys, ctx->S)) return LAYERS_WIDE;
-  return ctx->lay.layers_xn && tall_layers_fit(slots, R, keys, ctx->S) ? LAYERS_TALL : LAYERS_CHAIN;
+  return ctx->lay.layers_x2 && tall_layers_fit(slots, R, keys, ctx->S) ? LAYERS_TALL : LAYERS_CHAIN;
 }
 int layers_split_of(const bpd_ctx* ctx, int slots, int R) {
   const bpd_config& c = ctx->cfg;
@@ -783,7 +783,6 @@ void launch_layers(bpd_ctx* ctx, int R, int way) {
   p.stride = c.n_dec_layers > 1 ? (long)((const char*)L.dec[1].wqkv - (const char*)w.wqkv) : 0;      // (every layer's arrays are laid out alike)
   p.n_layers = c.n_dec_layers; p.R = R; p.slots = ctx->Bs; p.per_job = layers_per_job(ctx->Bs); p.jobs = (ctx->Bs + p.per_job - 1) / p.per_job;
   p.split = layers_split_of(ctx, ctx->Bs, R);
-  p.few = attention_keys(ctx, (int)slots, R, 1) <= 128;
   p.x = L.x; p.q = (bf16_t*)L.q; p.part = L.attn_part; p.attn = (bf16_t*)L.attn; p.ffh = (bf16_t*)L.ffh;
   p.selfK = (bf16_t*)L.selfK; p.selfV = (bf16_t*)L.selfV; p.crossK = (const bf16_t*)L.crossK; p.crossV = (const bf16_t*)L.crossV;
   p.self_layer = (long)c.max_batch * kv_rows(c, slots) * d; p.src_layer = (long)c.max_batch * kv_rows(c, c.max_src_len) * d;
@@ -795,6 +794,7 @@ void launch_layers(bpd_ctx* ctx, int R, int way) {
   ctx->layers_ran = true;
   if (way == LAYERS_WIDE) {
     p.jobs = p.per_job = p.split = 0;
+    p.xn = (bf16_t*)L.layers_xn; p.x1 = L.layers_x1; p.attn = (bf16_t*)L.layers_attn2; p.ffh = (bf16_t*)L.layers_ffh;
     static bool attr_set = false;
     if (!attr_set) { (void)hipFuncSetAttribute((const void*)wide_layers_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, WkLds::BYTES); attr_set = true; }
     hipLaunchKernelGGL(wide_layers_kernel, dim3(WK_XCDS * LK_PLACES), dim3(512), WkLds::BYTES, ctx->stream, p);

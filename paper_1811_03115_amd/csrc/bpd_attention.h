@@ -118,8 +118,8 @@ __device__ __forceinline__ void attn_load_kv(rsrc_t kr, rsrc_t vr, int c, int nw
 }
 // The item's work from the point where its queries (qhi + qlo) and the first groups of K and V are at hand or under way (parameters as in
 // attention_mfma_body; first, hop: this split's first group and the distance to its next round; lim: limit[b]).  STORE: results are written through the L2
-// (ATTN_THROUGH), or no word of them is EMPTY_WORD (ATTN_WORDS).
-enum { ATTN_PLAIN, ATTN_THROUGH, ATTN_WORDS };
+// (ATTN_THROUGH), no word of them is EMPTY_WORD (ATTN_WORDS), or both.
+enum { ATTN_PLAIN, ATTN_THROUGH, ATTN_WORDS, ATTN_THROUGH_WORDS };
 template <bool KVNT, bool LIMF, int QU, int G, int STORE = ATTN_PLAIN>
 __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLds& sm, int h, int b, int tile, int split, int r0, int nrows,
                                                     int nheads, int nz, int tid, int nw, int first, int hop, rsrc_t kr, rsrc_t vr,
@@ -220,9 +220,9 @@ __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLd
       float inv = __builtin_amdgcn_rcpf(L);
       inv = inv * fmaf(-L, inv, 2.f);            // (one Newton step: the quotient to fp32)
       u32x2 w = u32x2{cvt_pk_bf16(o[0] * inv, o[1] * inv), cvt_pk_bf16(o[2] * inv, o[3] * inv)};
-      if constexpr (STORE == ATTN_WORDS) w = full_words(w);
+      if constexpr (STORE == ATTN_WORDS || STORE == ATTN_THROUGH_WORDS) w = full_words(w);
       bf16_t* to = out + ((size_t)b * p.R + r0 + lr) * p.d + h * DH + dim;
-      if constexpr (STORE == ATTN_THROUGH) asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(to), "v"(w) : "memory");      // (to memory, for other XCDs)
+      if constexpr (STORE == ATTN_THROUGH || STORE == ATTN_THROUGH_WORDS) asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(to), "v"(w) : "memory");      // (to memory, for other XCDs)
       else *(u32x2*)to = w;
     }
   } else {

@@ -65,7 +65,7 @@ struct Layout {
   unsigned char* stack_ex = nullptr; unsigned* stack_flags = nullptr; unsigned* stack_err = nullptr; unsigned* xcc_map = nullptr;
   unsigned long long* stack_trace = nullptr; void* stack_layers = nullptr;
   void* layers_xn = nullptr; float* layers_x2 = nullptr;         // tall_layers_kernel: LayersP::xn, x2
-  float *layers_x1 = nullptr, *layers_x3 = nullptr; void* layers_attn2 = nullptr;      // layers_kernel: LayersP::x1, x3, attn2
+  float *layers_x1 = nullptr, *layers_x3 = nullptr; void *layers_attn2 = nullptr, *layers_ffh = nullptr;      // layers_kernel: LayersP::x1, x3, attn2; wide_layers_kernel: x1, attn, ffh
   unsigned* layers_sync = nullptr;               // layers_kernel: what its workgroups count in
   // encoder activations (max_batch * max_src rows)
   float *xe, *qe; void *xen, *ke, *ve, *attne, *ffhe, *mem;
@@ -242,7 +242,9 @@ size_t build_layout(const bpd_config& c, char* base, Layout& L, std::vector<std:
   L.sched = ints(B * (size_t)c.max_out_len);
   L.dyn = a.take(64); L.tick = ints(B); L.imp_next = ints(B); L.steps_done = ints(B); L.fin_step = ints(B); L.slot_seq = ints(B); L.slot_L = ints(B); L.slot_src = ints(B); L.slot_row = ints(B); L.n_live = ints(1);
   L.stats = (long long*)a.take(32 * 8);
-  if (wide_layers_shape(c) && M > 16) { L.layers_xn = a.take((size_t)LK_JOBS * TALL_LAYERS_ROWS * d * as); L.layers_x2 = vec(TALL_LAYERS_ROWS * d); }
+  if (wide_layers_shape(c)) L.layers_xn = a.take((size_t)LK_JOBS * 64 * d * as);
+  if (wide_layers_shape(c) && M > 16) { L.layers_x2 = vec(TALL_LAYERS_ROWS * d); }
+  if (wide_layers_shape(c)) { L.layers_x1 = vec((size_t)6 * 16 * d); L.layers_attn2 = a.take((size_t)4 * 16 * d * as); L.layers_ffh = a.take((size_t)2 * 16 * F * as); }
   if (layers_shape(c)) { L.layers_x1 = vec((size_t)2 * LK_JOBS * 16 * d); L.layers_x3 = vec((size_t)LK_JOBS * 16 * d); L.layers_attn2 = a.take((size_t)LK_JOBS * 16 * d * as); }
   L.layers_sync = layers_shape(c) || wide_layers_shape(c) ? (unsigned*)a.take((size_t)LK_WORDS * 4) : nullptr;
   L.xcc_map = (unsigned*)a.take(XCC_MAP_MAX * 4);

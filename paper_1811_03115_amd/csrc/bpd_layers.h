@@ -47,7 +47,7 @@ struct LayersP {
   const float *ln1, *ln2, *ln3, *b1, *b2;        // gains, biases of a LayerNorm d floats behind
   long stride;                                   // bytes to the next layer's
   int n_layers, R, slots, per_job, jobs, group;  // R rows per slot; slots per job; members that a group waits for
-  int split, few;                                // workgroups per (head, slot) of the self-attention; few: up to 128 keys
+  int split;                                     // workgroups per (head, slot) of the self-attention
   float *x, *part;
   bf16_t *q, *attn, *ffh, *selfK, *selfV;         // q: a row is 2 d wide (bf16 hi and lo parts)
   float *x1, *x3;                                // layers_kernel: the residual stream behind the two attentions (x1, then x2) and between layers
@@ -176,6 +176,17 @@ struct LkPoll {
   bool* broken;
   long long* error;
   bool on;                                       // (off: the data is known to be there)
+  int turn = -1;                                 // first()
+  // One of N pieces of 1 KB, ahead of all: a longer wait with less traffic (turn: members that wait for the same ask for different ones)
+  template <int N> __device__ __forceinline__ void first(const rsrc_t& r, unsigned at, int lane) const {
+    if (turn < 0 || !on || *broken) return;
+    const unsigned off = at + turn % N * 1024 + lane * 16;
+#pragma unroll 1
+    for (int s = 0; s < LK_POLLS; ++s) {
+      if (!__any(lk_top(0, lk_load16(r, off)) == EMPTY_WORD)) return;
+      asm volatile("" ::: "memory");
+    }
+  }
   // load: fetches and returns the largest word
   template <class Load> __device__ __forceinline__ void operator()(Load&& load) const {
 #pragma unroll 1
@@ -242,6 +253,7 @@ template <int K, int M>
 __device__ __forceinline__ void lk_copy_rows(const rsrc_t& r, int rows, bf16_t* xs, int hw, int lane, LkPoll poll) {
   constexpr int N = K / 512;
   u32x4 v[M][N];
+  poll.first<N>(r, hw * K * 2, lane);
   poll([&] {
 #pragma unroll
     for (int i = 0; i < M; ++i)
@@ -534,10 +546,12 @@ struct LkHelper {
   }
   __device__ __forceinline__ void self_attention(int l) {
     const int items = self_places();
-    const bool few = lk_args().few;
 #pragma unroll 1
     for (int place = j.rank; place < items; place += j.members) {
-      if (few) self_place<1>(l, place); else self_place<2>(l, place);
+      const LayersP& p = lk_args();
+      const int lim = lk_const(p.base, j.slot0 + (place >> 3) % j.slots);
+      // (up to 128 keys: a group of 32 per wave)
+      if (p.split == 1 && ((lim + p.R + 31) >> 5) - (attn_first_key(attn_args(true), lim) >> 5) <= 4) self_place<1>(l, place); else self_place<2>(l, place);
     }
   }
   // LayerNorm, queries of one head and attention over the source

@@ -94,23 +94,7 @@ struct TkHelper : WkHelper {
   }
   __device__ __forceinline__ void norm_row(f32x4 (&v)[4], const f32x4 (&g)[4], const f32x4 (&b)[4], bf16_t* to) {
     const int lane = lk_lane();
-    const f32x4 t = (v[0] + v[1]) + (v[2] + v[3]);
-    const float mu = wave_sum((t[0] + t[1]) + (t[2] + t[3])) * (1.f / D);
-    f32x4 q = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      v[h] -= mu;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) q[r] = fmaf(v[h][r], v[h][r], q[r]);
-    }
-    const float rs = inv_sqrt(fmaf(wave_sum((q[0] + q[1]) + (q[2] + q[3])), 1.f / D, lk_args().eps));
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      f32x4 y;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) y[r] = fmaf(v[h][r] * rs, g[h][r], b[h][r]);
-      *(u32x2*)(to + h * 256 + lane * 4) = u32x2{cvt_pk_bf16(y[0], y[1]), cvt_pk_bf16(y[2], y[3])};
-    }
+    wk_norm_row(v, g, b, lk_args().eps, [&](int h, u32x2 w) { *(u32x2*)(to + h * 256 + lane * 4) = w; });
   }
   // Does layer l's first LayerNorm find its rows in another buffer than its own?
   __device__ __forceinline__ bool moved(int l) const { return l > 0 || residual(0) != lk_args().x; }
@@ -224,7 +208,6 @@ struct TkHelper : WkHelper {
   }
   template <int OP>
   __device__ __forceinline__ void attention(int l) {
-    const bool few = lk_args().few;
     ++op;
     bool mine = false;
 #pragma unroll 1
@@ -234,9 +217,8 @@ struct TkHelper : WkHelper {
 #pragma unroll 1
       for (int k = first; k < 2 * j.slots; k += 16) {
         const int item = TkPlaces::item(place, k);
-        if constexpr (OP == WK_CROSS) cross_item(l, item, residual(l), !mine);
-        else if (few) self_item<1, MT>(l, item, !mine);
-        else self_item<2, MT>(l, item, !mine);
+        if constexpr (OP == WK_CROSS) cross_item<ATTN_THROUGH>(l, item, residual(l), op - 1, poll(false), lk_args().attn, !mine);
+        else self_item<MT, ATTN_THROUGH>(l, item, op - 1, lk_args().attn, !mine);
         mine = true;
       }
     }

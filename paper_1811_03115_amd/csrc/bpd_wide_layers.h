@@ -3,20 +3,20 @@
 //
 // A layer of this shape has 29 MB of weights, more than one XCD streams in the time that the chain of operators takes (25 us at 1.2 TB/s), so all
 // XCDs work on one block: 256 members, one per CU, hold a layer's weights in their registers, fetched while they have no part in
-// an operator, and hand the block over between XCDs: results are written through to memory (sc1) and read past the L1; when they are
-// acknowledged a member raises a flag on its XCD, the XCD's first member (behind the second FFN layer, when that one's compute waves fetch weights, its
-// last: 0.8 us sooner) gathers these and raises a flag on every XCD.  An attention of few heads per XCD does without the gathering.
-// (Grid-wide hand-overs of a 40 KB block, a chain with nothing else: 3.0 us with atomic counters per XCD, 5.0 us with one flag per workgroup that all
-// poll, 2.7 us this way; one kernel per operator 4.2 us.)
+// an operator, and hand the block over between XCDs: results are written through to memory (sc1), read past the L1, and tell by themselves that they have come
+// (EMPTY_WORD, as in bpd_layers.h).  (With flags, gathered by one member of each XCD and passed on to all, six layers of one row took 120 us instead of 101, of ten
+// rows 151 instead of 137.)  Flags remain where the block's keys and values lie among older ones, inside an XCD, and to tell once that everybody has emptied what it
+// writes.  What bounds a hand-over of more rows is traffic: whoever waits asks memory again and again, and 256 members that fetch 40 KB a round to
+// normalise it are slower than ten waves per XCD that fetch a row each and hand 20 KB on inside the XCD.
 //
 // Places.  Place 32 x + r is that of member r on XCD x:  every place has a tile of the first FFN layer;  r < 8: one of the second;  r >= 8:
 // one of the queries, keys and values, those of heads 2 x and 2 x + 1, whose self-attention is with places r >= 24 of the same XCD (so that
 // this hand-over stays inside it: plain stores, local flags);  8 .. 15, 16 .. 23: output projections of the self- and the cross-attention;  24 ..:
 // cross-attention, beside the self-attention where there is room.
 //
-// Six layers of 10 rows, 40 keys, 32 source tokens: 204 us as a chain of 60 kernels, 147 here (with no weights fetched: 142), of one row 124, of 16 rows
-// in four slots 157.  What bounds it is the hand-over, six times a layer between XCDs: results acknowledged 0.2 .. 0.5 us, flags gathered 0.3 .. 0.5,
-// seen elsewhere 0.5 .. 0.8; then the input's staging (0.5 us, with LayerNorm of ten rows 1.35) and 0.7 from there to the stores.
+// Six layers of 10 rows, 20 .. 120 keys, 27 source tokens: 137 us (as a chain of 60 kernels some 200), of one row 101.  What bounds it is the hand-over, six times a layer
+// between XCDs: 0.5 .. 0.8 us until a result is seen elsewhere, a round of asking (0.7), another for all of the input; then the input's
+// staging and 0.7 us from there to the stores.
 //
 // Members register as in bpd_layers.h.  The first on each XCD closes its list when 32 have come or LK_CLOSE_TICKS have passed, and tells all XCDs
 // how many there are; an XCD where nobody has come is closed by others.  Fewer than 256 members share the places out, fetch weights as
@@ -25,6 +25,9 @@
 #pragma once
 
 constexpr int WK_HOLD = 40, WK_GAP = 1;           // pauses of the compute waves, as LK_HOLD and LK_GAP (six layers of 10 rows: hold 12: 151 us, 24: 150, 40: 147, 64: 149, 90: 150)
+// Blocks of more rows than this share what is normalised: see stage_norm (128 tokens of ten rows a step: 5.1 ms, 5.5 with every member normalising all; greedy: 5.0 ms,
+// 5.2 shared)
+constexpr int WK_ROWS_ALONE = 4;
 constexpr int WK_XCDS = 8, WK_CENSUS = 32, WK_GLOBAL = 64, WK_LOCAL = 96, WK_HEADS = 224, WK_AREA = 480;      // words of an XCD's area: [0] registered; members of each XCD; its operators done; flags [wave][member]; heads [XCD] [slot][head], a line each XCD
 static_assert(WK_XCDS * WK_AREA <= LK_WORDS, "both kernels count in the same words");
 
@@ -36,14 +39,23 @@ __device__ __forceinline__ void wk_store2(bf16_t* p, unsigned v) { asm volatile(
 
 // LayerNorm of up to 16 rows of 1024 into LDS as bf16, rows 1032 apart; wave hw takes rows hw, hw + 4, ..
 template <int N>
-__device__ __forceinline__ void wk_norm_rows(const rsrc_t& xr, int rows, const f32x4 (&g)[4], const f32x4 (&b)[4], float eps, bf16_t* xs, int hw, int lane) {
+__device__ __forceinline__ void wk_norm_rows(const rsrc_t& xr, int rows, const f32x4 (&g)[4], const f32x4 (&b)[4], float eps, bf16_t* xs, int hw, int lane, LkPoll poll) {
   constexpr int D = 1024;
   f32x4 v[N][4];
+  poll.first<4>(xr, hw * D * 4, lane);
+  poll([&] {
 #pragma unroll
-  for (int i = 0; i < N; ++i)
+    for (int i = 0; i < N; ++i)
 #pragma unroll
-    for (int h = 0; h < 4; ++h) v[i][h] = __builtin_bit_cast(f32x4, lk_load16(xr, ((hw + 4 * i) * D + h * 256 + lane * 4) * 4));
-  __builtin_amdgcn_sched_barrier(0);
+      for (int h = 0; h < 4; ++h) v[i][h] = __builtin_bit_cast(f32x4, lk_load16(xr, ((hw + 4 * i) * D + h * 256 + lane * 4) * 4));
+    __builtin_amdgcn_sched_barrier(0);
+    unsigned top = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int h = 0; h < 4; ++h) top = lk_top(top, __builtin_bit_cast(u32x4, v[i][h]));
+    return top;
+  });
   float mu[N], q[N];
 #pragma unroll
   for (int i = 0; i < N; ++i) { const f32x4 s = (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]); mu[i] = (s[0] + s[1]) + (s[2] + s[3]); }
@@ -74,12 +86,34 @@ __device__ __forceinline__ void wk_norm_rows(const rsrc_t& xr, int rows, const f
     }
   }
 }
-__device__ __forceinline__ void wk_norm(const float* x, int rows, const f32x4 (&g)[4], const f32x4 (&b)[4], float eps, bf16_t* xs, int hw, int lane) {
+// One row: the same for a wave that holds it (columns 256 h + 4 lane ..); store(h, bf16 of these)
+template <class Store>
+__device__ __forceinline__ void wk_norm_row(f32x4 (&v)[4], const f32x4 (&g)[4], const f32x4 (&b)[4], float eps, Store&& store) {
+  constexpr int D = 1024;
+  const f32x4 t = (v[0] + v[1]) + (v[2] + v[3]);
+  const float mu = wave_sum((t[0] + t[1]) + (t[2] + t[3])) * (1.f / D);
+  f32x4 q = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
+    v[h] -= mu;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) q[r] = fmaf(v[h][r], v[h][r], q[r]);
+  }
+  const float rs = inv_sqrt(fmaf(wave_sum((q[0] + q[1]) + (q[2] + q[3])), 1.f / D, eps));
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
+    f32x4 y;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) y[r] = fmaf(v[h][r] * rs, g[h][r], b[h][r]);
+    store(h, u32x2{cvt_pk_bf16(y[0], y[1]), cvt_pk_bf16(y[2], y[3])});
+  }
+}
+__device__ __forceinline__ void wk_norm(const float* x, int rows, const f32x4 (&g)[4], const f32x4 (&b)[4], float eps, bf16_t* xs, int hw, int lane, LkPoll poll = {nullptr, nullptr, false}) {
   const rsrc_t xr = rsrc_of(x, (unsigned)rows * 1024 * 4);
-  if (rows <= 4) wk_norm_rows<1>(xr, rows, g, b, eps, xs, hw, lane);
-  else if (rows <= 8) wk_norm_rows<2>(xr, rows, g, b, eps, xs, hw, lane);
-  else if (rows <= 12) wk_norm_rows<3>(xr, rows, g, b, eps, xs, hw, lane);
-  else { wk_norm_rows<2>(xr, rows, g, b, eps, xs, hw, lane); wk_norm_rows<2>(xr, rows, g, b, eps, xs, hw + 8, lane); }         // (registers)
+  if (rows <= 4) wk_norm_rows<1>(xr, rows, g, b, eps, xs, hw, lane, poll);
+  else if (rows <= 8) wk_norm_rows<2>(xr, rows, g, b, eps, xs, hw, lane, poll);
+  else if (rows <= 12) wk_norm_rows<3>(xr, rows, g, b, eps, xs, hw, lane, poll);
+  else { wk_norm_rows<2>(xr, rows, g, b, eps, xs, hw, lane, poll); wk_norm_rows<2>(xr, rows, g, b, eps, xs, hw + 8, lane, poll); }         // (registers)
 }
 
 enum { WK_QKV, WK_SELF, WK_O, WK_CROSS, WK_CO, WK_UP, WK_DOWN };
@@ -116,16 +150,15 @@ struct WkHelper {
   bool broken = false;
 
   __device__ __forceinline__ unsigned* area() const { return lk_args().sync + j.xcd * WK_AREA; }
-  // One or two slots: the members of a head tell all XCDs themselves (0.8 us until they see it, 1.25 through the first member; with eight heads
-  // per XCD, whose flags lie in one line, 1.8)
-  __device__ __forceinline__ bool heads_tell() const { return j.full && j.slots <= 2; }
-  // Operator `target` is done: a product, or an attention of n heads
-  __device__ __forceinline__ void wait(unsigned target, int n = 0) {
+  // (One piece first where a wait for everything would be 20 .. 80 KB a member, out of memory, round after round: 128 tokens of ten rows a step 5.1 ms, 5.5 without,
+  // and 5.3 if all ask for the same piece.)
+  __device__ __forceinline__ LkPoll poll(bool on = true) { return LkPoll{&broken, lk_args().error, on, j.rows > WK_ROWS_ALONE ? j.rank : -1}; }
+  // Operator `target` is done everywhere
+  __device__ __forceinline__ void wait(unsigned target) {
     if (broken || target == 0) return;
     const int lane = lk_lane();
-    const bool heads = n > 0 && heads_tell();
-    const unsigned* g = area() + (heads ? WK_HEADS + (lane >> 3) * 32 + (lane & 7) : WK_GLOBAL + (lane & 7));
-    const bool of = heads ? (lane & 7) * 8 < n : (j.xcds >> (lane & 7) & 1);
+    const unsigned* g = area() + WK_GLOBAL + (lane & 7);
+    const bool of = j.xcds >> (lane & 7) & 1;
 #pragma unroll 1
     for (int s = 0; s < LK_SPINS; ++s) {
       const unsigned v = lk_load(g);
@@ -137,11 +170,11 @@ struct WkHelper {
   // This wave's part of the operator is in memory; a member of the XCD passes it on when all members' parts are: those of waves < NF of members from ..
   // from + count - 1 (not full: of all waves of all)
   template <int NF>
-  __device__ __forceinline__ void done(bool mine, int from, int count, bool pass_on, int passer = 0) {
+  __device__ __forceinline__ void done(bool mine, int from, int count, bool pass_on) {
     const int lane = lk_lane();
     unsigned* flags = area() + WK_LOCAL;
     if (!j.full || (mine && hw < NF)) lk_raise(flags + hw * 32 + j.rank, op, lane);
-    if (hw != 3 || j.rank != (j.full ? passer : 0) || !(pass_on || !j.full)) return;
+    if (hw != 3 || j.rank != 0 || !(pass_on || !j.full)) return;
     if (j.full) lk_wait<NF>(flags, op, from, count, lane, broken, lk_args().error);
     else lk_wait<4>(flags, op, 0, j.here, lane, broken, lk_args().error);
     if (lane < WK_XCDS) wk_store4(lk_args().sync + lane * WK_AREA + WK_GLOBAL + j.xcd, op);
@@ -179,11 +212,80 @@ struct WkHelper {
     }
   }
 
-  template <int OP, int K, bool LN, bool BIAS>
-  __device__ __forceinline__ void product(int l, const float* LayersP::*lnp, const float* LayersP::*biasp, int from, int count, int heads = 0) {
+  // Buffers of what is handed over, two of each, which the layers use in turn: the residual stream behind the attentions (stage 1, 2) and between layers (3),
+  // the attentions' results, the hidden layer.
+  __device__ __forceinline__ static float* between(int stage, int l) { return lk_args().x1 + ((stage - 1) * 2 + (l & 1)) * (16 * D); }
+  __device__ __forceinline__ static float* stream(int l, int stage) {
+    const LayersP& p = lk_args();
+    if (stage == 0) return l == 0 ? p.x : between(3, l - 1);
+    return stage == 3 && l + 1 == p.n_layers ? p.x : between(stage, l);
+  }
+  __device__ __forceinline__ static bf16_t* heads(int which, int l) { return lk_args().attn + ((which == WK_CROSS ? 2 : 0) + (l & 1)) * (16 * D); }
+  __device__ __forceinline__ static bf16_t* hidden(int l) { return lk_args().ffh + (l & 1) * (16 * F); }
+  // Normalised rows of an XCD, for QKV and UP: each row by a wave of one member (hw 3 of member 8 + row), who hands it on inside the XCD
+  __device__ __forceinline__ bool shared(int op, int l) const { return j.full && j.rows > WK_ROWS_ALONE && !(op == WK_QKV && l == 0); }
+  __device__ __forceinline__ bf16_t* normed(int op, int l) const { return lk_args().xn + (size_t)((j.xcd * 2 + (op == WK_UP ? 1 : 0)) * 2 + (l & 1)) * (16 * D); }
+  __device__ __forceinline__ int norm_of() const { return hw == 3 && j.rank >= 8 && j.rank - 8 < j.rows ? j.rank - 8 : -1; }
+  __device__ __forceinline__ void empty_normed(int op, int l, int lane) const {
+    const int m = norm_of();
+    if (!j.full || m < 0) return;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) *(u32x2*)(normed(op, l) + m * D + h * 256 + lane * 4) = u32x2{EMPTY_WORD, EMPTY_WORD};
+  }
+  __device__ __forceinline__ void stage_norm(int op, int l, const float* in, const f32x4 (&g)[4], const f32x4 (&b)[4], int lane) {
+    const LayersP& p = lk_args();
+    if (!shared(op, l)) { wk_norm(in, j.rows, g, b, p.eps, xs, hw, lane, poll(op != WK_QKV || l > 0)); return; }
+    const int m = norm_of();
+    if (m >= 0) {
+      const rsrc_t xr = rsrc_of(in, (unsigned)j.rows * D * 4);
+      f32x4 v[4];
+      LkPoll{&broken, p.error, true}([&] {
+        unsigned top = 0;
+#pragma unroll
+        for (int h = 0; h < 4; ++h) v[h] = __builtin_bit_cast(f32x4, lk_load16(xr, (m * D + h * 256 + lane * 4) * 4));
+#pragma unroll
+        for (int h = 0; h < 4; ++h) top = lk_top(top, __builtin_bit_cast(u32x4, v[h]));
+        return top;
+      });
+      wk_norm_row(v, g, b, p.eps, [&](int h, u32x2 w) { *(u32x2*)(normed(op, l) + m * D + h * 256 + lane * 4) = full_words(w); });
+    }
+    lk_copy<D>(normed(op, l), j.rows, xs, hw, lane, poll());
+  }
+  // They are emptied (EMPTY_WORD) by who writes them, a layer after that, when all are known to have read them, and ahead of an operator of the writer's that
+  // the next readers wait for: QKV for CO's results, UP for all others.
+  __device__ __forceinline__ void empty_tile(float* x, int tile, int lane) const {
+    const int lr = lane & 15;
+    const float e = __uint_as_float(EMPTY_WORD);
+    if (hw == 0 && tile >= 0 && lr < j.rows) wk_store16(x + (size_t)lr * D + tile * 16 + (lane >> 4) * 4, f32x4{e, e, e, e});
+  }
+  __device__ __forceinline__ void rows_of_head(bf16_t* attn, int item, unsigned with, int lane) const {
+    const LayersP& p = lk_args();
+    const int lr = lane & 15;
+    if (item >= 0 && lr < p.R) wk_store8(attn + (size_t)((item >> 4) * p.R + lr) * D + (item & 15) * 64 + hw * 16 + (lane >> 4) * 4, u32x2{with, with});
+  }
+  __device__ __forceinline__ void empty_hidden(int l, int place, int lane) const {
+    const int lr = lane & 15;
+    if (hw == 0 && lr < j.rows) wk_store8(hidden(l) + (size_t)lr * F + place * 16 + (lane >> 4) * 4, u32x2{EMPTY_WORD, EMPTY_WORD});
+  }
+  // What place writes, both buffers of everything: ahead of the first hand-over, nothing is assumed of what they hold
+  __device__ __forceinline__ void empty_all(int lane) const {
+    for (int l = 0; l < 2; ++l) { empty_normed(WK_QKV, l, lane); empty_normed(WK_UP, l, lane); }
+#pragma unroll 1
+    for (int place = j.place; place < 256; place += j.members)
+#pragma unroll 1
+      for (int l = 0; l < 2; ++l) {
+        empty_tile(between(1, l), WkMember::tile(WK_O, place), lane); empty_tile(between(2, l), WkMember::tile(WK_CO, place), lane);
+        empty_tile(between(3, l), WkMember::tile(WK_DOWN, place), lane); empty_hidden(l, place, lane);
+        rows_of_head(heads(WK_SELF, l), j.item(WK_SELF, place), EMPTY_WORD, lane); rows_of_head(heads(WK_CROSS, l), j.item(WK_CROSS, place), EMPTY_WORD, lane);
+      }
+  }
+
+  template <int OP, int K>
+  __device__ __forceinline__ void product(int l) {
+    constexpr bool LN = OP == WK_QKV || OP == WK_UP, BIAS = OP == WK_UP || OP == WK_DOWN, RES = !LN;
     const LayersP& p = lk_args();
     const int lane = lk_lane(), lr = lane & 15, lq = lane >> 4;
-    ++op;
+    if constexpr (OP == WK_QKV) ++op;
     bool staged = false;
 #pragma unroll 1
     for (int place = j.place; place < 256; place += j.members) {
@@ -191,22 +293,37 @@ struct WkHelper {
       if (tile < 0) continue;
       const int n = tile * 16 + lq * 4;
       f32x4 bs, res;
-      if constexpr (BIAS) if (hw == 0) bs = *(const f32x4*)((const float*)((const char*)(p.*biasp) + l * p.stride) + n);
+      if constexpr (BIAS) if (hw == 0) bs = *(const f32x4*)((const float*)((const char*)(OP == WK_UP ? p.b1 : p.b2) + l * p.stride) + n);
+      float* const in = stream(l, OP == WK_QKV || OP == WK_O ? 0 : (OP == WK_CO ? 1 : 2));        // LN: the rows; otherwise what the result is added to
+      const rsrc_t rr = rsrc_of(in, (unsigned)j.rows * D * 4);
       f32x4 g[4], b[4];
+      if constexpr (LN) if (!staged) load_norm((const float*)((const char*)(OP == WK_QKV ? p.ln1 : p.ln3) + l * p.stride), g, b, lane);
+      if (!staged && OP != WK_QKV && OP != WK_DOWN && l == 0) wait(1);         // (everybody has emptied what it writes)
+      if constexpr (RES) if (hw == 0) res = __builtin_bit_cast(f32x4, lk_load16(rr, (lr * D + n) * 4));
       if (!staged) {
-        if constexpr (LN) load_norm((const float*)((const char*)(p.*lnp) + l * p.stride), g, b, lane);
-        wait(op - 1, heads);
-      }
-      // (behind the wait: another member wrote the tile, O's, CO's or DOWN's)
-      if constexpr (OP == WK_O || OP == WK_CO || OP == WK_DOWN) if (hw == 0) res = __builtin_bit_cast(f32x4, lk_load16(rsrc_of(p.x, (unsigned)j.rows * D * 4), (lr * D + n) * 4));
-      if (!staged) {
-        if constexpr (LN) wk_norm(p.x, j.rows, g, b, p.eps, xs, hw, lane);
-        else if constexpr (OP == WK_DOWN) lk_copy<F>(p.ffh, j.rows, xs, hw, lane);
-        else lk_copy<D>(p.attn, j.rows, xs, hw, lane);
-        staged = true;
+        if constexpr (LN) stage_norm(OP, l, in, g, b, lane);
+        else if constexpr (OP == WK_DOWN) lk_copy<F>(hidden(l), j.rows, xs, hw, lane, poll());
+        else lk_copy<D>(heads(OP == WK_O ? WK_SELF : WK_CROSS, l), j.rows, xs, hw, lane, poll());
       }
       lk_barrier();                              // the input is staged, the partial sums of the place before are read
+      if constexpr (OP == WK_QKV) {
+        if (l > 0) empty_normed(WK_UP, l - 1, lane);
+        if (l > 0) empty_tile(between(2, l - 1), WkMember::tile(WK_CO, place), lane);          // (x3 of the layer before is there: DOWN and UP have read x2)
+        else if (j.full) { empty_all(lane); lk_stores_done(); }
+      }
+      if constexpr (OP == WK_UP) {               // (x2 is there: CO has read x1 and the cross-attention's results, O the self-attention's and x3)
+        empty_normed(WK_QKV, l, lane);
+        empty_tile(between(1, l), WkMember::tile(WK_O, place), lane);
+        rows_of_head(heads(WK_SELF, l), j.item(WK_SELF, place), EMPTY_WORD, lane); rows_of_head(heads(WK_CROSS, l), j.item(WK_CROSS, place), EMPTY_WORD, lane);
+        if (l > 0) { empty_tile(between(3, l - 1), WkMember::tile(WK_DOWN, place), lane); empty_hidden(l - 1, place, lane); }
+      }
+      // (the cross-attention has read all of x1, but this wave may have asked too early; x2 and x3 it has read itself)
+      if constexpr (OP == WK_CO) if (hw == 0) poll()([&] {
+        if (__any(lk_top(0, __builtin_bit_cast(u32x4, res)) == EMPTY_WORD)) res = __builtin_bit_cast(f32x4, lk_load16(rr, (lr * D + n) * 4));
+        return lk_top(0, __builtin_bit_cast(u32x4, res));
+      });
       lk_barrier();                              // the partial sums are there
+      staged = true;
       if (hw > 0) continue;
       f32x4 v = partial_sums(1, 0, lane);
       if (lr >= j.rows) continue;
@@ -216,14 +333,17 @@ struct WkHelper {
         v += bs;
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.f);
-        wk_store8(p.ffh + (size_t)lr * F + n, u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])});
+        wk_store8(hidden(l) + (size_t)lr * F + n, full_words(u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])}));
       } else {
         if constexpr (BIAS) v += bs;
         v += res;
-        wk_store16(p.x + (size_t)lr * D + n, v);
+        wk_store16(stream(l, OP == WK_O ? 1 : (OP == WK_CO ? 2 : 3)) + (size_t)lr * D + n, __builtin_bit_cast(f32x4, full_words(v)));
       }
     }
-    done<1>(staged, from, count, OP != WK_QKV, OP == WK_DOWN ? LK_PLACES - 1 : 0);
+    if constexpr (OP == WK_QKV) {
+      if (l == 0) done<1>(true, 0, 32, true);      // (that everything is empty: to all)
+      else done<1>(staged, 8, 24, false);
+    }
   }
 
   __device__ __forceinline__ static AttnP attn_args(bool self) {
@@ -236,8 +356,18 @@ struct WkHelper {
   }
   __device__ __forceinline__ static int sequence(int slot) { const LayersP& p = lk_args(); return p.seq ? lk_const(p.seq, slot) : slot; }
 
-  template <int G, int NF>
-  __device__ __forceinline__ void self_item(int l, int item, bool first_item) {
+  // Up to 128 keys: a group of 32 per wave
+  __device__ __forceinline__ static bool few(int slot) {
+    const LayersP& p = lk_args();
+    const int lim = lk_const(p.base, slot);
+    return ((lim + p.R + 31) >> 5) - (attn_first_key(attn_args(true), lim) >> 5) <= 4;
+  }
+  template <int NF, int STORE>
+  __device__ __forceinline__ void self_item(int l, int item, unsigned after, bf16_t* out, bool first_item) {
+    if (few(item >> 4)) self_groups<1, NF, STORE>(l, item, after, out, first_item); else self_groups<2, NF, STORE>(l, item, after, out, first_item);
+  }
+  template <int G, int NF, int STORE>
+  __device__ __forceinline__ void self_groups(int l, int item, unsigned after, bf16_t* out, bool first_item) {
     const LayersP& p = lk_args();
     const int lane = lk_lane(), lr = lane & 15, lq = lane >> 4;
     const int h = item & 15, slot = item >> 4, s = sequence(slot);
@@ -247,7 +377,6 @@ struct WkHelper {
     const size_t at = l * p.self_layer + ((size_t)(s < 0 ? 0 : s) * H + h) * p.self_groups * KV_GROUP;
     const rsrc_t kr = rsrc_of(p.selfK + at, (unsigned)groups * (KV_GROUP * 2)), vr = rsrc_of(p.selfV + at, (unsigned)groups * (KV_GROUP * 2));
     const rsrc_t qr = rsrc_of(p.q + (size_t)slot * p.R * (2 * D), (unsigned)p.R * (4 * D));
-    bf16_t* out = p.attn;
     if (!first_item) {
       lk_barrier();                              // the results of the item before are out of LDS
     } else if (j.full) {
@@ -255,13 +384,17 @@ struct WkHelper {
       unsigned t[G];
 #pragma unroll
       for (int g = 0; g < G; ++g) t[g] = __builtin_amdgcn_raw_buffer_load_b32(lane < 32 ? kr : vr, (lane & 31) * 128, (first + hw + g * 4) * (KV_GROUP * 2), 16);
-      lk_wait<NF>(area() + WK_LOCAL, op - 1, 8, 24, lane, broken, p.error);
+      lk_wait<NF>(area() + WK_LOCAL, after, 8, 24, lane, broken, p.error);
 #pragma unroll
       for (int g = 0; g < G; ++g) asm volatile("" ::"v"(t[g]));
     } else {
-      wait(op - 1);
+      wait(after);
     }
-    if (s < 0) { lk_barrier(); return; }         // (as the attention's own)
+    if (s < 0) {                                 // (rows of nobody; a barrier as the attention's own)
+      if (STORE == ATTN_THROUGH_WORDS) rows_of_head(out, item, 0, lane);
+      lk_barrier();
+      return;
+    }
     const unsigned off = lr * (4 * D) + (h * 64 + 8 * lq) * 2;
     bf16x8 qhi[2], qlo[2];
 #pragma unroll
@@ -272,30 +405,20 @@ struct WkHelper {
     u32x4 kf[G][4], vf[G][4];
     attn_load_kv<false, G>(kr, vr, first + hw, 4, lane, kf, vf);
     __builtin_amdgcn_sched_barrier(0);
-    attention_mfma_core<false, true, G == 2 ? -1 : 0, G, ATTN_THROUGH>(a, sm, h, slot, 0, 0, 0, p.R, H, 1, hw * 64 + lane, 4, first, 4 * G, kr, vr, kf, vf, qhi, qlo, lim, out);
-  }
-  __device__ __forceinline__ void heads_done(int which, bool mine) {
-    if (!heads_tell()) { done<4>(mine, 24 + (which == WK_CROSS ? j.cross_first() : 0), 2 * j.slots, true); return; }
-    if (!mine) return;
-    lk_stores_done();
-    lk_barrier();
-    const int lane = lk_lane(), item = j.item(which, j.place);
-    if (hw == 0 && lane < WK_XCDS) wk_store4(lk_args().sync + lane * WK_AREA + WK_HEADS + j.xcd * 32 + (item >> 4) * 2 + (item & 1), op);
+    attention_mfma_core<false, true, G == 2 ? -1 : 0, G, STORE>(a, sm, h, slot, 0, 0, 0, p.R, H, 1, hw * 64 + lane, 4, first, 4 * G, kr, vr, kf, vf, qhi, qlo, lim, out);
   }
   __device__ __forceinline__ void self_attention(int l) {
-    ++op;
-    const bool few = lk_args().few;
     bool mine = false;
 #pragma unroll 1
     for (int place = j.place; place < 256; place += j.members) {
       const int item = j.item(WK_SELF, place);
       if (item < 0) continue;
-      if (few) self_item<1, 1>(l, item, !mine); else self_item<2, 1>(l, item, !mine);
+      self_item<1, ATTN_THROUGH_WORDS>(l, item, op, heads(WK_SELF, l), !mine);
       mine = true;
     }
-    heads_done(WK_SELF, mine);
   }
-  __device__ __forceinline__ void cross_item(int l, int item, const float* x, bool first_item) {
+  template <int STORE>
+  __device__ __forceinline__ void cross_item(int l, int item, const float* x, unsigned after, LkPoll poll, bf16_t* out, bool first_item) {
     const LayersP& p = lk_args();
     const int lane = lk_lane(), lr = lane & 15, lq = lane >> 4;
     const AttnP a = attn_args(false);
@@ -307,9 +430,9 @@ struct WkHelper {
     load_norm((const float*)((const char*)p.ln2 + l * p.stride), g, b, lane);
     attn_load_kv<false, 1>(kr, vr, hw, 4, lane, kf, vf);
     const int lim = lk_const(p.src_len, slot);
-    if (first_item) wait(op - 1);
+    if (first_item) wait(after);
     else lk_barrier();                         // the results of the item before are out of LDS
-    wk_norm(x + (size_t)slot * p.R * D, p.R, g, b, p.eps, xs, hw, lane);
+    wk_norm(x + (size_t)slot * p.R * D, p.R, g, b, p.eps, xs, hw, lane, poll);
     lk_barrier();
     lk_barrier();
     {
@@ -326,20 +449,18 @@ struct WkHelper {
       qhi[s2] = __builtin_bit_cast(bf16x8, *(const u32x4*)&q_s[(s2 * 64 + lane) * 2]);
       qlo[s2] = __builtin_bit_cast(bf16x8, *(const u32x4*)&q_s[256 + (s2 * 64 + lane) * 2]);
     }
-    if (s < 0) { lk_barrier(); return; }     // (as the attention's own)
-    attention_mfma_core<false, false, 0, 1, ATTN_THROUGH>(a, sm, h, slot, 0, 0, 0, p.R, H, 1, hw * 64 + lane, 4, 0, 4, kr, vr, kf, vf, qhi, qlo, lim, p.attn);
+    if (s < 0) { if (STORE == ATTN_THROUGH_WORDS) rows_of_head(out, item, 0, lane); lk_barrier(); return; }     // (as the attention's own)
+    attention_mfma_core<false, false, 0, 1, STORE>(a, sm, h, slot, 0, 0, 0, p.R, H, 1, hw * 64 + lane, 4, 0, 4, kr, vr, kf, vf, qhi, qlo, lim, out);
   }
   __device__ __forceinline__ void cross_attention(int l) {
-    ++op;
     bool mine = false;
 #pragma unroll 1
     for (int place = j.place; place < 256; place += j.members) {
       const int item = j.item(WK_CROSS, place);
       if (item < 0) continue;
-      cross_item(l, item, lk_args().x, !mine);
+      cross_item<ATTN_THROUGH_WORDS>(l, item, stream(l, 1), l == 0, poll(), heads(WK_CROSS, l), !mine);
       mine = true;
     }
-    heads_done(WK_CROSS, mine);
   }
 
   __device__ __forceinline__ void run() {
@@ -350,15 +471,19 @@ struct WkHelper {
       sb = p.seq ? p.seq[slot] : slot;
       key = p.base[slot] + m - slot * p.R;
     }
+    if (!j.full || j.rank < 8) {                 // (the others: in the first operator, which these have no part in)
+      empty_all(lk_lane());
+      lk_stores_done();
+    }
 #pragma unroll 1
     for (int l = 0; l < layers; ++l) {
-      product<WK_QKV, D, true, false>(l, &LayersP::ln1, nullptr, 8, 24);
+      product<WK_QKV, D>(l);
       self_attention(l);
-      product<WK_O, D, false, false>(l, nullptr, nullptr, 8, 8, 16 * j.slots);
+      product<WK_O, D>(l);
       cross_attention(l);
-      product<WK_CO, D, false, false>(l, nullptr, nullptr, 16, 8, 16 * j.slots);
-      product<WK_UP, D, true, true>(l, &LayersP::ln3, &LayersP::b1, 0, 32);
-      product<WK_DOWN, F, false, true>(l, nullptr, &LayersP::b2, 0, 8);
+      product<WK_CO, D>(l);
+      product<WK_UP, D>(l);
+      product<WK_DOWN, F>(l);
     }
   }
 };
@@ -412,7 +537,6 @@ struct WkCompute {
         mine = 1;
         lk_barrier();
       }
-      if (self && j.slots <= 2) lk_barrier();      // (heads_done)
       product<WK_O>(one(), &LayersP::wo, l);
       if (o || self) {
         __builtin_amdgcn_s_sleep(WK_HOLD);
@@ -433,7 +557,6 @@ struct WkCompute {
         lk_barrier();
         lk_barrier();
       }
-      if (cross && j.slots <= 2) lk_barrier();
       product<WK_CO>(one(), &LayersP::co, l);
       product<WK_UP>(a1, &LayersP::w1, l);
       if (qkv) { __builtin_amdgcn_s_sleep(WK_HOLD); load<WK_GAP>(a1, &LayersP::w1, next, j.place); }
