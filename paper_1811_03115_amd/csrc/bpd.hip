@@ -69,7 +69,8 @@ struct bpd_ctx {
   // workgroups per XCD that layers_kernel and wide_layers_kernel wait for (for tests, BPD_LAYERS_GROUP at creation: fewer; 33: they wait in vain; 64 n
   // added: the second one is left to n XCDs).  0: none of the kernels of all layers is used
   int layers_group = LK_PLACES;
-  bool layers_ran = false;             // layers_kernel has been launched and the LayerNorm behind it has not (that LayerNorm clears layers_sync)
+  bool layers_ran = false;             // a kernel of all layers has been launched and the kernel behind it has not (that one clears layers_sync)
+  bool layers_normed = false;          // ... and has left the normalised rows in hn and h
   bool weights_exceed_llc = false;     // decoder-side weights read per step > 192 MB (the Infinity Cache holds 256 MB)
   const int* cur_imposed = nullptr; int cur_imposed_stride = 0, cur_imposed_step = 0;   // of the step being run
   // pinned host memory, read and written by kernels directly: the words that say what has happened, the arguments of
@@ -318,7 +319,7 @@ void prefetch_epilogue(Epi& e, const GemmP& p, int mt, int nt, const float* zero
 
 template <bool ARGMAX>
 bool dispatch_ldsx(const GemmP& p, const Epi& e_in, unsigned long long* keys, float* logits, int groups, hipStream_t s,
-                   const LiveP& live, const float* zeros = nullptr) {
+                   const LiveP& live, const float* zeros = nullptr, const LnP& ln = LnP{}) {
   Epi e = e_in;
   int mt, nt;
   const int kslice = p.ksplit > 1 ? p.K / p.ksplit : p.K;
@@ -336,7 +337,7 @@ bool dispatch_ldsx(const GemmP& p, const Epi& e_in, unsigned long long* keys, fl
 #undef BPD_CASE
     }
   }
-#define BPD_CASE(MT_, NT_, KC_) if (mt == MT_ && nt == NT_) { launch_ldsx<MT_, NT_, KC_, ARGMAX>(p, e, keys, logits, groups, s, live); return false; }
+#define BPD_CASE(MT_, NT_, KC_) if (mt == MT_ && nt == NT_) { launch_ldsx<MT_, NT_, KC_, ARGMAX>(p, e, keys, logits, groups, s, live, ln); return false; }
   BPD_CASE(3, 1, 256) BPD_CASE(2, 1, 256) BPD_CASE(1, 1, 256)
   BPD_CASE(8, 2, 128) BPD_CASE(7, 2, 128) BPD_CASE(5, 2, 128) BPD_CASE(4, 2, 128) BPD_CASE(3, 2, 128) BPD_CASE(2, 2, 128) BPD_CASE(1, 2, 128)
   BPD_CASE(8, 4, 64) BPD_CASE(7, 4, 64) BPD_CASE(5, 4, 64) BPD_CASE(4, 4, 64) BPD_CASE(3, 4, 64) BPD_CASE(2, 4, 64) BPD_CASE(1, 4, 64)
@@ -377,6 +378,14 @@ int residual_k_slices(const bpd_ctx* ctx, const GemmP& p) {
   return residual_k_slices_of(ctx->cfg.d_model, ctx->lay.n_kpart, p.M, p.N, p.K);
 }
 
+// What the next kernel clears: the words that a kernel of all layers has counted in
+uint4* clear_behind_layers(bpd_ctx* ctx, int& n) {
+  if (!ctx->layers_ran) return nullptr;
+  ctx->layers_ran = false;
+  n = LK_WORDS / 4;
+  return (uint4*)ctx->lay.layers_sync;
+}
+
 // Y = epilogue(X W).  bf16 mode: M <= 16 -> skinny kernel; otherwise the LDS-staged kernel
 // (K % 64 == 0) or the plain MFMA kernel.  fp32 mode: one thread per output.
 // Returns true if the kernel left the per-tile LayerNorm statistics of its output in e.stats_out in the layout of the
@@ -410,7 +419,8 @@ bool gemm(bpd_ctx* ctx, const GemmP& p, const Epi& e_in, int groups = 1) {
         return false;
       }
     }
-    return dispatch_ldsx<false>(p, e, nullptr, nullptr, groups, s, live_rows(ctx, p.M), ctx->lay.zeros);
+    if (!e.stats_out) none.clear = clear_behind_layers(ctx, none.nclear);
+    return dispatch_ldsx<false>(p, e, nullptr, nullptr, groups, s, live_rows(ctx, p.M), ctx->lay.zeros, none);
   } else {
     e.stats_out = nullptr;
     if (p.M > 64) launch_gemm_bf16<8, 1, 4>(p, e, groups, s);
@@ -532,9 +542,9 @@ Epi kv_split(const bpd_ctx* ctx, float* Qf, void* Ka, void* Va, int chunk0, int 
 template <int D>
 void launch_ln_row(bpd_ctx* ctx, float* x, LnW w, int M, void* ya, float* yf, int nsl, const float* bias) {
 #define BPD_LN(NSL) hipLaunchKernelGGL((ln_row_kernel<D, NSL>), dim3(M), dim3(ln_row_threads(D)), 0, ctx->stream, x, w.g, w.b, M, ctx->cfg.ln_eps, \
-                                       (bf16_t*)ya, yf, (const float*)ctx->lay.kpart, bias, clear, clear ? LK_WORDS / 4 : 0)
-  u32x4* clear = ctx->layers_ran ? (u32x4*)ctx->lay.layers_sync : nullptr;
-  ctx->layers_ran = false;
+                                       (bf16_t*)ya, yf, (const float*)ctx->lay.kpart, bias, clear, nclear)
+  int nclear = 0;
+  u32x4* clear = (u32x4*)clear_behind_layers(ctx, nclear);
   switch (nsl) {
     case 0: BPD_LN(0); break;
     case 2: BPD_LN(2); break;
@@ -791,7 +801,8 @@ void launch_layers(bpd_ctx* ctx, int R, int way) {
   p.eps = c.ln_eps; p.scale = 1.0f / sqrtf(64.f); p.local_q = ctx->local_q; p.local_m = ctx->local_m;
   p.group = way == LAYERS_JOBS ? ctx->layers_group & 63 : ctx->layers_group;
   p.sync = L.layers_sync; p.error = L.stats + 31;
-  ctx->layers_ran = true;
+  if (ctx->layers_ran) fill_i32(ctx, (int*)L.layers_sync, LK_WORDS, 0);         // (nobody came between)
+  ctx->layers_ran = true; ctx->layers_normed = false;
   if (way == LAYERS_WIDE) {
     p.jobs = p.per_job = p.split = 0;
     p.xn = (bf16_t*)L.layers_xn; p.x1 = L.layers_x1; p.attn = (bf16_t*)L.layers_attn2; p.ffh = (bf16_t*)L.layers_ffh;
@@ -811,6 +822,8 @@ void launch_layers(bpd_ctx* ctx, int R, int way) {
     return;
   }
   p.x1 = L.layers_x1; p.x3 = L.layers_x3; p.attn2 = (bf16_t*)L.layers_attn2;
+  // One row tile is normalised by the GEMM behind; more rows here: 1.0 us instead of 4.7 in a kernel of its own (24 and 80 rows)
+  if (ctx->Bs * R > 16) { p.lnf = L.dec_lnf.g; p.h = L.h; p.hn = (bf16_t*)L.hn; ctx->layers_normed = true; }
   const bool nt = (size_t)2 * c.n_dec_layers * ctx->Bs * slots * d * 2 > ((size_t)128 << 20);       // (as in attention())
   if (nt) launch_layers_kernel<true>(ctx, p); else launch_layers_kernel<false>(ctx, p);
 }
@@ -851,7 +864,7 @@ int heads_two_phase(bpd_ctx* ctx, int k) {
   const size_t as = act_size(c);
   const int* seq = ctx->seq;
   // phase 1: head 1 (the base model's p_1) at every block row
-  layernorm(ctx, L.x, L.dec_lnf, M, L.hn, L.h);
+  if (!(ctx->layers_ran && ctx->layers_normed)) layernorm(ctx, L.x, L.dec_lnf, M, L.hn, L.h);
   gemm(ctx, gp(L.hn, d, L.hw1, c.k_max * F, M, F, d), plain(L.hb1, 1, nullptr, 0, nullptr, 0, L.H, F));
   gemm(ctx, gp(L.H, F, L.hw2, d, M, d, F), plain(L.hb2, 0, L.h, d, nullptr, 0, L.O, d));
   unsigned long long* keys2 = L.keys_h1 + M;           // this step's second-phase keys follow its M head-1 keys: one fill clears both
@@ -1084,11 +1097,13 @@ int forward(bpd_ctx* ctx, int R, int k, int zero_input, float* logits) {
   {
     PhaseTimer t(ctx, BPD_PHASE_HEAD_HIDDEN);
     // behind the layers kernels one row tile is normalised by the GEMM that reads it
-    if (ctx->layers_ran && M <= 16 && !ctx->pend_slices) {
+    if (ctx->layers_ran && ctx->layers_normed) {
+      gemm(ctx, gp(L.hn, d, L.hw1, c.k_max * F, M, k * F, d), plain(L.hb1, 1, nullptr, 0, nullptr, 0, L.H, k * F));
+    } else if (ctx->layers_ran && M <= 16 && !ctx->pend_slices) {
       GemmP p = gp(nullptr, d, L.hw1, c.k_max * F, M, k * F, d);
-      LnP ln{L.x, L.dec_lnf.g, L.dec_lnf.b, nullptr, c.ln_eps, L.h, (uint4*)L.layers_sync, LK_WORDS / 4};
+      LnP ln{L.x, L.dec_lnf.g, L.dec_lnf.b, nullptr, c.ln_eps, L.h};
+      ln.clear = clear_behind_layers(ctx, ln.nclear);
       const Epi e = plain(L.hb1, 1, nullptr, 0, nullptr, 0, L.H, k * F);
-      ctx->layers_ran = false;
       if (p.N / 16 >= 2048) launch_skinny<2, 2, false>(ctx, p, e, ln, nullptr, nullptr, 1);
       else launch_skinny<1, 2, false>(ctx, p, e, ln, nullptr, nullptr, 1);
     } else if (lean) {

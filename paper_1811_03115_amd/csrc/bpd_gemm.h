@@ -156,7 +156,7 @@ struct LnP {
   const float* stats;   // partial sums written by the producer of x
   float eps;
   float* yf;            // XLN = 2: the normalised rows in fp32, for a later kernel
-  uint4* clear;         // XLN = 2: as ln_row_kernel's (nclear pieces of 16 bytes; null: none)
+  uint4* clear;         // XLN = 2, and gemm_ldsx_kernel without LayerNorm: as ln_row_kernel's (nclear pieces of 16 bytes; null: none)
   int nclear;
 };
 
@@ -886,6 +886,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
   // launches live for a few microseconds whatever their rows, would not get back.  (Rows past the end in the last block
   // are computed for nothing, like all dead rows of the small tiles.)
   if (MT * NT >= 8 && m0 >= rows_in_use(live, p.M)) return;
+  if constexpr (!ARGMAX && !XLN && !STATS && !ROWAFF) {
+    if (ln.clear && (blockIdx.x | blockIdx.y | blockIdx.z) == 0)
+      for (int i = tid; i < ln.nclear; i += 256) ln.clear[i] = make_uint4(0, 0, 0, 0);
+  }
   const int M = p.M;
   const int nt0 = (bx * 4 + wave) * NT;
   const int lr = lane & 15, lq = lane >> 4;

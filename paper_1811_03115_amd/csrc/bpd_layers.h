@@ -50,6 +50,7 @@ struct LayersP {
   int split;                                     // workgroups per (head, slot) of the self-attention
   float *x, *part;
   bf16_t *q, *attn, *ffh, *selfK, *selfV;         // q: a row is 2 d wide (bf16 hi and lo parts)
+  const float* lnf; float* h; bf16_t* hn;         // layers_kernel: the LayerNorm behind the layers (gains, then biases) and where it goes; hn null: x is stored as it is
   float *x1, *x3;                                // layers_kernel: the residual stream behind the two attentions (x1, then x2) and between layers
   bf16_t *attn2;                                  // ... and the cross-attention's results
   const bf16_t *crossK, *crossV;
@@ -369,7 +370,7 @@ struct LkHelper {
   __device__ __forceinline__ static float* stream(int l, int stage) {
     const LayersP& p = lk_args();
     if (stage == 0) return l == 0 ? p.x : p.x3;
-    if (stage == 3) return l + 1 == p.n_layers ? p.x : p.x3;
+    if (stage == 3) return l + 1 == p.n_layers && !p.hn ? p.x : p.x3;
     return stage == 1 ? p.x1 : p.x1 + LK_JOBS * 16 * 512;
   }
   // What this member writes is emptied when everybody is known to have read it: by the lanes that wrote it, at the latest an operator ahead of its own
@@ -598,6 +599,39 @@ struct LkHelper {
     }
   }
 
+  // The LayerNorm behind the last layer, a row per member
+  __device__ __forceinline__ void final_norm() {
+    constexpr int D = 512;
+    const LayersP& p = lk_args();
+    if (hw != 3 || !p.hn) return;
+    const int lane = lk_lane();
+    f32x4 g[2], b[2], v[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) { g[h] = *(const f32x4*)(p.lnf + lane * 8 + h * 4); b[h] = *(const f32x4*)(p.lnf + D + lane * 8 + h * 4); }
+#pragma unroll 1
+    for (int m = j.rank; m < j.rows; m += j.members) {
+      const size_t row = (size_t)(j.row0 + m) * D;
+      const rsrc_t xr = rsrc_of(p.x3 + row, D * 4);
+      poll()([&] {
+        v[0] = __builtin_bit_cast(f32x4, lk_load16(xr, lane * 32)); v[1] = __builtin_bit_cast(f32x4, lk_load16(xr, lane * 32 + 16));
+        return lk_top(lk_top(0, __builtin_bit_cast(u32x4, v[0])), __builtin_bit_cast(u32x4, v[1]));
+      });
+      const f32x4 s = v[0] + v[1];
+      const float mu = wave_sum((s[0] + s[1]) + (s[2] + s[3])) * (1.f / D);
+      v[0] -= mu; v[1] -= mu;
+      f32x4 q = v[0] * v[0];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) q[r] = fmaf(v[1][r], v[1][r], q[r]);
+      const float rs = inv_sqrt(fmaf(wave_sum((q[0] + q[1]) + (q[2] + q[3])), 1.f / D, p.eps));
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[h][r] = fmaf(v[h][r] * rs, g[h][r], b[h][r]);
+      *(f32x4*)(p.h + row + lane * 8) = v[0]; *(f32x4*)(p.h + row + lane * 8 + 4) = v[1];
+      *(u32x4*)(p.hn + row + lane * 8) = u32x4{cvt_pk_bf16(v[0][0], v[0][1]), cvt_pk_bf16(v[0][2], v[0][3]), cvt_pk_bf16(v[1][0], v[1][1]), cvt_pk_bf16(v[1][2], v[1][3])};
+    }
+  }
+
   __device__ __forceinline__ void job() {
     const int layers = lk_args().n_layers;
     {
@@ -618,6 +652,7 @@ struct LkHelper {
       product<UP, F / 512, 512>(l);
       product<DOWN, 1, F>(l);
     }
+    final_norm();
   }
 };
 
