@@ -610,7 +610,7 @@ bool attention_qproj_ok(const bpd_ctx* ctx, int B, int R) {
 }
 
 void attention(bpd_ctx* ctx, const float* Q, const void* Kc, const void* Vc, void* out, int cap,
-               int B, int R, const int* limit, int causal, const int* seq, const QProjP* qproj = nullptr) {
+               int B, int R, const int* limit, int causal, const int* seq, const QProjP* qproj = nullptr, const int* row0 = nullptr) {
   const long kv_seq_stride = (long)cap * ctx->cfg.d_model;
   const int capg = (cap + 31) / 32;
   const bpd_config& c = ctx->cfg;
@@ -649,6 +649,12 @@ void attention(bpd_ctx* ctx, const float* Q, const void* Kc, const void* Vc, voi
         return;
       }
       const bool nt = causal && kv_bytes > ((size_t)128 << 20);
+      if (row0) {                                // (packed: packed_source_rows())
+        p.row0 = row0;
+        if (few) hipLaunchKernelGGL(attention_mfma_packed_kernel<0>, grid, dim3(64 * 4), 0, ctx->stream, p, qp_);
+        else hipLaunchKernelGGL(attention_mfma_packed_kernel<-1>, grid, dim3(64 * 4), 0, ctx->stream, p, qp_);
+        return;
+      }
       if (two) {
         if (nt && limf) BPD_ATTN(true, true, -1) else if (nt) BPD_ATTN(true, false, -1) else if (limf) BPD_ATTN(false, true, -1) else BPD_ATTN(false, false, -1)
       } else {
@@ -1237,12 +1243,17 @@ void small_decode(bpd_ctx* ctx, int k, int hgroup, int steps, const int* imposed
   else small_launch<small_decode_kernel<4>>(ctx, p, n);
 }
 
-int encoder(bpd_ctx* ctx) {
+// rows: of packed sources (packed_source_rows()), 0: B x S
+int encoder(bpd_ctx* ctx, int rows) {
   const bpd_config& c = ctx->cfg;
   Layout& L = ctx->lay;
-  const int B = ctx->B, S = ctx->S, d = c.d_model, F = c.d_ff, M = B * S;
+  const int B = ctx->B, S = ctx->S, d = c.d_model, F = c.d_ff, M = rows ? rows : B * S;
   const size_t as = act_size(c);
-  embed(ctx, L.src_ids, S, nullptr, S, M, L.pos_src, L.xe, 0);
+  // packed rows are slots of one row each, at their positions
+  const int R = rows ? 1 : S;
+  const int *pos = rows ? L.src_pos : nullptr, *seq = rows ? L.src_seq : nullptr, *row0 = rows ? L.src_row0 : nullptr;
+  if (rows) embed(ctx, L.src_packed, 1, pos, 1, M, L.pos_src, L.xe, 0);
+  else embed(ctx, L.src_ids, S, nullptr, S, M, L.pos_src, L.xe, 0);
   // 17 .. 128 source rows of a width that bpd_row_gemm.h is not built for: the residual GEMMs leave LayerNorm statistics for the LayerNorm-fused GEMM that follows
   const bool lean = lean_encoder_ok(c, M), bigs = !lean && c.dtype == BPD_BF16 && M > 16 && M <= LDSX_LN_M_MAX && d % 64 == 0 && d <= 1024;
   auto residual = [&](const float* bias) {
@@ -1253,16 +1264,16 @@ int encoder(bpd_ctx* ctx) {
   bool xs = false;      // L.stats_big describes the current L.xe
   for (int l = 0; l < c.n_enc_layers; ++l) {
     EncL& w = L.enc[l];
-    const Epi kv = kv_split(ctx, L.qe, L.ke, L.ve, 0, S, S, nullptr, nullptr);
+    const Epi kv = kv_split(ctx, L.qe, L.ke, L.ve, 0, R, S, pos, seq);
     if (lean) {
       lean_ln_gemm<RG_QKV>(ctx, L.xe, w.ln1, L.xen, rg_kv(ctx, nullptr, w.wqkv, M, 3 * d, kv));
-      attention(ctx, L.qe, L.ke, L.ve, L.attne, S, B, S, L.src_len, 0, nullptr);
+      attention(ctx, L.qe, L.ke, L.ve, L.attne, S, B, S, L.src_len, 0, nullptr, nullptr, row0);
       lean_residual(ctx, L.attne, d, w.wo, nullptr, M, L.xe);
       lean_ffn(ctx, L.xe, w.ln2, L.xen, w.w1, w.b1, L.ffhe, w.w2, w.b2, M);
       continue;
     }
     gemm_ln(ctx, L.xe, w.ln1, L.xen, nullptr, gp(L.xen, d, w.wqkv, 3 * d, M, 3 * d, d), kv, false, xs);
-    attention(ctx, L.qe, L.ke, L.ve, L.attne, S, B, S, L.src_len, 0, nullptr);
+    attention(ctx, L.qe, L.ke, L.ve, L.attne, S, B, S, L.src_len, 0, nullptr, nullptr, row0);
     xs = gemm(ctx, gp(L.attne, d, w.wo, d, M, d, d), residual(nullptr));
     gemm_ln(ctx, L.xe, w.ln2, L.xen, nullptr, gp(L.xen, d, w.w1, F, M, F, d), plain(w.b1, 1, nullptr, 0, nullptr, 0, L.ffhe, F), false, xs);
     xs = gemm(ctx, gp(L.ffhe, F, w.w2, d, M, d, F), residual(w.b2));
@@ -1273,7 +1284,7 @@ int encoder(bpd_ctx* ctx) {
   const long wz = c.n_dec_layers > 1 ? ((const char*)L.dec[1].ckv - (const char*)L.dec[0].ckv) / (long)as : 0;      // (every layer's arrays are laid out alike)
   const bool together = lean || (c.dtype == BPD_BF16 && d % 64 == 0 && M > 16);
   for (int l = 0; l < (together ? 1 : c.n_dec_layers); ++l) {
-    Epi kv = kv_split(ctx, nullptr, (char*)L.crossK + src_layer * l * as, (char*)L.crossV + src_layer * l * as, 1, S, c.max_src_len, nullptr, nullptr);
+    Epi kv = kv_split(ctx, nullptr, (char*)L.crossK + src_layer * l * as, (char*)L.crossV + src_layer * l * as, 1, R, c.max_src_len, pos, seq);
     if (lean) {
       RowGemmP p = rg_kv(ctx, L.mem, L.dec[l].ckv, M, 2 * d, kv);
       p.wz = wz; p.kvz = (long)src_layer;
@@ -1524,7 +1535,7 @@ int bpd_create(const bpd_config* cfg, void* workspace, size_t workspace_bytes, v
   (void)hipMemsetAsync(ctx->lay.stats_ln, 0, 64 * 16 * 2 * 4, ctx->stream);
   {
     const size_t B = cfg->max_batch, k = cfg->k_max, S = cfg->max_src_len, T = cfg->max_out_len;
-    const size_t n_in = B * S + 2 * B, n_sched = B * T;
+    const size_t n_in = B * S + 3 * B, n_sched = B * T;
     ctx->n_stage_out = std::min(FETCH_KERNEL_MAX, std::max(B * T + B, B * k * (k + 1) + 2 * B) + 64);      // (64: the statistics)
     const size_t ints = 4 * B + 16 + n_in + n_sched + ctx->n_stage_out;
     if (hipHostMalloc((void**)&ctx->report, ints * sizeof(int), hipHostMallocDefault) != hipSuccess) {
@@ -1654,7 +1665,7 @@ int bpd_encode(bpd_ctx* ctx, const int32_t* src_ids, const int32_t* src_len, con
   // Host arrays are validated here and pass through the pinned staging area (free again once the last encode that used it has
   // read its own); the kernel that takes them clamps, so device arrays are safe as well.  In a graph of the caller's the area
   // would be read at every replay, whatever lies there by then: host arrays are copied from where they are instead.
-  int *h_ids = ctx->stage_in, *h_len = h_ids + (size_t)c.max_batch * c.max_src_len, *h_max = h_len + c.max_batch;
+  int *h_ids = ctx->stage_in, *h_len = h_ids + (size_t)c.max_batch * c.max_src_len, *h_max = h_len + c.max_batch, *h_first = h_max + c.max_batch;
   const bool host_ids = is_host_ptr(src_ids), host_len = is_host_ptr(src_len), host_max = max_len && is_host_ptr(max_len);
   if (host_len) {
     for (int b = 0; b < B; ++b)
@@ -1685,12 +1696,19 @@ int bpd_encode(bpd_ctx* ctx, const int32_t* src_ids, const int32_t* src_len, con
     if (host_len) { HIPCHK(hipMemcpyAsync(L.src_len, src_len, (size_t)B * 4, hipMemcpyHostToDevice, ctx->stream)); from_len = L.src_len; }
     if (host_max) { HIPCHK(hipMemcpyAsync(L.max_len, max_len, (size_t)B * 4, hipMemcpyHostToDevice, ctx->stream)); from_max = L.max_len; }
   }
+  // Lengths that the host has: without the padding.  (In a graph of the caller's they are whatever lies there at the replay.)
+  PackP packed{};
+  if (staged && host_len && kv_grouped(c) && attention_nsplit(ctx, S, B, S, 0) == 1) {
+    long tokens = 0;
+    for (int b = 0; b < B; ++b) { h_first[b] = (int)tokens; tokens += h_len[b]; }
+    packed = PackP{h_first, packed_source_rows(tokens, (long)B * S), L.src_row0, L.src_seq, L.src_pos, L.src_packed};
+  }
   for (int b = 0; b < B; ++b) ctx->remaining[b] = !max_len ? c.max_out_len : (host_max ? max_len[b] : -1);
   {
     const size_t most = std::max((size_t)B * S, (size_t)B * std::max(c.max_out_len, c.k_max * c.k_max));
     hipLaunchKernelGGL(encode_init_kernel, dim3((unsigned)std::min<size_t>(256, (most + 255) / 256)), dim3(256), 0, ctx->stream, state_params(ctx),
                        from_ids, from_len, from_max, L.src_ids, L.src_len, B, S, c.vocab, c.pad_id,
-                       (unsigned*)L.step_counter, staged ? &ctx->done[1] : nullptr, ctx->encode_tag + 1);
+                       (unsigned*)L.step_counter, staged ? &ctx->done[1] : nullptr, ctx->encode_tag + 1, packed);
     LAUNCHCHK();
     if (staged) ++ctx->encode_tag;
   }
@@ -1699,8 +1717,8 @@ int bpd_encode(bpd_ctx* ctx, const int32_t* src_ids, const int32_t* src_len, con
     small_encode(ctx);
   } else {
     ctx->steps = 0;
-    const int rc = run_planned(ctx, PLAN_ENCODE, {B, S, ctx->local_q, ctx->local_m, layers_way(ctx, B, 1)}, [&]() -> int {
-      int rc = encoder(ctx);
+    const int rc = run_planned(ctx, PLAN_ENCODE, {B, S, ctx->local_q, ctx->local_m, layers_way(ctx, B, 1), packed.rows}, [&]() -> int {
+      int rc = encoder(ctx, packed.rows);
       if (rc) return rc;
       // first invocation: position 0 only, all heads -> first proposals
       rc = forward(ctx, 1, c.k_max, 1, nullptr);

@@ -256,14 +256,22 @@ __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLd
 // LIMF: the sequence's length is fetched first and only groups that hold keys are fetched: one more dependent round trip
 // (many sequences: the traffic is what counts; local attention: where the keys start depends on it).
 // ARGS: p lies in the kernel's arguments.
-template <bool KVNT, bool LIMF, int QU, bool ARGS>
+// PACKED: as many query rows as keys, from AttnP::row0[b] on (nothing to do for tiles past the last); no splits, not causal.
+template <bool KVNT, bool LIMF, int QU, bool ARGS, bool PACKED = false>
 __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP& qp, const AttnLds& sm, int h, int b, int sb, int z,
                                                     int nheads, int nz, int tid, int nw) {
   constexpr int RT = 16, DH = 64, G = QU < 0 ? 2 : 1;       // groups of keys per wave and round
   int split = 0, tile = z;
   if (p.nsplit > 1) { tile = z / p.nsplit; split = z - tile * p.nsplit; }
+  static_assert(!PACKED || (LIMF && QU <= 0), "the length is read first");
   const int r0 = tile * RT;
-  const int nrows = min(RT, p.R - r0);
+  int nrows = min(RT, p.R - r0);
+  long row = (long)b * p.R + r0;                 // of the queries and the results
+  if constexpr (PACKED) {
+    row = p.row0[b] + r0;
+    nrows = min(RT, p.limit[b] - r0);
+    if (nrows <= 0) return;                      // (the whole workgroup)
+  }
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lq = lane >> 4;
   const size_t head_at = ((size_t)sb * nheads + h) * p.capg * KV_GROUP;
@@ -390,7 +398,7 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
       qlo[s2] = __builtin_bit_cast(bf16x8, *(const u32x4*)&sm.q_s[256 + (s2 * 64 + lane) * 2]);
     }
   } else {
-    const rsrc_t qr = rsrc_of(p.Q + ((size_t)b * p.R + r0) * p.d, (unsigned)nrows * p.d * 4);
+    const rsrc_t qr = rsrc_of(p.Q + row * p.d, (unsigned)nrows * p.d * 4);
     const unsigned off = (lr * p.d + h * DH + 8 * lq) * 4;
     u32x4 qa[2][2];
 #pragma unroll
@@ -407,11 +415,13 @@ __device__ __forceinline__ void attention_mfma_body(const AttnP& p, const QProjP
       split_bf16x8(v, qhi[s2], qlo[s2]);
     }
   }
-  attention_mfma_core<KVNT, LIMF, QU>(p, sm, h, b, tile, split, r0, nrows, nheads, nz, tid, nw, first, hop, kr, vr, kf, vf, qhi, qlo, lim, out);
+  // (the results' row is b * p.R + r0; what lies past the last key only r0 of a causal block tells)
+  if constexpr (PACKED) attention_mfma_core<KVNT, LIMF, QU>(p, sm, h, 0, tile, split, (int)row, nrows, nheads, nz, tid, nw, first, hop, kr, vr, kf, vf, qhi, qlo, lim, out);
+  else attention_mfma_core<KVNT, LIMF, QU>(p, sm, h, b, tile, split, r0, nrows, nheads, nz, tid, nw, first, hop, kr, vr, kf, vf, qhi, qlo, lim, out);
 }
 // SLOTS: a step of a batch some of whose sequences may have ended (AttnP::seq); a kernel of its own, since looking the
 // sequence up is one more round trip ahead of the K/V loads.
-template <bool KVNT, bool LIMF, int QU, bool SLOTS>
+template <bool KVNT, bool LIMF, int QU, bool SLOTS, bool PACKED = false>
 __device__ __forceinline__ void attention_mfma_entry(const AttnP& p, const QProjP& qp) {
   constexpr int NW = ATTN_WAVES, RT = 16;
   __shared__ f32x4 o_s[NW][4][64];
@@ -423,10 +433,13 @@ __device__ __forceinline__ void attention_mfma_entry(const AttnP& p, const QProj
   sm.o_s = o_s; sm.m_s = m_s; sm.l_s = l_s; sm.q_s = q_s; sm.gb_s = gb_s; sm.st_s = st_s;
   const int sb = SLOTS ? p.seq[blockIdx.y] : blockIdx.y;
   if (SLOTS && sb < 0) return;
-  attention_mfma_body<KVNT, LIMF, QU, true>(p, qp, sm, blockIdx.x, blockIdx.y, sb, blockIdx.z, gridDim.x, gridDim.z, threadIdx.x, QU > 0 ? NW : blockDim.x >> 6);
+  attention_mfma_body<KVNT, LIMF, QU, true, PACKED>(p, qp, sm, blockIdx.x, blockIdx.y, sb, blockIdx.z, gridDim.x, gridDim.z, threadIdx.x, QU > 0 ? NW : blockDim.x >> 6);
 }
 // (QU == 0: four or eight waves; QU < 0: four; otherwise eight)
 template <bool KVNT, bool LIMF, int QU>
 __global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_kernel(AttnP p, QProjP qp) { attention_mfma_entry<KVNT, LIMF, QU, false>(p, qp); }
 template <bool KVNT, bool LIMF, int QU>
 __global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_slots_kernel(AttnP p, QProjP qp) { attention_mfma_entry<KVNT, LIMF, QU, true>(p, qp); }
+// Source rows that lie one sequence behind the other (encoder of a ragged batch)
+template <int QU>
+__global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_packed_kernel(AttnP p, QProjP qp) { attention_mfma_entry<false, true, QU, false, true>(p, qp); }

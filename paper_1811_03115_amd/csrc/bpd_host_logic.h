@@ -70,6 +70,7 @@ struct Layout {
   // encoder activations (max_batch * max_src rows)
   float *xe, *qe; void *xen, *ke, *ve, *attne, *ffhe, *mem;
   // state
+  int *src_row0, *src_seq, *src_pos, *src_packed;         // packed source rows: PackP
   int *L, *j, *finished, *max_len, *src_len, *src_ids, *P, *A, *accepted, *out_ids, *step_counter, *imposed1, *sched;
   void* dyn; int *tick, *imp_next; int *steps_done, *fin_step, *slot_seq, *slot_L, *slot_src, *slot_row, *n_live;
   long long* stats;
@@ -160,6 +161,15 @@ constexpr int LEAN_K_WHOLE = 2048;
 constexpr int LEAN_PART_M = 192;        // more rows: the slices of the LDS-staged kernel (192 rows 6.8 against 7.25 us, 256 rows 8.0 against 7.3)
 bool lean_encoder_ok(const bpd_config& c, long M) { return lean_ok(c, M) && (c.d_model <= 512 || M <= LEAN_ENC_WIDE_M_MAX); }
 
+// Rows of the encoder for sources of `tokens` tokens together in B x S places: packed, a multiple of 16, where at least an eighth of the places is padding; otherwise
+// all of them (0).  A packed encode looks up each row's sequence and position: a load ahead of each attention, two at the entry of the GEMMs that store keys and values,
+// some 0.5 us each of a layer's 25 .. 50, what an eighth of the rows costs.  Whole calls, ms, padded and packed: 13 sequences, 319 of 780 places, d = 512 2.158,
+// 2.066;  32, 1090 of 2240, d = 1024 17.63, 17.39;  5, 250 places 4.690, 4.633.
+inline int packed_source_rows(long tokens, long places) {
+  const long rows = (tokens + 15) / 16 * 16;
+  return rows * 8 <= places * 7 ? (int)rows : 0;
+}
+
 // Other decoder blocks of more than 128 rows run their LayerNorm-then-GEMM pairs as one GEMM on weights with the LayerNorm
 // folded in (ROWAFF in bpd_gemm.h); contexts that can see such blocks keep a folded copy of those matrices.
 constexpr int LDSX_LN_M_MAX = 128;     // LayerNorm-fused consumers and statistics-writing producers: blocks of at most 128 rows
@@ -240,6 +250,7 @@ size_t build_layout(const bpd_config& c, char* base, Layout& L, std::vector<std:
   L.src_ids = ints(Me); L.P = ints(B * k); L.A = ints(B * k * k); L.accepted = ints(B); L.topn_ok = ints(B * k); L.sel = ints(B);
   L.out_ids = ints(B * (size_t)c.max_out_len); L.step_counter = ints(1); L.imposed1 = ints(B);
   L.sched = ints(B * (size_t)c.max_out_len);
+  if (kv_grouped(c)) { L.src_row0 = ints(B); L.src_seq = ints(Me); L.src_pos = ints(Me); L.src_packed = ints(Me); }
   L.dyn = a.take(64); L.tick = ints(B); L.imp_next = ints(B); L.steps_done = ints(B); L.fin_step = ints(B); L.slot_seq = ints(B); L.slot_L = ints(B); L.slot_src = ints(B); L.slot_row = ints(B); L.n_live = ints(1);
   L.stats = (long long*)a.take(32 * 8);
   if (wide_layers_shape(c)) L.layers_xn = a.take((size_t)LK_JOBS * 64 * d * as);

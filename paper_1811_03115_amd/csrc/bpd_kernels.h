@@ -734,6 +734,7 @@ struct AttnP {
   float* part;            // nsplit > 1: partial results [b][h][tile][split][16*DH acc | 16 max | 16 sum]
   int cap;                // other heads: rows per sequence in the K/V buffer (loads are clamped to it)
   long kv_seq_stride;
+  const int* row0;        // attention_mfma_packed_kernel: first row of each sequence in Q and out
 };
 
 // first key that the row at position t may see
@@ -1025,10 +1026,23 @@ __global__ void fill_i32_kernel(int* p, long n, int v) {
 // area, which the kernel reads directly, or the state's own arrays) and empties the decode state.  `taken` (host memory; null:
 // nothing was staged) is set to `tag` by the last workgroup: the staging area may be written again.  counter: a zero in device
 // memory, zero again afterwards.
+// packed.rows > 0: the source rows also without the padding between them, `first`: the row that each sequence begins at.  Rows past the last token: of
+// no sequence.
+struct PackP { const int* first; int rows; int *row0, *seq, *pos, *ids; };
 __global__ __launch_bounds__(256) void encode_init_kernel(StateP s, const int* src_ids, const int* src_len, const int* max_len, int* d_ids, int* d_len,
                                                           int B, int S, int V, int pad, unsigned* counter, unsigned long long* taken,
-                                                          unsigned long long tag) {
+                                                          unsigned long long tag, PackP packed) {
   const int i = blockIdx.x * 256 + threadIdx.x, n = gridDim.x * 256;
+  if (packed.rows) {
+    for (int q = i; q < B * S; q += n) {
+      const int b = q / S, at = q - b * S, t = src_ids[q];
+      if (at >= src_len[b]) continue;
+      const int row = packed.first[b] + at;
+      packed.seq[row] = b; packed.pos[row] = at; packed.ids[row] = t < 0 ? 0 : (t >= V ? V - 1 : t);
+    }
+    for (int q = i; q < B; q += n) packed.row0[q] = packed.first[q];
+    for (int q = packed.first[B - 1] + src_len[B - 1] + i; q < packed.rows; q += n) { packed.seq[q] = -1; packed.pos[q] = 0; packed.ids[q] = 0; }
+  }
   for (int q = i; q < B * S; q += n) { const int t = src_ids[q]; d_ids[q] = t < 0 ? 0 : (t >= V ? V - 1 : t); }
   for (int q = i; q < B; q += n) {
     const int sl = src_len[q], m = max_len ? max_len[q] : s.max_out;

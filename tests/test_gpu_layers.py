@@ -233,3 +233,26 @@ def test_captured_steps(k, B, d):
             ref.bpd_step(k, two)
             cap.bpd_step(k, two)
     assert acc[0].tolist() == acc[1].tolist() == [2] * B
+
+
+# Sources of ragged batches without their padding: lengths that the host has; with lengths on the device the encoder computes the padding, too.  A tile of 16 rows (skinny
+# kernels), one sequence in more room than it needs, tiles with rows of no sequence, widths with and without kernels of constant K, more than 128 keys, more rows than those
+# kernels take.  Both ways the logits are within TOL of the oracle's, so within twice that of each other.
+@pytest.mark.parametrize("d,S,lens", [(320, 9, [1, 3, 9]), (320, 60, [5, 60, 30, 2]), (128, 40, [1, 1, 40]), (512, 140, [16, 17, 1, 33, 140]), (1024, 128, [27]),
+                                      (1024, 140, [140, 100, 60, 90, 3]), (512, 48, [15 + b % 17 for b in range(33)])])
+def test_packed_sources(d, S, lens):
+    B, k = len(lens), 3
+    cfg = config(k, B, S, 8, layers=2, d=d)
+    weights = wl.make_weights(cfg)
+    rng = np.random.default_rng(d + S)
+    src = rng.integers(3, 272, (B, S)).astype(np.int32)
+    n = np.array(lens, np.int32)
+    tok = torch.from_numpy(rng.integers(3, 272, (B, k)).astype(np.int32)).cuda()
+    got = []
+    ctx = gpu_context(cfg, weights)
+    for lengths in (n, torch.from_numpy(n).cuda(), n):
+        ctx.bpd_encode(src, lengths, np.full(B, 8, np.int32))
+        ctx.bpd_set_proposals(tok)
+        got.append(ctx.bpd_debug_step_logits(k).cpu().numpy())
+    assert np.abs(got[0] - got[1]).max() <= 2 * TOL["bf16"]
+    assert (got[0] == got[2]).all()
