@@ -440,6 +440,113 @@ template <bool KVNT, bool LIMF, int QU>
 __global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_kernel(AttnP p, QProjP qp) { attention_mfma_entry<KVNT, LIMF, QU, false>(p, qp); }
 template <bool KVNT, bool LIMF, int QU>
 __global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_slots_kernel(AttnP p, QProjP qp) { attention_mfma_entry<KVNT, LIMF, QU, true>(p, qp); }
+// Source rows of up to 128 keys: a wave has all keys and values of its (sequence, head) in registers and `per` row tiles of 16 in turn, the next one's queries under way
+// meanwhile.  With the keys dealt to four waves, as above, a launch of many tiles is bound by instructions, half of them the softmax's exchange between lanes and
+// the waves' meeting, which here come once per 128 keys and not at all.  No LDS, no barrier.  32 sequences of 128 tokens, 16 heads, 8 row tiles: 20.6 us dealt to waves (with a
+// workgroup's keys and values kept for four tiles 21.8: not what bounds it), 12.6 here; launches of few tiles wait for one wave's chain instead: 4 x 40 tokens, 8 heads 4.2, 4.8,
+// 5 x 50, 16 heads 4.7, 5.7.
+// PACKED: as in attention_mfma_body.
+template <bool PACKED>
+__global__ __launch_bounds__(256, 2) void attention_mfma_tiles_kernel(AttnP p, int per) {
+  constexpr int RT = 16, DH = 64, G = 4;
+  const int h = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lr = lane & 15, lq = lane >> 4;
+  const int len = p.limit[b], rows = PACKED ? len : p.R, first = (blockIdx.z * 4 + wave) * per;
+  const long row0 = PACKED ? p.row0[b] : (long)b * p.R;
+  const int end = min(first + per, (rows + RT - 1) / RT);
+  if (first >= end) return;
+  const int cap = min(p.capg, G) * 32, lim = len < 0 ? 0 : (len < cap ? len : cap), ngr = (lim + 31) >> 5;
+  const size_t head_at = ((size_t)b * gridDim.x + h) * p.capg * KV_GROUP;
+  const rsrc_t kr = rsrc_of((const bf16_t*)p.Kc + head_at, (unsigned)ngr * (KV_GROUP * 2)), vr = rsrc_of((const bf16_t*)p.Vc + head_at, (unsigned)ngr * (KV_GROUP * 2));
+  const rsrc_t qr = rsrc_of(p.Q + row0 * p.d, (unsigned)rows * p.d * 4);
+  u32x4 qa[4], kf[G][4], vf[G][4];
+  auto queries = [&](int tile) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) qa[i] = buf_load16(qr, ((tile * RT + lr) * p.d + h * DH + 8 * lq) * 4 + (i >> 1) * 128 + (i & 1) * 16, 0);
+  };
+  queries(first);
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    if (g >= ngr) continue;                      // (the same for the whole wave, as every test of g below)
+#pragma unroll
+    for (int x = 0; x < 4; ++x) { kf[g][x] = buf_load16(kr, lane * 16 + x * 1024, g * (KV_GROUP * 2)); vf[g][x] = buf_load16(vr, lane * 16 + x * 1024, g * (KV_GROUP * 2)); }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+    if (g < ngr && 32 * g + 32 > lim) {          // values of keys past the last one: their probabilities are zero, their bits unknown
+      const int left = lim - 32 * g - 8 * lq;    // of this lane's eight
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) vf[g][dt][w] = left > 2 * w + 1 ? vf[g][dt][w] : (left > 2 * w ? vf[g][dt][w] & 0xFFFFu : 0u);
+    }
+#pragma unroll 1
+  for (int tile = first; tile < end; ++tile) {
+    bf16x8 qhi[2], qlo[2];
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2) {
+      const f32x4 q0 = __builtin_bit_cast(f32x4, qa[2 * s2]), q1 = __builtin_bit_cast(f32x4, qa[2 * s2 + 1]);
+      const float v[8] = {q0[0] * p.scale, q0[1] * p.scale, q0[2] * p.scale, q0[3] * p.scale, q1[0] * p.scale, q1[1] * p.scale, q1[2] * p.scale, q1[3] * p.scale};
+      split_bf16x8(v, qhi[s2], qlo[s2]);
+    }
+    if (tile + 1 < end) queries(tile + 1);
+    // scores: s[g][t][r] = key 32 g + 8 lq + 4 t + r against query row lr
+    f32x4 s[G][2];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      if (g >= ngr) continue;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f}, al = a;       // (two chains)
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+          const bf16x8 ka = __builtin_bit_cast(bf16x8, kf[g][2 * t + s2]);
+          a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qhi[s2], a, 0, 0, 0);
+          al = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qlo[s2], al, 0, 0, 0);
+        }
+        s[g][t] = a + al;
+      }
+      if (32 * g + 32 > lim)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) s[g][t][r] = 32 * g + 8 * lq + 4 * t + r < lim ? s[g][t][r] : -INFINITY;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[g][t][r]);
+    }
+    mx = max_rows(mx);
+    float sum = 0.f;
+    f32x4 acc[4];                                // out^T tile dt: head dimensions 16 dt + 4 lq + r, row lr
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      if (g >= ngr) continue;
+      float pv[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) { pv[i] = __expf(s[g][i >> 2][i & 3] - mx); sum += pv[i]; }
+      bf16x8 phi, plo;
+      split_bf16x8(pv, phi, plo);
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt) {
+        const bf16x8 va = __builtin_bit_cast(bf16x8, vf[g][dt]);
+        acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, phi, acc[dt], 0, 0, 0);
+        acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, plo, acc[dt], 0, 0, 0);
+      }
+    }
+    sum = sum_rows(sum);
+    float inv = __builtin_amdgcn_rcpf(sum);
+    inv = inv * fmaf(-sum, inv, 2.f);            // (one Newton step: the quotient to fp32)
+    if (tile * RT + lr < rows) {
+      bf16_t* to = (bf16_t*)p.out + (row0 + tile * RT + lr) * p.d + h * DH + 4 * lq;
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt) *(u32x2*)(to + 16 * dt) = u32x2{cvt_pk_bf16(acc[dt][0] * inv, acc[dt][1] * inv), cvt_pk_bf16(acc[dt][2] * inv, acc[dt][3] * inv)};
+    }
+  }
+}
 // Source rows that lie one sequence behind the other (encoder of a ragged batch)
 template <int QU>
 __global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_packed_kernel(AttnP p, QProjP qp) { attention_mfma_entry<false, true, QU, false, true>(p, qp); }

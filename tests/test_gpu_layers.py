@@ -1,5 +1,7 @@
 """All decoder layers as one kernel: a job of up to 16 rows per XCD (d = 512, d_ff = 2048), or one block of up to 16 or of 17 .. 64 rows on the whole chip (d =
 1024, d_ff = 4096).  Rows and slots at their limits, long caches, whose attention several workgroups may share, groups that are not full, and sequences that end."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -256,3 +258,11 @@ def test_packed_sources(d, S, lens):
         got.append(ctx.bpd_debug_step_logits(k).cpu().numpy())
     assert np.abs(got[0] - got[1]).max() <= 2 * TOL["bf16"]
     assert (got[0] == got[2]).all()
+
+
+# Source rows without padding, several row tiles a workgroup of the encoder's attention: a last tile that is not full, a last workgroup with fewer; and so many rows that the GEMM
+# of the long K takes one round of 256-column tiles (3640 and 4100 rows)
+@pytest.mark.parametrize("d,batch,S", [(1024, 28, 130), (1024, 41, 100), (512, 64, 81), (512, 70, 128), (1024, 33, 49)])
+def test_many_source_rows(d, batch, S):
+    cfg = dataclasses.replace(config(2, batch, S, 6, layers=1, d=d), src_len_kind="fixed")
+    lockstep(cfg, 1)
