@@ -280,11 +280,21 @@ size_t build_layout(const bpd_config& c, char* base, Layout& L, std::vector<std:
 constexpr int LDSX_LN_MT_MAX = 3;      // LayerNorm-fused consumers and statistics-writing producers: tiles of at most 48 rows
 constexpr long LDSX_MIN_WGS = 440;
 constexpr long LDSX_MIN_WGS_LONGK = 400;   // K >= 2048, fewer than 1024 rows: a workgroup lives long enough that about 1.5 per CU suffice
-                                           // (the encoder's 4096-row FFN output: 64-row tiles, 512 workgroups, beat 80-row tiles, 416: encode -2%)
 // (chosen at 80 .. 320 rows.  Of 64 GEMMs of 700 .. 4096 rows its tile is within 5 % of the best at 37 and within 10 % at 48; worst: 780 x 3072 x 1024 25.8 us, 80 x 128 tiles
-// 15.5; 2240 x 1024 x 4096 50.8, 39.6; 4096 x 1024 x 4096 53.6, 64 x 256 tiles 45.1)
+// 15.5; 2240 x 1024 x 4096 50.8, 39.6)
+// A long K and many rows: a tile of 256 columns that gives every CU one workgroup, and hardly more CUs than that, keeps four steps of weights in flight per wave and
+// fetches least per product.  us, the rule above and this: 3584 x 1024 x 4096 47.9, 41.1;  4096 51.6, 43.6;  5000 59.0, 56.9;  6144 73.1, 62.6;  8192 93.1, 72.5;  5000 x 768 x
+// 3072 46.1, 37.2;  6144 50.9, 43.0;  8192 64.1, 52.8.  (K = 2048: 4096 x 1024 31.7, 30.0, but 5000 36.2, 40.9.  Below 220 workgroups the rule above is as good: 4096 x 1024 at
+// 208 47.2, 3000 at 188 53.7 against 39.5.)
+constexpr int LDSX_ONE_ROUND_K = 3072, LDSX_ONE_ROUND_M = 2048;
+constexpr long LDSX_ONE_ROUND_MIN = 220, LDSX_ONE_ROUND_MAX = 256;
 void pick_tile(int M, int N, int K, long zdim, int& mt, int& nt, int mt_max = 8) {
   const int mts[7] = {8, 7, 5, 4, 3, 2, 1};
+  if (K >= LDSX_ONE_ROUND_K && K % 128 == 0 && M >= LDSX_ONE_ROUND_M && zdim == 1 && mt_max >= 8)
+    for (int m : {8, 7, 5, 4}) {
+      const long wgs = (long)((M + 16 * m - 1) / (16 * m)) * ((N / 16 + 15) / 16);
+      if (wgs >= LDSX_ONE_ROUND_MIN && wgs <= LDSX_ONE_ROUND_MAX) { mt = m; nt = 4; return; }
+    }
   long best_area = 0, best_pad = 0;
   mt = 1; nt = (K % 256 == 0) ? 1 : 4;
   for (int n : {1, 2, 4}) {
