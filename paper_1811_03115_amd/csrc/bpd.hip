@@ -777,7 +777,7 @@ int layers_way(const bpd_ctx* ctx, int slots, int R) {
   if (layers_shape(c)) return layers_fit(slots, R) ? LAYERS_JOBS : LAYERS_CHAIN;
   const long keys = attention_keys(ctx, c.max_out_len + c.k_max + 1, R, 1);
   if (wide_layers_fit(slots, R, keys, ctx->S)) return LAYERS_WIDE;
-  return ctx->lay.layers_x2 && tall_layers_fit(slots, R, keys, ctx->S) ? LAYERS_TALL : LAYERS_CHAIN;
+  return ctx->lay.layers_slices && tall_layers_fit(slots, R, keys, ctx->S) ? LAYERS_TALL : LAYERS_CHAIN;
 }
 int layers_split_of(const bpd_ctx* ctx, int slots, int R) {
   const bpd_config& c = ctx->cfg;
@@ -828,7 +828,7 @@ void launch_layers(bpd_ctx* ctx, int R, int way) {
   }
   if (way == LAYERS_TALL) {
     p.jobs = p.per_job = p.split = 0;
-    p.xn = (bf16_t*)L.layers_xn; p.x2 = L.layers_x2; p.part = L.kpart;
+    p.xn = (bf16_t*)L.layers_xn; p.x1 = L.layers_x1; p.attn = (bf16_t*)L.layers_attn2; p.ffh = (bf16_t*)L.layers_ffh; p.slices = L.layers_slices; p.part = L.kpart;
     const int tiles = (ctx->Bs * R + 15) / 16;
     if (tiles <= 2) launch_tall_layers<2>(ctx, p);
     else if (tiles == 3) launch_tall_layers<3>(ctx, p);

@@ -64,7 +64,7 @@ struct Layout {
   // decoder stack kernel (blocks of at most 16 rows): exchange buffers, flags, error word, probe output
   unsigned char* stack_ex = nullptr; unsigned* stack_flags = nullptr; unsigned* stack_err = nullptr; unsigned* xcc_map = nullptr;
   unsigned long long* stack_trace = nullptr; void* stack_layers = nullptr;
-  void* layers_xn = nullptr; float* layers_x2 = nullptr;         // tall_layers_kernel: LayersP::xn, x2
+  void* layers_xn = nullptr; float* layers_slices = nullptr;     // tall_layers_kernel: LayersP::xn, slices
   float *layers_x1 = nullptr, *layers_x3 = nullptr; void *layers_attn2 = nullptr, *layers_ffh = nullptr;      // layers_kernel: LayersP::x1, x3, attn2; wide_layers_kernel: x1, attn, ffh
   unsigned* layers_sync = nullptr;               // layers_kernel: what its workgroups count in
   // encoder activations (max_batch * max_src rows)
@@ -253,9 +253,12 @@ size_t build_layout(const bpd_config& c, char* base, Layout& L, std::vector<std:
   if (kv_grouped(c)) { L.src_row0 = ints(B); L.src_seq = ints(Me); L.src_pos = ints(Me); L.src_packed = ints(Me); }
   L.dyn = a.take(64); L.tick = ints(B); L.imp_next = ints(B); L.steps_done = ints(B); L.fin_step = ints(B); L.slot_seq = ints(B); L.slot_L = ints(B); L.slot_src = ints(B); L.slot_row = ints(B); L.n_live = ints(1);
   L.stats = (long long*)a.take(32 * 8);
-  if (wide_layers_shape(c)) L.layers_xn = a.take((size_t)LK_JOBS * 64 * d * as);
-  if (wide_layers_shape(c) && M > 16) { L.layers_x2 = vec(TALL_LAYERS_ROWS * d); }
-  if (wide_layers_shape(c)) { L.layers_x1 = vec((size_t)6 * 16 * d); L.layers_attn2 = a.take((size_t)4 * 16 * d * as); L.layers_ffh = a.take((size_t)2 * 16 * F * as); }
+  if (wide_layers_shape(c)) {                  // (what both of them use: of the larger one)
+    const size_t rows = M > 16 ? TALL_LAYERS_ROWS : 16;
+    L.layers_xn = a.take((size_t)LK_JOBS * 4 * rows * d * as);
+    L.layers_x1 = vec((M > 16 ? 4 : 6) * rows * d); L.layers_attn2 = a.take(4 * rows * d * as); L.layers_ffh = a.take(2 * rows * F * as);
+    if (M > 16) L.layers_slices = vec((size_t)2 * 4 * rows * d);
+  }
   if (layers_shape(c)) { L.layers_x1 = vec((size_t)2 * LK_JOBS * 16 * d); L.layers_x3 = vec((size_t)LK_JOBS * 16 * d); L.layers_attn2 = a.take((size_t)LK_JOBS * 16 * d * as); }
   L.layers_sync = layers_shape(c) || wide_layers_shape(c) ? (unsigned*)a.take((size_t)LK_WORDS * 4) : nullptr;
   L.xcc_map = (unsigned*)a.take(XCC_MAP_MAX * 4);

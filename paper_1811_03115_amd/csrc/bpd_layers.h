@@ -59,7 +59,7 @@ struct LayersP {
   const int *base, *src_len, *seq;               // per slot: cache rows, source length, sequence (null: the slot; -1: none)
   float eps, scale;
   int local_q, local_m;
-  bf16_t* xn; float* x2;                         // tall_layers_kernel: normalised rows, one copy per XCD; the residual stream's second buffer.  Its slices: part
+  bf16_t* xn; float* slices;                     // normalised rows, copies per XCD; tall_layers_kernel: the second FFN layer's K slices between layers (of the last: part)
   unsigned* sync;                                // [LK_WORDS], zero at the start of a launch (the LayerNorm behind it clears it)
   long long* error;                              // set to 1 if a wait ran out
 };

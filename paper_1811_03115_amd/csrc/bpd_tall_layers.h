@@ -1,15 +1,15 @@
 // As bpd_wide_layers.h, for blocks of 17 .. 64 rows of up to 16 slots: MT = 2 .. 4 MFMA row tiles.  Included by bpd_kernels.h behind it.
 //
-// With one row tile every member normalises all rows of an operator's input itself, which costs 0.42 us a row and wave: here a wave has
+// With one row tile of a few rows every member normalises all of an operator's input itself, which costs 0.42 us a row and wave: here a wave has
 // one row, and the XCD's waves hand their rows on inside the XCD (every XCD normalises all rows: a hand-over between XCDs
 // costs more than the row).  The second FFN layer (four times as long as the others) is split over K among four members per tile, all 256 of
-// them: each multiplies 1024 of 4096, as everywhere else, so that one staging buffer of 16 MT x 1024 holds any input; the LayerNorm that follows adds the
-// four slices, and so does ln_row_kernel behind the last layer.  Since every XCD reads the residual stream that this LayerNorm writes, two
-// buffers of it take turns; the last layer's is LayersP::x.
+// them: each multiplies 1024 of 4096, as everywhere else, so that one staging buffer of 16 MT x 1024 holds any input; whoever reads the residual stream next adds the
+// four slices: the LayerNorm and the output projection that follow, and ln_row_kernel behind the last layer.  Results tell by themselves that they have come, as there.
 //
-// Six layers of 40 rows in five slots: 264 us as a chain of 60 kernels, 187 here; of 18 rows in two slots 160, of 32 in four 170 (with MT = 3 170 and 180),
-// of 56 in seven 207, of 64 in four 222, in sixteen 240 (chain: 280 .. 300).  It is bound as the other is, by eight hand-overs a layer, the two of
-// normalised rows inside the XCD (0.6 us), and by staging 2 KB a row for each operator (40 rows: 0.9 .. 1.4 us).
+// Six layers of 40 rows in five slots: 264 us as a chain of 60 kernels, 181 here (with flags behind the results, gathered per XCD and passed on, 192); of 32 rows in
+// four slots 154 (171), of 56 .. 64 in seven 206 (225).  A layer of 40 rows, us from the results of the operator before: first LayerNorm staged 4.0, queries, keys and values out 1.2;
+// self-attention out 2.4; output projection staged 2.6, out 0.9; cross-attention out 4.9; its projection staged 1.6, out 0.9; third LayerNorm staged 3.7, first FFN layer
+// out 1.2; second staged 2.9, out 1.0.  Staging is what bounds it: a trip to memory, then 80 KB a member from the L2 and into the LDS (0.9 .. 1.4 us).
 //
 // Places.  r < 8: no queries, keys and values, but the cross-attention's first eight heads of an XCD, 24 .. 31: the self-attention's (the
 // other way round for more; from nine slots on two heads or more per place); 8 .. 15, 16 .. 23: the output projections; every place has a tile of the first FFN layer and one K slice of a tile of the second.
@@ -28,17 +28,20 @@ struct TkPlaces {
   // (slot, head) as slot * 16 + head
   __device__ __forceinline__ static int item(int place, int k) { return (k >> 1) * 16 + 2 * (place >> 5) + (k & 1); }
   __device__ __forceinline__ static bool any(int op, int place, int slots) { const int k = order(op, place); return k >= 0 && k < 2 * slots; }
-  // the members of an XCD that have one
-  __device__ __forceinline__ static unsigned mask(int op, int slots) {
-    const int n = slots < 8 ? 2 * slots : 16, a = n < 8 ? n : 8, b = n - a;
-    const unsigned first = (1u << a) - 1, rest = (1u << b) - 1;
-    return op == WK_SELF ? first << 24 | rest : first | rest << 24;
-  }
 };
 
 template <int MT>
 struct TkHelper : WkHelper {
-  __device__ __forceinline__ const float* residual(int l) const { const LayersP& p = lk_args(); return (p.n_layers - 1 - l) & 1 ? p.x2 : p.x; }
+  // Buffers of what is handed over, two of each, which the layers use in turn: the residual stream behind the attentions (stage 1, 2), the attentions' results, the hidden
+  // layer, the second FFN layer's four slices (the last layer's: LayersP::part, for the kernel behind), and an XCD's normalised rows.
+  __device__ __forceinline__ static float* between(int stage, int l) { return lk_args().x1 + ((stage - 1) * 2 + (l & 1)) * (TK_ROWS * D); }
+  __device__ __forceinline__ static bf16_t* heads(int which, int l) { return lk_args().attn + ((which == WK_CROSS ? 2 : 0) + (l & 1)) * (TK_ROWS * D); }
+  __device__ __forceinline__ static bf16_t* hidden(int l) { return lk_args().ffh + (l & 1) * (TK_ROWS * F); }
+  __device__ __forceinline__ static float* slices(int l) { const LayersP& p = lk_args(); return l + 1 == p.n_layers ? p.part : p.slices + (l & 1) * (4 * TK_ROWS * D); }
+  __device__ __forceinline__ bf16_t* normed(int op, int l) const { return lk_args().xn + (size_t)((j.xcd * 2 + (op == WK_UP ? 1 : 0)) * 2 + (l & 1)) * (TK_ROWS * D); }
+  // the row that this wave normalises for its XCD (full: the members with queries, keys and values)
+  __device__ __forceinline__ int norm_of() const { const int m = hw < 3 && j.rank >= 8 ? hw * 24 + j.rank - 8 : TK_ROWS; return m < j.rows ? m : -1; }
+  __device__ __forceinline__ LkPoll poll() { return LkPoll{&broken, lk_args().error, true, j.rank}; }
 
   // The first NF waves of the members in the mask have done this XCD's part: its first member passes it on (not full: all waves of all)
   template <int NF>
@@ -64,50 +67,85 @@ struct TkHelper : WkHelper {
     if (lane < WK_XCDS) wk_store4(lk_args().sync + lane * WK_AREA + WK_GLOBAL + j.xcd, op);
   }
 
-  // Row m of layer l's residual stream: of its buffer or, first, what the layer before left (merge)
-  __device__ __forceinline__ void load_row(int l, int m, bool merge, f32x4 (&v)[4]) {
+  // Row m ahead of layer l's first LayerNorm (OP = WK_QKV: what the layer before left, its slices being what is waited for: the rows behind the cross-attention were there
+  // for the LayerNorm in between), or ahead of its third
+  template <int OP>
+  __device__ __forceinline__ void load_row(int l, int m, f32x4 (&v)[4]) {
     const LayersP& p = lk_args();
     const int lane = lk_lane();
-    const float* from = merge ? (l > 0 ? residual(l - 1) : p.x) : residual(l);
-    const rsrc_t xr = rsrc_of(from, (unsigned)j.rows * D * 4), pr = rsrc_of(p.part, (unsigned)j.rows * D * 16);
-    f32x4 s[4][4], bias[4];
+    const rsrc_t xr = rsrc_of(OP == WK_UP ? between(2, l) : (l > 0 ? between(2, l - 1) : p.x), (unsigned)j.rows * D * 4);
+    if constexpr (OP == WK_UP) {
+      LkPoll w = poll();
+      w.turn = -1;
+      w([&] {
 #pragma unroll
-    for (int h = 0; h < 4; ++h) v[h] = __builtin_bit_cast(f32x4, lk_load16(xr, (m * D + h * 256 + lane * 4) * 4));
-    if (merge && l > 0) {
+        for (int h = 0; h < 4; ++h) v[h] = __builtin_bit_cast(f32x4, lk_load16(xr, (m * D + h * 256 + lane * 4) * 4));
+        unsigned top = 0;
+#pragma unroll
+        for (int h = 0; h < 4; ++h) top = lk_top(top, __builtin_bit_cast(u32x4, v[h]));
+        return top;
+      });
+    } else if (l == 0) {
+#pragma unroll
+      for (int h = 0; h < 4; ++h) v[h] = __builtin_bit_cast(f32x4, lk_load16(xr, (m * D + h * 256 + lane * 4) * 4));
+    } else {
+      const rsrc_t pr = rsrc_of(slices(l - 1), (unsigned)j.rows * D * 16);
       const float* b2 = (const float*)((const char*)p.b2 + (l - 1) * p.stride);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int h = 0; h < 4; ++h) s[i][h] = __builtin_bit_cast(f32x4, lk_load16(pr, ((i * j.rows + m) * D + h * 256 + lane * 4) * 4));
+      f32x4 s[4][4], bias[4];
 #pragma unroll
       for (int h = 0; h < 4; ++h) bias[h] = *(const f32x4*)(b2 + h * 256 + lane * 4);
-      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int h = 0; h < 4; ++h) v[h] = __builtin_bit_cast(f32x4, lk_load16(xr, (m * D + h * 256 + lane * 4) * 4));
+      LkPoll w = poll();
+      w.first<4>(pr, ((j.rank >> 2 & 3) * j.rows + m) * (D * 4), lane);
+      w([&] {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int h = 0; h < 4; ++h) s[i][h] = __builtin_bit_cast(f32x4, lk_load16(pr, ((i * j.rows + m) * D + h * 256 + lane * 4) * 4));
+        __builtin_amdgcn_sched_barrier(0);
+        unsigned top = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int h = 0; h < 4; ++h) top = lk_top(top, __builtin_bit_cast(u32x4, s[i][h]));
+        return top;
+      });
 #pragma unroll
       for (int h = 0; h < 4; ++h) v[h] += (((s[0][h] + s[1][h]) + s[2][h]) + s[3][h]) + bias[h];
     }
     __builtin_amdgcn_sched_barrier(0);
   }
-  __device__ __forceinline__ void keep_row(int l, int m, const f32x4 (&v)[4]) {
-    float* x = (float*)residual(l) + (size_t)m * D;
-#pragma unroll
-    for (int h = 0; h < 4; ++h) wk_store16(x + h * 256 + lk_lane() * 4, v[h]);
-  }
-  __device__ __forceinline__ void norm_row(f32x4 (&v)[4], const f32x4 (&g)[4], const f32x4 (&b)[4], bf16_t* to) {
-    const int lane = lk_lane();
-    wk_norm_row(v, g, b, lk_args().eps, [&](int h, u32x2 w) { *(u32x2*)(to + h * 256 + lane * 4) = w; });
-  }
-  // Does layer l's first LayerNorm find its rows in another buffer than its own?
-  __device__ __forceinline__ bool moved(int l) const { return l > 0 || residual(0) != lk_args().x; }
-  // bf16 rows of 1024 (ld: bytes between them) into LDS, 1032 apart
-  __device__ __forceinline__ void stage(const bf16_t* src, unsigned ld) {
+  // bf16 rows of 1024 (ld: bytes between them) into LDS, 1032 apart; poll: until they have come.  (One piece first, as in bpd_wide_layers.h; then of all rows those that
+  // are missing again: 80 KB a member each time would be too much.)
+  __device__ __forceinline__ void stage(const bf16_t* src, unsigned ld, bool wait_for) {
     const int lane = lk_lane();
     const rsrc_t r = rsrc_of(src, (unsigned)(j.rows - 1) * ld + D * 2);
     u32x4 v[4 * MT][2];
+    if (wait_for) poll().template first<2>(r, hw * ld, lane);
 #pragma unroll
     for (int i = 0; i < 4 * MT; ++i)
 #pragma unroll
       for (int h = 0; h < 2; ++h) v[i][h] = lk_load16(r, (hw + 4 * i) * ld + h * 1024 + lane * 16);
     __builtin_amdgcn_sched_barrier(0);
+    if (wait_for && !broken) {
+      bool seen = false;
+#pragma unroll 1
+      for (int s = 0; s < LK_POLLS; ++s) {
+        unsigned top = 0;
+#pragma unroll
+        for (int i = 0; i < 4 * MT; ++i) { top = lk_top(top, v[i][0]); top = lk_top(top, v[i][1]); }
+        if (!__any(top == EMPTY_WORD)) { seen = true; break; }
+#pragma unroll
+        for (int i = 0; i < 4 * MT; ++i)
+          if (__any(lk_top(lk_top(0, v[i][0]), v[i][1]) == EMPTY_WORD)) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) v[i][h] = lk_load16(r, (hw + 4 * i) * ld + h * 1024 + lane * 16);
+          }
+        asm volatile("" ::: "memory");
+      }
+      if (!seen) { broken = true; if (lane == 0) *lk_args().error = 1; }
+    }
 #pragma unroll
     for (int i = 0; i < 4 * MT; ++i)
       if (hw + 4 * i < j.rows) {
@@ -116,45 +154,89 @@ struct TkHelper : WkHelper {
       }
   }
   // LayerNorm of all rows into LDS
-  __device__ __forceinline__ void stage_norm(int l, const float* ln, bool merge) {
+  template <int OP>
+  __device__ __forceinline__ void stage_norm(int l, const float* ln) {
     const LayersP& p = lk_args();
-    const int lane = lk_lane(), m = hw < 3 && j.rank >= 8 ? hw * 24 + j.rank - 8 : TK_ROWS;         // (full: the members with queries, keys and values)
+    const int lane = lk_lane();
     f32x4 g[4], b[4], v[4];
     load_norm(ln, g, b, lane);
-    wait(op - 1);
     if (!j.full) {
 #pragma unroll 1
       for (int r = hw; r < j.rows; r += 4) {
-        load_row(l, r, merge, v);
-        if (merge && moved(l) && j.place == 8 % j.members) keep_row(l, r, v);      // (place 8: the first with a tile here)
-        norm_row(v, g, b, xs + r * (D + 8));
+        load_row<OP>(l, r, v);
+        wk_norm_row(v, g, b, p.eps, [&](int h, u32x2 w) { *(u32x2*)(xs + r * (D + 8) + h * 256 + lane * 4) = w; });
       }
       return;
     }
-    bf16_t* mine = p.xn + (size_t)j.xcd * TK_ROWS * D;
-    unsigned* flags = area() + WK_NORM;
-    if (m < j.rows) {
-      load_row(l, m, merge, v);
-      norm_row(v, g, b, mine + (size_t)m * D);
-      lk_raise(flags + m, op, lane);
+    const int m = norm_of();
+    bf16_t* to = normed(OP, l);
+    if (m >= 0) {
+      load_row<OP>(l, m, v);
+      wk_norm_row(v, g, b, p.eps, [&](int h, u32x2 w) { *(u32x2*)(to + (size_t)m * D + h * 256 + lane * 4) = full_words(w); });
     }
-    if (!broken) {
-      bool seen = false;
+    if (OP == WK_QKV && l == 0) {                // (nothing is empty yet: a flag each)
+      unsigned* flags = area() + WK_NORM;
+      if (m >= 0) lk_raise(flags + m, op, lane);
+      if (!broken) {
+        bool seen = false;
 #pragma unroll 1
-      for (int s = 0; s < LK_SPINS; ++s) {
-        const unsigned v = lk_load(flags + lane);
-        if (__all(lane >= j.rows || v >= op)) { seen = true; break; }
+        for (int s = 0; s < LK_SPINS; ++s) {
+          const unsigned f = lk_load(flags + lane);
+          if (__all(lane >= j.rows || f >= op)) { seen = true; break; }
+        }
+        if (!seen) { broken = true; if (lane == 0) *p.error = 1; }
       }
-      if (!seen) { broken = true; if (lane == 0) *p.error = 1; }
     }
-    stage(mine, D * 2);
+    stage(to, D * 2, OP != WK_QKV || l > 0);
+  }
+
+  // Emptied (EMPTY_WORD) by the waves that write it, a layer later, when all have read it, and ahead of a result of the writer's that the next readers wait for: the
+  // first FFN layer's input is there when both attentions' results, what they read, the first LayerNorm's rows and the slices, rows and hidden layer of the layer
+  // before have been read; the next layer's first input when the third LayerNorm's rows have.  A wave's stores have arrived when loads behind them have, and its next
+  // operator stages, meets the other waves and then stores.
+  __device__ __forceinline__ void empty_normed(int op, int l, int lane) const {
+    const int m = norm_of();
+    if (!j.full || m < 0) return;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) *(u32x2*)(normed(op, l) + m * D + h * 256 + lane * 4) = u32x2{EMPTY_WORD, EMPTY_WORD};
+  }
+  __device__ __forceinline__ void empty_tile(float* x, int tile, int lane) const {
+    const int m = hw * 16 + (lane & 15);
+    const float e = __uint_as_float(EMPTY_WORD);
+    if (hw < MT && tile >= 0 && m < j.rows) wk_store16(x + (size_t)m * D + tile * 16 + (lane >> 4) * 4, f32x4{e, e, e, e});
+  }
+  __device__ __forceinline__ void empty_heads(int which, int l, int place, int lane) const {
+    const int first = TkPlaces::order(which, place);
+    if (first < 0) return;
+#pragma unroll 1
+    for (int k = first; k < 2 * j.slots; k += 16) rows_of_head(heads(which, l), TkPlaces::item(place, k), EMPTY_WORD, lane);
+  }
+  __device__ __forceinline__ void empty_hidden(int l, int place, int lane) const {
+    const int m = hw * 16 + (lane & 15);
+    if (hw < MT && m < j.rows) wk_store8(hidden(l) + (size_t)m * F + place * 16 + (lane >> 4) * 4, u32x2{EMPTY_WORD, EMPTY_WORD});
+  }
+  __device__ __forceinline__ void empty_slice(int l, int place, int lane) const { empty_tile(slices(l) + (size_t)(place & 3) * j.rows * D, place >> 2, lane); }
+  // Everything that this member writes, but what the first LayerNorm of the first layer has written
+  __device__ __forceinline__ void empty_all(int lane) const {
+    const int layers = lk_args().n_layers;
+    empty_normed(WK_QKV, 1, lane);
+    for (int l = 0; l < 2; ++l) empty_normed(WK_UP, l, lane);
+#pragma unroll 1
+    for (int place = j.place; place < 256; place += j.members)
+#pragma unroll 1
+      for (int l = 0; l < 2; ++l) {
+        empty_tile(between(1, l), WkMember::tile(WK_O, place), lane); empty_tile(between(2, l), WkMember::tile(WK_CO, place), lane);
+        empty_heads(WK_SELF, l, place, lane); empty_heads(WK_CROSS, l, place, lane);
+        empty_hidden(l, place, lane);
+        if (l + 1 < layers) empty_slice(l, place, lane);
+      }
   }
 
   template <int OP>
   __device__ __forceinline__ void product(int l) {
     const LayersP& p = lk_args();
     const int lane = lk_lane(), lr = lane & 15, lq = lane >> 4, m = hw * 16 + lr;
-    ++op;
+    if constexpr (OP == WK_QKV) ++op;
     bool staged = false;
 #pragma unroll 1
     for (int place = j.place; place < 256; place += j.members) {
@@ -162,17 +244,43 @@ struct TkHelper : WkHelper {
       if (tile < 0) continue;
       const int n = tile * 16 + lq * 4;
       f32x4 bs, res;
-      if constexpr (OP == WK_UP) bs = *(const f32x4*)((const float*)((const char*)p.b1 + l * p.stride) + n);
-      if (!staged) {
-        if constexpr (OP == WK_QKV) stage_norm(l, (const float*)((const char*)p.ln1 + l * p.stride), true);
-        else if constexpr (OP == WK_UP) stage_norm(l, (const float*)((const char*)p.ln3 + l * p.stride), false);
-        else wait(op - 1);
+      if (!staged && OP != WK_QKV && OP != TK_DOWN && l == 0) wait(1);       // (everybody has emptied what it writes)
+      const rsrc_t rr = rsrc_of(OP == WK_CO ? between(1, l) : (l > 0 ? between(2, l - 1) : p.x), (unsigned)j.rows * D * 4);
+      if constexpr (OP == WK_O || OP == WK_CO) res = __builtin_bit_cast(f32x4, lk_load16(rr, (m * D + n) * 4));
+      if constexpr (OP == WK_O) if (l > 0) {     // (all there: the first LayerNorm has read them)
+        const rsrc_t pr = rsrc_of(slices(l - 1), (unsigned)j.rows * D * 16);
+        f32x4 s[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[i] = __builtin_bit_cast(f32x4, lk_load16(pr, ((i * j.rows + m) * D + n) * 4));      // (rows past the last: of another slice, not used)
+        bs = *(const f32x4*)((const float*)((const char*)p.b2 + (l - 1) * p.stride) + n);
+        __builtin_amdgcn_sched_barrier(0);
+        res += (((s[0] + s[1]) + s[2]) + s[3]) + bs;
+        __builtin_amdgcn_sched_barrier(0);
       }
-      if constexpr (OP == WK_O || OP == WK_CO) res = __builtin_bit_cast(f32x4, lk_load16(rsrc_of(residual(l), (unsigned)j.rows * D * 4), (m * D + n) * 4));
-      if constexpr (OP == TK_DOWN) stage(p.ffh + (place & 3) * D, F * 2);          // (another place: another slice)
-      else if constexpr (OP == WK_O || OP == WK_CO) { if (!staged) stage(p.attn, D * 2); }
-      staged = true;
+      if constexpr (OP == TK_DOWN) stage(hidden(l) + (place & 3) * D, F * 2, true);          // (another place: another slice)
+      else if (!staged) {
+        if constexpr (OP == WK_QKV) stage_norm<OP>(l, (const float*)((const char*)p.ln1 + l * p.stride));
+        else if constexpr (OP == WK_UP) stage_norm<OP>(l, (const float*)((const char*)p.ln3 + l * p.stride));
+        else stage(heads(OP == WK_O ? WK_SELF : WK_CROSS, l), D * 2, true);
+      }
       lk_barrier();                              // the input is staged, the partial sums of the place before are read
+      if constexpr (OP == WK_QKV) {
+        if (l > 0) { if (!staged) empty_normed(WK_UP, l - 1, lane); }
+        else if (j.full) empty_all(lane);
+      }
+      if constexpr (OP == WK_UP) {
+        bs = *(const f32x4*)((const float*)((const char*)p.b1 + l * p.stride) + n);          // (not ahead of the staging: registers)
+        if (!staged) empty_normed(WK_QKV, l, lane);
+        empty_tile(between(1, l), WkMember::tile(WK_O, place), lane);
+        empty_heads(WK_SELF, l, place, lane); empty_heads(WK_CROSS, l, place, lane);
+        if (l > 0) { empty_tile(between(2, l - 1), WkMember::tile(WK_CO, place), lane); empty_hidden(l - 1, place, lane); empty_slice(l - 1, place, lane); }
+      }
+      // (the cross-attention has read all of x1, but this wave may have asked too early)
+      if constexpr (OP == WK_CO) poll()([&] {
+        if (__any(lk_top(0, __builtin_bit_cast(u32x4, res)) == EMPTY_WORD)) res = __builtin_bit_cast(f32x4, lk_load16(rr, (m * D + n) * 4));
+        return lk_top(0, __builtin_bit_cast(u32x4, res));
+      });
+      staged = true;
       lk_barrier();                              // the partial sums are there
       if (hw >= MT) continue;
       f32x4 part[4];
@@ -187,28 +295,23 @@ struct TkHelper : WkHelper {
         v += bs;
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.f);
-        wk_store8(p.ffh + (size_t)m * F + n, u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])});
+        wk_store8(hidden(l) + (size_t)m * F + n, full_words(u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])}));
       } else if constexpr (OP == TK_DOWN) {
-        wk_store16(p.part + ((size_t)(place & 3) * j.rows + m) * D + n, v);
+        wk_store16(slices(l) + ((size_t)(place & 3) * j.rows + m) * D + n, __builtin_bit_cast(f32x4, full_words(v)));
       } else {
         v += res;
-        wk_store16((float*)residual(l) + (size_t)m * D + n, v);
+        const f32x4 w = __builtin_bit_cast(f32x4, full_words(v));
+        wk_store16(between(OP == WK_O ? 1 : 2, l) + (size_t)m * D + n, w);
+        if (OP == WK_CO && l + 1 == p.n_layers) wk_store16(p.x + (size_t)m * D + n, v);          // (for the kernel behind)
       }
     }
-    // Members without queries, keys and values carry the residual stream over to the layer's own buffer (one of those that normalise it took 1.2 us
-    // longer for it, and all waited).  Their flags count with the self-attention's: the next operator that reads it follows that
-    if (OP == WK_QKV && j.full && j.rank < 8 && hw == 0 && moved(l) && j.rank * 8 + j.xcd < j.rows) {
-      f32x4 v[4];
-      wait(op - 1);
-      load_row(l, j.rank * 8 + j.xcd, true, v);
-      keep_row(l, j.rank * 8 + j.xcd, v);
+    if constexpr (OP == WK_QKV) {
+      if (l == 0) this->template done<4>(true, ~0u, true);       // (that everything is empty: to all)
+      else this->template done<MT>(staged, 0xFFFFFF00u, false);
     }
-    constexpr unsigned MASK = OP == WK_QKV ? 0xFFFFFF00u : (OP == WK_O ? 0xFF00u : (OP == WK_CO ? 0xFF0000u : 0xFFFFFFFFu));
-    this->template done<MT>(staged, MASK, OP != WK_QKV);
   }
   template <int OP>
   __device__ __forceinline__ void attention(int l) {
-    ++op;
     bool mine = false;
 #pragma unroll 1
     for (int place = j.place; place < 256; place += j.members) {
@@ -217,12 +320,11 @@ struct TkHelper : WkHelper {
 #pragma unroll 1
       for (int k = first; k < 2 * j.slots; k += 16) {
         const int item = TkPlaces::item(place, k);
-        if constexpr (OP == WK_CROSS) cross_item<ATTN_THROUGH>(l, item, residual(l), op - 1, poll(false), lk_args().attn, !mine);
-        else self_item<MT, ATTN_THROUGH>(l, item, op - 1, lk_args().attn, !mine);
+        if constexpr (OP == WK_CROSS) cross_item<ATTN_THROUGH_WORDS>(l, item, between(1, l), l == 0, poll(), heads(OP, l), !mine);
+        else self_item<MT, ATTN_THROUGH_WORDS>(l, item, op, heads(OP, l), !mine);
         mine = true;
       }
     }
-    this->template done<4>(mine || (OP == WK_SELF && j.rank < 8), TkPlaces::mask(OP, j.slots) | (OP == WK_SELF ? 0xFFu : 0u), true);
   }
   __device__ __forceinline__ void run() {
     const int layers = lk_args().n_layers;
@@ -232,6 +334,7 @@ struct TkHelper : WkHelper {
       sb = p.seq ? p.seq[slot] : slot;
       key = p.base[slot] + m - slot * p.R;
     }
+    if (!j.full || j.rank < 8) empty_all(lk_lane());          // (the others: in the first operator, which these have no part in)
 #pragma unroll 1
     for (int l = 0; l < layers; ++l) {
       this->template product<WK_QKV>(l);
