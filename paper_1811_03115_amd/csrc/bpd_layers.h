@@ -39,7 +39,7 @@
 
 constexpr unsigned LK_CLOSED = 0x10000u, LK_NO_JOB = 0xFFFFu;
 constexpr long long LK_CLOSE_TICKS = 2000;                      // of the 100 MHz counter: 20 us
-constexpr int LK_HOLD = 12, LK_GAP = 1, LK_PACE = 2;            // pauses of the compute waves, units of 64 cycles: LkCompute::job
+constexpr int LK_HOLD = 20, LK_GAP = 1, LK_PACE = 2;            // pauses of the compute waves, units of 64 cycles: LkCompute::job (hold 12: a sentence 2.52 ms, three images 59.1, 20: 2.54, 58.3, 28: 2.55, 58.3, 40: 2.56, 58.6)
 constexpr int LK_SPINS = 1 << 22;                               // (a second: only a defect gets there)
 
 struct LayersP {
@@ -353,6 +353,7 @@ struct LkHelper {
   int key, sb;                                   // of row lr: its row in the cache, its sequence
   unsigned op;                                   // first products done
   bool broken;
+  unsigned ahead[8];                             // fetch_ahead()
 
   __device__ __forceinline__ void raise() { lk_raise(flags + hw * 32 + j.rank, op, lk_lane()); }
 
@@ -457,7 +458,7 @@ struct LkHelper {
       if (place != j.rank) operands(place);
       lk_barrier();                              // the input is staged, the partial sums of the place before are read
       if (place == j.rank) {
-        if constexpr (OP == QKV) { empty_hidden(lane); if (l == 0) empty_all(lane); }         // (read: DOWN's results are there)
+        if constexpr (OP == QKV) { fetch_ahead(l); empty_hidden(lane); if (l == 0) empty_all(lane); }         // (read: DOWN's results are there)
         if constexpr (OP == CO) empty_self(lane);                                                // (O's results were there ahead of the cross-attention's)
         if constexpr (OP == UP) empty_cross(lane);                                               // (CO's are there)
       }
@@ -488,7 +489,7 @@ struct LkHelper {
         if (OP != O || l > 0) empty_tile(in, place, lane);          // (everybody has read the input: it has led to what this operator waited for)
       }
     }
-    if constexpr (OP == QKV) { ++op; raise(); }
+    if constexpr (OP == QKV) { ++op; if (hw < 3 || l == 0) raise(); }         // (the wave without a tile: that it has emptied what it writes)
   }
 
   __device__ __forceinline__ static AttnP attn_args(bool self) {
@@ -503,6 +504,20 @@ struct LkHelper {
 
   // Places (split, slot, head), the heads fastest
   __device__ __forceinline__ int self_places() const { return 8 * j.slots * lk_args().split; }
+  // Keys and values of the first round of this member's part of the self-attention come out of memory into the L2 (they lie in the same lines as the block's own to come:
+  // nothing may enter the L1) while it multiplies for them: asked for by the wave that has no tile of queries, keys and values, since loads return in order, and acknowledgements
+  // with them.  (Asked for by each wave ahead of its wait for the flags, which then waited for them, too, a sentence of 64 tokens took 2.607 ms instead of 2.578.)
+  __device__ __forceinline__ void fetch_ahead(int l) {
+    const LayersP& p = lk_args();
+    if (hw != 3 || j.rank >= self_places()) return;
+    const int lane = lk_lane(), ss = j.rank >> 3, split = p.split > 1 ? ss / j.slots : 0, slot = j.slot0 + ss - split * j.slots, s = sequence(slot);
+    const int lim = lk_const(p.base, slot), held = (lim + p.R + 31) >> 5, groups = held < p.self_groups ? held : p.self_groups;
+    const int first = (attn_first_key(attn_args(true), lim) >> 5) + split * 8;
+    const size_t at = l * p.self_layer + ((size_t)(s < 0 ? 0 : s) * 8 + (j.rank & 7)) * p.self_groups * KV_GROUP;
+    const rsrc_t kr = rsrc_of(p.selfK + at, (unsigned)groups * (KV_GROUP * 2)), vr = rsrc_of(p.selfV + at, (unsigned)groups * (KV_GROUP * 2));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ahead[i] = __builtin_amdgcn_raw_buffer_load_b32(i < 4 ? kr : vr, lane * 128, (first + 2 * (i & 3)) * (KV_GROUP * 2), 16);      // (a word of each line of two groups)
+  }
   // G groups of 32 keys per wave and round
   template <int G>
   __device__ __forceinline__ void self_place(int l, int place) {
@@ -519,14 +534,10 @@ struct LkHelper {
     if (place != j.rank) {
       lk_barrier();                              // the results of the place before are out of LDS
     } else {
-      // the wave's keys and values come out of memory into the L2 while it waits for the block's own among them (which lie in the same lines: nothing
-      // may enter the L1)
-      unsigned t[G];
-#pragma unroll
-      for (int g = 0; g < G; ++g) t[g] = __builtin_amdgcn_raw_buffer_load_b32(lane < 32 ? kr : vr, (lane & 31) * 128, (first + hw + g * 4) * (KV_GROUP * 2), 16);
       lk_wait<3>(flags, op, 0, j.members, lane, broken, p.error);
+      if (hw == 3)
 #pragma unroll
-      for (int g = 0; g < G; ++g) asm volatile("" ::"v"(t[g]));
+        for (int i = 0; i < 8; ++i) asm volatile("" ::"v"(ahead[i]));
     }
     if (s < 0) {                                 // (rows of nobody; a barrier as the attention's own)
       if (p.split > 1) part_rows(slot, h, split, f32x4{0.f, 0.f, 0.f, 0.f}, 0.f, 1.f, lane); else empty_rows(out, slot, h, u32x2{0, 0}, lane);

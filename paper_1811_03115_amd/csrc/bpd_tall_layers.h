@@ -265,6 +265,7 @@ struct TkHelper : WkHelper {
       }
       lk_barrier();                              // the input is staged, the partial sums of the place before are read
       if constexpr (OP == WK_QKV) {
+        if (MT < 4 && j.full && TkPlaces::any(WK_SELF, place, j.slots)) fetch_ahead(l, TkPlaces::item(place, TkPlaces::order(WK_SELF, place)));
         if (l > 0) { if (!staged) empty_normed(WK_UP, l - 1, lane); }
         else if (j.full) empty_all(lane);
       }

@@ -148,6 +148,8 @@ struct WkHelper {
   int key, sb;                                   // of row lr: its row in the cache, its sequence
   unsigned op = 0;
   bool broken = false;
+  unsigned ahead[8];                             // fetch_ahead()
+  bool fetched = false;
 
   __device__ __forceinline__ unsigned* area() const { return lk_args().sync + j.xcd * WK_AREA; }
   // (One piece first where a wait for everything would be 20 .. 80 KB a member, out of memory, round after round: 128 tokens of ten rows a step 5.1 ms, 5.5 without,
@@ -307,6 +309,7 @@ struct WkHelper {
       }
       lk_barrier();                              // the input is staged, the partial sums of the place before are read
       if constexpr (OP == WK_QKV) {
+        if (j.full) fetch_ahead(l, j.item(WK_SELF, place));
         if (l > 0) empty_normed(WK_UP, l - 1, lane);
         if (l > 0) empty_tile(between(2, l - 1), WkMember::tile(WK_CO, place), lane);          // (x3 of the layer before is there: DOWN and UP have read x2)
         else if (j.full) { empty_all(lane); lk_stores_done(); }
@@ -362,6 +365,20 @@ struct WkHelper {
     const int lim = lk_const(p.base, slot);
     return ((lim + p.R + 31) >> 5) - (attn_first_key(attn_args(true), lim) >> 5) <= 4;
   }
+  // As LkHelper::fetch_ahead: by a wave that stores no queries, keys and values (only where this XCD writes the block's own among them)
+  __device__ __forceinline__ void fetch(const rsrc_t& kr, const rsrc_t& vr, int first, int lane) {
+    if (hw != 3) return;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ahead[i] = __builtin_amdgcn_raw_buffer_load_b32(i < 4 ? kr : vr, lane * 128, (first + 2 * (i & 3)) * (KV_GROUP * 2), 16);
+  }
+  __device__ __forceinline__ void fetch_ahead(int l, int item) {
+    if (item < 0) return;
+    const LayersP& p = lk_args();
+    const int slot = item >> 4, s = sequence(slot), lim = lk_const(p.base, slot), held = (lim + p.R + 31) >> 5, groups = held < p.self_groups ? held : p.self_groups;
+    const size_t at = l * p.self_layer + ((size_t)(s < 0 ? 0 : s) * H + (item & 15)) * p.self_groups * KV_GROUP;
+    fetch(rsrc_of(p.selfK + at, (unsigned)groups * (KV_GROUP * 2)), rsrc_of(p.selfV + at, (unsigned)groups * (KV_GROUP * 2)), attn_first_key(attn_args(true), lim) >> 5, lk_lane());
+    fetched = true;
+  }
   template <int NF, int STORE>
   __device__ __forceinline__ void self_item(int l, int item, unsigned after, bf16_t* out, bool first_item) {
     if (few(item >> 4)) self_groups<1, NF, STORE>(l, item, after, out, first_item); else self_groups<2, NF, STORE>(l, item, after, out, first_item);
@@ -379,14 +396,20 @@ struct WkHelper {
     const rsrc_t qr = rsrc_of(p.q + (size_t)slot * p.R * (2 * D), (unsigned)p.R * (4 * D));
     if (!first_item) {
       lk_barrier();                              // the results of the item before are out of LDS
-    } else if (j.full) {
-      // keys and values come into the L2 meanwhile (as in LkHelper::self_place; only where this XCD writes the block's own among them)
+    } else if (j.full && NF == 4) {              // (all four waves store queries, keys and values)
       unsigned t[G];
 #pragma unroll
       for (int g = 0; g < G; ++g) t[g] = __builtin_amdgcn_raw_buffer_load_b32(lane < 32 ? kr : vr, (lane & 31) * 128, (first + hw + g * 4) * (KV_GROUP * 2), 16);
       lk_wait<NF>(area() + WK_LOCAL, after, 8, 24, lane, broken, p.error);
 #pragma unroll
       for (int g = 0; g < G; ++g) asm volatile("" ::"v"(t[g]));
+    } else if (j.full) {
+      if (!fetched) fetch(kr, vr, first, lane);
+      lk_wait<NF>(area() + WK_LOCAL, after, 8, 24, lane, broken, p.error);
+      if (hw == 3)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) asm volatile("" ::"v"(ahead[i]));
+      fetched = false;
     } else {
       wait(after);
     }
