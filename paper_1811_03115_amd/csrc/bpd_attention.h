@@ -117,9 +117,16 @@ __device__ __forceinline__ void attn_load_kv(rsrc_t kr, rsrc_t vr, int c, int nw
   }
 }
 // The item's work from the point where its queries (qhi + qlo) and the first groups of K and V are at hand or under way (parameters as in
-// attention_mfma_body; first, hop: this split's first group and the distance to its next round; lim: limit[b]).  STORE: results are written through the L2
-// (ATTN_THROUGH), no word of them is EMPTY_WORD (ATTN_WORDS), or both.
-enum { ATTN_PLAIN, ATTN_THROUGH, ATTN_WORDS, ATTN_THROUGH_WORDS };
+// attention_mfma_body; first, hop: this split's first group and the distance to its next round; lim: limit[b]).  STORE: no word of the results is EMPTY_WORD (ATTN_WORDS),
+// and they are written through the L2 (ATTN_THROUGH_WORDS).
+enum { ATTN_PLAIN, ATTN_WORDS, ATTN_THROUGH_WORDS };
+template <int STORE>
+__device__ __forceinline__ void attention_store(bf16_t* to, const f32x4& v) {
+  u32x2 w = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
+  if constexpr (STORE != ATTN_PLAIN) w = full_words(w);
+  if constexpr (STORE == ATTN_THROUGH_WORDS) asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(to), "v"(w) : "memory");      // (to memory, for other XCDs)
+  else *(u32x2*)to = w;
+}
 template <bool KVNT, bool LIMF, int QU, int G, int STORE = ATTN_PLAIN>
 __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLds& sm, int h, int b, int tile, int split, int r0, int nrows,
                                                     int nheads, int nz, int tid, int nw, int first, int hop, rsrc_t kr, rsrc_t vr,
@@ -163,7 +170,6 @@ __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLd
       }
     mx = max_rows(mx);
     const float m_new = fmaxf(m_run, mx);
-    const float alpha = (m_new == -INFINITY) ? 1.f : __expf(m_run - m_new);
     float sum = 0.f;
 #pragma unroll
     for (int gg = 0; gg < G; ++gg)
@@ -176,10 +182,16 @@ __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLd
           sum += pv;
         }
     sum = sum_rows(sum);
-    l_run = l_run * alpha + sum;
-    m_run = m_new;
+    // What there was before is relative to another maximum.  (The first round skips that in layers_kernel: three images of up to 3000 intensities 58.0 ms, 57.6; in the others'
+    // code the branch costs more than it saves: tall_layers_kernel, five sentences 4.46 ms, 4.50.)
+    if (STORE == ATTN_WORDS && c == first) l_run = sum;
+    else {
+      const float alpha = (m_new == -INFINITY) ? 1.f : __expf(m_run - m_new);
+      l_run = l_run * alpha + sum;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt) acc[dt] *= alpha;
+      for (int dt = 0; dt < 4; ++dt) acc[dt] *= alpha;
+    }
+    m_run = m_new;
 #pragma unroll
     for (int gg = 0; gg < G; ++gg) {
       const int g0 = 32 * (c + wave + gg * nw);
@@ -187,9 +199,11 @@ __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLd
       if (g0 + 32 > nkeys) {                     // values of keys past the last one: their probabilities are zero, their bits unknown
         const int left = nkeys - g0 - 8 * lq;    // of this lane's eight
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
+        for (int w = 0; w < 4; ++w) {
+          const unsigned known = left > 2 * w + 1 ? ~0u : (left > 2 * w ? 0xFFFFu : 0u);
 #pragma unroll
-          for (int w = 0; w < 4; ++w) vf[gg][dt][w] = left > 2 * w + 1 ? vf[gg][dt][w] : (left > 2 * w ? vf[gg][dt][w] & 0xFFFFu : 0u);
+          for (int dt = 0; dt < 4; ++dt) vf[gg][dt][w] &= known;
+        }
       }
       const float pv[8] = {sacc[gg][0][0], sacc[gg][0][1], sacc[gg][0][2], sacc[gg][0][3], sacc[gg][1][0], sacc[gg][1][1], sacc[gg][1][2], sacc[gg][1][3]};
       bf16x8 phi, plo;
@@ -202,6 +216,17 @@ __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLd
       }
     }
     if (c + hop + wave < ngr) attn_load_kv<KVNT, G>(kr, vr, c + hop + wave, nw, lane, kf, vf);
+  }
+  // At most 32 keys: the first wave has them all, and all 64 dimensions.  (Through the LDS as below, four waves storing 16 each: 0.25 us more.)
+  if (QU >= 0 && ngr - first <= 1 && p.nsplit == 1) {
+    if (wave == 0 && lr < nrows) {
+      float inv = __builtin_amdgcn_rcpf(l_run);
+      inv = inv * fmaf(-l_run, inv, 2.f);        // (one Newton step: the quotient to fp32)
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt) attention_store<STORE>(out + ((size_t)b * p.R + r0 + lr) * p.d + h * DH + 16 * dt + 4 * lq, acc[dt] * inv);
+    }
+    __syncthreads();
+    return;
   }
   // the waves meet (those without keys bring zeros): wave w of the first four finishes head dimensions 16w .. 16w+15
 #pragma unroll
@@ -219,11 +244,7 @@ __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLd
     if (lr < nrows) {
       float inv = __builtin_amdgcn_rcpf(L);
       inv = inv * fmaf(-L, inv, 2.f);            // (one Newton step: the quotient to fp32)
-      u32x2 w = u32x2{cvt_pk_bf16(o[0] * inv, o[1] * inv), cvt_pk_bf16(o[2] * inv, o[3] * inv)};
-      if constexpr (STORE == ATTN_WORDS || STORE == ATTN_THROUGH_WORDS) w = full_words(w);
-      bf16_t* to = out + ((size_t)b * p.R + r0 + lr) * p.d + h * DH + dim;
-      if constexpr (STORE == ATTN_THROUGH || STORE == ATTN_THROUGH_WORDS) asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(to), "v"(w) : "memory");      // (to memory, for other XCDs)
-      else *(u32x2*)to = w;
+      attention_store<STORE>(out + ((size_t)b * p.R + r0 + lr) * p.d + h * DH + dim, o * inv);
     }
   } else {
     const int tiles = nz / p.nsplit;

@@ -4,7 +4,7 @@
 // A layer is seven dependent operators.  As kernels of their own each costs 2.5 .. 6 us, of which a launch that does nothing is 1.7;
 // the workgroups of one XCD share an L2, and there a hand-over (store, acknowledgement, a flag; a poll that sees it) takes 0.3 us
 // one way (690 cycles; between XCDs 950, with the data written through to memory).  Six layers of 8 rows, 40 keys, 32 source tokens: 156 us
-// as 42 kernels, 82 us here; eight such blocks on eight XCDs 90 us (chain of kernels over 64 rows: 200 us).  What bounds it now is the chain within
+// as 42 kernels, 80 us here; eight such blocks on eight XCDs 90 us (chain of kernels over 64 rows: 200 us).  What bounds it now is the chain within
 // an operator: a load of lines that another CU has just written (550 .. 900 cycles), LayerNorm or softmax at one wave
 // per SIMD (4 cycles an instruction), LDS twice: 1.1 .. 2.9 us each.
 //
@@ -458,7 +458,7 @@ struct LkHelper {
       if (place != j.rank) operands(place);
       lk_barrier();                              // the input is staged, the partial sums of the place before are read
       if (place == j.rank) {
-        if constexpr (OP == QKV) { fetch_ahead(l); empty_hidden(lane); if (l == 0) empty_all(lane); }         // (read: DOWN's results are there)
+        if constexpr (OP == QKV) { fetch_ahead(l); empty_hidden(lane); if (l == 0) { empty_all(lane); lk_stores_done(); } }         // (read: DOWN's results are there)
         if constexpr (OP == CO) empty_self(lane);                                                // (O's results were there ahead of the cross-attention's)
         if constexpr (OP == UP) empty_cross(lane);                                               // (CO's are there)
       }

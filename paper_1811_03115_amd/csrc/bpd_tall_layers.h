@@ -267,7 +267,7 @@ struct TkHelper : WkHelper {
       if constexpr (OP == WK_QKV) {
         if (MT < 4 && j.full && TkPlaces::any(WK_SELF, place, j.slots)) fetch_ahead(l, TkPlaces::item(place, TkPlaces::order(WK_SELF, place)));
         if (l > 0) { if (!staged) empty_normed(WK_UP, l - 1, lane); }
-        else if (j.full) empty_all(lane);
+        else if (j.full) { empty_all(lane); lk_stores_done(); }          // (ahead of the barrier: which wave stores an attention's results depends on the keys)
       }
       if constexpr (OP == WK_UP) {
         bs = *(const f32x4*)((const float*)((const char*)p.b1 + l * p.stride) + n);          // (not ahead of the staging: registers)
@@ -322,7 +322,10 @@ struct TkHelper : WkHelper {
       for (int k = first; k < 2 * j.slots; k += 16) {
         const int item = TkPlaces::item(place, k);
         if constexpr (OP == WK_CROSS) cross_item<ATTN_THROUGH_WORDS>(l, item, between(1, l), l == 0, poll(), heads(OP, l), !mine);
-        else self_item<MT, ATTN_THROUGH_WORDS>(l, item, op, heads(OP, l), !mine);
+        else {
+          if (l == 0 && !mine && j.rank < 8) wait(1);         // (its waves have met no barrier since they emptied these)
+          self_item<MT, ATTN_THROUGH_WORDS>(l, item, op, heads(OP, l), !mine);
+        }
         mine = true;
       }
     }

@@ -14,7 +14,7 @@
 // this hand-over stays inside it: plain stores, local flags);  8 .. 15, 16 .. 23: output projections of the self- and the cross-attention;  24 ..:
 // cross-attention, beside the self-attention where there is room.
 //
-// Six layers of 10 rows, 20 .. 120 keys, 27 source tokens: 137 us (as a chain of 60 kernels some 200), of one row 101.  What bounds it is the hand-over, six times a layer
+// Six layers of 10 rows, 20 .. 120 keys, 27 source tokens: 132 us (as a chain of 60 kernels some 200), of one row 101.  What bounds it is the hand-over, six times a layer
 // between XCDs: 0.5 .. 0.8 us until a result is seen elsewhere, a round of asking (0.7), another for all of the input; then the input's
 // staging and 0.7 us from there to the stores.
 //
