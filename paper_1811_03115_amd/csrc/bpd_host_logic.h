@@ -291,8 +291,25 @@ constexpr long LDSX_MIN_WGS_LONGK = 400;   // K >= 2048, fewer than 1024 rows: a
 // 208 47.2, 3000 at 188 53.7 against 39.5.)
 constexpr int LDSX_ONE_ROUND_K = 3072, LDSX_ONE_ROUND_M = 2048;
 constexpr long LDSX_ONE_ROUND_MIN = 220, LDSX_ONE_ROUND_MAX = 256;
+// Several groups with a long K and few rows (the heads' output layers) stream their weights, and what counts are the rounds of one workgroup per CU: us by row tiles and rounds, of
+// 8 and 10 groups of 4096 x 1024 out of memory.  us, by largest useful area and by this: 8 groups, 64 rows 26.1, 22.7;  80 33.2, 23.9;  104 35.2, 29.4;  130 46.0, 33.4;  10 groups,
+// 64 rows 36.9, 30.7;  80 35.6, 28.0;  130 37.3, 33.3;  2048 x 512, 10 groups, 104 rows 12.6, 10.4.  (Two groups or K slices: not measured.)
+constexpr int LDSX_ROUNDS_M = 144;
+inline int ldsx_rounds_cost(int mt, long wgs) {
+  constexpr int us[3][4] = {{190, 235, 340, 430}, {225, 290, 365, 440}, {239, 334, 430, 530}};
+  const long r = (wgs + 255) / 256;
+  return r <= 4 ? us[mt - 1][r - 1] : us[mt - 1][3] + (int)(r - 4) * 100;
+}
 void pick_tile(int M, int N, int K, long zdim, int& mt, int& nt, int mt_max = 8) {
   const int mts[7] = {8, 7, 5, 4, 3, 2, 1};
+  if (zdim > 2 && K >= 2048 && K % 256 == 0 && M > 16 && M <= LDSX_ROUNDS_M && mt_max >= 3) {
+    int best = 0;
+    for (int m : {1, 2, 3}) {
+      const int c = ldsx_rounds_cost(m, (long)((M + 16 * m - 1) / (16 * m)) * ((N / 16 + 3) / 4) * zdim);
+      if (best == 0 || c < best) { best = c; mt = m; nt = 1; }
+    }
+    return;
+  }
   if (K >= LDSX_ONE_ROUND_K && K % 128 == 0 && M >= LDSX_ONE_ROUND_M && zdim == 1 && mt_max >= 8)
     for (int m : {8, 7, 5, 4}) {
       const long wgs = (long)((M + 16 * m - 1) / (16 * m)) * ((N / 16 + 15) / 16);
