@@ -1347,7 +1347,7 @@ void release_retired(bpd_ctx* ctx) {
 // for the PLAN_SIGHTS'th time while it is among them.  Recording costs 0.2 .. 0.6 ms.
 //   Steps (keys: batch sizes and cache lengths) at the second sight.  Without: base model, one sentence 4.09 instead of 3.83 ms, big
 //   model, greedy 8.11 instead of 7.13, eight images 102.4 instead of 96.5.
-//   Encodes (keys: batch sizes and source lengths) at the eighth.  The GPU is no sooner done with a recorded one (base model, one
+//   Encodes (keys: batch sizes, source lengths, packed rows) at the eighth.  The GPU is no sooner done with a recorded one (base model, one
 //   sentence of 64 tokens: 282 us launch by launch, 289), but the host is (50 instead of 220 us), which steps that go out launch by launch then
 //   have as a lead (five sentences in steps of the big model 5.58 instead of 5.93 ms, thirteen of the base model 3.62 instead of
 //   3.87).  At the second sight source lengths as they come cost more than that: 100 lengths in turn are recorded, given up and
