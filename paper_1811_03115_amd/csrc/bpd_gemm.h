@@ -882,14 +882,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
   int bx, by;                                    // (the map: bpd_tile_map.h)
   ldsx_tile_of(p.lx, gridDim.x, gridDim.y, blockIdx.x, blockIdx.y, blockIdx.z, g, by, bx);
   const int m0 = by * BM;
-  // Row blocks past the rows in use end at once.  Large tiles only: the look costs 0.3 us, which the small tiles, whose
-  // launches live for a few microseconds whatever their rows, would not get back.  (Rows past the end in the last block
-  // are computed for nothing, like all dead rows of the small tiles.)
-  if (MT * NT >= 8 && m0 >= rows_in_use(live, p.M)) return;
+  // (ahead of the return: no row at all may be in use)
   if constexpr (!ARGMAX && !XLN && !STATS && !ROWAFF) {
     if (ln.clear && (blockIdx.x | blockIdx.y | blockIdx.z) == 0)
       for (int i = tid; i < ln.nclear; i += 256) ln.clear[i] = make_uint4(0, 0, 0, 0);
   }
+  // Row blocks past the rows in use end at once.  Large tiles only: the look costs 0.3 us, which the small tiles, whose
+  // launches live for a few microseconds whatever their rows, would not get back.  (Rows past the end in the last block
+  // are computed for nothing, like all dead rows of the small tiles.)
+  if (MT * NT >= 8 && m0 >= rows_in_use(live, p.M)) return;
   const int M = p.M;
   const int nt0 = (bx * 4 + wave) * NT;
   const int lr = lane & 15, lq = lane >> 4;

@@ -237,6 +237,43 @@ def test_captured_steps(k, B, d):
     assert acc[0].tolist() == acc[1].tolist() == [2] * B
 
 
+# Steps past the end of every sequence: no row is in use.  With 98 .. 128 rows the GEMM behind the layers kernel has tiles that then end at once, and still the words that workgroups
+# count in have to be cleared: the next source is decoded as by a context that has seen nothing else.
+@pytest.mark.parametrize("k,B,captured", [(16, 8, False), (14, 7, False), (16, 7, True), (5, 8, False)])
+def test_steps_past_the_end(k, B, captured):
+    from test_gpu_captured import capture
+    cfg = config(k, B, 9, 40)
+    weights = wl.make_weights(cfg)
+    src, n = wl.make_sources(cfg)
+    other = np.where(src > 0, 271 - src, 0).astype(np.int32)
+    budgets = np.full(B, 40, np.int32)
+    sched = np.random.default_rng(k).integers(1, k + 1, (40, B)).astype(np.int32)
+
+    def results(c):
+        c.bpd_encode(other, n, budgets)
+        first = c.bpd_get_state()[0]
+        ids, lens, _ = c.bpd_decode(k, sched)
+        c.bpd_encode(other, n, budgets)
+        c.bpd_step(k, whole)
+        return first, ids, lens, c.bpd_debug_step_logits(k).cpu().numpy()
+
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        whole = torch.full((B,), k, dtype=torch.int32, device="cuda")
+        ctx, ref = gpu_context(cfg, weights), gpu_context(cfg, weights)
+        ctx.bpd_encode(src, n, budgets)
+        if captured:
+            g = capture(stream, lambda: ctx.bpd_step_static(k, whole))
+        else:
+            ctx.bpd_decode(k, sched)
+        for _ in range(6 if captured else 3):
+            g.replay() if captured else ctx.bpd_step(k, whole)
+            ctx.bpd_get_stats()
+        assert ctx.bpd_get_state()[3].all()
+        for got, want in zip(results(ctx), results(ref)):
+            np.testing.assert_array_equal(got, want)
+
+
 # Sources of ragged batches without their padding: lengths that the host has; with lengths on the device the encoder computes the padding, too.  A tile of 16 rows (skinny
 # kernels), one sequence in more room than it needs, tiles with rows of no sequence, widths with and without kernels of constant K, more than 128 keys, more rows than those
 # kernels take.  Both ways the logits are within TOL of the oracle's, so within twice that of each other.
