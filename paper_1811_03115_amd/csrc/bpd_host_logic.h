@@ -161,12 +161,15 @@ constexpr int LEAN_K_WHOLE = 2048;
 constexpr int LEAN_PART_M = 192;        // more rows: the slices of the LDS-staged kernel (192 rows 6.8 against 7.25 us, 256 rows 8.0 against 7.3)
 bool lean_encoder_ok(const bpd_config& c, long M) { return lean_ok(c, M) && (c.d_model <= 512 || M <= LEAN_ENC_WIDE_M_MAX); }
 
-// Rows of the encoder for sources of `tokens` tokens together in B x S places: packed, a multiple of 16, where at least an eighth of the places is padding; otherwise
-// all of them (0).  A packed encode looks up each row's sequence and position: a load ahead of each attention, two at the entry of the GEMMs that store keys and values,
+// Rows of the encoder for sources of `tokens` tokens together in B x S places: packed, where at least an eighth of the places is padding; otherwise all of them (0).
+// A packed encode looks up each row's sequence and position: a load ahead of each attention, two at the entry of the GEMMs that store keys and values,
 // some 0.5 us each of a layer's 25 .. 50, what an eighth of the rows costs.  Whole calls, ms, padded and packed: 13 sequences, 319 of 780 places, d = 512 2.158,
 // 2.066;  32, 1090 of 2240, d = 1024 17.63, 17.39;  5, 250 places 4.690, 4.633.
+// In steps of an eighth of the places (whole row tiles): recorded encodes are found by their rows, and lengths that change from call to call have at most seven of them
+// (in steps of one row tile few of their encodes were recorded: 32 sequences in 4096 places 306 us of host time, 66 so; 5 in 250, d = 768, the first 40 calls 2.64 ms,
+// 2.52;  13 in 780 4.25, 3.85).
 inline int packed_source_rows(long tokens, long places) {
-  const long rows = (tokens + 15) / 16 * 16;
+  const long step = (places + 127) / 128 * 16, rows = (tokens + step - 1) / step * step;
   return rows * 8 <= places * 7 ? (int)rows : 0;
 }
 

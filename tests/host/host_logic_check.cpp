@@ -202,12 +202,17 @@ int main() {
     const bpd_config c = fp32_model(m);
     if (10 * std::min(m[6], m[7]) < 9 * std::max(m[6], m[7])) EXPECT(small_encode_pays(c, m[5]) == (m[6] < m[7]), "encode d %d F %d L %d S %d", m[0], m[1], m[3], m[5]);
   }
-  // packed source rows: whole row tiles that hold every token and are fewer than the places there are (buffers are sized for those)
-  for (long places = 1; places <= 600; ++places)
+  // packed source rows: whole row tiles that hold every token and are fewer than the places there are (buffers are sized for those), and few different numbers of
+  // them, since recorded encodes are found by it
+  for (long places = 1; places <= 600; ++places) {
+    std::set<long> seen;
     for (long tokens = 1; tokens <= places; ++tokens) {
       const long rows = packed_source_rows(tokens, places);
-      EXPECT(rows == 0 || (rows % 16 == 0 && rows >= tokens && rows - tokens < 16 && rows <= places), "packed rows %ld of %ld tokens, %ld places", rows, tokens, places);
+      EXPECT(rows == 0 || (rows % 16 == 0 && rows >= tokens && 8 * rows <= 7 * places), "packed rows %ld of %ld tokens, %ld places", rows, tokens, places);
+      seen.insert(rows);
     }
+    EXPECT(seen.size() <= 8, "%zu numbers of packed rows, %ld places", seen.size(), places);
+  }
   // the tile rule: every answer is a tile the library has, K is a multiple of the chunk depth, the cap on rows is kept
   long tiles = 0;
   for (int M : {17, 20, 33, 48, 64, 80, 100, 128, 153, 252, 320, 512, 1000, 3200, 4096})
