@@ -288,36 +288,9 @@ constexpr long LDSX_MIN_WGS = 440;
 constexpr long LDSX_MIN_WGS_LONGK = 400;   // K >= 2048, fewer than 1024 rows: a workgroup lives long enough that about 1.5 per CU suffice
 // (chosen at 80 .. 320 rows.  Of 64 GEMMs of 700 .. 4096 rows its tile is within 5 % of the best at 37 and within 10 % at 48; worst: 780 x 3072 x 1024 25.8 us, 80 x 128 tiles
 // 15.5; 2240 x 1024 x 4096 50.8, 39.6)
-// A long K and many rows: a tile of 256 columns that gives every CU one workgroup, and hardly more CUs than that, keeps four steps of weights in flight per wave and
-// fetches least per product.  us, the rule above and this: 3584 x 1024 x 4096 47.9, 41.1;  4096 51.6, 43.6;  5000 59.0, 56.9;  6144 73.1, 62.6;  8192 93.1, 72.5;  5000 x 768 x
-// 3072 46.1, 37.2;  6144 50.9, 43.0;  8192 64.1, 52.8.  (K = 2048: 4096 x 1024 31.7, 30.0, but 5000 36.2, 40.9.  Below 220 workgroups the rule above is as good: 4096 x 1024 at
-// 208 47.2, 3000 at 188 53.7 against 39.5.)
-constexpr int LDSX_ONE_ROUND_K = 3072, LDSX_ONE_ROUND_M = 2048;
-constexpr long LDSX_ONE_ROUND_MIN = 220, LDSX_ONE_ROUND_MAX = 256;
-// Several groups with a long K and few rows (the heads' output layers) stream their weights, and what counts are the rounds of one workgroup per CU: us by row tiles and rounds, of
-// 8 and 10 groups of 4096 x 1024 out of memory.  us, by largest useful area and by this: 8 groups, 64 rows 26.1, 22.7;  80 33.2, 23.9;  104 35.2, 29.4;  130 46.0, 33.4;  10 groups,
-// 64 rows 36.9, 30.7;  80 35.6, 28.0;  130 37.3, 33.3;  2048 x 512, 10 groups, 104 rows 12.6, 10.4.  (Two groups or K slices: not measured.)
-constexpr int LDSX_ROUNDS_M = 144;
-inline int ldsx_rounds_cost(int mt, long wgs) {
-  constexpr int us[3][4] = {{190, 235, 340, 430}, {225, 290, 365, 440}, {239, 334, 430, 530}};
-  const long r = (wgs + 255) / 256;
-  return r <= 4 ? us[mt - 1][r - 1] : us[mt - 1][3] + (int)(r - 4) * 100;
-}
-void pick_tile(int M, int N, int K, long zdim, int& mt, int& nt, int mt_max = 8) {
+// The largest useful area that fills the chip
+void pick_tile_by_area(int M, int N, int K, long zdim, int& mt, int& nt, int mt_max) {
   const int mts[7] = {8, 7, 5, 4, 3, 2, 1};
-  if (zdim > 2 && K >= 2048 && K % 256 == 0 && M > 16 && M <= LDSX_ROUNDS_M && mt_max >= 3) {
-    int best = 0;
-    for (int m : {1, 2, 3}) {
-      const int c = ldsx_rounds_cost(m, (long)((M + 16 * m - 1) / (16 * m)) * ((N / 16 + 3) / 4) * zdim);
-      if (best == 0 || c < best) { best = c; mt = m; nt = 1; }
-    }
-    return;
-  }
-  if (K >= LDSX_ONE_ROUND_K && K % 128 == 0 && M >= LDSX_ONE_ROUND_M && zdim == 1 && mt_max >= 8)
-    for (int m : {8, 7, 5, 4}) {
-      const long wgs = (long)((M + 16 * m - 1) / (16 * m)) * ((N / 16 + 15) / 16);
-      if (wgs >= LDSX_ONE_ROUND_MIN && wgs <= LDSX_ONE_ROUND_MAX) { mt = m; nt = 4; return; }
-    }
   long best_area = 0, best_pad = 0;
   mt = 1; nt = (K % 256 == 0) ? 1 : 4;
   for (int n : {1, 2, 4}) {
@@ -335,7 +308,43 @@ void pick_tile(int M, int N, int K, long zdim, int& mt, int& nt, int mt_max = 8)
     }
   }
 }
-
+// A long K and many rows: a tile of 256 columns that gives every CU one workgroup, and hardly more CUs than that, keeps four steps of weights in flight per wave and
+// fetches least per product.  us, the rule above and this: 3584 x 1024 x 4096 47.9, 41.1;  4096 51.6, 43.6;  5000 59.0, 56.9;  6144 73.1, 62.6;  8192 93.1, 72.5;  5000 x 768 x
+// 3072 46.1, 37.2;  6144 50.9, 43.0;  8192 64.1, 52.8.  (K = 2048: 4096 x 1024 31.7, 30.0, but 5000 36.2, 40.9.  Below 220 workgroups the rule above is as good: 4096 x 1024 at
+// 208 47.2, 3000 at 188 53.7 against 39.5.)
+constexpr int LDSX_ONE_ROUND_K = 3072, LDSX_ONE_ROUND_M = 2048;
+constexpr long LDSX_ONE_ROUND_MIN = 220, LDSX_ONE_ROUND_MAX = 256;
+// Several groups with a long K and few rows (the heads' output layers) stream their weights, and what counts are the rounds of one workgroup per CU: us by row tiles and rounds, of
+// 8 and 10 groups of 4096 x 1024 out of memory.  us, by largest useful area and by this: 8 groups, 64 rows 26.1, 22.7;  80 33.2, 23.9;  104 35.2, 29.4;  130 46.0, 33.4;  10 groups,
+// 64 rows 36.9, 30.7;  80 35.6, 28.0;  130 37.3, 33.3;  2048 x 512, 10 groups, 104 rows 12.6, 10.4.  (Two groups: not measured.)  Up to 256 column blocks of 64 in all groups
+// together: of 427 of 3 .. 16 groups, K 2048 .. 4096, N 256 .. 2048, 17 .. 144 rows, that come out otherwise, 344 are faster by more than 2 % (4096 x 1024, 16 groups, 144 rows 92.7, 49.1),
+// 47 slower, by up to 8 %, at 280 .. 360 workgroups of 16 rows (3 groups, 96 rows 18.8, 20.2).  More column blocks have tiles of 32 rows or more and 128 columns, two to a CU in one
+// round, where the map deals whole groups to XCDs (ldsx_map_of): those are kept: 4096 x 2048, 16 groups, 64 rows 55.6, by rounds 65.6;  128 rows 69.3, 88.3;  6144 x 1536, 12
+// groups, 96 rows 63.3, 74.1.  (The map does not: 13 groups, 96 rows 124.9, by rounds 79.5.  More than one round: 4096 x 2048, 12 groups, 96 rows 69.7, 54.8.)
+constexpr int LDSX_ROUNDS_M = 144, LDSX_ROUNDS_COLS = 256;
+inline int ldsx_rounds_cost(int mt, long wgs) {
+  constexpr int us[3][4] = {{190, 235, 340, 430}, {225, 290, 365, 440}, {239, 334, 430, 530}};
+  const long r = (wgs + 255) / 256;
+  return r <= 4 ? us[mt - 1][r - 1] : us[mt - 1][3] + (int)(r - 4) * 100;
+}
+void pick_tile(int M, int N, int K, long zdim, int& mt, int& nt, int mt_max = 8) {
+  pick_tile_by_area(M, N, K, zdim, mt, nt, mt_max);
+  if (zdim > 2 && K >= 2048 && K % 256 == 0 && M > 16 && M <= LDSX_ROUNDS_M && mt_max >= 3) {
+    const long wide = (N / 16 + 7) / 8;
+    if ((N / 16 + 3) / 4 * zdim > LDSX_ROUNDS_COLS && nt == 2 && mt >= 2 && (M + 16 * mt - 1) / (16 * mt) * wide * zdim <= 2 * LDSX_ROUNDS_COLS && wide % 2 == 0 && wide / 2 * zdim % 8 == 0) return;
+    int best = 0;
+    for (int m : {1, 2, 3}) {
+      const int c = ldsx_rounds_cost(m, (long)((M + 16 * m - 1) / (16 * m)) * ((N / 16 + 3) / 4) * zdim);
+      if (best == 0 || c < best) { best = c; mt = m; nt = 1; }
+    }
+    return;
+  }
+  if (K >= LDSX_ONE_ROUND_K && K % 128 == 0 && M >= LDSX_ONE_ROUND_M && zdim == 1 && mt_max >= 8)
+    for (int m : {8, 7, 5, 4}) {
+      const long wgs = (long)((M + 16 * m - 1) / (16 * m)) * ((N / 16 + 15) / 16);
+      if (wgs >= LDSX_ONE_ROUND_MIN && wgs <= LDSX_ONE_ROUND_MAX) { mt = m; nt = 4; return; }
+    }
+}
 
 // In-place residual update with a long K and few output tiles on the LDS-staged kernel: the number of K slices it is
 // split into (1: not split): the fewest with which a tile of at least 48 rows still fills the chip; if no slicing gets

@@ -4,6 +4,7 @@
 // the launches write into them; the tile rule only returns tiles the library instantiates.
 // Built by tests/test_host_logic.py with the system compiler under -fsanitize=address,undefined.
 #include <algorithm>
+#include <array>
 #include <cstdio>
 #include <cstdlib>
 #include <random>
@@ -228,6 +229,13 @@ int main() {
             EXPECT(!(nt == 4 && mt >= 4) || K % 128 == 0, "deep tile %d x %d with K = %d", mt, nt, K);
             ++tiles;
           }
+  // many groups of many columns: tiles of 128 columns where one round of them fills the chip and the map deals whole groups to XCDs (groups, rows, N, tile)
+  for (auto& w : {std::array<int, 5>{16, 60, 2048, 2, 2}, {16, 104, 2048, 4, 2}, {16, 144, 2048, 5, 2}, {10, 96, 2048, 2, 2}, {10, 128, 2048, 3, 2}, {12, 96, 1536, 2, 2},
+                  {12, 96, 2048, 3, 1}, {13, 96, 1536, 3, 1}, {14, 96, 1536, 3, 1}}) {
+    int mt = 0, nt = 0;
+    pick_tile(w[1], w[2], 4096, w[0], mt, nt);
+    EXPECT(mt == w[3] && nt == w[4], "tile %d x %d of %d rows, %d groups of %d columns", mt, nt, w[1], w[0], w[2]);
+  }
   // the workgroup -> tile map of the LDS-staged GEMM: every (group, row block, column block) of a grid exactly once,
   // for one group, K slices in z, and several groups (with and without the grouped map)
   long grids = 0;
