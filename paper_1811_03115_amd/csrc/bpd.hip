@@ -1710,7 +1710,7 @@ int bpd_encode(bpd_ctx* ctx, const int32_t* src_ids, const int32_t* src_len, con
   if (staged && host_len && kv_grouped(c) && attention_nsplit(ctx, S, B, S, 0) == 1) {
     long tokens = 0;
     for (int b = 0; b < B; ++b) { h_first[b] = (int)tokens; tokens += h_len[b]; }
-    packed = PackP{h_first, packed_source_rows(tokens, (long)B * S), L.src_row0, L.src_seq, L.src_pos, L.src_packed};
+    packed = PackP{h_first, packed_source_rows(c, tokens, (long)B * S), L.src_row0, L.src_seq, L.src_pos, L.src_packed};
   }
   for (int b = 0; b < B; ++b) ctx->remaining[b] = !max_len ? c.max_out_len : (host_max ? max_len[b] : -1);
   {

@@ -161,16 +161,25 @@ constexpr int LEAN_K_WHOLE = 2048;
 constexpr int LEAN_PART_M = 192;        // more rows: the slices of the LDS-staged kernel (192 rows 6.8 against 7.25 us, 256 rows 8.0 against 7.3)
 bool lean_encoder_ok(const bpd_config& c, long M) { return lean_ok(c, M) && (c.d_model <= 512 || M <= LEAN_ENC_WIDE_M_MAX); }
 
-// Rows of the encoder for sources of `tokens` tokens together in B x S places: packed, where at least an eighth of the places is padding; otherwise all of them (0).
-// A packed encode looks up each row's sequence and position: a load ahead of each attention, two at the entry of the GEMMs that store keys and values,
-// some 0.5 us each of a layer's 25 .. 50, what an eighth of the rows costs.  Whole calls, ms, padded and packed: 13 sequences, 319 of 780 places, d = 512 2.158,
-// 2.066;  32, 1090 of 2240, d = 1024 17.63, 17.39;  5, 250 places 4.690, 4.633.
-// In steps of an eighth of the places (whole row tiles): recorded encodes are found by their rows, and lengths that change from call to call have at most seven of them
+// Rows of the encoder for sources of `tokens` tokens together in B x S places: packed, where that pays; otherwise all of them (0).
+// A packed encode looks up each row's sequence and position: a load ahead of each attention, two at the entry of the GEMMs that store keys and values, some 0.5 us
+// each.  Whole calls, ms, padded and packed: 13 sequences, 319 of 780 places, d = 512 2.158, 2.066;  32, 1090 of 2240, d = 1024 17.63, 17.39;  5, 250 places
+// 4.690, 4.633.  Encodes of 64 .. 8192 places, 30 .. 84 % of them tokens, us, padded and packed:
+//   d = 1024  seven eighths of the places and less: 960 places, 589 tokens 843, 772;  512, 442 687, 671.  Slower where the tiles of so many rows are poor ones: 1120 of 1280 rows
+//             996, 1013 (d = 768 740, 786), 3584 of 4096 1643, 1664, 96 of 120 428, 433
+//   d = 512   as fast or faster below seven eighths (960, 589 448, 429), at seven eighths the tiles decide (1120 of 1280 rows 542, 564;  1568 of 1792 588, 625;  2688 of 3072 752, 711)
+//   narrower  layers too short for the lookups: d = 384, 768, 440 654, 673;  256, 162 486, 501;  d = 128, 2048, 1146 324, 335;  d = 64, 1024, 587 365, 370.  It pays
+//             with many places (d = 384, 2048, 1146 758, 695;  d = 256, 2048, 1146 401, 363;  d = 128, 4096, 2266 382, 345) and where the padding alone is beyond the
+//             kernels of constant K (d = 128, 768, 566 307, 249;  d = 256, 768, 566 319, 302)
+// In steps of an eighth of the places: recorded encodes are found by their rows, and lengths that change from call to call have at most seven of them
 // (in steps of one row tile few of their encodes were recorded: 32 sequences in 4096 places 306 us of host time, 66 so; 5 in 250, d = 768, the first 40 calls 2.64 ms,
-// 2.52;  13 in 780 4.25, 3.85).
-inline int packed_source_rows(long tokens, long places) {
-  const long step = (places + 127) / 128 * 16, rows = (tokens + step - 1) / step * step;
-  return rows * 8 <= places * 7 ? (int)rows : 0;
+// 2.52;  13 in 780 4.25, 3.85).  Whole pairs of row tiles, which is what the GEMMs of some hundred rows walk in: d = 1024, 544 rows 760 us, 560 849, 576 761, all 800 places 824.
+constexpr long PACKED_NARROW_PLACES = 1L << 19;      // places x d_model from which on packing pays below d = 512
+inline int packed_source_rows(const bpd_config& c, long tokens, long places) {
+  const long step = (places + 127) / 128 * 16, rows = ((tokens + step - 1) / step * step + 31) / 32 * 32;
+  if (c.d_model > 512 ? rows * 8 > places * 7 : rows * 8 >= places * 7) return 0;
+  const bool narrow = c.d_model < 512 && places * c.d_model < PACKED_NARROW_PLACES;
+  return narrow && !(lean_encoder_ok(c, rows) && !lean_encoder_ok(c, places)) ? 0 : (int)rows;
 }
 
 // Other decoder blocks of more than 128 rows run their LayerNorm-then-GEMM pairs as one GEMM on weights with the LayerNorm
