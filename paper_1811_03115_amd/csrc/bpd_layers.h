@@ -60,7 +60,7 @@ struct LayersP {
   float eps, scale;
   int local_q, local_m;
   bf16_t* xn; float* slices;                     // normalised rows, copies per XCD; tall_layers_kernel: the second FFN layer's K slices between layers (of the last: part)
-  unsigned* sync;                                // [LK_WORDS], zero at the start of a launch (the LayerNorm behind it clears it)
+  unsigned* sync;                                // [LK_WORDS], zero at the start of a launch (cleared by the next kernel: the LayerNorm or the GEMM of the heads' hidden layers)
   long long* error;                              // set to 1 if a wait ran out
 };
 

@@ -3,7 +3,7 @@
 
 constexpr int LK_PLACES = 32, LK_XCDS = 16, LK_JOBS = 8;
 constexpr int LK_CTL = 32, LK_FLAGS = 64, LK_AREA = 192;        // words of an XCD's area: [0] registered; members, then jobs; flags [wave][member]
-constexpr int LK_NEXT_JOB = LK_XCDS * LK_AREA, LK_WORDS = LK_NEXT_JOB + 768;      // (the wide kernel needs as many)
+constexpr int LK_NEXT_JOB = LK_XCDS * LK_AREA, LK_WORDS = LK_NEXT_JOB + 32;
 // Slots of a job: they are dealt evenly to at most LK_JOBS of them, and a job holds at most 16 rows of four slots
 inline int layers_per_job(int slots) { return (slots + LK_JOBS - 1) / LK_JOBS; }
 inline bool layers_fit(int slots, int R) { return layers_per_job(slots) <= LK_PLACES / 8 && layers_per_job(slots) * R <= 16; }

@@ -16,7 +16,7 @@
 #pragma once
 
 constexpr int TK_ROWS = TALL_LAYERS_ROWS;        // rows of the XCD's copies of normalised rows
-constexpr int WK_NORM = WK_HEADS;                // flags of the rows that the XCD's waves normalise (the heads' words are free: eight slots do not use them)
+static_assert(WK_NORM + TK_ROWS <= WK_AREA, "a flag per row");
 enum { TK_DOWN = WK_DOWN };
 
 struct TkPlaces {

@@ -28,7 +28,7 @@ constexpr int WK_HOLD = 40, WK_GAP = 1;           // pauses of the compute waves
 // Blocks of more rows than this share what is normalised: see stage_norm (128 tokens of ten rows a step: 5.1 ms, 5.5 with every member normalising all; greedy: 5.0 ms,
 // 5.2 shared)
 constexpr int WK_ROWS_ALONE = 4;
-constexpr int WK_XCDS = 8, WK_CENSUS = 32, WK_GLOBAL = 64, WK_LOCAL = 96, WK_HEADS = 224, WK_AREA = 480;      // words of an XCD's area: [0] registered; members of each XCD; its operators done; flags [wave][member]; heads [XCD] [slot][head], a line each XCD
+constexpr int WK_XCDS = 8, WK_CENSUS = 32, WK_GLOBAL = 64, WK_LOCAL = 96, WK_NORM = 224, WK_AREA = 288;      // words of an XCD's area: [0] registered; members of each XCD; its operators done; flags [wave][member]; flags of the rows that its waves normalise (tall_layers_kernel)
 static_assert(WK_XCDS * WK_AREA <= LK_WORDS, "both kernels count in the same words");
 
 __device__ __forceinline__ void wk_store4(unsigned* p, unsigned v) { asm volatile("global_store_dword %0, %1, off sc1" ::"v"(p), "v"(v) : "memory"); }
