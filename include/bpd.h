@@ -30,7 +30,7 @@
  * Contexts on streams of their own may decode at the same time.  A kernel of all decoder layers
  * (blocks of few rows, d_model 512 with d_ff 2048 or 1024 with 4096) takes all CUs, so that such
  * contexts then take turns.  At d_model 1024 kernel by kernel is the faster way for two or more
- * that are busy at once (one sentence each: two 8.6 instead of 10.6 ms, four 12.3 instead of 18):
+ * that are busy at once (one sentence each: two 8.5 instead of 9.2 ms, four 12.3 instead of 17):
  * a context that is created with BPD_LAYERS_GROUP=0 in the environment goes that way throughout.
  *
  * Pointer arguments marked [host|device] may be either; arguments marked [device] are

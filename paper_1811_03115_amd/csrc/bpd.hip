@@ -609,7 +609,8 @@ bool attention_qproj_ok(const bpd_ctx* ctx, int B, int R) {
          c.n_heads * B <= ATTN_QPROJ_MAX_WGS && attention_nsplit(ctx, c.max_src_len, B, R, 0) == 1;
 }
 
-constexpr int ATTN_TILES_MIN = 1024;             // (row tile, head, sequence) triples from which on a wave takes whole ones: 4096 gain 8 us of 21, 320 lose 1 of 5
+constexpr int ATTN_TILES_MIN = 1024;             // (row tile, head, sequence) triples from which on a wave takes whole ones: 4096 gain 8 us of 21, 320 lose 1 of 5.  Packed
+                                                 // rows: of the padded shape, of which 0.3 .. 0.8 are there; encodes so and dealt to waves, us: 624 of 1024 858, 861;  640 of 1280 515, 513;  2288 of 5120 1391, 1400
 void attention(bpd_ctx* ctx, const float* Q, const void* Kc, const void* Vc, void* out, int cap,
                int B, int R, const int* limit, int causal, const int* seq, const QProjP* qproj = nullptr, const int* row0 = nullptr) {
   const long kv_seq_stride = (long)cap * ctx->cfg.d_model;

@@ -325,7 +325,8 @@ constexpr int LDSX_ONE_ROUND_K = 3072, LDSX_ONE_ROUND_M = 2048;
 constexpr long LDSX_ONE_ROUND_MIN = 220, LDSX_ONE_ROUND_MAX = 256;
 // Several groups with a long K and few rows (the heads' output layers) stream their weights, and what counts are the rounds of one workgroup per CU: us by row tiles and rounds, of
 // 8 and 10 groups of 4096 x 1024 out of memory.  us, by largest useful area and by this: 8 groups, 64 rows 26.1, 22.7;  80 33.2, 23.9;  104 35.2, 29.4;  130 46.0, 33.4;  10 groups,
-// 64 rows 36.9, 30.7;  80 35.6, 28.0;  130 37.3, 33.3;  2048 x 512, 10 groups, 104 rows 12.6, 10.4.  (Two groups: not measured.)  Up to 256 column blocks of 64 in all groups
+// 64 rows 36.9, 30.7;  80 35.6, 28.0;  130 37.3, 33.3;  2048 x 512, 10 groups, 104 rows 12.6, 10.4.  (Two groups: not measured.)  K slices of 2048 or more go by it, too: six layers of d = 1024, d_ff = 8192, 130 rows 438, 420, in four slices of
+// 48-row tiles instead of eight of 32;  d_ff = 16384 578, 548;  d = 2048, d_ff = 8192 783, 744;  other sliced blocks of 24 .. 144 rows the same.  Up to 256 column blocks of 64 in all groups
 // together: of 427 of 3 .. 16 groups, K 2048 .. 4096, N 256 .. 2048, 17 .. 144 rows, that come out otherwise, 344 are faster by more than 2 % (4096 x 1024, 16 groups, 144 rows 92.7, 49.1),
 // 47 slower, by up to 8 %, at 280 .. 360 workgroups of 16 rows (3 groups, 96 rows 18.8, 20.2).  More column blocks have tiles of 32 rows or more and 128 columns, two to a CU in one
 // round, where the map deals whole groups to XCDs (ldsx_map_of): those are kept: 4096 x 2048, 16 groups, 64 rows 55.6, by rounds 65.6;  128 rows 69.3, 88.3;  6144 x 1536, 12

@@ -2,8 +2,8 @@
 // bpd_kernels.h.
 //
 // A layer is seven dependent operators.  As kernels of their own each costs 2.5 .. 6 us, of which a launch that does nothing is 1.7;
-// the workgroups of one XCD share an L2, and there a hand-over (store, acknowledgement, a flag; a poll that sees it) takes 0.3 us
-// one way (690 cycles; between XCDs 950, with the data written through to memory).  Six layers of 8 rows, 40 keys, 32 source tokens: 156 us
+// the workgroups of one XCD share an L2, and there a hand-over takes 0.3 us one way even by a flag (store, acknowledgement, the flag, a poll that sees it: 690 cycles;
+// between XCDs 950, with the data written through to memory), less where the result itself is polled for (Memory, below).  Six layers of 8 rows, 40 keys, 32 source tokens: 156 us
 // as 42 kernels, 80 us here; eight such blocks on eight XCDs 90 us (chain of kernels over 64 rows: 200 us).  What bounds it now is the chain within
 // an operator: a load of lines that another CU has just written (550 .. 900 cycles), LayerNorm or softmax at one wave
 // per SIMD (4 cycles an instruction), LDS twice: 1.1 .. 2.9 us each.
@@ -14,11 +14,11 @@
 //
 // A group forms itself: a workgroup registers with the XCD that it finds itself on and the first 32 to come are members.
 // If fewer have come LK_CLOSE_TICKS after the first (CUs held by other launches), the group closes with those and they share the places out (six layers
-// of 8 rows by members, us: 32 92, 31 118, 16 119, 8 168).
+// of 8 rows by members, by events, us: 32 84, 31 111, 16 111, 8 161).
 // So whoever waits waits for a workgroup that is running: no residency of the whole grid is assumed, launches on several
 // streams cannot block each other, and the mapping of workgroups to XCDs matters for speed only.  Groups fetch jobs until none is left.
 // What launches on several streams do is take turns, since a workgroup fills its CU: decodes of one sentence, ms, chains of kernels and this: one context 3.8,
-// 2.7, two 4.3, 3.1, four 5.9, 5.3; bpd_wide_layers.h, d = 1024: 6.3, 5.5; 8.6, 10.6; 12.3, 18.2 (BPD_LAYERS_GROUP=0 at creation: a context of chains).
+// 2.5, two 4.2, 3.1, four 5.8, 5.1; bpd_wide_layers.h, d = 1024: 6.3, 5.2; 8.5, 9.2; 12.3, 17.1 (BPD_LAYERS_GROUP=0 at creation: a context of chains).
 //
 // Inside a workgroup.  Four compute waves hold weights, K split over them; four helper waves poll for the operator's input, stage it in
 // LDS (through LayerNorm where it has one), add the compute waves' partial sums, store the results and do the

@@ -20,11 +20,11 @@
 //
 // Members register as in bpd_layers.h.  The first on each XCD closes its list when 32 have come or LK_CLOSE_TICKS have passed, and tells all XCDs
 // how many there are; an XCD where nobody has come is closed by others.  Fewer than 256 members share the places out, fetch weights as
-// they go and hand everything over through memory (six layers of 10 rows by members per XCD, us: 32 154, 31 169, 16 233, 8 368; seven XCDs of 32 287; bpd_tall_layers.h,
-// 40 rows: 193, 390, 412, 595; 480).
+// they go and hand everything over through memory (six layers of 10 rows by members per XCD, by events, us: 32 135, 31 155, 16 220, 8 357; seven XCDs of 32 308, which includes
+// 60 until the eighth is given up (288 when flags were polled: whoever normalises all rows asks memory for them, round after round); bpd_tall_layers.h, 40 rows: 181, 360, 370, 559; 454).
 #pragma once
 
-constexpr int WK_HOLD = 40, WK_GAP = 1;           // pauses of the compute waves, as LK_HOLD and LK_GAP (six layers of 10 rows: hold 12: 151 us, 24: 150, 40: 147, 64: 149, 90: 150)
+constexpr int WK_HOLD = 40, WK_GAP = 1;           // pauses of the compute waves, as LK_HOLD and LK_GAP (hold 12 .. 64: within 1 us of each other at 1 x 1, 1 x 10, 5 x 8, 8 x 8 and 16 x 4 rows)
 // Blocks of more rows than this share what is normalised: see stage_norm (128 tokens of ten rows a step: 5.1 ms, 5.5 with every member normalising all; greedy: 5.0 ms,
 // 5.2 shared)
 constexpr int WK_ROWS_ALONE = 4;
