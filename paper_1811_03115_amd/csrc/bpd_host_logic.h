@@ -171,12 +171,13 @@ bool lean_encoder_ok(const bpd_config& c, long M) { return lean_ok(c, M) && (c.d
 //   narrower  layers too short for the lookups: d = 384, 768, 440 654, 673;  256, 162 486, 501;  d = 128, 2048, 1146 324, 335;  d = 64, 1024, 587 365, 370.  It pays
 //             with many places (d = 384, 2048, 1146 758, 695;  d = 256, 2048, 1146 401, 363;  d = 128, 4096, 2266 382, 345) and where the padding alone is beyond the
 //             kernels of constant K (d = 128, 768, 566 307, 249;  d = 256, 768, 566 319, 302)
-// In steps of an eighth of the places: recorded encodes are found by their rows, and lengths that change from call to call have at most seven of them
+// In steps of a sixteenth of the places: recorded encodes are found by their rows, and lengths that change from call to call have at most fourteen of them, mostly two to six
 // (in steps of one row tile few of their encodes were recorded: 32 sequences in 4096 places 306 us of host time, 66 so; 5 in 250, d = 768, the first 40 calls 2.64 ms,
-// 2.52;  13 in 780 4.25, 3.85).  Whole pairs of row tiles, which is what the GEMMs of some hundred rows walk in: d = 1024, 544 rows 760 us, 560 849, 576 761, all 800 places 824.
+// 2.52;  13 in 780 4.25, 3.85;  in steps of an eighth more rows are computed for nothing: encodes of 13 in 780 357 us, so 349, of 32 in 4096 1283, 1265, of 24 in 1440, where the
+// tiles decide, 440, 448).  Whole pairs of row tiles, which is what the GEMMs of some hundred rows walk in: d = 1024, 544 rows 760 us, 560 849, 576 761, all 800 places 824.
 constexpr long PACKED_NARROW_PLACES = 1L << 19;      // places x d_model from which on packing pays below d = 512
 inline int packed_source_rows(const bpd_config& c, long tokens, long places) {
-  const long step = (places + 127) / 128 * 16, rows = ((tokens + step - 1) / step * step + 31) / 32 * 32;
+  const long step = (places + 255) / 256 * 16, rows = ((tokens + step - 1) / step * step + 31) / 32 * 32;
   if (c.d_model > 512 ? rows * 8 > places * 7 : rows * 8 >= places * 7) return 0;
   const bool narrow = c.d_model < 512 && places * c.d_model < PACKED_NARROW_PLACES;
   return narrow && !(lean_encoder_ok(c, rows) && !lean_encoder_ok(c, places)) ? 0 : (int)rows;
