@@ -167,19 +167,21 @@ bool lean_encoder_ok(const bpd_config& c, long M) { return lean_ok(c, M) && (c.d
 // 4.690, 4.633.  Encodes of 64 .. 8192 places, 30 .. 84 % of them tokens, us, padded and packed:
 //   d = 1024  seven eighths of the places and less: 960 places, 589 tokens 843, 772;  512, 442 687, 671.  Slower where the tiles of so many rows are poor ones: 1120 of 1280 rows
 //             996, 1013 (d = 768 740, 786), 3584 of 4096 1643, 1664, 96 of 120 428, 433
-//   d = 512   as fast or faster below seven eighths (960, 589 448, 429), at seven eighths the tiles decide (1120 of 1280 rows 542, 564;  1568 of 1792 588, 625;  2688 of 3072 752, 711)
+//   d = 512   as fast or faster below seven eighths (960, 589 448, 429), at seven eighths the tiles decide (1120 of 1280 rows 542, 564;  1568 of 1792 588, 625;  2688 of 3072 752, 711).
+//             Up to 128 places, where a row tile less saves nothing, below three quarters (96 of 128 rows 240, 242;  64 of 128 251, 246)
 //   narrower  layers too short for the lookups: d = 384, 768, 440 654, 673;  256, 162 486, 501;  d = 128, 2048, 1146 324, 335;  d = 64, 1024, 587 365, 370.  It pays
 //             with many places (d = 384, 2048, 1146 758, 695;  d = 256, 2048, 1146 401, 363;  d = 128, 4096, 2266 382, 345) and where the padding alone is beyond the
 //             kernels of constant K (d = 128, 768, 566 307, 249;  d = 256, 768, 566 319, 302)
+//   d = 640, 896   (wider, but without kernels of constant K) as the narrower ones: by rows of 384 places, 160: 6, 3 % slower, 288: 7, 3, 320: 6, 6;  of 1024, d = 640, 512: 6 % faster
 // In steps of a sixteenth of the places: recorded encodes are found by their rows, and lengths that change from call to call have at most fourteen of them, mostly two to six
 // (in steps of one row tile few of their encodes were recorded: 32 sequences in 4096 places 306 us of host time, 66 so; 5 in 250, d = 768, the first 40 calls 2.64 ms,
 // 2.52;  13 in 780 4.25, 3.85;  in steps of an eighth more rows are computed for nothing: encodes of 13 in 780 357 us, so 349, of 32 in 4096 1283, 1265, of 24 in 1440, where the
 // tiles decide, 440, 448).  Whole pairs of row tiles, which is what the GEMMs of some hundred rows walk in: d = 1024, 544 rows 760 us, 560 849, 576 761, all 800 places 824.
-constexpr long PACKED_NARROW_PLACES = 1L << 19;      // places x d_model from which on packing pays below d = 512
+constexpr long PACKED_NARROW_PLACES = 1L << 19;      // places x d_model from which on packing pays for them
 inline int packed_source_rows(const bpd_config& c, long tokens, long places) {
   const long step = (places + 255) / 256 * 16, rows = ((tokens + step - 1) / step * step + 31) / 32 * 32;
-  if (c.d_model > 512 ? rows * 8 > places * 7 : rows * 8 >= places * 7) return 0;
-  const bool narrow = c.d_model < 512 && places * c.d_model < PACKED_NARROW_PLACES;
+  if (c.d_model > 512 ? rows * 8 > places * 7 : rows * 8 >= places * (places <= 128 ? 6 : 7)) return 0;
+  const bool narrow = (c.d_model < 512 || (c.d_model < 1024 && !lean_width(c.d_model))) && places * c.d_model < PACKED_NARROW_PLACES;
   return narrow && !(lean_encoder_ok(c, rows) && !lean_encoder_ok(c, places)) ? 0 : (int)rows;
 }
 

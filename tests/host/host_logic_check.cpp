@@ -204,9 +204,9 @@ int main() {
     if (10 * std::min(m[6], m[7]) < 9 * std::max(m[6], m[7])) EXPECT(small_encode_pays(c, m[5]) == (m[6] < m[7]), "encode d %d F %d L %d S %d", m[0], m[1], m[3], m[5]);
   }
   // packed source rows: whole pairs of row tiles that hold every token and are fewer than the places there are (buffers are sized for those), and few different
-  // numbers of them, since recorded encodes are found by it; up to d = 512 fewer than seven eighths, below that only of many places or where the padding is
-  // beyond the kernels of constant K
-  for (int d : {64, 128, 384, 512, 768, 1024}) {
+  // numbers of them, since recorded encodes are found by it; up to d = 512 fewer than seven eighths (of up to 128 places: three quarters), for narrow widths and those without
+  // kernels of constant K only of many places or where the padding is beyond those kernels
+  for (int d : {64, 128, 384, 512, 640, 768, 1024}) {
     bpd_config c{};
     c.d_model = d; c.d_ff = 4 * d; c.n_heads = d / 64; c.dtype = BPD_BF16;
     for (long places : {1L, 31L, 32L, 33L, 40L, 64L, 120L, 250L, 256L, 528L, 768L, 800L, 1280L, 1365L, 1366L, 2240L, 4096L, 8192L}) {
@@ -214,12 +214,12 @@ int main() {
       for (long tokens = 1; tokens <= places; ++tokens) {
         const long rows = packed_source_rows(c, tokens, places);
         EXPECT(rows == 0 || (rows % 32 == 0 && rows >= tokens && 8 * rows <= 7 * places), "packed rows %ld of %ld tokens, %ld places", rows, tokens, places);
-        EXPECT(rows == 0 || d > 512 || 8 * rows < 7 * places, "d %d, packed rows %ld of %ld places", d, rows, places);
-        EXPECT(rows == 0 || d >= 512 || places * d >= 1L << 19 || (rows <= 640 && places > 640 && d != 64 && d != 384), "d %d, packed rows %ld of %ld places", d, rows, places);
+        EXPECT(rows == 0 || d > 512 || 8 * rows < (places <= 128 ? 6 : 7) * places, "d %d, packed rows %ld of %ld places", d, rows, places);
+        EXPECT(rows == 0 || (d >= 512 && d != 640) || places * d >= 1L << 19 || (rows <= 640 && places > 640 && d == 128), "d %d, packed rows %ld of %ld places", d, rows, places);
         seen.insert(rows);
       }
       EXPECT(seen.size() <= 15, "%zu numbers of packed rows, %ld places", seen.size(), places);
-      EXPECT(seen.size() > 1 || places <= 40 || (d < 512 && places * d < 1L << 19 && (places <= 640 || d == 64 || d == 384)), "d %d, nothing packed of %ld places", d, places);
+      EXPECT(seen.size() > 1 || places <= 42 || ((d < 512 || d == 640) && places * d < 1L << 19 && (places <= 640 || d != 128)), "d %d, nothing packed of %ld places", d, places);
     }
   }
   // the tile rule: every answer is a tile the library has, K is a multiple of the chunk depth, the cap on rows is kept
