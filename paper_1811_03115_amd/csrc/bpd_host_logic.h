@@ -173,12 +173,15 @@ bool lean_encoder_ok(const bpd_config& c, long M) { return lean_ok(c, M) && (c.d
 //             with many places (d = 384, 2048, 1146 758, 695;  d = 256, 2048, 1146 401, 363;  d = 128, 4096, 2266 382, 345) and where the padding alone is beyond the
 //             kernels of constant K (d = 128, 768, 566 307, 249;  d = 256, 768, 566 319, 302)
 //   d = 640, 896   (wider, but without kernels of constant K) as the narrower ones: by rows of 384 places, 160: 6, 3 % slower, 288: 7, 3, 320: 6, 6;  of 1024, d = 640, 512: 6 % faster
-// In steps of a sixteenth of the places: recorded encodes are found by their rows, and lengths that change from call to call have at most fourteen of them, mostly two to six
+//   one row tile   goes through the kernels for it: d = 384, 28 places 463, 407;  d = 640, 24 568, 481;  d = 512, 42 231, 228;  d = 1024, 42 364, 335, but 28 333, 327, with d_ff 8192
+//             579, 588;  d = 64, 128, 256, 39 306, 325;  191, 193;  218, 220
+// In steps of a sixteenth of the places: recorded encodes are found by their rows, and lengths that change from call to call have at most fifteen of them, mostly two to six
 // (in steps of one row tile few of their encodes were recorded: 32 sequences in 4096 places 306 us of host time, 66 so; 5 in 250, d = 768, the first 40 calls 2.64 ms,
 // 2.52;  13 in 780 4.25, 3.85;  in steps of an eighth more rows are computed for nothing: encodes of 13 in 780 357 us, so 349, of 32 in 4096 1283, 1265, of 24 in 1440, where the
 // tiles decide, 440, 448).  Whole pairs of row tiles, which is what the GEMMs of some hundred rows walk in: d = 1024, 544 rows 760 us, 560 849, 576 761, all 800 places 824.
 constexpr long PACKED_NARROW_PLACES = 1L << 19;      // places x d_model from which on packing pays for them
 inline int packed_source_rows(const bpd_config& c, long tokens, long places) {
+  if (tokens <= 16 && c.d_model > 256 && (places > 32 || (places > 18 && c.d_model < 1024 && !lean_width(c.d_model)))) return 16;
   const long step = (places + 255) / 256 * 16, rows = ((tokens + step - 1) / step * step + 31) / 32 * 32;
   if (c.d_model > 512 ? rows * 8 > places * 7 : rows * 8 >= places * (places <= 128 ? 6 : 7)) return 0;
   const bool narrow = (c.d_model < 512 || (c.d_model < 1024 && !lean_width(c.d_model))) && places * c.d_model < PACKED_NARROW_PLACES;
