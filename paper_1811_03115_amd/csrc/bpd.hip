@@ -935,10 +935,6 @@ int lean_slices(const bpd_ctx* ctx, int M) {
   if (c.d_ff > LEAN_K_WHOLE && M <= LEAN_PART_M) return c.d_ff / 1024;
   return c.d_ff > LEAN_K_WHOLE || (c.d_ff == LEAN_K_WHOLE && M > LEAN_WHOLE_M) ? residual_k_slices(ctx, gp(nullptr, c.d_ff, nullptr, c.d_model, M, c.d_model, c.d_ff)) : 1;
 }
-// LayerNorm inside the GEMM that follows, or in a kernel of its own?  (with K = 1024 every column block of 64 KB of x costs: 24 rows
-// 5.05 us against 1.9 + 3.6, 40 rows 6.6 against 2.0 + 4.3; with K = 512 80 rows 3.3 against 1.9 + 2.5, 256 rows 5.4 against 1.9 + 3.9, 320 rows 6.8
-// against 1.9 + 4.3)
-bool lean_fuse(int d, int M) { return d <= 512 ? M <= 256 : M <= 32; }
 
 template <int WAVES, int U, bool LN, int EPI>
 void launch_row_gemm(const bpd_ctx* ctx, const RowGemmP& p, int slices) {

@@ -160,6 +160,10 @@ bool lean_ok(const bpd_config& c, long M) {
 constexpr int LEAN_K_WHOLE = 2048;
 constexpr int LEAN_PART_M = 192;        // more rows: the slices of the LDS-staged kernel (192 rows 6.8 against 7.25 us, 256 rows 8.0 against 7.3)
 bool lean_encoder_ok(const bpd_config& c, long M) { return lean_ok(c, M) && (c.d_model <= 512 || M <= LEAN_ENC_WIDE_M_MAX); }
+// LayerNorm inside the GEMM that follows, or in a kernel of its own?  (with K = 1024 every column block of 64 KB of x costs: 24 rows
+// 5.05 us against 1.9 + 3.6, 40 rows 6.6 against 2.0 + 4.3; with K = 512 80 rows 3.3 against 1.9 + 2.5, 256 rows 5.4 against 1.9 + 3.9, 320 rows 6.8
+// against 1.9 + 4.3)
+bool lean_fuse(int d, long M) { return d <= 512 ? M <= 256 : M <= 32; }
 
 // Rows of the encoder for sources of `tokens` tokens together in B x S places: packed, where that pays; otherwise all of them (0).
 // A packed encode looks up each row's sequence and position: a load ahead of each attention, two at the entry of the GEMMs that store keys and values, some 0.5 us
@@ -167,25 +171,29 @@ bool lean_encoder_ok(const bpd_config& c, long M) { return lean_ok(c, M) && (c.d
 // 4.690, 4.633.  Encodes of 64 .. 8192 places, 30 .. 84 % of them tokens, us, padded and packed:
 //   d = 1024  seven eighths of the places and less: 960 places, 589 tokens 843, 772;  512, 442 687, 671.  Slower where the tiles of so many rows are poor ones: 1120 of 1280 rows
 //             996, 1013 (d = 768 740, 786), 3584 of 4096 1643, 1664, 96 of 120 428, 433
-//   d = 512   as fast or faster below seven eighths (960, 589 448, 429), at seven eighths the tiles decide (1120 of 1280 rows 542, 564;  1568 of 1792 588, 625;  2688 of 3072 752, 711).
+//   d = 512   as fast or faster up to five sixths (960, 589 448, 429), beyond the tiles decide (832 of 960 rows 458, 470;  1120 of 1280 542, 564;  1568 of 1792 588, 625;  2688 of 3072 752, 711).
 //             Up to 128 places, where a row tile less saves nothing, below three quarters (96 of 128 rows 240, 242;  64 of 128 251, 246)
 //   narrower  layers too short for the lookups: d = 384, 768, 440 654, 673;  256, 162 486, 501;  d = 128, 2048, 1146 324, 335;  d = 64, 1024, 587 365, 370.  It pays
 //             with many places (d = 384, 2048, 1146 758, 695;  d = 256, 2048, 1146 401, 363;  d = 128, 4096, 2266 382, 345) and where the padding alone is beyond the
-//             kernels of constant K (d = 128, 768, 566 307, 249;  d = 256, 768, 566 319, 302)
+//             kernels of constant K (d = 128, 768, 566 307, 249;  d = 256, 768, 566 319, 302) or beyond LayerNorm inside them (by rows of 288 .. 448 places, d = 128, 256: 128 .. 256
+//             6 .. 13 % faster, 288 .. 384 0 .. 2 % slower)
 //   d = 640, 896   (wider, but without kernels of constant K) as the narrower ones: by rows of 384 places, 160: 6, 3 % slower, 288: 7, 3, 320: 6, 6;  of 1024, d = 640, 512: 6 % faster
 //   one row tile   goes through the kernels for it: d = 384, 28 places 463, 407;  d = 640, 24 568, 481;  d = 512, 42 231, 228;  d = 1024, 42 364, 335, but 28 333, 327, with d_ff 8192
 //             579, 588;  d = 64, 128, 256, 39 306, 325;  191, 193;  218, 220
 // In steps of a sixteenth of the places: recorded encodes are found by their rows, and lengths that change from call to call have at most fifteen of them, mostly two to six
 // (in steps of one row tile few of their encodes were recorded: 32 sequences in 4096 places 306 us of host time, 66 so; 5 in 250, d = 768, the first 40 calls 2.64 ms,
 // 2.52;  13 in 780 4.25, 3.85;  in steps of an eighth more rows are computed for nothing: encodes of 13 in 780 357 us, so 349, of 32 in 4096 1283, 1265, of 24 in 1440, where the
-// tiles decide, 440, 448).  Whole pairs of row tiles, which is what the GEMMs of some hundred rows walk in: d = 1024, 544 rows 760 us, 560 849, 576 761, all 800 places 824.
+// tiles decide, 440, 448).  Whole pairs of row tiles, which is what the LDS-staged GEMMs walk in: d = 1024, 544 rows 760 us, 560 849, 576 761, all 800 places 824;  d = 1536, 172
+// tokens of 256 places in 176 rows 1047, in 192 929, padded 975.  Up to 256 rows of the kernels of constant K single ones (d = 1024, 210 of 528 in 240 rows 601, in 288 648).
 constexpr long PACKED_NARROW_PLACES = 1L << 19;      // places x d_model from which on packing pays for them
 inline int packed_source_rows(const bpd_config& c, long tokens, long places) {
   if (tokens <= 16 && c.d_model > 256 && (places > 32 || (places > 18 && c.d_model < 1024 && !lean_width(c.d_model)))) return 16;
-  const long step = (places + 255) / 256 * 16, rows = ((tokens + step - 1) / step * step + 31) / 32 * 32;
-  if (c.d_model > 512 ? rows * 8 > places * 7 : rows * 8 >= places * (places <= 128 ? 6 : 7)) return 0;
+  const long step = (places + 255) / 256 * 16, tiles = (tokens + step - 1) / step * step;
+  const long rows = tiles > 16 && tiles <= 256 && lean_encoder_ok(c, tiles) ? tiles : (tiles + 31) / 32 * 32;
+  if (c.d_model > 512 ? rows * 8 > places * 7 : (places <= 128 ? rows * 4 >= places * 3 : rows * 6 > places * 5)) return 0;
   const bool narrow = (c.d_model < 512 || (c.d_model < 1024 && !lean_width(c.d_model))) && places * c.d_model < PACKED_NARROW_PLACES;
-  return narrow && !(lean_encoder_ok(c, rows) && !lean_encoder_ok(c, places)) ? 0 : (int)rows;
+  const bool other = lean_encoder_ok(c, rows) && (!lean_encoder_ok(c, places) || (lean_fuse(c.d_model, rows) && !lean_fuse(c.d_model, places)));
+  return narrow && !other ? 0 : (int)rows;
 }
 
 // Other decoder blocks of more than 128 rows run their LayerNorm-then-GEMM pairs as one GEMM on weights with the LayerNorm

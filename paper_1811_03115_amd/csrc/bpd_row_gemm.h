@@ -33,7 +33,7 @@ struct RowGemmP {
 // LN: X = LayerNorm(x): every wave takes mean and squared distances of its columns of the rows, these meet in LDS (row_moments), and
 // the wave normalises in registers the fragments it already holds.  One barrier more than without, and twice the bytes for x: 0.8 us at K = 512,
 // 1.2 us at K = 1024, against 1.9 us for a LayerNorm kernel of its own; but every column block repeats it, so that with
-// K = 1024 and more than 32 rows (K = 512: 256) the kernel of its own is the faster one (lean_fuse() in bpd.hip).
+// K = 1024 and more than 32 rows (K = 512: 256) the kernel of its own is the faster one (lean_fuse() in bpd_host_logic.h).
 // 8 x 512 x 1536 with LayerNorm: 3.95 -> 2.84 us per kernel of a chain;  10 x 1024 x 3072: 5.6 -> 4.2;  8 x 512 x 512: 3.2 -> 2.1;
 // 10 x 1024 x 1024: 3.7 -> 2.6.  More waves (16) and fewer columns per workgroup (8, 4 of a tile) are slower; more columns (NT), then more
 // rows (MT), pay once the workgroups would outnumber the CUs: 192 x 1024 x 3072 8.1 us with MT = 1, 7.05 with 3 (the LDS-staged kernel 10.2), 320 x 1024 x

@@ -279,7 +279,7 @@ def test_steps_past_the_end(k, B, captured):
 # kernels take; widths below 512 with padding beyond those kernels, and with many places.  Both ways the logits are within TOL of the oracle's, so within twice that of each other.
 @pytest.mark.parametrize("d,S,lens", [(320, 9, [1, 3, 9]), (320, 60, [5, 60, 30, 2]), (128, 40, [1, 1, 40]), (512, 140, [16, 17, 1, 33, 140]), (1024, 128, [27]),
                                       (1024, 140, [140, 100, 60, 90, 3]), (512, 48, [15 + b % 17 for b in range(33)]), (128, 40, [9 + b for b in range(17)]),
-                                      (128, 96, [20 + b for b in range(44)]), (320, 60, [1 + 2 * b for b in range(28)]), (512, 21, [9, 1, 5]), (1024, 14, [10, 2, 3])])
+                                      (128, 96, [20 + b for b in range(44)]), (320, 60, [1 + 2 * b for b in range(28)]), (512, 21, [9, 1, 5]), (1024, 14, [10, 2, 3]), (128, 12, [3 + b % 10 for b in range(30)])])
 def test_packed_sources(d, S, lens):
     B, k = len(lens), 3
     cfg = config(k, B, S, 8, layers=2, d=d)
