@@ -602,13 +602,32 @@ long attention_keys(const bpd_ctx* ctx, int cap, int R, int causal) {
 // caller checks), at most 16 rows per sequence, 64-wide heads, d = 128 / 256 / 512 / 1024, one workgroup per (head,
 // sequence) and few enough of them that each streaming its head's 128 d bytes of weights beats one GEMM doing it once.
 constexpr int ATTN_QPROJ_MAX_WGS = 128;       // (512 workgroups, batch 32 of Transformer-big: the step took 26 us longer than with the separate GEMM)
+// More of them, up to a workgroup per CU, go two sequences to a workgroup (d = 512, 1024; sources of at most 128 keys, a group of 32 for each wave).  LayerNorm, GEMM and attention of a
+// layer at 32 x 10 rows, us: 17.2 as three kernels, 8.9;  32 x 1 rows 11.3 as two, 8.0.
+constexpr int ATTN_QPROJ_MAX_PAIRS = 256;
+bool attention_qproj_pairs(const bpd_ctx* ctx, int B) {
+  const bpd_config& c = ctx->cfg;
+  return c.n_heads * B > ATTN_QPROJ_MAX_WGS && c.n_heads * ((B + 1) / 2) <= ATTN_QPROJ_MAX_PAIRS && (c.d_model == 512 || c.d_model == 1024) && c.max_src_len <= 128;
+}
 bool attention_qproj_ok(const bpd_ctx* ctx, int B, int R) {
   const bpd_config& c = ctx->cfg;
   const int d = c.d_model;
   return c.dtype == BPD_BF16 && R <= 16 && d == 64 * c.n_heads && (d == 128 || d == 256 || d == 512 || d == 1024) &&
-         c.n_heads * B <= ATTN_QPROJ_MAX_WGS && attention_nsplit(ctx, c.max_src_len, B, R, 0) == 1;
+         (c.n_heads * B <= ATTN_QPROJ_MAX_WGS || attention_qproj_pairs(ctx, B)) && attention_nsplit(ctx, c.max_src_len, B, R, 0) == 1;
 }
 
+template <int QU>
+void launch_attention_pairs(const bpd_ctx* ctx, const AttnP& p, const QProjP& qp, int B) {
+  constexpr int lds = AttnPairsLds<QU>::BYTES;
+  static bool attr_set = false;                 // per width: allow more than 64 KiB of LDS
+  if (!attr_set) {
+    for (const void* k : {(const void*)attention_mfma_pairs_kernel<QU, true>, (const void*)attention_mfma_pairs_kernel<QU, false>}) (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    attr_set = true;
+  }
+  const dim3 grid(ctx->cfg.n_heads, (B + 1) / 2);
+  if (p.seq) hipLaunchKernelGGL((attention_mfma_pairs_kernel<QU, true>), grid, dim3(64 * ATTN_WAVES), lds, ctx->stream, p, qp, B);
+  else hipLaunchKernelGGL((attention_mfma_pairs_kernel<QU, false>), grid, dim3(64 * ATTN_WAVES), lds, ctx->stream, p, qp, B);
+}
 constexpr int ATTN_TILES_MIN = 1024;             // (row tile, head, sequence) triples from which on a wave takes whole ones: 4096 gain 8 us of 21, 320 lose 1 of 5.  Packed
                                                  // rows: of the padded shape, of which 0.3 .. 0.8 are there; encodes so and dealt to waves, us: 624 of 1024 858, 861;  640 of 1280 515, 513;  2288 of 5120 1391, 1400
 void attention(bpd_ctx* ctx, const float* Q, const void* Kc, const void* Vc, void* out, int cap,
@@ -641,6 +660,10 @@ void attention(bpd_ctx* ctx, const float* Q, const void* Kc, const void* Vc, voi
       const bool few = attention_keys(ctx, cap, R, causal) <= 128, two = !few && (limf || nsplit > 1);
       const int waves = few || two ? 4 : ATTN_WAVES;
       const QProjP qp_ = qproj ? *qproj : QProjP{};
+      if (qproj && attention_qproj_pairs(ctx, B)) {
+        if (c.d_model == 512) launch_attention_pairs<4>(ctx, p, qp_, B); else launch_attention_pairs<8>(ctx, p, qp_, B);
+        return;
+      }
       if (qproj) {                               // queries projected in the kernel (attention_qproj_ok() holds)
         switch (c.d_model / 128) {
           case 1: BPD_ATTN(false, false, 1) break;

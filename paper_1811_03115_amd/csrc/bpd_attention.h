@@ -46,6 +46,19 @@ __device__ __forceinline__ void split_bf16x8(const float (&v)[8], bf16x8& hi, bf
   lo = __builtin_bit_cast(bf16x8, (u32x4{l[0], l[1], l[2], l[3]}));
 }
 
+// Four columns of scaled queries as the attention's operands
+__device__ __forceinline__ void lk_halves(const f32x4& v, u32x2& hi, u32x2& lo) {
+  hi = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
+  lo = u32x2{cvt_pk_bf16(v[0] - __uint_as_float(hi[0] << 16), v[1] - __uint_as_float(hi[0] & 0xFFFF0000u)),
+             cvt_pk_bf16(v[2] - __uint_as_float(hi[1] << 16), v[3] - __uint_as_float(hi[1] & 0xFFFF0000u))};
+}
+// Workgroup barrier that leaves global loads under way (the waves meet over LDS only)
+__device__ __forceinline__ void lk_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // QU > 0 (at most 16 rows per sequence, d = 128 * QU): the queries are projected inside the kernel,
 //   Q = LayerNorm(x) Wq[:, 64 h .. 64 h + 63]   (x: fp32 residual stream),
 // instead of being read from p.Q: the waves split the contraction, their partial sums meet in LDS, and the K/V loads of
@@ -118,7 +131,7 @@ __device__ __forceinline__ void attn_load_kv(rsrc_t kr, rsrc_t vr, int c, int nw
 }
 // The item's work from the point where its queries (qhi + qlo) and the first groups of K and V are at hand or under way (parameters as in
 // attention_mfma_body; first, hop: this split's first group and the distance to its next round; lim: limit[b]).  STORE: no word of the results is EMPTY_WORD (ATTN_WORDS),
-// and they are written through the L2 (ATTN_THROUGH_WORDS).
+// and they are written through the L2 (ATTN_THROUGH_WORDS).  ONCE: no wave has a second round.
 enum { ATTN_PLAIN, ATTN_WORDS, ATTN_THROUGH_WORDS };
 template <int STORE>
 __device__ __forceinline__ void attention_store(bf16_t* to, const f32x4& v) {
@@ -127,7 +140,7 @@ __device__ __forceinline__ void attention_store(bf16_t* to, const f32x4& v) {
   if constexpr (STORE == ATTN_THROUGH_WORDS) asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(to), "v"(w) : "memory");      // (to memory, for other XCDs)
   else *(u32x2*)to = w;
 }
-template <bool KVNT, bool LIMF, int QU, int G, int STORE = ATTN_PLAIN>
+template <bool KVNT, bool LIMF, int QU, int G, int STORE = ATTN_PLAIN, bool ONCE = false>
 __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLds& sm, int h, int b, int tile, int split, int r0, int nrows,
                                                     int nheads, int nz, int tid, int nw, int first, int hop, rsrc_t kr, rsrc_t vr,
                                                     u32x4 (&kf)[G][4], u32x4 (&vf)[G][4], const bf16x8 (&qhi)[2], const bf16x8 (&qlo)[2], int lim, bf16_t* out) {
@@ -215,6 +228,7 @@ __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLd
         acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, plo, acc[dt], 0, 0, 0);
       }
     }
+    if constexpr (ONCE) break;
     if (c + hop + wave < ngr) attn_load_kv<KVNT, G>(kr, vr, c + hop + wave, nw, lane, kf, vf);
   }
   // At most 32 keys: the first wave has them all, and all 64 dimensions.  (Through the LDS as below, four waves storing 16 each: 0.25 us more.)
@@ -461,6 +475,134 @@ template <bool KVNT, bool LIMF, int QU>
 __global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_kernel(AttnP p, QProjP qp) { attention_mfma_entry<KVNT, LIMF, QU, false>(p, qp); }
 template <bool KVNT, bool LIMF, int QU>
 __global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_slots_kernel(AttnP p, QProjP qp) { attention_mfma_entry<KVNT, LIMF, QU, true>(p, qp); }
+// The same with queries projected inside (QU > 1) for two sequences of up to 128 keys per workgroup: one reading of the head's weights serves two row tiles, and each half of the waves
+// then has one of the sequences.  (One workgroup per sequence: with more than 128 of them the weights, 128 KB each at d = 1024, cost more than the kernels saved.)
+// A wave normalises whole rows, a line at a time, and the operands are read out of the LDS: as operands straight from the rows in memory a load touches 64 lines, which the L1 looks up one by
+// one (64 cycles instead of 16: of 20 rows the last wave had its sums 4 us after the launch).
+template <int QU>
+struct AttnPairsLds {
+  static constexpr int K = 128 * QU, XS = 32 * (K + 8) * 2, RED = ATTN_WAVES * 8 * 64 * 16, QS = 2 * 512 * 8, ML = 2 * ATTN_WAVES * 16 * 4;
+  static constexpr int BYTES = XS + RED + QS + ML;
+};
+template <int QU, bool SLOTS>
+__global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_pairs_kernel(AttnP p, QProjP qp, int B) {
+  constexpr int NW = ATTN_WAVES, K = 128 * QU, KSTEPS = K / 32, U = KSTEPS / NW, H = K / 256;
+  static_assert(U * NW == KSTEPS && H * 256 == K, "every wave has k-steps, every lane columns");
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  using Lds = AttnPairsLds<QU>;
+  bf16_t* xs = (bf16_t*)smem_raw;                // normalised rows, K + 8 apart
+  f32x4* red = (f32x4*)(smem_raw + Lds::XS);     // partial sums [wave][row tile, column tile][lane]; then the halves' results, as AttnLds
+  u32x2* q_s = (u32x2*)(smem_raw + Lds::XS + Lds::RED);
+  float (*m_s)[16] = (float (*)[16])(smem_raw + Lds::XS + Lds::RED + Lds::QS), (*l_s)[16] = m_s + NW;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = wave >> 2;
+  const int lr = lane & 15, lq = lane >> 4, h = blockIdx.x, b0 = 2 * blockIdx.y, b = b0 + half, there = b0 + 1 < B ? 2 : 1;
+  const int bc = half < there ? b : b0;
+  int sb = half < there ? b : -1;
+  if (SLOTS) {
+    const int s0 = p.seq[b0], s1 = there > 1 ? p.seq[b0 + 1] : -1;
+    if (s0 < 0 && s1 < 0) return;                // (the whole workgroup)
+    sb = half ? s1 : s0;
+  }
+  const int ks0 = wave * U, rows = __builtin_amdgcn_readfirstlane(there * p.R);
+  // every load of the kernel but keys and values: rows wave, wave + 8, .. of x first
+  f32x4 v[4][H], g[H], be[H];
+  const rsrc_t xr = rsrc_of(qp.x + (size_t)b0 * p.R * K, (unsigned)rows * K * 4);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (wave + NW * i >= rows) break;
+#pragma unroll
+    for (int c = 0; c < H; ++c) v[i][c] = __builtin_bit_cast(f32x4, buf_load16(xr, (unsigned)((wave + NW * i) * K + c * 256 + lane * 4) * 4, 0));
+  }
+#pragma unroll
+  for (int c = 0; c < H; ++c) { g[c] = *(const f32x4*)(qp.g + c * 256 + lane * 4); be[c] = *(const f32x4*)(qp.b + c * 256 + lane * 4); }
+  int lim = p.limit[bc];
+  u32x4 wf[4][U];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int i = 0; i < U; ++i) wf[j][i] = *(const u32x4*)((const char*)qp.W + ((size_t)(4 * h + j) * KSTEPS + ks0 + i) * 1024 + lane * 16);
+  bf16_t* out = arg_now((bf16_t*)p.out);
+  __builtin_amdgcn_sched_barrier(0);
+  // K and V of this half's sequence
+  lim = sb < 0 || lim < 0 ? 0 : __builtin_amdgcn_readfirstlane(lim);
+  const int glim = (lim + 31) >> 5 < p.capg ? (lim + 31) >> 5 : p.capg;
+  const size_t head_at = ((size_t)(sb < 0 ? 0 : sb) * gridDim.x + h) * p.capg * KV_GROUP;
+  const rsrc_t kr = rsrc_of((const bf16_t*)p.Kc + head_at, (unsigned)glim * (KV_GROUP * 2));
+  const rsrc_t vr = rsrc_of((const bf16_t*)p.Vc + head_at, (unsigned)glim * (KV_GROUP * 2));
+  u32x4 kf[1][4], vf[1][4];
+  attn_load_kv<false, 1>(kr, vr, wave & 3, 4, lane, kf, vf);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (wave + NW * i >= rows) break;
+    f32x4 s4 = f32x4{0.f, 0.f, 0.f, 0.f}, q4 = s4;
+#pragma unroll
+    for (int c = 0; c < H; ++c) s4 += v[i][c];
+    const float mu = wave_sum((s4[0] + s4[1]) + (s4[2] + s4[3])) * (1.f / K);
+#pragma unroll
+    for (int c = 0; c < H; ++c) {
+      v[i][c] -= mu;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) q4[r] = fmaf(v[i][c][r], v[i][c][r], q4[r]);
+    }
+    const float rs = inv_sqrt(fmaf(wave_sum((q4[0] + q4[1]) + (q4[2] + q4[3])), 1.f / K, qp.eps));
+#pragma unroll
+    for (int c = 0; c < H; ++c) {
+      f32x4 y;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) y[r] = fmaf(v[i][c][r] * rs, g[c][r], be[c][r]);
+      *(u32x2*)(xs + (wave + NW * i) * (K + 8) + c * 256 + lane * 4) = u32x2{cvt_pk_bf16(y[0], y[1]), cvt_pk_bf16(y[2], y[3])};
+    }
+  }
+  lk_barrier();
+  f32x4 qa[2][4];
+  const bf16_t* row[2];                          // (rows past the last: the last)
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int m = t * p.R + (lr < p.R ? lr : p.R - 1);
+    row[t] = xs + (m < rows ? m : rows - 1) * (K + 8) + ks0 * 32 + lq * 8;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) qa[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+#pragma unroll
+  for (int i = 0; i < U; ++i)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const bf16x8 x8 = __builtin_bit_cast(bf16x8, *(const u32x4*)(row[t] + i * 32));
+#pragma unroll
+      for (int j = 0; j < 4; ++j) qa[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[j][i]), x8, qa[t][j], 0, 0, 0);
+    }
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) red[(wave * 8 + t * 4 + j) * 64 + lane] = qa[t][j];
+  lk_barrier();
+  {                                              // wave 4 t + j finishes column tile j of row tile t
+    f32x4 part[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) part[w] = red[(w * 8 + wave) * 64 + lane];
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 sum = part[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) sum += part[w];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sum[r] *= p.scale;
+    u32x2 hi, lo;
+    lk_halves(sum, hi, lo);
+    const int j = wave & 3, at = half * 512 + ((j >> 1) * 64 + ((j & 1) * 2 + (lq >> 1)) * 16 + lr) * 2 + (lq & 1);       // (as in attention_mfma_body)
+    q_s[at] = hi; q_s[256 + at] = lo;
+  }
+  lk_barrier();
+  bf16x8 qhi[2], qlo[2];
+#pragma unroll
+  for (int s2 = 0; s2 < 2; ++s2) {
+    qhi[s2] = __builtin_bit_cast(bf16x8, *(const u32x4*)&q_s[half * 512 + (s2 * 64 + lane) * 2]);
+    qlo[s2] = __builtin_bit_cast(bf16x8, *(const u32x4*)&q_s[half * 512 + 256 + (s2 * 64 + lane) * 2]);
+  }
+  AttnLds sm = AttnLds::carve((unsigned char*)(red + half * (4 * 4 * 64)));
+  sm.m_s = m_s + half * 4; sm.l_s = l_s + half * 4;
+  attention_mfma_core<false, false, 0, 1, ATTN_PLAIN, true>(p, sm, h, b, 0, 0, 0, sb < 0 ? 0 : p.R, gridDim.x, 1, threadIdx.x & 255, 4, 0, 4, kr, vr, kf, vf, qhi, qlo, lim, out);
+}
 // Source rows of up to 128 keys: a wave has all keys and values of its (sequence, head) in registers and `per` row tiles of 16 in turn, the next one's queries under way
 // meanwhile.  With the keys dealt to four waves, as above, a launch of many tiles is bound by instructions, half of them the softmax's exchange between lanes and
 // the waves' meeting, which here come once per 128 keys and not at all.  No LDS, no barrier.  32 sequences of 128 tokens, 16 heads, 8 row tiles: 20.6 us dealt to waves (with a

@@ -91,13 +91,6 @@ __device__ __forceinline__ int lk_lane() {
   asm volatile("" : "+v"(t));
   return t;
 }
-// Workgroup barrier that leaves global loads under way (the waves meet over LDS only)
-__device__ __forceinline__ void lk_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // ---- compute waves
 // The N tiles from `tile` on, this wave's U k-steps of each.  PACE > 0: a pause between requests (units of 64 cycles)
 template <int PACE, int N, int U>
@@ -158,12 +151,6 @@ __device__ __forceinline__ void lk_wait(const unsigned* flags, unsigned target, 
 __device__ __forceinline__ void lk_raise(unsigned* flag, unsigned v, int lane) {
   lk_stores_done();
   if (lane == 0) lk_store(flag, v);
-}
-// Four columns of scaled queries as the attention's operands
-__device__ __forceinline__ void lk_halves(const f32x4& v, u32x2& hi, u32x2& lo) {
-  hi = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
-  lo = u32x2{cvt_pk_bf16(v[0] - __uint_as_float(hi[0] << 16), v[1] - __uint_as_float(hi[0] & 0xFFFF0000u)),
-             cvt_pk_bf16(v[2] - __uint_as_float(hi[1] << 16), v[3] - __uint_as_float(hi[1] & 0xFFFF0000u))};
 }
 // Results that carry their own news (EMPTY_WORD: bpd_attention.h): a buffer is empty in every word until its producers store into it, so that whoever loads it
 // again and again until no word is empty needs no flag, and the producers wait for no acknowledgement.

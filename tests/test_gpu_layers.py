@@ -59,6 +59,14 @@ def test_ended_sequences(k, B, d):
     lockstep(config(k, B, 4, 4 * k + 1, d=d), 4, np.array([1 + (5 * b) % (4 * k + 1) for b in range(B)], np.int32))
 
 
+# Blocks beyond the kernels of all layers whose cross-attention projects the queries of two sequences per workgroup: an odd sequence, one row and sixteen, one key
+# and 128, sequences that end (a pair of which one or none goes on)
+@pytest.mark.parametrize("k,B,S,d,ended", [(10, 9, 33, 1024, False), (16, 12, 128, 1024, False), (3, 31, 1, 1024, True), (10, 32, 64, 1024, True), (8, 17, 40, 512, False), (5, 40, 128, 512, True), (9, 64, 7, 512, True)])
+def test_two_sequences_per_workgroup(k, B, S, d, ended):
+    budgets = np.array([1 + (7 * (b // 2) + 3 * (b % 3)) % (4 * k) for b in range(B)], np.int32) if ended else None
+    lockstep(config(k, B, S, 4 * k + 1, layers=1, d=d), 4 if ended else 2, budgets)
+
+
 # caches of more keys than a workgroup takes in one round, of more than 1024, which three workgroups share, two slots per job, a window.  Both ways the logits
 # are within TOL of the oracle's (shown above and for the kernel chain elsewhere), so within twice that of each other.
 @pytest.mark.parametrize("k,B,out,steps,local,d", [(16, 1, 400, 20, 0, 512), (10, 3, 700, 60, 0, 512), (16, 8, 1100, 66, 0, 512), (8, 16, 600, 60, 0, 512), (9, 2, 700, 70, 256, 512),
