@@ -429,7 +429,7 @@ bool gemm(bpd_ctx* ctx, const GemmP& p, const Epi& e_in, int groups = 1) {
   return false;
 }
 
-void layernorm(bpd_ctx* ctx, float* x, LnW w, int M, void* ya, float* yf);
+void layernorm(bpd_ctx* ctx, float* x, LnW w, int M, void* ya, float* yf, bool packed = false);
 
 // Y = epilogue(LayerNorm(x) W).  Block of <= 16 rows: LayerNorm is applied inside the skinny
 // kernel from the partial statistics the producer of x left in L.stats_ln.  More rows, with per-tile statistics of
@@ -540,9 +540,10 @@ Epi kv_split(const bpd_ctx* ctx, float* Qf, void* Ka, void* Va, int chunk0, int 
 }
 
 template <int D>
-void launch_ln_row(bpd_ctx* ctx, float* x, LnW w, int M, void* ya, float* yf, int nsl, const float* bias) {
-#define BPD_LN(NSL) hipLaunchKernelGGL((ln_row_kernel<D, NSL>), dim3(M), dim3(ln_row_threads(D)), 0, ctx->stream, x, w.g, w.b, M, ctx->cfg.ln_eps, \
-                                       (bf16_t*)ya, yf, (const float*)ctx->lay.kpart, bias, clear, nclear)
+void launch_ln_row(bpd_ctx* ctx, float* x, LnW w, int M, void* ya, float* yf, int nsl, const float* bias, bool packed) {
+  const dim3 grid(packed ? (M + 127) / 128 * 128 : M);
+#define BPD_LN(NSL) hipLaunchKernelGGL((ln_row_kernel<D, NSL>), grid, dim3(ln_row_threads(D)), 0, ctx->stream, x, w.g, w.b, M, ctx->cfg.ln_eps, \
+                                       (bf16_t*)ya, yf, (const float*)ctx->lay.kpart, bias, clear, nclear, (int)packed)
   int nclear = 0;
   u32x4* clear = (u32x4*)clear_behind_layers(ctx, nclear);
   switch (nsl) {
@@ -555,7 +556,8 @@ void launch_ln_row(bpd_ctx* ctx, float* x, LnW w, int M, void* ya, float* yf, in
   }
 #undef BPD_LN
 }
-void layernorm(bpd_ctx* ctx, float* x, LnW w, int M, void* ya, float* yf) {
+// packed (widths of constant K): ya as row_gemm_kernel reads it
+void layernorm(bpd_ctx* ctx, float* x, LnW w, int M, void* ya, float* yf, bool packed) {
   const int d = ctx->cfg.d_model;
   dim3 grid((M + 3) / 4);
   int nsl = 0;
@@ -563,11 +565,11 @@ void layernorm(bpd_ctx* ctx, float* x, LnW w, int M, void* ya, float* yf) {
   if (ctx->pend_slices && ctx->pend_x == x) { nsl = ctx->pend_slices; bias = ctx->pend_bias; ctx->pend_slices = 0; }
   if (ctx->cfg.dtype == BPD_BF16 && lean_width(d) && (nsl == 0 || nsl == 2 || nsl == 3 || nsl == 4 || nsl == 8 || nsl == 16)) {
     switch (d) {
-      case 128: launch_ln_row<128>(ctx, x, w, M, ya, yf, nsl, bias); break;
-      case 256: launch_ln_row<256>(ctx, x, w, M, ya, yf, nsl, bias); break;
-      case 512: launch_ln_row<512>(ctx, x, w, M, ya, yf, nsl, bias); break;
-      case 768: launch_ln_row<768>(ctx, x, w, M, ya, yf, nsl, bias); break;
-      default: launch_ln_row<1024>(ctx, x, w, M, ya, yf, nsl, bias); break;
+      case 128: launch_ln_row<128>(ctx, x, w, M, ya, yf, nsl, bias, packed); break;
+      case 256: launch_ln_row<256>(ctx, x, w, M, ya, yf, nsl, bias, packed); break;
+      case 512: launch_ln_row<512>(ctx, x, w, M, ya, yf, nsl, bias, packed); break;
+      case 768: launch_ln_row<768>(ctx, x, w, M, ya, yf, nsl, bias, packed); break;
+      default: launch_ln_row<1024>(ctx, x, w, M, ya, yf, nsl, bias, packed); break;
     }
     return;
   }
@@ -631,14 +633,14 @@ void launch_attention_pairs(const bpd_ctx* ctx, const AttnP& p, const QProjP& qp
 constexpr int ATTN_TILES_MIN = 1024;             // (row tile, head, sequence) triples from which on a wave takes whole ones: 4096 gain 8 us of 21, 320 lose 1 of 5.  Packed
                                                  // rows: of the padded shape, of which 0.3 .. 0.8 are there; encodes so and dealt to waves, us: 624 of 1024 858, 861;  640 of 1280 515, 513;  2288 of 5120 1391, 1400
 void attention(bpd_ctx* ctx, const float* Q, const void* Kc, const void* Vc, void* out, int cap,
-               int B, int R, const int* limit, int causal, const int* seq, const QProjP* qproj = nullptr, const int* row0 = nullptr) {
+               int B, int R, const int* limit, int causal, const int* seq, bool packed, const QProjP* qproj = nullptr, const int* row0 = nullptr) {
   const long kv_seq_stride = (long)cap * ctx->cfg.d_model;
   const int capg = (cap + 31) / 32;
   const bpd_config& c = ctx->cfg;
   const int dh = c.d_model / c.n_heads;
   AttnP p{};
   p.Q = Q; p.Kc = Kc; p.Vc = Vc; p.out = out; p.kv_seq_stride = kv_seq_stride; p.cap = cap; p.capg = capg; p.d = c.d_model; p.R = R;
-  p.limit = limit; p.causal = causal; p.seq = seq; p.scale = 1.0f / sqrtf((float)dh);
+  p.packed = packed; p.limit = limit; p.causal = causal; p.seq = seq; p.scale = 1.0f / sqrtf((float)dh);
   const bool local = causal && ctx->local_q > 0;
   p.local_q = local ? ctx->local_q : 0; p.local_m = local ? ctx->local_m : 0;
   const int tiles = (R + 15) / 16, wgs = c.n_heads * B * tiles;
@@ -997,7 +999,7 @@ void lean_ln_gemm(bpd_ctx* ctx, float* x, LnW w, void* xn, RowGemmP p) {
     p.X = x; p.g = w.g; p.b = w.b;
     row_gemm<true, EPI>(ctx, p, d);
   } else {
-    layernorm(ctx, x, w, p.M, xn, nullptr);
+    layernorm(ctx, x, w, p.M, xn, nullptr, true);
     p.X = xn;
     row_gemm<false, EPI>(ctx, p, d);
   }
@@ -1013,12 +1015,14 @@ RowGemmP rg_kv(const bpd_ctx* ctx, const void* X, const void* W, int M, int N, c
   p.Kc = (bf16_t*)e.Ka; p.Vc = (bf16_t*)e.Va; p.base = e.base; p.seq = e.seq;
   return p;
 }
+// (X as rows: the LDS-staged kernel's)
+bool residual_by_rows(int K, int M) { return K >= LEAN_K_WHOLE && M > (K > LEAN_K_WHOLE ? LEAN_PART_M : LEAN_WHOLE_M); }
 // x += X W + bias; K slices of a long K are left for the LayerNorm of x that follows (ctx->pend_*)
 void lean_residual(bpd_ctx* ctx, const void* X, int K, const void* W, const float* bias, int M, float* x) {
   const int d = ctx->cfg.d_model;
   RowGemmP p = rg(X, K, W, M, d);
   p.ldy = d; p.bias = bias;
-  if (K >= LEAN_K_WHOLE && M > (K > LEAN_K_WHOLE ? LEAN_PART_M : LEAN_WHOLE_M)) {
+  if (residual_by_rows(K, M)) {
     gemm(ctx, gp(X, K, W, d, M, d, K), plain(bias, 0, x, d, x, d, nullptr, 0));
   } else if (K > LEAN_K_WHOLE) {
     p.Y = ctx->lay.kpart; p.ksteps = K / 32;
@@ -1032,7 +1036,7 @@ void lean_residual(bpd_ctx* ctx, const void* X, int K, const void* W, const floa
 void lean_ffn(bpd_ctx* ctx, float* x, LnW ln, void* xn, const void* w1, const float* b1, void* hidden, const void* w2, const float* b2, int M) {
   const int F = ctx->cfg.d_ff;
   RowGemmP p = rg(nullptr, 0, w1, M, F);
-  p.bias = b1; p.Y = hidden; p.ldy = F;
+  p.bias = b1; p.Y = hidden; p.ldy = F; p.packed = !residual_by_rows(F, M);
   lean_ln_gemm<RG_RELU>(ctx, x, ln, xn, p);
   lean_residual(ctx, hidden, F, w2, b2, M, x);
 }
@@ -1093,15 +1097,15 @@ int forward(bpd_ctx* ctx, int R, int k, int zero_input, float* logits) {
           lean_ln_gemm<RG_QKV>(ctx, L.x, w.ln1, L.xn, q);
         } else {
           lean_ln_gemm<RG_QKV>(ctx, L.x, w.ln1, L.xn, rg_kv(ctx, nullptr, w.wqkv, M, 3 * d, kv));
-          attention(ctx, L.q, Kl, Vl, L.attn, slots, B, R, base, 1, seq);
+          attention(ctx, L.q, Kl, Vl, L.attn, slots, B, R, base, 1, seq, lean);
         }
         lean_residual(ctx, L.attn, d, w.wo, nullptr, M, L.x);
         if (qproj) {
           const QProjP qp{L.x, w.ln2.g, w.ln2.b, w.cq, c.ln_eps};
-          attention(ctx, nullptr, cK, cV, L.attn, c.max_src_len, B, R, srcs, 0, seq, &qp);
+          attention(ctx, nullptr, cK, cV, L.attn, c.max_src_len, B, R, srcs, 0, seq, lean, &qp);
         } else {
           lean_ln_gemm<RG_QKV>(ctx, L.x, w.ln2, L.xn, rg_kv(ctx, nullptr, w.cq, M, d, kv));
-          attention(ctx, L.q, cK, cV, L.attn, c.max_src_len, B, R, srcs, 0, seq);
+          attention(ctx, L.q, cK, cV, L.attn, c.max_src_len, B, R, srcs, 0, seq, lean);
         }
         lean_residual(ctx, L.attn, d, w.co, nullptr, M, L.x);
         lean_ffn(ctx, L.x, w.ln3, L.xn, w.w1, w.b1, L.ffh, w.w2, w.b2, M);
@@ -1109,15 +1113,15 @@ int forward(bpd_ctx* ctx, int R, int k, int zero_input, float* logits) {
       }
       // self-attention sublayer: K/V of the block rows go straight into the cache at L_b + i'
       gemm_ln(ctx, L.x, w.ln1, L.xn, nullptr, gp(L.xn, d, w.wqkv, 3 * d, M, 3 * d, d), kv, sp, xs, folds ? &w.f_qkv : nullptr);
-      attention(ctx, L.q, Kl, Vl, L.attn, slots, B, R, base, 1, seq);
+      attention(ctx, L.q, Kl, Vl, L.attn, slots, B, R, base, 1, seq, lean);
       xs = gemm(ctx, gp(L.attn, d, w.wo, d, M, d, d), residual(nullptr, d));
       // cross-attention sublayer over the encoder memory
       if (qproj) {
         const QProjP qp{L.x, w.ln2.g, w.ln2.b, w.cq, c.ln_eps};
-        attention(ctx, nullptr, cK, cV, L.attn, c.max_src_len, B, R, srcs, 0, seq, &qp);
+        attention(ctx, nullptr, cK, cV, L.attn, c.max_src_len, B, R, srcs, 0, seq, lean, &qp);
       } else {
         gemm_ln(ctx, L.x, w.ln2, L.xn, nullptr, gp(L.xn, d, w.cq, d, M, d, d), plain(nullptr, 0, nullptr, 0, L.q, d, nullptr, 0), sp, xs, folds ? &w.f_cq : nullptr);
-        attention(ctx, L.q, cK, cV, L.attn, c.max_src_len, B, R, srcs, 0, seq);
+        attention(ctx, L.q, cK, cV, L.attn, c.max_src_len, B, R, srcs, 0, seq, lean);
       }
       xs = gemm(ctx, gp(L.attn, d, w.co, d, M, d, d), residual(nullptr, d));
       // feed-forward sublayer
@@ -1296,18 +1300,18 @@ int encoder(bpd_ctx* ctx, int rows) {
     const Epi kv = kv_split(ctx, L.qe, L.ke, L.ve, 0, R, S, pos, seq);
     if (lean) {
       lean_ln_gemm<RG_QKV>(ctx, L.xe, w.ln1, L.xen, rg_kv(ctx, nullptr, w.wqkv, M, 3 * d, kv));
-      attention(ctx, L.qe, L.ke, L.ve, L.attne, S, B, S, L.src_len, 0, nullptr, nullptr, row0);
+      attention(ctx, L.qe, L.ke, L.ve, L.attne, S, B, S, L.src_len, 0, nullptr, lean, nullptr, row0);
       lean_residual(ctx, L.attne, d, w.wo, nullptr, M, L.xe);
       lean_ffn(ctx, L.xe, w.ln2, L.xen, w.w1, w.b1, L.ffhe, w.w2, w.b2, M);
       continue;
     }
     gemm_ln(ctx, L.xe, w.ln1, L.xen, nullptr, gp(L.xen, d, w.wqkv, 3 * d, M, 3 * d, d), kv, false, xs);
-    attention(ctx, L.qe, L.ke, L.ve, L.attne, S, B, S, L.src_len, 0, nullptr, nullptr, row0);
+    attention(ctx, L.qe, L.ke, L.ve, L.attne, S, B, S, L.src_len, 0, nullptr, lean, nullptr, row0);
     xs = gemm(ctx, gp(L.attne, d, w.wo, d, M, d, d), residual(nullptr));
     gemm_ln(ctx, L.xe, w.ln2, L.xen, nullptr, gp(L.xen, d, w.w1, F, M, F, d), plain(w.b1, 1, nullptr, 0, nullptr, 0, L.ffhe, F), false, xs);
     xs = gemm(ctx, gp(L.ffhe, F, w.w2, d, M, d, F), residual(w.b2));
   }
-  layernorm(ctx, L.xe, L.enc_lnf, M, L.mem, nullptr);
+  layernorm(ctx, L.xe, L.enc_lnf, M, L.mem, nullptr, lean);
   // cross keys and values of all decoder layers in one launch (fp32 and shapes without a tiled kernel: one each)
   const size_t src_layer = (size_t)c.max_batch * kv_rows(c, c.max_src_len) * d;
   const long wz = c.n_dec_layers > 1 ? ((const char*)L.dec[1].ckv - (const char*)L.dec[0].ckv) / (long)as : 0;      // (every layer's arrays are laid out alike)

@@ -231,13 +231,17 @@ __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLd
     if constexpr (ONCE) break;
     if (c + hop + wave < ngr) attn_load_kv<KVNT, G>(kr, vr, c + hop + wave, nw, lane, kf, vf);
   }
+  // (16 dimensions on: 16 elements, or 256 of the packed form)
+  const bool packed = STORE == ATTN_PLAIN && p.packed;
+  bf16_t* const to = out + (packed ? packed_at((long)b * p.R + r0 + lr, h * DH + 4 * lq, p.d) : ((size_t)b * p.R + r0 + lr) * p.d + h * DH + 4 * lq);
+  const int on = packed ? 256 : 16;
   // At most 32 keys: the first wave has them all, and all 64 dimensions.  (Through the LDS as below, four waves storing 16 each: 0.25 us more.)
   if (QU >= 0 && ngr - first <= 1 && p.nsplit == 1) {
     if (wave == 0 && lr < nrows) {
       float inv = __builtin_amdgcn_rcpf(l_run);
       inv = inv * fmaf(-l_run, inv, 2.f);        // (one Newton step: the quotient to fp32)
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt) attention_store<STORE>(out + ((size_t)b * p.R + r0 + lr) * p.d + h * DH + 16 * dt + 4 * lq, acc[dt] * inv);
+      for (int dt = 0; dt < 4; ++dt) attention_store<STORE>(to + dt * on, acc[dt] * inv);
     }
     __syncthreads();
     return;
@@ -258,7 +262,7 @@ __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLd
     if (lr < nrows) {
       float inv = __builtin_amdgcn_rcpf(L);
       inv = inv * fmaf(-L, inv, 2.f);            // (one Newton step: the quotient to fp32)
-      attention_store<STORE>(out + ((size_t)b * p.R + r0 + lr) * p.d + h * DH + dim, o * inv);
+      attention_store<STORE>(to + wave * on, o * inv);
     }
   } else {
     const int tiles = nz / p.nsplit;
@@ -704,9 +708,10 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_tiles_kernel(AttnP p, i
     float inv = __builtin_amdgcn_rcpf(sum);
     inv = inv * fmaf(-sum, inv, 2.f);            // (one Newton step: the quotient to fp32)
     if (tile * RT + lr < rows) {
-      bf16_t* to = (bf16_t*)p.out + (row0 + tile * RT + lr) * p.d + h * DH + 4 * lq;
+      bf16_t* to = (bf16_t*)p.out + attn_out_at(p, row0 + tile * RT + lr, h * DH + 4 * lq);
+      const int on = p.packed ? 256 : 16;        // 16 dimensions on
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt) *(u32x2*)(to + 16 * dt) = u32x2{cvt_pk_bf16(acc[dt][0] * inv, acc[dt][1] * inv), cvt_pk_bf16(acc[dt][2] * inv, acc[dt][3] * inv)};
+      for (int dt = 0; dt < 4; ++dt) *(u32x2*)(to + dt * on) = u32x2{cvt_pk_bf16(acc[dt][0] * inv, acc[dt][1] * inv), cvt_pk_bf16(acc[dt][2] * inv, acc[dt][3] * inv)};
     }
   }
 }

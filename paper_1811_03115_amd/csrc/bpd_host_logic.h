@@ -260,7 +260,8 @@ size_t build_layout(const bpd_config& c, char* base, Layout& L, std::vector<std:
   size_t enc_part = 0;
   if (c.d_ff > LEAN_K_WHOLE && lean_encoder_ok(c, 1)) enc_part = F / 1024 * (B * S < (size_t)LEAN_PART_M ? B * S : (size_t)LEAN_PART_M) * d;
   L.kpart = vec(L.n_kpart > enc_part ? L.n_kpart : enc_part);
-  L.xn = a.take(M * d * as); L.attn = a.take(M * d * as); L.ffh = a.take(M * F * as);
+  const size_t Mt = (M + 15) / 16 * 16;       // (whole row tiles: packed_at())
+  L.xn = a.take(Mt * d * as); L.attn = a.take(Mt * d * as); L.ffh = a.take(Mt * F * as);
   L.hn = a.take(M * d * as); L.H = a.take(M * k * F * as); L.O = a.take(M * k * d * as);
   L.keys = (unsigned long long*)a.take(M * k * 8);
   L.keys_h1 = (unsigned long long*)a.take(2 * M * 8);     // keys of head 1 at the step's B*k rows, then the second phase's B*(k-1)
@@ -269,8 +270,9 @@ size_t build_layout(const bpd_config& c, char* base, Layout& L, std::vector<std:
   const size_t Me = B * S;
   L.stats_big = vec((size_t)(d / 64 + 1) * (M > Me ? M : Me) * 2);   // per 64-column block and row: sum, sum of squares
   L.xe = vec(Me * d); L.qe = vec(Me * d);
-  L.xen = a.take(Me * d * as); L.ke = a.take(B * src_rows * d * as); L.ve = a.take(B * src_rows * d * as);
-  L.attne = a.take(Me * d * as); L.ffhe = a.take(Me * F * as); L.mem = a.take(Me * d * as);
+  const size_t Met = (Me + 15) / 16 * 16;
+  L.xen = a.take(Met * d * as); L.ke = a.take(B * src_rows * d * as); L.ve = a.take(B * src_rows * d * as);
+  L.attne = a.take(Met * d * as); L.ffhe = a.take(Met * F * as); L.mem = a.take(Met * d * as);
   auto ints = [&](size_t n) { return (int*)a.take(n * 4); };
   L.L = ints(B); L.j = ints(B); L.finished = ints(B); L.max_len = ints(B); L.src_len = ints(B);
   L.src_ids = ints(Me); L.P = ints(B * k); L.A = ints(B * k * k); L.accepted = ints(B); L.topn_ok = ints(B * k); L.sel = ints(B);

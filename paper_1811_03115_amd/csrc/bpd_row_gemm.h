@@ -11,11 +11,12 @@
 enum { RG_RELU, RG_RES, RG_QKV, RG_PART };
 struct RowGemmP {
   const void* W;                       // packed tiles
-  const void* X;                       // LN: fp32 residual stream [M][K];  otherwise bf16 [M][ldx]
+  const void* X;                       // LN: fp32 residual stream [M][K];  otherwise bf16, packed_at() with K = ldx
   const float* g; const float* b;      // LN: gain, bias
   int M, ntiles, ldx, ldy;
+  bool packed;
   const float* bias;                   // RELU, RES (null: none)
-  void* Y;                             // RELU: bf16 [M][ldy];  RES: fp32 [M][ldy], added to;  PART: fp32 [slice][M][ldy];  QKV: fp32 queries [M][K]
+  void* Y;                             // RELU: bf16 [M][ldy], packed: packed_at() with K = ldy;  RES: fp32 [M][ldy], added to;  PART: fp32 [slice][M][ldy];  QKV: fp32 queries [M][K]
   float eps;
   int ksteps;                          // PART: k-steps of all slices
   // QKV: columns of K each go to the queries (chunk 0), K cache (1), V cache (2), counted from chunk0
@@ -24,7 +25,7 @@ struct RowGemmP {
   bf16_t* Kc; bf16_t* Vc;
   const int* base; const int* seq;     // first key row of each slot (null: 0) and its sequence (null: the slot; -1: none)
   long wz, kvz;                        // several matrices and caches side by side (grid z; cross keys and values of all layers): elements between them
-  bf16_t* vout;                        // not null: values also to [M][K] (a row that sees one key: its attention is that key's value)
+  bf16_t* vout;                        // not null: values also to [M][K], packed_at() (a row that sees one key: its attention is that key's value)
 };
 
 // Y = epilogue(X W) for 16 MT rows x 16 NT columns per workgroup, K = 32 * WAVES * U (PART: of one slice, grid z).  The waves
@@ -59,14 +60,14 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
     for (int i = 0; i < U; ++i) a[u][i] = *(const u32x4*)(Wb + i * 1024 + lane * 16);
   }
   const int ldx = LN ? K : p.ldx;
-  const rsrc_t xr = rsrc_of(p.X, (unsigned)p.M * ldx * XB);
+  const rsrc_t xr = rsrc_of(p.X, (unsigned)(LN ? p.M : (p.M + 15) & ~15) * ldx * XB);
   u32x4 xv[MT][U][LN ? 2 : 1];
 #pragma unroll
   for (int t = 0; t < MT; ++t) {
-    const unsigned off = ((m0 + t * 16 + lr) * ldx + ks0 * 32 + lq * 8) * XB;
+    const unsigned off = LN ? ((m0 + t * 16 + lr) * ldx + ks0 * 32 + lq * 8) * XB : (((m0 >> 4) + t) * (ldx >> 5) + ks0) * 1024 + lane * 16;
 #pragma unroll
     for (int i = 0; i < U; ++i) {
-      xv[t][i][0] = buf_load16(xr, off + i * (32 * XB), 0);
+      xv[t][i][0] = buf_load16(xr, off + i * (LN ? 32 * XB : 1024), 0);
       if constexpr (LN) xv[t][i][1] = buf_load16(xr, off + i * (32 * XB) + 16, 0);
     }
   }
@@ -186,7 +187,7 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
       v += bias[j];
 #pragma unroll
       for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.f);
-      *(u32x2*)((bf16_t*)Y + (size_t)m * p.ldy + n) = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
+      *(u32x2*)((bf16_t*)Y + (p.packed ? packed_at(m, n, p.ldy) : (size_t)m * p.ldy + n)) = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
     } else if constexpr (EPI == RG_RES) {
       v += bias[j];
       v += res[j];
@@ -200,7 +201,7 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
       } else if (sb[j] >= 0) {                   // (a slot behind the last one has no cache rows)
         bf16_t* cache = (c + p.chunk0 == 1 ? Kc : Vc) + blockIdx.z * p.kvz;
         const unsigned lo = cvt_pk_bf16(v[0], v[1]), hi = cvt_pk_bf16(v[2], v[3]);
-        if (p.vout && c + p.chunk0 == 2) *(u32x2*)(p.vout + (size_t)m * K + col) = u32x2{lo, hi};
+        if (p.vout && c + p.chunk0 == 2) *(u32x2*)(p.vout + packed_at(m, col, K)) = u32x2{lo, hi};
         if (p.capg) kv_frag_store(cache, c + p.chunk0 == 2, sb[j], p.heads, p.capg, key0[j] + row0[j], col, lo, hi);
         else *(u32x2*)(cache + (size_t)(key0[j] + row0[j]) * K + col) = u32x2{lo, hi};
       }
@@ -215,12 +216,17 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
 constexpr int ln_row_threads(int D) { return D < 256 ? 64 : D / 4; }
 template <int D, int NSL>
 __global__ __launch_bounds__(ln_row_threads(D)) void ln_row_kernel(float* x, const float* g, const float* b, int M, float eps, bf16_t* ya, float* yf,
-                                                                   const float* part, const float* pbias, u32x4* clear, int nclear) {
+                                                                   const float* part, const float* pbias, u32x4* clear, int nclear, int packed) {
   constexpr int WAVES = ln_row_threads(D) / 64;
   __shared__ float2 st[WAVES];
   const int tid = threadIdx.x;
   const bool in = 4 * tid < D;                   // (D < 256: the last lanes hold zeros)
-  const size_t at = (size_t)blockIdx.x * D + (in ? 4 * tid : 0);
+  int row = blockIdx.x;
+  if (packed) {                                  // ya: packed_at(); a row tile's rows in workgroups of one XCD, whose L2 puts their pieces together
+    row = ((row >> 7) * 8 + (row & 7)) * 16 + ((row >> 3) & 15);
+    if (row >= M) return;
+  }
+  const size_t at = (size_t)row * D + (in ? 4 * tid : 0);
   f32x4 v = *(const f32x4*)(x + at);
   f32x4 pv[NSL > 0 ? NSL : 1], pb;
   if constexpr (NSL > 0) {
@@ -254,6 +260,6 @@ __global__ __launch_bounds__(ln_row_threads(D)) void ln_row_kernel(float* x, con
 #pragma unroll
   for (int r = 0; r < 4; ++r) v[r] = fmaf(fmaf(c[r], rs, off), gv[r], bv[r]);
   if (!in) return;
-  if (ya) *(u32x2*)(ya + at) = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
+  if (ya) *(u32x2*)(ya + (packed ? packed_at(row, 4 * tid, D) : at)) = u32x2{cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3])};
   if (yf) *(f32x4*)(yf + at) = v;
 }
