@@ -1171,19 +1171,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
   }
   // Plain chunk c (weights in AC, activations in xc): chunk c + 1 starts moving into AL / xl, chunk c is multiplied, and
   // the workgroup meets once activation chunk c + 1 has landed: its request is the youngest, so that is when nothing is
-  // outstanding any more.  The last chunk requests itself again (branch-free).
+  // outstanding any more.  Behind the last chunk there is nothing to ask or wait for (it used to ask for itself again: 24 x 16384 x 512 6.0 us, 5.4;  eight groups of 24 x 512 x
+  // 2048 8.1, 7.7;  310 x 1024 x 4096 in four slices 11.9, 10.5).
 #define BPD_CHUNK(AC, AL, xc, xl, c)                                                         \
   {                                                                                          \
-    const int cl = cbase + ((c) + 1 < nchunks ? (c) + 1 : nchunks - 1);                      \
+    const int cl = cbase + (c) + 1;                                                          \
     BPD_LOAD_W(AL, cl)                                                                       \
     BPD_X_TO_LDS(xl, cl)                                                                     \
     __builtin_amdgcn_sched_barrier(0);                                                       \
-    _Pragma("unroll") for (int s = 0; s < KS; ++s) {                                         \
-      BPD_STEP(AC[s], xc, s)                                                                 \
-      __builtin_amdgcn_sched_barrier(0);                                                     \
-    }                                                                                        \
+    BPD_CHUNK_END(AC, xc)                                                                    \
     BPD_WAIT_VM(0);                                                                          \
     __syncthreads();                                                                         \
+  }
+#define BPD_CHUNK_END(AC, xc)                                                                \
+  _Pragma("unroll") for (int s = 0; s < KS; ++s) {                                           \
+    BPD_STEP(AC[s], xc, s)                                                                   \
+    __builtin_amdgcn_sched_barrier(0);                                                       \
   }
   // DEEP chunk c (its two steps' weights in A: a0 / a1 in turn; activations in xa).  The row tiles of a step go in two
   // halves: while the matrix instructions of one half are issued the other half's fragments (of the same step, or of the
@@ -1202,7 +1205,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
 #define BPD_READ_HI(xc, s) _Pragma("unroll") for (int t = 0; t < MH; ++t) bhi[t] = BPD_XFRAG(xc, s, ML + t); __builtin_amdgcn_sched_barrier(0);
 #define BPD_CHUNK_DEEP(A, c)                                                                 \
   {                                                                                          \
-    const int cl = cbase + ((c) + 2 < nchunks ? (c) + 2 : nchunks - 1);                      \
+    const int cl = cbase + (c) + 2;                                                          \
     _Pragma("unroll") for (int s = 0; s < KS - 1; ++s) {                                     \
       BPD_READ_HI(xa, s)                                                                     \
       BPD_HALF(A[s], blo, 0, ML)                                                             \
@@ -1222,31 +1225,58 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
     __builtin_amdgcn_sched_barrier(0);                                                       \
     { const bf16_t* t_ = xa; xa = xb; xb = xf; xf = (bf16_t*)t_; }                           \
   }
+  // The last two chunks ask for nothing (asking for themselves again, so that all chunks are alike, was an eighth of the traffic at K = 1024: 3200 x 32768 x 1024 176 us, 172;  320 x
+  // 40960 x 1024 40.3, 38.5 .. 40.3); younger than the last chunk's activations are then only the weights of its second step.
+#define BPD_CHUNK_LAST(A, MORE)                                                              \
+  {                                                                                          \
+    _Pragma("unroll") for (int s = 0; s < KS - 1; ++s) {                                     \
+      BPD_READ_HI(xa, s)                                                                     \
+      BPD_HALF(A[s], blo, 0, ML)                                                             \
+      BPD_READ_LO(xa, s + 1)                                                                 \
+      BPD_HALF(A[s], bhi, ML, MH)                                                            \
+    }                                                                                        \
+    BPD_READ_HI(xa, KS - 1)                                                                  \
+    BPD_HALF(A[KS - 1], blo, 0, ML)                                                          \
+    if (MORE) {                                                                              \
+      BPD_WAIT_VM(NT);                                                                       \
+      __syncthreads();                                                                       \
+      BPD_READ_LO(xb, 0)                                                                     \
+    }                                                                                        \
+    BPD_HALF(A[KS - 1], bhi, ML, MH)                                                         \
+    xa = xb;                                                                                 \
+  }
   if constexpr (DEEP) {
     static_assert(KS * NT <= 63, "vmcnt range");
     constexpr int ML = MT / 2, MH = MT - ML;
     uint4 blo[ML > 0 ? ML : 1], bhi[MH];
     BPD_READ_LO(xa, 0)
-    for (int c = 0; c < nchunks; c += 2) {       // (an even number of chunks: the host's tile choice sees to it)
+    for (int c = 0; c + 2 < nchunks; c += 2) {   // (an even number of chunks: the host's tile choice sees to it)
       BPD_CHUNK_DEEP(a0, c)
       BPD_CHUNK_DEEP(a1, c + 1)
     }
-    BPD_WAIT_VM(0);                              // the last chunks requested themselves again: those copies still land in LDS
-    __syncthreads();
+    BPD_CHUNK_LAST(a0, true)
+    BPD_CHUNK_LAST(a1, false)
+    __syncthreads();                             // (the epilogue works where the activations lay)
   } else {
     int c = 0;
-    for (; c + 1 < nchunks; c += 2) {
+    for (; c + 2 < nchunks; c += 2) {
       BPD_CHUNK(a0, a1, xs0, xs1, c)
       BPD_CHUNK(a1, a0, xs1, xs0, c + 1)
     }
-    if (c < nchunks) BPD_CHUNK(a0, a1, xs0, xs1, c)
+    if (c + 1 < nchunks) {
+      BPD_CHUNK(a0, a1, xs0, xs1, c)
+      BPD_CHUNK_END(a1, xs1)
+    } else BPD_CHUNK_END(a0, xs0)
+    if (ARGMAX || NT == 4) __syncthreads();      // (the epilogue works where the activations lay)
   }
 #undef BPD_READ_HI
 #undef BPD_READ_LO
 #undef BPD_HALF
 #undef BPD_XFRAG
 #undef BPD_CHUNK_DEEP
+#undef BPD_CHUNK_LAST
 #undef BPD_CHUNK
+#undef BPD_CHUNK_END
 #undef BPD_STEP
 #undef BPD_WAIT_VM
 #undef BPD_LOAD_W
