@@ -129,9 +129,19 @@ __device__ __forceinline__ void attn_load_kv(rsrc_t kr, rsrc_t vr, int c, int nw
     for (int x = 0; x < 4; ++x) vf[gg][x] = __builtin_amdgcn_raw_buffer_load_b128(vr, lane * 16 + x * 1024, at, KVNT ? 2 : 0);
   }
 }
+// ... one of the two
+template <bool KVNT, int G>
+__device__ __forceinline__ void attn_load_one(rsrc_t r, int c, int nw, int lane, u32x4 (&f)[G][4]) {
+#pragma unroll
+  for (int gg = 0; gg < G; ++gg) {
+    const unsigned at = (unsigned)__builtin_amdgcn_readfirstlane(c + gg * nw) * (KV_GROUP * 2);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) f[gg][x] = __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + x * 1024, at, KVNT ? 2 : 0);
+  }
+}
 // The item's work from the point where its queries (qhi + qlo) and the first groups of K and V are at hand or under way (parameters as in
 // attention_mfma_body; first, hop: this split's first group and the distance to its next round; lim: limit[b]).  STORE: no word of the results is EMPTY_WORD (ATTN_WORDS),
-// and they are written through the L2 (ATTN_THROUGH_WORDS).  ONCE: no wave has a second round.
+// and they are written through the L2 (ATTN_THROUGH_WORDS).  ONCE: no wave has a second round.  AHEAD: the next round's keys and values are asked for within this one.
 enum { ATTN_PLAIN, ATTN_WORDS, ATTN_THROUGH_WORDS };
 template <int STORE>
 __device__ __forceinline__ void attention_store(bf16_t* to, const f32x4& v) {
@@ -145,6 +155,7 @@ __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLd
                                                     int nheads, int nz, int tid, int nw, int first, int hop, rsrc_t kr, rsrc_t vr,
                                                     u32x4 (&kf)[G][4], u32x4 (&vf)[G][4], const bf16x8 (&qhi)[2], const bf16x8 (&qlo)[2], int lim, bf16_t* out) {
   constexpr int RT = 16, DH = 64;
+  constexpr bool AHEAD = STORE == ATTN_WORDS && G == 2;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lq = lane >> 4;
   lim = lim < 0 ? 0 : lim;
@@ -181,6 +192,16 @@ __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLd
         }
         sacc[gg][t] = a;
       }
+    // The next round's keys are asked for as soon as their registers are free, also past the last round (the buffer ends there: nothing is read): behind a condition the
+    // compiler would wait for them together with this round's values.  layers_kernel, eight images of up to 3000 intensities, mean over a decode 142.9 us, 140.6 (at 3000
+    // keys 168, 166); three with windows of 520 keys 100.7, 99.9.  Not kept: both sets of registers twice (spills); the later rounds fetched into the L2 by the compute waves
+    // while queries, keys and values are multiplied (147.7 with one round, 151.8 with two: the CU's loads return in order, and the waits for flags queue behind); two
+    // groups per wave in cross-attentions of 192 keys (one round instead of two, 140.8).
+    if constexpr (AHEAD) {
+      __builtin_amdgcn_sched_barrier(0);
+      attn_load_one<KVNT, G>(kr, c + hop + wave, nw, lane, kf);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     mx = max_rows(mx);
     const float m_new = fmaxf(m_run, mx);
     float sum = 0.f;
@@ -229,7 +250,8 @@ __device__ __forceinline__ void attention_mfma_core(const AttnP& p, const AttnLd
       }
     }
     if constexpr (ONCE) break;
-    if (c + hop + wave < ngr) attn_load_kv<KVNT, G>(kr, vr, c + hop + wave, nw, lane, kf, vf);
+    if constexpr (AHEAD) attn_load_one<KVNT, G>(vr, c + hop + wave, nw, lane, vf);
+    else if (c + hop + wave < ngr) attn_load_kv<KVNT, G>(kr, vr, c + hop + wave, nw, lane, kf, vf);
   }
   // (16 dimensions on: 16 elements, or 256 of the packed form)
   const bool packed = STORE == ATTN_PLAIN && p.packed;
