@@ -113,6 +113,131 @@ __device__ __forceinline__ void store_tiles(const Epi& e_in, int g, const f32x4 
   }
 }
 
+// The tiles of a wave that has 64 or 32 whole columns (NT 4, 2), modes and results as store_tiles without statistics; stage: 2 KB of LDS of this wave's own.  store_tiles loads
+// bias and residual tile by tile, and since loads and stores are counted together each waits for the stores before it; for keys and values it divides by the width and the
+// length for every tile and stores values 2 bytes at a time.  Here bias and lookups come first, a row tile's residual ahead of the stores of the one before, and what is the same
+// for the whole wave (which of queries, keys and values; the head) is computed once.  us, so and now: 4096 x 4096 x 1024 to bf16 45 .. 46, 36;  4096 x 1024 x 4096 onto
+// the residual stream 49, 43 (tiles of 64 x 256);  4096 x 1024 x 1024 21.9, 16.3 (the same);  4096 x 3072 x 1024 to queries, keys and values 38, 31 (the same).  What is left of the
+// first is 25 .. 29 us of products per 1024 of K (1.2 .. 1.4 PFLOP/s; 256 x 256 tiles of eight waves that multiply and read in turn take as long) and 10 us for launch, first
+// loads and the 33 MB that it writes.
+template <int MT, int NT>
+__device__ __forceinline__ void finish_tiles(const Epi& e, int g, const f32x4 (&acc)[MT][NT], int m0, int nt0, int ntiles, int M, int lane, unsigned char* stage) {
+  static_assert(NT == 2 || NT == 4, "half a head or a head");
+  constexpr int ROW = NT * 32, SEGS = NT * 2;    // of bf16 in LDS: bytes, pieces of 16
+  const int lr = lane & 15, lq = lane >> 4;
+  if (nt0 + NT > ntiles || (e.mode != 0 && (!e.capg || (e.dsplit & 63))) || (e.mode == 0 && e.Ya && ((e.ldya & 7) || (e.ya_g & 7) || ((size_t)e.Ya & 15)))) {
+    store_tiles<MT, NT, false>(e, g, acc, m0, nt0, ntiles, M, lane, nullptr, nullptr, nullptr, nullptr, nullptr, stage);
+    return;
+  }
+  const int n0 = nt0 * 16;
+  if (e.mode == 0) {
+    f32x4 bs[NT], res[2][NT];
+    auto residual = [&](int t) {
+      int m = m0 + t * 16 + lr;
+      m = m < M ? m : M - 1;
+#pragma unroll
+      for (int u = 0; u < NT; ++u) res[t & 1][u] = *(const f32x4*)(e.R + g * e.r_g + (long)m * e.ldr + n0 + u * 16 + lq * 4);
+    };
+#pragma unroll
+    for (int u = 0; u < NT; ++u) bs[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (e.bias) {
+#pragma unroll
+      for (int u = 0; u < NT; ++u) bs[u] = *(const f32x4*)(e.bias + g * e.bias_g + n0 + u * 16 + lq * 4);
+    }
+    if (e.R) residual(0);
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      const int m = m0 + t * 16 + lr;
+      if (t + 1 < MT && e.R) residual(t + 1);
+      f32x4 v[NT];
+#pragma unroll
+      for (int u = 0; u < NT; ++u) {
+        v[u] = acc[t][u] + bs[u];
+        if (e.relu) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) v[u][r] = fmaxf(v[u][r], 0.f);
+        }
+        if (e.R) v[u] += res[t & 1][u];
+      }
+      if (e.Yf && m < M) {
+#pragma unroll
+        for (int u = 0; u < NT; ++u) *(f32x4*)(e.Yf + g * e.yf_g + (long)m * e.ldyf + n0 + u * 16 + lq * 4) = v[u];
+      }
+      if (e.Ya) {                                // (through LDS, as in store_tiles)
+#pragma unroll
+        for (int u = 0; u < NT; ++u)
+          *(uint2*)(stage + lr * ROW + ((u * 2 + (lane >> 5)) ^ (lr & (SEGS - 1))) * 16 + (lq & 1) * 8) = make_uint2(cvt_pk_bf16(v[u][0], v[u][1]), cvt_pk_bf16(v[u][2], v[u][3]));
+#pragma unroll
+        for (int h = 0; h < NT / 2; ++h) {
+          const int r = h * (64 / SEGS) + lane / SEGS, sg = lane & (SEGS - 1), mm = m0 + t * 16 + r;
+          const uint4 w = *(const uint4*)(stage + r * ROW + ((sg ^ (r & (SEGS - 1))) * 16));
+          if (mm < M) *(uint4*)((bf16_t*)e.Ya + g * e.ya_g + (long)mm * e.ldya + n0 + sg * 8) = w;
+        }
+      }
+    }
+    return;
+  }
+  const int q = __builtin_amdgcn_readfirstlane(n0 / e.dsplit), c = q + e.chunk0, col = __builtin_amdgcn_readfirstlane(n0 - q * e.dsplit);
+  if (c == 0) {
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      const int m = m0 + t * 16 + lr;
+      if (m < M) {
+#pragma unroll
+        for (int u = 0; u < NT; ++u) *(f32x4*)(e.Qf + (long)m * e.dsplit + col + u * 16 + lq * 4) = acc[t][u];
+      }
+    }
+    return;
+  }
+  bf16_t* const cache = (bf16_t*)(c == 1 ? e.Ka : e.Va) + g * e.kv_g + (size_t)(col >> 6) * e.capg * 2048;       // (2048: KV_GROUP)
+  const size_t per_seq = (size_t)(e.dsplit >> 6) * e.capg * 2048;
+  if (c == 2 && !e.seq && !e.base && ((e.rows_per_seq | M) & 7) == 0) {
+    // Values of eight consecutive keys lie side by side: 64 (32) columns x 16 rows go through LDS and leave as 16 bytes per lane instead of 2
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+#pragma unroll
+      for (int u = 0; u < NT; ++u) {
+        const unsigned lo = cvt_pk_bf16(acc[t][u][0], acc[t][u][1]), hi = cvt_pk_bf16(acc[t][u][2], acc[t][u][3]);
+        bf16_t* const to = (bf16_t*)stage + (u * 16 + lq * 4) * 16 + lr;
+        to[0] = (bf16_t)lo; to[16] = (bf16_t)(lo >> 16); to[32] = (bf16_t)hi; to[48] = (bf16_t)(hi >> 16);
+      }
+      const int m = m0 + t * 16 + (lane & 1) * 8, b = m / e.rows_per_seq, key = m - b * e.rows_per_seq;
+#pragma unroll
+      for (int h = 0; h < NT / 2; ++h) {
+        const uint4 w = *(const uint4*)(stage + (h * 64 + lane) * 16);
+        if (m < M) *(uint4*)(cache + b * per_seq + v_frag_at(key, (col & 63) + h * 32 + (lane >> 1))) = w;
+      }
+    }
+    return;
+  }
+  int sb[MT], key[MT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    int m = m0 + t * 16 + lr;
+    const bool in = m < M;
+    m = in ? m : M - 1;
+    const int b = m / e.rows_per_seq;
+    key[t] = m - b * e.rows_per_seq;
+    if (e.base) key[t] += e.base[b];
+    sb[t] = e.seq ? e.seq[b] : b;
+    sb[t] = in ? sb[t] : -1;
+  }
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    if (sb[t] < 0) continue;
+    bf16_t* const dst = cache + sb[t] * per_seq;
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+      const unsigned lo = cvt_pk_bf16(acc[t][u][0], acc[t][u][1]), hi = cvt_pk_bf16(acc[t][u][2], acc[t][u][3]);
+      if (c == 1) *(uint2*)(dst + k_frag_at(key[t], (col & 63) + u * 16 + lq * 4)) = make_uint2(lo, hi);
+      else {
+        bf16_t* const v = dst + v_frag_at(key[t], (col & 63) + u * 16 + lq * 4);
+        v[0] = (bf16_t)lo; v[8] = (bf16_t)(lo >> 16); v[16] = (bf16_t)hi; v[24] = (bf16_t)(hi >> 16);
+      }
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------------------
 // LayerNorm statistics travel with the residual stream: every kernel that writes x (16-column
 // tile by tile) also writes, per tile and row, the partial sum and sum of squares of its 16
@@ -1267,7 +1392,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
       BPD_CHUNK(a0, a1, xs0, xs1, c)
       BPD_CHUNK_END(a1, xs1)
     } else BPD_CHUNK_END(a0, xs0)
-    if (ARGMAX || NT == 4) __syncthreads();      // (the epilogue works where the activations lay)
+    if (ARGMAX || NT >= 2) __syncthreads();      // (the epilogue works where the activations lay)
   }
 #undef BPD_READ_HI
 #undef BPD_READ_LO
@@ -1329,5 +1454,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
     }
     return;
   }
-  store_tiles<MT, NT, STATS, ROWAFF>(e, g, acc, m0, nt0, ntiles, M, lane, ra_ms, ra_c4, ra_d4, PREF ? pre_b : nullptr, PREF ? pre_r : nullptr, smem_raw + wave * 2048);
+  if constexpr (NT >= 2 && MT * NT > 3 && !STATS && !ROWAFF) finish_tiles<MT, NT>(e, g, acc, m0, nt0, ntiles, M, lane, smem_raw + wave * 2048);
+  else store_tiles<MT, NT, STATS, ROWAFF>(e, g, acc, m0, nt0, ntiles, M, lane, ra_ms, ra_c4, ra_d4, PREF ? pre_b : nullptr, PREF ? pre_r : nullptr, smem_raw + wave * 2048);
 }

@@ -101,6 +101,8 @@ __device__ __forceinline__ void row_moments(const float2* st, int stride, float 
 //          (a K/V cache write at the sequence's current length; with slots cap is 0 and base holds whole cache rows,
 //          StateP::slot_row).  capg > 0: 64-wide heads, whose caches lie in operand order (bpd_attention.h), capg groups of 32
 //          keys per sequence; base is then always the sequence's length, and seq (null: the slot; -1: none) its place.
+__device__ __forceinline__ unsigned k_frag_at(int key, int c);        // bpd_attention.h
+__device__ __forceinline__ unsigned v_frag_at(int key, int c);
 __device__ __forceinline__ void kv_frag_store(bf16_t* cache, bool is_v, int sb, int heads, int capg, int key, int col, unsigned lo, unsigned hi);   // bpd_attention.h
 struct Epi {
   int mode;
