@@ -324,7 +324,7 @@ bool dispatch_ldsx(const GemmP& p, const Epi& e_in, unsigned long long* keys, fl
   int mt, nt;
   const int kslice = p.ksplit > 1 ? p.K / p.ksplit : p.K;
   const bool stats_req = !ARGMAX && e.mode == 0 && e.stats_out != nullptr && groups == 1 && p.ksplit <= 1;
-  pick_tile(p.M, p.N, kslice, groups, mt, nt, stats_req ? LDSX_LN_MT_MAX : 8);   // groups = K slices for a split-K launch
+  pick_tile(p.M, p.N, kslice, groups, mt, nt, stats_req ? LDSX_LN_MT_MAX : 8, !ARGMAX);   // groups = K slices for a split-K launch
   // (the statistics are per 64-column block: every wave of a workgroup must own whole tiles of it)
   const bool stats = stats_req && p.N % (64 * nt) == 0;
   if constexpr (!ARGMAX) prefetch_epilogue(e, p, mt, nt, zeros);

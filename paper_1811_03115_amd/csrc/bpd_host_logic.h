@@ -333,12 +333,32 @@ void pick_tile_by_area(int M, int N, int K, long zdim, int& mt, int& nt, int mt_
     }
   }
 }
-// A long K and many rows: a tile of 256 columns that gives every CU one workgroup, and hardly more CUs than that, keeps four steps of weights in flight per wave and
-// fetches least per product.  us, the rule above and this: 3584 x 1024 x 4096 47.9, 41.1;  4096 51.6, 43.6;  5000 59.0, 56.9;  6144 73.1, 62.6;  8192 93.1, 72.5;  5000 x 768 x
-// 3072 46.1, 37.2;  6144 50.9, 43.0;  8192 64.1, 52.8.  (K = 2048: 4096 x 1024 31.7, 30.0, but 5000 36.2, 40.9.  Below 220 workgroups the rule above is as good: 4096 x 1024 at
-// 208 47.2, 3000 at 188 53.7 against 39.5.)
-constexpr int LDSX_ONE_ROUND_K = 3072, LDSX_ONE_ROUND_M = 2048;
-constexpr long LDSX_ONE_ROUND_MIN = 220, LDSX_ONE_ROUND_MAX = 256;
+// More rows than the kernels of constant K take, one group (encoders): the tile of the least estimated time.  In us, per 1024 of K: a workgroup on its own `lat`, the busiest CU
+// with w workgroups `area` per tile of 16 x 64 (mt * nt) and `edge` per operand tile that it fetches (mt + 4 nt); once: `fixed`, and `out` per 8 tiles of 16 x 64 that the CU
+// stores.  Fitted to 485 products of 700 .. 8192 rows, 384 .. 4096 columns, K 384 .. 4096, each with fourteen tiles (products and residual updates, keys and values): 3 % slower
+// than the best tile on average, 11 % at the ninth decile, where the largest useful area (and, beyond K = 3072, one round of 256-column tiles) was 12 % and 31 %.  us, so and now:
+// 2560 x 1024 x 4096 47.1, 33.2;  4096 x 3072 x 1024 40.4, 31.6;  8192 x 1024 x 1024 32.8, 25.5;  3072 x 1536 x 512 12.7, 9.9;  slower by more than 10 % 13 of them (4096 x 1536 x 512
+// 14.7 against 11.6 for the best of all).
+constexpr int LDSX_COST_M = 640;
+inline float ldsx_cost(int M, int N, int K, int mt, int nt) {
+  struct C { float fixed, area, edge, lat, out; };
+  constexpr C of[4] = {{3.65f, .20f, .15f, 1.46f, 1.05f}, {1.49f, .30f, .09f, 8.05f, 1.36f}, {3.31f, .34f, .12f, 3.81f, .75f}, {3.15f, .42f, .18f, 1.98f, .56f}};
+  const C& c = of[nt == 4 ? (mt >= 4 ? 0 : 1) : (nt == 2 ? 2 : 3)];
+  const long wgs = (long)((M + 16 * mt - 1) / (16 * mt)) * ((N + 64 * nt - 1) / (64 * nt)), w = (wgs + 255) / 256;
+  const int side_by_side = nt == 4 ? (mt >= 5 ? 2 : 3) : (nt == 2 && mt >= 4 ? (mt >= 7 ? 2 : 3) : 4);
+  const float k = K / 1024.f, busy = w * (c.area * (mt * nt) + c.edge * (mt + 4 * nt)) * k, alone = (w + side_by_side - 1) / side_by_side * c.lat * k;
+  return c.fixed + (busy > alone ? busy + .5f * alone : alone + .5f * busy) + c.out * w * (mt * nt) * .125f;
+}
+inline bool pick_tile_by_cost(int M, int N, int K, int& mt, int& nt) {
+  float best = 0.f;
+  for (int n : {4, 2, 1})
+    for (int m : {8, 7, 5, 4, 3, 2, 1}) {
+      if (K % (n == 4 && m >= 4 ? 128 : 256 / n) != 0 || (n == 1 ? m > 3 : m == 1)) continue;
+      const float c = ldsx_cost(M, N, K, m, n);
+      if (best == 0.f || c < best) { best = c; mt = m; nt = n; }
+    }
+  return best > 0.f;
+}
 // Several groups with a long K and few rows (the heads' output layers) stream their weights, and what counts are the rounds of one workgroup per CU: us by row tiles and rounds, of
 // 8 and 10 groups of 4096 x 1024 out of memory.  us, by largest useful area and by this: 8 groups, 64 rows 26.1, 22.7;  80 33.2, 23.9;  104 35.2, 29.4;  130 46.0, 33.4;  10 groups,
 // 64 rows 36.9, 30.7;  80 35.6, 28.0;  130 37.3, 33.3;  2048 x 512, 10 groups, 104 rows 12.6, 10.4.  (Two groups: not measured.)  K slices of 2048 or more go by it, too: six layers of d = 1024, d_ff = 8192, 130 rows 438, 420, in four slices of
@@ -353,7 +373,9 @@ inline int ldsx_rounds_cost(int mt, long wgs) {
   const long r = (wgs + 255) / 256;
   return r <= 4 ? us[mt - 1][r - 1] : us[mt - 1][3] + (int)(r - 4) * 100;
 }
-void pick_tile(int M, int N, int K, long zdim, int& mt, int& nt, int mt_max = 8) {
+// by_cost: not for the vocabulary projection, which stores nothing
+void pick_tile(int M, int N, int K, long zdim, int& mt, int& nt, int mt_max = 8, bool by_cost = true) {
+  if (by_cost && M > LDSX_COST_M && zdim == 1 && mt_max >= 8 && pick_tile_by_cost(M, N, K, mt, nt)) return;
   pick_tile_by_area(M, N, K, zdim, mt, nt, mt_max);
   if (zdim > 2 && K >= 2048 && K % 256 == 0 && M > 16 && M <= LDSX_ROUNDS_M && mt_max >= 3) {
     const long wide = (N / 16 + 7) / 8;
@@ -365,11 +387,6 @@ void pick_tile(int M, int N, int K, long zdim, int& mt, int& nt, int mt_max = 8)
     }
     return;
   }
-  if (K >= LDSX_ONE_ROUND_K && K % 128 == 0 && M >= LDSX_ONE_ROUND_M && zdim == 1 && mt_max >= 8)
-    for (int m : {8, 7, 5, 4}) {
-      const long wgs = (long)((M + 16 * m - 1) / (16 * m)) * ((N / 16 + 15) / 16);
-      if (wgs >= LDSX_ONE_ROUND_MIN && wgs <= LDSX_ONE_ROUND_MAX) { mt = m; nt = 4; return; }
-    }
 }
 
 // In-place residual update with a long K and few output tiles on the LDS-staged kernel: the number of K slices it is
@@ -379,7 +396,7 @@ void pick_tile(int M, int N, int K, long zdim, int& mt, int& nt, int mt_max = 8)
 inline int residual_k_slices_of(int d_model, size_t n_kpart, int M, int N, int K) {
   if (N != d_model || K < 2048 || K % 64 != 0) return 1;
   int mt, nt, ns = 1;
-  pick_tile(M, N, K, 1, mt, nt);
+  pick_tile(M, N, K, 1, mt, nt, 8, false);
   if (nt == 1 && mt < 3) {
     for (int t = 2; t <= KSPLIT_MAX && K % (t * 512) == 0 && (size_t)t * M * N <= n_kpart; t *= 2) {
       ns = t;
