@@ -503,21 +503,25 @@ template <bool KVNT, bool LIMF, int QU>
 __global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_slots_kernel(AttnP p, QProjP qp) { attention_mfma_entry<KVNT, LIMF, QU, true>(p, qp); }
 // The same with queries projected inside (QU > 1) for two sequences of up to 128 keys per workgroup: one reading of the head's weights serves two row tiles, and each half of the waves
 // then has one of the sequences.  (One workgroup per sequence: with more than 128 of them the weights, 128 KB each at d = 1024, cost more than the kernels saved.)
-// A wave normalises whole rows, a line at a time, and the operands are read out of the LDS: as operands straight from the rows in memory a load touches 64 lines, which the L1 looks up one by
-// one (64 cycles instead of 16: of 20 rows the last wave had its sums 4 us after the launch).
+// A wave normalises whole rows, half a line of eight places at a time, and the operands are read out of the LDS: as operands straight from the rows in memory a load touches 64 lines, which the
+// L1 looks up one by one (64 cycles instead of 16: of 20 rows the last wave had its sums 4 us after the launch).
+// Every sum is taken in the order of row_gemm_kernel with LayerNorm inside: moments of 128 columns by four lanes each, products of 128 of K one behind the other, these parts in turn.  Up to
+// where that kernel is the other way (lean_fuse()) the queries have its bits.
 template <int QU>
 struct AttnPairsLds {
-  static constexpr int K = 128 * QU, XS = 32 * (K + 8) * 2, RED = ATTN_WAVES * 8 * 64 * 16, QS = 2 * 512 * 8, ML = 2 * ATTN_WAVES * 16 * 4;
+  static constexpr int K = 128 * QU, XS = 32 * (K + 8) * 2, RED = QU * 8 * 64 * 16, QS = 2 * 512 * 8, ML = 2 * ATTN_WAVES * 16 * 4;
   static constexpr int BYTES = XS + RED + QS + ML;
+  static_assert(RED >= 2 * (int)AttnLds::OS_BYTES && QS >= 32 * QU * 8, "the halves' results; a row's moments");
 };
 template <int QU, bool SLOTS>
 __global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_pairs_kernel(AttnP p, QProjP qp, int B) {
-  constexpr int NW = ATTN_WAVES, K = 128 * QU, KSTEPS = K / 32, U = KSTEPS / NW, H = K / 256;
-  static_assert(U * NW == KSTEPS && H * 256 == K, "every wave has k-steps, every lane columns");
+  // parts of 128 columns, of U k-steps; row tiles per wave; rows that a wave normalises at once, and how often
+  constexpr int NW = ATTN_WAVES, K = 128 * QU, U = 4, KSTEPS = QU * U, TW = 2 * QU / NW, RW = 16 / QU, PASSES = 32 / (NW * RW);
+  static_assert(TW * NW == 2 * QU && PASSES * NW * RW == 32, "every wave has a part and row tiles, every row lanes");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   using Lds = AttnPairsLds<QU>;
-  bf16_t* xs = (bf16_t*)smem_raw;                // normalised rows, K + 8 apart
-  f32x4* red = (f32x4*)(smem_raw + Lds::XS);     // partial sums [wave][row tile, column tile][lane]; then the halves' results, as AttnLds
+  bf16_t* xs = (bf16_t*)smem_raw;                // normalised rows, K + 8 apart, k-step i of part w at i ^ (w & 3): the pieces that 16 lanes store lie in different banks
+  f32x4* red = (f32x4*)(smem_raw + Lds::XS);     // partial sums [part][row tile, column tile][lane]; then the halves' results, as AttnLds
   u32x2* q_s = (u32x2*)(smem_raw + Lds::XS + Lds::RED);
   float (*m_s)[16] = (float (*)[16])(smem_raw + Lds::XS + Lds::RED + Lds::QS), (*l_s)[16] = m_s + NW;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = wave >> 2;
@@ -529,18 +533,23 @@ __global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_pairs_kernel(A
     if (s0 < 0 && s1 < 0) return;                // (the whole workgroup)
     sb = half ? s1 : s0;
   }
-  const int ks0 = wave * U, rows = __builtin_amdgcn_readfirstlane(there * p.R);
-  // every load of the kernel but keys and values: rows wave, wave + 8, .. of x first
-  f32x4 v[4][H], g[H], be[H];
+  const int kg = wave % QU, t0 = wave / QU * TW, ks0 = kg * U, rows = __builtin_amdgcn_readfirstlane(there * p.R);
+  // every load of the kernel but keys and values: rows of x first (those past the last: zeros).  A lane has k-steps of eight columns of a part, as the operands are
+  const int part = (lane >> 2) % QU, pq = lane & 3, row0 = wave * RW + (lane >> 2) / QU, at = part * 128 + pq * 8;
+  f32x4 v[PASSES][U][2], g[U][2], be[U][2];
   const rsrc_t xr = rsrc_of(qp.x + (size_t)b0 * p.R * K, (unsigned)rows * K * 4);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if (wave + NW * i >= rows) break;
+  for (int n = 0; n < PASSES; ++n) {
+    if ((wave + NW * n) * RW >= rows) break;
 #pragma unroll
-    for (int c = 0; c < H; ++c) v[i][c] = __builtin_bit_cast(f32x4, buf_load16(xr, (unsigned)((wave + NW * i) * K + c * 256 + lane * 4) * 4, 0));
+    for (int i = 0; i < U; ++i)
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) v[n][i][hh] = __builtin_bit_cast(f32x4, buf_load16(xr, (unsigned)((row0 + NW * RW * n) * K + at + i * 32 + hh * 4) * 4, 0));
   }
 #pragma unroll
-  for (int c = 0; c < H; ++c) { g[c] = *(const f32x4*)(qp.g + c * 256 + lane * 4); be[c] = *(const f32x4*)(qp.b + c * 256 + lane * 4); }
+  for (int i = 0; i < U; ++i)
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) { g[i][hh] = *(const f32x4*)(qp.g + at + i * 32 + hh * 4); be[i][hh] = *(const f32x4*)(qp.b + at + i * 32 + hh * 4); }
   int lim = p.limit[bc];
   u32x4 wf[4][U];
 #pragma unroll
@@ -559,33 +568,46 @@ __global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_pairs_kernel(A
   attn_load_kv<false, 1>(kr, vr, wave & 3, 4, lane, kf, vf);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if (wave + NW * i >= rows) break;
+  for (int n = 0; n < PASSES; ++n) {
+    if ((wave + NW * n) * RW >= rows) break;
+    float2* const st = (float2*)q_s + (row0 + NW * RW * n) * QU;       // (of this wave's rows: written and read by it alone)
     f32x4 s4 = f32x4{0.f, 0.f, 0.f, 0.f}, q4 = s4;
 #pragma unroll
-    for (int c = 0; c < H; ++c) s4 += v[i][c];
-    const float mu = wave_sum((s4[0] + s4[1]) + (s4[2] + s4[3])) * (1.f / K);
+    for (int i = 0; i < U; ++i)
 #pragma unroll
-    for (int c = 0; c < H; ++c) {
-      v[i][c] -= mu;
+      for (int hh = 0; hh < 2; ++hh) s4 += v[n][i][hh];
+    const float s = quad_sum((s4[0] + s4[1]) + (s4[2] + s4[3])), mw = s * (1.f / 128);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) q4[r] = fmaf(v[i][c][r], v[i][c][r], q4[r]);
-    }
-    const float rs = inv_sqrt(fmaf(wave_sum((q4[0] + q4[1]) + (q4[2] + q4[3])), 1.f / K, qp.eps));
+    for (int i = 0; i < U; ++i)
 #pragma unroll
-    for (int c = 0; c < H; ++c) {
-      f32x4 y;
+      for (int hh = 0; hh < 2; ++hh) {
+        v[n][i][hh] -= mw;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) y[r] = fmaf(v[i][c][r] * rs, g[c][r], be[c][r]);
-      *(u32x2*)(xs + (wave + NW * i) * (K + 8) + c * 256 + lane * 4) = u32x2{cvt_pk_bf16(y[0], y[1]), cvt_pk_bf16(y[2], y[3])};
+        for (int r = 0; r < 4; ++r) q4[r] = fmaf(v[n][i][hh][r], v[n][i][hh][r], q4[r]);
+      }
+    const float q = quad_sum((q4[0] + q4[1]) + (q4[2] + q4[3]));
+    if (pq == 0) st[part] = make_float2(s, q);
+    __builtin_amdgcn_wave_barrier();
+    float mu, rs;
+    row_moments<QU, 128>(st, 1, qp.eps, mu, rs);
+    const float off = (mw - mu) * rs;
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      float y[8];
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) y[4 * hh + r] = fmaf(fmaf(v[n][i][hh][r], rs, off), g[i][hh][r], be[i][hh][r]);
+      *(u32x4*)(xs + (row0 + NW * RW * n) * (K + 8) + part * 128 + (i ^ (part & 3)) * 32 + pq * 8) =
+          u32x4{cvt_pk_bf16(y[0], y[1]), cvt_pk_bf16(y[2], y[3]), cvt_pk_bf16(y[4], y[5]), cvt_pk_bf16(y[6], y[7])};
     }
   }
   lk_barrier();
-  f32x4 qa[2][4];
-  const bf16_t* row[2];                          // (rows past the last: the last)
+  f32x4 qa[TW][4];
+  const bf16_t* row[TW];                         // (rows past the last: the last)
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int m = t * p.R + (lr < p.R ? lr : p.R - 1);
+  for (int t = 0; t < TW; ++t) {
+    const int m = (t0 + t) * p.R + (lr < p.R ? lr : p.R - 1);
     row[t] = xs + (m < rows ? m : rows - 1) * (K + 8) + ks0 * 32 + lq * 8;
 #pragma unroll
     for (int j = 0; j < 4; ++j) qa[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -593,24 +615,24 @@ __global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_pairs_kernel(A
 #pragma unroll
   for (int i = 0; i < U; ++i)
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const bf16x8 x8 = __builtin_bit_cast(bf16x8, *(const u32x4*)(row[t] + i * 32));
+    for (int t = 0; t < TW; ++t) {
+      const bf16x8 x8 = __builtin_bit_cast(bf16x8, *(const u32x4*)(row[t] + (i ^ (kg & 3)) * 32));
 #pragma unroll
       for (int j = 0; j < 4; ++j) qa[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[j][i]), x8, qa[t][j], 0, 0, 0);
     }
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+  for (int t = 0; t < TW; ++t)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) red[(wave * 8 + t * 4 + j) * 64 + lane] = qa[t][j];
+    for (int j = 0; j < 4; ++j) red[(kg * 8 + (t0 + t) * 4 + j) * 64 + lane] = qa[t][j];
   lk_barrier();
   {                                              // wave 4 t + j finishes column tile j of row tile t
-    f32x4 part[NW];
+    f32x4 part[QU];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) part[w] = red[(w * 8 + wave) * 64 + lane];
+    for (int w = 0; w < QU; ++w) part[w] = red[(w * 8 + wave) * 64 + lane];
     __builtin_amdgcn_sched_barrier(0);
     f32x4 sum = part[0];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) sum += part[w];
+    for (int w = 1; w < QU; ++w) sum += part[w];
 #pragma unroll
     for (int r = 0; r < 4; ++r) sum[r] *= p.scale;
     u32x2 hi, lo;

@@ -65,9 +65,13 @@ __device__ __forceinline__ float max_rows(float v) {
 }
 // ... and over the whole wave: lanes of a 16-lane row first (data-parallel-primitive moves), then the rows
 template <int CTRL> __device__ __forceinline__ float dpp_move(float v) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true)); }
-__device__ __forceinline__ float wave_sum(float v) {
+// (four lanes side by side: added as sum_rows() adds its four)
+__device__ __forceinline__ float quad_sum(float v) {
   v += dpp_move<0xB1>(v);                        // quad_perm 1 0 3 2
-  v += dpp_move<0x4E>(v);                        // quad_perm 2 3 0 1
+  return v + dpp_move<0x4E>(v);                  // quad_perm 2 3 0 1
+}
+__device__ __forceinline__ float wave_sum(float v) {
+  v = quad_sum(v);
   v += dpp_move<0x141>(v);                       // row_half_mirror
   v += dpp_move<0x140>(v);                       // row_mirror
   return sum_rows(v);

@@ -67,6 +67,24 @@ def test_two_sequences_per_workgroup(k, B, S, d, ended):
     lockstep(config(k, B, S, 4 * k + 1, layers=1, d=d), 4 if ended else 2, budgets)
 
 
+# Their queries have the bits of the separate kernels up to the rows whose LayerNorm those take inside the query projection (d = 512: 256, 1024: 32; sums in the same order): room for
+# sources of 160 tokens takes the separate kernels, and states and scores are the same
+@pytest.mark.parametrize("k,B,S,d,F", [(1, 17, 33, 512, 2048), (8, 20, 40, 512, 2048), (4, 64, 100, 512, 1024), (1, 32, 128, 1024, 4096), (2, 16, 64, 1024, 1024), (3, 10, 9, 1024, 2048)])
+def test_two_sequences_per_workgroup_bits(k, B, S, d, F):
+    cfg = wl.Config("pairs", 81, 1, 2, d, d // 64, F, 528, k, B, 160, 3 * k + 4, "bf16", 2)
+    weights = wl.make_weights(cfg)
+    src, n = (a[:, :S] if a.ndim > 1 else np.minimum(a, S - np.arange(B) % max(1, S // 2)).astype(np.int32) for a in wl.make_sources(cfg))
+    src = np.ascontiguousarray(np.where(np.arange(S)[None, :] < n[:, None], src, cfg.pad_id)).astype(np.int32)
+    seen = []
+    for room in (160, S):
+        w = dict(weights, pos_src=np.ascontiguousarray(weights["pos_src"][:room]))
+        ctx = gpu_context(dataclasses.replace(cfg, max_src=room), w)
+        ctx.bpd_encode(src, n, np.full(B, cfg.max_out, np.int32))
+        seen.append([np.asarray(ctx.bpd_get_state()[0])] + [ctx.bpd_debug_step_logits(r).cpu().numpy().copy() for r in sorted({1, k})])
+    for separate, pairs in zip(*seen):
+        np.testing.assert_array_equal(pairs, separate)
+
+
 # caches of more keys than a workgroup takes in one round, of more than 1024, which three workgroups share, two slots per job, a window.  Both ways the logits
 # are within TOL of the oracle's (shown above and for the kernel chain elsewhere), so within twice that of each other.
 @pytest.mark.parametrize("k,B,out,steps,local,d", [(16, 1, 400, 20, 0, 512), (10, 3, 700, 60, 0, 512), (16, 8, 1100, 66, 0, 512), (8, 16, 600, 60, 0, 512), (9, 2, 700, 70, 256, 512),
