@@ -1269,7 +1269,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
     ra_part[MT == 1 ? tid : wave * 64 + lane] = make_float2(sq, qq);      // [class][16 rows] or [wave][64 rows]
   }
   __syncthreads();
-  if constexpr (ROWAFF) {                        // read back in the epilogue, many barriers later
+  if constexpr (ROWAFF) {                        // read back in the epilogue, behind a barrier of the loop's or (one chunk) the one after it
     if (tid < BM) {
       constexpr int NP = MT == 1 ? 16 : 4, PS = MT == 1 ? 16 : 64;
       float S = ra_part[tid].x, Q = ra_part[tid].y;
@@ -1392,7 +1392,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_
       BPD_CHUNK(a0, a1, xs0, xs1, c)
       BPD_CHUNK_END(a1, xs1)
     } else BPD_CHUNK_END(a0, xs0)
-    if (ARGMAX || NT >= 2) __syncthreads();      // (the epilogue works where the activations lay)
+    // The epilogue works where the activations lay (NT >= 2, arg-max), or reads what other waves wrote behind the last barrier (ROWAFF with one chunk: ra_ms)
+    if (ARGMAX || NT >= 2 || (ROWAFF && nchunks == 1)) __syncthreads();
   }
 #undef BPD_READ_HI
 #undef BPD_READ_LO

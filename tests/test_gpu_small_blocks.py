@@ -43,6 +43,19 @@ def test_encoder_large_tiles(d, F, B, S, ragged):
     lockstep(cfg, 1)
 
 
+# LayerNorm folded into weights of K = 256, which the tiles of 64 columns walk in one chunk: the row statistics that the first wave puts together are for all four.  (d_ff 640 and more
+# than 640 rows: no kernels of constant K.)  Every sequence's scores
+@pytest.mark.parametrize("F,k,B", [(640, 10, 60), (640, 9, 17), (1024, 13, 50)])
+def test_folded_weights_of_one_chunk(F, k, B):
+    cfg = wl.Config("fold", 82, 1, 2, 256, 4, F, 272, k, B, 5, 2 * k + 4, "bf16", 2, src_len_kind="lognormal")
+    weights = wl.make_weights(cfg)
+    ctx = gpu_context(cfg, weights)
+    src, n = wl.make_sources(cfg)
+    ls = LockStep(cfg, weights, ctx, src, n, np.full(B, cfg.max_out, np.int32), sample=range(B))
+    for _ in range(2):
+        ls.step(imposed=np.full(B, k, np.int32))
+
+
 # K slices of the encoder (F > 2048) of more source rows than the decoder ever has: up to 192 rows leave some
 @pytest.mark.parametrize("d,F,B,S", [(1024, 4096, 1, 17), (1024, 4096, 4, 48), (768, 3072, 1, 70), (512, 4096, 1, 193)])
 def test_encoder_slices(d, F, B, S):
