@@ -958,13 +958,20 @@ __device__ __forceinline__ unsigned lds_address(const void* p) {
 // XI * 4096 bytes).
 // Two workgroups share a CU whenever the accumulators (4*MT*NT registers), the two weight chunks
 // (8*NT*KC/32) and the operand fragments (4*MT) leave room for it in half the register file: the
-// second wave per SIMD covers the LDS and memory latencies of the first.
+// second wave per SIMD covers the LDS and memory latencies of the first.  Tiles of 256 columns get three (64 and 48 rows) or four (32 and 16) where a third or a quarter will do: the
+// code of the last chunks takes a few registers more than the loop needs (48 rows 178 instead of 148, 32 rows 132 instead of 124: a workgroup per CU less), which the compiler saves when it is
+// told how many waves there have to be, without scratch.  us, so and now: 3200 x 32768 x 1024 with arg-max in tiles of 48 rows 247, 217, of 64 190, 182; 4096 x 2048 x 512 of 48 rows 20.0,
+// 17.0, of 32 20.1, 18.2.  (Narrower tiles need the registers for loads under way: the heads' output layers of two-phase steps in 16 x 64 tiles 14.0 us, with four waves asked for 17.5.  AFFINE:
+// forms that keep row statistics or LayerNorm operands would spill.)
 template <int MT, int NT, int KC>
 constexpr int ldsx_regs() { return 4 * MT * NT + 8 * NT * (KC / 32) + 4 * MT + 40; }
-template <int MT, int NT, int KC>
-constexpr int ldsx_waves_min() { return ldsx_regs<MT, NT, KC>() <= 272 ? 2 : 1; }
-template <int MT, int NT, int KC>
-constexpr int ldsx_waves_max() { return ldsx_regs<MT, NT, KC>() <= 168 ? 4 : ldsx_waves_min<MT, NT, KC>(); }
+template <int MT, int NT, int KC, bool AFFINE = false>
+constexpr int ldsx_waves_min() {
+  constexpr int R = ldsx_regs<MT, NT, KC>();
+  return NT == 4 && !AFFINE && R <= 184 ? (R <= 144 ? 4 : 3) : (R <= 272 ? 2 : 1);
+}
+template <int MT, int NT, int KC, bool AFFINE = false>
+constexpr int ldsx_waves_max() { return ldsx_regs<MT, NT, KC>() <= 168 ? 4 : ldsx_waves_min<MT, NT, KC, AFFINE>(); }
 
 // Large tiles (64 or more rows, 256 columns, chunks of 64) keep more in flight (DEEP): four 32-deep steps of weights in
 // registers, each requested again right after the step that used them (what a chunk waits for is the slowest of its ~100
@@ -989,7 +996,7 @@ constexpr size_t ldsx_lds_bytes() { return (size_t)(ldsx_deep<MT, NT, KC>() ? 3 
 // producer's partial statistics (requested before everything else, reduced while the first chunk arrives), applied in
 // the epilogue.  X comes through the direct loads like any bf16 operand: no LayerNorm kernel and no normalisation here.
 template <int MT, int NT, int KC, bool ARGMAX, bool XLN, bool STATS, bool ROWAFF = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_min<MT, NT, KC>(), ldsx_waves_max<MT, NT, KC>()))) void gemm_ldsx_kernel(GemmP p, Epi e, unsigned long long* keys, float* logits, LnP ln, LiveP live) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ldsx_waves_min<MT, NT, KC, XLN || ROWAFF>(), ldsx_waves_max<MT, NT, KC, XLN || ROWAFF>()))) void gemm_ldsx_kernel(GemmP p, Epi e, unsigned long long* keys, float* logits, LnP ln, LiveP live) {
   constexpr int BM = 16 * MT, KS = KC / 32, SEG = KC / 8;
   static_assert(!ROWAFF || (BM <= 64 && !XLN && !ARGMAX), "row statistics: one pass over at most 64 rows");
   __shared__ float2 ra_part[ROWAFF ? 4 * 64 : 1];

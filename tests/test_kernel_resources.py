@@ -78,3 +78,29 @@ def test_no_step_kernel_uses_scratch(tmp_path):
         hits = [n for n in by_name if re.search(r"(^|\W)" + re.escape(req) + r"(\W|$)", n)]
         assert hits, f"kernel {req} not found"
         assert all(by_name[n] == 0 for n in hits), f"{req} uses scratch"
+
+
+def tile_waves(tmp_path, tiles):
+    """Waves per SIMD that the registers of gemm_ldsx_kernel<MT, NT, KC>, plain and with arg-max, leave room for."""
+    hipcc = build.hipcc()
+    if shutil.which(hipcc) is None and not os.path.exists(hipcc):
+        pytest.skip("hipcc not found")
+    src = tmp_path / "tiles.hip"
+    csrc = os.path.dirname(build.SOURCES[0])
+    src.write_text(f'#include "{csrc}/bpd_kernels.h"\n' + "".join(
+        f"template __global__ void gemm_ldsx_kernel<{mt}, {nt}, {256 // nt}, {m}, false, false, false>(GemmP, Epi, unsigned long long*, float*, LnP, LiveP);\n"
+        for mt, nt in tiles for m in ("false", "true")))
+    flags = [f for f in build.FLAGS if f not in ("-shared", "-fPIC")]
+    res = subprocess.run([hipcc] + flags + ["--cuda-device-only", "-c", str(src), "-o", str(tmp_path / "tiles.o"), "-Rpass-analysis=kernel-resource-usage"],
+                         stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert res.returncode == 0, res.stdout[-2000:]
+    found = re.findall(r"Function Name: _Z\d+gemm_ldsx_kernelILi(\d)ELi(\d)ELi\d+ELb([01])E.*?Occupancy \[waves/SIMD\]: (\d)", res.stdout, re.S)
+    assert len(found) == 2 * len(tiles)
+    return {(int(mt), int(nt), m == "1"): int(w) for mt, nt, m, w in found}
+
+
+def test_waves_of_wide_tiles(tmp_path):
+    """Tiles of 256 columns: three workgroups per CU up to 64 rows, four up to 32."""
+    waves = tile_waves(tmp_path, [(mt, 4) for mt in (1, 2, 3, 4, 5, 7, 8)])
+    for (mt, nt, _), w in waves.items():
+        assert w == (4 if mt <= 2 else (3 if mt <= 4 else 2)), f"{16 * mt} x 256: {w} waves per SIMD"
