@@ -311,9 +311,7 @@ size_t build_layout(const bpd_config& c, char* base, Layout& L, std::vector<std:
 constexpr int LDSX_LN_MT_MAX = 3;      // LayerNorm-fused consumers and statistics-writing producers: tiles of at most 48 rows
 constexpr long LDSX_MIN_WGS = 440;
 constexpr long LDSX_MIN_WGS_LONGK = 400;   // K >= 2048, fewer than 1024 rows: a workgroup lives long enough that about 1.5 per CU suffice
-// (chosen at 80 .. 320 rows.  Of 64 GEMMs of 700 .. 4096 rows its tile is within 5 % of the best at 37 and within 10 % at 48; worst: 780 x 3072 x 1024 25.8 us, 80 x 128 tiles
-// 15.5; 2240 x 1024 x 4096 50.8, 39.6)
-// The largest useful area that fills the chip
+// The largest useful area that fills the chip: several groups, K slices, arg-max, up to LDSX_COST_M rows (chosen at 80 .. 320 rows)
 void pick_tile_by_area(int M, int N, int K, long zdim, int& mt, int& nt, int mt_max) {
   const int mts[7] = {8, 7, 5, 4, 3, 2, 1};
   long best_area = 0, best_pad = 0;
@@ -333,19 +331,28 @@ void pick_tile_by_area(int M, int N, int K, long zdim, int& mt, int& nt, int mt_
     }
   }
 }
-// More rows than the kernels of constant K take, one group (encoders): the tile of the least estimated time.  In us, per 1024 of K: a workgroup on its own `lat`, the busiest CU
-// with w workgroups `area` per tile of 16 x 64 (mt * nt) and `edge` per operand tile that it fetches (mt + 4 nt); once: `fixed`, and `out` per 8 tiles of 16 x 64 that the CU
-// stores.  Fitted to 485 products of 700 .. 8192 rows, 384 .. 4096 columns, K 384 .. 4096, each with fourteen tiles (products and residual updates, keys and values): 3 % slower
-// than the best tile on average, 11 % at the ninth decile, where the largest useful area (and, beyond K = 3072, one round of 256-column tiles) was 12 % and 31 %.  us, so and now:
-// 2560 x 1024 x 4096 47.1, 33.2;  4096 x 3072 x 1024 40.4, 31.6;  8192 x 1024 x 1024 32.8, 25.5;  3072 x 1536 x 512 12.7, 9.9;  slower by more than 10 % 13 of them (4096 x 1536 x 512
-// 14.7 against 11.6 for the best of all).
-constexpr int LDSX_COST_M = 640;
+// Workgroups of a tile that one CU holds, by registers and LDS (tests/test_kernel_resources.py has the built kernels' numbers)
+inline int ldsx_side_by_side(int mt, int nt) {
+  if (nt == 1) return mt == 2 ? 4 : 3;
+  return mt <= (nt == 2 ? 3 : 2) ? 4 : (mt <= (nt == 2 ? 5 : 4) ? 3 : 2);
+}
+// More rows than the kernels of constant K take, one group, results that are stored (encoders; the heads' hidden layers and decoder blocks of so many rows): the tile of the least
+// estimated time.  In us, per 1024 of K: a workgroup on its own `lat`, the busiest of 256 CUs with w workgroups `area` per tile of 16 x 64 (mt * nt) and `edge` per operand tile that it
+// fetches (mt + 4 nt); once: `fixed`, and `out` per 8 tiles of 16 x 64 that the CU stores.  Measured on 426 products of 660 .. 8192 rows, 384 .. 4096 columns, K 384 .. 4096, each with all
+// fifteen tiles (products, residual updates, queries with keys and values): 4 % slower than the best tile on average, 13 % at the ninth decile, where the largest useful area is 11 % and 30 %; on
+// 42 hidden layers of 660 .. 1024 rows, 8192 .. 40960 columns, K 512 and 1024: 2 % and 6 %, by area 3 % and 8 % (1024 x 8192 x 512 17.1 us, so 14.0; 660 x 16384 x 1024 30.5, 27.1; slowest
+// against it 960 x 8192 x 512 13.0, 13.9).  us, by area (beyond K = 3072: one round of 256-column tiles) and by this: 2560 x 1024 x 4096 47.1, 33.2;  4096 x 3072 x 1024 40.4, 31.6;  8192
+// x 1024 x 1024 32.8, 25.5;  3072 x 1536 x 512 12.7, 9.9.  By more than 10 % slower than the best 65 of the 468 (900 x 3072 x 1024 14.9, 10.9).  Fitted again to these the constants choose as well.
+// Shorter K, where a workgroup's first loads are most of its time, goes by area up to 5000 rows: of 178 products of K = 64 .. 256 slower than the best tile on average, by area and by cost: up to
+// 1100 rows 7 %, 15;  up to 5000 9, 16;  8192 rows 9, 8.  (K = 320 6, 5.)  Encodes, us: d = 64, 2048 rows 175, 184;  d = 128, 2048 167, 176;  d = 256, 4096 261, 271;  1536 206, 204;  d = 128,
+// 8192 258, 247.
+constexpr int LDSX_COST_M = 640, LDSX_COST_K = 320, LDSX_COST_SHORT_K_M = 5000;
 inline float ldsx_cost(int M, int N, int K, int mt, int nt) {
   struct C { float fixed, area, edge, lat, out; };
   constexpr C of[4] = {{3.65f, .20f, .15f, 1.46f, 1.05f}, {1.49f, .30f, .09f, 8.05f, 1.36f}, {3.31f, .34f, .12f, 3.81f, .75f}, {3.15f, .42f, .18f, 1.98f, .56f}};
   const C& c = of[nt == 4 ? (mt >= 4 ? 0 : 1) : (nt == 2 ? 2 : 3)];
   const long wgs = (long)((M + 16 * mt - 1) / (16 * mt)) * ((N + 64 * nt - 1) / (64 * nt)), w = (wgs + 255) / 256;
-  const int side_by_side = nt == 4 ? (mt >= 5 ? 2 : 3) : (nt == 2 && mt >= 4 ? (mt >= 7 ? 2 : 3) : 4);
+  const int side_by_side = ldsx_side_by_side(mt, nt);
   const float k = K / 1024.f, busy = w * (c.area * (mt * nt) + c.edge * (mt + 4 * nt)) * k, alone = (w + side_by_side - 1) / side_by_side * c.lat * k;
   return c.fixed + (busy > alone ? busy + .5f * alone : alone + .5f * busy) + c.out * w * (mt * nt) * .125f;
 }
@@ -375,7 +382,7 @@ inline int ldsx_rounds_cost(int mt, long wgs) {
 }
 // by_cost: not for the vocabulary projection, which stores nothing
 void pick_tile(int M, int N, int K, long zdim, int& mt, int& nt, int mt_max = 8, bool by_cost = true) {
-  if (by_cost && M > LDSX_COST_M && zdim == 1 && mt_max >= 8 && pick_tile_by_cost(M, N, K, mt, nt)) return;
+  if (by_cost && M > (K >= LDSX_COST_K ? LDSX_COST_M : LDSX_COST_SHORT_K_M) && zdim == 1 && mt_max >= 8 && pick_tile_by_cost(M, N, K, mt, nt)) return;
   pick_tile_by_area(M, N, K, zdim, mt, nt, mt_max);
   if (zdim > 2 && K >= 2048 && K % 256 == 0 && M > 16 && M <= LDSX_ROUNDS_M && mt_max >= 3) {
     const long wide = (N / 16 + 7) / 8;

@@ -229,19 +229,27 @@ int main() {
   }
   // the tile rule: every answer is a tile the library has, K is a multiple of the chunk depth, the cap on rows is kept
   long tiles = 0;
-  for (int M : {17, 20, 33, 48, 64, 80, 100, 128, 153, 252, 320, 512, 1000, 3200, 4096})
+  // (by_cost: products that store; more rows than LDSX_COST_M otherwise go by area, too)
+  for (int M : {17, 20, 33, 48, 64, 80, 100, 128, 153, 252, 320, 512, 640, 641, 660, 704, 1000, 3200, 4096, 5001, 8192})
     for (int N : {64, 256, 528, 1024, 3072, 4096, 32768, 40960})
       for (int K : {64, 128, 192, 256, 320, 512, 1024, 2048, 4096})
         for (long z : {1L, 2L, 4L, 10L, 16L})
-          for (int cap : {8, 3}) {
-            int mt = 0, nt = 0;
-            pick_tile(M, N, K, z, mt, nt, cap);
-            EXPECT(TILES.count({mt, nt}) == 1, "tile %d x %d for M=%d N=%d K=%d", mt, nt, M, N, K);
-            EXPECT(mt <= cap && K % (256 / nt) == 0, "tile %d x %d cap %d K %d", mt, nt, cap, K);
-            // the 256-column tiles of 64+ rows walk K two chunks of 64 at a time (no code for an odd last chunk)
-            EXPECT(!(nt == 4 && mt >= 4) || K % 128 == 0, "deep tile %d x %d with K = %d", mt, nt, K);
-            ++tiles;
-          }
+          for (int cap : {8, 3})
+            for (bool by_cost : {false, true}) {
+              int mt = 0, nt = 0;
+              pick_tile(M, N, K, z, mt, nt, cap, by_cost);
+              EXPECT(TILES.count({mt, nt}) == 1, "tile %d x %d for M=%d N=%d K=%d", mt, nt, M, N, K);
+              EXPECT(mt <= cap && K % (256 / nt) == 0, "tile %d x %d cap %d K %d", mt, nt, cap, K);
+              // the 256-column tiles of 64+ rows walk K two chunks of 64 at a time (no code for an odd last chunk)
+              EXPECT(!(nt == 4 && mt >= 4) || K % 128 == 0, "deep tile %d x %d with K = %d", mt, nt, K);
+              // the cost rule is asked where it says it is, and nowhere else
+              int am = 0, an = 0, cm = 0, cn = 0;
+              pick_tile(M, N, K, z, am, an, cap, false);
+              const bool asked = by_cost && M > (K >= 320 ? 640 : 5000) && z == 1 && cap >= 8;
+              if (asked && pick_tile_by_cost(M, N, K, cm, cn)) EXPECT(mt == cm && nt == cn, "tile %d x %d by cost %d x %d", mt, nt, cm, cn);
+              else EXPECT(mt == am && nt == an, "tile %d x %d by area %d x %d", mt, nt, am, an);
+              ++tiles;
+            }
   // many groups of many columns: tiles of 128 columns where one round of them fills the chip and the map deals whole groups to XCDs (groups, rows, N, tile)
   for (auto& w : {std::array<int, 5>{16, 60, 2048, 2, 2}, {16, 104, 2048, 4, 2}, {16, 144, 2048, 5, 2}, {10, 96, 2048, 2, 2}, {10, 128, 2048, 3, 2}, {12, 96, 1536, 2, 2},
                   {12, 96, 2048, 3, 1}, {13, 96, 1536, 3, 1}, {14, 96, 1536, 3, 1}}) {

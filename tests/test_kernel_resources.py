@@ -99,8 +99,18 @@ def tile_waves(tmp_path, tiles):
     return {(int(mt), int(nt), m == "1"): int(w) for mt, nt, m, w in found}
 
 
-def test_waves_of_wide_tiles(tmp_path):
-    """Tiles of 256 columns: three workgroups per CU up to 64 rows, four up to 32."""
-    waves = tile_waves(tmp_path, [(mt, 4) for mt in (1, 2, 3, 4, 5, 7, 8)])
-    for (mt, nt, _), w in waves.items():
-        assert w == (4 if mt <= 2 else (3 if mt <= 4 else 2)), f"{16 * mt} x 256: {w} waves per SIMD"
+def test_workgroups_side_by_side(tmp_path):
+    """The tile rule's count of workgroups per CU is what registers and LDS of the built kernels allow (four waves each); tiles of 256 columns: three up to 64 rows, four up to 32."""
+    tiles = [(mt, nt) for nt in (1, 2, 4) for mt in (1, 2, 3, 4, 5, 7, 8) if nt > 1 or mt <= 3]
+    src = tmp_path / "count.cpp"
+    src.write_text(f'#include <cstdio>\n#include "{os.path.dirname(build.SOURCES[0])}/bpd_host_logic.h"\nint main() {{ for (int nt : {{1, 2, 4}}) for (int mt = 1; mt <= 8; ++mt) printf("%d %d %d\\n", mt, nt, ldsx_side_by_side(mt, nt)); }}\n')
+    subprocess.run(["g++", "-std=c++17", str(src), "-o", str(tmp_path / "count")], check=True)
+    count = {(mt, nt): n for mt, nt, n in (map(int, line.split()) for line in subprocess.run([str(tmp_path / "count")], stdout=subprocess.PIPE, text=True).stdout.splitlines())}
+    waves = tile_waves(tmp_path, tiles)
+    for (mt, nt, argmax), w in waves.items():
+        deep = nt == 4 and mt >= 4
+        lds = (3 if deep else 2) * ((16 * mt * (256 // nt // 8) + 255) // 256) * 4096
+        if not argmax:
+            assert count[mt, nt] == min(4, w, 160 * 1024 // lds), f"{16 * mt} x {64 * nt}: {w} waves per SIMD, {lds} bytes of LDS"
+        if nt == 4:
+            assert w == (4 if mt <= 2 else (3 if mt <= 4 else 2)), f"{16 * mt} x 256: {w} waves per SIMD"
