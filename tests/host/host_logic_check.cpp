@@ -46,6 +46,13 @@ static void check_config(const bpd_config& c) {
   const size_t sliced = std::min(B * S, (size_t)LEAN_PART_M);
   if (c.d_ff > LEAN_K_WHOLE && lean_encoder_ok(c, (long)sliced)) EXPECT((size_t)((char*)L.xn - (char*)L.kpart) >= F / 1024 * sliced * d * 4, "the encoder's K slices, %zu rows, d=%zu F=%zu k=%zu B=%zu", sliced, d, F, k, B);
   EXPECT((size_t)((char*)L.keys_h1 - (char*)L.keys) >= M * k * 8, "keys");
+  // activations that kernels write and read by whole row tiles (packed_at())
+  const size_t as = act_size(c), Mt = (M + 15) / 16 * 16, Met = (B * S + 15) / 16 * 16;
+  auto room = [&](const void* p) { for (auto& r : log) if (r.first == (size_t)p) return r.second; return (size_t)0; };      // (the layout starts at null)
+  for (const void* p : {L.xn, L.attn}) EXPECT(room(p) >= Mt * d * as, "normalised rows, attention: %zu of %zu rows", room(p), Mt);
+  EXPECT(room(L.ffh) >= Mt * F * as, "hidden layer: %zu of %zu rows", room(L.ffh), Mt);
+  for (const void* p : {L.xen, L.attne, L.mem}) EXPECT(room(p) >= Met * d * as, "the encoder's rows: %zu of %zu rows", room(p), Met);
+  EXPECT(room(L.ffhe) >= Met * F * as, "the encoder's hidden layer: %zu of %zu rows", room(L.ffhe), Met);
   EXPECT((size_t)((char*)L.hn2 - (char*)L.keys_h1) >= 2 * M * 8, "head-1 and second-phase keys");
   EXPECT(L.n_zeros >= std::max({k * F, V, 3 * d}), "zero vector");
   // folded copies of the decoder's matrices: there whenever a block of the context needs them, and only then
