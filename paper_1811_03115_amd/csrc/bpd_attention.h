@@ -752,7 +752,7 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_tiles_kernel(AttnP p, i
     float inv = __builtin_amdgcn_rcpf(sum);
     inv = inv * fmaf(-sum, inv, 2.f);            // (one Newton step: the quotient to fp32)
     if (tile * RT + lr < rows) {
-      bf16_t* to = (bf16_t*)p.out + attn_out_at(p, row0 + tile * RT + lr, h * DH + 4 * lq);
+      bf16_t* to = (bf16_t*)p.out + attn_out_at<bf16_t>(p, row0 + tile * RT + lr, h * DH + 4 * lq);
       const int on = p.packed ? 256 : 16;        // 16 dimensions on
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt) *(u32x2*)(to + dt * on) = u32x2{cvt_pk_bf16(acc[dt][0] * inv, acc[dt][1] * inv), cvt_pk_bf16(acc[dt][2] * inv, acc[dt][3] * inv)};

@@ -726,7 +726,7 @@ template <int DH> struct RowLoader<bf16_t, DH> {
 // as operands out of rows in memory, a load of 1 KB touches 64 lines, which the L1 looks up one by one: 64 cycles instead of 16: the queries, keys
 // and values of 320 x 1024 10.6 us, packed 8.3, their first FFN layer 12.8, 9.8, an output projection 6.8, 5.9;  170 rows 8.9, 7.3;  8.5, 6.4;  5.3, 5.1.)
 __device__ __forceinline__ size_t packed_at(long m, int c, int K) {
-  return ((size_t)(m >> 4) * (K >> 5) + (c >> 5)) * 512 + ((c >> 3) & 3) * 128 + (int)(m & 15) * 8 + (c & 7);
+  return (size_t)(m & ~15l) * K + (c >> 5) * 512 + ((c >> 3) & 3) * 128 + (int)(m & 15) * 8 + (c & 7);
 }
 struct AttnP {
   // (what the first loads need comes first: one scalar load)
@@ -749,7 +749,16 @@ struct AttnP {
   const int* row0;        // attention_mfma_packed_kernel: first row of each sequence in Q and out
   int packed;             // out: as packed_at(), otherwise rows
 };
-__device__ __forceinline__ size_t attn_out_at(const AttnP& p, long m, int c) { return p.packed ? packed_at(m, c, p.d) : (size_t)m * p.d + c; }
+// element (m, c) of out: that of column 0, and the rest (fp32 models have rows)
+__device__ __forceinline__ size_t attn_out_row(const AttnP& p, long m) {
+  const int in = p.packed ? 15 : 0;              // rows side by side
+  return (size_t)(m & ~(long)in) * p.d + ((int)m & in) * 8;
+}
+template <typename ACT>
+__device__ __forceinline__ size_t attn_out_at(const AttnP& p, long m, int c) {
+  if constexpr (sizeof(ACT) == 4) return (size_t)m * p.d + c;
+  return attn_out_row(p, m) + (p.packed ? (c >> 5) * 512 + ((c >> 3) & 3) * 128 + (c & 7) : c);
+}
 
 // first key that the row at position t may see
 __device__ __forceinline__ int attn_first_key(const AttnP& p, int t) {
@@ -906,7 +915,7 @@ __global__ __launch_bounds__(256) void attention_kernel(AttnP p) {
       const int i = idx / DH, cc = idx % DH;
       float s = 0.f;
       for (int gg = 0; gg < G; ++gg) s += red[(gg * RT + i) * DH + cc];
-      ((ACT*)p.out)[attn_out_at(p, (long)b * p.R + r0 + i, h * DH + cc)] = from_f<ACT>(s / l_s[i]);
+      ((ACT*)p.out)[attn_out_at<ACT>(p, (long)b * p.R + r0 + i, h * DH + cc)] = from_f<ACT>(s / l_s[i]);
     }
   } else {
     const int tiles = gridDim.z / p.nsplit;
@@ -958,7 +967,7 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(AttnP p) {
     num.x = fmaf(a[s].x, w, num.x); num.y = fmaf(a[s].y, w, num.y); num.z = fmaf(a[s].z, w, num.z); num.w = fmaf(a[s].w, w, num.w);
     den = fmaf(l[s], w, den);
   }
-  ACT* o = (ACT*)p.out + attn_out_at(p, (long)b * p.R + r0 + i, h * DH + 4 * c4);
+  ACT* o = (ACT*)p.out + attn_out_at<ACT>(p, (long)b * p.R + r0 + i, h * DH + 4 * c4);
   if constexpr (sizeof(ACT) == 2) {
     *(uint2*)o = make_uint2(cvt_pk_bf16(num.x / den, num.y / den),
                             cvt_pk_bf16(num.z / den, num.w / den));

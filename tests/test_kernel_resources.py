@@ -80,23 +80,35 @@ def test_no_step_kernel_uses_scratch(tmp_path):
         assert all(by_name[n] == 0 for n in hits), f"{req} uses scratch"
 
 
-def tile_waves(tmp_path, tiles):
-    """Waves per SIMD that the registers of gemm_ldsx_kernel<MT, NT, KC>, plain and with arg-max, leave room for."""
+def waves_of(tmp_path, instantiations):
+    """[(mangled name, waves per SIMD that the registers leave room for)] of explicit instantiations of kernels."""
     hipcc = build.hipcc()
     if shutil.which(hipcc) is None and not os.path.exists(hipcc):
         pytest.skip("hipcc not found")
-    src = tmp_path / "tiles.hip"
-    csrc = os.path.dirname(build.SOURCES[0])
-    src.write_text(f'#include "{csrc}/bpd_kernels.h"\n' + "".join(
-        f"template __global__ void gemm_ldsx_kernel<{mt}, {nt}, {256 // nt}, {m}, false, false, false>(GemmP, Epi, unsigned long long*, float*, LnP, LiveP);\n"
-        for mt, nt in tiles for m in ("false", "true")))
+    src = tmp_path / "kernels.hip"
+    src.write_text(f'#include "{os.path.dirname(build.SOURCES[0])}/bpd_kernels.h"\n' + "".join(f"template __global__ void {i};\n" for i in instantiations))
     flags = [f for f in build.FLAGS if f not in ("-shared", "-fPIC")]
-    res = subprocess.run([hipcc] + flags + ["--cuda-device-only", "-c", str(src), "-o", str(tmp_path / "tiles.o"), "-Rpass-analysis=kernel-resource-usage"],
+    res = subprocess.run([hipcc] + flags + ["--cuda-device-only", "-c", str(src), "-o", str(tmp_path / "kernels.o"), "-Rpass-analysis=kernel-resource-usage"],
                          stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert res.returncode == 0, res.stdout[-2000:]
-    found = re.findall(r"Function Name: _Z\d+gemm_ldsx_kernelILi(\d)ELi(\d)ELi\d+ELb([01])E.*?Occupancy \[waves/SIMD\]: (\d)", res.stdout, re.S)
+    return [(n, int(w)) for n, w in re.findall(r"Function Name: (\S+).*?Occupancy \[waves/SIMD\]: (\d+)", res.stdout, re.S)]
+
+
+def tile_waves(tmp_path, tiles):
+    """Those of gemm_ldsx_kernel<MT, NT, KC>, plain and with arg-max."""
+    got = waves_of(tmp_path, [f"gemm_ldsx_kernel<{mt}, {nt}, {256 // nt}, {m}, false, false, false>(GemmP, Epi, unsigned long long*, float*, LnP, LiveP)"
+                              for mt, nt in tiles for m in ("false", "true")])
+    found = [(re.match(r"_Z\d+gemm_ldsx_kernelILi(\d)ELi(\d)ELi\d+ELb([01])E", n), w) for n, w in got]
+    found = {(int(m[1]), int(m[2]), m[3] == "1"): w for m, w in found if m}
     assert len(found) == 2 * len(tiles)
-    return {(int(mt), int(nt), m == "1"): int(w) for mt, nt, m, w in found}
+    return found
+
+
+def test_combine_waves(tmp_path):
+    """Sixteen partial results per thread: 64 registers of values, and not as many again for where they go."""
+    got = waves_of(tmp_path, [f"attention_combine_kernel<{act}, {dh}, 16>(AttnP)" for act, dh in (("bf16_t", 64), ("bf16_t", 16), ("float", 16))])
+    got = [w for n, w in got if "attention_combine_kernel" in n]
+    assert len(got) == 3 and min(got) >= 5, got
 
 
 def test_workgroups_side_by_side(tmp_path):
