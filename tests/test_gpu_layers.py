@@ -67,6 +67,14 @@ def test_two_sequences_per_workgroup(k, B, S, d, ended):
     lockstep(config(k, B, S, 4 * k + 1, layers=1, d=d), 4 if ended else 2, budgets)
 
 
+# ... in blocks of other kernels: LayerNorm folded into the weights of what follows (more than 640 rows, or a depth without kernels of constant K), or its statistics left behind by what goes
+# before (up to 128 rows)
+@pytest.mark.parametrize("k,B,S,d,F,ended", [(11, 60, 40, 512, 2048, False), (16, 41, 128, 512, 2048, True), (12, 63, 7, 512, 1024, True), (10, 20, 33, 1024, 1280, True), (4, 11, 64, 1024, 1280, False)])
+def test_two_sequences_per_workgroup_of_other_blocks(k, B, S, d, F, ended):
+    budgets = np.array([1 + (7 * (b // 2) + 3 * (b % 3)) % (4 * k) for b in range(B)], np.int32) if ended else None
+    lockstep(dataclasses.replace(config(k, B, S, 4 * k + 1, layers=2, d=d), d_ff=F), 4 if ended else 2, budgets)
+
+
 # Their queries have the bits of the separate kernels up to the rows whose LayerNorm those take inside the query projection (d = 512: 256, 1024: 32; sums in the same order): room for
 # sources of 160 tokens takes the separate kernels, and states and scores are the same
 @pytest.mark.parametrize("k,B,S,d,F", [(1, 17, 33, 512, 2048), (8, 20, 40, 512, 2048), (4, 64, 100, 512, 1024), (1, 32, 128, 1024, 4096), (2, 16, 64, 1024, 1024), (3, 10, 9, 1024, 2048)])

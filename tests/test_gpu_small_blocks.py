@@ -37,7 +37,7 @@ def test_encoder_rows(d, F, B, S):
 # encoders of more rows, whose large tiles finish whole 32 or 64 columns of a wave: lengths that are and are not multiples of 8 keys, rows past the last whole tile, columns past it
 # (d = 320, 576), ragged batches
 @pytest.mark.parametrize("d,F,B,S,ragged", [(512, 2048, 8, 96, False), (512, 1024, 7, 101, False), (1024, 4096, 9, 120, False), (384, 1536, 13, 56, False), (320, 1280, 9, 88, False),
-                                            (576, 576, 11, 72, False), (1024, 2048, 20, 104, False), (1024, 1024, 40, 128, True), (512, 2048, 64, 128, True)])
+                                            (576, 576, 11, 72, False), (1024, 2048, 20, 104, False), (1024, 1024, 40, 128, True), (512, 2048, 64, 128, True), (768, 1536, 48, 100, True), (1024, 2048, 64, 72, True), (640, 1280, 50, 128, True), (384, 768, 64, 128, True)])
 def test_encoder_large_tiles(d, F, B, S, ragged):
     cfg = wl.Config("rows", 75, 2, 1, d, d // 64, F, 272, 2, B, S, 8, "bf16", 2, src_len_kind="lognormal" if ragged else "fixed")
     lockstep(cfg, 1)
