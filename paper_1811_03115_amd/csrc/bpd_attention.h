@@ -536,7 +536,7 @@ __global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_pairs_kernel(A
   const int kg = wave % QU, t0 = wave / QU * TW, ks0 = kg * U, rows = __builtin_amdgcn_readfirstlane(there * p.R);
   // every load of the kernel but keys and values: rows of x first (those past the last: zeros).  A lane has k-steps of eight columns of a part, as the operands are
   const int part = (lane >> 2) % QU, pq = lane & 3, row0 = wave * RW + (lane >> 2) / QU, at = part * 128 + pq * 8;
-  f32x4 v[PASSES][U][2], g[U][2], be[U][2];
+  f32x4 v[PASSES][U][2], gb[U][2];               // (gain in the lower half of the lanes, bias in the upper one)
   const rsrc_t xr = rsrc_of(qp.x + (size_t)b0 * p.R * K, (unsigned)rows * K * 4);
 #pragma unroll
   for (int n = 0; n < PASSES; ++n) {
@@ -549,7 +549,7 @@ __global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_pairs_kernel(A
 #pragma unroll
   for (int i = 0; i < U; ++i)
 #pragma unroll
-    for (int hh = 0; hh < 2; ++hh) { g[i][hh] = *(const f32x4*)(qp.g + at + i * 32 + hh * 4); be[i][hh] = *(const f32x4*)(qp.b + at + i * 32 + hh * 4); }
+    for (int hh = 0; hh < 2; ++hh) gb[i][hh] = *(const f32x4*)((lane < 32 ? qp.g : qp.b) + at + i * 32 + hh * 4);
   int lim = p.limit[bc];
   u32x4 wf[4][U];
 #pragma unroll
@@ -597,7 +597,10 @@ __global__ __launch_bounds__(64 * ATTN_WAVES) void attention_mfma_pairs_kernel(A
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) y[4 * hh + r] = fmaf(fmaf(v[n][i][hh][r], rs, off), g[i][hh][r], be[i][hh][r]);
+        for (int r = 0; r < 4; ++r) {
+          const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(gb[i][hh][r]), __float_as_uint(gb[i][hh][r]), false, false);
+          y[4 * hh + r] = fmaf(fmaf(v[n][i][hh][r], rs, off), __uint_as_float(w[0]), __uint_as_float(w[1]));
+        }
       *(u32x4*)(xs + (row0 + NW * RW * n) * (K + 8) + part * 128 + (i ^ (part & 3)) * 32 + pq * 8) =
           u32x4{cvt_pk_bf16(y[0], y[1]), cvt_pk_bf16(y[2], y[3]), cvt_pk_bf16(y[4], y[5]), cvt_pk_bf16(y[6], y[7])};
     }
