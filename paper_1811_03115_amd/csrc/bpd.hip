@@ -604,8 +604,10 @@ long attention_keys(const bpd_ctx* ctx, int cap, int R, int causal) {
 // caller checks), at most 16 rows per sequence, 64-wide heads, d = 128 / 256 / 512 / 1024, one workgroup per (head,
 // sequence) and few enough of them that each streaming its head's 128 d bytes of weights beats one GEMM doing it once.
 constexpr int ATTN_QPROJ_MAX_WGS = 128;       // (512 workgroups, batch 32 of Transformer-big: the step took 26 us longer than with the separate GEMM)
-// More of them, up to a workgroup per CU, go two sequences to a workgroup (d = 512, 1024; sources of at most 128 keys, a group of 32 for each wave).  LayerNorm, GEMM and attention of a
-// layer at 32 x 10 rows, us: 17.2 as three kernels, 8.9;  32 x 1 rows 11.3 as two, 8.0.
+// More of them, up to a workgroup per CU, go two sequences to a workgroup (d = 512, 1024, whose parts of 128 columns divide among eight waves; room for at most 128 source tokens, a group of
+// 32 keys for each wave).  Steps of four layers, us, as separate kernels and so, by sequences x rows:  d = 1024, d_ff 4096, 32 x 10 403, 380;  d_ff 1280 (statistics, folded weights) 10 x 4 210, 196;
+// 20 x 10 302, 292;  d = 512, d_ff 2048, 40 x 4 172, 159;  64 x 8 264, 248;  folded weights 60 x 12 318, 312;  64 x 16 395, 390.  More workgroups than CUs gain nothing: d = 1024, 40 x 5 304, 308;
+// 48 x 10 542, 544;  48 x 1 201, 213;  64 x 5 372, 367.  The kernel alone by trace 9.9 at 32 x 10 rows, 8.9 at 32 x 1.
 constexpr int ATTN_QPROJ_MAX_PAIRS = 256;
 bool attention_qproj_pairs(const bpd_ctx* ctx, int B) {
   const bpd_config& c = ctx->cfg;

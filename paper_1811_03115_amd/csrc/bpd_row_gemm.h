@@ -213,6 +213,9 @@ __global__ __launch_bounds__(WAVES * 64) void row_gemm_kernel(RowGemmP p) {
 // GEMM, in this order of slices, and is stored.  One load of everything, one barrier (each wave takes the squares about the mean of its
 // own columns, row_moments puts the waves together; against sums of squares about zero this costs 0.5 % of a sentence's decode): 1.9 us in a chain of kernels where one
 // wave per row took 4.2 us (D = 512, 80 rows) .. 5.2 us (D = 1024, 8 slices).
+// packed: ya as packed_at(), in pieces of 8 bytes.  Means of rows and packed by turns on two cards, us: 80 .. 320 rows of 1024 with four slices 4.03, 3.95 and 3.76, 4.27;  up to 256 rows without 3.11, 2.99 and
+// 3.35, 2.89;  96 of 512 with four 3.70, 3.61 and 3.31, 3.18.  A tile's rows on one XCD against rows in order: big-batch32 15.72 ms, 15.77, two-phase 14.27, 14.32, base-batch13-top2 2.020, 2.031; eight
+// or four rows on one XCD as sixteen.  A wave per row and four or eight rows per workgroup, which leave through LDS in pieces of 16 bytes: big-batch32 15.79 and 16.00 ms for 15.69.
 constexpr int ln_row_threads(int D) { return D < 256 ? 64 : D / 4; }
 template <int D, int NSL>
 __global__ __launch_bounds__(ln_row_threads(D)) void ln_row_kernel(float* x, const float* g, const float* b, int M, float eps, bf16_t* ya, float* yf,
